@@ -63,16 +63,14 @@ bool nhwc_bwd_filter_dot2_supported(const Geom &g, int V);
 hipError_t nhwc_bwd_filter_dot2(const Geom &g, int V, const void *x, const void *dy, float *ws, int CT, int nctiles,
                                 int nowtiles, int TH, int nstrips, int NI, unsigned nblocks, hipStream_t st);
 
-// ---- NCHW LDS-tile kernels (nchw.hip) ----------------------------------------------------------
-// TR = rows per unit.  K in {3,5}, stride in {1,2}, any pad, any multiplier for forward and the
-// filter gradient; flip = true gives backward-data for stride 1, "same" padding, multiplier 1.
-bool nchw_fwd_supported(const Geom &g, int TR);
-hipError_t nchw_fwd(const Geom &g, int dtype, const void *x, const void *w, void *y, bool flip, int TR, hipStream_t st);
-bool nchw_bwd_data_k3s2_supported(const Geom &g, int TR);
-hipError_t nchw_bwd_data_k3s2(const Geom &g, int dtype, const void *dy, const void *w, void *dx, int TR, hipStream_t st);
-int nchw_bwd_filter_parts(const Geom &g, int TR, int NI);   // 0 = unsupported
-hipError_t nchw_bwd_filter(const Geom &g, int dtype, const void *x, const void *dy, float *ws, int TR, int NI,
-                           hipStream_t st);
+// ---- NCHW kernels for rows of any width (nchw_flat.hip): K 3, 5 or 7, stride 1 or 2, any padding -----
+// Any multiplier; the input gradient multiplier 1 or 2.
+bool nchwf_fwd_supported(const Geom &g, int dtype);
+hipError_t nchwf_fwd(const Geom &g, int dtype, const void *x, const void *w, void *y, hipStream_t st);
+bool nchwf_bwd_data_supported(const Geom &g, int dtype);
+hipError_t nchwf_bwd_data(const Geom &g, int dtype, const void *dy, const void *w, void *dx, hipStream_t st);
+int nchwf_bwd_filter_parts(const Geom &g, int dtype);       // 0 = unsupported
+hipError_t nchwf_bwd_filter(const Geom &g, int dtype, const void *x, const void *dy, float *ws, int parts, hipStream_t st);
 
 // ---- NCHW row-walk kernels for rows that are whole 16-byte vectors (nchw_direct.hip) -----------
 // pass: 0 fwd, 1 bwd_data, 2 bwd_filter.  Returns the columns per lane, 0 if not applicable.

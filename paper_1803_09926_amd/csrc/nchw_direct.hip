@@ -1292,7 +1292,7 @@ int nchwd_vec(const Geom &g, int dtype, int pass)
     if (pass == 1 && g.m != 1) return 0;
     if (pass == 2 && g.K != 3 && !(g.K == 5 && s1)) return 0;
     if (pass == 2 && g.O > 65535) return 0;      // the filter-gradient launches put the channel on gridDim.y
-    if (g.H < 16) return 0;                      // small planes go to the LDS-tile kernels
+    if (g.H < 16) return 0;                      // small planes: nchw_small.hip, nchw_flat.hip
     const int wv = s1 ? g.W : g.Wo;              // the dimension that lanes split into vectors
     if (s2 && pass == 1) {                       // dy columns per lane; dx is stored 2V wide
         if (dtype == DT_F32) return wv % 2 == 0 ? 2 : 0;

@@ -1,0 +1,626 @@
+// NCHW kernels for rows of any width: 3x3, 5x5 and 7x7 filters, stride 1 and 2, any padding, any multiplier (the input
+// gradient: 1 and 2).
+//
+// Rows of 19, 37 or 74 elements are no whole number of 16-byte vectors, but a run of rows of a plane is one flat range of
+// memory, and so is a run of whole planes.  A block takes U planes and a band of TR output rows of each: the input rows go to
+// LDS as flat ranges in memory order (16 bytes per lane straight into LDS, `dma_range`: no register, no wait before
+// the block's barrier), a lane owns one output column of one plane and walks down the band, and the outputs leave through a
+// second LDS area as flat 16-byte streaming stores.  Every lane of the block is in the same row at the same time, so what
+// depends on the row (padding above and below, the first and last steps of the walk) is scalar; padding to the left and
+// right is one select per value read.  A step reads K values of one input row (consecutive lanes consecutive words: no bank
+// conflict) for K*K multiply-adds.  Every block is short; several blocks per compute unit overlap one's loads with
+// another's arithmetic.
+#include "kernels.hpp"
+#include <type_traits>
+
+namespace dwc {
+
+namespace {
+
+template <typename T> constexpr int ve_of() { return 16 / (int)sizeof(T); }
+
+// Bands of planes staged in LDS.  Whole planes (`whole`) are one range; otherwise every plane's band is a segment of its own,
+// `pitch` elements apart in LDS.  A range starts in LDS at the 16-byte boundary below its first element.
+struct Bands {
+    int plane0, nplanes;   // planes in the tile
+    int HW, W;             // plane size, row width
+    int r0, r1;            // rows of the band (inside the plane)
+    int pitch;             // LDS elements between segments (0: whole planes, one range)
+    __device__ __forceinline__ int first(int j) const { return (plane0 + j) * HW + r0 * W; }       // element index of segment j
+    // LDS element of row r0, column 0 of plane j
+    template <typename T> __device__ __forceinline__ int at(int j) const
+    {
+        return pitch ? j * pitch + (first(j) & (ve_of<T>() - 1)) : (first(0) & (ve_of<T>() - 1)) + j * HW;
+    }
+};
+
+typedef __attribute__((address_space(1))) const void *gptr_t;
+typedef __attribute__((address_space(3))) void *lptr_t;
+
+// Copies the bands to `lds` (16-byte aligned).  The caller waits (dma_wait) and synchronises before reading.
+template <typename T>
+__device__ __forceinline__ void dma_bands(const T *__restrict__ src, int total, const Bands &b, T *lds)
+{
+    constexpr int VE = ve_of<T>();
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const int nseg = b.pitch ? b.nplanes : 1, len = b.pitch ? (b.r1 - b.r0) * b.W : b.nplanes * b.HW;
+    const int nc = (len + VE - 1 + VE - 1) / VE / 64 + 1;          // 64-vector chunks of a segment, at most
+    for (int i = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); i < nseg * nc; i += nw) {
+        const int s = i / nc, ch = i - s * nc;
+        const int e0 = b.first(s), a0 = e0 & ~(VE - 1), nvec = (e0 + len - a0 + VE - 1) / VE;
+        const int idx = ch * 64 + lane, a = a0 + idx * VE;
+        T *base = lds + s * b.pitch + ch * 64 * VE;
+        if (idx < nvec) {
+            if (a + VE <= total)
+                __builtin_amdgcn_global_load_lds((gptr_t)(src + a), (lptr_t)base, 16, 0, 0);
+            else {                                                   // the last vector of a tensor that is no whole number of vectors
+                for (int j = 0; j < VE; ++j)
+                    if (a + j < total) base[lane * VE + j] = src[a + j];
+            }
+        }
+    }
+}
+__device__ __forceinline__ void dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// The bands from LDS to memory; the first and the last vector of a range may be partial.
+template <typename T>
+__device__ __forceinline__ void store_bands(T *__restrict__ dst, const Bands &b, const T *lds, bool stream)
+{
+    constexpr int VE = ve_of<T>();
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const int nseg = b.pitch ? b.nplanes : 1, len = b.pitch ? (b.r1 - b.r0) * b.W : b.nplanes * b.HW;
+    const int nc = (len + VE - 1 + VE - 1) / VE / 64 + 1;
+    for (int i = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); i < nseg * nc; i += nw) {
+        const int s = i / nc, ch = i - s * nc;
+        const int e0 = b.first(s), e1 = e0 + len, a0 = e0 & ~(VE - 1);
+        const int idx = ch * 64 + lane, a = a0 + idx * VE;
+        const T *p = lds + s * b.pitch + idx * VE;
+        if (a >= e0 && a + VE <= e1) {
+            const u4v_t v = *reinterpret_cast<const u4v_t *>(p);
+            if (stream) __builtin_nontemporal_store(v, reinterpret_cast<u4v_t *>(dst + a));
+            else *reinterpret_cast<u4v_t *>(dst + a) = v;
+        } else if (a < e1) {
+            for (int j = 0; j < VE; ++j)
+                if (a + j >= e0 && a + j < e1) dst[a + j] = p[j];
+        }
+    }
+}
+
+// What a launch of these kernels is cut into.
+struct FlatTile {
+    int U, TR, nbands;     // planes per block, output rows per band (bwd_data_s2: row pairs), bands per plane
+    int pin, pout;         // LDS pitches (0: whole planes)
+    int nin;               // LDS elements of the input area
+    int threads;
+};
+
+// A value read beside the row (padding) is cleared by its lane's mask: a select would let the compiler branch around the read.
+__device__ __forceinline__ float masked(float f, uint32_t m) { return __uint_as_float(__float_as_uint(f) & m); }
+
+constexpr int GUARD = 8;   // LDS elements in front of and behind the input area that an edge lane may read (and drop)
+
+}  // namespace
+
+// ---------------------------------------------------------------------------------------------
+// out[plane][oh][ow] = sum over q < M, kh, kw of w[kh][kw] * in[plane * M / mdiv + q][oh*S - pad + kh][ow*S - pad + kw].
+// Forward: M = 1, mdiv = the multiplier.  Input gradient of a stride-1 layer (flip): in = dy, filters rotated by 180
+// degrees, pad = K - 1 - p, M = the multiplier.
+// ---------------------------------------------------------------------------------------------
+template <typename T, int K, int S, int M, bool SAME>
+__global__ __launch_bounds__(512) void k_nchwf_conv(const T *__restrict__ in, const T *__restrict__ w, T *__restrict__ out,
+                                                    int nplanes, int OC, int Hi, int Wi, int Ho, int Wo, int pad, int mdiv,
+                                                    int total_in, int flip, FlatTile ft, unsigned nblocks, int nt)
+{
+    extern __shared__ uint4 smem[];
+    constexpr int NA = (K + S - 1) / S;
+    const unsigned lb = xcd_remap(blockIdx.x, nblocks);
+    const int band = (int)(lb % (unsigned)ft.nbands), p0 = (int)(lb / (unsigned)ft.nbands) * ft.U;
+    const int np = min(ft.U, nplanes - p0);
+    const int oh0 = band * ft.TR, oh1 = min(Ho, oh0 + ft.TR);
+    const int ip0 = M > 1 ? p0 * M : p0 / mdiv, ip1 = M > 1 ? (p0 + np) * M : (p0 + np - 1) / mdiv + 1;
+    const int r0 = min(max(oh0 * S - pad, 0), Hi), r1 = max(min((oh1 - 1) * S - pad + K, Hi), r0);
+    const Bands bi = {ip0, ip1 - ip0, Hi * Wi, Wi, r0, r1, ft.pin};
+    const Bands bo = {p0, np, Ho * Wo, Wo, oh0, oh1, ft.pout};
+    T *lin = reinterpret_cast<T *>(smem) + GUARD, *lout = lin + ft.nin + GUARD;
+    dma_bands<T>(in, total_in, bi, lin);
+
+    const int u = (int)threadIdx.x / Wo, ow = (int)threadIdx.x - u * Wo;
+    const bool active = u < np;
+    const int pl = p0 + (active ? u : 0), oc = pl % OC;
+    uint32_t ok[K];
+#pragma unroll
+    for (int kw = 0; kw < K; ++kw) ok[kw] = (unsigned)(ow * S - pad + kw) < (unsigned)Wi ? ~0u : 0u;
+    const int col0 = min(max(ow * S - pad, -K), Wi);       // a column further out has every tap dropped anyway
+    float wr[M][K][K];
+    int src[M];                                            // LDS element of (plane, row r0, column col0)
+#pragma unroll
+    for (int q = 0; q < M; ++q) {
+#pragma unroll
+        for (int kh = 0; kh < K; ++kh)
+#pragma unroll
+            for (int kw = 0; kw < K; ++kw) {
+                const int tap = kh * K + kw;
+                wr[q][kh][kw] = ldf(w + (oc * M + q) * K * K + (flip ? K * K - 1 - tap : tap));
+            }
+        src[q] = bi.at<T>((M > 1 ? pl * M + q : pl / mdiv) - ip0) + col0;
+    }
+    // a lane without a column writes its sums to the guard elements in front of the output area: no lane mask in the walk
+    int dst = active ? bo.at<T>(u) + ow : -1;
+    const int dstep = active ? Wo : 0;
+    float acc[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) acc[i] = 0.f;
+    dma_wait();
+    __syncthreads();
+
+    // Step t reads the S input rows from row (oh0 + t)*S - pad on; they meet the outputs of rows oh0 + t - i, and the one with
+    // i = NA - 1 is complete.  Steps [ta, tb) have all their rows in the band and check nothing.
+    // At the ends of the walk only the outputs of the band are added to.
+    const int base = oh0 * S - pad - r0, nrows = r1 - r0, TRb = oh1 - oh0;
+    auto step = [&](int t, auto checked) {
+        constexpr bool CK = decltype(checked)::value;
+#pragma unroll
+        for (int j = 0; j < S; ++j) {
+            const int row = base + t * S + j;              // everything about the row is uniform
+            if (CK && (row < 0 || row >= nrows)) continue; // padding
+#pragma unroll
+            for (int q = 0; q < M; ++q) {
+                const T *p = lin + src[q] + row * Wi;
+                float v[K];
+#pragma unroll
+                for (int kw = 0; kw < K; ++kw) {
+                    const float f = ldf(p + kw);
+                    v[kw] = SAME && kw == K / 2 ? f : masked(f, ok[kw]);      // the centre tap is never outside
+                }
+#pragma unroll
+                for (int i = 0; i < NA; ++i) {
+                    if (j + i * S >= K || (CK && K > 3 && (unsigned)(t - i) >= (unsigned)TRb)) continue;
+#pragma unroll
+                    for (int kw = 0; kw < K; ++kw) acc[i] = fmaf(wr[q][j + i * S][kw], v[kw], acc[i]);
+                }
+            }
+        }
+        if (!CK || t >= NA - 1) { stf(lout + dst, acc[NA - 1]); dst += dstep; }
+#pragma unroll
+        for (int i = NA - 1; i > 0; --i) acc[i] = acc[i - 1];
+        acc[0] = 0.f;
+    };
+    const int steps = TRb + NA - 1;
+    const int ta = (S - 1 - base) / S, tb = min((nrows - base) / S, K > 3 ? TRb : steps);
+    int t = 0;
+    for (; t < min(max(ta, NA - 1), steps); ++t) step(t, std::true_type());
+#pragma unroll NA
+    for (; t < tb; ++t) step(t, std::false_type());
+    for (; t < steps; ++t) step(t, std::true_type());
+    __syncthreads();
+    store_bands<T>(out, bo, lout, nt != 0);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Input gradient of a stride-2 layer.  With h + p = 2a + f and c + p = 2b + e the taps that reach dx[h][c] are kh = 2k + f,
+// kw = 2l + e against dy[a - k][b - l]: a lane owns the dx columns of one b, walks down the dy rows with the K/2 row
+// pairs a row reaches in rotating accumulators, and a dy row costs (K+1)/2 reads and K*K multiply-adds for four outputs.
+// ---------------------------------------------------------------------------------------------
+template <typename T, int K, int M>
+__global__ __launch_bounds__(512) void k_nchwf_bwd_data_s2(const T *__restrict__ dy, const T *__restrict__ w, T *__restrict__ dx,
+                                                           int nplanes, int C, int H, int W, int Ho, int Wo, int pad, int NB,
+                                                           int total_dy, FlatTile ft, unsigned nblocks, int nt)
+{
+    extern __shared__ uint4 smem[];
+    constexpr int NA = (K + 1) / 2;
+    const unsigned lb = xcd_remap(blockIdx.x, nblocks);
+    const int band = (int)(lb % (unsigned)ft.nbands), p0 = (int)(lb / (unsigned)ft.nbands) * ft.U;
+    const int np = min(ft.U, nplanes - p0);
+    const int a0 = pad / 2 + band * ft.TR, a1 = min((H - 1 + pad) / 2 + 1, a0 + ft.TR);      // row pairs of the band
+    const int r0 = min(max(a0 - (NA - 1), 0), Ho), r1 = max(min(a1, Ho), r0);
+    const int h0 = max(2 * a0 - pad, 0), h1 = min(2 * a1 - pad, H);
+    const Bands bi = {p0 * M, np * M, Ho * Wo, Wo, r0, r1, ft.pin};
+    const Bands bo = {p0, np, H * W, W, h0, h1, ft.pout};
+    T *lin = reinterpret_cast<T *>(smem) + GUARD, *lout = lin + ft.nin + GUARD;
+    dma_bands<T>(dy, total_dy, bi, lin);
+
+    const int u = (int)threadIdx.x / NB, b = pad / 2 + (int)threadIdx.x - u * NB;
+    const bool active = u < np;
+    const int pl = p0 + (active ? u : 0), c = pl % C;
+    uint32_t ok[NA];
+#pragma unroll
+    for (int l = 0; l < NA; ++l) ok[l] = (unsigned)(b - l) < (unsigned)Wo ? ~0u : 0u;
+    const int colb = min(b, Wo + NA - 1);                  // a column further out has every tap dropped anyway
+    float wr[M][K][K];
+    int src[M];
+#pragma unroll
+    for (int q = 0; q < M; ++q) {
+#pragma unroll
+        for (int kh = 0; kh < K; ++kh)
+#pragma unroll
+            for (int kw = 0; kw < K; ++kw) wr[q][kh][kw] = ldf(w + (c * M + q) * K * K + kh * K + kw);
+        src[q] = bi.at<T>((active ? u : 0) * M + q) + colb;
+    }
+    // columns 2b - pad and the next; a lane writes what it does not own to the guard elements in front of the output area
+    const int col = 2 * b - pad;
+    const bool st0 = active && col >= 0 && col < W, st1 = active && col + 1 < W;
+    const int first = bo.at<T>(active ? u : 0) + col + (2 * a0 - pad - h0) * W;
+    int dst0 = st0 ? first : -1, dst1 = st1 ? first + 1 : -1;
+    const int step0 = st0 ? W : 0, step1 = st1 ? W : 0;
+    float acc[NA][2][2];
+#pragma unroll
+    for (int k = 0; k < NA; ++k) acc[k][0][0] = acc[k][0][1] = acc[k][1][0] = acc[k][1][1] = 0.f;
+    dma_wait();
+    __syncthreads();
+
+    // dy row r reaches the row pairs r .. r + NA - 1; pair r is complete after it.  Rows [r0, r1) are in the band.
+    auto step = [&](int r, auto read, auto checked) {
+        constexpr bool CK = decltype(checked)::value;
+        if constexpr (decltype(read)::value) {
+#pragma unroll
+            for (int q = 0; q < M; ++q) {
+                const T *p = lin + src[q] + (r - r0) * Wo;
+                float v[NA];
+#pragma unroll
+                for (int l = 0; l < NA; ++l) v[l] = masked(ldf(p - l), ok[l]);
+#pragma unroll
+                for (int k = 0; k < NA; ++k)
+#pragma unroll
+                    for (int f = 0; f < 2; ++f)
+#pragma unroll
+                        for (int l = 0; l < NA; ++l)
+#pragma unroll
+                            for (int e = 0; e < 2; ++e)
+                                if (2 * k + f < K && 2 * l + e < K) acc[k][f][e] = fmaf(wr[q][2 * k + f][2 * l + e], v[l], acc[k][f][e]);
+            }
+        }
+        if (!CK || r >= a0) {
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+                const int h = 2 * r - pad + f;
+                if (!CK || (h >= h0 && h < h1)) {              // uniform
+                    stf(lout + dst0 + f * step0, acc[0][f][0]);
+                    stf(lout + dst1 + f * step1, acc[0][f][1]);
+                }
+            }
+            dst0 += 2 * step0; dst1 += 2 * step1;
+        }
+#pragma unroll
+        for (int k = 0; k < NA; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[k][i >> 1][i & 1] = k + 1 < NA ? acc[k + 1][i >> 1][i & 1] : 0.f;
+    };
+    // rows above r0 are padding; pairs [ra, rb) lie in the band with both their rows
+    const int ra = a0 + (2 * a0 - pad < h0 ? 1 : 0), rb = min(r1, a1 - (2 * a1 - pad > h1 ? 1 : 0));
+    int r = max(a0 - (NA - 1), r0);
+    for (; r < min(ra, r1); ++r) step(r, std::true_type(), std::true_type());
+#pragma unroll NA
+    for (; r < rb; ++r) step(r, std::true_type(), std::false_type());
+    for (; r < r1; ++r) step(r, std::true_type(), std::true_type());
+    for (; r < a1; ++r) step(r, std::false_type(), std::true_type());
+    __syncthreads();
+    store_bands<T>(dx, bo, lout, nt != 0);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Filter gradient, stage 1.  A block owns U output channels and walks (image, band) items: x and dy bands staged as above, a
+// lane keeps the K*K sums of its column over all of them against a window of the last K/S dy rows.  The columns of a
+// channel are added through LDS in a fixed order at the end, one partial per block.
+// ---------------------------------------------------------------------------------------------
+template <typename T, int K, int S, bool SAME>
+__global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__restrict__ x, const T *__restrict__ dy,
+                                                          float *__restrict__ ws, int parts, int per_part, FlatTile ft,
+                                                          unsigned nblocks)
+{
+    extern __shared__ uint4 smem[];
+    constexpr int NA = (K + S - 1) / S;
+    const unsigned lb = xcd_remap(blockIdx.x, nblocks);
+    const int part = (int)(lb % (unsigned)parts), o0 = (int)(lb / (unsigned)parts) * ft.U;
+    const int np = min(ft.U, g.O - o0);
+    const int c0 = o0 / g.m, c1 = (o0 + np - 1) / g.m + 1;
+    const int u = (int)threadIdx.x / g.Wo, ow = (int)threadIdx.x - u * g.Wo;
+    const bool active = u < np;
+    const int uu = active ? u : 0, ju = (o0 + uu) / g.m - c0;
+    uint32_t ok[K];
+#pragma unroll
+    for (int kw = 0; kw < K; ++kw) ok[kw] = (unsigned)(ow * S - g.p + kw) < (unsigned)g.W ? ~0u : 0u;
+    const int col0 = min(max(ow * S - g.p, -K), g.W), owc = active ? ow : 0;
+    T *lx = reinterpret_cast<T *>(smem) + GUARD, *ldy = lx + ft.nin + GUARD;
+    float acc[K][K];
+#pragma unroll
+    for (int kh = 0; kh < K; ++kh)
+#pragma unroll
+        for (int kw = 0; kw < K; ++kw) acc[kh][kw] = 0.f;
+
+    const int items = g.N * ft.nbands, it1 = min(items, (part + 1) * per_part);
+    for (int it = part * per_part; it < it1; ++it) {
+        const int n = it / ft.nbands, band = it - n * ft.nbands;
+        const int oh0 = band * ft.TR, oh1 = min(g.Ho, oh0 + ft.TR);
+        const int r0 = min(max(oh0 * S - g.p, 0), g.H), r1 = max(min((oh1 - 1) * S - g.p + K, g.H), r0);
+        const Bands bx = {n * g.C + c0, c1 - c0, g.H * g.W, g.W, r0, r1, ft.pin};
+        const Bands by = {n * g.O + o0, np, g.Ho * g.Wo, g.Wo, oh0, oh1, ft.pout};
+        dma_bands<T>(x, g.N * g.C * g.H * g.W, bx, lx);
+        dma_bands<T>(dy, g.N * g.O * g.Ho * g.Wo, by, ldy);
+        const T *px = lx + bx.at<T>(ju) + col0, *pd = ldy + by.at<T>(uu) + owc;
+        float d[NA];
+#pragma unroll
+        for (int i = 0; i < NA; ++i) d[i] = 0.f;
+        dma_wait();
+        __syncthreads();
+        // step t: the S x rows from row (oh0 + t)*S - p on, against dy rows oh0 + t - i; steps [ta, tb) have all of them in the band
+        const int rows = oh1 - oh0, steps = rows + NA - 1;
+        const int base = oh0 * S - g.p - r0, nrows = r1 - r0;
+        auto step = [&](int t, auto checked) {
+            constexpr bool CK = decltype(checked)::value;
+            d[0] = !CK || t < rows ? ldf(pd + t * g.Wo) : 0.f;
+#pragma unroll
+            for (int j = 0; j < S; ++j) {
+                const int row = base + t * S + j;
+                if (CK && (row < 0 || row >= nrows)) continue;
+                const T *p = px + row * g.W;
+                float v[K];
+#pragma unroll
+                for (int kw = 0; kw < K; ++kw) {
+                    const float e = ldf(p + kw);
+                    v[kw] = SAME && kw == K / 2 ? e : masked(e, ok[kw]);
+                }
+#pragma unroll
+                for (int i = 0; i < NA; ++i) {
+                    if (j + i * S >= K || (CK && K > 3 && (unsigned)(t - i) >= (unsigned)rows)) continue;
+#pragma unroll
+                    for (int kw = 0; kw < K; ++kw) acc[j + i * S][kw] = fmaf(d[i], v[kw], acc[j + i * S][kw]);
+                }
+            }
+#pragma unroll
+            for (int i = NA - 1; i > 0; --i) d[i] = d[i - 1];
+        };
+        const int ta = (S - 1 - base) / S, tb = min((nrows - base) / S, rows);
+        int t = 0;
+        for (; t < min(K > 3 ? max(ta, NA - 1) : ta, steps); ++t) step(t, std::true_type());
+#pragma unroll NA
+        for (; t < tb; ++t) step(t, std::false_type());
+        for (; t < steps; ++t) step(t, std::true_type());
+        __syncthreads();
+    }
+
+    // CH sums at a time (all of them up to 5x5): [CH][threads] in LDS, then Q lanes per (channel, tap) add every Q-th column
+    const int Q = g.Wo < 16 ? 1 : g.Wo < 64 ? 4 : 8;
+    constexpr int CH = K * K <= 25 ? K * K : 25;
+    float *red = reinterpret_cast<float *>(smem);
+    const int J = g.O * K * K, nt = blockDim.x;
+#pragma unroll
+    for (int e0 = 0; e0 < K * K; e0 += CH) {
+        const int ne = K * K - e0 < CH ? K * K - e0 : CH;
+#pragma unroll
+        for (int e = 0; e < CH; ++e)
+            if (e0 + e < K * K) red[e * nt + threadIdx.x] = acc[(e0 + e) / K][(e0 + e) % K];
+        __syncthreads();
+        const int jobs = np * ne;
+        for (int f0 = 0; f0 < jobs * Q; f0 += nt) {        // uniform trip count
+            const int f = f0 + (int)threadIdx.x, job = f / Q, q = f & (Q - 1);
+            const int uj = job / ne, e = job - uj * ne;
+            float s = 0.f;
+            if (job < jobs)
+                for (int i = q; i < g.Wo; i += Q) s += red[e * nt + uj * g.Wo + i];
+            for (int h = Q >> 1; h >= 1; h >>= 1) s += __shfl_xor(s, h, 64);
+            if (job < jobs && q == 0) ws[(size_t)part * J + (o0 + uj) * K * K + e0 + e] = s;
+        }
+        __syncthreads();
+    }
+}
+
+// ---- host side --------------------------------------------------------------------------------
+
+namespace {
+
+// U planes of `cols` lanes each and the block size that leave the fewest lanes idle, at up to 256 threads (blocks of 448 filled
+// better on rows of 74 and 147 and still measured 5-20 % slower: fewer of them overlap), 512 for wider rows.
+void pick_lanes(int cols, int planes, int maxu, int *U, int *threads)
+{
+    double best = -1.0;
+    *U = 0;
+    const int tmax = cols > 256 ? 512 : 256;
+    for (int t = 192; t <= tmax; t += 64) {
+        int u = t / cols;
+        if (u > maxu) u = maxu;
+        if (u > planes) u = planes;
+        if (u < 1) continue;
+        int tt = (u * cols + 63) / 64 * 64;
+        const double eff = (double)(u * cols) / tt;
+        if (eff > best + 1e-9) { best = eff; *U = u; *threads = tt; }
+    }
+}
+
+// LDS of a block.  Bands of about 32 KiB (five blocks per compute unit): halves of that read too many halo rows, more leaves
+// too few blocks to overlap (74x74 fp32 forward at batch 32, 256 channels: 16 KiB 88 us, 20 78, 26 73, 32 70, 40 73, 50 76;
+// bf16 63, 47, 47, 46, 49, 50).  Whole planes, which have no halo, up to 40 KiB (19x19 stride 2, 728 channels: 16.5 -> 11.5 us
+// against bands of 32 KiB; 28x28 7x7 46 -> 38 us).  5x5 and 7x7 have the longer halos: bands of 40 KiB (28x28 7x7 forward
+// at batch 64, 256 channels 47 -> 38 us, filter gradient 71 -> 56; bf16 5x5 41x41 64 -> 59).
+inline int lds_target(int K) { return K == 3 ? 32 << 10 : 40 << 10; }
+constexpr int LDS_WHOLE = 40 << 10;
+constexpr int LDS_MOST = 64 << 10;
+
+inline int round_up(int a, int b) { return (a + b - 1) / b * b; }
+
+// Tile of a launch: `cols` lanes per plane; an output band of t units (rows, or row pairs) has out_rows(t) output rows and
+// needs in_rows(t) input rows; `mi` input planes per `mo` output planes.
+template <typename FI, typename FO>
+bool pick_tile(int esz, int cols, int units, int nplanes, int maxu, int Hi, int Wi, int Ho, int Wo, FI in_rows, FO out_rows,
+               int Mi, int mdiv, int target, FlatTile *ft)
+{
+    const int VE = 16 / esz;
+    pick_lanes(cols, nplanes, maxu, &ft->U, &ft->threads);
+    if (ft->U < 1) return false;
+    for (;;) {
+        const int nin_planes = Mi > 1 ? ft->U * Mi : (mdiv > 1 ? (ft->U - 1) / mdiv + 2 : ft->U);
+        auto lds = [&](int t, FlatTile *o) {
+            const bool whole = t >= units;
+            const int ir = in_rows(t) < Hi ? in_rows(t) : Hi, orr = out_rows(t) < Ho ? out_rows(t) : Ho;
+            o->TR = t; o->nbands = whole ? 1 : (units + t - 1) / t;
+            o->pin = whole ? 0 : round_up(ir * Wi + VE, VE);
+            o->pout = whole ? 0 : round_up(orr * Wo + VE, VE);
+            o->nin = whole ? round_up(nin_planes * Hi * Wi + VE, VE) : nin_planes * o->pin;
+            const int nout = whole ? round_up(ft->U * Ho * Wo + VE, VE) : ft->U * o->pout;
+            return (long long)(o->nin + nout + 3 * GUARD) * esz;
+        };
+        int t = units;
+        if (lds(t, ft) > LDS_WHOLE)
+            while (t > 1 && lds(t, ft) > target) --t;
+        // balanced bands
+        const int nb = (units + t - 1) / t;
+        t = (units + nb - 1) / nb;
+        if (lds(t, ft) <= LDS_MOST && (t >= 4 || t >= units || ft->U == 1)) return true;
+        if (ft->U == 1) return false;
+        ft->U = (ft->U + 1) / 2;
+        ft->threads = (ft->U * cols + 63) / 64 * 64;
+    }
+}
+
+size_t tile_lds(const FlatTile &ft, int esz, int Ho, int Wo)
+{
+    const int VE = 16 / esz;
+    const int nout = ft.pout ? ft.U * ft.pout : round_up(ft.U * Ho * Wo + VE, VE);
+    return (size_t)(ft.nin + nout + 3 * GUARD) * esz;
+}
+
+// Planes per block, at most: about two blocks per compute unit in the launch (planes of more than 24 rows are several bands),
+// but a wavefront's worth of columns.
+int most_planes(long long planes, int rows, int cols)
+{
+    const long long want = planes * (rows > 24 ? rows / 24 : 1) / 512, wave = (63 + cols) / cols, u = want > wave ? want : wave;
+    return (int)(u < 64 ? u : 64);
+}
+
+bool flat_k(const Geom &g) { return (g.K == 3 || g.K == 5 || g.K == 7) && (g.s == 1 || g.s == 2); }
+
+bool conv_tile(const Geom &g, int dtype, bool bwd, FlatTile *ft)
+{
+    const int esz = dtype == DT_F32 ? 4 : 2, K = g.K, S = g.s;
+    auto in_rows = [&](int t) { return (t - 1) * S + K; };
+    auto out_rows = [&](int t) { return t; };
+    if (!bwd) return pick_tile(esz, g.Wo, g.Ho, g.N * g.O, most_planes((long long)g.N * g.O, g.Ho, g.Wo), g.H, g.W, g.Ho, g.Wo, in_rows, out_rows, 1, g.m, lds_target(K), ft);
+    return pick_tile(esz, g.W, g.H, g.N * g.C, most_planes((long long)g.N * g.C, g.H, g.W), g.Ho, g.Wo, g.H, g.W, in_rows, out_rows, g.m, 1, lds_target(K), ft);
+}
+
+int s2_cols(const Geom &g) { return (g.W - 1 + g.p) / 2 - g.p / 2 + 1; }
+int s2_pairs(const Geom &g) { return (g.H - 1 + g.p) / 2 - g.p / 2 + 1; }
+bool s2_tile(const Geom &g, int dtype, FlatTile *ft)
+{
+    const int esz = dtype == DT_F32 ? 4 : 2, NA = (g.K + 1) / 2;
+    auto in_rows = [&](int t) { return t + NA - 1; };
+    auto out_rows = [&](int t) { return 2 * t; };
+    return pick_tile(esz, s2_cols(g), s2_pairs(g), g.N * g.C, most_planes((long long)g.N * g.C, g.H, s2_cols(g)), g.Ho, g.Wo, g.H, g.W, in_rows, out_rows, g.m, 1, lds_target(g.K), ft);
+}
+bool filter_tile(const Geom &g, int dtype, FlatTile *ft)
+{
+    const int esz = dtype == DT_F32 ? 4 : 2, K = g.K, S = g.s;
+    auto in_rows = [&](int t) { return (t - 1) * S + K; };
+    auto out_rows = [&](int t) { return t; };
+    return pick_tile(esz, g.Wo, g.Ho, g.O, most_planes((long long)g.N * g.O, g.Ho, g.Wo), g.H, g.W, g.Ho, g.Wo, in_rows, out_rows, 1, g.m, lds_target(K), ft);
+}
+
+}  // namespace
+
+bool nchwf_fwd_supported(const Geom &g, int dtype)
+{
+    FlatTile ft;
+    return flat_k(g) && conv_tile(g, dtype, false, &ft);
+}
+bool nchwf_bwd_data_supported(const Geom &g, int dtype)
+{
+    FlatTile ft;
+    if (!flat_k(g) || g.m > 2) return false;
+    return g.s == 1 ? conv_tile(g, dtype, true, &ft) : s2_tile(g, dtype, &ft);
+}
+
+int nchwf_bwd_filter_parts(const Geom &g, int dtype)
+{
+    FlatTile ft;
+    if (!flat_k(g) || !filter_tile(g, dtype, &ft)) return 0;
+    // about eight blocks per compute unit in the launch, two items per block and more where the launch has more than four
+    // blocks per compute unit that way, and at most 8 MiB of partials
+    const long long groups = (g.O + ft.U - 1) / ft.U, items = (long long)g.N * ft.nbands;
+    long long parts = (2048 + groups - 1) / groups;
+    if (groups * items > 1024 && parts > (items + 1) / 2) parts = (items + 1) / 2;
+    if (parts > items) parts = items;
+    const long long J = (long long)g.O * g.K * g.K;
+    if (parts * J * 4 > (8 << 20)) parts = (8 << 20) / (J * 4);
+    if (parts < 1) parts = 1;
+    const long long per = (items + parts - 1) / parts;
+    return (int)((items + per - 1) / per);
+}
+
+template <typename T, int K, int S, int M>
+static hipError_t conv_go(const Geom &g, int dtype, const void *in, const void *w, void *out, bool bwd, hipStream_t st)
+{
+    FlatTile ft;
+    if (!conv_tile(g, dtype, bwd, &ft)) return hipErrorInvalidValue;
+    const int Hi = bwd ? g.Ho : g.H, Wi = bwd ? g.Wo : g.W, Ho = bwd ? g.H : g.Ho, Wo = bwd ? g.W : g.Wo;
+    const int OC = bwd ? g.C : g.O, nplanes = g.N * OC;
+    const unsigned nblocks = (unsigned)((nplanes + ft.U - 1) / ft.U) * ft.nbands;
+    const int total_in = g.N * (bwd ? g.O : g.C) * Hi * Wi;
+    const int nt = stream_stores("NCHWF", 0, 0);
+    const bool same = (bwd ? K - 1 - g.p : g.p) == K / 2;
+    auto kernel = same ? k_nchwf_conv<T, K, S, M, true> : k_nchwf_conv<T, K, S, M, false>;
+    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(ft.threads), tile_lds(ft, sizeof(T), Ho, Wo), st, (const T *)in, (const T *)w,
+                        (T *)out, nplanes, OC, Hi, Wi, Ho, Wo, bwd ? K - 1 - g.p : g.p, bwd ? 1 : g.m, total_in,
+                       bwd ? 1 : 0, ft, nblocks, nt);
+    return hipGetLastError();
+}
+template <typename T, int K, int M>
+static hipError_t s2_go(const Geom &g, int dtype, const void *dy, const void *w, void *dx, hipStream_t st)
+{
+    FlatTile ft;
+    if (!s2_tile(g, dtype, &ft)) return hipErrorInvalidValue;
+    const int nplanes = g.N * g.C;
+    const unsigned nblocks = (unsigned)((nplanes + ft.U - 1) / ft.U) * ft.nbands;
+    const int nt = stream_stores("NCHWF", 0, 0);
+    hipLaunchKernelGGL((k_nchwf_bwd_data_s2<T, K, M>), dim3(nblocks), dim3(ft.threads), tile_lds(ft, sizeof(T), g.H, g.W), st, (const T *)dy,
+                       (const T *)w, (T *)dx, nplanes, g.C, g.H, g.W, g.Ho, g.Wo, g.p, s2_cols(g), g.N * g.O * g.Ho * g.Wo, ft,
+                       nblocks, nt);
+    return hipGetLastError();
+}
+template <typename T, int K, int S>
+static hipError_t filter_go(const Geom &g, int dtype, const void *x, const void *dy, float *ws, int parts, hipStream_t st)
+{
+    FlatTile ft;
+    if (!filter_tile(g, dtype, &ft)) return hipErrorInvalidValue;
+    const int items = g.N * ft.nbands, per = (items + parts - 1) / parts;
+    const unsigned nblocks = (unsigned)((g.O + ft.U - 1) / ft.U) * parts;
+    size_t lds = tile_lds(ft, sizeof(T), g.Ho, g.Wo);
+    const size_t red = (size_t)(K * K <= 25 ? K * K : 25) * ft.threads * 4;
+    if (red > lds) lds = red;
+    auto kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true> : k_nchwf_bwd_filter<T, K, S, false>;
+    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(ft.threads), lds, st, g, (const T *)x, (const T *)dy, ws, parts,
+                       per, ft, nblocks);
+    return hipGetLastError();
+}
+
+#define BY_K(F, ...) (g.K == 3 ? F<T, 3, __VA_ARGS__> : g.K == 5 ? F<T, 5, __VA_ARGS__> : F<T, 7, __VA_ARGS__>)
+template <typename T>
+static hipError_t fwd_t(const Geom &g, int dtype, const void *x, const void *w, void *y, hipStream_t st)
+{
+    return (g.s == 1 ? BY_K(conv_go, 1, 1) : BY_K(conv_go, 2, 1))(g, dtype, x, w, y, false, st);
+}
+template <typename T>
+static hipError_t bwd_data_t(const Geom &g, int dtype, const void *dy, const void *w, void *dx, hipStream_t st)
+{
+    if (g.s == 1) return (g.m == 1 ? BY_K(conv_go, 1, 1) : BY_K(conv_go, 1, 2))(g, dtype, dy, w, dx, true, st);
+    return (g.m == 1 ? BY_K(s2_go, 1) : BY_K(s2_go, 2))(g, dtype, dy, w, dx, st);
+}
+template <typename T>
+static hipError_t bwd_filter_t(const Geom &g, int dtype, const void *x, const void *dy, float *ws, int parts, hipStream_t st)
+{
+    return (g.s == 1 ? BY_K(filter_go, 1) : BY_K(filter_go, 2))(g, dtype, x, dy, ws, parts, st);
+}
+#undef BY_K
+
+hipError_t nchwf_fwd(const Geom &g, int dtype, const void *x, const void *w, void *y, hipStream_t st)
+{
+    return dtype == DT_F32 ? fwd_t<float>(g, dtype, x, w, y, st) : fwd_t<bf16_t>(g, dtype, x, w, y, st);
+}
+hipError_t nchwf_bwd_data(const Geom &g, int dtype, const void *dy, const void *w, void *dx, hipStream_t st)
+{
+    return dtype == DT_F32 ? bwd_data_t<float>(g, dtype, dy, w, dx, st) : bwd_data_t<bf16_t>(g, dtype, dy, w, dx, st);
+}
+hipError_t nchwf_bwd_filter(const Geom &g, int dtype, const void *x, const void *dy, float *ws, int parts, hipStream_t st)
+{
+    return dtype == DT_F32 ? bwd_filter_t<float>(g, dtype, x, dy, ws, parts, st) : bwd_filter_t<bf16_t>(g, dtype, x, dy, ws, parts, st);
+}
+
+}  // namespace dwc

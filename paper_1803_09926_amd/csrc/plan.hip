@@ -78,18 +78,6 @@ static int nhwc_th1(int dtype) { return dtype == DT_BF16 ? 28 : 14; }
 // measured 3-4 % faster than 14 inside the step, on the forward pass and on the input gradient.
 static int nchwd_th1(int dtype, int W) { return dtype == DT_BF16 ? 28 : (W <= 56 ? 8 : 14); }
 
-// NCHW: rows per unit.  Small planes are taken whole; larger ones in strips of 8 output rows
-// (halo rows come from L2), shrunk until the tile fits in LDS.
-static int nchw_pick_tr(const Geom &g, bool (*fits)(const Geom &, int))
-{
-    int tr = g.Ho <= 16 ? g.Ho : 8;
-    tr = tune("DWCONV_TUNE_TH", tr);
-    if (tr > g.Ho) tr = g.Ho;
-    while (tr > 1 && !fits(g, tr)) tr = (tr + 1) / 2;
-    return fits(g, tr) ? tr : 0;
-}
-static bool fits_bwd_filter(const Geom &g, int tr) { return nchw_bwd_filter_parts(g, tr, 1) > 0; }
-
 // Small-plane NCHW kernels: rows of up to 14 always, and whenever the row walk cannot take the shape (bf16 rows that
 // are not whole 16-byte vectors).  Rows of 28, where both families apply, go to whichever measured faster inside the
 // benchmark step: the filter gradient always to the small-plane kernel (37 against 46 us on the 28x28x256 layer at
@@ -108,20 +96,57 @@ static bool use_small(const Geom &g, int dtype, int pass)
     return g.s == 1;
 }
 
+// The any-width NCHW kernels (nchw_flat.hip) take what neither the small planes nor the row walk takes, and of the
+// row walk's shapes the fp32 5x5 layers at stride 1 whose arithmetic the row walk does not hide: forward and input gradient
+// (batch 64, us, row walk -> any width: 16x16x480 27 -> 17, 20x20x480 34 -> 26, 40x40x240 63 -> 48, 48x48x240 91 -> 69, 56x56x128
+// at batch 128 125 -> 102, 96x96x128 152 -> 145, 112x112x128 214 -> 210; the input gradient of 28x28x240 at batch 128 71 -> 51),
+// filter gradient up to rows of 24 (16x16 33 -> 23, 24x24 58 -> 45; 32x32 38 -> 47 and 56x56 107 -> 121 stay).  bf16 stays with
+// the packed-pair row walk (40x40x240 34 against 55).
+static bool flat_over_rowwalk(const Geom &g, int dtype, int pass)
+{
+    return dtype == DT_F32 && g.K == 5 && g.s == 1 && (pass < 2 || g.W <= 24);
+}
+
+static const char *flat_name(int K, int s, int pass)
+{
+    static const char *const names[3][3][2] = {
+        {{"nchw_flat_k3s1", "nchw_flat_k3s2"}, {"nchw_flat_k5s1", "nchw_flat_k5s2"}, {"nchw_flat_k7s1", "nchw_flat_k7s2"}},
+        {{"nchw_flat_k3s1_flip", "nchw_flat_bwd_data_k3s2"}, {"nchw_flat_k5s1_flip", "nchw_flat_bwd_data_k5s2"},
+         {"nchw_flat_k7s1_flip", "nchw_flat_bwd_data_k7s2"}},
+        {{"nchw_flat_bwd_filter_k3s1", "nchw_flat_bwd_filter_k3s2"}, {"nchw_flat_bwd_filter_k5s1", "nchw_flat_bwd_filter_k5s2"},
+         {"nchw_flat_bwd_filter_k7s1", "nchw_flat_bwd_filter_k7s2"}}};
+    return names[pass][(K - 3) / 2][s - 1];
+}
+static bool plan_flat(const Geom &g, int dtype, int pass, Plan &pl)
+{
+    // 7x7 layers of a few thousand outputs stay with the generic kernels.  The filter gradient: its two reductions cost more
+    // than the sums (2x8x9x9 4.6 us against 9.9, 4x32x14x14 7.8 against 10.0, 8x64x28x28 44 against 14).  Forward and input
+    // gradient at this size differ by two microseconds at most (7.4 against 5.2).
+    if (g.K == 7 && (long long)g.N * g.O * g.Ho * g.Wo < (pass == 2 ? 32768 : 2048)) return false;
+    if (pass == 0 ? !nchwf_fwd_supported(g, dtype) : pass == 1 ? !nchwf_bwd_data_supported(g, dtype) : false) return false;
+    if (pass == 2) {
+        const int parts = nchwf_bwd_filter_parts(g, dtype);
+        if (parts < 1) return false;
+        pl.parts = parts;
+    }
+    pl.variant = pass == 0 ? V_NCHWF_FWD : pass == 1 ? V_NCHWF_BWD_DATA : V_NCHWF_BWD_FILTER;
+    pl.name = flat_name(g.K, g.s, pass);
+    return true;
+}
+
 Plan plan_fwd(const Geom &g, int layout, int dtype)
 {
     Plan pl = {V_GENERIC, 0, 0, 0, 0, "generic"};
     if (layout == LAYOUT_NCHW) {
         if (use_small(g, dtype, 0)) { pl.variant = V_NCHWS_FWD; pl.name = g.K == 5 ? "nchw_smallplane_k5s1" : (g.s == 1 ? "nchw_smallplane_k3s1" : "nchw_smallplane_fwd_k3s2"); return pl; }
-        const int V = nchwd_vec(g, dtype, 0);
+        const int V = flat_over_rowwalk(g, dtype, 0) ? 0 : nchwd_vec(g, dtype, 0);
         if (V) {
             pl.a = V;
             if (g.s == 1) { pl.variant = V_NCHWD_S1; pl.b = pick_th(g.H, 1, nchwd_th1(dtype, g.W)); pl.name = g.K == 3 ? "nchw_rowwalk_k3s1" : "nchw_rowwalk_k5s1"; }
             else { pl.variant = V_NCHWD_K3S2; pl.b = pick_th(g.Ho, 2); pl.name = "nchw_rowwalk_fwd_k3s2"; }
             return pl;
         }
-        const int tr = nchw_pick_tr(g, nchw_fwd_supported);
-        if (tr) { pl.variant = V_NCHW_FWD; pl.b = tr; pl.name = "nchw_tile_fwd"; }
+        plan_flat(g, dtype, 0, pl);
         return pl;
     }
     if (layout == LAYOUT_NHWC) {
@@ -146,20 +171,14 @@ Plan plan_bwd_data(const Geom &g, int layout, int dtype)
             else { pl.variant = V_NCHWS_BWD_DATA_S2; pl.name = "nchw_smallplane_bwd_data_k3s2"; }
             return pl;
         }
-        const int V = nchwd_vec(g, dtype, 1);
+        const int V = flat_over_rowwalk(g, dtype, 1) ? 0 : nchwd_vec(g, dtype, 1);
         if (V) {
             pl.a = V;
             if (g.s == 1) { pl.variant = V_NCHWD_S1; pl.b = pick_th(g.H, 1, nchwd_th1(dtype, g.W)); pl.name = g.K == 3 ? "nchw_rowwalk_k3s1_flip" : "nchw_rowwalk_k5s1_flip"; }
             else { pl.variant = V_NCHWD_K3S2; pl.b = pick_th(g.Ho, 2, 14, g.Ho >= 56 ? 2 : 4); pl.name = "nchw_rowwalk_bwd_data_k3s2"; }
             return pl;
         }
-        if (g.m == 1 && same_pad_s1(g)) {
-            const int tr = nchw_pick_tr(g, nchw_fwd_supported);
-            if (tr) { pl.variant = V_NCHW_FWD; pl.b = tr; pl.name = "nchw_tile_fwd_flip"; }
-        } else if (g.m == 1 && k3s2p1(g)) {
-            const int tr = nchw_pick_tr(g, nchw_bwd_data_k3s2_supported);
-            if (tr) { pl.variant = V_NCHW_BWD_DATA_K3S2; pl.b = tr; pl.name = "nchw_tile_bwd_data_k3s2"; }
-        }
+        plan_flat(g, dtype, 1, pl);
         return pl;
     }
     if (layout == LAYOUT_NHWC) {
@@ -220,25 +239,8 @@ static Plan plan_bwd_filter_v(const Geom &g, int layout, int dtype, int force_v)
     Plan pl = {V_GENERIC, generic_bwd_filter_parts(g), 0, 0, 0, "generic"};
     if (layout == LAYOUT_NCHW) {
         if (use_small(g, dtype, 2) && plan_bwd_filter_nchws(g, dtype, pl)) return pl;
-        if (plan_bwd_filter_nchwd(g, dtype, pl)) return pl;
-        const int tr = nchw_pick_tr(g, fits_bwd_filter);
-        if (tr) {
-            // images per block: keep about 4096 blocks in the launch
-            const int wpl = g.Wo <= 8 ? 8 : g.Wo <= 16 ? 16 : g.Wo <= 32 ? 32 : g.Wo <= 64 ? 64 : g.Wo <= 128 ? 128 : 256;
-            const long long ublocks = ((long long)g.O * ceil_div(g.Ho, tr) + (256 / wpl) - 1) / (256 / wpl);
-            int NI = (int)((ublocks * g.N) / 4096);
-            if (NI < 1) NI = 1;
-            if (NI > g.N) NI = g.N;
-            NI = tune("DWCONV_TUNE_NI", NI);
-            int parts = nchw_bwd_filter_parts(g, tr, NI);
-            while ((long long)parts * g.O * g.K * g.K * 4 > (64ll << 20) && NI < g.N) {
-                NI *= 2;
-                parts = nchw_bwd_filter_parts(g, tr, NI);
-            }
-            if ((long long)parts * g.O * g.K * g.K * 4 <= (64ll << 20)) {
-                pl.variant = V_NCHW_BWD_FILTER; pl.b = tr; pl.c = NI; pl.parts = parts; pl.name = "nchw_tile_bwd_filter";
-            }
-        }
+        if (!flat_over_rowwalk(g, dtype, 2) && plan_bwd_filter_nchwd(g, dtype, pl)) return pl;
+        plan_flat(g, dtype, 2, pl);
         return pl;
     }
     if (layout == LAYOUT_NHWC) {
@@ -360,7 +362,7 @@ hipError_t launch_fwd(const Plan &pl, const Geom &g, int layout, int dtype, cons
     switch (pl.variant) {
     case V_NHWC_S1: return nhwc_s1(g, dtype, pl.a, x, w, y, false, pl.b, nhwc_pf(g, dtype), st);
     case V_NHWC_K3S2: return nhwc_k3s2(g, dtype, pl.a, x, w, y, false, pl.b, st);
-    case V_NCHW_FWD: return nchw_fwd(g, dtype, x, w, y, false, pl.b, st);
+    case V_NCHWF_FWD: return nchwf_fwd(g, dtype, x, w, y, st);
     case V_NCHWD_S1: return nchwd_s1(g, dtype, pl.a, x, w, y, false, pl.b, st);
     case V_NCHWS_FWD: return nchws_fwd(g, dtype, x, w, y, false, st);
     case V_NCHWD_K3S2: return nchwd_k3s2(g, dtype, pl.a, x, w, y, false, pl.b, st);
@@ -374,12 +376,11 @@ hipError_t launch_bwd_data(const Plan &pl, const Geom &g, int layout, int dtype,
     switch (pl.variant) {
     case V_NHWC_S1: return nhwc_s1(g, dtype, pl.a, dy, w, dx, true, pl.b, nhwc_pf(g, dtype), st);
     case V_NHWC_K3S2: return nhwc_k3s2(g, dtype, pl.a, dy, w, dx, true, pl.b, st);
-    case V_NCHW_FWD: return nchw_fwd(g, dtype, dy, w, dx, true, pl.b, st);
+    case V_NCHWF_BWD_DATA: return nchwf_bwd_data(g, dtype, dy, w, dx, st);
     case V_NCHWD_S1: return nchwd_s1(g, dtype, pl.a, dy, w, dx, true, pl.b, st);
     case V_NCHWS_FWD: return nchws_fwd(g, dtype, dy, w, dx, true, st);
     case V_NCHWS_BWD_DATA_S2: return nchws_bwd_data_s2(g, dtype, dy, w, dx, st);
     case V_NCHWD_K3S2: return nchwd_k3s2(g, dtype, pl.a, dy, w, dx, true, pl.b, st);
-    case V_NCHW_BWD_DATA_K3S2: return nchw_bwd_data_k3s2(g, dtype, dy, w, dx, pl.b, st);
     default: return generic_bwd_data(g, layout, dtype, dy, w, dx, st);
     }
 }
@@ -389,7 +390,7 @@ hipError_t launch_bwd_filter(const Plan &pl, const Geom &g, int layout, int dtyp
 {
     switch (pl.variant) {
     case V_NHWC_BWD_FILTER: return nhwc_bwd_filter(g, dtype, pl.a, x, dy, ws, pl.b, pl.c, st);
-    case V_NCHW_BWD_FILTER: return nchw_bwd_filter(g, dtype, x, dy, ws, pl.b, pl.c, st);
+    case V_NCHWF_BWD_FILTER: return nchwf_bwd_filter(g, dtype, x, dy, ws, pl.parts, st);
     case V_NCHWD_BWD_FILTER: return nchwd_bwd_filter(g, dtype, pl.a, x, dy, ws, pl.b, st);
     case V_NCHWS_BWD_FILTER: return nchws_bwd_filter(g, dtype, x, dy, ws, pl.a, pl.c, st);
     default: return generic_bwd_filter(g, layout, dtype, x, dy, ws, pl.parts, st);

@@ -1,0 +1,48 @@
+"""GPU parity of the NCHW any-width kernels (rows of any number of elements; 3x3, 5x5 and 7x7; stride 1 and 2; any padding)
+against the CPU oracle, element by element, at the edges of their tiling.  Tolerances as in gpu_util (fp32 sums of up to 49
+products in the forward and input-gradient passes; the filter gradient in fp32 whatever the storage type)."""
+import pytest
+
+import paper_1803_09926_amd as dw
+from paper_1803_09926_amd import workloads as wl
+from paper_1803_09926_amd.workloads import Layer
+
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    (3, Layer("whole_planes_odd", 37, 19, 19)),                        # a tile of several planes ends inside an image
+    (2, Layer("bands_short_last", 11, 75, 74)),                        # bands of unequal height, segments at every alignment
+    (1, Layer("one_plane_per_block", 5, 41, 147)),
+    (1, Layer("wide_rows", 3, 9, 509)),                                # more lanes than 256
+    (2, Layer("row_of_one", 9, 31, 1)),
+    (2, Layer("s2_odd_both", 13, 37, 37, 3, 2, 1)),
+    (2, Layer("s2_even_rows_odd", 13, 38, 75, 3, 2, 1)),
+    (2, Layer("s2_pad0", 7, 40, 41, 3, 2, 0)),
+    (2, Layer("pad2_k3", 7, 21, 22, 3, 1, 2)),
+    (2, Layer("pad_above_filter", 6, 10, 11, 3, 1, 5)),                # rows and columns of pure padding
+    (2, Layer("pad_above_filter_s2", 6, 10, 11, 5, 2, 6)),
+    (2, Layer("k5_41", 12, 41, 41, 5, 1, 2)),
+    (2, Layer("k5_rowwalk_width", 6, 40, 48, 5, 1, 2)),
+    (4, Layer("k5_s2_planes", 21, 15, 14, 5, 2, 2)),
+    (2, Layer("k5_s2_bands", 9, 57, 56, 5, 2, 2)),
+    (3, Layer("k7", 24, 28, 28, 7, 1, 3)),
+    (4, Layer("k7_pad1", 24, 30, 29, 7, 1, 1)),
+    (3, Layer("k7_s2", 24, 57, 31, 7, 2, 3)),
+    (2, Layer("k7_large", 16, 60, 59, 7, 1, 3)),
+    (2, Layer("m2", 10, 37, 37, 3, 1, 1, 2)),                          # output planes 2c and 2c + 1 read input plane c
+    (2, Layer("m2_k5_s2", 10, 29, 31, 5, 2, 2, 2)),
+    (2, Layer("m3", 7, 23, 22, 3, 1, 1, 3)),
+    (5, Layer("m2_k7", 12, 20, 21, 7, 1, 3, 2)),
+]
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("N,layer", CASES, ids=[l.name for _, l in CASES])
+def test_any_width_kernels_match_oracle(gpu_lib, N, layer, dtype):
+    d = gu.desc_for(layer, N, wl.NCHW, dtype)
+    print("case", layer, N, dtype, [dw.variant_name(d, i) for i in range(3)], flush=True)
+    if layer.name != "k5_rowwalk_width" or dtype == wl.F32:
+        assert dw.variant_name(d, 0).startswith("nchw_flat"), dw.variant_name(d, 0)
+    gu.check_layer_full(layer, N, wl.NCHW, dtype, seed=8100 + layer.C + dtype)
