@@ -264,6 +264,17 @@ static GPlan gplan(const GGeom &g, int layout, int dtype, int pass)
                 : pass == 1 ? (mm ? "group_nhwc_mfma_k3s1_flip" : "group_nhwc_rowwalk_k3s1_flip") : "group_nhwc_bwd_filter_k3s1";
         if (pass == 2) pl.parts = gconv_nhwc_bwd_filter_parts(g, dtype);
     }
+    // What no kernel above takes, and NCHW groups of a multiple of 16 channels in place of the row walk (14x14, 16 channels a
+    // group, 512 channels, fp32 batch 64: 62 -> 45 us; 32 channels at batch 4: 53 -> 15): the 16x16 matrix instructions, from
+    // 2048 outputs on.  Below that the generic kernels' one output per thread is as fast as laying out the filter (2x9x9x12,
+    // 5x5: 11 us against 17; 3x3 stride 2 5.7 against 9).
+    const bool rowwalk16 = pl.variant == GV_NCHW_K3S1 && g.Cg % 16 == 0 && g.Og % 16 == 0;
+    const long long outputs = (long long)g.N * (pass == 1 ? (long long)g.C * g.H * g.W : (long long)g.O * g.Ho * g.Wo);
+    if ((pl.variant == GV_GENERIC || rowwalk16) && outputs >= 2048 && gconv_gemm_supported(g, layout, dtype, pass)) {
+        pl.variant = GV_GEMM;
+        pl.name = pass == 0 ? "group_mfma16" : pass == 1 ? "group_mfma16_bwd_data" : "group_mfma16_bwd_filter";
+        if (pass == 2) pl.parts = gconv_gemm_parts(g, layout, dtype);
+    }
     // a tuned filter gradient whose partial sums would not fit in 64 MiB (very wide rows): the generic kernels
     if (pass == 2 && pl.variant != GV_GENERIC && (long long)pl.parts * g.O * g.Cg * g.K * g.K * 4 > (64ll << 20)) {
         const GPlan gen = {GV_GENERIC, gconv_generic_bwd_filter_parts(g), 0, 0, 0, "group_generic"};
@@ -354,6 +365,7 @@ int gconv_fwd(const dwconv_group_desc *desc, const void *x, const void *w, void 
     else if (pl.variant == GV_NCHW_K3S1) e = gconv_nchw_s1(g, desc->dtype, x, w, y, false, (hipStream_t)stream);
     else if (pl.variant == GV_NHWC_K3S1) e = gconv_nhwc_s1(g, desc->dtype, x, w, y, false, (hipStream_t)stream);
     else if (pl.variant == GV_NHWC_MFMA_S2) e = gconv_nhwc_mfma_s2(g, desc->dtype, x, w, y, false, (hipStream_t)stream);
+    else if (pl.variant == GV_GEMM) e = gconv_gemm(g, desc->layout, desc->dtype, x, w, y, false, (hipStream_t)stream);
     else e = gconv_generic_fwd(g, desc->layout, desc->dtype, x, w, y, (hipStream_t)stream);
     return e == hipSuccess ? DWCONV_OK : DWCONV_ERR_LAUNCH;
 }
@@ -377,6 +389,7 @@ int gconv_bwd_data(const dwconv_group_desc *desc, const void *dy, const void *w,
     else if (pl.variant == GV_NCHW_K3S1) e = gconv_nchw_s1(g, desc->dtype, dy, w, dx, true, (hipStream_t)stream);
     else if (pl.variant == GV_NHWC_K3S1) e = gconv_nhwc_s1(g, desc->dtype, dy, w, dx, true, (hipStream_t)stream);
     else if (pl.variant == GV_NHWC_MFMA_S2) e = gconv_nhwc_mfma_s2(g, desc->dtype, dy, w, dx, true, (hipStream_t)stream);
+    else if (pl.variant == GV_GEMM) e = gconv_gemm(g, desc->layout, desc->dtype, dy, w, dx, true, (hipStream_t)stream);
     else e = gconv_generic_bwd_data(g, desc->layout, desc->dtype, dy, w, dx, (hipStream_t)stream);
     return e == hipSuccess ? DWCONV_OK : DWCONV_ERR_LAUNCH;
 }
@@ -406,6 +419,7 @@ int gconv_bwd_filter(const dwconv_group_desc *desc, const void *x, const void *d
     else if (pl.variant == GV_NHWC_BWD_FILTER_S2) e = gconv_nhwc_bwd_filter_s2(g, desc->dtype, x, dy, (float *)workspace, pl.parts, (hipStream_t)stream);
     else if (pl.variant == GV_NCHW_K3S1) e = gconv_nchw_bwd_filter(g, desc->dtype, x, dy, (float *)workspace, pl.parts, (hipStream_t)stream);
     else if (pl.variant == GV_NHWC_K3S1) e = gconv_nhwc_bwd_filter(g, desc->dtype, x, dy, (float *)workspace, pl.parts, (hipStream_t)stream);
+    else if (pl.variant == GV_GEMM) e = gconv_gemm_bwd_filter(g, desc->layout, desc->dtype, x, dy, (float *)workspace, (hipStream_t)stream);
     else e = gconv_generic_bwd_filter(g, desc->layout, desc->dtype, x, dy, (float *)workspace, pl.parts, (hipStream_t)stream);
     if (e != hipSuccess) return DWCONV_ERR_LAUNCH;
     e = reduce_partials((const float *)workspace, pl.parts, J, (float *)dw, (hipStream_t)stream);

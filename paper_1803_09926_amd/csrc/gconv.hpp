@@ -12,7 +12,7 @@ struct GGeom {
     int Ho, Wo;
 };
 
-enum GVariant { GV_GENERIC = 0, GV_NCHW_K3S1, GV_NHWC_K3S1, GV_NCHWS_K3S1, GV_NHWC_MFMA_S2, GV_NHWC_BWD_FILTER_S2, GV_NCHWS_MFMA_BWD_FILTER, GV_NCHWS_MFMA_FWD, GV_NHWC_LDS_MFMA_BWD_FILTER, GV_NHWC_TR_BWD_FILTER };
+enum GVariant { GV_GENERIC = 0, GV_NCHW_K3S1, GV_NHWC_K3S1, GV_NCHWS_K3S1, GV_NHWC_MFMA_S2, GV_NHWC_BWD_FILTER_S2, GV_NCHWS_MFMA_BWD_FILTER, GV_NCHWS_MFMA_FWD, GV_NHWC_LDS_MFMA_BWD_FILTER, GV_NHWC_TR_BWD_FILTER, GV_GEMM };
 
 struct GPlan {
     int variant;
@@ -28,6 +28,13 @@ hipError_t gconv_generic_bwd_data(const GGeom &g, int layout, int dtype, const v
 int gconv_generic_bwd_filter_parts(const GGeom &g);
 hipError_t gconv_generic_bwd_filter(const GGeom &g, int layout, int dtype, const void *x, const void *dy, float *ws,
                                     int parts, hipStream_t st);
+
+// ---- any group size, filter of up to 7x7, stride of up to 4, padding, both layouts on the 16x16 matrix instructions
+// (gconv_gemm.hip); filter gradient: K 1, 3 or 5
+bool gconv_gemm_supported(const GGeom &g, int layout, int dtype, int pass);
+hipError_t gconv_gemm(const GGeom &g, int layout, int dtype, const void *in, const void *w, void *out, bool bwd, hipStream_t st);
+int gconv_gemm_parts(const GGeom &g, int layout, int dtype);
+hipError_t gconv_gemm_bwd_filter(const GGeom &g, int layout, int dtype, const void *x, const void *dy, float *ws, hipStream_t st);
 
 // ---- NCHW row-walk kernels, 3x3 stride 1 pad 1, 2, 4 or 8 channels per group on both sides (gconv_nchw.hip)
 bool gconv_nchw_supported(const GGeom &g);
