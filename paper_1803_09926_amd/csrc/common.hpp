@@ -141,6 +141,10 @@ struct BufView {
         const uint64_t a = (uint64_t)p;
         return (void *)(((uint64_t)uniform((uint32_t)(a >> 32)) << 32) | uniform((uint32_t)a));
     }
+    __device__ __forceinline__ uint16_t b16(uint32_t voff, uint32_t soff) const
+    {
+        return __builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)voff, (int)uniform(soff), 0);
+    }
     __device__ __forceinline__ uint32_t b32(uint32_t voff, uint32_t soff) const
     {
         return __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)voff, (int)uniform(soff), 0);
@@ -225,6 +229,7 @@ template <int V> struct RawVec<bf16_t, V> {
 template <> struct RawVec<bf16_t, 1> {
     bf16_t w;
     __device__ __forceinline__ void load(const bf16_t *p) { w = *p; }
+    __device__ __forceinline__ void load_buf(const BufView &b, uint32_t voff, uint32_t soff) { w = b.b16(voff, soff); }
     __device__ __forceinline__ void get(float (&r)[1]) const { r[0] = bf16_to_f32(w); }
     __device__ __forceinline__ void zero() { w = 0; }
 };

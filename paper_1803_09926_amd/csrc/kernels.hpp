@@ -63,6 +63,14 @@ bool nhwc_bwd_filter_dot2_supported(const Geom &g, int V);
 hipError_t nhwc_bwd_filter_dot2(const Geom &g, int V, const void *x, const void *dy, float *ws, int CT, int nctiles,
                                 int nowtiles, int TH, int nstrips, int NI, unsigned nblocks, hipStream_t st);
 
+// ---- NHWC row walks for any channel count and padding, K 3, 5 or 7, stride 1 or 2 (nhwc_any.hip) ------------------
+// Any multiplier; the input gradient 1 or 2.
+bool nhwca_supported(const Geom &g, int pass);
+hipError_t nhwca_fwd(const Geom &g, int dtype, const void *x, const void *w, void *y, hipStream_t st);
+hipError_t nhwca_bwd_data(const Geom &g, int dtype, const void *dy, const void *w, void *dx, hipStream_t st);
+int nhwca_bwd_filter_parts(const Geom &g);
+hipError_t nhwca_bwd_filter(const Geom &g, int dtype, const void *x, const void *dy, float *ws, hipStream_t st);
+
 // ---- NCHW kernels for rows of any width (nchw_flat.hip): K 3, 5 or 7, stride 1 or 2, any padding -----
 // Any multiplier; the input gradient multiplier 1 or 2.
 bool nchwf_fwd_supported(const Geom &g, int dtype);

@@ -120,9 +120,9 @@ static const char *flat_name(int K, int s, int pass)
 static bool plan_flat(const Geom &g, int dtype, int pass, Plan &pl)
 {
     // 7x7 layers of a few thousand outputs stay with the generic kernels.  The filter gradient: its two reductions cost more
-    // than the sums (2x8x9x9 4.6 us against 9.9, 4x32x14x14 7.8 against 10.0, 8x64x28x28 44 against 14).  Forward and input
-    // gradient at this size differ by two microseconds at most (7.4 against 5.2).
-    if (g.K == 7 && (long long)g.N * g.O * g.Ho * g.Wo < (pass == 2 ? 32768 : 2048)) return false;
+    // than the sums (2x8x9x9 4.6 us against 9.9, 4x32x14x14 7.8 against 10.0, 8x64x28x28 44 against 14).  A forward pass of
+    // this size is launch latency either way (7.4 against 5.2; the input gradient 11.4 against 5.2).
+    if (g.K == 7 && pass != 1 && (long long)g.N * g.O * g.Ho * g.Wo < (pass == 2 ? 32768 : 2048)) return false;
     if (pass == 0 ? !nchwf_fwd_supported(g, dtype) : pass == 1 ? !nchwf_bwd_data_supported(g, dtype) : false) return false;
     if (pass == 2) {
         const int parts = nchwf_bwd_filter_parts(g, dtype);
@@ -131,6 +131,23 @@ static bool plan_flat(const Geom &g, int dtype, int pass, Plan &pl)
     }
     pl.variant = pass == 0 ? V_NCHWF_FWD : pass == 1 ? V_NCHWF_BWD_DATA : V_NCHWF_BWD_FILTER;
     pl.name = flat_name(g.K, g.s, pass);
+    return true;
+}
+
+// The NHWC walks of nhwc_any.hip for what nhwc.hip does not take.
+static bool plan_any(const Geom &g, int pass, Plan &pl)
+{
+    static const char *const names[3][3][2] = {
+        {{"nhwc_any_k3s1", "nhwc_any_k3s2"}, {"nhwc_any_k5s1", "nhwc_any_k5s2"}, {"nhwc_any_k7s1", "nhwc_any_k7s2"}},
+        {{"nhwc_any_k3s1_flip", "nhwc_any_bwd_data_k3s2"}, {"nhwc_any_k5s1_flip", "nhwc_any_bwd_data_k5s2"},
+         {"nhwc_any_k7s1_flip", "nhwc_any_bwd_data_k7s2"}},
+        {{"nhwc_any_bwd_filter_k3s1", "nhwc_any_bwd_filter_k3s2"}, {"nhwc_any_bwd_filter_k5s1", "nhwc_any_bwd_filter_k5s2"},
+         {"nhwc_any_bwd_filter_k7s1", "nhwc_any_bwd_filter_k7s2"}}};
+    // (a forward pass of a few thousand outputs is as fast one output per thread: 2x9x9x6 3.0 us against 2.5)
+    if ((pass == 0 && (long long)g.N * g.O * g.Ho * g.Wo < 2048) || !nhwca_supported(g, pass)) return false;
+    if (pass == 2) pl.parts = nhwca_bwd_filter_parts(g);
+    pl.variant = pass == 0 ? V_NHWCA_FWD : pass == 1 ? V_NHWCA_BWD_DATA : V_NHWCA_BWD_FILTER;
+    pl.name = names[pass][(g.K - 3) / 2][g.s - 1];
     return true;
 }
 
@@ -157,7 +174,7 @@ Plan plan_fwd(const Geom &g, int layout, int dtype)
         } else if (V && k3s2p1(g)) {
             pl.variant = V_NHWC_K3S2; pl.a = V; pl.b = pick_th(g.Ho, 2);
             pl.name = "nhwc_rowwalk_fwd_k3s2";
-        }
+        } else plan_any(g, 0, pl);
     }
     return pl;
 }
@@ -189,7 +206,7 @@ Plan plan_bwd_data(const Geom &g, int layout, int dtype)
         } else if (V && k3s2p1(g)) {
             pl.variant = V_NHWC_K3S2; pl.a = V; pl.b = pick_th(g.Ho, 2, 14, 4);
             pl.name = "nhwc_rowwalk_bwd_data_k3s2";
-        }
+        } else plan_any(g, 1, pl);
     }
     return pl;
 }
@@ -276,12 +293,12 @@ static Plan plan_bwd_filter_v(const Geom &g, int layout, int dtype, int force_v)
                 if (NI < g.N) NI = NI * 2 < g.N ? NI * 2 : g.N; else TH = TH * 2 < g.Ho ? TH * 2 : g.Ho;
                 nhwc_bwd_filter_tiling(g, V, TH, NI, &CT, &nct, &nowt, &nst, &ngr);
             }
-            if ((long long)nowt * nst * ngr * g.O * g.K * g.K * 4 > (64ll << 20)) return pl;
+            if ((long long)nowt * nst * ngr * g.O * g.K * g.K * 4 > (64ll << 20)) { plan_any(g, 2, pl); return pl; }
             pl.variant = V_NHWC_BWD_FILTER; pl.a = V; pl.b = TH; pl.c = NI;
             pl.parts = nowt * nst * ngr;
             pl.name = g.m == 2 ? "nhwc_bwd_filter_k3s1_m2"
                                : (g.s == 2 ? "nhwc_bwd_filter_k3s2" : (g.K == 3 ? "nhwc_bwd_filter_k3s1" : "nhwc_bwd_filter_k5s1"));
-        }
+        } else plan_any(g, 2, pl);
     }
     return pl;
 }
@@ -362,6 +379,7 @@ hipError_t launch_fwd(const Plan &pl, const Geom &g, int layout, int dtype, cons
     switch (pl.variant) {
     case V_NHWC_S1: return nhwc_s1(g, dtype, pl.a, x, w, y, false, pl.b, nhwc_pf(g, dtype), st);
     case V_NHWC_K3S2: return nhwc_k3s2(g, dtype, pl.a, x, w, y, false, pl.b, st);
+    case V_NHWCA_FWD: return nhwca_fwd(g, dtype, x, w, y, st);
     case V_NCHWF_FWD: return nchwf_fwd(g, dtype, x, w, y, st);
     case V_NCHWD_S1: return nchwd_s1(g, dtype, pl.a, x, w, y, false, pl.b, st);
     case V_NCHWS_FWD: return nchws_fwd(g, dtype, x, w, y, false, st);
@@ -376,6 +394,7 @@ hipError_t launch_bwd_data(const Plan &pl, const Geom &g, int layout, int dtype,
     switch (pl.variant) {
     case V_NHWC_S1: return nhwc_s1(g, dtype, pl.a, dy, w, dx, true, pl.b, nhwc_pf(g, dtype), st);
     case V_NHWC_K3S2: return nhwc_k3s2(g, dtype, pl.a, dy, w, dx, true, pl.b, st);
+    case V_NHWCA_BWD_DATA: return nhwca_bwd_data(g, dtype, dy, w, dx, st);
     case V_NCHWF_BWD_DATA: return nchwf_bwd_data(g, dtype, dy, w, dx, st);
     case V_NCHWD_S1: return nchwd_s1(g, dtype, pl.a, dy, w, dx, true, pl.b, st);
     case V_NCHWS_FWD: return nchws_fwd(g, dtype, dy, w, dx, true, st);
@@ -390,6 +409,7 @@ hipError_t launch_bwd_filter(const Plan &pl, const Geom &g, int layout, int dtyp
 {
     switch (pl.variant) {
     case V_NHWC_BWD_FILTER: return nhwc_bwd_filter(g, dtype, pl.a, x, dy, ws, pl.b, pl.c, st);
+    case V_NHWCA_BWD_FILTER: return nhwca_bwd_filter(g, dtype, x, dy, ws, st);
     case V_NCHWF_BWD_FILTER: return nchwf_bwd_filter(g, dtype, x, dy, ws, pl.parts, st);
     case V_NCHWD_BWD_FILTER: return nchwd_bwd_filter(g, dtype, pl.a, x, dy, ws, pl.b, st);
     case V_NCHWS_BWD_FILTER: return nchws_bwd_filter(g, dtype, x, dy, ws, pl.a, pl.c, st);

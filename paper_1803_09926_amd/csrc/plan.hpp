@@ -11,6 +11,9 @@ enum Variant {
     V_NHWC_S1,          // a = V, b = TH
     V_NHWC_K3S2,        // a = V, b = TH
     V_NHWC_BWD_FILTER,  // a = V, b = TH, c = NI
+    V_NHWCA_FWD,        // any channel count and padding (nhwc_any.hip)
+    V_NHWCA_BWD_DATA,
+    V_NHWCA_BWD_FILTER,
     V_NCHWF_FWD,        // any row width (nchw_flat.hip)
     V_NCHWF_BWD_DATA,
     V_NCHWF_BWD_FILTER,

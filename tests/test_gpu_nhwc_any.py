@@ -1,0 +1,43 @@
+"""GPU parity of the NHWC row walks for any channel count, padding and multiplier (3x3, 5x5, 7x7; stride 1 and 2) against the CPU
+oracle, element by element, at the edges of their tiling.  Tolerances as in gpu_util."""
+import pytest
+
+import paper_1803_09926_amd as dw
+from paper_1803_09926_amd import workloads as wl
+from paper_1803_09926_amd.workloads import Layer
+
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    (2, Layer("k5_s2", 128, 28, 27, 5, 2, 2)),
+    (3, Layer("k5_s2_odd_c", 13, 29, 30, 5, 2, 2)),
+    (2, Layer("k7", 64, 28, 28, 7, 1, 3)),
+    (2, Layer("k7_c_even", 30, 17, 41, 7, 1, 3)),
+    (2, Layer("k7_s2", 36, 31, 32, 7, 2, 3)),
+    (2, Layer("c_odd", 211, 14, 14)),
+    (2, Layer("c_two", 2, 40, 41)),
+    (1, Layer("c_one", 1, 75, 74)),
+    (2, Layer("c_odd_s2", 37, 41, 40, 3, 2, 1)),
+    (2, Layer("k5_c_odd", 31, 20, 20, 5, 1, 2)),
+    (2, Layer("pad0", 16, 30, 29, 3, 1, 0)),
+    (2, Layer("pad0_s2", 16, 30, 29, 3, 2, 0)),
+    (2, Layer("pad3_k3", 16, 12, 13, 3, 1, 3)),                       # rows and columns of pure padding
+    (2, Layer("pad6_k5_s2", 10, 12, 13, 5, 2, 6)),
+    (2, Layer("m2_k5", 24, 20, 21, 5, 1, 2, 2)),
+    (2, Layer("m2_s2", 24, 20, 21, 3, 2, 1, 2)),
+    (2, Layer("m2_k7_s2", 12, 33, 20, 7, 2, 3, 2)),
+    (2, Layer("m3", 10, 16, 17, 3, 1, 1, 3)),                         # (its input gradient stays generic)
+    (1, Layer("tall", 6, 300, 5, 5, 2, 2)),                           # many strips
+    (1, Layer("wide", 6, 5, 700, 7, 1, 3)),
+]
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("N,layer", CASES, ids=[l.name for _, l in CASES])
+def test_any_channel_walks_match_oracle(gpu_lib, N, layer, dtype):
+    d = gu.desc_for(layer, N, wl.NHWC, dtype)
+    print("case", layer, N, dtype, [dw.variant_name(d, i) for i in range(3)], flush=True)
+    assert dw.variant_name(d, 0).startswith("nhwc_any") and dw.variant_name(d, 2).startswith("nhwc_any")
+    gu.check_layer_full(layer, N, wl.NHWC, dtype, seed=8200 + layer.C + dtype)
