@@ -133,38 +133,74 @@ def bwd_workspace_bytes(d: Desc) -> int:
     return int(load().dwconv_bwd_workspace_bytes(ctypes.byref(d)))
 
 
-def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+# ---- what a call checks and passes on --------------------------------------------------------------------
+# A small layer's kernels take 3 to 5 us, so the calls below avoid what costs a microsecond each: a stream object, wrapped
+# pointers (ctypes takes plain integers for void*), a second entry into the library for the output size.
+
+_torch = _raw_stream = _device = None
+
+
+def _bind_torch():
+    global _torch, _raw_stream, _device
+    import torch
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    _device = getattr(torch._C, "_cuda_getDevice", None)
+    if _raw_stream is None or _device is None:
+        _raw_stream, _device = (lambda dev: torch.cuda.current_stream().cuda_stream), (lambda: 0)
+    _torch = torch
 
 
 def _stream(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    """The hipStream_t handle of `stream`, by default of torch's current stream on the current device."""
+    return _raw_stream(_device()) if stream is None else stream.cuda_stream
 
 
-def _check_tensor(t, name, d: Desc, numel: int, fp32_always=False):
-    import torch
-    want = torch.float32 if (fp32_always or d.dtype == F32) else torch.bfloat16
+def _check_tensor(t, name, d, numel: int, fp32_always=False):
+    if _torch is None:
+        _bind_torch()
+    want = _torch.float32 if (fp32_always or d.dtype == F32) else _torch.bfloat16
+    if t.is_cuda and t.dtype is want and t.is_contiguous() and t.numel() == numel:
+        return
     if not t.is_cuda:
         raise ValueError("%s must be a device tensor" % name)
     if t.dtype != want:
         raise ValueError("%s must be %s" % (name, want))
-    if not t.is_contiguous() or t.numel() != numel:
-        raise ValueError("%s must be contiguous with %d elements (has %d)" % (name, numel, t.numel()))
+    raise ValueError("%s must be contiguous with %d elements (has %d)" % (name, numel, t.numel()))
+
+
+def _workspace(workspace):
+    """(pointer, bytes) of a workspace tensor."""
+    if workspace is None or not workspace.is_cuda:
+        raise ValueError("workspace must be a device tensor")
+    return workspace.data_ptr(), workspace.numel() * workspace.element_size()
+
+
+# Element counts of (x, y, w) by the values of a descriptor's fields.
+_size_memo = {}
+
+
+def _remember(key, sizes):
+    if len(_size_memo) >= 1024:
+        _size_memo.clear()
+    _size_memo[key] = sizes
+    return sizes
 
 
 def _sizes(d: Desc):
+    key = bytes(d)
+    found = _size_memo.get(key)
+    if found is not None:
+        return found
     ho, wo = out_dims(d)
     O = d.C * d.mult
-    return d.N * d.C * d.H * d.W, d.N * O * ho * wo, O * d.K * d.K
+    return _remember(key, (d.N * d.C * d.H * d.W, d.N * O * ho * wo, O * d.K * d.K))
 
 
 def fwd(d: Desc, x, w, y, stream=None):
     """Enqueue y = depthwise cross-correlation of x with w on `stream` (default: torch's current)."""
     nx, ny, nw = _sizes(d)
     _check_tensor(x, "x", d, nx); _check_tensor(w, "w", d, nw); _check_tensor(y, "y", d, ny)
-    rc = load().dwconv_fwd(ctypes.byref(d), _ptr(x), _ptr(w), _ptr(y), _stream(stream))
+    rc = load().dwconv_fwd(d, x.data_ptr(), w.data_ptr(), y.data_ptr(), _stream(stream))
     if rc != 0:
         raise DwconvError(rc, "dwconv_fwd")
     return y
@@ -174,7 +210,7 @@ def bwd_data(d: Desc, dy, w, dx, stream=None):
     """Enqueue dx = input gradient."""
     nx, ny, nw = _sizes(d)
     _check_tensor(dy, "dy", d, ny); _check_tensor(w, "w", d, nw); _check_tensor(dx, "dx", d, nx)
-    rc = load().dwconv_bwd_data(ctypes.byref(d), _ptr(dy), _ptr(w), _ptr(dx), _stream(stream))
+    rc = load().dwconv_bwd_data(d, dy.data_ptr(), w.data_ptr(), dx.data_ptr(), _stream(stream))
     if rc != 0:
         raise DwconvError(rc, "dwconv_bwd_data")
     return dx
@@ -185,11 +221,9 @@ def bwd_filter(d: Desc, x, dy, dw, workspace, stream=None):
     bwd_filter_workspace_bytes(d) bytes."""
     nx, ny, nw = _sizes(d)
     _check_tensor(x, "x", d, nx); _check_tensor(dy, "dy", d, ny); _check_tensor(dw, "dw", d, nw, fp32_always=True)
-    if workspace is None or not workspace.is_cuda:
-        raise ValueError("workspace must be a device tensor")
-    nbytes = workspace.numel() * workspace.element_size()
-    rc = load().dwconv_bwd_filter(ctypes.byref(d), _ptr(x), _ptr(dy), _ptr(dw), _ptr(workspace),
-                                  ctypes.c_size_t(nbytes), _stream(stream))
+    ws, nbytes = _workspace(workspace)
+    rc = load().dwconv_bwd_filter(d, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), ws,
+                                  nbytes, _stream(stream))
     if rc != 0:
         raise DwconvError(rc, "dwconv_bwd_filter")
     return dw
@@ -200,7 +234,7 @@ def bwd_filter_noalloc(d: Desc, x, dy, dw, stream=None):
     (the partial sums go to a fixed array inside the library; shapes that need more raise DWCONV_ERR_SCRATCH)."""
     nx, ny, nw = _sizes(d)
     _check_tensor(x, "x", d, nx); _check_tensor(dy, "dy", d, ny); _check_tensor(dw, "dw", d, nw, fp32_always=True)
-    rc = load().dwconv_bwd_filter_noalloc(ctypes.byref(d), _ptr(x), _ptr(dy), _ptr(dw), _stream(stream))
+    rc = load().dwconv_bwd_filter_noalloc(d, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), _stream(stream))
     if rc != 0:
         raise DwconvError(rc, "dwconv_bwd_filter_noalloc")
     return dw
@@ -212,11 +246,9 @@ def bwd(d: Desc, x, dy, w, dx, dw, workspace, stream=None):
     nx, ny, nw = _sizes(d)
     _check_tensor(x, "x", d, nx); _check_tensor(dy, "dy", d, ny); _check_tensor(w, "w", d, nw)
     _check_tensor(dx, "dx", d, nx); _check_tensor(dw, "dw", d, nw, fp32_always=True)
-    if workspace is None or not workspace.is_cuda:
-        raise ValueError("workspace must be a device tensor")
-    nbytes = workspace.numel() * workspace.element_size()
-    rc = load().dwconv_bwd(ctypes.byref(d), _ptr(x), _ptr(dy), _ptr(w), _ptr(dx), _ptr(dw), _ptr(workspace),
-                           ctypes.c_size_t(nbytes), _stream(stream))
+    ws, nbytes = _workspace(workspace)
+    rc = load().dwconv_bwd(d, x.data_ptr(), dy.data_ptr(), w.data_ptr(), dx.data_ptr(), dw.data_ptr(), ws,
+                           nbytes, _stream(stream))
     if rc != 0:
         raise DwconvError(rc, "dwconv_bwd")
     return dx, dw
@@ -235,7 +267,7 @@ def gconv_variant_name(d: GroupDesc, which: int) -> str:
 
 def gconv_out_dims(d: GroupDesc):
     ho, wo = ctypes.c_int32(0), ctypes.c_int32(0)
-    rc = load().gconv_out_dims(ctypes.byref(d), ctypes.byref(ho), ctypes.byref(wo))
+    rc = load().gconv_out_dims(d, ctypes.byref(ho), ctypes.byref(wo))
     if rc != 0:
         raise DwconvError(rc, "gconv_out_dims")
     return ho.value, wo.value
@@ -246,15 +278,19 @@ def gconv_bwd_filter_workspace_bytes(d: GroupDesc) -> int:
 
 
 def _gsizes(d: GroupDesc):
+    key = bytes(d)                       # one field longer than a Desc: the two never collide
+    found = _size_memo.get(key)
+    if found is not None:
+        return found
     ho, wo = gconv_out_dims(d)
-    return d.N * d.C * d.H * d.W, d.N * d.O * ho * wo, d.O * (d.C // d.groups) * d.K * d.K
+    return _remember(key, (d.N * d.C * d.H * d.W, d.N * d.O * ho * wo, d.O * (d.C // d.groups) * d.K * d.K))
 
 
 def gconv_fwd(d: GroupDesc, x, w, y, stream=None):
     """Enqueue y = group cross-correlation of x with w (w [O,Cg,K,K] for NCHW, [K,K,Cg,O] for NHWC)."""
     nx, ny, nw = _gsizes(d)
     _check_tensor(x, "x", d, nx); _check_tensor(w, "w", d, nw); _check_tensor(y, "y", d, ny)
-    rc = load().gconv_fwd(ctypes.byref(d), _ptr(x), _ptr(w), _ptr(y), _stream(stream))
+    rc = load().gconv_fwd(d, x.data_ptr(), w.data_ptr(), y.data_ptr(), _stream(stream))
     if rc != 0:
         raise DwconvError(rc, "gconv_fwd")
     return y
@@ -264,7 +300,7 @@ def gconv_bwd_data(d: GroupDesc, dy, w, dx, stream=None):
     """Enqueue dx = input gradient of the group convolution."""
     nx, ny, nw = _gsizes(d)
     _check_tensor(dy, "dy", d, ny); _check_tensor(w, "w", d, nw); _check_tensor(dx, "dx", d, nx)
-    rc = load().gconv_bwd_data(ctypes.byref(d), _ptr(dy), _ptr(w), _ptr(dx), _stream(stream))
+    rc = load().gconv_bwd_data(d, dy.data_ptr(), w.data_ptr(), dx.data_ptr(), _stream(stream))
     if rc != 0:
         raise DwconvError(rc, "gconv_bwd_data")
     return dx
@@ -275,11 +311,9 @@ def gconv_bwd_filter(d: GroupDesc, x, dy, dw, workspace, stream=None):
     at least gconv_bwd_filter_workspace_bytes(d) bytes."""
     nx, ny, nw = _gsizes(d)
     _check_tensor(x, "x", d, nx); _check_tensor(dy, "dy", d, ny); _check_tensor(dw, "dw", d, nw, fp32_always=True)
-    if workspace is None or not workspace.is_cuda:
-        raise ValueError("workspace must be a device tensor")
-    nbytes = workspace.numel() * workspace.element_size()
-    rc = load().gconv_bwd_filter(ctypes.byref(d), _ptr(x), _ptr(dy), _ptr(dw), _ptr(workspace),
-                                 ctypes.c_size_t(nbytes), _stream(stream))
+    ws, nbytes = _workspace(workspace)
+    rc = load().gconv_bwd_filter(d, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), ws,
+                                 nbytes, _stream(stream))
     if rc != 0:
         raise DwconvError(rc, "gconv_bwd_filter")
     return dw

@@ -459,8 +459,14 @@ bool pick_tile(int esz, int cols, int units, int nplanes, int maxu, int Hi, int 
             return (long long)(o->nin + nout + 3 * GUARD) * esz;
         };
         int t = units;
-        if (lds(t, ft) > LDS_WHOLE)
-            while (t > 1 && lds(t, ft) > target) --t;
+        if (lds(t, ft) > LDS_WHOLE) {                        // the tallest band within the target, by bisection
+            int lo = 1, hi = units - 1 > 1 ? units - 1 : 1;
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) / 2;
+                if (lds(mid, ft) <= target) lo = mid; else hi = mid - 1;
+            }
+            t = lo;
+        }
         // balanced bands
         const int nb = (units + t - 1) / t;
         t = (units + nb - 1) / nb;
