@@ -50,14 +50,20 @@ static int nhwc_pf(const Geom &g, int dtype)
 // short strips win (14 input rows at stride 1, 7 output rows at stride 2) even though each strip
 // re-reads K-1 halo rows (those come from L2): more, shorter walks keep the launch's accesses
 // closer together in memory.
-static int pick_th(int rows, int stride, int dflt1 = 14, int dflt2 = 0)
+// A launch with fewer than MIN_LANES lanes (`lanes` per strip) takes strips of half the height, and half again down to four
+// rows: it is one short round of wavefronts, each as long as its walk.  us with tall strips -> short ones, forward: bf16 NCHW
+// 4x240x40x40 5x5 20.9 -> 5.7, 3x3 15.3 -> 4.7; bf16 NHWC 8x32x112x112 9.4 -> 4.7, 16x128x56x56 10.1 -> 6.4, 64x256x28x28 12.5 ->
+// 10.1; fp32 NHWC 1x512x14x14 4.5 -> 3.0.  Half the limit leaves the NHWC 5x5 at 16.1 where this gives 6.6.
+constexpr int MIN_LANES = 65536;
+static int pick_th(int rows, long long lanes, int stride, int dflt1 = 14, int dflt2 = 0)
 {
     // stride 2: 7 output rows, 4 on tall maps (56 output rows and more: 1-4 % on the 112x112 and 56x56 layers);
     // the input gradient takes 4 dy rows on every map (28 dy rows: NHWC 45.2 -> 42.2 us, NCHW 44.0 -> 42.5 us; 14 dy
     // rows: NHWC 21.1 -> 19.5 us) and in NCHW 2 on tall maps (its 112x112 layer: 118 -> 110 us inside the step; NHWC
     // lost 1 % with it)
     if (dflt2 == 0) dflt2 = rows >= 56 ? 4 : 7;
-    const int target = stride == 1 ? tune("DWCONV_TUNE_TH1", dflt1) : tune("DWCONV_TUNE_TH2", dflt2);
+    int target = stride == 1 ? tune("DWCONV_TUNE_TH1", dflt1) : tune("DWCONV_TUNE_TH2", dflt2);
+    while (target > 4 && lanes * ceil_div(rows, target) < MIN_LANES) target = (target + 1) / 2;
     // balanced strips: the number of strips that brings their height closest to the target, then equal
     // heights (19 rows are one strip of 19, not 14 + 5; 37 rows are 13 + 13 + 11)
     int nstrips = (rows + target / 2) / target;
@@ -159,8 +165,8 @@ Plan plan_fwd(const Geom &g, int layout, int dtype)
         const int V = flat_over_rowwalk(g, dtype, 0) ? 0 : nchwd_vec(g, dtype, 0);
         if (V) {
             pl.a = V;
-            if (g.s == 1) { pl.variant = V_NCHWD_S1; pl.b = pick_th(g.H, 1, nchwd_th1(dtype, g.W)); pl.name = g.K == 3 ? "nchw_rowwalk_k3s1" : "nchw_rowwalk_k5s1"; }
-            else { pl.variant = V_NCHWD_K3S2; pl.b = pick_th(g.Ho, 2); pl.name = "nchw_rowwalk_fwd_k3s2"; }
+            if (g.s == 1) { pl.variant = V_NCHWD_S1; pl.b = pick_th(g.H, (long long)g.N * g.O * (g.W / V), 1, nchwd_th1(dtype, g.W)); pl.name = g.K == 3 ? "nchw_rowwalk_k3s1" : "nchw_rowwalk_k5s1"; }
+            else { pl.variant = V_NCHWD_K3S2; pl.b = pick_th(g.Ho, (long long)g.N * g.O * (g.Wo / V), 2); pl.name = "nchw_rowwalk_fwd_k3s2"; }
             return pl;
         }
         plan_flat(g, dtype, 0, pl);
@@ -169,10 +175,10 @@ Plan plan_fwd(const Geom &g, int layout, int dtype)
     if (layout == LAYOUT_NHWC) {
         const int V = nhwc_vec(g, dtype);
         if (V && same_pad_s1(g)) {
-            pl.variant = V_NHWC_S1; pl.a = V; pl.b = pick_th(g.H, 1, nhwc_th1(dtype));
+            pl.variant = V_NHWC_S1; pl.a = V; pl.b = pick_th(g.H, (long long)g.N * g.W * (g.O / V), 1, nhwc_th1(dtype));
             pl.name = g.m == 2 ? "nhwc_rowwalk_k3s1_m2" : (g.K == 3 ? "nhwc_rowwalk_k3s1" : "nhwc_rowwalk_k5s1");
         } else if (V && k3s2p1(g)) {
-            pl.variant = V_NHWC_K3S2; pl.a = V; pl.b = pick_th(g.Ho, 2);
+            pl.variant = V_NHWC_K3S2; pl.a = V; pl.b = pick_th(g.Ho, (long long)g.N * g.Wo * (g.O / V), 2);
             pl.name = "nhwc_rowwalk_fwd_k3s2";
         } else plan_any(g, 0, pl);
     }
@@ -191,8 +197,8 @@ Plan plan_bwd_data(const Geom &g, int layout, int dtype)
         const int V = flat_over_rowwalk(g, dtype, 1) ? 0 : nchwd_vec(g, dtype, 1);
         if (V) {
             pl.a = V;
-            if (g.s == 1) { pl.variant = V_NCHWD_S1; pl.b = pick_th(g.H, 1, nchwd_th1(dtype, g.W)); pl.name = g.K == 3 ? "nchw_rowwalk_k3s1_flip" : "nchw_rowwalk_k5s1_flip"; }
-            else { pl.variant = V_NCHWD_K3S2; pl.b = pick_th(g.Ho, 2, 14, g.Ho >= 56 ? 2 : 4); pl.name = "nchw_rowwalk_bwd_data_k3s2"; }
+            if (g.s == 1) { pl.variant = V_NCHWD_S1; pl.b = pick_th(g.H, (long long)g.N * g.O * (g.W / V), 1, nchwd_th1(dtype, g.W)); pl.name = g.K == 3 ? "nchw_rowwalk_k3s1_flip" : "nchw_rowwalk_k5s1_flip"; }
+            else { pl.variant = V_NCHWD_K3S2; pl.b = pick_th(g.Ho, (long long)g.N * g.O * (g.Wo / V), 2, 14, g.Ho >= 56 ? 2 : 4); pl.name = "nchw_rowwalk_bwd_data_k3s2"; }
             return pl;
         }
         plan_flat(g, dtype, 1, pl);
@@ -201,10 +207,10 @@ Plan plan_bwd_data(const Geom &g, int layout, int dtype)
     if (layout == LAYOUT_NHWC) {
         const int V = nhwc_vec(g, dtype);
         if (V && same_pad_s1(g)) {
-            pl.variant = V_NHWC_S1; pl.a = V; pl.b = pick_th(g.H, 1, nhwc_th1(dtype));
+            pl.variant = V_NHWC_S1; pl.a = V; pl.b = pick_th(g.H, (long long)g.N * g.W * (g.O / V), 1, nhwc_th1(dtype));
             pl.name = g.m == 2 ? "nhwc_rowwalk_k3s1_flip_m2" : (g.K == 3 ? "nhwc_rowwalk_k3s1_flip" : "nhwc_rowwalk_k5s1_flip");
         } else if (V && k3s2p1(g)) {
-            pl.variant = V_NHWC_K3S2; pl.a = V; pl.b = pick_th(g.Ho, 2, 14, 4);
+            pl.variant = V_NHWC_K3S2; pl.a = V; pl.b = pick_th(g.Ho, (long long)g.N * g.Wo * (g.O / V), 2, 14, 4);
             pl.name = "nhwc_rowwalk_bwd_data_k3s2";
         } else plan_any(g, 1, pl);
     }
