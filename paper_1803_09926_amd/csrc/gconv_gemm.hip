@@ -115,7 +115,7 @@ __device__ __forceinline__ bool stage_pixels(const T *__restrict__ in, T *lx, in
                 const bool ok = locate(pix, n, h, w) && i < total && c < C;
                 at[b] = i < total ? pix * pitch + v * VE : -1;
                 q[b] = u4v_t{0u, 0u, 0u, 0u};
-                if (ok) q[b] = *reinterpret_cast<const u4v_t *>(in + (((size_t)n * H + h) * W + w) * C + c);
+                if (ok) q[b] = *reinterpret_cast<const u4v_t *>(in + (unsigned)(((n * H + h) * W + w) * C + c));
             }
 #pragma unroll
             for (int b = 0; b < B; ++b) {
@@ -135,7 +135,7 @@ __device__ __forceinline__ bool stage_pixels(const T *__restrict__ in, T *lx, in
         constexpr int B = 2;
         const int nq = CL / 4, nr = (W + 3) / 4, rows = nimg * LH, total = nr * rows * nq;
         const float rnr = 1.0f / (float)nr, rrows = 1.0f / (float)rows;
-        const size_t end = (size_t)N * C * H * W;
+        const unsigned end = (unsigned)(N * C * H * W), plane = (unsigned)(H * W);
         for (int i0 = threadIdx.x; i0 < total; i0 += B * 256) {
             T e[B][4][4];
             int at[B], len[B], col[B];
@@ -147,14 +147,14 @@ __device__ __forceinline__ bool stage_pixels(const T *__restrict__ in, T *lx, in
                 col[b] = run * 4 - w0;
                 at[b] = (r * LW + col[b]) * pitch + qd * 4;
                 len[b] = i < total ? min(4, W - run * 4) : 0;
-                const size_t p0 = (((size_t)n * C + c) * H + h) * W + run * 4;
+                const unsigned p0 = (unsigned)(((n * C + c) * H + h) * W + run * 4);
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
 #pragma unroll
                     for (int j = 0; j < 4; ++j) e[b][k][j] = T(0);
                     if (ok && c + k < C) {
-                        const T *p = in + p0 + (size_t)k * H * W;
-                        if (p0 + (size_t)k * H * W + 4 <= end) __builtin_memcpy(e[b][k], p, 4 * sizeof(T));      // any alignment
+                        const T *p = in + p0 + k * plane;
+                        if (p0 + k * plane + 4 <= end) __builtin_memcpy(e[b][k], p, 4 * sizeof(T));      // any alignment
                         else {
 #pragma unroll
                             for (int j = 0; j < 4; ++j) if (j < len[b]) e[b][k][j] = p[j];
@@ -194,7 +194,7 @@ __device__ __forceinline__ bool stage_pixels(const T *__restrict__ in, T *lx, in
             int n, h, w;
             const bool ok = locate(pix, n, h, w) && i < total;
             at[b] = i < total ? pix * pitch + c - ca : -1;
-            const T *p = in + (NHWC ? (((size_t)n * H + h) * W + w) * C + c : (((size_t)n * C + c) * H + h) * W + w);
+            const T *p = in + (unsigned)(NHWC ? ((n * H + h) * W + w) * C + c : ((n * C + c) * H + h) * W + w);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 e[b][k] = T(0);
@@ -267,8 +267,10 @@ __global__ __launch_bounds__(256) void k_gconv_gemm(GemmGeom g, const T *__restr
     T *lx = reinterpret_cast<T *>(lw + (size_t)g.NS * KK * g.nk * 64);
     const int npos = g.TN * g.TA * g.TB, npt = (npos + 15) / 16;
 
-    // the filter entries in operand order, WB fragments of a lane loaded at a time
-    constexpr int WB = 4;
+    // the filter entries in operand order, WB fragments of a lane loaded at a time; the first ones (all of a 3x3
+    // filter with up to 16 input channels a group) are on their way while the first tile is staged (NHWC: 14x14
+    // 16 channels a group 14.4 -> 13.3 us; in NCHW the registers they take cost a wavefront per SIMD: 57x57 bf16 67 -> 74)
+    constexpr int WB = 3;
     const int nfrag = g.NS * KK * g.nk * 64;
     auto load_filter = [&](int i0, T (&e)[WB][4]) {
 #pragma unroll
@@ -282,7 +284,7 @@ __global__ __launch_bounds__(256) void k_gconv_gemm(GemmGeom g, const T *__restr
                 const int c = c0 + k;
                 const int fo = g.bwd ? c : o, fc = g.bwd ? o - grp * g.Cgo : c - cg0;
                 e[b][k] = T(0);
-                if (c >= cg0 && c < cg1) e[b][k] = NHWC ? w[((size_t)tap * g.FCg + fc) * g.FO + fo] : w[((size_t)fo * g.FCg + fc) * KK + tap];
+                if (c >= cg0 && c < cg1) e[b][k] = w[(unsigned)(NHWC ? (tap * g.FCg + fc) * g.FO + fo : (fo * g.FCg + fc) * KK + tap)];
             }
         }
     };
@@ -295,11 +297,14 @@ __global__ __launch_bounds__(256) void k_gconv_gemm(GemmGeom g, const T *__restr
             else lw[i].v = make_uint2((uint32_t)e[b][0] | (uint32_t)e[b][1] << 16, (uint32_t)e[b][2] | (uint32_t)e[b][3] << 16);
         }
     };
-    for (int i0 = threadIdx.x; i0 < nfrag; i0 += WB * 256) {
-        T e[WB][4];
-        load_filter(i0, e);
-        put_filter(i0, e);
-    }
+    [[maybe_unused]] T wfirst[WB][4];
+    if constexpr (NHWC) load_filter(threadIdx.x, wfirst);
+    else
+        for (int i0 = threadIdx.x; i0 < nfrag; i0 += WB * 256) {
+            T e[WB][4];
+            load_filter(i0, e);
+            put_filter(i0, e);
+        }
 
     if (!NHWC && FAST)
         for (int i = threadIdx.x; i < g.TN * g.LH * g.LW * g.pitch / VE; i += 256) reinterpret_cast<u4v_t *>(lx)[i] = u4v_t{0u, 0u, 0u, 0u};
@@ -310,6 +315,14 @@ __global__ __launch_bounds__(256) void k_gconv_gemm(GemmGeom g, const T *__restr
         __syncthreads();                                     // the previous tile has been read (first: nothing to wait for)
         bool bad = stage_pixels<T, NHWC, FAST>(in, lx, g.N, g.CI, g.Hi, g.Wi, n0, g.TN, g.IS * a0 - g.ip + g.lo, g.IS * b0 - g.ip + g.lo,
                                          g.LH, g.LW, ca, g.CL, g.pitch, g.packed != 0);
+        if (NHWC && tile == part) {
+            put_filter(threadIdx.x, wfirst);
+            for (int i0 = threadIdx.x + WB * 256; i0 < nfrag; i0 += WB * 256) {
+                T e[WB][4];
+                load_filter(i0, e);
+                put_filter(i0, e);
+            }
+        }
         if (g.packed) bad = __syncthreads_or(bad); else { __syncthreads(); bad = false; }
 
         if (__builtin_expect(bad, 0)) {
@@ -359,7 +372,7 @@ __global__ __launch_bounds__(256) void k_gconv_gemm(GemmGeom g, const T *__restr
                     const int row = row0[p] + f, col = col0[p] + e;
                     if (img[p] >= g.N || (unsigned)row >= (unsigned)g.Ho || (unsigned)col >= (unsigned)g.Wo || o >= g.CO) continue;
                     if constexpr (NHWC) {
-                        T *po = out + (((size_t)img[p] * g.Ho + row) * g.Wo + col) * g.CO + o;
+                        T *po = out + (unsigned)(((img[p] * g.Ho + row) * g.Wo + col) * g.CO + o);
                         const float r[4] = {acc[p][0], acc[p][1], acc[p][2], acc[p][3]};
                         if (g.CO % 4 == 0) Vec<T, 4>::store(po, r);
                         else {
@@ -367,9 +380,9 @@ __global__ __launch_bounds__(256) void k_gconv_gemm(GemmGeom g, const T *__restr
                             for (int k = 0; k < 4; ++k) if (o + k < g.CO) stf(po + k, r[k]);
                         }
                     } else {
-                        T *po = out + (((size_t)img[p] * g.CO + o) * g.Ho + row) * g.Wo + col;
+                        T *po = out + (unsigned)(((img[p] * g.CO + o) * g.Ho + row) * g.Wo + col);
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) if (o + k < g.CO) stf(po + (size_t)k * g.Ho * g.Wo, acc[p][k]);
+                        for (int k = 0; k < 4; ++k) if (o + k < g.CO) stf(po + (unsigned)(k * g.Ho * g.Wo), acc[p][k]);
                     }
                 }
             }
@@ -449,9 +462,11 @@ __global__ __launch_bounds__(256) void k_gconv_gemm_filter(GemmGeom g, const T *
     for (int r = 0; r < 4; ++r) {
         const int ci = c0 + r;
         if ((unsigned)ci >= (unsigned)g.Cgi) continue;
+        // (consecutive entries of a lane through one pointer, so that their stores merge)
+        float *q = dst + (unsigned)(NHWC ? ci * g.FO + o : (o * g.FCg + ci) * KK);
+        const unsigned tstep = NHWC ? (unsigned)(g.FCg * g.FO) : 1u;
 #pragma unroll
-        for (int t = 0; t < KK; ++t)
-            dst[NHWC ? ((size_t)t * g.FCg + ci) * g.FO + o : ((size_t)o * g.FCg + ci) * KK + t] = acc[t][r];
+        for (int t = 0; t < KK; ++t) q[NHWC ? t * tstep : t] = acc[t][r];
     }
 }
 
