@@ -4,7 +4,7 @@
 // Rows of 19, 37 or 74 elements are no whole number of 16-byte vectors, but a run of rows of a plane is one flat range of
 // memory, and so is a run of whole planes.  A block takes U planes and a band of TR output rows of each: the input rows go to
 // LDS as flat ranges in memory order (16 bytes per lane straight into LDS, `dma_range`: no register, no wait before
-// the block's barrier), a lane owns one output column of one plane and walks down the band, and the outputs leave through a
+// the block's barrier), a lane owns one output column (or two) of one plane and walks down the band, and the outputs leave through a
 // second LDS area as flat 16-byte streaming stores.  Every lane of the block is in the same row at the same time, so what
 // depends on the row (padding above and below, the first and last steps of the walk) is scalar; padding to the left and
 // right is one select per value read.  A step reads K values of one input row (consecutive lanes consecutive words: no bank
@@ -97,7 +97,7 @@ struct FlatTile {
 // A value read beside the row (padding) is cleared by its lane's mask: a select would let the compiler branch around the read.
 __device__ __forceinline__ float masked(float f, uint32_t m) { return __uint_as_float(__float_as_uint(f) & m); }
 
-constexpr int GUARD = 8;   // LDS elements in front of and behind the input area that an edge lane may read (and drop)
+constexpr int GUARD = 16;  // LDS elements in front of and behind the input area that an edge lane may read (and drop)
 
 }  // namespace
 
@@ -106,7 +106,7 @@ constexpr int GUARD = 8;   // LDS elements in front of and behind the input area
 // Forward: M = 1, mdiv = the multiplier.  Input gradient of a stride-1 layer (flip): in = dy, filters rotated by 180
 // degrees, pad = K - 1 - p, M = the multiplier.
 // ---------------------------------------------------------------------------------------------
-template <typename T, int K, int S, int M, bool SAME>
+template <typename T, int K, int S, int M, bool SAME, int NC>
 __global__ __launch_bounds__(512) void k_nchwf_conv(const T *__restrict__ in, const T *__restrict__ w, T *__restrict__ out,
                                                     int nplanes, int OC, int Hi, int Wi, int Ho, int Wo, int pad, int mdiv,
                                                     int total_in, int flip, FlatTile ft, unsigned nblocks, int nt)
@@ -124,13 +124,15 @@ __global__ __launch_bounds__(512) void k_nchwf_conv(const T *__restrict__ in, co
     T *lin = reinterpret_cast<T *>(smem) + GUARD, *lout = lin + ft.nin + GUARD;
     dma_bands<T>(in, total_in, bi, lin);
 
-    const int u = (int)threadIdx.x / Wo, ow = (int)threadIdx.x - u * Wo;
+    constexpr int VW = S * (NC - 1) + K;                   // values of an input row that the lane's NC columns reach
+    const int ncol = (Wo + NC - 1) / NC;
+    const int u = (int)threadIdx.x / ncol, ow = ((int)threadIdx.x - u * ncol) * NC;
     const bool active = u < np;
     const int pl = p0 + (active ? u : 0), oc = pl % OC;
-    uint32_t ok[K];
+    uint32_t ok[VW];
 #pragma unroll
-    for (int kw = 0; kw < K; ++kw) ok[kw] = (unsigned)(ow * S - pad + kw) < (unsigned)Wi ? ~0u : 0u;
-    const int col0 = min(max(ow * S - pad, -K), Wi);       // a column further out has every tap dropped anyway
+    for (int i = 0; i < VW; ++i) ok[i] = (unsigned)(ow * S - pad + i) < (unsigned)Wi ? ~0u : 0u;
+    const int col0 = min(max(ow * S - pad, -VW), Wi);      // a column further out has every tap dropped anyway
     float wr[M][K][K];
     int src[M];                                            // LDS element of (plane, row r0, column col0)
 #pragma unroll
@@ -144,12 +146,19 @@ __global__ __launch_bounds__(512) void k_nchwf_conv(const T *__restrict__ in, co
             }
         src[q] = bi.at<T>((M > 1 ? pl * M + q : pl / mdiv) - ip0) + col0;
     }
-    // a lane without a column writes its sums to the guard elements in front of the output area: no lane mask in the walk
-    int dst = active ? bo.at<T>(u) + ow : -1;
-    const int dstep = active ? Wo : 0;
-    float acc[NA];
+    // a column that is none writes its sums to the guard elements in front of the output area: no lane mask in the walk
+    int dst[NC], dstep[NC];
 #pragma unroll
-    for (int i = 0; i < NA; ++i) acc[i] = 0.f;
+    for (int n = 0; n < NC; ++n) {
+        const bool mine = active && ow + n < Wo;
+        dst[n] = mine ? bo.at<T>(u) + ow + n : -1;
+        dstep[n] = mine ? Wo : 0;
+    }
+    float acc[NA][NC];
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int n = 0; n < NC; ++n) acc[i][n] = 0.f;
     dma_wait();
     __syncthreads();
 
@@ -166,24 +175,32 @@ __global__ __launch_bounds__(512) void k_nchwf_conv(const T *__restrict__ in, co
 #pragma unroll
             for (int q = 0; q < M; ++q) {
                 const T *p = lin + src[q] + row * Wi;
-                float v[K];
+                float v[VW];
 #pragma unroll
-                for (int kw = 0; kw < K; ++kw) {
-                    const float f = ldf(p + kw);
-                    v[kw] = SAME && kw == K / 2 ? f : masked(f, ok[kw]);      // the centre tap is never outside
+                for (int i = 0; i < VW; ++i) {
+                    const float f = ldf(p + i);
+                    v[i] = SAME && NC == 1 && i == K / 2 ? f : masked(f, ok[i]);      // the centre tap is never outside
                 }
 #pragma unroll
                 for (int i = 0; i < NA; ++i) {
                     if (j + i * S >= K || (CK && K > 3 && (unsigned)(t - i) >= (unsigned)TRb)) continue;
 #pragma unroll
-                    for (int kw = 0; kw < K; ++kw) acc[i] = fmaf(wr[q][j + i * S][kw], v[kw], acc[i]);
+                    for (int kw = 0; kw < K; ++kw)
+#pragma unroll
+                        for (int n = 0; n < NC; ++n) acc[i][n] = fmaf(wr[q][j + i * S][kw], v[n * S + kw], acc[i][n]);
                 }
             }
         }
-        if (!CK || t >= NA - 1) { stf(lout + dst, acc[NA - 1]); dst += dstep; }
+        if (!CK || t >= NA - 1) {
 #pragma unroll
-        for (int i = NA - 1; i > 0; --i) acc[i] = acc[i - 1];
-        acc[0] = 0.f;
+            for (int n = 0; n < NC; ++n) { stf(lout + dst[n], acc[NA - 1][n]); dst[n] += dstep[n]; }
+        }
+#pragma unroll
+        for (int i = NA - 1; i > 0; --i)
+#pragma unroll
+            for (int n = 0; n < NC; ++n) acc[i][n] = acc[i - 1][n];
+#pragma unroll
+        for (int n = 0; n < NC; ++n) acc[0][n] = 0.f;
     };
     const int steps = TRb + NA - 1;
     const int ta = (S - 1 - base) / S, tb = min((nrows - base) / S, K > 3 ? TRb : steps);
@@ -302,7 +319,7 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_data_s2(const T *__restrict__
 // lane keeps the K*K sums of its column over all of them against a window of the last K/S dy rows.  The columns of a
 // channel are added through LDS in a fixed order at the end, one partial per block.
 // ---------------------------------------------------------------------------------------------
-template <typename T, int K, int S, bool SAME>
+template <typename T, int K, int S, bool SAME, int NC>
 __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__restrict__ x, const T *__restrict__ dy,
                                                           float *__restrict__ ws, int parts, int per_part, FlatTile ft,
                                                           unsigned nblocks)
@@ -313,13 +330,19 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__res
     const int part = (int)(lb % (unsigned)parts), o0 = (int)(lb / (unsigned)parts) * ft.U;
     const int np = min(ft.U, g.O - o0);
     const int c0 = o0 / g.m, c1 = (o0 + np - 1) / g.m + 1;
-    const int u = (int)threadIdx.x / g.Wo, ow = (int)threadIdx.x - u * g.Wo;
+    constexpr int VW = S * (NC - 1) + K;
+    const int ncol = (g.Wo + NC - 1) / NC;
+    const int u = (int)threadIdx.x / ncol, ow = ((int)threadIdx.x - u * ncol) * NC;
     const bool active = u < np;
     const int uu = active ? u : 0, ju = (o0 + uu) / g.m - c0;
-    uint32_t ok[K];
+    uint32_t ok[VW];
 #pragma unroll
-    for (int kw = 0; kw < K; ++kw) ok[kw] = (unsigned)(ow * S - g.p + kw) < (unsigned)g.W ? ~0u : 0u;
-    const int col0 = min(max(ow * S - g.p, -K), g.W), owc = active ? ow : 0;
+    for (int i = 0; i < VW; ++i) ok[i] = (unsigned)(ow * S - g.p + i) < (unsigned)g.W ? ~0u : 0u;
+    // the dy columns of the lane; the last lane of a row may have one that is none
+    uint32_t okd[NC];
+#pragma unroll
+    for (int n = 0; n < NC; ++n) okd[n] = ow + n < g.Wo ? ~0u : 0u;
+    const int col0 = min(max(ow * S - g.p, -VW), g.W), owc = active ? ow : 0;
     T *lx = reinterpret_cast<T *>(smem) + GUARD, *ldy = lx + ft.nin + GUARD;
     float acc[K][K];
 #pragma unroll
@@ -337,9 +360,11 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__res
         dma_bands<T>(x, g.N * g.C * g.H * g.W, bx, lx);
         dma_bands<T>(dy, g.N * g.O * g.Ho * g.Wo, by, ldy);
         const T *px = lx + bx.at<T>(ju) + col0, *pd = ldy + by.at<T>(uu) + owc;
-        float d[NA];
+        float d[NA][NC];
 #pragma unroll
-        for (int i = 0; i < NA; ++i) d[i] = 0.f;
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+            for (int n = 0; n < NC; ++n) d[i][n] = 0.f;
         dma_wait();
         __syncthreads();
         // step t: the S x rows from row (oh0 + t)*S - p on, against dy rows oh0 + t - i; steps [ta, tb) have all of them in the band
@@ -347,27 +372,35 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__res
         const int base = oh0 * S - g.p - r0, nrows = r1 - r0;
         auto step = [&](int t, auto checked) {
             constexpr bool CK = decltype(checked)::value;
-            d[0] = !CK || t < rows ? ldf(pd + t * g.Wo) : 0.f;
+#pragma unroll
+            for (int n = 0; n < NC; ++n) {
+                d[0][n] = !CK || t < rows ? ldf(pd + t * g.Wo + n) : 0.f;
+                if (n > 0) d[0][n] = masked(d[0][n], okd[n]);
+            }
 #pragma unroll
             for (int j = 0; j < S; ++j) {
                 const int row = base + t * S + j;
                 if (CK && (row < 0 || row >= nrows)) continue;
                 const T *p = px + row * g.W;
-                float v[K];
+                float v[VW];
 #pragma unroll
-                for (int kw = 0; kw < K; ++kw) {
-                    const float e = ldf(p + kw);
-                    v[kw] = SAME && kw == K / 2 ? e : masked(e, ok[kw]);
+                for (int i = 0; i < VW; ++i) {
+                    const float e = ldf(p + i);
+                    v[i] = SAME && NC == 1 && i == K / 2 ? e : masked(e, ok[i]);
                 }
 #pragma unroll
                 for (int i = 0; i < NA; ++i) {
                     if (j + i * S >= K || (CK && K > 3 && (unsigned)(t - i) >= (unsigned)rows)) continue;
 #pragma unroll
-                    for (int kw = 0; kw < K; ++kw) acc[j + i * S][kw] = fmaf(d[i], v[kw], acc[j + i * S][kw]);
+                    for (int kw = 0; kw < K; ++kw)
+#pragma unroll
+                        for (int n = 0; n < NC; ++n) acc[j + i * S][kw] = fmaf(d[i][n], v[n * S + kw], acc[j + i * S][kw]);
                 }
             }
 #pragma unroll
-            for (int i = NA - 1; i > 0; --i) d[i] = d[i - 1];
+            for (int i = NA - 1; i > 0; --i)
+#pragma unroll
+                for (int n = 0; n < NC; ++n) d[i][n] = d[i - 1][n];
         };
         const int ta = (S - 1 - base) / S, tb = min((nrows - base) / S, rows);
         int t = 0;
@@ -379,7 +412,7 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__res
     }
 
     // CH sums at a time (all of them up to 5x5): [CH][threads] in LDS, then Q lanes per (channel, tap) add every Q-th column
-    const int Q = g.Wo < 16 ? 1 : g.Wo < 64 ? 4 : 8;
+    const int Q = ncol < 16 ? 1 : ncol < 64 ? 4 : 8;
     constexpr int CH = K * K <= 25 ? K * K : 25;
     float *red = reinterpret_cast<float *>(smem);
     const int J = g.O * K * K, nt = blockDim.x;
@@ -396,7 +429,7 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__res
             const int uj = job / ne, e = job - uj * ne;
             float s = 0.f;
             if (job < jobs)
-                for (int i = q; i < g.Wo; i += Q) s += red[e * nt + uj * g.Wo + i];
+                for (int i = q; i < ncol; i += Q) s += red[e * nt + uj * ncol + i];
             for (int h = Q >> 1; h >= 1; h >>= 1) s += __shfl_xor(s, h, 64);
             if (job < jobs && q == 0) ws[(size_t)part * J + (o0 + uj) * K * K + e0 + e] = s;
         }
@@ -494,13 +527,19 @@ int most_planes(long long planes, int rows, int cols)
 
 bool flat_k(const Geom &g) { return (g.K == 3 || g.K == 5 || g.K == 7) && (g.s == 1 || g.s == 2); }
 
+// Output columns per lane of the forward kernel and the filter gradient: two for 5x5 and 7x7 in bf16, whose K values a row and
+// column are 16-bit LDS reads that have to be widened (28x28x256 7x7 batch 64: forward 35 -> 32 us, filter gradient 47 -> 42;
+// 56x56x128 5x5 stride 2: 35 -> 30 and 42 -> 32).  In fp32 half the lanes per LDS byte cost more than the shared reads give
+// (40 -> 52 us).
+int flat_cols(const Geom &g, int dtype) { return g.K > 3 && dtype == DT_BF16 ? 2 : 1; }
+
 bool conv_tile(const Geom &g, int dtype, bool bwd, FlatTile *ft)
 {
-    const int esz = dtype == DT_F32 ? 4 : 2, K = g.K, S = g.s;
+    const int esz = dtype == DT_F32 ? 4 : 2, K = g.K, S = g.s, nc = flat_cols(g, dtype);
     auto in_rows = [&](int t) { return (t - 1) * S + K; };
     auto out_rows = [&](int t) { return t; };
-    if (!bwd) return pick_tile(esz, g.Wo, g.Ho, g.N * g.O, most_planes((long long)g.N * g.O, g.Ho, g.Wo), g.H, g.W, g.Ho, g.Wo, in_rows, out_rows, 1, g.m, lds_target(K), ft);
-    return pick_tile(esz, g.W, g.H, g.N * g.C, most_planes((long long)g.N * g.C, g.H, g.W), g.Ho, g.Wo, g.H, g.W, in_rows, out_rows, g.m, 1, lds_target(K), ft);
+    if (!bwd) return pick_tile(esz, (g.Wo + nc - 1) / nc, g.Ho, g.N * g.O, most_planes((long long)g.N * g.O, g.Ho, (g.Wo + nc - 1) / nc), g.H, g.W, g.Ho, g.Wo, in_rows, out_rows, 1, g.m, lds_target(K), ft);
+    return pick_tile(esz, (g.W + nc - 1) / nc, g.H, g.N * g.C, most_planes((long long)g.N * g.C, g.H, (g.W + nc - 1) / nc), g.Ho, g.Wo, g.H, g.W, in_rows, out_rows, g.m, 1, lds_target(K), ft);
 }
 
 int s2_cols(const Geom &g) { return (g.W - 1 + g.p) / 2 - g.p / 2 + 1; }
@@ -514,10 +553,10 @@ bool s2_tile(const Geom &g, int dtype, FlatTile *ft)
 }
 bool filter_tile(const Geom &g, int dtype, FlatTile *ft)
 {
-    const int esz = dtype == DT_F32 ? 4 : 2, K = g.K, S = g.s;
+    const int esz = dtype == DT_F32 ? 4 : 2, K = g.K, S = g.s, nc = flat_cols(g, dtype);
     auto in_rows = [&](int t) { return (t - 1) * S + K; };
     auto out_rows = [&](int t) { return t; };
-    return pick_tile(esz, g.Wo, g.Ho, g.O, most_planes((long long)g.N * g.O, g.Ho, g.Wo), g.H, g.W, g.Ho, g.Wo, in_rows, out_rows, 1, g.m, lds_target(K), ft);
+    return pick_tile(esz, (g.Wo + nc - 1) / nc, g.Ho, g.O, most_planes((long long)g.N * g.O, g.Ho, (g.Wo + nc - 1) / nc), g.H, g.W, g.Ho, g.Wo, in_rows, out_rows, 1, g.m, lds_target(K), ft);
 }
 
 }  // namespace
@@ -562,7 +601,8 @@ static hipError_t conv_go(const Geom &g, int dtype, const void *in, const void *
     const int total_in = g.N * (bwd ? g.O : g.C) * Hi * Wi;
     const int nt = stream_stores("NCHWF", 0, 0);
     const bool same = (bwd ? K - 1 - g.p : g.p) == K / 2;
-    auto kernel = same ? k_nchwf_conv<T, K, S, M, true> : k_nchwf_conv<T, K, S, M, false>;
+    auto kernel = same ? k_nchwf_conv<T, K, S, M, true, 1> : k_nchwf_conv<T, K, S, M, false, 1>;
+    if constexpr (K > 3 && sizeof(T) == 2) { if (flat_cols(g, dtype) == 2) kernel = same ? k_nchwf_conv<T, K, S, M, true, 2> : k_nchwf_conv<T, K, S, M, false, 2>; }
     hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(ft.threads), tile_lds(ft, sizeof(T), Ho, Wo), st, (const T *)in, (const T *)w,
                         (T *)out, nplanes, OC, Hi, Wi, Ho, Wo, bwd ? K - 1 - g.p : g.p, bwd ? 1 : g.m, total_in,
                        bwd ? 1 : 0, ft, nblocks, nt);
@@ -591,7 +631,8 @@ static hipError_t filter_go(const Geom &g, int dtype, const void *x, const void 
     size_t lds = tile_lds(ft, sizeof(T), g.Ho, g.Wo);
     const size_t red = (size_t)(K * K <= 25 ? K * K : 25) * ft.threads * 4;
     if (red > lds) lds = red;
-    auto kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true> : k_nchwf_bwd_filter<T, K, S, false>;
+    auto kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, 1> : k_nchwf_bwd_filter<T, K, S, false, 1>;
+    if constexpr (K > 3 && sizeof(T) == 2) { if (flat_cols(g, dtype) == 2) kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, 2> : k_nchwf_bwd_filter<T, K, S, false, 2>; }
     hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(ft.threads), lds, st, g, (const T *)x, (const T *)dy, ws, parts,
                        per, ft, nblocks);
     return hipGetLastError();

@@ -31,6 +31,9 @@ CASES = [
     (4, Layer("k7_pad1", 24, 30, 29, 7, 1, 1)),
     (3, Layer("k7_s2", 24, 57, 31, 7, 2, 3)),
     (2, Layer("k7_large", 16, 60, 59, 7, 1, 3)),
+    (2, Layer("k5_row_of_one", 9, 31, 1, 5, 1, 2)),                    # bf16: the second column of the only lane is none
+    (2, Layer("k7_s2_even", 10, 32, 30, 7, 2, 3)),                     # 15 outputs a row: 8 lanes of two columns, the last half used
+    (1, Layer("k5_wide_rows", 3, 9, 511, 5, 1, 2)),
     (2, Layer("m2", 10, 37, 37, 3, 1, 1, 2)),                          # output planes 2c and 2c + 1 read input plane c
     (2, Layer("m2_k5_s2", 10, 29, 31, 5, 2, 2, 2)),
     (2, Layer("m3", 7, 23, 22, 3, 1, 1, 3)),
