@@ -216,7 +216,8 @@ __device__ __forceinline__ bool stage_pixels(const T *__restrict__ in, T *lx, in
     return bad;
 }
 
-// A tile that holds an infinity or NaN, where 16 outputs span several groups: one output per lane, its own group's channels only.
+// A tile that holds an infinity or NaN where 16 outputs span several groups, or whose filter does: one output per lane, its own
+// group's channels and the taps inside the image only.
 template <typename T, bool NHWC>
 __device__ __forceinline__ void own_group_only(const GemmGeom &g, const Frag<T> *lw, const T *lx, T *__restrict__ out, int n0, int a0,
                                                          int b0, int ob, int ca)
@@ -236,6 +237,7 @@ __device__ __forceinline__ void own_group_only(const GemmGeom &g, const Frag<T> 
 #pragma unroll 1
             for (int kw = e, l = 0; kw < g.K; kw += g.OS, ++l) {
                 const int ro = g.bwd ? -k : kh, co = g.bwd ? -l : kw;
+                if ((unsigned)(g.IS * (a0 + da) - g.ip + ro) >= (unsigned)g.Hi || (unsigned)(g.IS * (b0 + db) - g.ip + co) >= (unsigned)g.Wi) continue;
                 const T *px = lx + ((im * g.LH + g.IS * da + ro - g.lo) * g.LW + g.IS * db + co - g.lo) * g.pitch;
 #pragma unroll 1
                 for (int c = c0; c < c0 + g.Cgi; ++c) {
@@ -288,9 +290,12 @@ __global__ __launch_bounds__(256) void k_gconv_gemm(GemmGeom g, const T *__restr
             }
         }
     };
+    bool wbad = false;
     auto put_filter = [&](int i0, const T (&e)[WB][4]) {
 #pragma unroll
         for (int b = 0; b < WB; ++b) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) wbad |= nonfinite<T>(e[b][k]);
             const int i = i0 + b * 256;
             if (i >= nfrag) continue;
             if constexpr (sizeof(T) == 4) lw[i].v = make_float4(e[b][0], e[b][1], e[b][2], e[b][3]);
@@ -323,7 +328,9 @@ __global__ __launch_bounds__(256) void k_gconv_gemm(GemmGeom g, const T *__restr
                 put_filter(i0, e);
             }
         }
-        if (g.packed) bad = __syncthreads_or(bad); else { __syncthreads(); bad = false; }
+        if (tile == part) wbad = __syncthreads_or(wbad);      // (either is the barrier behind the staging)
+        else if (!g.packed) __syncthreads();
+        bad = wbad || (g.packed && __syncthreads_or(bad));
 
         if (__builtin_expect(bad, 0)) {
             own_group_only<T, NHWC>(g, lw, lx, out, n0, a0, b0, ob, ca);

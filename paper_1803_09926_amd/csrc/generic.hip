@@ -1,22 +1,10 @@
 // Generic fallback kernels: correct for any K, stride, pad and channel multiplier, both layouts,
 // both storage types.  One thread per output element; not tuned.  Also holds the second stage of
 // the filter-gradient reduction, which every bwd_filter variant shares.
-#include "kernels.hpp"
+#include "point.hpp"
 
 namespace dwc {
 
-template <int LAYOUT>
-__device__ __forceinline__ int at(int CH, int HH, int WW, int n, int ch, int h, int w)
-{
-    if (LAYOUT == LAYOUT_NCHW) return ((n * CH + ch) * HH + h) * WW + w;
-    return ((n * HH + h) * WW + w) * CH + ch;
-}
-template <int LAYOUT>
-__device__ __forceinline__ int wat(int O, int K, int o, int kh, int kw)
-{
-    if (LAYOUT == LAYOUT_NCHW) return (o * K + kh) * K + kw;
-    return (kh * K + kw) * O + o;
-}
 // Decompose a flat element index of a [N,CH,HH,WW] / [N,HH,WW,CH] tensor.
 template <int LAYOUT>
 __device__ __forceinline__ void unflat(int idx, int CH, int HH, int WW, int &n, int &ch, int &h, int &w)
@@ -37,18 +25,7 @@ __global__ __launch_bounds__(256) void k_generic_fwd(Geom g, const T *__restrict
     int idx = (int)uidx;
     int n, o, oh, ow;
     unflat<LAYOUT>(idx, g.O, g.Ho, g.Wo, n, o, oh, ow);
-    const int c = o / g.m;
-    float acc = 0.f;
-    for (int kh = 0; kh < g.K; ++kh) {
-        int ih = oh * g.s - g.p + kh;
-        if (ih < 0 || ih >= g.H) continue;
-        for (int kw = 0; kw < g.K; ++kw) {
-            int iw = ow * g.s - g.p + kw;
-            if (iw < 0 || iw >= g.W) continue;
-            acc = fmaf(ldf(w + wat<LAYOUT>(g.O, g.K, o, kh, kw)), ldf(x + at<LAYOUT>(g.C, g.H, g.W, n, c, ih, iw)), acc);
-        }
-    }
-    stf(y + idx, acc);
+    stf(y + idx, point_fwd<T, LAYOUT>(g, x, w, n, o, oh, ow));
 }
 
 template <typename T, int LAYOUT>
@@ -60,25 +37,7 @@ __global__ __launch_bounds__(256) void k_generic_bwd_data(Geom g, const T *__res
     int idx = (int)uidx;
     int n, c, ih, iw;
     unflat<LAYOUT>(idx, g.C, g.H, g.W, n, c, ih, iw);
-    float acc = 0.f;
-    for (int q = 0; q < g.m; ++q) {
-        const int o = c * g.m + q;
-        for (int kh = 0; kh < g.K; ++kh) {
-            int th = ih + g.p - kh;
-            if (th < 0 || th % g.s != 0) continue;
-            int oh = th / g.s;
-            if (oh >= g.Ho) continue;
-            for (int kw = 0; kw < g.K; ++kw) {
-                int tw = iw + g.p - kw;
-                if (tw < 0 || tw % g.s != 0) continue;
-                int ow = tw / g.s;
-                if (ow >= g.Wo) continue;
-                acc = fmaf(ldf(w + wat<LAYOUT>(g.O, g.K, o, kh, kw)),
-                           ldf(dy + at<LAYOUT>(g.O, g.Ho, g.Wo, n, o, oh, ow)), acc);
-            }
-        }
-    }
-    stf(dx + idx, acc);
+    stf(dx + idx, point_bwd_data<T, LAYOUT>(g, dy, w, n, c, ih, iw));
 }
 
 // Stage 1, NCHW: block (tap j = (o*K+kh)*K+kw, part).  Threads stride over the pixels
@@ -143,9 +102,54 @@ __global__ __launch_bounds__(256) void k_generic_bwd_filter_nhwc(Geom g, const T
 // before the first is used, also in the last, partly filled batch (clamped index, value dropped):
 // the kernel is a few microseconds of pure load latency, so one latency per batch is what counts.
 // The batch is added in a fixed tree, then the PT sub-sums in a fixed tree through LDS.
-template <int JT>
+// (see FilterGradSrc; every thread of the block)
+__device__ __forceinline__ float entry_inside(const FilterGradSrc &f, int j, float *red)
+{
+    const bool nhwc = f.layout == LAYOUT_NHWC;
+    const int KK = f.K * f.K, tap = nhwc ? j / (f.Cg * f.O) : j % KK, kh = tap / f.K, kw = tap - kh * f.K;
+    const int o = nhwc ? j % f.O : j / KK / f.Cg, ci = (nhwc ? j / f.O : j / KK) % f.Cg, c = o / f.Og * f.Cg + ci;
+    const int npix = f.N * f.Ho * f.Wo;
+    float acc = 0.f;
+#pragma unroll 1
+    for (int pix = threadIdx.x; pix < npix; pix += 256) {
+        const int ow = pix % f.Wo, t = pix / f.Wo, oh = t % f.Ho, n = t / f.Ho, ih = oh * f.s - f.p + kh, iw = ow * f.s - f.p + kw;
+        if ((unsigned)ih >= (unsigned)f.H || (unsigned)iw >= (unsigned)f.W) continue;
+        const size_t px = nhwc ? ((size_t)(n * f.H + ih) * f.W + iw) * f.C + c : ((size_t)(n * f.C + c) * f.H + ih) * f.W + iw;
+        const size_t py = nhwc ? (size_t)pix * f.O + o : ((size_t)(n * f.O + o) * f.Ho + oh) * f.Wo + ow;
+        acc = f.dtype == DT_F32 ? fmaf(((const float *)f.dy)[py], ((const float *)f.x)[px], acc)
+                                : fmaf(ldf((const bf16_t *)f.dy + py), ldf((const bf16_t *)f.x + px), acc);
+    }
+    acc = wave_sum(acc);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    return (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// total[e]: the block's entries j0 + e < J, in LDS
+template <int JT, bool CHECK>
+__device__ __forceinline__ void store_entries(const FilterGradSrc &src, const float *total, int j0, int J, float *dw)
+{
+    const int t = threadIdx.x;
+    const bool mine = t < JT && j0 + t < J;
+    const float v = t < JT ? total[t] : 0.f;
+    const bool bad = CHECK && mine && !(__builtin_fabsf(v) < __builtin_inff());
+    if (mine && !bad) dw[j0 + t] = v;
+    if constexpr (CHECK) {
+        if (!__syncthreads_or(bad)) return;
+        __shared__ float red[4];
+#pragma unroll 1
+        for (int e = 0; e < JT && j0 + e < J; ++e) {
+            if (__builtin_fabsf(total[e]) < __builtin_inff()) continue;
+            const float s = entry_inside(src, j0 + e, red);
+            if (t == 0) dw[j0 + e] = s;
+        }
+    }
+}
+
+template <int JT, bool CHECK>
 __global__ __launch_bounds__(256) void k_reduce_partials(const float *__restrict__ ws, int parts, int J,
-                                                         float *__restrict__ dw)
+                                                         float *__restrict__ dw, FilterGradSrc src)
 {
     constexpr int PT = 256 / JT;
     __shared__ float red[PT][JT + 1];
@@ -172,13 +176,14 @@ __global__ __launch_bounds__(256) void k_reduce_partials(const float *__restrict
         if (r < half) red[r][jj] += red[r + half][jj];
         __syncthreads();
     }
-    if (r == 0 && j < J) dw[j] = red[0][jj];
+    store_entries<JT, CHECK>(src, red[0], blockIdx.x * JT, J, dw);
 }
 
 // The same for J a multiple of 4: a lane takes four consecutive j, so that a wavefront reads 256 to 1024 consecutive bytes of a
 // partial row instead of 32 to 256; JT / 4 lanes across j, the others across the partials.
-template <int JT>
-__global__ __launch_bounds__(256) void k_reduce_partials4(const float *__restrict__ ws, int parts, int J, float *__restrict__ dw)
+template <int JT, bool CHECK>
+__global__ __launch_bounds__(256) void k_reduce_partials4(const float *__restrict__ ws, int parts, int J, float *__restrict__ dw,
+                                                          FilterGradSrc src)
 {
     constexpr int JL = JT / 4, PT = 256 / JL;
     __shared__ float4 red[PT][JL];
@@ -205,7 +210,8 @@ __global__ __launch_bounds__(256) void k_reduce_partials4(const float *__restric
         if (r < half) red[r][jj] = add(red[r][jj], red[r + half][jj]);
         __syncthreads();
     }
-    if (r == 0 && j < J) *reinterpret_cast<float4 *>(dw + j) = red[0][jj];
+    if constexpr (CHECK) store_entries<JT, true>(src, &red[0][0].x, blockIdx.x * JT, J, dw);
+    else if (r == 0 && j < J) *reinterpret_cast<float4 *>(dw + j) = red[0][jj];
 }
 
 // ---- host side --------------------------------------------------------------------------------
@@ -265,7 +271,8 @@ hipError_t generic_bwd_filter(const Geom &g, int layout, int dtype, const void *
     return hipGetLastError();
 }
 
-hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, hipStream_t st)
+template <bool CHECK>
+static hipError_t reduce_go(const float *ws, int parts, int J, float *dw, const FilterGradSrc &src, hipStream_t st)
 {
     // threads per output chosen so that one batch of eight loads per thread covers the partials
     // (PT = 256/JT about parts/8), but enough blocks to spread small J over the chip
@@ -274,7 +281,7 @@ hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, hipStre
     if (J % 4 == 0 && J >= 2048) {
         int jt = 16;
         while (jt < 64 && (256 / (jt / 4)) * 8 > parts && (J + 2 * jt - 1) / (2 * jt) >= 128) jt *= 2;
-#define GO(JT) hipLaunchKernelGGL(k_reduce_partials4<JT>, dim3((J + JT - 1) / JT), dim3(256), 0, st, ws, parts, J, dw)
+#define GO(JT) hipLaunchKernelGGL((k_reduce_partials4<JT, CHECK>), dim3((J + JT - 1) / JT), dim3(256), 0, st, ws, parts, J, dw, src)
         if (jt == 16) GO(16);
         else if (jt == 32) GO(32);
         else GO(64);
@@ -283,7 +290,7 @@ hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, hipStre
     }
     int jt = 4;
     while (jt < 64 && (256 / jt) * 8 > parts && (J + 2 * jt - 1) / (2 * jt) >= 8) jt *= 2;
-#define GO(JT) hipLaunchKernelGGL(k_reduce_partials<JT>, dim3((J + JT - 1) / JT), dim3(256), 0, st, ws, parts, J, dw)
+#define GO(JT) hipLaunchKernelGGL((k_reduce_partials<JT, CHECK>), dim3((J + JT - 1) / JT), dim3(256), 0, st, ws, parts, J, dw, src)
     switch (jt) {
     case 4: GO(4); break;
     case 8: GO(8); break;
@@ -293,6 +300,15 @@ hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, hipStre
     }
 #undef GO
     return hipGetLastError();
+}
+
+hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, hipStream_t st)
+{
+    return reduce_go<false>(ws, parts, J, dw, FilterGradSrc{}, st);
+}
+hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, const FilterGradSrc &src, hipStream_t st)
+{
+    return reduce_go<true>(ws, parts, J, dw, src, st);
 }
 
 }  // namespace dwc

@@ -39,6 +39,13 @@ hipError_t generic_bwd_filter(const Geom &g, int layout, int dtype, const void *
 // ---- second stage of the filter-gradient reduction (generic.hip) ----------------------------
 // dw[j] = sum_{p < parts} ws[p*J + j], j < J, added in a fixed order.
 hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, hipStream_t st);
+// The same where stage 1 multiplies dy with the zeros of the padding: an entry that comes out as an infinity or NaN is added up again
+// from the products inside the image.  Depthwise: Cg = 1, Og = the multiplier.
+struct FilterGradSrc {
+    const void *x, *dy;
+    int dtype, layout, N, C, H, W, K, s, p, O, Cg, Og, Ho, Wo;
+};
+hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, const FilterGradSrc &src, hipStream_t st);
 
 // ---- NHWC row-walk kernels, multiplier 1 (nhwc.hip) ------------------------------------------
 // V = channels per lane (4 for fp32; 8 or 4 for bf16), TH = rows per strip.

@@ -10,7 +10,7 @@
 // right is one select per value read.  A step reads K values of one input row (consecutive lanes consecutive words: no bank
 // conflict) for K*K multiply-adds.  Every block is short; several blocks per compute unit overlap one's loads with
 // another's arithmetic.
-#include "kernels.hpp"
+#include "point.hpp"
 #include <type_traits>
 
 namespace dwc {
@@ -109,7 +109,7 @@ constexpr int GUARD = 16;  // LDS elements in front of and behind the input area
 template <typename T, int K, int S, int M, bool SAME, int NC>
 __global__ __launch_bounds__(512) void k_nchwf_conv(const T *__restrict__ in, const T *__restrict__ w, T *__restrict__ out,
                                                     int nplanes, int OC, int Hi, int Wi, int Ho, int Wo, int pad, int mdiv,
-                                                    int total_in, int flip, FlatTile ft, unsigned nblocks, int nt)
+                                                    int total_in, int flip, FlatTile ft, unsigned nblocks, int nt, Geom g)
 {
     extern __shared__ uint4 smem[];
     constexpr int NA = (K + S - 1) / S;
@@ -159,6 +159,12 @@ __global__ __launch_bounds__(512) void k_nchwf_conv(const T *__restrict__ in, co
     for (int i = 0; i < NA; ++i)
 #pragma unroll
         for (int n = 0; n < NC; ++n) acc[i][n] = 0.f;
+    NonFinite bad;
+#pragma unroll
+    for (int q = 0; q < M; ++q)
+#pragma unroll
+        for (int e = 0; e < K * K; ++e) bad.add(wr[q][e / K][e % K]);
+    const bool redo = bad.any() && active;
     dma_wait();
     __syncthreads();
 
@@ -209,6 +215,16 @@ __global__ __launch_bounds__(512) void k_nchwf_conv(const T *__restrict__ in, co
 #pragma unroll NA
     for (; t < tb; ++t) step(t, std::false_type());
     for (; t < steps; ++t) step(t, std::true_type());
+    if (__builtin_expect(redo, 0)) {          // the lane's columns again, without the padding
+        const int n = pl / OC;
+#pragma unroll 1
+        for (int i = 0; i < TRb * NC; ++i) {
+            const int t = i / NC, c = ow + i - t * NC;
+            if (c < Wo)
+                stf(lout + bo.at<T>(u) + t * Wo + c, flip ? point_bwd_data<T, LAYOUT_NCHW>(g, in, w, n, oc, oh0 + t, c)
+                                                          : point_fwd<T, LAYOUT_NCHW>(g, in, w, n, oc, oh0 + t, c));
+        }
+    }
     __syncthreads();
     store_bands<T>(out, bo, lout, nt != 0);
 }
@@ -221,7 +237,7 @@ __global__ __launch_bounds__(512) void k_nchwf_conv(const T *__restrict__ in, co
 template <typename T, int K, int M>
 __global__ __launch_bounds__(512) void k_nchwf_bwd_data_s2(const T *__restrict__ dy, const T *__restrict__ w, T *__restrict__ dx,
                                                            int nplanes, int C, int H, int W, int Ho, int Wo, int pad, int NB,
-                                                           int total_dy, FlatTile ft, unsigned nblocks, int nt)
+                                                           int total_dy, FlatTile ft, unsigned nblocks, int nt, Geom g)
 {
     extern __shared__ uint4 smem[];
     constexpr int NA = (K + 1) / 2;
@@ -262,6 +278,12 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_data_s2(const T *__restrict__
     float acc[NA][2][2];
 #pragma unroll
     for (int k = 0; k < NA; ++k) acc[k][0][0] = acc[k][0][1] = acc[k][1][0] = acc[k][1][1] = 0.f;
+    NonFinite bad;
+#pragma unroll
+    for (int q = 0; q < M; ++q)
+#pragma unroll
+        for (int e = 0; e < K * K; ++e) bad.add(wr[q][e / K][e % K]);
+    const bool redo = bad.any() && active;
     dma_wait();
     __syncthreads();
 
@@ -310,6 +332,14 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_data_s2(const T *__restrict__
     for (; r < rb; ++r) step(r, std::true_type(), std::false_type());
     for (; r < r1; ++r) step(r, std::true_type(), std::true_type());
     for (; r < a1; ++r) step(r, std::false_type(), std::true_type());
+    if (__builtin_expect(redo, 0)) {          // the lane's columns again, without the padding
+        const int n = pl / C;
+#pragma unroll 1
+        for (int i = 0; i < 2 * (h1 - h0); ++i) {
+            const int h = h0 + i / 2, cw = col + i % 2;
+            if ((unsigned)cw < (unsigned)W) stf(lout + bo.at<T>(u) + (h - h0) * W + cw, point_bwd_data<T, LAYOUT_NCHW>(g, dy, w, n, c, h, cw));
+        }
+    }
     __syncthreads();
     store_bands<T>(dx, bo, lout, nt != 0);
 }
@@ -605,7 +635,7 @@ static hipError_t conv_go(const Geom &g, int dtype, const void *in, const void *
     if constexpr (K > 3 && sizeof(T) == 2) { if (flat_cols(g, dtype) == 2) kernel = same ? k_nchwf_conv<T, K, S, M, true, 2> : k_nchwf_conv<T, K, S, M, false, 2>; }
     hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(ft.threads), tile_lds(ft, sizeof(T), Ho, Wo), st, (const T *)in, (const T *)w,
                         (T *)out, nplanes, OC, Hi, Wi, Ho, Wo, bwd ? K - 1 - g.p : g.p, bwd ? 1 : g.m, total_in,
-                       bwd ? 1 : 0, ft, nblocks, nt);
+                       bwd ? 1 : 0, ft, nblocks, nt, g);
     return hipGetLastError();
 }
 template <typename T, int K, int M>
@@ -618,7 +648,7 @@ static hipError_t s2_go(const Geom &g, int dtype, const void *dy, const void *w,
     const int nt = stream_stores("NCHWF", 0, 0);
     hipLaunchKernelGGL((k_nchwf_bwd_data_s2<T, K, M>), dim3(nblocks), dim3(ft.threads), tile_lds(ft, sizeof(T), g.H, g.W), st, (const T *)dy,
                        (const T *)w, (T *)dx, nplanes, g.C, g.H, g.W, g.Ho, g.Wo, g.p, s2_cols(g), g.N * g.O * g.Ho * g.Wo, ft,
-                       nblocks, nt);
+                       nblocks, nt, g);
     return hipGetLastError();
 }
 template <typename T, int K, int S>

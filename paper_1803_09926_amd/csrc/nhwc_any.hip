@@ -10,7 +10,7 @@
 // One output per thread -> these kernels, us on one MI355X at batch 64, forward / input gradient / filter gradient: 56x56x128 5x5
 // stride 2 fp32 142 / 347 / 900 -> 36 / 37 / 41 (bound by its K vector loads per row and column, 8 bytes a lane); 28x28x256 7x7 fp32
 // 660 / 890 / 2430 -> 58 / 58 / 73; 56x56x30 3x3 fp32 49 / 67 / 954 -> 12.5 / 12.5 / 18.
-#include "kernels.hpp"
+#include "point.hpp"
 #include <type_traits>
 
 namespace dwc {
@@ -35,7 +35,7 @@ template <typename T, int V> __device__ __forceinline__ void load_filter_vec(con
 // ---------------------------------------------------------------------------------------------
 template <typename T, int V, int K, int S, int M>
 __global__ __launch_bounds__(256) void k_nhwca_conv(AnyGeom g, const T *__restrict__ in, const T *__restrict__ w, T *__restrict__ out, int OW,
-                                                    int flip, unsigned nblocks, int nt)
+                                                    int flip, unsigned nblocks, int nt, Geom q)
 {
     constexpr int NA = (K + S - 1) / S, VI = V * M;
     unsigned b = xcd_remap(blockIdx.x, nblocks);
@@ -106,6 +106,10 @@ __global__ __launch_bounds__(256) void k_nhwca_conv(AnyGeom g, const T *__restri
 #pragma unroll
         for (int v = 0; v < V; ++v) acc[0][v] = 0.f;
     };
+    NonFinite bad;
+#pragma unroll
+    for (int e = 0; e < K * K * VI; ++e) bad.add(wr[e / VI / K][e / VI % K][e % VI]);
+    const bool redo = bad.any();
     RawVec<T, VI> ra[S][K], rb[S][K];
     fetch(0, ra);
     int t = 0;
@@ -117,6 +121,15 @@ __global__ __launch_bounds__(256) void k_nhwca_conv(AnyGeom g, const T *__restri
         step(t + 1, rb);
     }
     if (t < steps) step(t, ra);
+
+    if (__builtin_expect(redo, 0)) {                    // the lane's outputs again, without the padding
+#pragma unroll 1
+        for (int i = 0; i < TRb * V; ++i) {
+            const int row = oh0 + i / V, ch = c + i % V;
+            stf(out + (((size_t)n * g.Ho + row) * g.Wo + ow) * g.Co + ch,
+                flip ? point_bwd_data<T, LAYOUT_NHWC>(q, in, w, n, ch, row, ow) : point_fwd<T, LAYOUT_NHWC>(q, in, w, n, ch, row, ow));
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -125,7 +138,7 @@ __global__ __launch_bounds__(256) void k_nhwca_conv(AnyGeom g, const T *__restri
 // ---------------------------------------------------------------------------------------------
 template <typename T, int V, int K, int M>
 __global__ __launch_bounds__(256) void k_nhwca_bwd_data_s2(AnyGeom g, const T *__restrict__ dy, const T *__restrict__ w, T *__restrict__ dx, int NB,
-                                                           unsigned nblocks, int nt)
+                                                           unsigned nblocks, int nt, Geom q)
 {
     constexpr int NA = (K + 1) / 2, VI = V * M;
     unsigned bid = xcd_remap(blockIdx.x, nblocks);
@@ -198,6 +211,10 @@ __global__ __launch_bounds__(256) void k_nhwca_bwd_data_s2(AnyGeom g, const T *_
 #pragma unroll
                 for (int v = 0; v < V; ++v) acc[k][i >> 1][i & 1][v] = k + 1 < NA ? acc[k + 1][i >> 1][i & 1][v] : 0.f;
     };
+    NonFinite bad;
+#pragma unroll
+    for (int e = 0; e < K * K * VI; ++e) bad.add(wr[e / VI / K][e / VI % K][e % VI]);
+    const bool redo = bad.any();
     RawVec<T, VI> ra[NA], rb[NA];
     int r = a0 - (NA - 1);
     fetch(r, ra);
@@ -209,6 +226,15 @@ __global__ __launch_bounds__(256) void k_nhwca_bwd_data_s2(AnyGeom g, const T *_
         step(r + 1, rb);
     }
     if (r < a1) step(r, ra);
+
+    if (__builtin_expect(redo, 0)) {                    // the lane's outputs again, without the padding
+#pragma unroll 1
+        for (int i = 0; i < (a1 - a0) * 4 * V; ++i) {
+            const int h = 2 * a0 - g.pad + i / (2 * V), cw = col + i / V % 2, ch = c + i % V;
+            if ((unsigned)h < (unsigned)g.Ho && (unsigned)cw < (unsigned)g.Wo)
+                stf(dx + (((size_t)n * g.Ho + h) * g.Wo + cw) * g.Co + ch, point_bwd_data<T, LAYOUT_NHWC>(q, dy, w, n, ch, h, cw));
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -397,7 +423,7 @@ static hipError_t conv_any(const Geom &q, const void *in, const void *w, void *o
     if (nb >= (1LL << 31)) return hipErrorInvalidValue;
     const unsigned nblocks = (unsigned)nb;
     hipLaunchKernelGGL((k_nhwca_conv<T, V, K, S, M>), dim3(nblocks), dim3(256), 0, st, g, (const T *)in, (const T *)w, (T *)out, q.O, bwd ? 1 : 0,
-                       nblocks, stream_stores("NHWCA", 0, 0));
+                       nblocks, stream_stores("NHWCA", 0, 0), q);
     return hipGetLastError();
 }
 template <typename T, int V, int K, int M>
@@ -413,7 +439,7 @@ static hipError_t s2_any(const Geom &q, const void *dy, const void *w, void *dx,
     if (nb >= (1LL << 31)) return hipErrorInvalidValue;
     const unsigned nblocks = (unsigned)nb;
     hipLaunchKernelGGL((k_nhwca_bwd_data_s2<T, V, K, M>), dim3(nblocks), dim3(256), 0, st, g, (const T *)dy, (const T *)w, (T *)dx, NB, nblocks,
-                       stream_stores("NHWCA", 0, 0));
+                       stream_stores("NHWCA", 0, 0), q);
     return hipGetLastError();
 }
 template <typename T, int V, int K, int S>

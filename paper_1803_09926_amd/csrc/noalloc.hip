@@ -49,6 +49,6 @@ extern "C" int dwconv_bwd_filter_noalloc(const dwconv_desc *desc, const void *x,
     // stage 1 writes every partial that stage 2 reads, so what an earlier call left in the array is never seen
     hipError_t e = launch_bwd_filter(pl, g, desc->layout, desc->dtype, x, dy, ws, (hipStream_t)stream);
     if (e != hipSuccess) return DWCONV_ERR_LAUNCH;
-    e = reduce_partials(ws, pl.parts, g.O * g.K * g.K, (float *)dw, (hipStream_t)stream);
+    e = launch_reduce(pl, g, desc->layout, desc->dtype, x, dy, ws, (float *)dw, (hipStream_t)stream);
     return e == hipSuccess ? DWCONV_OK : DWCONV_ERR_LAUNCH;
 }

@@ -423,6 +423,14 @@ hipError_t launch_bwd_filter(const Plan &pl, const Geom &g, int layout, int dtyp
     }
 }
 
+hipError_t launch_reduce(const Plan &pl, const Geom &g, int layout, int dtype, const void *x, const void *dy, const float *ws, float *dw,
+                         hipStream_t st)
+{
+    const int J = g.O * g.K * g.K;
+    if (pl.variant != V_NCHWF_BWD_FILTER && pl.variant != V_NHWCA_BWD_FILTER) return reduce_partials(ws, pl.parts, J, dw, st);
+    return reduce_partials(ws, pl.parts, J, dw, {x, dy, dtype, layout, g.N, g.C, g.H, g.W, g.K, g.s, g.p, g.O, 1, g.m, g.Ho, g.Wo}, st);
+}
+
 hipError_t launch_bwd_fused(const Plan &pl, const Geom &g, int layout, int dtype, const void *x, const void *dy,
                             const void *w, void *dx, float *ws, hipStream_t st)
 {

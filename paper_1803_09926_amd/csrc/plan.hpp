@@ -50,6 +50,9 @@ hipError_t launch_bwd_data(const Plan &pl, const Geom &g, int layout, int dtype,
                            void *dx, hipStream_t st);
 hipError_t launch_bwd_filter(const Plan &pl, const Geom &g, int layout, int dtype, const void *x, const void *dy,
                              float *ws, hipStream_t st);
+// second stage of the filter gradient for what launch_bwd_filter has left in ws
+hipError_t launch_reduce(const Plan &pl, const Geom &g, int layout, int dtype, const void *x, const void *dy, const float *ws, float *dw,
+                         hipStream_t st);
 hipError_t launch_bwd_fused(const Plan &pl, const Geom &g, int layout, int dtype, const void *x, const void *dy,
                             const void *w, void *dx, float *ws, hipStream_t st);
 
