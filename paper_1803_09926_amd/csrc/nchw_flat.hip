@@ -4,9 +4,11 @@
 // Rows of 19, 37 or 74 elements are no whole number of 16-byte vectors, but a run of rows of a plane is one flat range of
 // memory, and so is a run of whole planes.  A block takes U planes and a band of TR output rows of each: the input rows go to
 // LDS as flat ranges in memory order (16 bytes per lane straight into LDS, `dma_range`: no register, no wait before
-// the block's barrier), a lane owns one output column (or two) of one plane and walks down the band, and the outputs leave through a
-// second LDS area as flat 16-byte streaming stores.  Every lane of the block is in the same row at the same time, so what
-// depends on the row (padding above and below, the first and last steps of the walk) is scalar; padding to the left and
+// the block's barrier), a lane owns one output column (or two) of one plane and walks down the band, and every output row leaves
+// straight from the registers: consecutive lanes consecutive elements, lines completed in L2 by the next row or plane.  (Gathered in
+// a second LDS area and stored as 16-byte vectors they left room for half as many blocks: forward at batch 64 28x28x256 7x7 fp32
+// 46 -> 34 us, 41x41x240 5x5 bf16 55 -> 44, 19x19x728 fp32 17.7 -> 13.7, 74x74x256 bf16 46.6 -> 44.8, the last two at batch 32.)
+// Every lane of the block is in the same row at the same time, so what depends on the row (padding above and below, the first and last steps of the walk) is scalar; padding to the left and
 // right is one select per value read.  A step reads K values of one input row (consecutive lanes consecutive words: no bank
 // conflict) for K*K multiply-adds.  Every block is short; several blocks per compute unit overlap one's loads with
 // another's arithmetic.
@@ -62,34 +64,32 @@ __device__ __forceinline__ void dma_bands(const T *__restrict__ src, int total, 
 }
 __device__ __forceinline__ void dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// The bands from LDS to memory; the first and the last vector of a range may be partial.
-template <typename T>
-__device__ __forceinline__ void store_bands(T *__restrict__ dst, const Bands &b, const T *lds, bool stream)
+// One element of a lane, soff the same in every lane.  (Without the readfirstlane of BufView's own members, which keeps a loop from
+// being unrolled: the row offset comes from the loop counter and is scalar as it is.)
+template <typename T> __device__ __forceinline__ void store_one(const BufView &v, float f, uint32_t voff, uint32_t soff)
 {
-    constexpr int VE = ve_of<T>();
-    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
-    const int nseg = b.pitch ? b.nplanes : 1, len = b.pitch ? (b.r1 - b.r0) * b.W : b.nplanes * b.HW;
-    const int nc = (len + VE - 1 + VE - 1) / VE / 64 + 1;
-    for (int i = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); i < nseg * nc; i += nw) {
-        const int s = i / nc, ch = i - s * nc;
-        const int e0 = b.first(s), e1 = e0 + len, a0 = e0 & ~(VE - 1);
-        const int idx = ch * 64 + lane, a = a0 + idx * VE;
-        const T *p = lds + s * b.pitch + idx * VE;
-        if (a >= e0 && a + VE <= e1) {
-            const u4v_t v = *reinterpret_cast<const u4v_t *>(p);
-            if (stream) __builtin_nontemporal_store(v, reinterpret_cast<u4v_t *>(dst + a));
-            else *reinterpret_cast<u4v_t *>(dst + a) = v;
-        } else if (a < e1) {
-            for (int j = 0; j < VE; ++j)
-                if (a + j >= e0 && a + j < e1) dst[a + j] = p[j];
-        }
+    if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(f), v.rsrc, (int)voff, (int)soff, 0);
+    else {
+        T h;
+        stf(&h, f);
+        __builtin_amdgcn_raw_buffer_store_b16(h, v.rsrc, (int)voff, (int)soff, 0);
     }
+}
+template <typename T> __device__ __forceinline__ void store_two(const BufView &v, float f, float h, uint32_t voff, uint32_t soff)
+{
+    if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_buffer_store_b64(u2raw_t{__float_as_uint(f), __float_as_uint(h)}, v.rsrc, (int)voff, (int)soff, 0);
+    else __builtin_amdgcn_raw_buffer_store_b32(pack2_bf16(f, h), v.rsrc, (int)voff, (int)soff, 0);
+}
+template <typename T> __device__ __forceinline__ T load_one(const BufView &v, uint32_t voff, uint32_t soff)
+{
+    if constexpr (sizeof(T) == 4) return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(v.rsrc, (int)voff, (int)soff, 0));
+    else return __builtin_amdgcn_raw_buffer_load_b16(v.rsrc, (int)voff, (int)soff, 0);
 }
 
 // What a launch of these kernels is cut into.
 struct FlatTile {
     int U, TR, nbands;     // planes per block, output rows per band (bwd_data_s2: row pairs), bands per plane
-    int pin, pout;         // LDS pitches (0: whole planes)
+    int pin, pout;         // LDS elements from plane to plane (0: whole planes); of dy, if it is in LDS too (0: it is not)
     int nin;               // LDS elements of the input area
     int threads;
 };
@@ -109,7 +109,7 @@ constexpr int GUARD = 16;  // LDS elements in front of and behind the input area
 template <typename T, int K, int S, int M, bool SAME, int NC>
 __global__ __launch_bounds__(512) void k_nchwf_conv(const T *__restrict__ in, const T *__restrict__ w, T *__restrict__ out,
                                                     int nplanes, int OC, int Hi, int Wi, int Ho, int Wo, int pad, int mdiv,
-                                                    int total_in, int flip, FlatTile ft, unsigned nblocks, int nt, Geom g)
+                                                    int total_in, int flip, FlatTile ft, unsigned nblocks, Geom g)
 {
     extern __shared__ uint4 smem[];
     constexpr int NA = (K + S - 1) / S;
@@ -120,8 +120,7 @@ __global__ __launch_bounds__(512) void k_nchwf_conv(const T *__restrict__ in, co
     const int ip0 = M > 1 ? p0 * M : p0 / mdiv, ip1 = M > 1 ? (p0 + np) * M : (p0 + np - 1) / mdiv + 1;
     const int r0 = min(max(oh0 * S - pad, 0), Hi), r1 = max(min((oh1 - 1) * S - pad + K, Hi), r0);
     const Bands bi = {ip0, ip1 - ip0, Hi * Wi, Wi, r0, r1, ft.pin};
-    const Bands bo = {p0, np, Ho * Wo, Wo, oh0, oh1, ft.pout};
-    T *lin = reinterpret_cast<T *>(smem) + GUARD, *lout = lin + ft.nin + GUARD;
+    T *lin = reinterpret_cast<T *>(smem) + GUARD;
     dma_bands<T>(in, total_in, bi, lin);
 
     constexpr int VW = S * (NC - 1) + K;                   // values of an input row that the lane's NC columns reach
@@ -146,14 +145,11 @@ __global__ __launch_bounds__(512) void k_nchwf_conv(const T *__restrict__ in, co
             }
         src[q] = bi.at<T>((M > 1 ? pl * M + q : pl / mdiv) - ip0) + col0;
     }
-    // a column that is none writes its sums to the guard elements in front of the output area: no lane mask in the walk
-    int dst[NC], dstep[NC];
+    // a column that is none is stored outside the view: no lane mask in the walk
+    const BufView vout(out + (size_t)p0 * Ho * Wo, (uint32_t)(np * Ho * Wo) * (uint32_t)sizeof(T));
+    uint32_t voff[NC];
 #pragma unroll
-    for (int n = 0; n < NC; ++n) {
-        const bool mine = active && ow + n < Wo;
-        dst[n] = mine ? bo.at<T>(u) + ow + n : -1;
-        dstep[n] = mine ? Wo : 0;
-    }
+    for (int n = 0; n < NC; ++n) voff[n] = active && ow + n < Wo ? (uint32_t)((u * Ho + oh0) * Wo + ow + n) * (uint32_t)sizeof(T) : BufView::OUTSIDE;
     float acc[NA][NC];
 #pragma unroll
     for (int i = 0; i < NA; ++i)
@@ -198,8 +194,9 @@ __global__ __launch_bounds__(512) void k_nchwf_conv(const T *__restrict__ in, co
             }
         }
         if (!CK || t >= NA - 1) {
+            const uint32_t so = (uint32_t)((t - (NA - 1)) * Wo) * (uint32_t)sizeof(T);
 #pragma unroll
-            for (int n = 0; n < NC; ++n) { stf(lout + dst[n], acc[NA - 1][n]); dst[n] += dstep[n]; }
+            for (int n = 0; n < NC; ++n) store_one<T>(vout, acc[NA - 1][n], voff[n], so);
         }
 #pragma unroll
         for (int i = NA - 1; i > 0; --i)
@@ -221,23 +218,23 @@ __global__ __launch_bounds__(512) void k_nchwf_conv(const T *__restrict__ in, co
         for (int i = 0; i < TRb * NC; ++i) {
             const int t = i / NC, c = ow + i - t * NC;
             if (c < Wo)
-                stf(lout + bo.at<T>(u) + t * Wo + c, flip ? point_bwd_data<T, LAYOUT_NCHW>(g, in, w, n, oc, oh0 + t, c)
+                stf(out + ((size_t)pl * Ho + oh0 + t) * Wo + c, flip ? point_bwd_data<T, LAYOUT_NCHW>(g, in, w, n, oc, oh0 + t, c)
                                                           : point_fwd<T, LAYOUT_NCHW>(g, in, w, n, oc, oh0 + t, c));
         }
     }
-    __syncthreads();
-    store_bands<T>(out, bo, lout, nt != 0);
 }
 
 // ---------------------------------------------------------------------------------------------
 // Input gradient of a stride-2 layer.  With h + p = 2a + f and c + p = 2b + e the taps that reach dx[h][c] are kh = 2k + f,
-// kw = 2l + e against dy[a - k][b - l]: a lane owns the dx columns of one b, walks down the dy rows with the K/2 row
+// kw = 2l + e against dy[a - k][b - l]: a lane owns two neighbouring dx columns, walks down the dy rows with the K/2 row
 // pairs a row reaches in rotating accumulators, and a dy row costs (K+1)/2 reads and K*K multiply-adds for four outputs.
+// SH: the columns are e = 0, 1 of one b for an even padding and e = 1 of b, e = 0 of b + 1 for an odd one, so that either way
+// the first is even and rows of an even width take both in one aligned store (74x74x256 3x3 fp32: 71 us with the pairs at odd columns).
 // ---------------------------------------------------------------------------------------------
-template <typename T, int K, int M>
+template <typename T, int K, int M, int SH>
 __global__ __launch_bounds__(512) void k_nchwf_bwd_data_s2(const T *__restrict__ dy, const T *__restrict__ w, T *__restrict__ dx,
                                                            int nplanes, int C, int H, int W, int Ho, int Wo, int pad, int NB,
-                                                           int total_dy, FlatTile ft, unsigned nblocks, int nt, Geom g)
+                                                           int total_dy, FlatTile ft, unsigned nblocks, Geom g)
 {
     extern __shared__ uint4 smem[];
     constexpr int NA = (K + 1) / 2;
@@ -248,17 +245,16 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_data_s2(const T *__restrict__
     const int r0 = min(max(a0 - (NA - 1), 0), Ho), r1 = max(min(a1, Ho), r0);
     const int h0 = max(2 * a0 - pad, 0), h1 = min(2 * a1 - pad, H);
     const Bands bi = {p0 * M, np * M, Ho * Wo, Wo, r0, r1, ft.pin};
-    const Bands bo = {p0, np, H * W, W, h0, h1, ft.pout};
-    T *lin = reinterpret_cast<T *>(smem) + GUARD, *lout = lin + ft.nin + GUARD;
+    T *lin = reinterpret_cast<T *>(smem) + GUARD;
     dma_bands<T>(dy, total_dy, bi, lin);
 
-    const int u = (int)threadIdx.x / NB, b = pad / 2 + (int)threadIdx.x - u * NB;
+    const int u = (int)threadIdx.x / NB, bi0 = (int)threadIdx.x - u * NB, b = (pad - SH) / 2 + bi0;
     const bool active = u < np;
     const int pl = p0 + (active ? u : 0), c = pl % C;
     uint32_t ok[NA];
 #pragma unroll
-    for (int l = 0; l < NA; ++l) ok[l] = (unsigned)(b - l) < (unsigned)Wo ? ~0u : 0u;
-    const int colb = min(b, Wo + NA - 1);                  // a column further out has every tap dropped anyway
+    for (int l = 0; l < NA; ++l) ok[l] = (unsigned)(b + SH - l) < (unsigned)Wo ? ~0u : 0u;
+    const int colb = min(b + SH, Wo + NA - 1);                  // a column further out has every tap dropped anyway
     float wr[M][K][K];
     int src[M];
 #pragma unroll
@@ -269,12 +265,12 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_data_s2(const T *__restrict__
             for (int kw = 0; kw < K; ++kw) wr[q][kh][kw] = ldf(w + (c * M + q) * K * K + kh * K + kw);
         src[q] = bi.at<T>((active ? u : 0) * M + q) + colb;
     }
-    // columns 2b - pad and the next; a lane writes what it does not own to the guard elements in front of the output area
-    const int col = 2 * b - pad;
-    const bool st0 = active && col >= 0 && col < W, st1 = active && col + 1 < W;
-    const int first = bo.at<T>(active ? u : 0) + col + (2 * a0 - pad - h0) * W;
-    int dst0 = st0 ? first : -1, dst1 = st1 ? first + 1 : -1;
-    const int step0 = st0 ? W : 0, step1 = st1 ? W : 0;
+    // columns col and col + 1; one that is none is stored outside the view.  Rows of an even width: one aligned store for both.
+    const int col = 2 * bi0;
+    const bool even = W % 2 == 0;
+    const BufView vout(dx + (size_t)p0 * H * W, (uint32_t)(np * H * W) * (uint32_t)sizeof(T));
+    const uint32_t v0 = active ? (uint32_t)(u * H * W + col) * (uint32_t)sizeof(T) : BufView::OUTSIDE;
+    const uint32_t v1 = active && col + 1 < W ? v0 + (uint32_t)sizeof(T) : BufView::OUTSIDE;
     float acc[NA][2][2];
 #pragma unroll
     for (int k = 0; k < NA; ++k) acc[k][0][0] = acc[k][0][1] = acc[k][1][0] = acc[k][1][1] = 0.f;
@@ -305,7 +301,7 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_data_s2(const T *__restrict__
                         for (int l = 0; l < NA; ++l)
 #pragma unroll
                             for (int e = 0; e < 2; ++e)
-                                if (2 * k + f < K && 2 * l + e < K) acc[k][f][e] = fmaf(wr[q][2 * k + f][2 * l + e], v[l], acc[k][f][e]);
+                                if (2 * k + f < K && 2 * l + e < K) acc[k][f][e] = fmaf(wr[q][2 * k + f][2 * l + e], v[e ? l + SH : l], acc[k][f][e]);
             }
         }
         if (!CK || r >= a0) {
@@ -313,11 +309,14 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_data_s2(const T *__restrict__
             for (int f = 0; f < 2; ++f) {
                 const int h = 2 * r - pad + f;
                 if (!CK || (h >= h0 && h < h1)) {              // uniform
-                    stf(lout + dst0 + f * step0, acc[0][f][0]);
-                    stf(lout + dst1 + f * step1, acc[0][f][1]);
+                    const uint32_t so = (uint32_t)(h * W) * (uint32_t)sizeof(T);
+                    if (even) store_two<T>(vout, acc[0][f][SH], acc[0][f][1 - SH], v0, so);
+                    else {
+                        store_one<T>(vout, acc[0][f][SH], v0, so);
+                        store_one<T>(vout, acc[0][f][1 - SH], v1, so);
+                    }
                 }
             }
-            dst0 += 2 * step0; dst1 += 2 * step1;
         }
 #pragma unroll
         for (int k = 0; k < NA; ++k)
@@ -337,19 +336,18 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_data_s2(const T *__restrict__
 #pragma unroll 1
         for (int i = 0; i < 2 * (h1 - h0); ++i) {
             const int h = h0 + i / 2, cw = col + i % 2;
-            if ((unsigned)cw < (unsigned)W) stf(lout + bo.at<T>(u) + (h - h0) * W + cw, point_bwd_data<T, LAYOUT_NCHW>(g, dy, w, n, c, h, cw));
+            if ((unsigned)cw < (unsigned)W) stf(dx + ((size_t)pl * H + h) * W + cw, point_bwd_data<T, LAYOUT_NCHW>(g, dy, w, n, c, h, cw));
         }
     }
-    __syncthreads();
-    store_bands<T>(dx, bo, lout, nt != 0);
 }
 
 // ---------------------------------------------------------------------------------------------
-// Filter gradient, stage 1.  A block owns U output channels and walks (image, band) items: x and dy bands staged as above, a
-// lane keeps the K*K sums of its column over all of them against a window of the last K/S dy rows.  The columns of a
-// channel are added through LDS in a fixed order at the end, one partial per block.
+// Filter gradient, stage 1.  A block owns U output channels and walks (image, band) items: x bands staged as above, dy read by the
+// lanes that own its columns a few rows ahead (or from LDS, see DY_LDS); a lane keeps the K*K sums of its column over all of
+// them against a window of the last K/S dy rows.  The columns of a channel are added through LDS in a fixed order at the end,
+// one partial per block.
 // ---------------------------------------------------------------------------------------------
-template <typename T, int K, int S, bool SAME, int NC>
+template <typename T, int K, int S, bool SAME, int NC, bool DYLDS>
 __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__restrict__ x, const T *__restrict__ dy,
                                                           float *__restrict__ ws, int parts, int per_part, FlatTile ft,
                                                           unsigned nblocks)
@@ -368,12 +366,12 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__res
     uint32_t ok[VW];
 #pragma unroll
     for (int i = 0; i < VW; ++i) ok[i] = (unsigned)(ow * S - g.p + i) < (unsigned)g.W ? ~0u : 0u;
-    // the dy columns of the lane; the last lane of a row may have one that is none
-    uint32_t okd[NC];
+    const int col0 = min(max(ow * S - g.p, -VW), g.W);
+    T *lx = reinterpret_cast<T *>(smem) + GUARD;
+    // the dy columns of the lane; one that is none reads as zero
+    uint32_t offd[NC];
 #pragma unroll
-    for (int n = 0; n < NC; ++n) okd[n] = ow + n < g.Wo ? ~0u : 0u;
-    const int col0 = min(max(ow * S - g.p, -VW), g.W), owc = active ? ow : 0;
-    T *lx = reinterpret_cast<T *>(smem) + GUARD, *ldy = lx + ft.nin + GUARD;
+    for (int n = 0; n < NC; ++n) offd[n] = active && ow + n < g.Wo ? (uint32_t)(u * g.Ho * g.Wo + ow + n) * (uint32_t)sizeof(T) : BufView::OUTSIDE;
     float acc[K][K];
 #pragma unroll
     for (int kh = 0; kh < K; ++kh)
@@ -386,26 +384,54 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__res
         const int oh0 = band * ft.TR, oh1 = min(g.Ho, oh0 + ft.TR);
         const int r0 = min(max(oh0 * S - g.p, 0), g.H), r1 = max(min((oh1 - 1) * S - g.p + K, g.H), r0);
         const Bands bx = {n * g.C + c0, c1 - c0, g.H * g.W, g.W, r0, r1, ft.pin};
-        const Bands by = {n * g.O + o0, np, g.Ho * g.Wo, g.Wo, oh0, oh1, ft.pout};
+        const BufView vd(dy + (size_t)(n * g.O + o0) * g.Ho * g.Wo, (uint32_t)(np * g.Ho * g.Wo) * (uint32_t)sizeof(T));
         dma_bands<T>(x, g.N * g.C * g.H * g.W, bx, lx);
-        dma_bands<T>(dy, g.N * g.O * g.Ho * g.Wo, by, ldy);
-        const T *px = lx + bx.at<T>(ju) + col0, *pd = ldy + by.at<T>(uu) + owc;
+        const T *px = lx + bx.at<T>(ju) + col0;
+        const T *pd = lx;
+        if constexpr (DYLDS) {
+            const Bands by = {n * g.O + o0, np, g.Ho * g.Wo, g.Wo, oh0, oh1, ft.pout};
+            T *ldy = lx + ft.nin + GUARD;
+            dma_bands<T>(dy, g.N * g.O * g.Ho * g.Wo, by, ldy);
+            pd = ldy + by.at<T>(active ? u : 0) + (active ? ow : 0);
+        }
         float d[NA][NC];
 #pragma unroll
         for (int i = 0; i < NA; ++i)
 #pragma unroll
             for (int n = 0; n < NC; ++n) d[i][n] = 0.f;
+        const int rows = oh1 - oh0, steps = rows + NA - 1;
+        // dy rows t .. t + PD - 1 are on their way (3x3: three rows ahead 84 us at 74x74x256 fp32, six 74, nine 84; 5x5: five 67 at
+        // 41x41x240, ten 70)
+        constexpr int PD = K == 3 ? 6 : NA;
+        T dq[PD][NC];
+        auto fetch = [&](int t, T (&q)[NC]) {
+#pragma unroll
+            for (int n = 0; n < NC; ++n) q[n] = load_one<T>(vd, offd[n], (uint32_t)((oh0 + min(t, rows - 1)) * g.Wo) * (uint32_t)sizeof(T));
+        };
+        if constexpr (!DYLDS) {
+#pragma unroll
+            for (int i = 0; i < PD; ++i) fetch(i, dq[i]);
+        }
         dma_wait();
         __syncthreads();
         // step t: the S x rows from row (oh0 + t)*S - p on, against dy rows oh0 + t - i; steps [ta, tb) have all of them in the band
-        const int rows = oh1 - oh0, steps = rows + NA - 1;
         const int base = oh0 * S - g.p - r0, nrows = r1 - r0;
         auto step = [&](int t, auto checked) {
             constexpr bool CK = decltype(checked)::value;
 #pragma unroll
             for (int n = 0; n < NC; ++n) {
-                d[0][n] = !CK || t < rows ? ldf(pd + t * g.Wo + n) : 0.f;
-                if (n > 0) d[0][n] = masked(d[0][n], okd[n]);
+                if constexpr (DYLDS) d[0][n] = !CK || t < rows ? ldf(pd + t * g.Wo) : 0.f;
+                else {
+                    const float f = ldf(&dq[0][n]);
+                    d[0][n] = !CK || t < rows ? f : 0.f;
+                }
+            }
+            if constexpr (!DYLDS) {
+#pragma unroll
+                for (int i = 0; i + 1 < PD; ++i)
+#pragma unroll
+                    for (int n = 0; n < NC; ++n) dq[i][n] = dq[i + 1][n];
+                fetch(t + PD, dq[PD - 1]);
             }
 #pragma unroll
             for (int j = 0; j < S; ++j) {
@@ -435,7 +461,7 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__res
         const int ta = (S - 1 - base) / S, tb = min((nrows - base) / S, rows);
         int t = 0;
         for (; t < min(K > 3 ? max(ta, NA - 1) : ta, steps); ++t) step(t, std::true_type());
-#pragma unroll NA
+#pragma unroll DYLDS ? NA : PD
         for (; t < tb; ++t) step(t, std::false_type());
         for (; t < steps; ++t) step(t, std::true_type());
         __syncthreads();
@@ -489,37 +515,39 @@ void pick_lanes(int cols, int planes, int maxu, int *U, int *threads)
     }
 }
 
-// LDS of a block.  Bands of about 32 KiB (five blocks per compute unit): halves of that read too many halo rows, more leaves
-// too few blocks to overlap (74x74 fp32 forward at batch 32, 256 channels: 16 KiB 88 us, 20 78, 26 73, 32 70, 40 73, 50 76;
-// bf16 63, 47, 47, 46, 49, 50).  Whole planes, which have no halo, up to 40 KiB (19x19 stride 2, 728 channels: 16.5 -> 11.5 us
-// against bands of 32 KiB; 28x28 7x7 46 -> 38 us).  5x5 and 7x7 have the longer halos: bands of 40 KiB (28x28 7x7 forward
-// at batch 64, 256 channels 47 -> 38 us, filter gradient 71 -> 56; bf16 5x5 41x41 64 -> 59).
+// LDS of a block.  Bands of about 32 KiB, 40 for the longer halos of 5x5 and 7x7, whole planes, which have no halo, up to 40 KiB: less
+// reads too many halo rows, more leaves too few blocks to overlap, with little between 24 and 40 (56x56x128 5x5 stride 2 fp32 forward at
+// batch 64 16 KiB 35 us, 24 31, 32 29, 40 30, filter gradient 46, 51, 48, 44; 56x56 5x5 multiplier 2 input gradient 16 KiB 99, 20 96,
+// 24 84, 32 83, 40 81).
 inline int lds_target(int K) { return K == 3 ? 32 << 10 : 40 << 10; }
 constexpr int LDS_WHOLE = 40 << 10;
 constexpr int LDS_MOST = 64 << 10;
 
 inline int round_up(int a, int b) { return (a + b - 1) / b * b; }
 
-// Tile of a launch: `cols` lanes per plane; an output band of t units (rows, or row pairs) has out_rows(t) output rows and
-// needs in_rows(t) input rows; `mi` input planes per `mo` output planes.
-template <typename FI, typename FO>
-bool pick_tile(int esz, int cols, int units, int nplanes, int maxu, int Hi, int Wi, int Ho, int Wo, FI in_rows, FO out_rows,
-               int Mi, int mdiv, int target, FlatTile *ft)
+int second_area(const FlatTile &ft) { return GUARD + ft.U * ft.pout; }       // LDS elements of the dy bands of a tile
+
+// Tile of a launch: `cols` lanes per plane; a band of t units (rows, or row pairs) needs in_rows(t) input rows; Mi input planes per
+// output plane, or mdiv output planes per input plane; second: bands of the output rows are in LDS too.
+template <typename FI>
+bool pick_tile(int esz, int cols, int units, int nplanes, int maxu, int Hi, int Wi, int Ho, int Wo, FI in_rows, int Mi, int mdiv,
+               int target, FlatTile *ft, bool second = false)
 {
     const int VE = 16 / esz;
-    pick_lanes(cols, nplanes, maxu, &ft->U, &ft->threads);
+    // a block's planes are one buffer view (2 GiB at most)
+    const long long fit = ((1LL << 31) - 1) / ((long long)Ho * Wo * esz);
+    pick_lanes(cols, nplanes, fit < maxu ? (int)fit : maxu, &ft->U, &ft->threads);
     if (ft->U < 1) return false;
     for (;;) {
         const int nin_planes = Mi > 1 ? ft->U * Mi : (mdiv > 1 ? (ft->U - 1) / mdiv + 2 : ft->U);
         auto lds = [&](int t, FlatTile *o) {
             const bool whole = t >= units;
-            const int ir = in_rows(t) < Hi ? in_rows(t) : Hi, orr = out_rows(t) < Ho ? out_rows(t) : Ho;
+            const int ir = in_rows(t) < Hi ? in_rows(t) : Hi;
             o->TR = t; o->nbands = whole ? 1 : (units + t - 1) / t;
             o->pin = whole ? 0 : round_up(ir * Wi + VE, VE);
-            o->pout = whole ? 0 : round_up(orr * Wo + VE, VE);
             o->nin = whole ? round_up(nin_planes * Hi * Wi + VE, VE) : nin_planes * o->pin;
-            const int nout = whole ? round_up(ft->U * Ho * Wo + VE, VE) : ft->U * o->pout;
-            return (long long)(o->nin + nout + 3 * GUARD) * esz;
+            o->pout = second ? round_up(t * Wo + VE, VE) : 0;
+            return (long long)(o->nin + 2 * GUARD + (second ? second_area(*o) : 0)) * esz;
         };
         int t = units;
         if (lds(t, ft) > LDS_WHOLE) {                        // the tallest band within the target, by bisection
@@ -540,12 +568,7 @@ bool pick_tile(int esz, int cols, int units, int nplanes, int maxu, int Hi, int 
     }
 }
 
-size_t tile_lds(const FlatTile &ft, int esz, int Ho, int Wo)
-{
-    const int VE = 16 / esz;
-    const int nout = ft.pout ? ft.U * ft.pout : round_up(ft.U * Ho * Wo + VE, VE);
-    return (size_t)(ft.nin + nout + 3 * GUARD) * esz;
-}
+size_t tile_lds(const FlatTile &ft, int esz) { return (size_t)(ft.nin + 2 * GUARD) * esz; }
 
 // Planes per block, at most: about two blocks per compute unit in the launch (planes of more than 24 rows are several bands),
 // but a wavefront's worth of columns.
@@ -560,33 +583,42 @@ bool flat_k(const Geom &g) { return (g.K == 3 || g.K == 5 || g.K == 7) && (g.s =
 // Output columns per lane of the forward kernel and the filter gradient: two for 5x5 and 7x7 in bf16, whose K values a row and
 // column are 16-bit LDS reads that have to be widened (28x28x256 7x7 batch 64: forward 35 -> 32 us, filter gradient 47 -> 42;
 // 56x56x128 5x5 stride 2: 35 -> 30 and 42 -> 32).  In fp32 half the lanes per LDS byte cost more than the shared reads give
-// (40 -> 52 us).
+// (40 -> 52 us), and so they do for 3x3 in bf16 (74x74x256 forward 45 -> 58 us, filter gradient 56 -> 67).
 int flat_cols(const Geom &g, int dtype) { return g.K > 3 && dtype == DT_BF16 ? 2 : 1; }
 
 bool conv_tile(const Geom &g, int dtype, bool bwd, FlatTile *ft)
 {
-    const int esz = dtype == DT_F32 ? 4 : 2, K = g.K, S = g.s, nc = flat_cols(g, dtype);
-    auto in_rows = [&](int t) { return (t - 1) * S + K; };
-    auto out_rows = [&](int t) { return t; };
-    if (!bwd) return pick_tile(esz, (g.Wo + nc - 1) / nc, g.Ho, g.N * g.O, most_planes((long long)g.N * g.O, g.Ho, (g.Wo + nc - 1) / nc), g.H, g.W, g.Ho, g.Wo, in_rows, out_rows, 1, g.m, lds_target(K), ft);
-    return pick_tile(esz, (g.W + nc - 1) / nc, g.H, g.N * g.C, most_planes((long long)g.N * g.C, g.H, (g.W + nc - 1) / nc), g.Ho, g.Wo, g.H, g.W, in_rows, out_rows, g.m, 1, lds_target(K), ft);
+    const int esz = dtype == DT_F32 ? 4 : 2, nc = flat_cols(g, dtype), cols = ((bwd ? g.W : g.Wo) + nc - 1) / nc;
+    auto in_rows = [&](int t) { return (t - 1) * g.s + g.K; };
+    if (!bwd)
+        return pick_tile(esz, cols, g.Ho, g.N * g.O, most_planes((long long)g.N * g.O, g.Ho, cols), g.H, g.W, g.Ho, g.Wo, in_rows, 1, g.m, lds_target(g.K), ft);
+    return pick_tile(esz, cols, g.H, g.N * g.C, most_planes((long long)g.N * g.C, g.H, cols), g.Ho, g.Wo, g.H, g.W, in_rows, g.m, 1, lds_target(g.K), ft);
 }
 
-int s2_cols(const Geom &g) { return (g.W - 1 + g.p) / 2 - g.p / 2 + 1; }
+int s2_cols(const Geom &g) { return (g.W + 1) / 2; }
 int s2_pairs(const Geom &g) { return (g.H - 1 + g.p) / 2 - g.p / 2 + 1; }
 bool s2_tile(const Geom &g, int dtype, FlatTile *ft)
 {
     const int esz = dtype == DT_F32 ? 4 : 2, NA = (g.K + 1) / 2;
     auto in_rows = [&](int t) { return t + NA - 1; };
-    auto out_rows = [&](int t) { return 2 * t; };
-    return pick_tile(esz, s2_cols(g), s2_pairs(g), g.N * g.C, most_planes((long long)g.N * g.C, g.H, s2_cols(g)), g.Ho, g.Wo, g.H, g.W, in_rows, out_rows, g.m, 1, lds_target(g.K), ft);
+    return pick_tile(esz, s2_cols(g), s2_pairs(g), g.N * g.C, most_planes((long long)g.N * g.C, g.H, s2_cols(g)), g.Ho, g.Wo, g.H, g.W, in_rows, g.m, 1,
+                     lds_target(g.K), ft);
 }
+// Whether the filter gradient reads dy from LDS too.  Every dy value is read once, by one lane, so that it needs no LDS, and without it
+// more blocks fit a compute unit: 28x28x256 7x7 fp32 batch 64 54 -> 42 us, 37x37x256 multiplier 2 41 -> 32, 19x19x728 bf16 17 -> 15,
+// 74x74x256 3x3 fp32 78 -> 74.  But a lane's own loads are short, and a band starts with a wait for them: planes that are
+// too large for LDS together with their dy keep bands of both there for 3x3 in bf16 (74x74x256 49 us against 56) and at stride 2 (fp32 55 against 63), and for 5x5 in fp32 (41x41x240 63 against 67;
+// at stride 2 56x56x128 47 against 45).
+template <typename T, int K, int S> constexpr bool DY_LDS = K == 3 ? sizeof(T) == 2 || S == 2 : K == 5 && S == 1 && sizeof(T) == 4;
 bool filter_tile(const Geom &g, int dtype, FlatTile *ft)
 {
-    const int esz = dtype == DT_F32 ? 4 : 2, K = g.K, S = g.s, nc = flat_cols(g, dtype);
-    auto in_rows = [&](int t) { return (t - 1) * S + K; };
-    auto out_rows = [&](int t) { return t; };
-    return pick_tile(esz, (g.Wo + nc - 1) / nc, g.Ho, g.O, most_planes((long long)g.N * g.O, g.Ho, (g.Wo + nc - 1) / nc), g.H, g.W, g.Ho, g.Wo, in_rows, out_rows, 1, g.m, lds_target(K), ft);
+    const int esz = dtype == DT_F32 ? 4 : 2, nc = flat_cols(g, dtype), cols = (g.Wo + nc - 1) / nc;
+    auto in_rows = [&](int t) { return (t - 1) * g.s + g.K; };
+    auto pick = [&](bool second) {
+        return pick_tile(esz, cols, g.Ho, g.O, most_planes((long long)g.N * g.O, g.Ho, cols), g.H, g.W, g.Ho, g.Wo, in_rows, 1, g.m, lds_target(g.K), ft, second);
+    };
+    const bool lds = g.K == 3 ? dtype == DT_BF16 || g.s == 2 : g.K == 5 && g.s == 1 && dtype == DT_F32;      // DY_LDS
+    return (lds && pick(true) && ft->nbands > 1) || pick(false);
 }
 
 }  // namespace
@@ -629,13 +661,12 @@ static hipError_t conv_go(const Geom &g, int dtype, const void *in, const void *
     const int OC = bwd ? g.C : g.O, nplanes = g.N * OC;
     const unsigned nblocks = (unsigned)((nplanes + ft.U - 1) / ft.U) * ft.nbands;
     const int total_in = g.N * (bwd ? g.O : g.C) * Hi * Wi;
-    const int nt = stream_stores("NCHWF", 0, 0);
     const bool same = (bwd ? K - 1 - g.p : g.p) == K / 2;
-    auto kernel = same ? k_nchwf_conv<T, K, S, M, true, 1> : k_nchwf_conv<T, K, S, M, false, 1>;
-    if constexpr (K > 3 && sizeof(T) == 2) { if (flat_cols(g, dtype) == 2) kernel = same ? k_nchwf_conv<T, K, S, M, true, 2> : k_nchwf_conv<T, K, S, M, false, 2>; }
-    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(ft.threads), tile_lds(ft, sizeof(T), Ho, Wo), st, (const T *)in, (const T *)w,
+    constexpr int NC = K > 3 && sizeof(T) == 2 ? 2 : 1;
+    auto kernel = same ? k_nchwf_conv<T, K, S, M, true, NC> : k_nchwf_conv<T, K, S, M, false, NC>;
+    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(ft.threads), tile_lds(ft, sizeof(T)), st, (const T *)in, (const T *)w,
                         (T *)out, nplanes, OC, Hi, Wi, Ho, Wo, bwd ? K - 1 - g.p : g.p, bwd ? 1 : g.m, total_in,
-                       bwd ? 1 : 0, ft, nblocks, nt, g);
+                       bwd ? 1 : 0, ft, nblocks, g);
     return hipGetLastError();
 }
 template <typename T, int K, int M>
@@ -645,10 +676,10 @@ static hipError_t s2_go(const Geom &g, int dtype, const void *dy, const void *w,
     if (!s2_tile(g, dtype, &ft)) return hipErrorInvalidValue;
     const int nplanes = g.N * g.C;
     const unsigned nblocks = (unsigned)((nplanes + ft.U - 1) / ft.U) * ft.nbands;
-    const int nt = stream_stores("NCHWF", 0, 0);
-    hipLaunchKernelGGL((k_nchwf_bwd_data_s2<T, K, M>), dim3(nblocks), dim3(ft.threads), tile_lds(ft, sizeof(T), g.H, g.W), st, (const T *)dy,
+    auto kernel = g.p % 2 ? k_nchwf_bwd_data_s2<T, K, M, 1> : k_nchwf_bwd_data_s2<T, K, M, 0>;
+    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(ft.threads), tile_lds(ft, sizeof(T)), st, (const T *)dy,
                        (const T *)w, (T *)dx, nplanes, g.C, g.H, g.W, g.Ho, g.Wo, g.p, s2_cols(g), g.N * g.O * g.Ho * g.Wo, ft,
-                       nblocks, nt, g);
+                       nblocks, g);
     return hipGetLastError();
 }
 template <typename T, int K, int S>
@@ -658,11 +689,14 @@ static hipError_t filter_go(const Geom &g, int dtype, const void *x, const void 
     if (!filter_tile(g, dtype, &ft)) return hipErrorInvalidValue;
     const int items = g.N * ft.nbands, per = (items + parts - 1) / parts;
     const unsigned nblocks = (unsigned)((g.O + ft.U - 1) / ft.U) * parts;
-    size_t lds = tile_lds(ft, sizeof(T), g.Ho, g.Wo);
+    size_t lds = tile_lds(ft, sizeof(T)) + (ft.pout ? (size_t)second_area(ft) * sizeof(T) : 0);
     const size_t red = (size_t)(K * K <= 25 ? K * K : 25) * ft.threads * 4;
     if (red > lds) lds = red;
-    auto kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, 1> : k_nchwf_bwd_filter<T, K, S, false, 1>;
-    if constexpr (K > 3 && sizeof(T) == 2) { if (flat_cols(g, dtype) == 2) kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, 2> : k_nchwf_bwd_filter<T, K, S, false, 2>; }
+    constexpr int NC = K > 3 && sizeof(T) == 2 ? 2 : 1;
+    auto kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, NC, false> : k_nchwf_bwd_filter<T, K, S, false, NC, false>;
+    if constexpr (DY_LDS<T, K, S>) {
+        if (ft.pout) kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, NC, true> : k_nchwf_bwd_filter<T, K, S, false, NC, true>;
+    }
     hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(ft.threads), lds, st, g, (const T *)x, (const T *)dy, ws, parts,
                        per, ft, nblocks);
     return hipGetLastError();

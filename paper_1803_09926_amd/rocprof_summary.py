@@ -55,7 +55,7 @@ VARIANT_KERNELS = {
     "bwd_filter:nchw_smallplane_bwd_filter_k5s1": [r"k_nchws_bwd_filter<[\w ]+, 5, 1, \d+, 1>"],
     # k_nchwf_conv<T, K, S, M, SAME, NC> (the input gradient of a stride-1 layer runs the same kernel as the forward pass)
     "fwd:nchw_flat_k5s1": [r"k_nchwf_conv<[\w ]+, 5, 1, 1, \w+, \d>"],
-    "bwd_filter:nchw_flat_bwd_filter_k5s1": [r"k_nchwf_bwd_filter<[\w ]+, 5, 1, \w+, \d>"],
+    "bwd_filter:nchw_flat_bwd_filter_k5s1": [r"k_nchwf_bwd_filter<[\w ]+, 5, 1, \w+, \d, \w+>"],
     # whole backward pass in one kernel (dwconv_bwd)
     # k_nhwc_bwd_fused_k3s1<T, V, PF, M>
     "bwd:nhwc_bwd_fused_k3s1": [r"k_nhwc_bwd_fused_k3s1<[\w ]+, \d+, \d+, 1>"],

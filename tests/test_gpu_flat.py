@@ -34,6 +34,10 @@ CASES = [
     (2, Layer("k5_row_of_one", 9, 31, 1, 5, 1, 2)),                    # bf16: the second column of the only lane is none
     (2, Layer("k7_s2_even", 10, 32, 30, 7, 2, 3)),                     # 15 outputs a row: 8 lanes of two columns, the last half used
     (1, Layer("k5_wide_rows", 3, 9, 511, 5, 1, 2)),
+    (2, Layer("s2_pad2", 9, 40, 43, 3, 2, 2)),                         # input gradient: column pairs of an even padding, odd width
+    (2, Layer("k5_s2_pad1", 9, 40, 42, 5, 2, 1)),                      # and of an odd padding
+    (2, Layer("k7_s2_pad2", 9, 33, 34, 7, 2, 2)),
+    (2, Layer("wide_s2", 5, 60, 155, 3, 2, 1)),                        # dy from LDS in bands
     (2, Layer("m2", 10, 37, 37, 3, 1, 1, 2)),                          # output planes 2c and 2c + 1 read input plane c
     (2, Layer("m2_k5_s2", 10, 29, 31, 5, 2, 2, 2)),
     (2, Layer("m3", 7, 23, 22, 3, 1, 1, 3)),
