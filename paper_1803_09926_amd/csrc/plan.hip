@@ -106,11 +106,16 @@ static bool use_small(const Geom &g, int dtype, int pass)
 // row walk's shapes the fp32 5x5 layers at stride 1 whose arithmetic the row walk does not hide: forward and input gradient
 // (batch 64, us, row walk -> any width: 16x16x480 27 -> 17, 20x20x480 34 -> 26, 40x40x240 63 -> 48, 48x48x240 91 -> 69, 56x56x128
 // at batch 128 125 -> 102, 96x96x128 152 -> 145, 112x112x128 214 -> 210; the input gradient of 28x28x240 at batch 128 71 -> 51),
-// filter gradient up to rows of 24 (16x16 33 -> 23, 24x24 58 -> 45; 32x32 38 -> 47 and 56x56 107 -> 121 stay).  bf16 stays with
-// the packed-pair row walk (40x40x240 34 against 55).
+// filter gradient up to rows of 24 (16x16 33 -> 23, 24x24 58 -> 45; 32x32 38 -> 49 and 56x56 104 -> 114 stay).  bf16 5x5 stays with
+// the packed-pair row walk (40x40x240 35 against 42).  Of the bf16 3x3 layers at stride 1 the forward and input gradient of rows that are
+// no whole number of 16-byte vectors, which the row walk reads 8 bytes a lane (batch 64: 20x20x256 12.1 -> 9.5, 36x36x256 25.6 -> 24.5 and
+// 31 -> 22, 52x52x128 31 -> 24, 60x60x128 38 -> 32, 76x76x64 30 -> 25, 100x100x64 49 -> 47; 140x140x32 45 -> 47 stays), from 2^22 outputs on
+// (at batch 8 20x20x256 3.1 against 4.4, 36x36x256 5.7 against 6.2).
 static bool flat_over_rowwalk(const Geom &g, int dtype, int pass)
 {
-    return dtype == DT_F32 && g.K == 5 && g.s == 1 && (pass < 2 || g.W <= 24);
+    if (g.s != 1) return false;
+    if (dtype == DT_F32) return g.K == 5 && (pass < 2 || g.W <= 24);
+    return g.K == 3 && g.W % 8 != 0 && g.W <= 128 && pass < 2 && (long long)g.N * g.O * g.Ho * g.Wo >= 1 << 22;
 }
 
 static const char *flat_name(int K, int s, int pass)

@@ -53,3 +53,13 @@ def test_any_width_kernels_match_oracle(gpu_lib, N, layer, dtype):
     if layer.name != "k5_rowwalk_width" or dtype == wl.F32:
         assert dw.variant_name(d, 0).startswith("nchw_flat"), dw.variant_name(d, 0)
     gu.check_layer_full(layer, N, wl.NCHW, dtype, seed=8100 + layer.C + dtype)
+
+
+@pytest.mark.parametrize("N,layer,flat", [(16, Layer("above", 656, 20, 20), True), (16, Layer("below", 655, 20, 20), False),
+                                          (16, Layer("rows_of_24", 656, 20, 24), False)], ids=lambda v: getattr(v, "name", str(v)))
+def test_bf16_rows_of_odd_quads(gpu_lib, N, layer, flat):
+    """From 2^22 outputs on the bf16 3x3 layers whose rows are no whole number of 16-byte vectors."""
+    d = gu.desc_for(layer, N, wl.NCHW, wl.BF16)
+    for i in range(2):
+        assert dw.variant_name(d, i).startswith("nchw_flat") == flat, dw.variant_name(d, i)
+    gu.check_layer_full(layer, N, wl.NCHW, wl.BF16, seed=8200 + layer.C)
