@@ -113,8 +113,8 @@ static bool use_small(const Geom &g, int dtype, int pass)
 // (at batch 8 20x20x256 3.1 against 4.4, 36x36x256 5.7 against 6.2).
 static bool flat_over_rowwalk(const Geom &g, int dtype, int pass)
 {
-    if (g.s != 1) return false;
-    if (dtype == DT_F32) return g.K == 5 && (pass < 2 || g.W <= 24);
+    if (g.s != 1 || g.W > 512) return false;                 // (the any-width kernels take rows of up to 512)
+    if (dtype == DT_F32) return g.K == 5 && (pass < 2 || g.W <= 24) && nchwf_fwd_supported(g, dtype) && nchwf_bwd_data_supported(g, dtype);
     return g.K == 3 && g.W % 8 != 0 && g.W <= 128 && pass < 2 && (long long)g.N * g.O * g.Ho * g.Wo >= 1 << 22;
 }
 

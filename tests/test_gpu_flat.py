@@ -63,3 +63,11 @@ def test_bf16_rows_of_odd_quads(gpu_lib, N, layer, flat):
     for i in range(2):
         assert dw.variant_name(d, i).startswith("nchw_flat") == flat, dw.variant_name(d, i)
     gu.check_layer_full(layer, N, wl.NCHW, wl.BF16, seed=8200 + layer.C)
+
+
+def test_rows_above_512_stay_with_the_row_walk(gpu_lib):
+    layer = Layer("k5_516", 3, 20, 516, 5, 1, 2)
+    d = gu.desc_for(layer, 1, wl.NCHW, wl.F32)
+    for i in range(3):
+        assert dw.variant_name(d, i).startswith("nchw_rowwalk"), dw.variant_name(d, i)
+    gu.check_layer_full(layer, 1, wl.NCHW, wl.F32, seed=8250)
