@@ -318,7 +318,7 @@ __global__ __launch_bounds__(256) void k_gconv_gemm(GemmGeom g, const T *__restr
         const int tb = tile % g.tb, ta = tile / g.tb % g.ta, tn = tile / g.tb / g.ta;
         const int n0 = tn * g.TN, a0 = g.a0 + ta * g.TA, b0 = g.b0 + tb * g.TB;
         __syncthreads();                                     // the previous tile has been read (first: nothing to wait for)
-        bool bad = stage_pixels<T, NHWC, FAST>(in, lx, g.N, g.CI, g.Hi, g.Wi, n0, g.TN, g.IS * a0 - g.ip + g.lo, g.IS * b0 - g.ip + g.lo,
+        const bool bad = stage_pixels<T, NHWC, FAST>(in, lx, g.N, g.CI, g.Hi, g.Wi, n0, g.TN, g.IS * a0 - g.ip + g.lo, g.IS * b0 - g.ip + g.lo,
                                          g.LH, g.LW, ca, g.CL, g.pitch, g.packed != 0);
         if (NHWC && tile == part) {
             put_filter(threadIdx.x, wfirst);
@@ -328,11 +328,9 @@ __global__ __launch_bounds__(256) void k_gconv_gemm(GemmGeom g, const T *__restr
                 put_filter(i0, e);
             }
         }
-        if (tile == part) wbad = __syncthreads_or(wbad);      // (either is the barrier behind the staging)
-        else if (!g.packed) __syncthreads();
-        bad = wbad || (g.packed && __syncthreads_or(bad));
-
-        if (__builtin_expect(bad, 0)) {
+        // One barrier behind the staging of every tile, whatever the filter and the tile hold: both paths below read pixels that other
+        // wavefronts staged.  (wbad: what this lane laid out of the filter, so it counts for every tile of the block.)
+        if (__builtin_expect(__syncthreads_or(wbad || bad), 0)) {
             own_group_only<T, NHWC>(g, lw, lx, out, n0, a0, b0, ob, ca);
             continue;
         }

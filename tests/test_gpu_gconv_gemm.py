@@ -75,3 +75,64 @@ def test_infinity_stays_inside_its_group(layout, dtype):
         assert np.isfinite(a[others]).all()
         gu.assert_close(a[others], b[others], 1e-6 if dtype == wl.F32 else gu.TOL_BF16, "other groups")
         assert not np.isfinite(a[4 * group:4 * group + 4]).all()
+
+
+# A block of the forward and input-gradient kernels takes at most 256 positions x 16 outputs a tile and a launch has at most 2048
+# blocks, so above 2^23 outputs a block has several tiles: the filter stays, the pixels are staged over the last tile's.
+SEVERAL = [
+    ("tiles_cg8", 12, 256, 256, 32, 53, 53, 3, 1, 2),
+    ("tiles_cg16", 12, 256, 256, 16, 53, 53, 3, 1, 2),             # whole 16-channel blocks: no zeros between groups
+    ("tiles_cg4_s2", 16, 500, 500, 125, 66, 66, 3, 2, 1),
+]
+
+
+def check_several(case, layout, dtype, plant):
+    name, N, C, O, G, H, W, K, s, p = case
+    d = dw.group_desc(N, C, H, W, K, s, p, G, O, layout, dtype)
+    names = [dw.gconv_variant_name(d, i) for i in range(3)]
+    print("case", name, layout, dtype, plant, names, flush=True)
+    assert names[:2] == ["group_mfma16", "group_mfma16_bwd_data"]
+    x, w, dy = wl.make_group_inputs(N, C, O, G, H, W, K, s, p, layout, dtype, seed=80)
+    assert min(x.size, dy.size) > 1 << 23
+    w = w.copy()
+    for o, ci, kh, kw, v in plant:
+        w[(o, ci, kh, kw) if layout == wl.NCHW else (kh, kw, ci, o)] = v
+    y, dx, _ = run_gpu(case, layout, dtype, x, w, dy)
+    kw = dict(K=K, stride=s, pad=p, groups=G, O=O, layout=layout, nthreads=8)
+    tol = gu.TOL_F32 if dtype == wl.F32 else gu.TOL_BF16
+    for what, got, ref in (("fwd ", gu.to_host(y), og.fwd(x, w, **kw)), ("bwd_data ", gu.to_host(dx), og.bwd_data(dy, w, x_shape=x.shape, **kw))):
+        assert (np.isnan(got) == np.isnan(ref)).all() and (np.isinf(got) == np.isinf(ref)).all(), what + name
+        m = np.isfinite(ref)
+        assert m.all() != bool(plant)
+        gu.assert_close(np.where(m, got, 0), np.where(m, ref, 0), tol, what + name)
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("layout", [wl.NCHW, wl.NHWC], ids=["nchw", "nhwc"])
+@pytest.mark.parametrize("case", SEVERAL, ids=[c[0] for c in SEVERAL])
+def test_several_tiles_per_block(case, layout, dtype):
+    check_several(case, layout, dtype, ())
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("layout", [wl.NCHW, wl.NHWC], ids=["nchw", "nhwc"])
+@pytest.mark.parametrize("case", SEVERAL[:2], ids=[c[0] for c in SEVERAL[:2]])
+def test_several_tiles_per_block_beside_a_non_finite_filter(case, layout, dtype):
+    """Every tile of a block whose filter holds an infinity or NaN goes one output at a time, from pixels that the whole block staged."""
+    check_several(case, layout, dtype, ((1, 2, 0, 0, np.inf), (20, 5, 2, 1, -np.inf), (250, 0, 1, 1, np.nan)))
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("layout", [wl.NCHW, wl.NHWC], ids=["nchw", "nhwc"])
+def test_several_tiles_per_block_of_the_filter_gradient(layout, dtype):
+    """Partials take at most 16 MiB: 28 of them at 64 channels a group, against 32 tiles of at most 256 positions."""
+    case = ("filter_tiles", 4, 256, 256, 4, 43, 43, 3, 1, 2)
+    name, N, C, O, G, H, W, K, s, p = case
+    d = dw.group_desc(N, C, H, W, K, s, p, G, O, layout, dtype)
+    print("case", name, layout, dtype, dw.gconv_variant_name(d, 2), flush=True)
+    assert dw.gconv_variant_name(d, 2) == "group_mfma16_bwd_filter"
+    x, w, dy = wl.make_group_inputs(N, C, O, G, H, W, K, s, p, layout, dtype, seed=81)
+    assert dw.gconv_bwd_filter_workspace_bytes(d) // (w.size * 4) * 256 < dy.size // O
+    _, _, dwt = run_gpu(case, layout, dtype, x, w, dy)
+    ref = og.bwd_filter(x, dy, K=K, stride=s, pad=p, groups=G, O=O, layout=layout, nthreads=8)
+    gu.assert_close(gu.to_host(dwt), ref, gu.TOL_F32_FILTER, "bwd_filter " + name)
