@@ -12,6 +12,7 @@
 // right is one select per value read.  A step reads K values of one input row (consecutive lanes consecutive words: no bank
 // conflict) for K*K multiply-adds.  Every block is short; several blocks per compute unit overlap one's loads with
 // another's arithmetic.
+#include "bounds.hpp"
 #include "point.hpp"
 #include <type_traits>
 
@@ -50,14 +51,14 @@ __device__ __forceinline__ void dma_bands(const T *__restrict__ src, int total, 
     for (int i = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); i < nseg * nc; i += nw) {
         const int s = i / nc, ch = i - s * nc;
         const int e0 = b.first(s), a0 = e0 & ~(VE - 1), nvec = (e0 + len - a0 + VE - 1) / VE;
-        const int idx = ch * 64 + lane, a = a0 + idx * VE;
+        const int idx = ch * 64 + lane;
         T *base = lds + s * b.pitch + ch * 64 * VE;
         if (idx < nvec) {
-            if (a + VE <= total)
+            const int a = a0 + idx * VE;
+            if (vector_inside(a, VE, total))
                 __builtin_amdgcn_global_load_lds((gptr_t)(src + a), (lptr_t)base, 16, 0, 0);
             else {                                                   // the last vector of a tensor that is no whole number of vectors
-                for (int j = 0; j < VE; ++j)
-                    if (a + j < total) base[lane * VE + j] = src[a + j];
+                for (int j = 0; j < VE && a <= total - 1 - j; ++j) base[lane * VE + j] = src[a + j];
             }
         }
     }

@@ -3,6 +3,7 @@ and every validation error is reported before any HIP call (so this runs with no
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -195,6 +196,28 @@ def test_buffer_view_kernels_stay_within_two_gib_images():
     assert dw.variant_name(edge, 0) == "nhwc_rowwalk_k5s1" and dw.variant_name(edge, 1) == "nhwc_rowwalk_k5s1_flip"
     k3 = dw.desc(1, 16384, 256, 256, 3, 1, 1, 1, dw.NHWC, dw.F32)          # a 4 GiB image
     assert dw.variant_name(k3, 0) == "nhwc_rowwalk_k3s1" and dw.variant_name(k3, 2) == "nhwc_bwd_filter_k3s1"
+
+
+def test_index_arithmetic_at_the_edge_of_a_tensor(tmp_path):
+    """The last vector of a tensor of up to 2^31 - 1 elements: whole only if all its elements are there."""
+    src = tmp_path / "bounds.cpp"
+    src.write_text("""
+#include "bounds.hpp"
+#include <initializer_list>
+#include <limits.h>
+using namespace dwc;
+int main()
+{
+    for (int ve = 4; ve <= 8; ve += 4)
+        for (long long total : {1ll, 3ll, 4ll, 7ll, 8ll, 9ll, 1000ll, 1ll << 30, (1ll << 31) - 8, (1ll << 31) - 7, (1ll << 31) - 4, (1ll << 31) - 3, (1ll << 31) - 1})
+            for (long long a = total / ve * ve; a >= 0 && a > total - 3 * ve; a -= ve)
+                if (a <= INT_MAX && vector_inside((int)a, ve, (int)total) != (a + ve <= total)) return 1;
+    return 0;
+}
+""")
+    exe = tmp_path / "bounds"
+    subprocess.check_call(["g++", "-std=c++17", "-ftrapv", "-I", os.path.join(os.path.dirname(dw.__file__), "csrc"), str(src), "-o", str(exe)])
+    assert subprocess.call([str(exe)]) == 0
 
 
 # ---- group convolution entry points --------------------------------------------------------------------
