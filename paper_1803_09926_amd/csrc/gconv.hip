@@ -422,10 +422,11 @@ int gconv_bwd_filter(const dwconv_group_desc *desc, const void *x, const void *d
     else if (pl.variant == GV_GEMM) e = gconv_gemm_bwd_filter(g, desc->layout, desc->dtype, x, dy, (float *)workspace, (hipStream_t)stream);
     else e = gconv_generic_bwd_filter(g, desc->layout, desc->dtype, x, dy, (float *)workspace, pl.parts, (hipStream_t)stream);
     if (e != hipSuccess) return DWCONV_ERR_LAUNCH;
-    if (pl.variant == GV_GEMM)
-        e = reduce_partials((const float *)workspace, pl.parts, J, (float *)dw,
-                            {x, dy, desc->dtype, desc->layout, g.N, g.C, g.H, g.W, g.K, g.s, g.p, g.O, g.Cg, g.Og, g.Ho, g.Wo}, (hipStream_t)stream);
-    else e = reduce_partials((const float *)workspace, pl.parts, J, (float *)dw, (hipStream_t)stream);
+    if (pl.variant == GV_GEMM) {
+        FilterGradSrc src = {x, dy, desc->dtype, desc->layout, g.N, g.C, g.H, g.W, g.K, g.s, g.p, g.O, g.Cg, g.Og, g.Ho, g.Wo};
+        gconv_gemm_filter_tiles(g, desc->layout, desc->dtype, &src);
+        e = reduce_partials((const float *)workspace, pl.parts, J, (float *)dw, src, (hipStream_t)stream);
+    } else e = reduce_partials((const float *)workspace, pl.parts, J, (float *)dw, (hipStream_t)stream);
     return e == hipSuccess ? DWCONV_OK : DWCONV_ERR_LAUNCH;
 }
 

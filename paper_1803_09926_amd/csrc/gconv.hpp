@@ -34,6 +34,7 @@ hipError_t gconv_generic_bwd_filter(const GGeom &g, int layout, int dtype, const
 bool gconv_gemm_supported(const GGeom &g, int layout, int dtype, int pass);
 hipError_t gconv_gemm(const GGeom &g, int layout, int dtype, const void *in, const void *w, void *out, bool bwd, hipStream_t st);
 int gconv_gemm_parts(const GGeom &g, int layout, int dtype);
+void gconv_gemm_filter_tiles(const GGeom &g, int layout, int dtype, FilterGradSrc *f);       // what its partials hold
 hipError_t gconv_gemm_bwd_filter(const GGeom &g, int layout, int dtype, const void *x, const void *dy, float *ws, hipStream_t st);
 
 // ---- NCHW row-walk kernels, 3x3 stride 1 pad 1, 2, 4 or 8 channels per group on both sides (gconv_nchw.hip)

@@ -637,6 +637,15 @@ int gconv_gemm_parts(const GGeom &g, int layout, int dtype)
     return gemm_plan(g, layout, dtype, 2, &pl) ? pl.nparts * (4 / pl.npair) : 0;
 }
 
+void gconv_gemm_filter_tiles(const GGeom &g, int layout, int dtype, FilterGradSrc *f)
+{
+    GemmPlan pl;
+    gemm_plan(g, layout, dtype, 2, &pl);
+    f->TN = pl.g.TN; f->TA = pl.g.TA; f->TB = pl.g.TB;
+    f->tn = pl.g.tn; f->ta = pl.g.ta; f->tb = pl.g.tb;
+    f->per = 0; f->nparts = pl.nparts; f->splits = 4 / pl.npair;
+}
+
 template <typename T, bool NHWC>
 static hipError_t gemm_go(const GemmPlan &pl, const void *in, const void *w, void *out, hipStream_t st)
 {

@@ -97,27 +97,39 @@ __global__ __launch_bounds__(256) void k_generic_bwd_filter_nhwc(Geom g, const T
         ws[(size_t)part * (g.O * g.K * g.K) + tap * g.O + o] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
 }
 
-// Stage 2: dw[j] = sum_p ws[p*J + j].  A block owns JT consecutive j; PT = 256/JT threads per j
-// take the partials p = r, r+PT, r+2PT, ... eight at a time.  All eight loads of a batch are issued
-// before the first is used, also in the last, partly filled batch (clamped index, value dropped):
-// the kernel is a few microseconds of pure load latency, so one latency per batch is what counts.
-// The batch is added in a fixed tree, then the PT sub-sums in a fixed tree through LDS.
-// (see FilterGradSrc; every thread of the block)
-__device__ __forceinline__ float entry_inside(const FilterGradSrc &f, int j, float *red)
+// Products of entry j inside the image over the outputs of one partial, added up by the block (see FilterGradSrc).  A NaN ends the
+// sum: whatever is added stays a NaN.
+__device__ __forceinline__ float partial_inside(const FilterGradSrc &f, int j, int partial, float *red)
 {
     const bool nhwc = f.layout == LAYOUT_NHWC;
     const int KK = f.K * f.K, tap = nhwc ? j / (f.Cg * f.O) : j % KK, kh = tap / f.K, kw = tap - kh * f.K;
     const int o = nhwc ? j % f.O : j / KK / f.Cg, ci = (nhwc ? j / f.O : j / KK) % f.Cg, c = o / f.Og * f.Cg + ci;
-    const int npix = f.N * f.Ho * f.Wo;
+    const int part = partial / f.splits, split = partial - part * f.splits;
+    const int ntiles = f.tn * f.ta * f.tb, step = f.per ? 1 : f.nparts, npos = f.TN * f.TA * f.TB;
+    const int first = f.per ? part * f.per : part, last = f.per && ntiles - first > f.per ? first + f.per : ntiles;
     float acc = 0.f;
-#pragma unroll 1
-    for (int pix = threadIdx.x; pix < npix; pix += 256) {
-        const int ow = pix % f.Wo, t = pix / f.Wo, oh = t % f.Ho, n = t / f.Ho, ih = oh * f.s - f.p + kh, iw = ow * f.s - f.p + kw;
-        if ((unsigned)ih >= (unsigned)f.H || (unsigned)iw >= (unsigned)f.W) continue;
-        const size_t px = nhwc ? ((size_t)(n * f.H + ih) * f.W + iw) * f.C + c : ((size_t)(n * f.C + c) * f.H + ih) * f.W + iw;
-        const size_t py = nhwc ? (size_t)pix * f.O + o : ((size_t)(n * f.O + o) * f.Ho + oh) * f.Wo + ow;
-        acc = f.dtype == DT_F32 ? fmaf(((const float *)f.dy)[py], ((const float *)f.x)[px], acc)
-                                : fmaf(ldf((const bf16_t *)f.dy + py), ldf((const bf16_t *)f.x + px), acc);
+    for (int tile = first; tile < last; tile += step) {
+        const int tb = tile % f.tb, ta = tile / f.tb % f.ta, tn = tile / f.tb / f.ta;
+        for (int q0 = 0; q0 < npos; q0 += 256 * 8) {
+            // eight products of a lane on their way at a time
+            float a[8], b[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int q = q0 + i * 256 + (int)threadIdx.x, r = q / f.TB, im = r / f.TA;
+                const int ow = tb * f.TB + q - r * f.TB, oh = ta * f.TA + r - im * f.TA, n = tn * f.TN + im;
+                const int ih = oh * f.s - f.p + kh, iw = ow * f.s - f.p + kw;
+                a[i] = b[i] = 0.f;
+                if (q >= npos || q / 16 % f.splits != split || n >= f.N || oh >= f.Ho || ow >= f.Wo || (unsigned)ih >= (unsigned)f.H ||
+                    (unsigned)iw >= (unsigned)f.W) continue;
+                const size_t px = nhwc ? ((size_t)(n * f.H + ih) * f.W + iw) * f.C + c : ((size_t)(n * f.C + c) * f.H + ih) * f.W + iw;
+                const size_t py = nhwc ? ((size_t)(n * f.Ho + oh) * f.Wo + ow) * f.O + o : ((size_t)(n * f.O + o) * f.Ho + oh) * f.Wo + ow;
+                a[i] = f.dtype == DT_F32 ? ((const float *)f.dy)[py] : ldf((const bf16_t *)f.dy + py);
+                b[i] = f.dtype == DT_F32 ? ((const float *)f.x)[px] : ldf((const bf16_t *)f.x + px);
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc = fmaf(a[i], b[i], acc);
+            if (__syncthreads_or(acc != acc)) return __builtin_nanf("");
+        }
     }
     acc = wave_sum(acc);
     __syncthreads();
@@ -126,9 +138,38 @@ __device__ __forceinline__ float entry_inside(const FilterGradSrc &f, int j, flo
     return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
+// Entry j again: its finite partials as they are, the others from the products inside the image, until the sum is a NaN.  What costs
+// time is a partial that is not finite and whose products inside the image are no NaN, so that all of them are read: one such value
+// per channel takes one partial per entry.  (64x147x147 3x3 NCHW fp32, batch 32, finite 0.09 ms: every dy a NaN 0.36 ms, one infinity per
+// channel 2.4, in the first corner of every image and channel 21; with all of dy read for every such entry 60 to 90 in each case.)
+__device__ float entry_inside(const FilterGradSrc &f, int j, const float *ws, int parts, int J, float *red, unsigned long long *flags)
+{
+    float total = 0.f, mine = 0.f;
+    for (int p0 = 0; p0 < parts; p0 += 256) {
+        const int p = p0 + (int)threadIdx.x;
+        const float v = p < parts ? ws[(size_t)p * J + j] : 0.f;
+        const bool finite = __builtin_fabsf(v) < __builtin_inff();
+        mine += finite ? v : 0.f;
+        const unsigned long long b = __ballot(!finite);
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0) flags[threadIdx.x >> 6] = b;
+        __syncthreads();
+        for (int w = 0; w < 4; ++w)
+            for (unsigned long long m = flags[w]; m; m &= m - 1) {         // uniform
+                total += partial_inside(f, j, p0 + w * 64 + __ffsll((long long)m) - 1, red);
+                if (total != total) return total;
+            }
+    }
+    mine = wave_sum(mine);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    return ((red[0] + red[1]) + (red[2] + red[3])) + total;
+}
+
 // total[e]: the block's entries j0 + e < J, in LDS
 template <int JT, bool CHECK>
-__device__ __forceinline__ void store_entries(const FilterGradSrc &src, const float *total, int j0, int J, float *dw)
+__device__ __forceinline__ void store_entries(const FilterGradSrc &src, const float *total, int j0, const float *ws, int parts, int J, float *dw)
 {
     const int t = threadIdx.x;
     const bool mine = t < JT && j0 + t < J;
@@ -138,15 +179,21 @@ __device__ __forceinline__ void store_entries(const FilterGradSrc &src, const fl
     if constexpr (CHECK) {
         if (!__syncthreads_or(bad)) return;
         __shared__ float red[4];
+        __shared__ unsigned long long flags[4];
 #pragma unroll 1
         for (int e = 0; e < JT && j0 + e < J; ++e) {
             if (__builtin_fabsf(total[e]) < __builtin_inff()) continue;
-            const float s = entry_inside(src, j0 + e, red);
+            const float s = entry_inside(src, j0 + e, ws, parts, J, red, flags);
             if (t == 0) dw[j0 + e] = s;
         }
     }
 }
 
+// Stage 2: dw[j] = sum_p ws[p*J + j].  A block owns JT consecutive j; PT = 256/JT threads per j
+// take the partials p = r, r+PT, r+2PT, ... eight at a time.  All eight loads of a batch are issued
+// before the first is used, also in the last, partly filled batch (clamped index, value dropped):
+// the kernel is a few microseconds of pure load latency, so one latency per batch is what counts.
+// The batch is added in a fixed tree, then the PT sub-sums in a fixed tree through LDS.
 template <int JT, bool CHECK>
 __global__ __launch_bounds__(256) void k_reduce_partials(const float *__restrict__ ws, int parts, int J,
                                                          float *__restrict__ dw, FilterGradSrc src)
@@ -176,7 +223,7 @@ __global__ __launch_bounds__(256) void k_reduce_partials(const float *__restrict
         if (r < half) red[r][jj] += red[r + half][jj];
         __syncthreads();
     }
-    store_entries<JT, CHECK>(src, red[0], blockIdx.x * JT, J, dw);
+    store_entries<JT, CHECK>(src, red[0], blockIdx.x * JT, ws, parts, J, dw);
 }
 
 // The same for J a multiple of 4: a lane takes four consecutive j, so that a wavefront reads 256 to 1024 consecutive bytes of a
@@ -210,7 +257,7 @@ __global__ __launch_bounds__(256) void k_reduce_partials4(const float *__restric
         if (r < half) red[r][jj] = add(red[r][jj], red[r + half][jj]);
         __syncthreads();
     }
-    if constexpr (CHECK) store_entries<JT, true>(src, &red[0][0].x, blockIdx.x * JT, J, dw);
+    if constexpr (CHECK) store_entries<JT, true>(src, &red[0][0].x, blockIdx.x * JT, ws, parts, J, dw);
     else if (r == 0 && j < J) *reinterpret_cast<float4 *>(dw + j) = red[0][jj];
 }
 

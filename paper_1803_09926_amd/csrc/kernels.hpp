@@ -39,11 +39,15 @@ hipError_t generic_bwd_filter(const Geom &g, int layout, int dtype, const void *
 // ---- second stage of the filter-gradient reduction (generic.hip) ----------------------------
 // dw[j] = sum_{p < parts} ws[p*J + j], j < J, added in a fixed order.
 hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, hipStream_t st);
-// The same where stage 1 multiplies dy with the zeros of the padding: an entry that comes out as an infinity or NaN is added up again
-// from the products inside the image.  Depthwise: Cg = 1, Og = the multiplier.
+// The same where stage 1 multiplies dy with the zeros of the padding: of an entry that comes out as an infinity or NaN the partials that
+// are not finite are added up again from the products inside the image.  Depthwise: Cg = 1, Og = the multiplier.
 struct FilterGradSrc {
     const void *x, *dy;
     int dtype, layout, N, C, H, W, K, s, p, O, Cg, Og, Ho, Wo;
+    // What a partial holds: every outputs of tiles of TN images x TA rows x TB columns (tn x ta x tb of them, columns fastest).  Partial q
+    // holds split q % splits of the tiles of part q / splits: per >= 1: per consecutive tiles, per = 0: every nparts-th tile; a split
+    // is every splits-th run of 16 positions of a tile.
+    int TN, TA, TB, tn, ta, tb, per, nparts, splits;
 };
 hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, const FilterGradSrc &src, hipStream_t st);
 
@@ -76,6 +80,7 @@ bool nhwca_supported(const Geom &g, int pass);
 hipError_t nhwca_fwd(const Geom &g, int dtype, const void *x, const void *w, void *y, hipStream_t st);
 hipError_t nhwca_bwd_data(const Geom &g, int dtype, const void *dy, const void *w, void *dx, hipStream_t st);
 int nhwca_bwd_filter_parts(const Geom &g);
+void nhwca_bwd_filter_tiles(const Geom &g, FilterGradSrc *f);               // what its partials hold
 hipError_t nhwca_bwd_filter(const Geom &g, int dtype, const void *x, const void *dy, float *ws, hipStream_t st);
 
 // ---- NCHW kernels for rows of any width (nchw_flat.hip): K 3, 5 or 7, stride 1 or 2, any padding -----
@@ -85,6 +90,7 @@ hipError_t nchwf_fwd(const Geom &g, int dtype, const void *x, const void *w, voi
 bool nchwf_bwd_data_supported(const Geom &g, int dtype);
 hipError_t nchwf_bwd_data(const Geom &g, int dtype, const void *dy, const void *w, void *dx, hipStream_t st);
 int nchwf_bwd_filter_parts(const Geom &g, int dtype);       // 0 = unsupported
+void nchwf_bwd_filter_tiles(const Geom &g, int dtype, int parts, FilterGradSrc *f);      // what its partials hold
 hipError_t nchwf_bwd_filter(const Geom &g, int dtype, const void *x, const void *dy, float *ws, int parts, hipStream_t st);
 
 // ---- NCHW row-walk kernels for rows that are whole 16-byte vectors (nchw_direct.hip) -----------

@@ -653,6 +653,15 @@ int nchwf_bwd_filter_parts(const Geom &g, int dtype)
     return (int)((items + per - 1) / per);
 }
 
+void nchwf_bwd_filter_tiles(const Geom &g, int dtype, int parts, FilterGradSrc *f)
+{
+    FlatTile ft;
+    filter_tile(g, dtype, &ft);
+    f->TN = 1; f->TA = ft.TR; f->TB = g.Wo;
+    f->tn = g.N; f->ta = ft.nbands; f->tb = 1;
+    f->per = (g.N * ft.nbands + parts - 1) / parts; f->nparts = parts; f->splits = 1;
+}
+
 template <typename T, int K, int S, int M>
 static hipError_t conv_go(const Geom &g, int dtype, const void *in, const void *w, void *out, bool bwd, hipStream_t st)
 {

@@ -410,6 +410,15 @@ int nhwca_bwd_filter_parts(const Geom &g)
     return any_k(g) && filter_tile_any(g, &f) ? f.parts : 0;
 }
 
+void nhwca_bwd_filter_tiles(const Geom &g, FilterGradSrc *f)
+{
+    FilterTile t;
+    filter_tile_any(g, &t);
+    f->TN = 1; f->TA = t.TH; f->TB = g.Wo;
+    f->tn = g.N; f->ta = t.nstrips; f->tb = 1;
+    f->per = t.per; f->nparts = t.parts; f->splits = 1;
+}
+
 template <typename T, int V, int K, int S, int M>
 static hipError_t conv_any(const Geom &q, const void *in, const void *w, void *out, bool bwd, hipStream_t st)
 {

@@ -433,7 +433,10 @@ hipError_t launch_reduce(const Plan &pl, const Geom &g, int layout, int dtype, c
 {
     const int J = g.O * g.K * g.K;
     if (pl.variant != V_NCHWF_BWD_FILTER && pl.variant != V_NHWCA_BWD_FILTER) return reduce_partials(ws, pl.parts, J, dw, st);
-    return reduce_partials(ws, pl.parts, J, dw, {x, dy, dtype, layout, g.N, g.C, g.H, g.W, g.K, g.s, g.p, g.O, 1, g.m, g.Ho, g.Wo}, st);
+    FilterGradSrc src = {x, dy, dtype, layout, g.N, g.C, g.H, g.W, g.K, g.s, g.p, g.O, 1, g.m, g.Ho, g.Wo};
+    if (pl.variant == V_NCHWF_BWD_FILTER) nchwf_bwd_filter_tiles(g, dtype, pl.parts, &src);
+    else nhwca_bwd_filter_tiles(g, &src);
+    return reduce_partials(ws, pl.parts, J, dw, src, st);
 }
 
 hipError_t launch_bwd_fused(const Plan &pl, const Geom &g, int layout, int dtype, const void *x, const void *dy,

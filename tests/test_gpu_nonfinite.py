@@ -3,6 +3,7 @@ image, or an infinite x value in its last row or column, leaves the results that
 with the CPU oracle: the same class (finite, +inf, -inf, NaN), and where finite the same value within the tolerance of gpu_util."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import oracle.gconv as og
@@ -95,3 +96,42 @@ def test_padding_is_no_product_in_a_group(gpu_lib, case, layout, dtype):
     for what, x2, dy2 in (("dy", x, plant(dy, layout, 1, 17, 0, Wo - 1, np.inf)), ("x", plant(x, layout, 0, 3, H - 1, W - 1, np.inf), dy)):
         _, _, dwt = run_gpu(case, layout, dtype, x2, w, dy2)
         assert_same(gu.to_host(dwt), og.bwd_filter(x2, dy2, **kw), gu.TOL_F32_FILTER, "bwd_filter " + name + ", " + what)
+
+
+SLOW = [
+    (wl.NCHW, Layer("nchw_k3_odd", 64, 147, 147)),
+    (wl.NCHW, Layer("nchw_k5_odd", 64, 75, 75, 5, 1, 2)),
+    (wl.NHWC, Layer("nhwc_k5_s2", 64, 112, 112, 5, 2, 2)),
+    (wl.NHWC, Layer("nhwc_k7", 64, 57, 57, 7, 1, 3)),
+]
+
+
+@pytest.mark.parametrize("layout,layer", SLOW, ids=[c[1].name for c in SLOW])
+@pytest.mark.parametrize("what", ["every value a NaN", "one infinity a channel", "one infinity a channel and image", "every value an infinity"])
+def test_an_overflowed_step_is_no_stall(gpu_lib, layout, layer, what):
+    """The filter gradient of an overflowed step: as many milliseconds as the one-output-per-thread kernels would take at most (5 to
+    50 times the finite step), not the hundreds that adding every entry up again from all of dy takes."""
+    N = 32
+    d = gu.desc_for(layer, N, layout, wl.F32)
+    print("case", layer, what, dw.variant_name(d, 2), flush=True)
+    x, w, dy = wl.make_inputs_device(layer, N, layout, wl.F32, 85)
+    ws = torch.empty(dw.bwd_filter_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+    dwt = torch.empty(w.shape, device="cuda")
+
+    def ms(dy):
+        dw.bwd_filter(d, x, dy, dwt, ws)
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record(); dw.bwd_filter(d, x, dy, dwt, ws); b.record(); b.synchronize()
+        return a.elapsed_time(b)
+    finite = ms(dy)
+    assert torch.isfinite(dwt).all()
+    bad = dy.clone()
+    if what.startswith("every value"):
+        bad[:] = float("nan") if "NaN" in what else float("inf")
+    else:
+        v = bad if "image" in what else bad[N // 2:N // 2 + 1]
+        (v[:, :, 20, 30] if layout == wl.NCHW else v[:, 20, 30, :])[:] = float("inf")
+    taken = ms(bad)
+    print("finite %.3f ms, %s %.3f ms" % (finite, what, taken), flush=True)
+    assert not torch.isfinite(dwt).any()
+    assert taken < 10 + 50 * finite
