@@ -53,6 +53,9 @@ hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, const F
 
 // ---- NHWC row-walk kernels, multiplier 1 (nhwc.hip) ------------------------------------------
 // V = channels per lane (4 for fp32; 8 or 4 for bf16), TH = rows per strip.
+// Block width of the flat (column x channel-vector) mapping, WQ lanes a row: 256 lanes, or 128 when that leaves fewer idle lanes in the
+// last chunk of a row.
+inline int nhwc_flat_block(int WQ) { return (WQ + 127) / 128 * 128 < (WQ + 255) / 256 * 256 ? 128 : 256; }
 // stride 1, K in {3,5}, pad (K-1)/2; flip = true gives backward-data.
 // PF = rows loaded ahead of the row being consumed.
 hipError_t nhwc_s1(const Geom &g, int dtype, int V, const void *x, const void *w, void *y, bool flip, int TH, int PF,

@@ -828,19 +828,12 @@ __global__ __launch_bounds__(256, (PF <= 2 && K == 3 && S == 1 && sizeof(T) == 4
 
 static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
-// Block width for the flat (column x channel-vector) mapping: 256 lanes, or 128 when that
-// leaves fewer idle lanes in the last chunk of a row.
-static inline int flat_block(int WQ)
-{
-    const int waste256 = ceil_div(WQ, 256) * 256 - WQ, waste128 = ceil_div(WQ, 128) * 128 - WQ;
-    return waste128 < waste256 ? 128 : 256;
-}
 
 template <typename T, int V, int K, int PF, int M>
 static hipError_t launch_s1(const Geom &g, const void *x, const void *w, void *y, bool flip, int TH, hipStream_t st)
 {
     const int lanes = g.W * (g.O / V);
-    const int bs = flat_block(lanes);
+    const int bs = nhwc_flat_block(lanes);
     const int nchunks = ceil_div(lanes, bs), nstrips = ceil_div(g.H, TH);
     const unsigned nblocks = (unsigned)g.N * nchunks * nstrips;
     const int nt = stream_stores(flip ? "NHWC_S1_BWD" : "NHWC_S1_FWD", (long long)g.N * g.H * g.W * (flip ? g.C : g.O) * sizeof(T), 0);
@@ -857,7 +850,7 @@ template <typename T, int V, int K, int PF, int NCOL>
 static hipError_t launch_s1_2col(const Geom &g, const void *x, const void *w, void *y, bool flip, int TH, hipStream_t st)
 {
     const int lanes = ((g.W + NCOL - 1) / NCOL) * (g.C / V);
-    const int bs = flat_block(lanes);
+    const int bs = nhwc_flat_block(lanes);
     const int nchunks = ceil_div(lanes, bs), nstrips = ceil_div(g.H, TH);
     const unsigned nblocks = (unsigned)g.N * nchunks * nstrips;
     const int nt = stream_stores(flip ? "NHWC_S1_BWD" : "NHWC_S1_FWD", (long long)g.N * g.H * g.W * g.C * sizeof(T), 0);
@@ -906,7 +899,7 @@ hipError_t nhwc_k3s2(const Geom &g, int dtype, int V, const void *in, const void
                      hipStream_t st)
 {
     const int WoQ = g.Wo * (g.C / V);
-    const int bs = flat_block(WoQ);
+    const int bs = nhwc_flat_block(WoQ);
     const int nchunks = ceil_div(WoQ, bs), nstrips = ceil_div(g.Ho, TH);
     const unsigned nblocks = (unsigned)g.N * nchunks * nstrips;
     // forward: a wave's store is one contiguous run, and the pass is read-dominated: stream the output.

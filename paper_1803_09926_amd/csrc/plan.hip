@@ -55,6 +55,12 @@ static int nhwc_pf(const Geom &g, int dtype)
 // 4x240x40x40 5x5 20.9 -> 5.7, 3x3 15.3 -> 4.7; bf16 NHWC 8x32x112x112 9.4 -> 4.7, 16x128x56x56 10.1 -> 6.4, 64x256x28x28 12.5 ->
 // 10.1; fp32 NHWC 1x512x14x14 4.5 -> 3.0.  Half the limit leaves the NHWC 5x5 at 16.1 where this gives 6.6.
 constexpr int MIN_LANES = 65536;
+// (NCHW fp32 keeps tall strips from 2^20 outputs on: 44x32x65x20 3x3 5.9 us, with short ones 7.1; 16x64x32x32 5x5 8.6 against 10.)
+static long long nchw_lanes(const Geom &g, int dtype, int V)
+{
+    const long long rows = (long long)g.N * g.O;
+    return dtype == DT_F32 && rows * g.H * g.W >= 1 << 20 ? MIN_LANES : rows * (g.W / V);
+}
 static int pick_th(int rows, long long lanes, int stride, int dflt1 = 14, int dflt2 = 0)
 {
     // stride 2: 7 output rows, 4 on tall maps (56 output rows and more: 1-4 % on the 112x112 and 56x56 layers);
@@ -71,6 +77,10 @@ static int pick_th(int rows, long long lanes, int stride, int dflt1 = 14, int df
     const int th = ceil_div(rows, nstrips);
     return tune("DWCONV_TUNE_TH", th);
 }
+
+// Lanes that a strip of the NHWC row walks launches, idle ones at the end of a row among them: an image of 12 lanes a row is a block of 128
+// whatever the strip (338x111x4x12 5x5 fp32: 19 us in strips of 14 rows, 26 in strips of 4, which counting 12 lanes asked for).
+static long long nhwc_lanes(int N, int WQ) { const int b = nhwc_flat_block(WQ); return (long long)N * ((WQ + b - 1) / b * b); }
 
 // Strip height of the NHWC stride-1 row walk: 14 rows for fp32; 28 for bf16, whose walks are bound by their
 // vector-ALU work and pay for every halo row a strip computes again (5x5: 46.5 -> 44.2 us and 44.5 -> 41.9 us per
@@ -170,7 +180,7 @@ Plan plan_fwd(const Geom &g, int layout, int dtype)
         const int V = flat_over_rowwalk(g, dtype, 0) ? 0 : nchwd_vec(g, dtype, 0);
         if (V) {
             pl.a = V;
-            if (g.s == 1) { pl.variant = V_NCHWD_S1; pl.b = pick_th(g.H, (long long)g.N * g.O * (g.W / V), 1, nchwd_th1(dtype, g.W)); pl.name = g.K == 3 ? "nchw_rowwalk_k3s1" : "nchw_rowwalk_k5s1"; }
+            if (g.s == 1) { pl.variant = V_NCHWD_S1; pl.b = pick_th(g.H, nchw_lanes(g, dtype, V), 1, nchwd_th1(dtype, g.W)); pl.name = g.K == 3 ? "nchw_rowwalk_k3s1" : "nchw_rowwalk_k5s1"; }
             else { pl.variant = V_NCHWD_K3S2; pl.b = pick_th(g.Ho, (long long)g.N * g.O * (g.Wo / V), 2); pl.name = "nchw_rowwalk_fwd_k3s2"; }
             return pl;
         }
@@ -180,10 +190,10 @@ Plan plan_fwd(const Geom &g, int layout, int dtype)
     if (layout == LAYOUT_NHWC) {
         const int V = nhwc_vec(g, dtype);
         if (V && same_pad_s1(g)) {
-            pl.variant = V_NHWC_S1; pl.a = V; pl.b = pick_th(g.H, (long long)g.N * g.W * (g.O / V), 1, nhwc_th1(dtype));
+            pl.variant = V_NHWC_S1; pl.a = V; pl.b = pick_th(g.H, nhwc_lanes(g.N, g.W * (g.O / V)), 1, nhwc_th1(dtype));
             pl.name = g.m == 2 ? "nhwc_rowwalk_k3s1_m2" : (g.K == 3 ? "nhwc_rowwalk_k3s1" : "nhwc_rowwalk_k5s1");
         } else if (V && k3s2p1(g)) {
-            pl.variant = V_NHWC_K3S2; pl.a = V; pl.b = pick_th(g.Ho, (long long)g.N * g.Wo * (g.O / V), 2);
+            pl.variant = V_NHWC_K3S2; pl.a = V; pl.b = pick_th(g.Ho, nhwc_lanes(g.N, g.Wo * (g.O / V)), 2);
             pl.name = "nhwc_rowwalk_fwd_k3s2";
         } else plan_any(g, 0, pl);
     }
@@ -202,7 +212,7 @@ Plan plan_bwd_data(const Geom &g, int layout, int dtype)
         const int V = flat_over_rowwalk(g, dtype, 1) ? 0 : nchwd_vec(g, dtype, 1);
         if (V) {
             pl.a = V;
-            if (g.s == 1) { pl.variant = V_NCHWD_S1; pl.b = pick_th(g.H, (long long)g.N * g.O * (g.W / V), 1, nchwd_th1(dtype, g.W)); pl.name = g.K == 3 ? "nchw_rowwalk_k3s1_flip" : "nchw_rowwalk_k5s1_flip"; }
+            if (g.s == 1) { pl.variant = V_NCHWD_S1; pl.b = pick_th(g.H, nchw_lanes(g, dtype, V), 1, nchwd_th1(dtype, g.W)); pl.name = g.K == 3 ? "nchw_rowwalk_k3s1_flip" : "nchw_rowwalk_k5s1_flip"; }
             else { pl.variant = V_NCHWD_K3S2; pl.b = pick_th(g.Ho, (long long)g.N * g.O * (g.Wo / V), 2, 14, g.Ho >= 56 ? 2 : 4); pl.name = "nchw_rowwalk_bwd_data_k3s2"; }
             return pl;
         }
@@ -212,10 +222,10 @@ Plan plan_bwd_data(const Geom &g, int layout, int dtype)
     if (layout == LAYOUT_NHWC) {
         const int V = nhwc_vec(g, dtype);
         if (V && same_pad_s1(g)) {
-            pl.variant = V_NHWC_S1; pl.a = V; pl.b = pick_th(g.H, (long long)g.N * g.W * (g.O / V), 1, nhwc_th1(dtype));
+            pl.variant = V_NHWC_S1; pl.a = V; pl.b = pick_th(g.H, nhwc_lanes(g.N, g.W * (g.O / V)), 1, nhwc_th1(dtype));
             pl.name = g.m == 2 ? "nhwc_rowwalk_k3s1_flip_m2" : (g.K == 3 ? "nhwc_rowwalk_k3s1_flip" : "nhwc_rowwalk_k5s1_flip");
         } else if (V && k3s2p1(g)) {
-            pl.variant = V_NHWC_K3S2; pl.a = V; pl.b = pick_th(g.Ho, (long long)g.N * g.Wo * (g.O / V), 2, 14, 4);
+            pl.variant = V_NHWC_K3S2; pl.a = V; pl.b = pick_th(g.Ho, nhwc_lanes(g.N, g.Wo * (g.O / V)), 2, 14, 4);
             pl.name = "nhwc_rowwalk_bwd_data_k3s2";
         } else plan_any(g, 1, pl);
     }
