@@ -21,6 +21,7 @@ struct AnyGeom {
     int N, Ci, Co, Hi, Wi, Ho, Wo;   // of the tensor read and the tensor written
     int pad, mdiv;                   // input row oh*S - pad + kh; input channel = output channel / mdiv (forward, V = 1)
     int TH, nstrips, nchunks;        // rows per strip (bwd_data_s2: row pairs)
+    int TW, ncols;                   // filter gradient: columns of an item, items across a row
 };
 
 template <typename T, int V> __device__ __forceinline__ void load_filter_vec(const T *w, float (&r)[V])
@@ -238,7 +239,7 @@ __global__ __launch_bounds__(256) void k_nhwca_bwd_data_s2(AnyGeom g, const T *_
 }
 
 // ---------------------------------------------------------------------------------------------
-// Filter gradient, stage 1.  A block: CT channel vectors x 256/CT columns; it takes (image, strip) items and, in each, every
+// Filter gradient, stage 1.  A block: CT channel vectors x 256/CT columns; it takes (image, strip, part of a row) items and, in each, every
 // column tile, so that it writes one partial for all of them.  A lane keeps K*K*V sums against a window of the last
 // ceil(K/S) dy rows.
 // ---------------------------------------------------------------------------------------------
@@ -261,15 +262,16 @@ __global__ __launch_bounds__(256) void k_nhwca_bwd_filter(AnyGeom g, const T *__
 #pragma unroll
             for (int v = 0; v < V; ++v) acc[kh][kw][v] = 0.f;
 
-    const int it1 = min(g.N * g.nstrips, (part + 1) * per_part);
+    const int it1 = min(g.N * g.nstrips * g.ncols, (part + 1) * per_part);
     for (int it = part * per_part; it < it1; ++it) {
-        const int n = it / g.nstrips, strip = it - n * g.nstrips;
+        const int row = it / g.ncols, col0 = (it - row * g.ncols) * g.TW, col1 = min(g.Wo, col0 + g.TW);
+        const int n = row / g.nstrips, strip = row - n * g.nstrips;
         const int oh0 = strip * g.TH, oh1 = min(g.Ho, oh0 + g.TH), rows = oh1 - oh0, steps = rows + NA - 1;
         const BufView vx(x + (size_t)n * g.Hi * g.Wi * g.Ci, (uint32_t)g.Hi * g.Wi * g.Ci * esz);
         const BufView vd(dy + (size_t)n * g.Ho * g.Wo * g.Co, (uint32_t)g.Ho * g.Wo * g.Co * esz);
-        for (int ow0 = 0; ow0 < g.Wo; ow0 += nty) {
+        for (int ow0 = col0; ow0 < col1; ow0 += nty) {
             const int ow = ow0 + ty;
-            const bool live = ow < g.Wo && cq < Q;           // the other lanes read zeros
+            const bool live = ow < col1 && cq < Q;           // the other lanes read zeros
             const uint32_t offd = live ? (uint32_t)(ow * g.Co + c) * esz : BufView::OUTSIDE;
             uint32_t off[K];
 #pragma unroll
@@ -364,29 +366,66 @@ int any_strips(int rows, int target, long long lanes)
     return cdiva(rows, n);
 }
 
+// Block size of the walks without a reduction: the one that leaves the fewest lanes of a row's last block idle (a row of 7 columns x 2
+// channels is 14 lanes), the largest of equals.
+int any_block(long long lanes)
+{
+    int best = 256;
+    for (int b = 192; b >= 64; b -= 64)
+        if ((lanes + b - 1) / b * b < (lanes + best - 1) / best * best) best = b;
+    return best;
+}
+
 int s2a_cols(const Geom &g) { return (g.W - 1 + g.p) / 2 - g.p / 2 + 1; }
 int s2a_pairs(const Geom &g) { return (g.H - 1 + g.p) / 2 - g.p / 2 + 1; }
 
-struct FilterTile { int V, CT, nct, TH, nstrips, parts, per; };
+// Launch of a walk without a reduction over `rows` rows of `lanes` lanes of N images.
+struct WalkTile { int TH, nstrips, bs, nchunks; long long blocks; };
+WalkTile walk_tile(int N, int rows, long long lanes, int target)
+{
+    WalkTile t;
+    t.TH = any_strips(rows, target, lanes * N);
+    t.nstrips = cdiva(rows, t.TH);
+    t.bs = any_block(lanes);
+    t.nchunks = (int)((lanes + t.bs - 1) / t.bs);
+    t.blocks = (long long)N * t.nstrips * t.nchunks;
+    return t;
+}
+WalkTile walk_tile(const Geom &g, int pass)
+{
+    const int V = any_vec(g), target = g.K == 3 ? 14 : 28;
+    if (pass == 0) return walk_tile(g.N, g.Ho, (long long)g.Wo * (g.O / V), target);
+    if (g.s == 1) return walk_tile(g.N, g.H, (long long)g.W * (g.C / V), target);
+    return walk_tile(g.N, s2a_pairs(g), (long long)s2a_cols(g) * (g.C / V), 14);
+}
+
+struct FilterTile { int V, CT, nct, TH, nstrips, TW, ncols, parts, per; };
 bool filter_tile_any(const Geom &g, FilterTile *f)
 {
     f->V = any_vec(g);
     const int Q = g.O / f->V;
-    // channel vectors across a block: the widest power of two that leaves few lanes idle
+    // channel vectors across a block: the widest power of two that leaves few lanes idle, across the channels and across the columns that
+    // the other lanes take (181x3x3x572 7x7 fp32: two across, as the channels alone would have it, 265 us with 3 of 128 columns there)
     int best = 0;
     double beste = 0.0;
     for (int ct = 64; ct >= 1; ct /= 2) {
-        const double e = (double)Q / (cdiva(Q, ct) * ct);
-        if (e > beste + 0.1) { beste = e; best = ct; }
+        const int nty = 256 / ct;
+        const double e = (double)Q / (cdiva(Q, ct) * ct) * ((double)g.Wo / ((double)cdiva(g.Wo, nty) * nty));
+        if (e > beste * 1.1) { beste = e; best = ct; }
     }
     f->CT = best; f->nct = cdiva(Q, best);
-    // about 768 blocks; strips only where there are not enough images
-    const int want = 768;
+    // about 768 blocks; strips only where there are not enough images, parts of a row only where there are not enough strips
+    const int want = 768, nty = 256 / best;
     int TH = g.Ho;
     while (TH > 7 && (long long)g.N * cdiva(g.Ho, TH) * f->nct < want) TH = (TH + 1) / 2;
     f->TH = cdiva(g.Ho, cdiva(g.Ho, TH));
     f->nstrips = cdiva(g.Ho, f->TH);
-    const long long items = (long long)g.N * f->nstrips, J = (long long)g.O * g.K * g.K;
+    const long long rows = (long long)g.N * f->nstrips;
+    int tiles = cdiva(g.Wo, nty);
+    while (tiles > 1 && rows * cdiva(cdiva(g.Wo, nty), tiles) * f->nct < want) tiles = (tiles + 1) / 2;
+    f->TW = tiles * nty;
+    f->ncols = cdiva(g.Wo, f->TW);
+    const long long items = rows * f->ncols, J = (long long)g.O * g.K * g.K;
     long long parts = cdiva(want, f->nct);
     if (parts > items) parts = items;
     if (parts * J * 4 > (8 << 20)) parts = (8 << 20) / (J * 4);
@@ -401,8 +440,12 @@ bool filter_tile_any(const Geom &g, FilterTile *f)
 bool nhwca_supported(const Geom &g, int pass)
 {
     if (!any_k(g)) return false;
-    return pass != 1 || g.m <= 2;
+    if (pass == 2) return true;
+    const WalkTile t = walk_tile(g, pass);
+    return t.blocks < (1LL << 31) && (pass != 1 || g.m <= 2);
 }
+
+int nhwca_row_lanes(const Geom &g) { return g.Wo * (g.O / any_vec(g)); }
 
 int nhwca_bwd_filter_parts(const Geom &g)
 {
@@ -414,40 +457,31 @@ void nhwca_bwd_filter_tiles(const Geom &g, FilterGradSrc *f)
 {
     FilterTile t;
     filter_tile_any(g, &t);
-    f->TN = 1; f->TA = t.TH; f->TB = g.Wo;
-    f->tn = g.N; f->ta = t.nstrips; f->tb = 1;
+    f->TN = 1; f->TA = t.TH; f->TB = t.TW;
+    f->tn = g.N; f->ta = t.nstrips; f->tb = t.ncols;
     f->per = t.per; f->nparts = t.parts; f->splits = 1;
 }
 
 template <typename T, int V, int K, int S, int M>
 static hipError_t conv_any(const Geom &q, const void *in, const void *w, void *out, bool bwd, hipStream_t st)
 {
-    AnyGeom g = bwd ? AnyGeom{q.N, q.O, q.C, q.Ho, q.Wo, q.H, q.W, K - 1 - q.p, 1, 0, 0, 0}
-                    : AnyGeom{q.N, q.C, q.O, q.H, q.W, q.Ho, q.Wo, q.p, q.m, 0, 0, 0};
-    const long long lanes = (long long)g.Wo * (g.Co / V);
-    g.TH = any_strips(g.Ho, K == 3 ? 14 : 28, lanes * g.N);
-    g.nstrips = cdiva(g.Ho, g.TH);
-    g.nchunks = (int)((lanes + 255) / 256);
-    const long long nb = (long long)g.N * g.nstrips * g.nchunks;
-    if (nb >= (1LL << 31)) return hipErrorInvalidValue;
-    const unsigned nblocks = (unsigned)nb;
-    hipLaunchKernelGGL((k_nhwca_conv<T, V, K, S, M>), dim3(nblocks), dim3(256), 0, st, g, (const T *)in, (const T *)w, (T *)out, q.O, bwd ? 1 : 0,
+    AnyGeom g = bwd ? AnyGeom{q.N, q.O, q.C, q.Ho, q.Wo, q.H, q.W, K - 1 - q.p, 1, 0, 0, 0, 0, 0}
+                    : AnyGeom{q.N, q.C, q.O, q.H, q.W, q.Ho, q.Wo, q.p, q.m, 0, 0, 0, 0, 0};
+    const WalkTile t = walk_tile(q, bwd ? 1 : 0);
+    g.TH = t.TH; g.nstrips = t.nstrips; g.nchunks = t.nchunks;
+    const unsigned nblocks = (unsigned)t.blocks;
+    hipLaunchKernelGGL((k_nhwca_conv<T, V, K, S, M>), dim3(nblocks), dim3(t.bs), 0, st, g, (const T *)in, (const T *)w, (T *)out, q.O, bwd ? 1 : 0,
                        nblocks, stream_stores("NHWCA", 0, 0), q);
     return hipGetLastError();
 }
 template <typename T, int V, int K, int M>
 static hipError_t s2_any(const Geom &q, const void *dy, const void *w, void *dx, hipStream_t st)
 {
-    AnyGeom g = {q.N, q.O, q.C, q.Ho, q.Wo, q.H, q.W, q.p, 1, 0, 0, 0};
-    const int NB = s2a_cols(q), pairs = s2a_pairs(q);
-    const long long lanes = (long long)NB * (g.Co / V);
-    g.TH = any_strips(pairs, 14, lanes * g.N);
-    g.nstrips = cdiva(pairs, g.TH);
-    g.nchunks = (int)((lanes + 255) / 256);
-    const long long nb = (long long)g.N * g.nstrips * g.nchunks;
-    if (nb >= (1LL << 31)) return hipErrorInvalidValue;
-    const unsigned nblocks = (unsigned)nb;
-    hipLaunchKernelGGL((k_nhwca_bwd_data_s2<T, V, K, M>), dim3(nblocks), dim3(256), 0, st, g, (const T *)dy, (const T *)w, (T *)dx, NB, nblocks,
+    AnyGeom g = {q.N, q.O, q.C, q.Ho, q.Wo, q.H, q.W, q.p, 1, 0, 0, 0, 0, 0};
+    const WalkTile t = walk_tile(q, 1);
+    g.TH = t.TH; g.nstrips = t.nstrips; g.nchunks = t.nchunks;
+    const unsigned nblocks = (unsigned)t.blocks;
+    hipLaunchKernelGGL((k_nhwca_bwd_data_s2<T, V, K, M>), dim3(nblocks), dim3(t.bs), 0, st, g, (const T *)dy, (const T *)w, (T *)dx, s2a_cols(q), nblocks,
                        stream_stores("NHWCA", 0, 0), q);
     return hipGetLastError();
 }
@@ -456,7 +490,7 @@ static hipError_t filter_any(const Geom &q, const void *x, const void *dy, float
 {
     FilterTile f;
     filter_tile_any(q, &f);
-    const AnyGeom g = {q.N, q.C, q.O, q.H, q.W, q.Ho, q.Wo, q.p, q.m, f.TH, f.nstrips, 0};
+    const AnyGeom g = {q.N, q.C, q.O, q.H, q.W, q.Ho, q.Wo, q.p, q.m, f.TH, f.nstrips, 0, f.TW, f.ncols};
     const unsigned nblocks = (unsigned)f.parts * f.nct;
     hipLaunchKernelGGL((k_nhwca_bwd_filter<T, V, K, S>), dim3(nblocks), dim3(256), 0, st, g, (const T *)x, (const T *)dy, ws, f.CT, f.parts, f.per,
                        nblocks);

@@ -164,8 +164,17 @@ static bool plan_any(const Geom &g, int pass, Plan &pl)
          {"nhwc_any_k7s1_flip", "nhwc_any_bwd_data_k7s2"}},
         {{"nhwc_any_bwd_filter_k3s1", "nhwc_any_bwd_filter_k3s2"}, {"nhwc_any_bwd_filter_k5s1", "nhwc_any_bwd_filter_k5s2"},
          {"nhwc_any_bwd_filter_k7s1", "nhwc_any_bwd_filter_k7s2"}}};
-    // (a forward pass of a few thousand outputs is as fast one output per thread: 2x9x9x6 3.0 us against 2.5)
-    if ((pass == 0 && (long long)g.N * g.O * g.Ho * g.Wo < 2048) || !nhwca_supported(g, pass)) return false;
+    if (!nhwca_supported(g, pass)) return false;
+    const long long pixels = (long long)g.N * g.Ho * g.Wo;
+    if (pass == 0) {
+        // a forward pass of a few thousand outputs is as fast one output per thread (2x9x9x6 3.0 us against 2.5), and so is one whose rows
+        // have so few lanes that most of a wavefront is idle (422x101x4x1 pad 0, multiplier 2 4.7 against 7.7, 506x90x3x2 5x5 stride 2 5.3 against 20)
+        if (pixels * g.O < 2048) return false;
+        if (nhwca_row_lanes(g) <= 4 && (long long)g.N * g.Ho >= 4096) return false;
+    }
+    // The filter gradient of a few pixels: the reduction over the block is longer than the sums (us, generic against this kernel, 3x3 up to
+    // 16 pixels 5.7 / 6.3, 32 6.7 / 6.2; 5x5 16 5.6 / 7.6, 64 8.8 / 7.5; 7x7 16 5.7 / 10.5, 64 8.4 / 10.9, 128 15.2 / 11.1).
+    if (pass == 2 && pixels < 2 * g.K * g.K) return false;
     if (pass == 2) pl.parts = nhwca_bwd_filter_parts(g);
     pl.variant = pass == 0 ? V_NHWCA_FWD : pass == 1 ? V_NHWCA_BWD_DATA : V_NHWCA_BWD_FILTER;
     pl.name = names[pass][(g.K - 3) / 2][g.s - 1];

@@ -138,6 +138,17 @@ def test_generic_fallback_is_selected_for_untuned_shapes():
     assert dw.variant_name(dw.desc(2, 8, 9, 9, 3, 3, 1, 1, dw.NHWC), 2) == "generic"       # stride 3
 
 
+def test_shapes_too_small_for_the_nhwc_walks_stay_generic():
+    """Where a block's fixed work is longer than the sums, or a row has work for a few lanes of a wavefront only."""
+    for K, pixels in ((3, 18), (5, 50), (7, 98)):
+        for n in (pixels - 1, pixels):
+            d = dw.desc(n, 7, 1, 1, K, 2, K // 2, 1, dw.NHWC)          # n images of one output pixel
+            assert dw.variant_name(d, 2) == ("generic" if n < pixels else "nhwc_any_bwd_filter_k%ds2" % K), (K, n)
+    assert dw.variant_name(dw.desc(64, 1, 101, 4, 3, 1, 1, 1, dw.NHWC), 0) == "generic"      # 4 lanes a row, 6464 rows
+    assert dw.variant_name(dw.desc(64, 1, 101, 5, 3, 1, 1, 1, dw.NHWC), 0) == "nhwc_any_k3s1"
+    assert dw.variant_name(dw.desc(16, 1, 101, 8, 3, 2, 1, 1, dw.NHWC), 0) == "nhwc_any_k3s2"         # 4 lanes, 816 rows
+
+
 def test_whole_backward_entry_point_validates_before_launch():
     lib = dw.load()
     for layout in (dw.NCHW, dw.NHWC):

@@ -31,6 +31,10 @@ CASES = [
     (2, Layer("m3", 10, 16, 17, 3, 1, 1, 3)),                         # (its input gradient stays generic)
     (1, Layer("tall", 6, 300, 5, 5, 2, 2)),                           # many strips
     (1, Layer("wide", 6, 5, 700, 7, 1, 3)),
+    (40, Layer("rows_of_7_lanes", 2, 30, 7, 7, 1, 3)),                # blocks of one wavefront, most of it idle
+    (2, Layer("rows_of_300_lanes", 6, 20, 100)),                      # blocks of 192
+    (1, Layer("rows_in_parts", 97, 4, 278, 5, 1, 2)),                 # one image, few rows: the filter gradient splits the columns
+    (31, Layer("images_of_9", 66, 3, 3, 7, 1, 3)),
 ]
 
 

@@ -28,6 +28,7 @@ LAYERS = [
     (wl.NHWC, 2, Layer("nhwc_k5_s2", 32, 57, 56, 5, 2, 2)),
     (wl.NHWC, 2, Layer("nhwc_k7", 92, 28, 28, 7, 1, 3)),               # 4508 filter entries: four a lane in the second stage
     (wl.NHWC, 2, Layer("nhwc_m2_s2", 30, 40, 41, 3, 2, 1, 2)),
+    (wl.NHWC, 1, Layer("nhwc_rows_in_parts", 64, 4, 278, 5, 1, 1)),    # partials of parts of a row
 ]
 GROUPS = [("cg16", 2, 64, 64, 4, 14, 15, 3, 1, 1), ("cg16_s2", 2, 64, 64, 4, 28, 27, 3, 2, 1), ("cg8_s2", 2, 32, 32, 4, 21, 23, 3, 2, 1)]
 
