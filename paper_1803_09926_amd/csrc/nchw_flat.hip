@@ -523,16 +523,18 @@ void pick_lanes(int cols, int planes, int maxu, int *U, int *threads)
 inline int lds_target(int K) { return K == 3 ? 32 << 10 : 40 << 10; }
 constexpr int LDS_WHOLE = 40 << 10;
 constexpr int LDS_MOST = 64 << 10;
+constexpr int MIN_LANES = 65536;
 
 inline int round_up(int a, int b) { return (a + b - 1) / b * b; }
 
 int second_area(const FlatTile &ft) { return GUARD + ft.U * ft.pout; }       // LDS elements of the dy bands of a tile
 
 // Tile of a launch: `cols` lanes per plane; a band of t units (rows, or row pairs) needs in_rows(t) input rows; Mi input planes per
-// output plane, or mdiv output planes per input plane; second: bands of the output rows are in LDS too.
+// output plane, or mdiv output planes per input plane; copies: launches of the planes side by side (images of the filter gradient);
+// second: bands of the output rows are in LDS too.
 template <typename FI>
 bool pick_tile(int esz, int cols, int units, int nplanes, int maxu, int Hi, int Wi, int Ho, int Wo, FI in_rows, int Mi, int mdiv,
-               int target, FlatTile *ft, bool second = false)
+               int target, FlatTile *ft, int copies, bool second = false)
 {
     const int VE = 16 / esz;
     // a block's planes are one buffer view (2 GiB at most)
@@ -562,7 +564,16 @@ bool pick_tile(int esz, int cols, int units, int nplanes, int maxu, int Hi, int 
         // balanced bands
         const int nb = (units + t - 1) / t;
         t = (units + nb - 1) / nb;
-        if (lds(t, ft) <= LDS_MOST && (t >= 4 || t >= units || ft->U == 1)) return true;
+        if (lds(t, ft) <= LDS_MOST && (t >= 4 || t >= units || ft->U == 1)) {
+            // A launch of fewer than MIN_LANES lanes is one short round of blocks, each as long as its band: bands of half the height,
+            // and half again down to four rows.
+            const long long groups = (long long)((nplanes - 1) / ft->U + 1) * copies;
+            while (ft->TR > 4 && groups * ft->nbands * ft->threads < MIN_LANES) {
+                const int h = (ft->TR + 1) / 2, n = (units + h - 1) / h;
+                lds((units + n - 1) / n, ft);
+            }
+            return true;
+        }
         if (ft->U == 1) return false;
         ft->U = (ft->U + 1) / 2;
         ft->threads = (ft->U * cols + 63) / 64 * 64;
@@ -592,8 +603,8 @@ bool conv_tile(const Geom &g, int dtype, bool bwd, FlatTile *ft)
     const int esz = dtype == DT_F32 ? 4 : 2, nc = flat_cols(g, dtype), cols = ((bwd ? g.W : g.Wo) + nc - 1) / nc;
     auto in_rows = [&](int t) { return (t - 1) * g.s + g.K; };
     if (!bwd)
-        return pick_tile(esz, cols, g.Ho, g.N * g.O, most_planes((long long)g.N * g.O, g.Ho, cols), g.H, g.W, g.Ho, g.Wo, in_rows, 1, g.m, lds_target(g.K), ft);
-    return pick_tile(esz, cols, g.H, g.N * g.C, most_planes((long long)g.N * g.C, g.H, cols), g.Ho, g.Wo, g.H, g.W, in_rows, g.m, 1, lds_target(g.K), ft);
+        return pick_tile(esz, cols, g.Ho, g.N * g.O, most_planes((long long)g.N * g.O, g.Ho, cols), g.H, g.W, g.Ho, g.Wo, in_rows, 1, g.m, lds_target(g.K), ft, 1);
+    return pick_tile(esz, cols, g.H, g.N * g.C, most_planes((long long)g.N * g.C, g.H, cols), g.Ho, g.Wo, g.H, g.W, in_rows, g.m, 1, lds_target(g.K), ft, 1);
 }
 
 int s2_cols(const Geom &g) { return (g.W + 1) / 2; }
@@ -603,7 +614,7 @@ bool s2_tile(const Geom &g, int dtype, FlatTile *ft)
     const int esz = dtype == DT_F32 ? 4 : 2, NA = (g.K + 1) / 2;
     auto in_rows = [&](int t) { return t + NA - 1; };
     return pick_tile(esz, s2_cols(g), s2_pairs(g), g.N * g.C, most_planes((long long)g.N * g.C, g.H, s2_cols(g)), g.Ho, g.Wo, g.H, g.W, in_rows, g.m, 1,
-                     lds_target(g.K), ft);
+                     lds_target(g.K), ft, 1);
 }
 // Whether the filter gradient reads dy from LDS too.  Every dy value is read once, by one lane, so that it needs no LDS, and without it
 // more blocks fit a compute unit: 28x28x256 7x7 fp32 batch 64 54 -> 42 us, 37x37x256 multiplier 2 41 -> 32, 19x19x728 bf16 17 -> 15,
@@ -616,7 +627,7 @@ bool filter_tile(const Geom &g, int dtype, FlatTile *ft)
     const int esz = dtype == DT_F32 ? 4 : 2, nc = flat_cols(g, dtype), cols = (g.Wo + nc - 1) / nc;
     auto in_rows = [&](int t) { return (t - 1) * g.s + g.K; };
     auto pick = [&](bool second) {
-        return pick_tile(esz, cols, g.Ho, g.O, most_planes((long long)g.N * g.O, g.Ho, cols), g.H, g.W, g.Ho, g.Wo, in_rows, 1, g.m, lds_target(g.K), ft, second);
+        return pick_tile(esz, cols, g.Ho, g.O, most_planes((long long)g.N * g.O, g.Ho, cols), g.H, g.W, g.Ho, g.Wo, in_rows, 1, g.m, lds_target(g.K), ft, g.N, second);
     };
     const bool lds = g.K == 3 ? dtype == DT_BF16 || g.s == 2 : g.K == 5 && g.s == 1 && dtype == DT_F32;      // DY_LDS
     return (lds && pick(true) && ft->nbands > 1) || pick(false);

@@ -42,6 +42,10 @@ CASES = [
     (2, Layer("m2_k5_s2", 10, 29, 31, 5, 2, 2, 2)),
     (2, Layer("m3", 7, 23, 22, 3, 1, 1, 3)),
     (5, Layer("m2_k7", 12, 20, 21, 7, 1, 3, 2)),
+    (1, Layer("few_tall_k7", 3, 149, 33, 7, 1, 3)),                    # few blocks: bands of four rows
+    (2, Layer("few_tall_s2", 2, 146, 147, 3, 2, 1)),
+    (1, Layer("few_tall_k5_m2", 2, 131, 30, 5, 1, 2, 2)),
+    (1, Layer("few_short", 2, 5, 130, 5, 1, 2)),                       # one band that is not cut
 ]
 
 
