@@ -348,7 +348,7 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_data_s2(const T *__restrict__
 // them against a window of the last K/S dy rows.  The columns of a channel are added through LDS in a fixed order at the end,
 // one partial per block.
 // ---------------------------------------------------------------------------------------------
-template <typename T, int K, int S, bool SAME, int NC, bool DYLDS>
+template <typename T, int K, int S, bool SAME, int NC, bool DYLDS, int SETS>
 __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__restrict__ x, const T *__restrict__ dy,
                                                           float *__restrict__ ws, int parts, int per_part, FlatTile ft,
                                                           unsigned nblocks)
@@ -373,11 +373,10 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__res
     uint32_t offd[NC];
 #pragma unroll
     for (int n = 0; n < NC; ++n) offd[n] = active && ow + n < g.Wo ? (uint32_t)(u * g.Ho * g.Wo + ow + n) * (uint32_t)sizeof(T) : BufView::OUTSIDE;
-    float acc[K][K];
+    // SETS = 2: steps add to either set in turn
+    float acc[SETS][K][K];
 #pragma unroll
-    for (int kh = 0; kh < K; ++kh)
-#pragma unroll
-        for (int kw = 0; kw < K; ++kw) acc[kh][kw] = 0.f;
+    for (int e = 0; e < SETS * K * K; ++e) acc[e / (K * K)][e / K % K][e % K] = 0.f;
 
     const int items = g.N * ft.nbands, it1 = min(items, (part + 1) * per_part);
     for (int it = part * per_part; it < it1; ++it) {
@@ -417,7 +416,7 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__res
         __syncthreads();
         // step t: the S x rows from row (oh0 + t)*S - p on, against dy rows oh0 + t - i; steps [ta, tb) have all of them in the band
         const int base = oh0 * S - g.p - r0, nrows = r1 - r0;
-        auto step = [&](int t, auto checked) {
+        auto step = [&](int t, auto checked, int set) {
             constexpr bool CK = decltype(checked)::value;
 #pragma unroll
             for (int n = 0; n < NC; ++n) {
@@ -451,7 +450,7 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__res
 #pragma unroll
                     for (int kw = 0; kw < K; ++kw)
 #pragma unroll
-                        for (int n = 0; n < NC; ++n) acc[j + i * S][kw] = fmaf(d[i][n], v[n * S + kw], acc[j + i * S][kw]);
+                        for (int n = 0; n < NC; ++n) acc[set][j + i * S][kw] = fmaf(d[i][n], v[n * S + kw], acc[set][j + i * S][kw]);
                 }
             }
 #pragma unroll
@@ -461,10 +460,18 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__res
         };
         const int ta = (S - 1 - base) / S, tb = min((nrows - base) / S, rows);
         int t = 0;
-        for (; t < min(K > 3 ? max(ta, NA - 1) : ta, steps); ++t) step(t, std::true_type());
-#pragma unroll DYLDS ? NA : PD
-        for (; t < tb; ++t) step(t, std::false_type());
-        for (; t < steps; ++t) step(t, std::true_type());
+        constexpr int UN = DYLDS ? NA : PD;                 // steps after which the windows are in the same registers
+        for (; t < min(K > 3 ? max(ta, NA - 1) : ta, steps); ++t) step(t, std::true_type(), 0);
+        if constexpr (SETS == 2) {
+#pragma unroll 1
+            for (; t + UN <= tb; t += UN) {
+#pragma unroll
+                for (int i = 0; i < UN; ++i) step(t + i, std::false_type(), i % 2);
+            }
+        }
+#pragma unroll SETS == 2 ? 1 : UN
+        for (; t < tb; ++t) step(t, std::false_type(), 0);
+        for (; t < steps; ++t) step(t, std::true_type(), 0);
         __syncthreads();
     }
 
@@ -478,15 +485,27 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__res
         const int ne = K * K - e0 < CH ? K * K - e0 : CH;
 #pragma unroll
         for (int e = 0; e < CH; ++e)
-            if (e0 + e < K * K) red[e * nt + threadIdx.x] = acc[(e0 + e) / K][(e0 + e) % K];
+            if (e0 + e < K * K) {
+                const float s = acc[0][(e0 + e) / K][(e0 + e) % K];
+                red[e * nt + threadIdx.x] = SETS == 2 ? s + acc[SETS - 1][(e0 + e) / K][(e0 + e) % K] : s;
+            }
         __syncthreads();
         const int jobs = np * ne;
         for (int f0 = 0; f0 < jobs * Q; f0 += nt) {        // uniform trip count
             const int f = f0 + (int)threadIdx.x, job = f / Q, q = f & (Q - 1);
             const int uj = job / ne, e = job - uj * ne;
             float s = 0.f;
-            if (job < jobs)
-                for (int i = q; i < ncol; i += Q) s += red[e * nt + uj * ncol + i];
+            if (job < jobs) {                              // four sums side by side: a chain of n adds 2^-24 * sqrt(n / 6) to the error
+                const float *col = red + e * nt + uj * ncol;
+                float p[4] = {0.f, 0.f, 0.f, 0.f};
+                int i = q;
+                for (; i + 3 * Q < ncol; i += 4 * Q) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) p[k] += col[i + k * Q];
+                }
+                for (; i < ncol; i += Q) p[0] += col[i];
+                s = (p[0] + p[1]) + (p[2] + p[3]);
+            }
             for (int h = Q >> 1; h >= 1; h >>= 1) s += __shfl_xor(s, h, 64);
             if (job < jobs && q == 0) ws[(size_t)part * J + (o0 + uj) * K * K + e0 + e] = s;
         }
@@ -621,6 +640,12 @@ bool s2_tile(const Geom &g, int dtype, FlatTile *ft)
 // 74x74x256 3x3 fp32 78 -> 74.  But a lane's own loads are short, and a band starts with a wait for them: planes that are
 // too large for LDS together with their dy keep bands of both there for 3x3 in bf16 (74x74x256 49 us against 56) and at stride 2 (fp32 55 against 63), and for 5x5 in fp32 (41x41x240 63 against 67;
 // at stride 2 56x56x128 47 against 45).
+// Sets of sums per lane.  A lane's chain of n products has a relative error of about 2^-24 * sqrt(n / 6); two sets halve n.  Over random
+// layers, against 64 bits, one set -> two (the kernels these replaced): 3x3 fp32 1.16e-7 -> 1.05e-7 (1.01e-7), bf16 7.95e-8 -> 7.84e-8
+// (7.81e-8), 5x5 fp32 1.06e-7 -> 1.00e-7 (0.96e-7), at the same time (74x74x256 3x3 72.0 -> 72.8 us, 41x41x240 5x5 62.9 -> 62.5).  5x5 rows of whole
+// vectors keep one: the row walk they came from is at 1.27e-7 against 1.09e-7, and 20x20x480 takes 29.6 us with one and 36 with two.  7x7 is
+// at 1.09e-7 (1.08e-7) with one; 49 more registers would cost 28x28x256 40 -> 52 us.
+constexpr int filter_sets(int K, bool f32, bool ragged) { return K == 3 || (K == 5 && f32 && ragged) ? 2 : 1; }
 template <typename T, int K, int S> constexpr bool DY_LDS = K == 3 ? sizeof(T) == 2 || S == 2 : K == 5 && S == 1 && sizeof(T) == 4;
 bool filter_tile(const Geom &g, int dtype, FlatTile *ft)
 {
@@ -714,9 +739,19 @@ static hipError_t filter_go(const Geom &g, int dtype, const void *x, const void 
     const size_t red = (size_t)(K * K <= 25 ? K * K : 25) * ft.threads * 4;
     if (red > lds) lds = red;
     constexpr int NC = K > 3 && sizeof(T) == 2 ? 2 : 1;
-    auto kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, NC, false> : k_nchwf_bwd_filter<T, K, S, false, NC, false>;
+    constexpr bool WIDE = sizeof(T) == 4;
+    auto kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, NC, false, filter_sets(K, WIDE, true)> : k_nchwf_bwd_filter<T, K, S, false, NC, false, filter_sets(K, WIDE, true)>;
     if constexpr (DY_LDS<T, K, S>) {
-        if (ft.pout) kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, NC, true> : k_nchwf_bwd_filter<T, K, S, false, NC, true>;
+        if (ft.pout) kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, NC, true, filter_sets(K, WIDE, true)> : k_nchwf_bwd_filter<T, K, S, false, NC, true, filter_sets(K, WIDE, true)>;
+    }
+    if constexpr (filter_sets(K, WIDE, false) != filter_sets(K, WIDE, true)) {
+        if (g.W % 4 == 0) {
+            constexpr int SETS = filter_sets(K, WIDE, false);
+            kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, NC, false, SETS> : k_nchwf_bwd_filter<T, K, S, false, NC, false, SETS>;
+            if constexpr (DY_LDS<T, K, S>) {
+                if (ft.pout) kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, NC, true, SETS> : k_nchwf_bwd_filter<T, K, S, false, NC, true, SETS>;
+            }
+        }
     }
     hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(ft.threads), lds, st, g, (const T *)x, (const T *)dy, ws, parts,
                        per, ft, nblocks);
