@@ -113,19 +113,28 @@ static bool use_small(const Geom &g, int dtype, int pass)
 }
 
 // The any-width NCHW kernels (nchw_flat.hip) take what neither the small planes nor the row walk takes, and of the
-// row walk's shapes the fp32 5x5 layers at stride 1 whose arithmetic the row walk does not hide: forward and input gradient
-// (batch 64, us, row walk -> any width: 16x16x480 27 -> 17, 20x20x480 34 -> 26, 40x40x240 63 -> 48, 48x48x240 91 -> 69, 56x56x128
-// at batch 128 125 -> 102, 96x96x128 152 -> 145, 112x112x128 214 -> 210; the input gradient of 28x28x240 at batch 128 71 -> 51),
-// filter gradient up to rows of 24 (16x16 33 -> 23, 24x24 58 -> 45; 32x32 38 -> 49 and 56x56 104 -> 114 stay).  bf16 5x5 stays with
-// the packed-pair row walk (40x40x240 35 against 42).  Of the bf16 3x3 layers at stride 1 the forward and input gradient of rows that are
-// no whole number of 16-byte vectors, which the row walk reads 8 bytes a lane (batch 64: 20x20x256 12.1 -> 9.5, 36x36x256 25.6 -> 24.5 and
-// 31 -> 22, 52x52x128 31 -> 24, 60x60x128 38 -> 32, 76x76x64 30 -> 25, 100x100x64 49 -> 47; 140x140x32 45 -> 47 stays), from 2^22 outputs on
-// (at batch 8 20x20x256 3.1 against 4.4, 36x36x256 5.7 against 6.2).
+// row walk's shapes
+// - the fp32 5x5 layers at stride 1 whose arithmetic the row walk does not hide.  Forward and input gradient (batch 64, us, row walk -> any
+//   width: 16x16x480 27 -> 17, 20x20x480 34 -> 26, 40x40x240 63 -> 48, 48x48x240 91 -> 69, 56x56x128 at batch 128 125 -> 102; the input
+//   gradient of 28x28x240 at batch 128 71 -> 51); small launches 7.5 -> 4.8, 9 -> 5.  The row walk keeps 1.5 to 2 million outputs, up to 4
+//   million on rows of 28 and more, where its blocks make whole rounds and these do not (35x15x128x120 17 against 25, 350x22x72x72 11.9 against
+//   14), and rows of 96 and more from 1.5 million on (as long or up to 20 % longer up to 2^24).  Filter gradient: rows of 12 to 24 on planes of
+//   up to 35 rows (16x16 33 -> 23, 24x24 58 -> 45; 32x32 38 -> 49, 56x56 104 -> 114, 158x16x150x16 25 -> 38, 32x793x39x8 27 -> 34 stay).
+// - of the bf16 3x3 layers at stride 1 the forward and input gradient of rows that are no whole number of 16-byte vectors, which the row walk
+//   reads 8 bytes a lane (batch 64: 20x20x256 12.1 -> 9.5, 36x36x256 25.6 -> 18.9 and 31 -> 22, 52x52x128 31 -> 24, 60x60x128 38 -> 32,
+//   76x76x64 30 -> 25, 100x100x64 49 -> 47; 140x140x32 45 -> 47 stays): rows of up to 24 from 2^22 outputs on (at batch 8 20x20x256 3.1
+//   against 4.4), up to 44 from 1.5 times that, wider ones from 2^24 (2^22.5 outputs on rows of 60 9.8 -> 12.4, of 92 9.8 -> 13.2).
+// bf16 5x5 stays with the packed-pair row walk (40x40x240 35 against 42).
 static bool flat_over_rowwalk(const Geom &g, int dtype, int pass)
 {
     if (g.s != 1 || g.W > 512) return false;                 // (the any-width kernels take rows of up to 512)
-    if (dtype == DT_F32) return g.K == 5 && (pass < 2 || g.W <= 24) && nchwf_fwd_supported(g, dtype) && nchwf_bwd_data_supported(g, dtype);
-    return g.K == 3 && g.W % 8 != 0 && g.W <= 128 && pass < 2 && (long long)g.N * g.O * g.Ho * g.Wo >= 1 << 22;
+    const long long outputs = (long long)g.N * g.O * g.Ho * g.Wo;
+    if (dtype == DT_F32) {
+        if (g.K != 5 || !nchwf_fwd_supported(g, dtype) || !nchwf_bwd_data_supported(g, dtype)) return false;
+        if (pass == 2) return g.W >= 12 && g.W <= 24 && g.H <= 35;
+        return outputs < 3 << 19 || (g.W < 96 && outputs >= (g.W < 28 ? 1 << 21 : 1 << 22));
+    }
+    return g.K == 3 && g.W % 8 != 0 && g.W <= 128 && pass < 2 && outputs >= (g.W <= 24 ? 1 << 22 : g.W <= 44 ? 3 << 21 : 1 << 24);
 }
 
 static const char *flat_name(int K, int s, int pass)

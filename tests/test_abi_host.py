@@ -138,6 +138,23 @@ def test_generic_fallback_is_selected_for_untuned_shapes():
     assert dw.variant_name(dw.desc(2, 8, 9, 9, 3, 3, 1, 1, dw.NHWC), 2) == "generic"       # stride 3
 
 
+def test_any_width_kernels_take_from_the_row_walk_what_they_shorten():
+    """fp32 5x5 and bf16 3x3 rows that both NCHW kernels can take: the measured side of each line."""
+    def flat(N, C, H, W, K, dtype, which=0):
+        name = dw.variant_name(dw.desc(N, C, H, W, K, 1, K // 2, 1, dw.NCHW, dtype), which)
+        assert name.startswith(("nchw_flat", "nchw_rowwalk")), name
+        return name.startswith("nchw_flat")
+    f32 = [(4, 64, 40, 40, True), (64, 240, 40, 40, True), (128, 128, 56, 56, True),       # short, and large launches
+           (35, 15, 120, 120, False), (22, 250, 20, 16, False), (44, 250, 20, 16, True),   # 6.3, 1.8 and 3.5 million outputs
+           (10, 50, 72, 60, False), (32, 50, 72, 60, True), (64, 128, 112, 112, False)]
+    for N, C, H, W, want in f32:
+        assert flat(N, C, H, W, 5, dw.F32) == flat(N, C, H, W, 5, dw.F32, 1) == want, (N, C, H, W)
+    for N, C, H, W, want in [(64, 480, 16, 16, True), (64, 480, 24, 24, True), (64, 240, 32, 32, False), (64, 240, 40, 16, False), (64, 240, 20, 8, False)]:
+        assert flat(N, C, H, W, 5, dw.F32, 2) == want, (N, C, H, W)
+    for N, C, H, W, want in [(16, 656, 20, 20, True), (64, 256, 36, 36, True), (16, 256, 36, 36, False), (64, 128, 60, 60, True), (16, 128, 60, 60, False)]:
+        assert flat(N, C, H, W, 3, dw.BF16) == want, (N, C, H, W)
+
+
 def test_shapes_too_small_for_the_nhwc_walks_stay_generic():
     """Where a block's fixed work is longer than the sums, or a row has work for a few lanes of a wavefront only."""
     for K, pixels in ((3, 18), (5, 50), (7, 98)):
