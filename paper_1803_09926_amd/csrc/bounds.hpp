@@ -6,4 +6,13 @@ namespace dwc {
 // Whether the ve elements from a on lie inside a tensor of `total` elements; a + ve may be 2^31 and more.
 constexpr bool vector_inside(int a, int ve, int total) { return a <= total - ve; }
 
+// ceil(a / b) for a >= 1, b >= 1 (a + b - 1 may be 2^31 and more)
+constexpr int cdiv(int a, int b) { return (a - 1) / b + 1; }
+
+// End of part `part` of `items` dealt `per` at a time; part * per < items.
+constexpr int part_end(int items, int per, int part) { return items - part * per < per ? items : part * per + per; }
+
+// Whether a launch has fewer than 2^32 lanes, which the runtime asks for.
+constexpr bool launchable(long long blocks, int threads) { return blocks * threads < 1LL << 32; }
+
 }  // namespace dwc

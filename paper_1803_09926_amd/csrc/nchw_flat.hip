@@ -378,7 +378,7 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__res
 #pragma unroll
     for (int e = 0; e < SETS * K * K; ++e) acc[e / (K * K)][e / K % K][e % K] = 0.f;
 
-    const int items = g.N * ft.nbands, it1 = min(items, (part + 1) * per_part);
+    const int items = g.N * ft.nbands, it1 = part_end(items, per_part, part);
     for (int it = part * per_part; it < it1; ++it) {
         const int n = it / ft.nbands, band = it - n * ft.nbands;
         const int oh0 = band * ft.TR, oh1 = min(g.Ho, oh0 + ft.TR);
@@ -663,13 +663,13 @@ bool filter_tile(const Geom &g, int dtype, FlatTile *ft)
 bool nchwf_fwd_supported(const Geom &g, int dtype)
 {
     FlatTile ft;
-    return flat_k(g) && conv_tile(g, dtype, false, &ft);
+    return flat_k(g) && conv_tile(g, dtype, false, &ft) && launchable((long long)cdiv(g.N * g.O, ft.U) * ft.nbands, ft.threads);
 }
 bool nchwf_bwd_data_supported(const Geom &g, int dtype)
 {
     FlatTile ft;
     if (!flat_k(g) || g.m > 2) return false;
-    return g.s == 1 ? conv_tile(g, dtype, true, &ft) : s2_tile(g, dtype, &ft);
+    return (g.s == 1 ? conv_tile(g, dtype, true, &ft) : s2_tile(g, dtype, &ft)) && launchable((long long)cdiv(g.N * g.C, ft.U) * ft.nbands, ft.threads);
 }
 
 int nchwf_bwd_filter_parts(const Geom &g, int dtype)
@@ -695,7 +695,7 @@ void nchwf_bwd_filter_tiles(const Geom &g, int dtype, int parts, FilterGradSrc *
     filter_tile(g, dtype, &ft);
     f->TN = 1; f->TA = ft.TR; f->TB = g.Wo;
     f->tn = g.N; f->ta = ft.nbands; f->tb = 1;
-    f->per = (g.N * ft.nbands + parts - 1) / parts; f->nparts = parts; f->splits = 1;
+    f->per = cdiv(g.N * ft.nbands, parts); f->nparts = parts; f->splits = 1;
 }
 
 template <typename T, int K, int S, int M>
@@ -705,7 +705,7 @@ static hipError_t conv_go(const Geom &g, int dtype, const void *in, const void *
     if (!conv_tile(g, dtype, bwd, &ft)) return hipErrorInvalidValue;
     const int Hi = bwd ? g.Ho : g.H, Wi = bwd ? g.Wo : g.W, Ho = bwd ? g.H : g.Ho, Wo = bwd ? g.W : g.Wo;
     const int OC = bwd ? g.C : g.O, nplanes = g.N * OC;
-    const unsigned nblocks = (unsigned)((nplanes + ft.U - 1) / ft.U) * ft.nbands;
+    const unsigned nblocks = (unsigned)cdiv(nplanes, ft.U) * ft.nbands;
     const int total_in = g.N * (bwd ? g.O : g.C) * Hi * Wi;
     const bool same = (bwd ? K - 1 - g.p : g.p) == K / 2;
     constexpr int NC = K > 3 && sizeof(T) == 2 ? 2 : 1;
@@ -721,7 +721,7 @@ static hipError_t s2_go(const Geom &g, int dtype, const void *dy, const void *w,
     FlatTile ft;
     if (!s2_tile(g, dtype, &ft)) return hipErrorInvalidValue;
     const int nplanes = g.N * g.C;
-    const unsigned nblocks = (unsigned)((nplanes + ft.U - 1) / ft.U) * ft.nbands;
+    const unsigned nblocks = (unsigned)cdiv(nplanes, ft.U) * ft.nbands;
     auto kernel = g.p % 2 ? k_nchwf_bwd_data_s2<T, K, M, 1> : k_nchwf_bwd_data_s2<T, K, M, 0>;
     hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(ft.threads), tile_lds(ft, sizeof(T)), st, (const T *)dy,
                        (const T *)w, (T *)dx, nplanes, g.C, g.H, g.W, g.Ho, g.Wo, g.p, s2_cols(g), g.N * g.O * g.Ho * g.Wo, ft,
@@ -733,8 +733,8 @@ static hipError_t filter_go(const Geom &g, int dtype, const void *x, const void 
 {
     FlatTile ft;
     if (!filter_tile(g, dtype, &ft)) return hipErrorInvalidValue;
-    const int items = g.N * ft.nbands, per = (items + parts - 1) / parts;
-    const unsigned nblocks = (unsigned)((g.O + ft.U - 1) / ft.U) * parts;
+    const int items = g.N * ft.nbands, per = cdiv(items, parts);
+    const unsigned nblocks = (unsigned)cdiv(g.O, ft.U) * parts;
     size_t lds = tile_lds(ft, sizeof(T)) + (ft.pout ? (size_t)second_area(ft) * sizeof(T) : 0);
     const size_t red = (size_t)(K * K <= 25 ? K * K : 25) * ft.threads * 4;
     if (red > lds) lds = red;

@@ -10,6 +10,7 @@
 // One output per thread -> these kernels, us on one MI355X at batch 64, forward / input gradient / filter gradient: 56x56x128 5x5
 // stride 2 fp32 142 / 347 / 900 -> 36 / 37 / 41 (bound by its K vector loads per row and column, 8 bytes a lane); 28x28x256 7x7 fp32
 // 660 / 890 / 2430 -> 58 / 58 / 73; 56x56x30 3x3 fp32 49 / 67 / 954 -> 12.5 / 12.5 / 18.
+#include "bounds.hpp"
 #include "point.hpp"
 #include <type_traits>
 
@@ -262,7 +263,7 @@ __global__ __launch_bounds__(256) void k_nhwca_bwd_filter(AnyGeom g, const T *__
 #pragma unroll
             for (int v = 0; v < V; ++v) acc[kh][kw][v] = 0.f;
 
-    const int it1 = min(g.N * g.nstrips * g.ncols, (part + 1) * per_part);
+    const int it1 = part_end(g.N * g.nstrips * g.ncols, per_part, part);
     for (int it = part * per_part; it < it1; ++it) {
         const int row = it / g.ncols, col0 = (it - row * g.ncols) * g.TW, col1 = min(g.Wo, col0 + g.TW);
         const int n = row / g.nstrips, strip = row - n * g.nstrips;
@@ -442,7 +443,7 @@ bool nhwca_supported(const Geom &g, int pass)
     if (!any_k(g)) return false;
     if (pass == 2) return true;
     const WalkTile t = walk_tile(g, pass);
-    return t.blocks < (1LL << 31) && (pass != 1 || g.m <= 2);
+    return launchable(t.blocks, t.bs) && (pass != 1 || g.m <= 2);
 }
 
 int nhwca_row_lanes(const Geom &g) { return g.Wo * (g.O / any_vec(g)); }

@@ -227,7 +227,8 @@ def test_buffer_view_kernels_stay_within_two_gib_images():
 
 
 def test_index_arithmetic_at_the_edge_of_a_tensor(tmp_path):
-    """The last vector of a tensor of up to 2^31 - 1 elements: whole only if all its elements are there."""
+    """The last vector of a tensor of up to 2^31 - 1 elements: whole only if all its elements are there.  The items of a part, and the limit
+    of a launch, at the same edge."""
     src = tmp_path / "bounds.cpp"
     src.write_text("""
 #include "bounds.hpp"
@@ -240,12 +241,31 @@ int main()
         for (long long total : {1ll, 3ll, 4ll, 7ll, 8ll, 9ll, 1000ll, 1ll << 30, (1ll << 31) - 8, (1ll << 31) - 7, (1ll << 31) - 4, (1ll << 31) - 3, (1ll << 31) - 1})
             for (long long a = total / ve * ve; a >= 0 && a > total - 3 * ve; a -= ve)
                 if (a <= INT_MAX && vector_inside((int)a, ve, (int)total) != (a + ve <= total)) return 1;
-    return 0;
+    for (int items : {1, 5, 2048, INT_MAX - 2048, INT_MAX - 1, INT_MAX})
+        for (int parts : {1, 3, 5, 64, 2048}) {
+            if (parts > items) continue;
+            const int per = cdiv(items, parts);
+            if (per != ((long long)items + parts - 1) / parts) return 2;
+            const int n = cdiv(items, per);
+            for (int part = 0; part < n; ++part)
+                if (part_end(items, per, part) != (((part + 1ll) * per < items) ? (part + 1ll) * per : items)) return 3;
+        }
+    return launchable((1ll << 24) - 1, 256) && !launchable(1ll << 24, 256) ? 0 : 4;
 }
 """)
     exe = tmp_path / "bounds"
     subprocess.check_call(["g++", "-std=c++17", "-ftrapv", "-I", os.path.join(os.path.dirname(dw.__file__), "csrc"), str(src), "-o", str(exe)])
     assert subprocess.call([str(exe)]) == 0
+
+
+def test_launches_of_2_32_lanes_stay_with_the_generic_kernels():
+    """Many tiny images: the walks start whole wavefronts for each image, and the runtime refuses a launch of 2^32 lanes.  The generic kernels
+    start one lane per output, so these shapes still run."""
+    tiny = [dw.desc(1 << 26, 1, 4, 5, 3, 1, 1, 1, dw.NHWC, dw.F32), dw.desc(1 << 26, 1, 4, 4, 3, 2, 1, 1, dw.NHWC, dw.BF16)]
+    for d in tiny:
+        assert dw.variant_name(d, 0) == dw.variant_name(d, 1) == "generic"
+    ok = dw.desc(1 << 20, 1, 4, 5, 3, 1, 1, 1, dw.NHWC, dw.F32)
+    assert [dw.variant_name(ok, i) for i in range(3)] == ["nhwc_any_k3s1", "nhwc_any_k3s1_flip", "nhwc_any_bwd_filter_k3s1"]
 
 
 # ---- group convolution entry points --------------------------------------------------------------------
