@@ -4,6 +4,7 @@
 // are the depthwise layer and run on its kernels.
 #include "../../include/dwconv.h"
 #include "gconv.hpp"
+#include <math.h>
 
 namespace dwc {
 
@@ -211,6 +212,63 @@ static Geom as_geom(const GGeom &g)
     return q;
 }
 
+// Estimated time in us of the generic kernels.  Forward and input gradient: a lane's products one after the other, or all of them at a rate that
+// is higher for larger filters and lower where the stride skips taps or lines; the filter gradient: blocks of (entry, part), each as
+// long as its lanes' pixels.  Fitted to 30 000 random layers: four of five between 0.65 and 1.2 times the measured time.
+static double generic_us(const GGeom &g, int layout, int pass)
+{
+    const bool nhwc = layout == LAYOUT_NHWC, strided = g.s > 1;
+    if (pass == 2) {
+        const double J = (double)g.O * g.Cg * g.K * g.K, pixels = (double)g.N * g.Ho * g.Wo, parts = gconv_generic_bwd_filter_parts(g);
+        if (!nhwc) {
+            const double steps = ceil(pixels / parts / 256), blocks = J * parts / 2048;
+            return 6 + 0.29 * steps + blocks * (0.8 * steps + 1.0);
+        }
+        const double steps = ceil(pixels / parts / 4), blocks = (double)((g.O + 63) / 64) * g.K * g.K * g.Cg * parts / 2048;
+        return 4.6 + 0.3 * steps + 0.53 * blocks * steps + 20e-6 * parts * J;
+    }
+    auto taps = [&](long long n) { return (double)(n < g.K ? n : g.K); };
+    double products, latency, rate, outputs;                     // products of an output; M products in a us
+    if (pass == 0) {
+        products = g.Cg * taps(g.H) * taps(g.W);
+        outputs = (double)g.N * g.O * g.Ho * g.Wo;
+        latency = 4 + 0.15 * products;
+        rate = (g.K == 1 ? 1.0 : g.K == 3 ? 1.95 : 2.3) * (strided ? 0.7 : 1.0);
+    } else {
+        const bool skips = nhwc && strided && g.K > 1;
+        products = g.Og * taps((long long)g.Ho * g.s) * taps((long long)g.Wo * g.s);
+        outputs = (double)g.N * g.C * g.H * g.W;
+        latency = 4.3 + (skips ? 0.13 : 0.23) * products;
+        rate = (g.K == 1 ? 0.6 : g.K == 3 ? 1.05 : 1.2) * (skips ? 1.8 : nhwc && g.K == 3 ? 0.65 : 1.0);
+    }
+    const double all = outputs * products * 1e-6 / rate;
+    return sqrt(latency * latency + all * all);
+}
+
+// Laying out the filter and staging a tile are a fixed 10 to 20 us, and a filter that takes the LDS leaves small tiles: few products per output
+// and few outputs, or few channels a group with a large filter, are shorter one output per thread.  Of random layers that both take, 38 % of
+// the forward passes and 22 % of the input gradients were slower by more than a tenth on the matrix instructions (2x8 channels a group at
+// 226x80x80 5x5 fp32 83 -> 282 us, 90x7x7x90 groups of 3 7x7 bf16 16 -> 88); with the estimates 1.7 and 1.5 %, and 1.4 and 3.3 % stay generic
+// that would be shorter here.  The filter gradient, whose time here hardly depends on the layer as long as it is short: 14 % -> 1 %, 1 %.
+static bool gemm_over_generic(const GGeom &g, int layout, int dtype, int pass)
+{
+    const double generic = generic_us(g, layout, pass);
+    if (pass == 2) return generic > (g.K == 1 ? 10.5 : g.K == 3 ? 12.5 : 16.0);
+    int positions, tiles;
+    return gconv_gemm_us(g, layout, dtype, pass, &positions, &tiles) * (pass == 0 ? 1.0 : 0.9) < generic;
+}
+
+// In place of the NCHW row walk: not where the filter leaves tiles of few positions and a block has several of them (fp32, 64 channels a
+// group, rows of 20: 257 -> 857 us), and not for the fp32 filter gradient of 16 channels a group on many pixels (1.03 times as long at the
+// median of random layers, up to 1.8).
+static bool gemm_over_rowwalk(const GGeom &g, int layout, int dtype, int pass)
+{
+    if (pass == 2) return !(dtype == DT_F32 && g.Cg == 16 && (long long)g.N * g.Ho * g.Wo >= 16384);
+    int positions, tiles;
+    gconv_gemm_us(g, layout, dtype, pass, &positions, &tiles);
+    return !(positions < 81 && tiles >= 3);
+}
+
 static GPlan gplan(const GGeom &g, int layout, int dtype, int pass)
 {
     GPlan pl = {GV_GENERIC, pass == 2 ? gconv_generic_bwd_filter_parts(g) : 0, 0, 0, 0, "group_generic"};
@@ -265,12 +323,11 @@ static GPlan gplan(const GGeom &g, int layout, int dtype, int pass)
         if (pass == 2) pl.parts = gconv_nhwc_bwd_filter_parts(g, dtype);
     }
     // What no kernel above takes, and NCHW groups of a multiple of 16 channels in place of the row walk (14x14, 16 channels a
-    // group, 512 channels, fp32 batch 64: 62 -> 45 us; 32 channels at batch 4: 53 -> 15): the 16x16 matrix instructions, from
-    // 2048 outputs on.  Below that the generic kernels' one output per thread is as fast as laying out the filter (2x9x9x12,
-    // 5x5: 11 us against 17; 3x3 stride 2 5.7 against 9).
+    // group, 512 channels, fp32 batch 64: 62 -> 45 us; 32 channels at batch 4: 53 -> 15): the 16x16 matrix instructions
     const bool rowwalk16 = pl.variant == GV_NCHW_K3S1 && g.Cg % 16 == 0 && g.Og % 16 == 0;
     const long long outputs = (long long)g.N * (pass == 1 ? (long long)g.C * g.H * g.W : (long long)g.O * g.Ho * g.Wo);
-    if ((pl.variant == GV_GENERIC || rowwalk16) && outputs >= 2048 && gconv_gemm_supported(g, layout, dtype, pass)) {
+    if ((pl.variant == GV_GENERIC || rowwalk16) && outputs >= 2048 && gconv_gemm_supported(g, layout, dtype, pass) &&
+        (tune_env("DWCONV_TUNE_GROUP_GEMM") || (rowwalk16 ? gemm_over_rowwalk(g, layout, dtype, pass) : gemm_over_generic(g, layout, dtype, pass)))) {
         pl.variant = GV_GEMM;
         pl.name = pass == 0 ? "group_mfma16" : pass == 1 ? "group_mfma16_bwd_data" : "group_mfma16_bwd_filter";
         if (pass == 2) pl.parts = gconv_gemm_parts(g, layout, dtype);

@@ -270,6 +270,24 @@ def test_launches_of_2_32_lanes_stay_with_the_generic_kernels():
 
 # ---- group convolution entry points --------------------------------------------------------------------
 
+def test_group_shapes_that_are_shorter_one_output_per_thread():
+    """The 16x16 matrix instructions lay out a filter and stage a tile first: few products per output in few outputs, and tiles that a
+    large filter leaves small, stay with the generic kernels; the row walk keeps what such tiles would lengthen."""
+    def names(*a, layout=dw.NCHW, dtype=dw.F32):
+        d = dw.group_desc(*a, layout=layout, dtype=dtype)
+        return [dw.gconv_variant_name(d, i) for i in range(3)]
+    gemm = ["group_mfma16", "group_mfma16_bwd_data", "group_mfma16_bwd_filter"]
+    for layout in (dw.NCHW, dw.NHWC):
+        for dtype in (dw.F32, dw.BF16):
+            assert names(4, 8, 8, 8, 1, 1, 0, 2, 8, layout=layout, dtype=dtype)[:2] == ["group_generic"] * 2
+            assert names(64, 96, 57, 57, 3, 2, 1, 6, 96, layout=layout, dtype=dtype) == gemm
+    assert names(226, 2, 80, 80, 5, 1, 2, 1, 2)[0] == "group_generic"
+    assert names(90, 90, 7, 7, 7, 1, 0, 30, 90, layout=dw.NHWC, dtype=dw.BF16)[:2] == ["group_generic"] * 2
+    assert names(148, 128, 21, 20, 3, 1, 1, 2, 128)[:2] == ["group_nchw_rowwalk_k3s1", "group_nchw_rowwalk_k3s1_flip"]
+    assert names(148, 128, 21, 20, 3, 1, 1, 2, 128, dtype=dw.BF16)[:2] == gemm[:2]
+    assert names(64, 512, 14, 14, 3, 1, 1, 32, 512)[:2] != ["group_generic"] * 2
+
+
 def test_group_desc_struct_matches_header_field_order():
     text = open(HEADER).read()
     body = re.search(r"typedef struct dwconv_group_desc \{(.*?)\} dwconv_group_desc;", text, re.S).group(1)

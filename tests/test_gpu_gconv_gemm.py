@@ -14,6 +14,14 @@ from test_gpu_gconv import run_gpu
 
 pytestmark = pytest.mark.gpu
 
+
+@pytest.fixture(autouse=True)
+def matrix_instructions():
+    """These kernels wherever they take the shape: the small ones below are shorter one output per thread and would go there."""
+    with dw.tuning_overrides({"DWCONV_TUNE_GROUP_GEMM": 1}):
+        yield
+
+
 # name, N, C, O, groups, H, W, K, stride, pad
 CASES = [
     ("cg16", 3, 32, 32, 2, 14, 14, 3, 1, 1),                       # several images a tile
