@@ -545,7 +545,7 @@ void pick_lanes(int cols, int planes, int maxu, int *U, int *threads)
 inline int lds_target(int K) { return K == 3 ? 32 << 10 : 40 << 10; }
 constexpr int LDS_WHOLE = 40 << 10;
 constexpr int LDS_MOST = 64 << 10;
-constexpr int MIN_LANES = 65536;
+constexpr int MIN_LANES = 65536, LEAST_BAND = 256, LEAST_FILTER_BAND = 1024;
 
 inline int round_up(int a, int b) { return (a + b - 1) / b * b; }
 
@@ -553,10 +553,10 @@ int second_area(const FlatTile &ft) { return GUARD + ft.U * ft.pout; }       // 
 
 // Tile of a launch: `cols` lanes per plane; a band of t units (rows, or row pairs) needs in_rows(t) input rows; Mi input planes per
 // output plane, or mdiv output planes per input plane; copies: launches of the planes side by side (images of the filter gradient);
-// second: bands of the output rows are in LDS too.
+// second: bands of the output rows are in LDS too; least: see the end.
 template <typename FI>
 bool pick_tile(int esz, int cols, int units, int nplanes, int maxu, int Hi, int Wi, int Ho, int Wo, FI in_rows, int Mi, int mdiv,
-               int target, FlatTile *ft, int copies, bool second = false)
+               int target, FlatTile *ft, int copies, int least, bool second = false)
 {
     const int VE = 16 / esz;
     // a block's planes are one buffer view (2 GiB at most)
@@ -588,11 +588,15 @@ bool pick_tile(int esz, int cols, int units, int nplanes, int maxu, int Hi, int 
         t = (units + nb - 1) / nb;
         if (lds(t, ft) <= LDS_MOST && (t >= 4 || t >= units || ft->U == 1)) {
             // A launch of fewer than MIN_LANES lanes is one short round of blocks, each as long as its band: bands of half the height,
-            // and half again down to four rows.
+            // and half again down to four rows, while a plane's band is `least` bytes and more.  Each is a DMA of its own, of up to 1024
+            // bytes, where whole planes of a block are one stream.  Of random layers with rows of up to 60, with every band halved / none below
+            // 256 bytes: 10 / 0.4 % of the 3x3 and 17 / 1.0 % of the 5x5 forward passes on rows under 13 were slower by more than a tenth than with
+            // the tall bands (15x50x23x3 3x3 stride 2: 7.4 and 4.9 us); the filter gradient, whose bands are partials too, below 1024: 20 / 0.1 %.
             const long long groups = (long long)((nplanes - 1) / ft->U + 1) * copies;
             while (ft->TR > 4 && groups * ft->nbands * ft->threads < MIN_LANES) {
-                const int h = (ft->TR + 1) / 2, n = (units + h - 1) / h;
-                lds((units + n - 1) / n, ft);
+                const int h = (ft->TR + 1) / 2, n = (units + h - 1) / h, t2 = (units + n - 1) / n;
+                if ((long long)in_rows(t2) * Wi * esz < least) break;
+                lds(t2, ft);
             }
             return true;
         }
@@ -625,8 +629,8 @@ bool conv_tile(const Geom &g, int dtype, bool bwd, FlatTile *ft)
     const int esz = dtype == DT_F32 ? 4 : 2, nc = flat_cols(g, dtype), cols = ((bwd ? g.W : g.Wo) + nc - 1) / nc;
     auto in_rows = [&](int t) { return (t - 1) * g.s + g.K; };
     if (!bwd)
-        return pick_tile(esz, cols, g.Ho, g.N * g.O, most_planes((long long)g.N * g.O, g.Ho, cols), g.H, g.W, g.Ho, g.Wo, in_rows, 1, g.m, lds_target(g.K), ft, 1);
-    return pick_tile(esz, cols, g.H, g.N * g.C, most_planes((long long)g.N * g.C, g.H, cols), g.Ho, g.Wo, g.H, g.W, in_rows, g.m, 1, lds_target(g.K), ft, 1);
+        return pick_tile(esz, cols, g.Ho, g.N * g.O, most_planes((long long)g.N * g.O, g.Ho, cols), g.H, g.W, g.Ho, g.Wo, in_rows, 1, g.m, lds_target(g.K), ft, 1, LEAST_BAND);
+    return pick_tile(esz, cols, g.H, g.N * g.C, most_planes((long long)g.N * g.C, g.H, cols), g.Ho, g.Wo, g.H, g.W, in_rows, g.m, 1, lds_target(g.K), ft, 1, LEAST_BAND);
 }
 
 int s2_cols(const Geom &g) { return (g.W + 1) / 2; }
@@ -636,7 +640,7 @@ bool s2_tile(const Geom &g, int dtype, FlatTile *ft)
     const int esz = dtype == DT_F32 ? 4 : 2, NA = (g.K + 1) / 2;
     auto in_rows = [&](int t) { return t + NA - 1; };
     return pick_tile(esz, s2_cols(g), s2_pairs(g), g.N * g.C, most_planes((long long)g.N * g.C, g.H, s2_cols(g)), g.Ho, g.Wo, g.H, g.W, in_rows, g.m, 1,
-                     lds_target(g.K), ft, 1);
+                     lds_target(g.K), ft, 1, LEAST_BAND);
 }
 // Whether the filter gradient reads dy from LDS too.  Every dy value is read once, by one lane, so that it needs no LDS, and without it
 // more blocks fit a compute unit: 28x28x256 7x7 fp32 batch 64 54 -> 42 us, 37x37x256 multiplier 2 41 -> 32, 19x19x728 bf16 17 -> 15,
@@ -655,7 +659,7 @@ bool filter_tile(const Geom &g, int dtype, FlatTile *ft)
     const int esz = dtype == DT_F32 ? 4 : 2, nc = flat_cols(g, dtype), cols = (g.Wo + nc - 1) / nc;
     auto in_rows = [&](int t) { return (t - 1) * g.s + g.K; };
     auto pick = [&](bool second) {
-        return pick_tile(esz, cols, g.Ho, g.O, most_planes((long long)g.N * g.O, g.Ho, cols), g.H, g.W, g.Ho, g.Wo, in_rows, 1, g.m, lds_target(g.K), ft, g.N, second);
+        return pick_tile(esz, cols, g.Ho, g.O, most_planes((long long)g.N * g.O, g.Ho, cols), g.H, g.W, g.Ho, g.Wo, in_rows, 1, g.m, lds_target(g.K), ft, g.N, LEAST_FILTER_BAND, second);
     };
     const bool lds = g.K == 3 ? dtype == DT_BF16 || g.s == 2 : g.K == 5 && g.s == 1 && dtype == DT_F32;      // DY_LDS
     return (lds && pick(true) && ft->nbands > 1) || pick(false);
