@@ -647,12 +647,12 @@ bool s2_tile(const Geom &g, int dtype, FlatTile *ft)
 // 74x74x256 3x3 fp32 78 -> 74.  But a lane's own loads are short, and a band starts with a wait for them: planes that are
 // too large for LDS together with their dy keep bands of both there for 3x3 in bf16 (74x74x256 49 us against 56) and at stride 2 (fp32 55 against 63), and for 5x5 in fp32 (41x41x240 63 against 67;
 // at stride 2 56x56x128 47 against 45).
-// Sets of sums per lane.  A lane's chain of n products has a relative error of about 2^-24 * sqrt(n / 6); two sets halve n.  Over random
-// layers, against 64 bits, one set -> two (the kernels these replaced): 3x3 fp32 1.16e-7 -> 1.05e-7 (1.01e-7), bf16 7.95e-8 -> 7.84e-8
-// (7.81e-8), 5x5 fp32 1.06e-7 -> 1.00e-7 (0.96e-7), at the same time (74x74x256 3x3 72.0 -> 72.8 us, 41x41x240 5x5 62.9 -> 62.5).  5x5 rows of whole
-// vectors keep one: the row walk they came from is at 1.27e-7 against 1.09e-7, and 20x20x480 takes 29.6 us with one and 36 with two.  7x7 is
-// at 1.09e-7 (1.08e-7) with one; 49 more registers would cost 28x28x256 40 -> 52 us.
-constexpr int filter_sets(int K, bool f32, bool ragged) { return K == 3 || (K == 5 && f32 && ragged) ? 2 : 1; }
+// Sets of sums per lane.  A lane's chain of n products has a relative error of about 2^-24 * sqrt(n / 6); two sets halve n.  Mean over
+// random layers against 64 bits, with this rule (the kernels these replaced): 3x3 fp32 1.05e-7 (1.01e-7; one set 1.16e-7), 3x3 bf16 7.78e-8
+// (7.75e-8; 7.95e-8), 5x5 fp32 1.03e-7 (0.96e-7; 1.06e-7), 5x5 bf16 7.59e-8 (7.41e-8), 7x7 fp32 1.09e-7 (1.07e-7), 7x7 bf16 8.02e-8 (7.84e-8).
+// They take the time of one where LDS bounds the waves: 74x74x256 3x3 72.0 -> 72.8 us, 41x41x240 5x5 with dy in LDS 62.1 -> 62.6.  Where
+// registers do, 25 more cost 21x21x240 5x5 batch 238 51 -> 62 us and 49 more 28x28x256 7x7 40 -> 52.
+constexpr int filter_sets(int K, bool dylds) { return K == 3 || (K == 5 && dylds) ? 2 : 1; }
 template <typename T, int K, int S> constexpr bool DY_LDS = K == 3 ? sizeof(T) == 2 || S == 2 : K == 5 && S == 1 && sizeof(T) == 4;
 bool filter_tile(const Geom &g, int dtype, FlatTile *ft)
 {
@@ -746,19 +746,10 @@ static hipError_t filter_go(const Geom &g, int dtype, const void *x, const void 
     const size_t red = (size_t)(K * K <= 25 ? K * K : 25) * ft.threads * 4;
     if (red > lds) lds = red;
     constexpr int NC = K > 3 && sizeof(T) == 2 ? 2 : 1;
-    constexpr bool WIDE = sizeof(T) == 4;
-    auto kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, NC, false, filter_sets(K, WIDE, true)> : k_nchwf_bwd_filter<T, K, S, false, NC, false, filter_sets(K, WIDE, true)>;
+    constexpr int SETS = filter_sets(K, false), SETS_LDS = filter_sets(K, true);
+    auto kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, NC, false, SETS> : k_nchwf_bwd_filter<T, K, S, false, NC, false, SETS>;
     if constexpr (DY_LDS<T, K, S>) {
-        if (ft.pout) kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, NC, true, filter_sets(K, WIDE, true)> : k_nchwf_bwd_filter<T, K, S, false, NC, true, filter_sets(K, WIDE, true)>;
-    }
-    if constexpr (filter_sets(K, WIDE, false) != filter_sets(K, WIDE, true)) {
-        if (g.W % 4 == 0) {
-            constexpr int SETS = filter_sets(K, WIDE, false);
-            kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, NC, false, SETS> : k_nchwf_bwd_filter<T, K, S, false, NC, false, SETS>;
-            if constexpr (DY_LDS<T, K, S>) {
-                if (ft.pout) kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, NC, true, SETS> : k_nchwf_bwd_filter<T, K, S, false, NC, true, SETS>;
-            }
-        }
+        if (ft.pout) kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, NC, true, SETS_LDS> : k_nchwf_bwd_filter<T, K, S, false, NC, true, SETS_LDS>;
     }
     hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(ft.threads), lds, st, g, (const T *)x, (const T *)dy, ws, parts,
                        per, ft, nblocks);
