@@ -227,16 +227,19 @@ static double generic_us(const GGeom &g, int layout, int pass)
         const double steps = ceil(pixels / parts / 4), blocks = (double)((g.O + 63) / 64) * g.K * g.K * g.Cg * parts / 2048;
         return 4.6 + 0.3 * steps + 0.53 * blocks * steps + 20e-6 * parts * J;
     }
-    auto taps = [&](long long n) { return (double)(n < g.K ? n : g.K); };
+    // rows (columns) of the filter that an output needs, or that the outputs of a wavefront need between them: the others of its lanes wait
+    // for each; in NHWC they are channels of one pixel
+    const bool together = !nhwc || (pass == 0 ? g.O : g.C) < 64;
+    auto taps = [&](long long n, int in, int out) { n = together ? in + (out - 1LL) * g.s : n; return (double)(n < g.K ? n : g.K); };
     double products, latency, rate, outputs;                     // products of an output; M products in a us
     if (pass == 0) {
-        products = g.Cg * taps(g.H) * taps(g.W);
+        products = g.Cg * taps(g.H, g.H, g.Ho) * taps(g.W, g.W, g.Wo);
         outputs = (double)g.N * g.O * g.Ho * g.Wo;
         latency = 4 + 0.15 * products;
         rate = (g.K == 1 ? 1.0 : g.K == 3 ? 1.95 : 2.3) * (strided ? 0.7 : 1.0);
     } else {
         const bool skips = nhwc && strided && g.K > 1;
-        products = g.Og * taps((long long)g.Ho * g.s) * taps((long long)g.Wo * g.s);
+        products = g.Og * taps((long long)g.Ho * g.s, g.H, g.Ho) * taps((long long)g.Wo * g.s, g.W, g.Wo);
         outputs = (double)g.N * g.C * g.H * g.W;
         latency = 4.3 + (skips ? 0.13 : 0.23) * products;
         rate = (g.K == 1 ? 0.6 : g.K == 3 ? 1.05 : 1.2) * (skips ? 1.8 : nhwc && g.K == 3 ? 0.65 : 1.0);
@@ -258,15 +261,17 @@ static bool gemm_over_generic(const GGeom &g, int layout, int dtype, int pass)
     return gconv_gemm_us(g, layout, dtype, pass, &positions, &tiles) * (pass == 0 ? 1.0 : 0.9) < generic;
 }
 
-// In place of the NCHW row walk: not where the filter leaves tiles of few positions and a block has several of them (fp32, 64 channels a
-// group, rows of 20: 257 -> 857 us), and not for the fp32 filter gradient of 16 channels a group on many pixels (1.03 times as long at the
-// median of random layers, up to 1.8).
+// In place of the NCHW row walk: in fp32 not where the filter leaves tiles of few positions, a block has several of them and the row walk,
+// at its usual 9 million products a us, is shorter (64 channels a group, rows of 20: 257 us against 857; 3456x89x24 in 54 groups, whose filter
+// is larger than the L2 and walked again for every strip, 3285 against 375), and not for the fp32 filter gradient of 16 channels a group on many
+// pixels (1.03 times as long at the median of random layers, up to 1.8).
 static bool gemm_over_rowwalk(const GGeom &g, int layout, int dtype, int pass)
 {
-    if (pass == 2) return !(dtype == DT_F32 && g.Cg == 16 && (long long)g.N * g.Ho * g.Wo >= 16384);
+    if (dtype != DT_F32) return true;
+    if (pass == 2) return !(g.Cg == 16 && (long long)g.N * g.Ho * g.Wo >= 16384);
     int positions, tiles;
-    gconv_gemm_us(g, layout, dtype, pass, &positions, &tiles);
-    return !(positions < 81 && tiles >= 3);
+    const double us = gconv_gemm_us(g, layout, dtype, pass, &positions, &tiles);
+    return !(positions < 81 && tiles >= 3) || us < (double)g.N * g.O * g.Ho * g.Wo * g.Cg * g.K * g.K / 9e6;
 }
 
 static GPlan gplan(const GGeom &g, int layout, int dtype, int pass)

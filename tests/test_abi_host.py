@@ -285,6 +285,10 @@ def test_group_shapes_that_are_shorter_one_output_per_thread():
     assert names(90, 90, 7, 7, 7, 1, 0, 30, 90, layout=dw.NHWC, dtype=dw.BF16)[:2] == ["group_generic"] * 2
     assert names(148, 128, 21, 20, 3, 1, 1, 2, 128)[:2] == ["group_nchw_rowwalk_k3s1", "group_nchw_rowwalk_k3s1_flip"]
     assert names(148, 128, 21, 20, 3, 1, 1, 2, 128, dtype=dw.BF16)[:2] == gemm[:2]
+    # the row walk reads its filter again for every strip: more than the L2 holds
+    assert names(1, 3456, 89, 24, 3, 1, 1, 54, 3456)[:2] == names(8, 3072, 15, 12, 3, 1, 1, 48, 3072)[:2] == gemm[:2]
+    # dy of one pixel: every input pixel needs one tap, a wavefront of pixels all of them
+    assert names(7, 48, 7, 7, 7, 2, 0, 3, 48, dtype=dw.BF16)[1] == names(123, 258, 5, 5, 5, 1, 0, 43, 258, dtype=dw.BF16)[1] == gemm[1]
     assert names(64, 512, 14, 14, 3, 1, 1, 32, 512)[:2] != ["group_generic"] * 2
 
 
