@@ -149,10 +149,10 @@ static const char *flat_name(int K, int s, int pass)
 }
 static bool plan_flat(const Geom &g, int dtype, int pass, Plan &pl)
 {
-    // 7x7 layers of a few thousand outputs stay with the generic kernels.  The filter gradient: its two reductions cost more
-    // than the sums (2x8x9x9 4.6 us against 9.9, 4x32x14x14 7.8 against 10.0, 8x64x28x28 44 against 14).  A forward pass of
-    // this size is launch latency either way (7.4 against 5.2; the input gradient 11.4 against 5.2).
-    if (g.K == 7 && pass != 1 && (long long)g.N * g.O * g.Ho * g.Wo < (pass == 2 ? 32768 : 2048)) return false;
+    // 7x7 filter gradients of a few thousand outputs stay with the generic kernels: the two reductions here cost more than the sums
+    // (generic against these, 2x8x9x9 4.6 us and 9.9, 4x32x14x14 7.8 and 10.0, 8x64x28x28 44 and 14).  The forward pass is shorter here at
+    // any size (2x8x9x9 fp32 8.1 us and 5.7, bf16 8.5 and 7.3, 1x256x7x7 unpadded 13.4 and 6.2).
+    if (g.K == 7 && pass == 2 && (long long)g.N * g.O * g.Ho * g.Wo < 32768) return false;
     if (pass == 0 ? !nchwf_fwd_supported(g, dtype) : pass == 1 ? !nchwf_bwd_data_supported(g, dtype) : false) return false;
     if (pass == 2) {
         const int parts = nchwf_bwd_filter_parts(g, dtype);
@@ -327,7 +327,7 @@ static Plan plan_bwd_filter_v(const Geom &g, int layout, int dtype, int force_v)
             nhwc_bwd_filter_tiling(g, V, TH, NI, &CT, &nct, &nowt, &nst, &ngr);
             // keep the partials within 64 MiB: more images per block, then taller strips; a shape that is
             // still above it with whole columns of the whole batch per block (very many channels times very
-            // wide rows) goes to the generic kernels, whose partials are a single O*K*K array in that case
+            // wide rows) goes to the any-channel kernels, whose partials are at most 8 MiB or a single O*K*K array
             while ((long long)nowt * nst * ngr * g.O * g.K * g.K * 4 > (64ll << 20) && (NI < g.N || TH < g.Ho)) {
                 if (NI < g.N) NI = NI * 2 < g.N ? NI * 2 : g.N; else TH = TH * 2 < g.Ho ? TH * 2 : g.Ho;
                 nhwc_bwd_filter_tiling(g, V, TH, NI, &CT, &nct, &nowt, &nst, &ngr);
