@@ -1,4 +1,8 @@
-// Group convolution of any group size, filter, stride and padding in either layout on the 16x16 matrix instructions.
+// Group convolution on the 16x16 matrix instructions: either layout, any group size and padding, strides up to 4, K up to 7 (filter gradient:
+// 5), where the filter entries of 16 outputs and the smallest tile fit 64 KiB of LDS.  Where they do not, one output per thread is left, in
+// the forward pass and, at stride 1, the input gradient: fp32 5x5 with 24 channels a group, and with 32 on rows of 16 and more (at stride 2
+// both on all rows); fp32 7x7 with 16 and fewer on rows of 28 and more; fp32 NCHW 3x3 stride 2 with 24 and 32 on rows from 75 on; bf16 5x5
+// with 24, and NCHW stride 2 with 32, on most rows from 56 on.
 //
 // Forward (and the input gradient): D[o][pixel] += sum over (tap, input channel) W[o][tap, ci] * X[tap, ci][pixel], 16 output
 // channels x 16 pixels per instruction.  A block owns up to a few times 16 output channels and a tile of positions; the

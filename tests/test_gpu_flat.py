@@ -46,6 +46,9 @@ CASES = [
     (2, Layer("few_tall_s2", 2, 146, 147, 3, 2, 1)),
     (1, Layer("few_tall_k5_m2", 2, 131, 30, 5, 1, 2, 2)),
     (1, Layer("few_short", 2, 5, 130, 5, 1, 2)),                       # one band that is not cut
+    (2, Layer("few_k7", 8, 9, 9, 7, 1, 3)),                            # the forward pass of any size, the filter gradient generic
+    (1, Layer("one_output_k7", 256, 7, 7, 7, 1, 0)),
+    (3, Layer("narrow_bands", 10, 104, 4, 5, 2, 2)),                   # rows too short to cut bands
 ]
 
 
