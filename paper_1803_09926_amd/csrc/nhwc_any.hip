@@ -9,7 +9,7 @@
 //
 // One output per thread -> these kernels, us on one MI355X at batch 64, forward / input gradient / filter gradient: 56x56x128 5x5
 // stride 2 fp32 142 / 347 / 900 -> 36 / 37 / 41 (bound by its K vector loads per row and column, 8 bytes a lane); 28x28x256 7x7 fp32
-// 660 / 890 / 2430 -> 58 / 58 / 73; 56x56x30 3x3 fp32 49 / 67 / 954 -> 12.5 / 12.5 / 18.
+// 660 / 890 / 2430 -> 58 / 58 / 65; 56x56x30 3x3 fp32 49 / 67 / 954 -> 12.5 / 12.5 / 18.
 #include "bounds.hpp"
 #include "point.hpp"
 #include <type_traits>
@@ -415,7 +415,8 @@ bool filter_tile_any(const Geom &g, FilterTile *f)
         if (e > beste * 1.1) { beste = e; best = ct; }
     }
     f->CT = best; f->nct = cdiva(Q, best);
-    // about 768 blocks; strips only where there are not enough images, parts of a row only where there are not enough strips
+    // about 768 blocks; strips only where there are not enough images, parts of a row only where the strips are fewer than the compute units:
+    // each part is a partial more (56x56x128 5x5 stride 2 batch 64, 256 strips: fp32 32 us with 256 partials, 36 with 512)
     const int want = 768, nty = 256 / best;
     int TH = g.Ho;
     while (TH > 7 && (long long)g.N * cdiva(g.Ho, TH) * f->nct < want) TH = (TH + 1) / 2;
@@ -423,7 +424,7 @@ bool filter_tile_any(const Geom &g, FilterTile *f)
     f->nstrips = cdiva(g.Ho, f->TH);
     const long long rows = (long long)g.N * f->nstrips;
     int tiles = cdiva(g.Wo, nty);
-    while (tiles > 1 && rows * cdiva(cdiva(g.Wo, nty), tiles) * f->nct < want) tiles = (tiles + 1) / 2;
+    while (tiles > 1 && rows * cdiva(cdiva(g.Wo, nty), tiles) * f->nct < 256) tiles = (tiles + 1) / 2;
     f->TW = tiles * nty;
     f->ncols = cdiva(g.Wo, f->TW);
     const long long items = rows * f->ncols, J = (long long)g.O * g.K * g.K;
