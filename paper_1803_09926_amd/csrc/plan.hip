@@ -55,11 +55,13 @@ static int nhwc_pf(const Geom &g, int dtype)
 // 4x240x40x40 5x5 20.9 -> 5.7, 3x3 15.3 -> 4.7; bf16 NHWC 8x32x112x112 9.4 -> 4.7, 16x128x56x56 10.1 -> 6.4, 64x256x28x28 12.5 ->
 // 10.1; fp32 NHWC 1x512x14x14 4.5 -> 3.0.  Half the limit leaves the NHWC 5x5 at 16.1 where this gives 6.6.
 constexpr int MIN_LANES = 65536;
-// (NCHW fp32 keeps tall strips from 2^20 outputs on: 44x32x65x20 3x3 5.9 us, with short ones 7.1; 16x64x32x32 5x5 8.6 against 10.)
+// (NCHW fp32 keeps tall strips from 2^20 outputs on where rows are under 64 and for 5x5: 44x32x65x20 3x3 5.9 us, with short ones 7.1;
+// 16x64x32x32 5x5 8.6 against 10.  3x3 on wider rows, 400 layers of 2^20 to 2^22 outputs: short ones 14 % faster up to 1.75 million, as long on
+// average from 2 million on, between 8 % slower and as fast.)
 static long long nchw_lanes(const Geom &g, int dtype, int V)
 {
     const long long rows = (long long)g.N * g.O;
-    return dtype == DT_F32 && rows * g.H * g.W >= 1 << 20 ? MIN_LANES : rows * (g.W / V);
+    return dtype == DT_F32 && (g.W < 64 || g.K == 5) && rows * g.H * g.W >= 1 << 20 ? MIN_LANES : rows * (g.W / V);
 }
 static int pick_th(int rows, long long lanes, int stride, int dflt1 = 14, int dflt2 = 0)
 {

@@ -95,7 +95,7 @@ def _one(pattern):
 
 
 def short(name):
-    name = re.sub(r"\(.*$", "", name)
+    name = re.sub(r"\(.*$", "", name.replace("(anonymous namespace)::", ""))
     return name.replace("void dwc::", "").replace("dwc::", "")
 
 
