@@ -248,30 +248,27 @@ static double generic_us(const GGeom &g, int layout, int pass)
     return sqrt(latency * latency + all * all);
 }
 
-// Laying out the filter and staging a tile are a fixed 10 to 20 us, and a filter that takes the LDS leaves small tiles: few products per output
-// and few outputs, or few channels a group with a large filter, are shorter one output per thread.  Of random layers that both take, 38 % of
-// the forward passes and 22 % of the input gradients were slower by more than a tenth on the matrix instructions (2x8 channels a group at
-// 226x80x80 5x5 fp32 83 -> 282 us, 90x7x7x90 groups of 3 7x7 bf16 16 -> 88); with the estimates 1.7 and 1.5 %, and 1.4 and 3.3 % stay generic
-// that would be shorter here.  The filter gradient, whose time here hardly depends on the layer as long as it is short: 14 % -> 1 %, 1 %.
+// Laying out the filter and staging a tile are a fixed 6 to 15 us, and a filter that takes the LDS leaves small tiles: few products per output
+// and few outputs, or few channels a group with a large filter, are shorter one output per thread.  Of random layers that came here by the
+// estimates from the generic kernels, 2.8 % of the forward passes and 1.2 % of the input gradients are slower by more than 8 % (at the mean
+// 0.47 and 0.28 of the time); the input gradient's generic estimate is the lower of the two by 0.85 at the median.  The filter gradient, whose
+// time here hardly depends on the layer as long as it is short: 1 % either way.
 static bool gemm_over_generic(const GGeom &g, int layout, int dtype, int pass)
 {
     const double generic = generic_us(g, layout, pass);
     if (pass == 2) return generic > (g.K == 1 ? 10.5 : g.K == 3 ? 12.5 : 16.0);
-    int positions, tiles;
-    return gconv_gemm_us(g, layout, dtype, pass, &positions, &tiles) * (pass == 0 ? 1.0 : 0.9) < generic;
+    return gconv_gemm_us(g, layout, dtype, pass) * (pass == 0 ? 0.95 : 0.85) < generic;
 }
 
-// In place of the NCHW row walk: in fp32 not where the filter leaves tiles of few positions, a block has several of them and the row walk,
-// at its usual 9 million products a us, is shorter (64 channels a group, rows of 20: 257 us against 857; 3456x89x24 in 54 groups, whose filter
+// In place of the NCHW row walk: in fp32 not where the filter leaves many tiles of few positions and the row walk, at its usual 9 million
+// products a us, is shorter (64 channels a group, rows of 90, batch 7: 196 us against 229; 3456x89x24 in 54 groups, whose filter
 // is larger than the L2 and walked again for every strip, 3285 against 375), and not for the fp32 filter gradient of 16 channels a group on many
 // pixels (1.03 times as long at the median of random layers, up to 1.8).
 static bool gemm_over_rowwalk(const GGeom &g, int layout, int dtype, int pass)
 {
     if (dtype != DT_F32) return true;
     if (pass == 2) return !(g.Cg == 16 && (long long)g.N * g.Ho * g.Wo >= 16384);
-    int positions, tiles;
-    const double us = gconv_gemm_us(g, layout, dtype, pass, &positions, &tiles);
-    return !(positions < 81 && tiles >= 3) || us < (double)g.N * g.O * g.Ho * g.Wo * g.Cg * g.K * g.K / 9e6;
+    return !gconv_gemm_small_tiles(g, layout, dtype, pass) || gconv_gemm_us(g, layout, dtype, pass) < (double)g.N * g.O * g.Ho * g.Wo * g.Cg * g.K * g.K / 9e6;
 }
 
 static GPlan gplan(const GGeom &g, int layout, int dtype, int pass)

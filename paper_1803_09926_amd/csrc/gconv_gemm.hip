@@ -1,13 +1,10 @@
 // Group convolution on the 16x16 matrix instructions: either layout, any group size and padding, strides up to 4, K up to 7 (filter gradient:
-// 5), where the filter entries of 16 outputs and the smallest tile fit 64 KiB of LDS.  Where they do not, one output per thread is left, in
-// the forward pass and, at stride 1, the input gradient: fp32 5x5 with 24 channels a group, and with 32 on rows of 16 and more (at stride 2
-// both on all rows); fp32 7x7 with 16 and fewer on rows of 28 and more; fp32 NCHW 3x3 stride 2 with 24 and 32 on rows from 75 on; bf16 5x5
-// with 24, and NCHW stride 2 with 32, on most rows from 56 on.
+// 5), where the filter entries of 16 outputs and the smallest tile fit the LDS of a compute unit.
 //
 // Forward (and the input gradient): D[o][pixel] += sum over (tap, input channel) W[o][tap, ci] * X[tap, ci][pixel], 16 output
-// channels x 16 pixels per instruction.  A block owns up to a few times 16 output channels and a tile of positions; the
-// input pixels its taps reach sit in LDS as [pixel][channel] with the zero padding written out, so that for any stride and
-// tap a lane's operand is four consecutive channels of one pixel: one 8-byte (bf16) or 16-byte (fp32) LDS read.  The filter
+// channels x 16 pixels per instruction, two taps or chunks of channels at a time in bf16.  A block owns up to a few times 16 output channels
+// and tiles of positions; the input pixels a tile's taps reach sit in LDS as [pixel][channel] with the zero padding written out, so that for
+// any stride and tap a lane's operand is four consecutive channels of one pixel: one 8-byte (bf16) or 16-byte (fp32) LDS read.  The filter
 // entries are laid out in LDS once per block in operand order.  With fewer than 16 channels per group the 16 outputs span
 // several groups and the entries that pair different groups are zeros; a tile that holds an infinity or NaN is then
 // computed without them, so that it stays inside its group.
@@ -15,13 +12,17 @@
 // s*s classes (f, e) of output pixels, each a stride-1 convolution over the same staged dy tile.
 // Filter gradient: D[o][ci] += dy[o][pixel] * X[ci][pixel + tap], the contraction over pixels, all taps in registers.
 //
-// What bounds it: not the matrix cores (the three passes of the 14x14 layer below need 2 us of them) but the latency of a short
-// block: filter, tile and outputs are three rounds to memory, so every lane issues its loads of a round together (with one load
-// at a time the same passes took 20, 20 and 40 us).  us on one MI355X, one output per thread -> these kernels, forward / input
-// gradient / filter gradient: 14x14x512, 16 channels a group, bf16 NHWC batch 32 207 / 777 / 888 -> 14 / 16 / 20; 56x56x256
-// stride 2, 8 channels a group, bf16 NCHW batch 16 183 / 893 / 396 -> 24 / 22 / 31; 57x57x128, 4 channels a group, fp32 NCHW
-// batch 64 629 / 950 / 1730 -> 155 / 154 / 145 (there 3 of 4 products are zeros).
+// What bounds it: not the matrix cores (the three passes of the 14x14 layer below need 2 us of them) nor the memory's latency (0.7 us of a
+// block) but the instructions around them: laying out the filter one entry a load took a block 2 to 4 us, dividing out every staged pixel 3,
+// positions of 16 lanes computed in all 64 a further one.  So the filter comes in whole vectors, a lane's place in the tile is found
+// once, positions are looked up in a table, the loop over taps and chunks is one, and the next tile's loads are under way while a tile is
+// computed.  us on one MI355X, one entry at a time -> now, forward / filter gradient (stage 1 and 2) / input gradient: 14x14x512, 16 channels
+// a group, bf16 NHWC batch 32 15.0 / 19.7 / 17.0 -> 9.9 / 14.5 / 10.6; 56x56x256 stride 2, 8 channels a group, bf16 NCHW batch 16
+// 24.9 / 31.5 / 21.8 -> 16.4 / 22.8 / 18.6; 57x57x128, 4 channels a group, fp32 NCHW batch 64 151 / 144 / 151 -> 116 / 134 / 116 (there 3 of 4
+// products are zeros: 49 us of matrix instructions a pass).  A tile may take more than 64 KiB of LDS where the filter does: 28x28x512, 32
+// channels a group at stride 2, fp32 NCHW batch 16, forward 83 -> 33.
 #include "gconv.hpp"
+#include <type_traits>
 
 namespace dwc {
 
@@ -29,6 +30,8 @@ namespace {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef short v4s __attribute__((ext_vector_type(4)));
+typedef __bf16 v8b __attribute__((ext_vector_type(8)));
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
 // four consecutive channels of one pixel, or of one output's filter entries, in the storage type
 template <typename T> struct Frag;
@@ -47,18 +50,67 @@ __device__ __forceinline__ v4f mma16(const Frag<bf16_t> &a, const Frag<bf16_t> &
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(v4s, a.v), __builtin_bit_cast(v4s, b.v), d, 0, 0, 0);
 }
 
+// two fragments of each side: one instruction of 32 products in bf16
+__device__ __forceinline__ v4f mma32(const Frag<float> &a0, const Frag<float> &a1, const Frag<float> &b0, const Frag<float> &b1, v4f d)
+{
+    return mma16(a1, b1, mma16(a0, b0, d));
+}
+__device__ __forceinline__ v4f mma32(const Frag<bf16_t> &a0, const Frag<bf16_t> &a1, const Frag<bf16_t> &b0, const Frag<bf16_t> &b1, v4f d)
+{
+    const u4v_t a = {a0.v.x, a0.v.y, a1.v.x, a1.v.y}, b = {b0.v.x, b0.v.y, b1.v.x, b1.v.y};
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b), d, 0, 0, 0);
+}
+
 __device__ __forceinline__ void gather4(Frag<float> &f, const float *a, const float *b, const float *c, const float *d)
 {
     f.v = make_float4(*a, *b, *c, *d);
 }
-__device__ __forceinline__ void gather4(Frag<bf16_t> &f, const bf16_t *a, const bf16_t *b, const bf16_t *c, const bf16_t *d)
-{
-    f.v = make_uint2((uint32_t)*a | (uint32_t)*b << 16, (uint32_t)*c | (uint32_t)*d << 16);
-}
-
 template <typename T> __device__ __forceinline__ bool nonfinite(T v);
 template <> __device__ __forceinline__ bool nonfinite<float>(float v) { return (__float_as_uint(v) & 0x7f800000u) == 0x7f800000u; }
 template <> __device__ __forceinline__ bool nonfinite<bf16_t>(bf16_t v) { return (v & 0x7f80u) == 0x7f80u; }
+
+// Whether values, as stored, hold an infinity or NaN: their products with zero (fp32), or the largest exponent of two to a word (bf16).
+template <typename T> struct Finite;
+template <> struct Finite<float> {
+    float m = 0.f;
+    __device__ __forceinline__ void add(uint32_t q) { m = fmaf(__uint_as_float(q), 0.f, m); }
+    __device__ __forceinline__ bool bad() const { return m != m; }
+};
+template <> struct Finite<bf16_t> {
+    uint32_t m = 0;
+    __device__ __forceinline__ void add(uint32_t q)
+    {
+        m = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, m), __builtin_bit_cast(u16x2, q & 0x7fff7fffu)));
+    }
+    __device__ __forceinline__ bool bad() const { return (m & 0xffffu) >= 0x7f80u || m >> 16 >= 0x7f80u; }
+};
+
+// V consecutive outputs at any alignment
+template <typename T, int V, typename A> __device__ __forceinline__ void store_run(T *p, const A &v)
+{
+    if constexpr (sizeof(T) == 4) {
+        float r[V];
+#pragma unroll
+        for (int i = 0; i < V; ++i) r[i] = v[i];
+        __builtin_memcpy(p, r, sizeof r);
+    } else {
+        uint32_t r[V / 2];
+#pragma unroll
+        for (int i = 0; i < V / 2; ++i) r[i] = pack2_bf16(v[2 * i], v[2 * i + 1]);
+        __builtin_memcpy(p, r, sizeof r);
+    }
+}
+
+// How the 256 lanes of a block copy a tile into LDS where FAST holds: lane t takes item t % per of row t / per, so that the divisions
+// are done once and an item costs a few additions; `rows` rows in nrit steps of RPI, for every `cols` columns of a wider tile again.
+// NHWC: an item is 16 bytes of channels of a pixel, a row one of the tile (all images); NCHW: four channels of four columns, a row one
+// of a channel quad.
+struct StageGeom {
+    int LH, LW, pitch;               // the tile: rows of an image, columns, elements between pixels
+    int imrows, rows, cols, per, nv; // imrows: rows of all images; nv: items of a pixel (NHWC)
+    int RPI, nrit, iters;
+    float rper, rnv, rLH, rimrows;
+};
 
 // One launch: the convolution from `in` (CI channels, Hi x Wi) to `out` (CO channels, Ho x Wo).  Position (a, b) of a tile
 // reads input row IS*a - ip + roff and writes output row OS*a + f - op; roff = kh forward, -k for tap kh = f + OS*k backward.
@@ -68,6 +120,7 @@ struct GemmGeom {
     int K, IS, OS, ip, op;
     int a0, na, b0, nb;    // positions of the whole image
     int bwd;
+    int pairs, shift;      // E = 2: a position's outputs are columns 2b - 2*(op/2) and the next one; shift: odd op, the second one is class 0 of position b + 1
     // tile
     int TN, TA, TB;        // images, rows and columns of positions
     int tn, ta, tb;        // tiles in each direction
@@ -77,26 +130,26 @@ struct GemmGeom {
     int nchb;              // channel blocks
     int packed;            // output blocks span groups
     int FO, FCg;           // filter dims: output channels, input channels per group (of the forward layer)
-    float rCgi, rCgo, rKK, rnk;   // reciprocals for fdiv
+    float rCgi, rCgo, rKK, rnk, rFCg, rTA, rTB, rta, rtb;   // reciprocals for fdiv
 };
 
 // n / d for 0 <= n < 2^21 and d with reciprocal r = 1.0f / d: the half keeps the product away from the integers by more than
 // its rounding error (0.5 / d against n / d * 2^-22), four instructions instead of the twenty of an integer division.
 __device__ __forceinline__ int fdiv(int n, float r) { return (int)(((float)n + 0.5f) * r); }
 
+__device__ __forceinline__ int uniform_div(int n, float r) { return __builtin_amdgcn_readfirstlane(fdiv(n, r)); }
+
 __device__ __forceinline__ int cin_first(int o0, const GemmGeom &g) { return fdiv(o0, g.rCgo) * g.Cgi & ~3; }
 
 // Input pixels of a tile to LDS as [image][row][column][channel]; what lies outside the image or the tensor's channels is
-// written as zero.  Returns whether the lane staged an infinity or NaN.
-// FAST: NHWC channel counts that are whole 16-byte vectors; NCHW tiles that span the rows.
-template <typename T, bool NHWC, bool FAST>
+// written as zero.  Any channel count, any width.  Returns whether the lane staged an infinity or NaN.
+template <typename T, bool NHWC>
 __device__ __forceinline__ bool stage_pixels(const T *__restrict__ in, T *lx, int N, int C, int H, int W, int n0, int nimg, int h0, int w0,
                                              int LH, int LW, int ca, int CL, int pitch, bool check)
 {
-    [[maybe_unused]] constexpr int VE = 16 / (int)sizeof(T);
     bool bad = false;
     const int npix = nimg * LH * LW;
-    const float rLW = 1.0f / (float)LW, rLH = 1.0f / (float)LH;
+    const float rLW = __builtin_amdgcn_rcpf((float)LW), rLH = __builtin_amdgcn_rcpf((float)LH);
     // image, row and column of a staged pixel; false if it lies outside
     auto locate = [&](int pix, int &n, int &h, int &w) {
         const int r = fdiv(pix, rLW), im = fdiv(r, rLH);
@@ -104,85 +157,6 @@ __device__ __forceinline__ bool stage_pixels(const T *__restrict__ in, T *lx, in
         return n < N && (unsigned)h < (unsigned)H && (unsigned)w < (unsigned)W;
     };
     // every lane has B loads in flight before its first LDS write
-    if constexpr (NHWC && FAST) {
-        // a lane copies 16 bytes of channels of one pixel; ca is a multiple of VE
-        constexpr int B = 8;
-        const int nv = CL / VE, total = npix * nv;
-        const float rnv = 1.0f / (float)nv;
-        for (int i0 = threadIdx.x; i0 < total; i0 += B * 256) {
-            u4v_t q[B];
-            int at[B];
-#pragma unroll
-            for (int b = 0; b < B; ++b) {
-                const int i = i0 + b * 256, pix = fdiv(i, rnv), v = i - pix * nv, c = ca + v * VE;
-                int n, h, w;
-                const bool ok = locate(pix, n, h, w) && i < total && c < C;
-                at[b] = i < total ? pix * pitch + v * VE : -1;
-                q[b] = u4v_t{0u, 0u, 0u, 0u};
-                if (ok) q[b] = *reinterpret_cast<const u4v_t *>(in + (unsigned)(((n * H + h) * W + w) * C + c));
-            }
-#pragma unroll
-            for (int b = 0; b < B; ++b) {
-                if (check) {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        bad |= (sizeof(T) == 2 && (q[b][k] & 0x7f80u) == 0x7f80u) || (q[b][k] & 0x7f800000u) == 0x7f800000u;
-                }
-                if (at[b] >= 0) *reinterpret_cast<u4v_t *>(lx + at[b]) = q[b];
-            }
-        }
-        return bad;
-    }
-    if constexpr (!NHWC && FAST) {
-        // whole rows: a lane copies four channels of four consecutive pixels of a row, transposed in registers; the columns
-        // beside the row are zero from the start and stay so
-        constexpr int B = 2;
-        const int nq = CL / 4, nr = (W + 3) / 4, rows = nimg * LH, total = nr * rows * nq;
-        const float rnr = 1.0f / (float)nr, rrows = 1.0f / (float)rows;
-        const unsigned end = (unsigned)(N * C * H * W), plane = (unsigned)(H * W);
-        for (int i0 = threadIdx.x; i0 < total; i0 += B * 256) {
-            T e[B][4][4];
-            int at[B], len[B], col[B];
-#pragma unroll
-            for (int b = 0; b < B; ++b) {
-                const int i = i0 + b * 256, t = fdiv(i, rnr), run = i - t * nr, qd = fdiv(t, rrows), r = t - qd * rows;
-                const int im = fdiv(r, rLH), h = r - im * LH + h0, n = n0 + im, c = ca + qd * 4;
-                const bool ok = n < N && (unsigned)h < (unsigned)H && i < total;
-                col[b] = run * 4 - w0;
-                at[b] = (r * LW + col[b]) * pitch + qd * 4;
-                len[b] = i < total ? min(4, W - run * 4) : 0;
-                const unsigned p0 = (unsigned)(((n * C + c) * H + h) * W + run * 4);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) e[b][k][j] = T(0);
-                    if (ok && c + k < C) {
-                        const T *p = in + p0 + k * plane;
-                        if (p0 + k * plane + 4 <= end) __builtin_memcpy(e[b][k], p, 4 * sizeof(T));      // any alignment
-                        else {
-#pragma unroll
-                            for (int j = 0; j < 4; ++j) if (j < len[b]) e[b][k][j] = p[j];
-                        }
-                    }
-                }
-            }
-#pragma unroll
-            for (int b = 0; b < B; ++b)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (j >= len[b] || (unsigned)(col[b] + j) >= (unsigned)LW) continue;      // a column that no tap reaches
-                    if (check) {
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) bad |= nonfinite<T>(e[b][k][j]);
-                    }
-                    Frag<T> f;
-                    if constexpr (sizeof(T) == 4) f.v = make_float4(e[b][0][j], e[b][1][j], e[b][2][j], e[b][3][j]);
-                    else f.v = make_uint2((uint32_t)e[b][0][j] | (uint32_t)e[b][1][j] << 16, (uint32_t)e[b][2][j] | (uint32_t)e[b][3][j] << 16);
-                    *reinterpret_cast<Frag<T> *>(lx + at[b] + j * pitch) = f;
-                }
-        }
-        return bad;
-    }
     // a lane gathers four channels of one pixel; consecutive lanes take consecutive pixels of the plane (NCHW) or
     // consecutive channels (NHWC with a channel count that is no whole number of vectors)
     constexpr int B = 4;
@@ -220,10 +194,165 @@ __device__ __forceinline__ bool stage_pixels(const T *__restrict__ in, T *lx, in
     return bad;
 }
 
+// The same where FAST holds, in two steps: load() sends out the loads of BT items of a lane, commit() writes them to LDS, so that the
+// next tile is on its way while this one is computed.
+template <typename T, bool NHWC, int BT> struct Stager;
+
+template <typename T, int BT> struct Stager<T, true, BT> {
+    static constexpr int VE = 16 / (int)sizeof(T);
+    u4raw_t q[BT];
+    int rsub, csub, v;
+    __device__ __forceinline__ Stager(const StageGeom &sg)
+    {
+        rsub = fdiv(threadIdx.x, sg.rper);
+        const int rem = threadIdx.x - rsub * sg.per;
+        csub = fdiv(rem, sg.rnv);
+        v = (rem - csub * sg.nv) * VE;
+    }
+    // row and column of the lane's item `it` (uniform); false if it has none
+    __device__ __forceinline__ bool locate(const StageGeom &sg, int it, int &r, int &col) const
+    {
+        col = csub;
+        while (it >= sg.nrit) { it -= sg.nrit; col += sg.cols; }
+        r = it * sg.RPI + rsub;
+        return rsub < sg.RPI && r < sg.rows && col < sg.LW;
+    }
+    // from image 0 of the view, nimg images: rows from h0, columns from w0, channels from ca
+    __device__ __forceinline__ void load(const StageGeom &sg, const BufView &view, int nimg, int C, int H, int W, int h0, int w0, int ca, int it0)
+    {
+#pragma unroll
+        for (int b = 0; b < BT; ++b) {
+            if (it0 + b >= sg.iters) break;
+            int h, w, im = 0;
+            bool ok = locate(sg, it0 + b, h, w);
+            if (sg.rows != sg.LH) { im = fdiv(h, sg.rLH); h -= im * sg.LH; }
+            h += h0; w += w0;
+            ok = ok && im < nimg && (unsigned)h < (unsigned)H && (unsigned)w < (unsigned)W && ca + v < C;
+            // (in range every factor is below 2^24)
+            const uint32_t at = (__umul24(__umul24(__umul24(im, H) + h, W) + w, C) + ca + v) * (uint32_t)sizeof(T);
+            q[b] = view.b128(ok ? at : BufView::OUTSIDE, 0);
+        }
+    }
+    __device__ __forceinline__ void commit(const StageGeom &sg, T *lx, int, int, int it0, bool check, Finite<T> &seen) const
+    {
+#pragma unroll
+        for (int b = 0; b < BT; ++b) {
+            if (it0 + b >= sg.iters) break;
+            int r, col;
+            const bool ok = locate(sg, it0 + b, r, col);
+            if (check) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) seen.add(q[b][k]);
+            }
+            if (ok) *reinterpret_cast<u4raw_t *>(lx + __umul24(__umul24(r, sg.LW) + col, sg.pitch) + v) = q[b];
+        }
+    }
+};
+
+// Four channels of four consecutive columns of a row, transposed in registers; the columns beside the row are zero from the start and
+// stay so.
+template <typename T, int BT> struct Stager<T, false, BT> {
+    static constexpr int NW = (int)sizeof(T);      // 32-bit words of four columns
+    typedef uint32_t word_t __attribute__((ext_vector_type(NW)));
+    word_t e[BT][4];
+    int rsub, csub;
+    __device__ __forceinline__ Stager(const StageGeom &sg)
+    {
+        rsub = fdiv(threadIdx.x, sg.rper);
+        csub = threadIdx.x - rsub * sg.per;
+    }
+    // row of all channel quads and run of four columns
+    __device__ __forceinline__ bool locate(const StageGeom &sg, int it, int W, int &r, int &run) const
+    {
+        run = csub;
+        while (it >= sg.nrit) { it -= sg.nrit; run += sg.cols; }
+        r = it * sg.RPI + rsub;
+        return rsub < sg.RPI && r < sg.rows && run * 4 < W;
+    }
+    // `in` at image 0 of nimg, `end` elements of the tensor from there
+    __device__ __forceinline__ void load(const StageGeom &sg, const T *__restrict__ in, unsigned end, int nimg, int C, int H, int W, int h0, int ca,
+                                         int it0)
+    {
+        const unsigned plane = (unsigned)(H * W);
+        const bool last = W % 4 && end <= (unsigned)(nimg * C) * plane;        // a run may pass the tensor's end
+#pragma unroll
+        for (int b = 0; b < BT; ++b) {
+            if (it0 + b >= sg.iters) break;
+            int h, run, im = 0, qd = 0;
+            bool ok = locate(sg, it0 + b, W, h, run);
+            if (sg.rows != sg.imrows) { qd = fdiv(h, sg.rimrows); h -= qd * sg.imrows; }
+            if (sg.imrows != sg.LH) { im = fdiv(h, sg.rLH); h -= im * sg.LH; }
+            h += h0;
+            const int c = ca + qd * 4;
+            ok = ok && im < nimg && (unsigned)h < (unsigned)H && c < C;
+            unsigned p0 = (unsigned)(im * C + c) * plane + (unsigned)(h * W + run * 4);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int j = 0; j < NW; ++j) e[b][k][j] = 0u;
+            if (ok) {
+                // (channels behind the last one meet zeros of the filter: the last one again)
+#pragma unroll
+                for (int k = 0; k < 4; ++k, p0 += c + k < C ? plane : 0u) {
+                    // any alignment; a run that passes the row's end reads the elements behind it, at the tensor's end those before it
+                    const unsigned at = min(p0, end - 4);
+                    __builtin_memcpy(&e[b][k], in + at, 4 * sizeof(T));
+                    if (last) e[b][k] = later(e[b][k], (int)(p0 - at));
+                }
+            }
+        }
+    }
+    // the four elements from element n on
+    static __device__ __forceinline__ word_t later(word_t q, int n)
+    {
+        if constexpr (sizeof(T) == 2) {
+            const uint64_t v = __builtin_bit_cast(uint64_t, q) >> 16 * n;
+            return __builtin_bit_cast(word_t, v);
+        } else {
+            if (n & 1) q = word_t{q[1], q[2], q[3], q[3]};
+            if (n & 2) q = word_t{q[2], q[3], q[3], q[3]};
+            return q;
+        }
+    }
+    // w0: the tile's first column
+    __device__ __forceinline__ void commit(const StageGeom &sg, T *lx, int W, int w0, int it0, bool check, Finite<T> &seen) const
+    {
+        const bool whole = W % 4 == 0 && w0 <= 0 && W - w0 <= sg.LW;                // every column of a run is one of the tile
+#pragma unroll
+        for (int b = 0; b < BT; ++b) {
+            if (it0 + b >= sg.iters) break;
+            int r, run, qd = 0;
+            const bool ok = locate(sg, it0 + b, W, r, run);
+            if (sg.rows != sg.imrows) { qd = fdiv(r, sg.rimrows); r -= qd * sg.imrows; }
+            const int col = run * 4 - w0, n = ok ? W - run * 4 : 0;
+            T *at = lx + ((int)__umul24(r, sg.LW) + col) * sg.pitch + qd * 4;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                Frag<T> f;
+                if constexpr (sizeof(T) == 4)
+                    f.v = make_float4(__uint_as_float(e[b][0][j]), __uint_as_float(e[b][1][j]), __uint_as_float(e[b][2][j]), __uint_as_float(e[b][3][j]));
+                else {
+                    const uint32_t sel = j & 1 ? 0x07060302u : 0x05040100u;
+                    f.v = make_uint2(__builtin_amdgcn_perm(e[b][1][j / 2], e[b][0][j / 2], sel), __builtin_amdgcn_perm(e[b][3][j / 2], e[b][2][j / 2], sel));
+                }
+                if (whole ? n > 0 : j < n && (unsigned)(col + j) < (unsigned)sg.LW) {
+                    if (check) {
+                        if constexpr (sizeof(T) == 4) {
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) seen.add(e[b][k][j]);
+                        } else { seen.add(f.v.x); seen.add(f.v.y); }
+                    }
+                    *reinterpret_cast<Frag<T> *>(at + j * sg.pitch) = f;
+                }
+            }
+        }
+    }
+};
+
 // A tile that holds an infinity or NaN where 16 outputs span several groups, or whose filter does: one output per lane, its own
 // group's channels and the taps inside the image only.
 template <typename T, bool NHWC>
-__device__ __forceinline__ void own_group_only(const GemmGeom &g, const Frag<T> *lw, const T *lx, T *__restrict__ out, int n0, int a0,
+__device__ __forceinline__ void own_group_only(const GemmGeom &g, const Frag<T> *lw, const int *slots, const T *lx, T *__restrict__ out, int n0, int a0,
                                                          int b0, int ob, int ca)
 {
     const int npos = g.TN * g.TA * g.TB, nch = g.NS * 16, KK = g.K * g.K;
@@ -231,7 +360,8 @@ __device__ __forceinline__ void own_group_only(const GemmGeom &g, const Frag<T> 
     for (int i = threadIdx.x; i < g.OS * g.OS * npos * nch; i += 256) {
         const int oc = i % nch, q = i / nch % npos, cls = i / nch / npos;
         const int f = cls / g.OS, e = cls - f * g.OS, im = q / (g.TA * g.TB), da = q / g.TB % g.TA, db = q % g.TB;
-        const int o = ob + oc, row = g.OS * (a0 + da) + f - g.op, col = g.OS * (b0 + db) + e - g.op;
+        const int sh = g.pairs && e == 0 ? g.shift : 0;
+        const int o = ob + oc, row = g.OS * (a0 + da) + f - g.op, col = g.OS * (b0 + db + sh) + e - g.op;
         if (o >= g.CO || n0 + im >= g.N || a0 + da >= g.a0 + g.na || b0 + db >= g.b0 + g.nb || (unsigned)row >= (unsigned)g.Ho ||
             (unsigned)col >= (unsigned)g.Wo) continue;
         const int s = oc / 16, c0 = o / g.Cgo * g.Cgi, cs = cin_first(ob + s * 16, g);
@@ -241,12 +371,12 @@ __device__ __forceinline__ void own_group_only(const GemmGeom &g, const Frag<T> 
 #pragma unroll 1
             for (int kw = e, l = 0; kw < g.K; kw += g.OS, ++l) {
                 const int ro = g.bwd ? -k : kh, co = g.bwd ? -l : kw;
-                if ((unsigned)(g.IS * (a0 + da) - g.ip + ro) >= (unsigned)g.Hi || (unsigned)(g.IS * (b0 + db) - g.ip + co) >= (unsigned)g.Wi) continue;
-                const T *px = lx + ((im * g.LH + g.IS * da + ro - g.lo) * g.LW + g.IS * db + co - g.lo) * g.pitch;
+                if ((unsigned)(g.IS * (a0 + da) - g.ip + ro) >= (unsigned)g.Hi || (unsigned)(g.IS * (b0 + db + sh) - g.ip + co) >= (unsigned)g.Wi) continue;
+                const T *px = lx + ((im * g.LH + g.IS * da + ro - g.lo) * g.LW + g.IS * (db + sh) + co - g.lo) * g.pitch;
 #pragma unroll 1
                 for (int c = c0; c < c0 + g.Cgi; ++c) {
                     const int j = c - cs;
-                    const T *pw = reinterpret_cast<const T *>(&lw[((s * KK + kh * g.K + kw) * g.nk + j / 16) * 64 + j % 16 / 4 * 16 + oc % 16]);
+                    const T *pw = reinterpret_cast<const T *>(&lw[((s * KK + (slots ? slots[kh * g.K + kw] : kh * g.K + kw)) * g.nk + j / 16) * 64 + j % 16 / 4 * 16 + oc % 16]);
                     acc = fmaf(ldf(pw + j % 4), ldf(px + c - ca), acc);
                 }
             }
@@ -255,10 +385,141 @@ __device__ __forceinline__ void own_group_only(const GemmGeom &g, const Frag<T> 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Forward and input gradient.  P: 16-pixel tiles that a wavefront computes at a time against one read of the filter.
+// The filter in LDS, in operand order: fragment [output block s][tap][chunk][lane] holds output s*16 + lane%16 against the input channels
+// chunk*16 + lane/16*4 .. +3 from cin_first of the block on.  FAST: 16 bytes of the filter a lane and load, each entry then written where it
+// belongs (one entry a load, gathered in operand order, cost a 14x14 layer of 16 channels a group 2 us forward and 4 us backward of its 13).
 // ---------------------------------------------------------------------------------------------
-template <typename T, bool NHWC, bool FAST, int P>
-__global__ __launch_bounds__(256) void k_gconv_gemm(GemmGeom g, const T *__restrict__ in, const T *__restrict__ w, T *__restrict__ out,
+template <typename T, bool NHWC, bool BWD> struct FilterLoader {
+    static constexpr int VE = 16 / (int)sizeof(T);
+    const GemmGeom &g;
+    int ob, KK;
+    int g0, g1;              // groups of the block's outputs
+    int fc0, X;              // the places in a group that are read (forward: all input channels, backward: those of the block's outputs)
+    int nvr, nvec, run;      // vectors of a row, of all rows; NCHW: elements of a row (0: all rows are one run)
+    float rnvr, rX;
+    unsigned first;          // element that the first vector starts at
+
+    // NHWC backward needs quads inside a group, NCHW at least a vector's entries for a pair of channels and a whole last vector.
+    static __device__ __forceinline__ bool takes(const GemmGeom &g)
+    {
+        const int KK = g.K * g.K;
+        return NHWC ? !BWD || g.Cgi % 4 == 0 : KK >= VE && (unsigned)(g.FO * g.FCg * KK) % VE == 0;
+    }
+
+    const int *slots;        // where a tap's entries go (null: in order)
+
+    __device__ __forceinline__ FilterLoader(const GemmGeom &geom, int ob_, const int *slots_) : g(geom), ob(ob_), KK(geom.K * geom.K), slots(slots_)
+    {
+        const int olast = min(ob + g.NS * 16, g.CO) - 1;
+        g0 = fdiv(ob, g.rCgo); g1 = fdiv(olast, g.rCgo);
+        fc0 = 0; X = g.FCg; run = 0;
+        if (BWD && g0 == g1) {
+            const int n = olast + 1 - ob;
+            if (NHWC || n * KK % VE == 0) { fc0 = ob - g0 * g.Cgo; X = n; }
+        }
+        int rows;
+        if (NHWC) {
+            // rows of (tap, place in the group): forward the block's outputs, backward the groups' input channels
+            first = BWD ? (unsigned)(g0 * g.Cgi) & ~(unsigned)(VE - 1) : (unsigned)ob;
+            nvr = BWD ? (int)((g1 + 1) * g.Cgi - first + VE - 1) / VE : g.NS * 16 / VE;
+            rows = KK * X;
+        } else {
+            first = BWD ? (unsigned)(g0 * g.Cgi * g.FCg + fc0) * KK : (unsigned)(ob * g.FCg) * KK;
+            rows = BWD ? (g1 - g0 + 1) * g.Cgi : olast + 1 - ob;
+            if (BWD && X < g.FCg) run = X * KK;
+            nvr = run ? run / VE : (rows * g.FCg * KK + VE - 1) / VE;
+            if (!run) rows = 1;
+        }
+        nvec = rows * nvr;
+        rnvr = __builtin_amdgcn_rcpf((float)nvr); rX = __builtin_amdgcn_rcpf((float)X);
+    }
+    __device__ __forceinline__ u4raw_t load(const T *__restrict__ w, int i) const
+    {
+        u4raw_t q = u4raw_t{0u, 0u, 0u, 0u};
+        if (i >= nvec) return q;
+        const int row = fdiv(i, rnvr), v = (i - row * nvr) * VE;
+        if constexpr (NHWC) {
+            unsigned at = (unsigned)row;
+            if (BWD) { const int tap = fdiv(row, rX); at = (unsigned)(tap * g.FCg + fc0 + row - tap * X); }
+            // (FO is a whole number of vectors, so is every row)
+            if ((int)first + v < g.FO) q = *reinterpret_cast<const u4raw_t *>(w + at * (unsigned)g.FO + first + v);
+        } else {
+            __builtin_memcpy(&q, w + first + (unsigned)(row * g.FCg * KK) + v, 16);               // any alignment
+        }
+        return q;
+    }
+    static __device__ __forceinline__ T entry(const u4raw_t &q, int j)
+    {
+        if constexpr (sizeof(T) == 4) return __uint_as_float(q[j]);
+        else return (T)(q[j / 2] >> 16 * (j & 1));
+    }
+    // element of lw at which output o's entry for input channel c and tap 0 lies (both of one group); -1 if o is not the block's
+    __device__ __forceinline__ int place(int o, int c) const
+    {
+        const int oi = o - ob, s = oi >> 4, rel = c - cin_first(ob + (s << 4), g);
+        if ((unsigned)oi >= (unsigned)(g.NS * 16) || o >= g.CO) return -1;
+        return (((s * KK) * g.nk + (rel >> 4)) * 64 + (rel >> 2 & 3) * 16 + (oi & 15)) * 4 + (rel & 3);
+    }
+    __device__ __forceinline__ void put(T *lw, int i, const u4raw_t &q, Finite<T> &seen) const
+    {
+        if (i >= nvec) return;
+        const int tstep = g.nk * 256;
+        const int row = fdiv(i, rnvr), v = (i - row * nvr) * VE;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) seen.add(q[k]);
+        if constexpr (NHWC && !BWD) {
+            const int tap = fdiv(row, rX), x = row - tap * X, o = ob + v;
+            if (!g.packed) {                                                   // one group, all outputs there
+                T *at = lw + place(o, fdiv(o, g.rCgo) * g.Cgi + x) + tap * tstep;
+#pragma unroll
+                for (int j = 0; j < VE; ++j) at[4 * j] = entry(q, j);
+            } else {
+                const int oi = o - ob, s = oi >> 4, c0 = cin_first(ob + (s << 4), g);
+                T *at = lw + (((s * KK + tap) * g.nk) * 64 + (oi & 15)) * 4;
+#pragma unroll
+                for (int j = 0; j < VE; ++j) {
+                    const int rel = fdiv(o + j, g.rCgo) * g.Cgi + x - c0;
+                    if (o + j < g.CO) at[(rel >> 4) * 256 + (rel >> 2 & 3) * 64 + 4 * j + (rel & 3)] = entry(q, j);
+                }
+            }
+        } else if constexpr (NHWC) {
+            const int tap = fdiv(row, rX), x = row - tap * X, c = (int)first + v;
+#pragma unroll
+            for (int u = 0; u < VE; u += 4) {
+                const int grp = fdiv(c + u, g.rCgi), at = place(grp * g.Cgo + fc0 + x, c + u);
+                if (at < 0 || grp < g0 || grp > g1) continue;
+                Frag<T> f;
+                if constexpr (sizeof(T) == 4) f.v = make_float4(entry(q, 0), entry(q, 1), entry(q, 2), entry(q, 3));
+                else f.v = make_uint2(q[u / 2], q[u / 2 + 1]);
+                *reinterpret_cast<Frag<T> *>(lw + at + (slots ? slots[tap] : tap) * tstep) = f;
+            }
+        } else {
+            // entries of (row, place in the group, tap) one after the other; a vector touches two places at most
+            const int e = run ? row * run + v : v, t = fdiv(e, g.rKK), tap = e - t * KK;
+            auto at_place = [&](int t) {
+                const int r = fdiv(t, rX), x = t - r * X;
+                if (!BWD) return r + ob < g.CO ? place(ob + r, fdiv(ob + r, g.rCgo) * g.Cgi + x) : -1;
+                const int gr = g0 + fdiv(r, g.rCgi);
+                return gr <= g1 ? place(gr * g.Cgo + fc0 + x, g0 * g.Cgi + r) : -1;
+            };
+            const int at0 = at_place(t), at1 = at_place(t + 1);
+#pragma unroll
+            for (int j = 0; j < VE; ++j) {
+                const bool next = tap + j >= KK;
+                const int at = next ? at1 : at0, tp = next ? tap + j - KK : tap + j;
+                if (at >= 0) lw[at + (BWD && slots ? slots[tp] : tp) * tstep] = entry(q, j);
+            }
+        }
+    }
+};
+
+// ---------------------------------------------------------------------------------------------
+// Forward and input gradient.  SCATTER: NCHW outputs that are not consecutive (strides of the input gradient).  P: 16-pixel tiles that a wavefront computes at a time against one read of the filter.  E = 2: the
+// input gradient at stride 2 in NCHW, both columns of a pair of output classes at a time, so that a lane's four positions are eight
+// consecutive outputs (aligned for rows of whole vectors: with an odd padding the pair is class 1 of a position and class 0 of the next).
+// ---------------------------------------------------------------------------------------------
+template <typename T, bool NHWC, bool BWD, bool FAST, int P, int E, bool SCATTER>
+__global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg, const T *__restrict__ in, const T *__restrict__ w, T *__restrict__ out,
                                                     int nparts, unsigned nblocks)
 {
     extern __shared__ uint4 smem[];
@@ -266,171 +527,332 @@ __global__ __launch_bounds__(256) void k_gconv_gemm(GemmGeom g, const T *__restr
     const int chb = (int)(lb % (unsigned)g.nchb), part = (int)(lb / (unsigned)g.nchb);
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int li = lane & 15, lk = lane >> 4;
+    constexpr bool OUTER = NHWC || SCATTER;                                // a lane has four outputs of one position, otherwise one output of four
+    const int OS = BWD ? g.OS : 1, IS = BWD ? 1 : g.IS;
     const int K = g.K, KK = K * K, ob = chb * g.NS * 16;
     constexpr int VE = 16 / (int)sizeof(T);
     const int ca = cin_first(ob, g) & ~(VE - 1);
     Frag<T> *lw = reinterpret_cast<Frag<T> *>(smem);                       // [sub-block][tap][chunk][lane]
-    T *lx = reinterpret_cast<T *>(lw + (size_t)g.NS * KK * g.nk * 64);
-    const int npos = g.TN * g.TA * g.TB, npt = (npos + 15) / 16;
-
-    // the filter entries in operand order, WB fragments of a lane loaded at a time; the first ones (all of a 3x3
-    // filter with up to 16 input channels a group) are on their way while the first tile is staged (NHWC: 14x14
-    // 16 channels a group 14.4 -> 13.3 us; in NCHW the registers they take cost a wavefront per SIMD: 57x57 bf16 67 -> 74)
-    constexpr int WB = 3;
+    const int npos = g.TN * g.TA * g.TB, ngrp = (npos + 16 * P - 1) / (16 * P), nent = ngrp * 16 * P;
+    // of every position: element of its first input pixel in LDS, element of its output (-1: none; the image's first for OS > 1), and
+    // for OS > 1 row and column of that
+    int *tabx = reinterpret_cast<int *>(lw + (size_t)g.NS * KK * g.nk * 64), *tabo = tabx + nent, *tabr = tabo + nent;
+    int *slots = OS > 1 ? tabr + 2 * nent : nullptr;       // taps in the order of their classes
+    int *flag = OS > 1 ? slots + 64 : tabr;                // an infinity or NaN in the filter or the tile (two, in turn)
+    T *lx = reinterpret_cast<T *>(flag + 4);
+    if (threadIdx.x < 2) flag[threadIdx.x] = 0;
+    const int ntiles = g.tn * g.ta * g.tb;
     const int nfrag = g.NS * KK * g.nk * 64;
-    auto load_filter = [&](int i0, T (&e)[WB][4]) {
-#pragma unroll
-        for (int b = 0; b < WB; ++b) {
-            const int i = i0 + b * 256, ln = i & 63, f = i >> 6, t = fdiv(f, g.rnk), kc = f - t * g.nk, s = fdiv(t, g.rKK), tap = t - s * KK;
+    const unsigned imin = (unsigned)(g.CI * g.Hi * g.Wi), imout = (unsigned)(g.CO * g.Ho * g.Wo);
+
+    auto tile_at = [&](int tile, int &n0, int &a0, int &b0) {
+        const int row = FAST ? uniform_div(tile, g.rtb) : tile / g.tb, tn = FAST ? uniform_div(row, g.rta) : row / g.ta;
+        n0 = tn * g.TN; a0 = g.a0 + (row - tn * g.ta) * g.TA; b0 = g.b0 + (tile - row * g.tb) * g.TB;
+    };
+    constexpr int BT = NHWC || sizeof(T) == 2 ? 4 : 2;       // items of a lane in flight
+    [[maybe_unused]] Stager<T, NHWC, BT> stager(sg);
+    auto load_tile = [&](int tile, int it0) {
+        if constexpr (FAST) {
+            int n0, a0, b0;
+            tile_at(tile, n0, a0, b0);
+            const int nimg = min(g.TN, g.N - n0), h0 = IS * a0 - g.ip + g.lo, w0 = IS * b0 - g.ip + g.lo;
+            const T *p = in + (size_t)n0 * imin;
+            if constexpr (NHWC) stager.load(sg, BufView(p, (uint32_t)nimg * imin * (uint32_t)sizeof(T)), nimg, g.CI, g.Hi, g.Wi, h0, w0, ca, it0);
+            else stager.load(sg, p, (unsigned)(g.N - n0) * imin, nimg, g.CI, g.Hi, g.Wi, h0, ca, it0);
+        }
+    };
+
+    load_tile(part, 0);
+    // zeros: entries that pair different groups, inputs beside the group, outputs beside the tensor; pixels beside the rows
+    Finite<T> wseen;
+    const bool vectors = FAST && FilterLoader<T, NHWC, BWD>::takes(g);
+    if (vectors && g.packed)
+        for (int i = threadIdx.x; i < nfrag * 4 / VE; i += 256) reinterpret_cast<u4v_t *>(lw)[i] = u4v_t{0u, 0u, 0u, 0u};
+    if (!NHWC && FAST)
+        for (int i = threadIdx.x; i < (g.TN * g.LH * g.LW * g.pitch + VE - 1) / VE; i += 256) reinterpret_cast<u4v_t *>(lx)[i] = u4v_t{0u, 0u, 0u, 0u};
+    if (OS > 1 && (int)threadIdx.x < KK) {
+        const int kh = (int)threadIdx.x / K, kw = (int)threadIdx.x - kh * K, f = kh % OS, e = kw % OS;
+        auto before = [&](int f) { int n = 0; for (int i = 0; i < f; ++i) n += (K - i + OS - 1) / OS; return n; };
+        const int nl = (K - e + OS - 1) / OS;
+        slots[threadIdx.x] = before(f) * K + (K - f + OS - 1) / OS * before(e) + kh / OS * nl + kw / OS;
+    }
+    if (!NHWC || g.packed || OS > 1) __syncthreads();
+    if (vectors) {
+        const FilterLoader<T, NHWC, BWD> fl(g, ob, slots);
+#pragma unroll 1
+        for (int i0 = threadIdx.x; i0 - (int)threadIdx.x < fl.nvec; i0 += 512) {
+            const u4raw_t q0 = fl.load(w, i0), q1 = fl.load(w, i0 + 256);
+            fl.put(reinterpret_cast<T *>(lw), i0, q0, wseen);
+            fl.put(reinterpret_cast<T *>(lw), i0 + 256, q1, wseen);
+        }
+    } else {
+        // four entries of a fragment at a time, in operand order
+#pragma unroll 1
+        for (int i = threadIdx.x; i < nfrag; i += 256) {
+            const int ln = i & 63, f = i >> 6, t = fdiv(f, g.rnk), kc = f - t * g.nk, s = fdiv(t, g.rKK), tap = t - s * KK;
             const int o = ob + s * 16 + (ln & 15), c0 = cin_first(ob + s * 16, g) + kc * 16 + (ln >> 4) * 4, grp = fdiv(o, g.rCgo);
             // the input channels of the output's group
-            const int cg0 = grp * g.Cgi, cg1 = o < g.CO && i < nfrag ? min(cg0 + g.Cgi, g.CI) : cg0;
+            const int cg0 = grp * g.Cgi, cg1 = o < g.CO ? min(cg0 + g.Cgi, g.CI) : cg0;
+            T e[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int c = c0 + k;
-                const int fo = g.bwd ? c : o, fc = g.bwd ? o - grp * g.Cgo : c - cg0;
-                e[b][k] = T(0);
-                if (c >= cg0 && c < cg1) e[b][k] = w[(unsigned)(NHWC ? (tap * g.FCg + fc) * g.FO + fo : (fo * g.FCg + fc) * KK + tap)];
+                const int fo = BWD ? c : o, fc = BWD ? o - grp * g.Cgo : c - cg0;
+                e[k] = T(0);
+                if (c >= cg0 && c < cg1) e[k] = w[(unsigned)(NHWC ? (tap * g.FCg + fc) * g.FO + fo : (fo * g.FCg + fc) * KK + tap)];
             }
-        }
-    };
-    bool wbad = false;
-    auto put_filter = [&](int i0, const T (&e)[WB][4]) {
+            Frag<T> q;
+            if constexpr (sizeof(T) == 4) {
+                q.v = make_float4(e[0], e[1], e[2], e[3]);
 #pragma unroll
-        for (int b = 0; b < WB; ++b) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) wbad |= nonfinite<T>(e[b][k]);
-            const int i = i0 + b * 256;
-            if (i >= nfrag) continue;
-            if constexpr (sizeof(T) == 4) lw[i].v = make_float4(e[b][0], e[b][1], e[b][2], e[b][3]);
-            else lw[i].v = make_uint2((uint32_t)e[b][0] | (uint32_t)e[b][1] << 16, (uint32_t)e[b][2] | (uint32_t)e[b][3] << 16);
+                for (int k = 0; k < 4; ++k) wseen.add(__float_as_uint(e[k]));
+            } else {
+                q.v = make_uint2((uint32_t)e[0] | (uint32_t)e[1] << 16, (uint32_t)e[2] | (uint32_t)e[3] << 16);
+                wseen.add(q.v.x); wseen.add(q.v.y);
+            }
+            lw[slots ? ((s * KK + slots[tap]) * g.nk + kc) * 64 + ln : i] = q;
         }
-    };
-    [[maybe_unused]] T wfirst[WB][4];
-    if constexpr (NHWC) load_filter(threadIdx.x, wfirst);
-    else
-        for (int i0 = threadIdx.x; i0 < nfrag; i0 += WB * 256) {
-            T e[WB][4];
-            load_filter(i0, e);
-            put_filter(i0, e);
-        }
+    }
+    const bool wbad = wseen.bad();
+    int turn = 0;
+    __syncthreads();
 
-    if (!NHWC && FAST)
-        for (int i = threadIdx.x; i < g.TN * g.LH * g.LW * g.pitch / VE; i += 256) reinterpret_cast<u4v_t *>(lx)[i] = u4v_t{0u, 0u, 0u, 0u};
-    const int ntiles = g.tn * g.ta * g.tb, ncls = g.OS * g.OS;
     for (int tile = part; tile < ntiles; tile += nparts) {
-        const int tb = tile % g.tb, ta = tile / g.tb % g.ta, tn = tile / g.tb / g.ta;
-        const int n0 = tn * g.TN, a0 = g.a0 + ta * g.TA, b0 = g.b0 + tb * g.TB;
-        __syncthreads();                                     // the previous tile has been read (first: nothing to wait for)
-        const bool bad = stage_pixels<T, NHWC, FAST>(in, lx, g.N, g.CI, g.Hi, g.Wi, n0, g.TN, g.IS * a0 - g.ip + g.lo, g.IS * b0 - g.ip + g.lo,
-                                         g.LH, g.LW, ca, g.CL, g.pitch, g.packed != 0);
-        if (NHWC && tile == part) {
-            put_filter(threadIdx.x, wfirst);
-            for (int i0 = threadIdx.x + WB * 256; i0 < nfrag; i0 += WB * 256) {
-                T e[WB][4];
-                load_filter(i0, e);
-                put_filter(i0, e);
+        int n0, a0, b0;
+        tile_at(tile, n0, a0, b0);
+        const int h0 = IS * a0 - g.ip + g.lo, w0 = IS * b0 - g.ip + g.lo;
+        if (tile != part) __syncthreads();                   // the previous tile has been read
+        bool bad = false;
+        if constexpr (FAST) {
+            Finite<T> seen;
+#pragma unroll 1
+            for (int it0 = 0;;) {
+                stager.commit(sg, lx, g.Wi, w0, it0, g.packed != 0, seen);
+                it0 += BT;
+                if (it0 >= sg.iters) break;
+                load_tile(tile, it0);
             }
+            bad = seen.bad();
+        } else
+            bad = stage_pixels<T, NHWC>(in, lx, g.N, g.CI, g.Hi, g.Wi, n0, g.TN, h0, w0, g.LH, g.LW, ca, g.CL, g.pitch, g.packed != 0);
+        for (int t = threadIdx.x; t < nent; t += 256) {
+            const int q = t < npos ? t : 0, r = fdiv(q, g.rTB), im = fdiv(r, g.rTA), da = r - im * g.TA, db = q - r * g.TB;
+            tabx[t] = ((im * g.LH + IS * da - g.lo) * g.LW + IS * db - g.lo) * g.pitch;
+            const bool there = t < npos && a0 + da < g.a0 + g.na && b0 + db < g.b0 + g.nb && n0 + im < g.N;
+            const int row = OS * (a0 + da) - g.op, col = OS * (b0 + db) - g.op + (E == 2 ? g.shift : 0);
+            const int o = NHWC ? ((im * g.Ho + row) * g.Wo + col) * g.CO : im * (int)imout + row * g.Wo + col;
+            if (OS == 1) tabo[t] = there && (unsigned)row < (unsigned)g.Ho && (unsigned)col < (unsigned)g.Wo ? o : -1;
+            else { tabo[t] = o; tabr[t] = there ? row : 1 << 29; tabr[nent + t] = col; }
         }
         // One barrier behind the staging of every tile, whatever the filter and the tile hold: both paths below read pixels that other
         // wavefronts staged.  (wbad: what this lane laid out of the filter, so it counts for every tile of the block.)
-        if (__builtin_expect(__syncthreads_or(wbad || bad), 0)) {
-            own_group_only<T, NHWC>(g, lw, lx, out, n0, a0, b0, ob, ca);
+        if (wbad || bad) flag[turn] = 1;
+        __syncthreads();
+        const bool alone = __builtin_amdgcn_readfirstlane(flag[turn]) != 0;
+        turn ^= 1;
+        if (threadIdx.x == 0) flag[turn] = 0;                // read by all before the last barrier, set again behind the next one
+        if (FAST && tile + nparts < ntiles) load_tile(tile + nparts, 0);       // on its way while this one is computed
+        if (__builtin_expect(alone, 0)) {
+            own_group_only<T, NHWC>(g, lw, slots, lx, out, n0, a0, b0, ob, ca);
             continue;
         }
 
-        const int ngrp = (npt + P - 1) / P;
-        const float rTA = 1.0f / (float)g.TA, rTB = 1.0f / (float)g.TB;
+        T *const on = out + (size_t)n0 * imout;
         for (int item = wv; item < g.NS * ngrp; item += 4) {
-            const int s = item % g.NS, pg = item / g.NS;
+            const int s = g.NS == 1 ? 0 : item % g.NS, pg = g.NS == 1 ? item : item / g.NS;
             if (ob + s * 16 >= g.CO) continue;
             const int cl = cin_first(ob + s * 16, g) - ca + lk * 4;
-            int base[P], row0[P], col0[P], img[P];
+            int base[P];
 #pragma unroll
-            for (int p = 0; p < P; ++p) {
-                const int q0 = (pg * P + p) * 16 + li, q = q0 < npos ? q0 : 0;
-                const int r = fdiv(q, rTB), im = fdiv(r, rTA), da = r - im * g.TA, db = q - r * g.TB;
-                base[p] = ((im * g.LH + g.IS * da - g.lo) * g.LW + g.IS * db - g.lo) * g.pitch + cl;
-                img[p] = n0 + im;
-                row0[p] = g.OS * (a0 + da) - g.op;
-                col0[p] = g.OS * (b0 + db) - g.op;
-                if (q0 >= npos || a0 + da >= g.a0 + g.na || b0 + db >= g.b0 + g.nb) img[p] = g.N;      // not a position of the image
-            }
-            for (int cls = 0; cls < ncls; ++cls) {
-                const int f = cls / g.OS, e = cls - f * g.OS;
-                v4f acc[P];
-#pragma unroll
-                for (int p = 0; p < P; ++p) acc[p] = v4f{0.f, 0.f, 0.f, 0.f};
-                auto tap = [&](int kh, int kw, int ro, int co) {
-                    const int toff = (ro * g.LW + co) * g.pitch;
-                    const Frag<T> *pw = lw + ((s * KK + kh * K + kw) * g.nk) * 64 + lane;
-                    for (int kc = 0; kc < g.nk; ++kc) {
-                        const Frag<T> a = pw[kc * 64];
-#pragma unroll
-                        for (int p = 0; p < P; ++p) {
-                            const Frag<T> b = *reinterpret_cast<const Frag<T> *>(lx + base[p] + toff + kc * 16);
-                            acc[p] = mma16(a, b, acc[p]);
-                        }
-                    }
-                };
-                for (int kh = f, k = 0; kh < K; kh += g.OS, ++k)
-                    for (int kw = e, l = 0; kw < K; kw += g.OS, ++l) tap(kh, kw, g.bwd ? -k : kh, g.bwd ? -l : kw);
-                const int o = ob + s * 16 + lk * 4;
+            for (int p = 0; p < P; ++p) base[p] = tabx[(pg * P + p) * 16 + li] + cl;
+            // where the outputs of the lane's positions go
+            [[maybe_unused]] int out0[P], row0[P], col0[P];
+            if constexpr (OUTER) {
 #pragma unroll
                 for (int p = 0; p < P; ++p) {
-                    const int row = row0[p] + f, col = col0[p] + e;
-                    if (img[p] >= g.N || (unsigned)row >= (unsigned)g.Ho || (unsigned)col >= (unsigned)g.Wo || o >= g.CO) continue;
-                    if constexpr (NHWC) {
-                        T *po = out + (unsigned)(((img[p] * g.Ho + row) * g.Wo + col) * g.CO + o);
-                        const float r[4] = {acc[p][0], acc[p][1], acc[p][2], acc[p][3]};
-                        if (g.CO % 4 == 0) Vec<T, 4>::store(po, r);
-                        else {
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) if (o + k < g.CO) stf(po + k, r[k]);
-                        }
-                    } else {
-                        T *po = out + (unsigned)(((img[p] * g.CO + o) * g.Ho + row) * g.Wo + col);
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) if (o + k < g.CO) stf(po + (unsigned)(k * g.Ho * g.Wo), acc[p][k]);
-                    }
+                    const int t = (pg * P + p) * 16 + li;
+                    out0[p] = tabo[t];
+                    if (OS > 1) { row0[p] = tabr[t]; col0[p] = tabr[nent + t]; }
                 }
             }
+            const Frag<T> *pw = lw + s * KK * g.nk * 64 + lane;
+            for (int f = 0; f < OS; ++f)
+                for (int e0 = 0; e0 < OS; e0 += E) {
+                    v4f acc[E][P];
+#pragma unroll
+                    for (int e = 0; e < E; ++e)
+#pragma unroll
+                        for (int p = 0; p < P; ++p) acc[e][p] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int e = 0; e < E; ++e) {
+                        // the class's fragments in order: chunks, columns, rows; two to an instruction
+                        const int nl = (K - e0 - e + OS - 1) / OS, n = (K - f + OS - 1) / OS * nl * g.nk;
+                        const int xs = BWD ? -g.pitch : g.pitch, rs = xs * (g.LW - nl);
+                        int kc = 0, l = 0, x = E == 2 && e == 0 ? g.shift * g.pitch : 0, i = 0;
+                        auto next = [&]() {
+                            const int at = x + kc * 16;
+                            if (++kc == g.nk) { kc = 0; x += xs; if (++l == nl) { l = 0; x += rs; } }
+                            return at;
+                        };
+#pragma unroll 1
+                        for (; i + 1 < n; i += 2, pw += 128) {
+                            const Frag<T> a0 = pw[0], a1 = pw[64];
+                            const int x0 = next(), x1 = next();
+                            Frag<T> b0[P], b1[P];
+#pragma unroll
+                            for (int p = 0; p < P; ++p) {
+                                b0[p] = *reinterpret_cast<const Frag<T> *>(lx + base[p] + x0);
+                                b1[p] = *reinterpret_cast<const Frag<T> *>(lx + base[p] + x1);
+                            }
+#pragma unroll
+                            for (int p = 0; p < P; ++p) acc[e][p] = OUTER ? mma32(a0, a1, b0[p], b1[p], acc[e][p]) : mma32(b0[p], b1[p], a0, a1, acc[e][p]);
+                        }
+                        if (i < n) {
+                            const Frag<T> a0 = *pw;
+                            Frag<T> b0[P];
+#pragma unroll
+                            for (int p = 0; p < P; ++p) b0[p] = *reinterpret_cast<const Frag<T> *>(lx + base[p] + x + kc * 16);
+#pragma unroll
+                            for (int p = 0; p < P; ++p) acc[e][p] = OUTER ? mma16(a0, b0[p], acc[e][p]) : mma16(b0[p], a0, acc[e][p]);
+                            pw += 64;
+                        }
+                    }
+                    // the outputs at a position's column and (E = 2) the next one
+                    auto lower = [&](int p, int r) { return E == 2 && g.shift ? acc[E - 1][p][r] : acc[0][p][r]; };
+                    [[maybe_unused]] auto upper = [&](int p, int r) { return E == 2 && g.shift ? acc[0][p][r] : acc[E - 1][p][r]; };
+                    const int o = ob + s * 16 + (OUTER ? lk * 4 : li);
+                    if (o >= g.CO) continue;
+#pragma unroll
+                    for (int p = 0; p < P; ++p) {
+                        if constexpr (OUTER) {
+                            int at = out0[p];
+                            bool ok = at >= 0;
+                            if (OS > 1) {
+                                ok = (unsigned)(row0[p] + f) < (unsigned)g.Ho && (unsigned)(col0[p] + e0) < (unsigned)g.Wo;
+                                at += (f * g.Wo + e0) * (NHWC ? g.CO : 1);
+                            }
+                            if (!ok) continue;
+                            if constexpr (!NHWC) {
+                                T *po = on + (size_t)((unsigned)o * (unsigned)(g.Ho * g.Wo)) + at;
+#pragma unroll
+                                for (int k = 0; k < 4; ++k) if (o + k < g.CO) stf(po + (unsigned)(k * g.Ho * g.Wo), acc[0][p][k]);
+                                continue;
+                            }
+                            T *po = on + (unsigned)(at + o);
+                            const float r[4] = {acc[0][p][0], acc[0][p][1], acc[0][p][2], acc[0][p][3]};
+                            if (FAST || g.CO % 4 == 0) Vec<T, 4>::store(po, r);
+                            else {
+#pragma unroll
+                                for (int k = 0; k < 4; ++k) if (o + k < g.CO) stf(po + k, r[k]);
+                            }
+                        } else {
+                            const int t = (pg * P + p) * 16 + lk * 4;
+                            const int4 at = *reinterpret_cast<const int4 *>(tabo + t);
+                            T *po = on + (size_t)((unsigned)o * (unsigned)(g.Ho * g.Wo)) + (f * g.Wo + e0);
+                            const int ats[4] = {at.x, at.y, at.z, at.w};
+                            if (OS == 1) {
+                                if (at.x >= 0 && at.w == at.x + 3) store_run<T, 4>(po + at.x, acc[0][p]);
+                                else {
+#pragma unroll
+                                    for (int r = 0; r < 4; ++r) if (ats[r] >= 0) stf(po + ats[r], acc[0][p][r]);
+                                }
+                                continue;
+                            }
+                            const int4 row = *reinterpret_cast<const int4 *>(tabr + t), col = *reinterpret_cast<const int4 *>(tabr + nent + t);
+                            const int rows[4] = {row.x, row.y, row.z, row.w}, cols[4] = {col.x, col.y, col.z, col.w};
+                            if constexpr (E == 2) {
+                                if (col.x >= 0 && col.w == col.x + 6 && row.w == row.x && col.w + 1 < g.Wo && (unsigned)(row.x + f) < (unsigned)g.Ho) {
+                                    typedef float v8f __attribute__((ext_vector_type(8)));
+                                    v8f v;
+#pragma unroll
+                                    for (int r = 0; r < 4; ++r) { v[2 * r] = lower(p, r); v[2 * r + 1] = upper(p, r); }
+                                    store_run<T, 8>(po + at.x, v);
+                                    continue;
+                                }
+                            }
+#pragma unroll
+                            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                                for (int e = 0; e < E; ++e)
+                                    if ((unsigned)(rows[r] + f) < (unsigned)g.Ho && (unsigned)(cols[r] + e0 + e) < (unsigned)g.Wo)
+                                        stf(po + ats[r] + e, e == 0 ? lower(p, r) : upper(p, r));
+                        }
+                    }
+                }
         }
     }
 }
 
 // ---------------------------------------------------------------------------------------------
-// Filter gradient, stage 1.  A wavefront owns one pair of 16 output channels and 16 input channels (a "pair") and every
-// WS-th step of 16 positions; a block holds NPAIR pairs and 4 / NPAIR = WS position splits, each of which is a partial.
+// Filter gradient, stage 1.  A wavefront owns one pair of 16 output channels and 16 input channels (a "pair") and every WS-th step of
+// the tile's positions; a block holds NPAIR pairs and 4 / NPAIR = WS position splits, whose sums it adds up in LDS: one partial a block.
+// A step is 32 positions in bf16, the lanes' operands read from [pixel][channel] with the transposing LDS reads (two instructions
+// instead of eight 2-byte reads and their packing for every tap), and 16 positions in fp32.
 // ---------------------------------------------------------------------------------------------
+template <typename T> constexpr int filter_step() { return sizeof(T) == 2 ? 32 : 16; }
+
+typedef __attribute__((address_space(3))) v4s lds_v4s;
+// Channel lane%16 of the block's four pixels: in every 16 lanes, lane l hands the address of channels l%4*4 .. +3 of pixel l/4.
+__device__ __forceinline__ v4s read_transposed(const bf16_t *p)
+{
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s *)p);
+}
+
 template <typename T, bool NHWC, bool FAST, int K>
-__global__ __launch_bounds__(256) void k_gconv_gemm_filter(GemmGeom g, const T *__restrict__ x, const T *__restrict__ dy, float *__restrict__ ws,
-                                                           int npair, int CLy, int pitchy, int nparts, int J, unsigned nblocks)
+__global__ __launch_bounds__(256, K > 3 ? 2 : sizeof(T) == 4 ? 3 : 4) void k_gconv_gemm_filter(GemmGeom g, StageGeom sx, StageGeom sy, const T *__restrict__ x,
+                                                                            const T *__restrict__ dy, float *__restrict__ ws, int npair, int nparts,
+                                                                            int J, unsigned nblocks)
 {
     extern __shared__ uint4 smem[];
-    constexpr int VE = 16 / (int)sizeof(T), KK = K * K;
+    constexpr int VE = 16 / (int)sizeof(T), KK = K * K, STEP = filter_step<T>();
     const unsigned lb = xcd_remap(blockIdx.x, nblocks);
     const int chb = (int)(lb % (unsigned)g.nchb), part = (int)(lb / (unsigned)g.nchb);
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int li = lane & 15, lk = lane >> 4;
-    const int WS = 4 / npair, pair = chb * npair + wv % npair, split = wv / npair;
+    const int WS = 4 / npair, mine = wv % npair, pair = chb * npair + mine, split = wv / npair;
     const int s = pair / g.nk, kc = pair - s * g.nk;                       // 16-channel output block, input chunk
     const int s0 = chb * npair / g.nk;
     const int cxa = (cin_first(s0 * 16, g) + (chb * npair - s0 * g.nk) * 16) & ~(VE - 1), cya = s0 * 16;
-    const int cx = cin_first(s * 16, g) + kc * 16 - cxa + li, cy = s * 16 - cya + li;
-    const int npos = g.TN * g.TA * g.TB, steps = (npos + 15) / 16;
+    const int cx = cin_first(s * 16, g) + kc * 16 - cxa, cy = s * 16 - cya;
+    const int npos = g.TN * g.TA * g.TB, steps = (npos + STEP - 1) / STEP, pitchy = sy.pitch;
     int *tab = reinterpret_cast<int *>(smem);                              // position -> LDS element of its input pixel
-    T *lx = reinterpret_cast<T *>(tab + steps * 16);
+    T *lx = reinterpret_cast<T *>(tab + steps * STEP);
     T *ly = lx + (size_t)g.TN * g.LH * g.LW * g.pitch;
-    const float rTA = 1.0f / (float)g.TA, rTB = 1.0f / (float)g.TB;
-    for (int p = threadIdx.x; p < steps * 16; p += 256) {
-        const int q = min(p, npos - 1), r = fdiv(q, rTB), im = fdiv(r, rTA), da = r - im * g.TA, db = q - r * g.TB;
+
+    const int ntiles = g.tn * g.ta * g.tb;
+    const unsigned imx = (unsigned)(g.CI * g.Hi * g.Wi), imy = (unsigned)(g.CO * g.Ho * g.Wo);
+    auto tile_at = [&](int tile, int &n0, int &a0, int &b0) {
+        const int row = FAST ? uniform_div(tile, g.rtb) : tile / g.tb, tn = FAST ? uniform_div(row, g.rta) : row / g.ta;
+        n0 = tn * g.TN; a0 = (row - tn * g.ta) * g.TA; b0 = (tile - row * g.tb) * g.TB;
+    };
+    constexpr int BT = NHWC ? 4 : sizeof(T) == 2 && K <= 3 ? 2 : 1;        // items of a lane in flight
+    [[maybe_unused]] Stager<T, NHWC, BT> stx(sx), sty(sy);
+    auto load_x = [&](int n0, int a0, int b0, int it0) {
+        const int nimg = min(g.TN, g.N - n0), h0 = g.IS * a0 - g.ip, w0 = g.IS * b0 - g.ip;
+        const T *p = x + (size_t)n0 * imx;
+        if constexpr (NHWC) stx.load(sx, BufView(p, (uint32_t)nimg * imx * (uint32_t)sizeof(T)), nimg, g.CI, g.Hi, g.Wi, h0, w0, cxa, it0);
+        else stx.load(sx, p, (unsigned)(g.N - n0) * imx, nimg, g.CI, g.Hi, g.Wi, h0, cxa, it0);
+    };
+    auto load_y = [&](int n0, int a0, int b0, int it0) {
+        const int nimg = min(g.TN, g.N - n0);
+        const T *p = dy + (size_t)n0 * imy;
+        if constexpr (NHWC) sty.load(sy, BufView(p, (uint32_t)nimg * imy * (uint32_t)sizeof(T)), nimg, g.CO, g.Ho, g.Wo, a0, b0, cya, it0);
+        else sty.load(sy, p, (unsigned)(g.N - n0) * imy, nimg, g.CO, g.Ho, g.Wo, a0, cya, it0);
+    };
+    if constexpr (FAST) {
+        int n0, a0, b0;
+        tile_at(part, n0, a0, b0);
+        load_x(n0, a0, b0, 0);
+        load_y(n0, a0, b0, 0);
+    }
+    for (int p = threadIdx.x; p < steps * STEP; p += 256) {
+        const int q = min(p, npos - 1), r = fdiv(q, g.rTB), im = fdiv(r, g.rTA), da = r - im * g.TA, db = q - r * g.TB;
         tab[p] = ((im * g.LH + g.IS * da) * g.LW + g.IS * db) * g.pitch;
     }
     // beside the rows of x (NCHW) and behind the positions of dy: zeros
     if (!NHWC && FAST)
-        for (int i = threadIdx.x; i < g.TN * g.LH * g.LW * g.pitch / VE; i += 256) reinterpret_cast<u4v_t *>(lx)[i] = u4v_t{0u, 0u, 0u, 0u};
-    for (int i = threadIdx.x; i < (steps * 16 - npos) * pitchy; i += 256) ly[npos * pitchy + i] = T(0);
+        for (int i = threadIdx.x; i < g.TN * g.LH * g.LW * g.pitch / 4; i += 256) reinterpret_cast<Frag<T> *>(lx)[i].v = decltype(Frag<T>::v){};
+    for (int i = threadIdx.x; i < (steps * STEP - npos) * pitchy; i += 256) ly[npos * pitchy + i] = T(0);
     // fp32: the 16 positions of a step are added up on their own before they join a sum.  A chain of n matrix instructions has a relative error of
     // about 2^-24 * sqrt(n / 6), and a 3x3 sum had up to twice the error of the kernels that these replaced (mean over random layers 1.65e-7
     // against the row walk's 1.12e-7, now 1.03e-7; 1.45e-7 against the generic kernels' 2.15e-7, now 1.02e-7), at 57x57x128 130 -> 141 us.  5x5 is
@@ -441,38 +863,92 @@ __global__ __launch_bounds__(256) void k_gconv_gemm_filter(GemmGeom g, const T *
     for (int t = 0; t < KK; ++t) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
     const bool live = s * 16 < g.CO;                                       // uniform: the last block may have pairs to spare
 
-    const int ntiles = g.tn * g.ta * g.tb;
     for (int tile = part; tile < ntiles; tile += nparts) {
-        const int tb = tile % g.tb, ta = tile / g.tb % g.ta, tn = tile / g.tb / g.ta;
-        const int n0 = tn * g.TN, a0 = ta * g.TA, b0 = tb * g.TB;
+        int n0, a0, b0;
+        tile_at(tile, n0, a0, b0);
         __syncthreads();
-        stage_pixels<T, NHWC, FAST>(x, lx, g.N, g.CI, g.Hi, g.Wi, n0, g.TN, g.IS * a0 - g.ip, g.IS * b0 - g.ip, g.LH, g.LW, cxa, g.CL, g.pitch, false);
-        stage_pixels<T, NHWC, FAST>(dy, ly, g.N, g.CO, g.Ho, g.Wo, n0, g.TN, a0, b0, g.TA, g.TB, cya, CLy, pitchy, false);
+        if constexpr (FAST) {
+            Finite<T> unused;
+            const int w0 = g.IS * b0 - g.ip;
+#pragma unroll 1
+            for (int it0 = 0;;) {
+                stx.commit(sx, lx, g.Wi, w0, it0, false, unused);
+                it0 += BT;
+                if (it0 >= sx.iters) break;
+                load_x(n0, a0, b0, it0);
+            }
+#pragma unroll 1
+            for (int it0 = 0;;) {
+                sty.commit(sy, ly, g.Wo, b0, it0, false, unused);
+                it0 += BT;
+                if (it0 >= sy.iters) break;
+                load_y(n0, a0, b0, it0);
+            }
+        } else {
+            stage_pixels<T, NHWC>(x, lx, g.N, g.CI, g.Hi, g.Wi, n0, g.TN, g.IS * a0 - g.ip, g.IS * b0 - g.ip, g.LH, g.LW, cxa, g.CL, g.pitch, false);
+            stage_pixels<T, NHWC>(dy, ly, g.N, g.CO, g.Ho, g.Wo, n0, g.TN, a0, b0, g.TA, g.TB, cya, pitchy / 16 * 16, pitchy, false);
+        }
         __syncthreads();
+        if (FAST && tile + nparts < ntiles) {                              // on its way while this one is computed
+            tile_at(tile + nparts, n0, a0, b0);
+            load_x(n0, a0, b0, 0);
+            load_y(n0, a0, b0, 0);
+        }
         if (!live) continue;
+#pragma unroll 1
         for (int st = split; st < steps; st += WS) {
-            const int q = st * 16 + lk * 4;                                // the lane's four positions
-            const int4 t4 = *reinterpret_cast<const int4 *>(tab + q);
-            const T *py = ly + q * pitchy + cy, *px[4] = {lx + t4.x + cx, lx + t4.y + cx, lx + t4.z + cx, lx + t4.w + cx};
-            Frag<T> d;
-            gather4(d, py, py + pitchy, py + 2 * pitchy, py + 3 * pitchy);
+            if constexpr (sizeof(T) == 2) {
+                const int q = st * 32 + lk * 4 + (li >> 2), c = (li & 3) * 4;
+                const T *py = ly + q * pitchy + cy + c, *px0 = lx + tab[q] + cx + c, *px1 = lx + tab[q + 16] + cx + c;
+                Frag<T> d0, d1;
+                d0.v = __builtin_bit_cast(uint2, read_transposed(py)); d1.v = __builtin_bit_cast(uint2, read_transposed(py + 16 * pitchy));
 #pragma unroll
-            for (int kh = 0; kh < K; ++kh)
+                for (int kh = 0; kh < K; ++kh)
 #pragma unroll
-                for (int kw = 0; kw < K; ++kw) {
-                    const int toff = (kh * g.LW + kw) * g.pitch;
-                    Frag<T> b;
-                    gather4(b, px[0] + toff, px[1] + toff, px[2] + toff, px[3] + toff);
-                    if constexpr (FRESH) acc[kh * K + kw] += mma16(b, d, v4f{0.f, 0.f, 0.f, 0.f});
-                    else acc[kh * K + kw] = mma16(b, d, acc[kh * K + kw]);
-                }
+                    for (int kw = 0; kw < K; ++kw) {
+                        const int toff = (kh * g.LW + kw) * g.pitch;
+                        Frag<T> b0, b1;
+                        b0.v = __builtin_bit_cast(uint2, read_transposed(px0 + toff)); b1.v = __builtin_bit_cast(uint2, read_transposed(px1 + toff));
+                        acc[kh * K + kw] = mma32(b0, b1, d0, d1, acc[kh * K + kw]);
+                    }
+            } else {
+                const int q = st * 16 + lk * 4;                            // the lane's four positions
+                const int4 t4 = *reinterpret_cast<const int4 *>(tab + q);
+                const T *py = ly + q * pitchy + cy + li, *px[4] = {lx + t4.x + cx + li, lx + t4.y + cx + li, lx + t4.z + cx + li, lx + t4.w + cx + li};
+                Frag<T> d;
+                gather4(d, py, py + pitchy, py + 2 * pitchy, py + 3 * pitchy);
+#pragma unroll
+                for (int kh = 0; kh < K; ++kh)
+#pragma unroll
+                    for (int kw = 0; kw < K; ++kw) {
+                        const int toff = (kh * g.LW + kw) * g.pitch;
+                        Frag<T> b;
+                        gather4(b, px[0] + toff, px[1] + toff, px[2] + toff, px[3] + toff);
+                        if constexpr (FRESH) acc[kh * K + kw] += mma16(b, d, v4f{0.f, 0.f, 0.f, 0.f});
+                        else acc[kh * K + kw] = mma16(b, d, acc[kh * K + kw]);
+                    }
+            }
+        }
+    }
+    // the splits' sums through LDS, taken up by split 0 in order
+    v4f *red = reinterpret_cast<v4f *>(smem) + (size_t)mine * KK * 64 + lane;
+    for (int t = 1; t < WS; ++t) {
+        __syncthreads();                                                   // the tile, or the split before, has been read
+        if (split == t) {
+#pragma unroll
+            for (int k = 0; k < KK; ++k) red[k * 64] = acc[k];
+        }
+        __syncthreads();
+        if (split == 0) {
+#pragma unroll
+            for (int k = 0; k < KK; ++k) acc[k] += red[k * 64];
         }
     }
     // lane: output s*16 + li against input channels kc*16 + lk*4 + r, so that 16 lanes write 16 consecutive outputs in NHWC
     // and a lane consecutive entries in NCHW; entries that pair different groups are dropped
     const int o = s * 16 + li, grp = fdiv(o, g.rCgo), c0 = cin_first(s * 16, g) + kc * 16 + lk * 4 - grp * g.Cgi;
-    if (!live || o >= g.CO) return;
-    float *dst = ws + (size_t)(part * WS + split) * J;
+    if (!live || split || o >= g.CO) return;
+    float *dst = ws + (size_t)part * J;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int ci = c0 + r;
@@ -508,12 +984,38 @@ void channel_span(GemmGeom &g, int ns, int VE, int *CL)
     *CL = cdivg(cl, 8) * 8;
 }
 
-constexpr size_t GEMM_LDS = 64 << 10;
+// two blocks on a compute unit; one where the filter leaves no room for two
+constexpr size_t LDS_OF_TWO = 80 << 10, LDS_OF_ONE = 160 << 10;
+// blocks of four wavefronts that the chip holds at a time where registers allow `most` on a compute unit
+int resident_blocks(size_t lds, int most)
+{
+    const size_t n = (160u << 10) / (lds ? (lds + 1279) / 1280 * 1280 : 1280);
+    return 256 * (int)(n < 1 ? 1 : n > (size_t)most ? most : n);
+}
 
-// positions of a tile: whole rows where they fit, several images of a small map
-void pick_positions(GemmGeom &g, int want, int maxb)
+// The widest tile (of positions from `from` down to `to`) that fits, as tile(positions) sets it up; half of it where that lets `most`
+// blocks onto a compute unit and it does not.  (14x14 16 channels a group 10.1 us with 256 positions, 13.0 with 128; 28x28 32 channels a
+// group, bf16 NHWC batch 64: 55 us with 256 positions and three blocks, 47 with 128 and four.)
+template <typename F> bool widest_tile(F tile, int from, int to, int most, size_t limit, const size_t *lds)
+{
+    for (int want = from; want >= to; want /= 2) {
+        tile(want);
+        if (*lds > limit) continue;
+        if (want / 2 >= 64 && resident_blocks(*lds, most) < 256 * most) {
+            tile(want / 2);
+            if (resident_blocks(*lds, most) < 256 * most) tile(want);
+        }
+        return true;
+    }
+    return false;
+}
+
+// positions of a tile: whole rows where they fit, several images of a small map; a row of a multiple of `quad` positions, so that
+// four of them have consecutive outputs
+void pick_positions(GemmGeom &g, int want, int maxb, int quad = 1)
 {
     g.TB = g.nb < maxb ? g.nb : cdivg(g.nb, cdivg(g.nb, maxb));
+    g.TB = cdivg(g.TB, quad) * quad;
     g.TA = want / g.TB;
     if (g.TA < 1) g.TA = 1;
     if (g.TA >= g.na) {
@@ -528,9 +1030,29 @@ void pick_positions(GemmGeom &g, int want, int maxb)
     g.tn = cdivg(g.N, g.TN); g.ta = cdivg(g.na, g.TA); g.tb = cdivg(g.nb, g.TB);
 }
 
-struct GemmPlan { GemmGeom g; size_t lds; int nparts; unsigned nblocks; int npair, CLy, pitchy; bool fast; };
+struct GemmPlan { GemmGeom g; StageGeom sg, sy; size_t lds; int nparts; unsigned nblocks; int npair, CLy, pitchy; bool fast; };
 
-bool gemm_plan(const GGeom &q, int layout, int dtype, int pass, GemmPlan *pl)
+// copying a tile of TN images of LH x LW pixels and CL channels (NCHW: rows of W columns) with 256 lanes
+StageGeom stage_geom(int layout, int VE, int TN, int LH, int LW, int CL, int pitch, int W)
+{
+    StageGeom s = {};
+    const bool nhwc = layout == LAYOUT_NHWC;
+    s.LH = LH; s.LW = LW; s.pitch = pitch;
+    s.imrows = TN * LH;
+    s.rows = nhwc ? s.imrows : s.imrows * (CL / 4);
+    s.nv = nhwc ? CL / VE : 1;
+    const int width = nhwc ? LW : cdivg(W, 4);                              // columns, or runs of four
+    const int most = 256 / s.nv > 0 ? 256 / s.nv : 1, passes = cdivg(width, most);
+    s.cols = cdivg(width, passes);
+    s.per = s.cols * s.nv;
+    s.RPI = 256 / s.per;
+    s.nrit = cdivg(s.rows, s.RPI);
+    s.iters = s.nrit * passes;
+    s.rper = 1.0f / (float)s.per; s.rnv = 1.0f / (float)s.nv; s.rLH = 1.0f / (float)LH; s.rimrows = 1.0f / (float)s.imrows;
+    return s;
+}
+
+bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, GemmPlan *pl)
 {
     const int esz = dtype == DT_F32 ? 4 : 2, VE = 16 / esz;
     if (q.C > 65536 || q.O > 65536 || q.s > 4 || q.K > 7) return false;
@@ -544,6 +1066,7 @@ bool gemm_plan(const GGeom &q, int layout, int dtype, int pass, GemmPlan *pl)
         g.CI = q.O; g.CO = q.C; g.Hi = q.Ho; g.Wi = q.Wo; g.Ho = q.H; g.Wo = q.W; g.Cgi = q.Og; g.Cgo = q.Cg;
         g.IS = 1; g.OS = q.s; g.ip = 0; g.op = q.p; g.lo = -((q.K + q.s - 1) / q.s - 1);
         g.a0 = g.b0 = q.p / q.s; g.na = (q.H - 1 + q.p) / q.s - g.a0 + 1; g.nb = (q.W - 1 + q.p) / q.s - g.b0 + 1;
+        if (pairs) { g.pairs = 1; g.shift = q.p & 1; g.nb = (q.W + 1) / 2; }
     }
     const int reach = pass == 1 ? 1 - g.lo : q.K;                           // input rows of one position
     const int blocks16 = cdivg(g.CO, 16);
@@ -557,20 +1080,24 @@ bool gemm_plan(const GGeom &q, int layout, int dtype, int pass, GemmPlan *pl)
             g.NS = ns;
             channel_span(g, ns, VE, &g.CL);
             g.packed = !(g.Cgo % 16 == 0 && g.Cgi % 16 == 0);
-            g.pitch = g.CL + VE;
-            for (int want = 256; want >= 16; want /= 2) {
-                pick_positions(g, want, layout == LAYOUT_NHWC ? 32 : 64);
-                g.LH = g.IS * (g.TA - 1) + reach; g.LW = g.IS * (g.TB - 1) + reach;
-                pl->lds = (size_t)ns * q.K * q.K * g.nk * 64 * 4 * esz + (size_t)g.TN * g.LH * g.LW * g.pitch * esz;
-                if (pl->lds <= GEMM_LDS) goto fits;
-            }
+            // (16-byte or, in NCHW, four-channel LDS stores)
+            g.pitch = g.CL + (layout == LAYOUT_NHWC ? VE : 4);
+            auto tile = [&](int want) {
+                pick_positions(g, want, layout == LAYOUT_NHWC ? 32 : 64, pairs ? 4 : 1);
+                g.LH = g.IS * (g.TA - 1) + reach; g.LW = g.IS * (g.TB - 1) + reach + g.shift;
+                // (positions in the tables up to a multiple of 64)
+                pl->lds = (size_t)ns * q.K * q.K * g.nk * 64 * 4 * esz + (size_t)cdivg(g.TN * g.TA * g.TB, 64) * 64 * (g.OS > 1 ? 16 : 8) + (g.OS > 1 ? 256 : 0) + 16 +
+                          ((size_t)g.TN * g.LH * g.LW * g.pitch * esz + 15) / 16 * 16;
+            };
+            if (widest_tile(tile, 256, 16, 4, LDS_OF_TWO, &pl->lds)) break;
+            if (ns == 1 && widest_tile(tile, 256, 16, 4, LDS_OF_ONE, &pl->lds)) break;
             if (ns == 1) return false;
         }
-    fits:
         g.nchb = cdivg(blocks16, g.NS);
         const long long tiles = (long long)g.tn * g.ta * g.tb;
-        // the filter is laid out once per block: up to 2048 blocks, the tiles of a channel block shared among them
-        long long parts = 2048 / g.nchb;
+        // the filter is laid out once per block and the next tile is on its way while one is computed: as many blocks as are resident,
+        // the tiles of a channel block shared among them
+        long long parts = resident_blocks(pl->lds, 4) / g.nchb;
         if (parts < 1) parts = 1;
         if (parts > tiles) parts = tiles;
         parts = (tiles + (tiles + parts - 1) / parts - 1) / ((tiles + parts - 1) / parts);
@@ -581,7 +1108,10 @@ bool gemm_plan(const GGeom &q, int layout, int dtype, int pass, GemmPlan *pl)
         int dummy;
         channel_span(g, 1, VE, &dummy);
         const int pairs = blocks16 * g.nk;
-        int npair = 4;
+        // NHWC: two pairs a block read whole 64-byte runs of channels (14x14 16 channels a group, bf16 batch 32: 14.5 us, with one 15.5); NCHW
+        // gains nothing by it and a pair alone leaves smaller tiles (56x56 8 channels a group at stride 2, bf16 batch 16: 23.6 against 28)
+        const int blocks = q.K > 3 ? 2 : 4;                                 // on a compute unit, by registers
+        int npair = q.K == 1 ? 4 : layout == LAYOUT_NHWC || g.nk > 1 ? 2 : 1;
         while (npair > pairs) npair /= 2;
         bool fits = false;
         for (; npair >= 1 && !fits; npair /= 2) {
@@ -602,34 +1132,49 @@ bool gemm_plan(const GGeom &q, int layout, int dtype, int pass, GemmPlan *pl)
             }
             if (clx >= 1 << 20) continue;
             g.CL = cdivg(clx, 8) * 8; pl->CLy = cly;
-            g.pitch = g.CL + VE; pl->pitchy = cly + VE;
+            g.pitch = g.CL + (layout == LAYOUT_NHWC ? VE : 4); pl->pitchy = cly + (layout == LAYOUT_NHWC ? VE : 4);
             // tiles of fewer than 64 positions only if nothing else fits
-            for (int want = 256; want >= (npair > 1 ? 64 : 16) && !fits; want /= 2) {
+            auto tile = [&](int want) {
                 pick_positions(g, want, layout == LAYOUT_NHWC ? 32 : 64);
                 g.LH = g.IS * (g.TA - 1) + q.K; g.LW = g.IS * (g.TB - 1) + q.K;
-                const int npos = g.TN * g.TA * g.TB, padded = (npos + 15) / 16 * 16;
+                const int npos = g.TN * g.TA * g.TB, step = esz == 2 ? 32 : 16, padded = (npos + step - 1) / step * step;
                 pl->lds = (size_t)padded * 4 + ((size_t)g.TN * g.LH * g.LW * g.pitch + (size_t)padded * pl->pitchy) * esz;
-                fits = pl->lds <= GEMM_LDS;
-            }
+                // the sums of a split, where there are several
+                const size_t sums = npair < 4 ? (size_t)npair * q.K * q.K * 1024 : 0;
+                if (pl->lds < sums) pl->lds = sums;
+            };
+            fits = widest_tile(tile, 256, npair > 1 ? 64 : 16, blocks, LDS_OF_TWO, &pl->lds);
             if (fits) break;
         }
         if (!fits) return false;
         const long long tiles = (long long)g.tn * g.ta * g.tb, J = (long long)q.O * q.Cg * q.K * q.K;
-        const int WS = 4 / npair;
-        long long parts = 2048 / g.nchb;
+        long long parts = resident_blocks(pl->lds, blocks) / g.nchb;
         if (parts > tiles) parts = tiles;
-        const long long most = (16ll << 20) / (WS * J * 4);
+        const long long most = (16ll << 20) / (J * 4);
         if (parts > most) parts = most;
         if (parts < 1) parts = 1;
-        if (WS * J * 4 > (64ll << 20)) return false;
+        if (J * 4 > (64ll << 20)) return false;
         parts = (tiles + (tiles + parts - 1) / parts - 1) / ((tiles + parts - 1) / parts);
         pl->nparts = (int)parts;
         pl->nblocks = (unsigned)(parts * g.nchb);
     }
     g.rCgi = 1.0f / (float)g.Cgi; g.rCgo = 1.0f / (float)g.Cgo; g.rKK = 1.0f / (float)(q.K * q.K); g.rnk = 1.0f / (float)g.nk;
-    pl->fast = layout == LAYOUT_NHWC ? q.C % VE == 0 && q.O % VE == 0 : g.tb == 1;
+    g.rFCg = 1.0f / (float)g.FCg; g.rTA = 1.0f / (float)g.TA; g.rTB = 1.0f / (float)g.TB;
+    g.rta = 1.0f / (float)g.ta; g.rtb = 1.0f / (float)g.tb;
+    // whole vectors of channels, or whole rows; the images of a tile below 2 GiB and 2^24 pixels, for the staging's offsets and products
+    const long long inpix = (long long)g.TN * g.Hi * g.Wi, outpix = (long long)g.TN * g.Ho * g.Wo;
+    pl->fast = (layout == LAYOUT_NHWC ? q.C % VE == 0 && q.O % VE == 0 : g.tb == 1) && inpix < 1 << 24 && outpix < 1 << 24 &&
+               inpix * g.CI * esz < 1ll << 31 && outpix * g.CO * esz < 1ll << 31 && (long long)g.tn * g.ta * g.tb < 1 << 21;
+    pl->sg = stage_geom(layout, VE, g.TN, g.LH, g.LW, g.CL, g.pitch, g.Wi);
+    if (pass == 2) pl->sy = stage_geom(layout, VE, g.TN, g.TA, g.TB, pl->CLy, pl->pitchy, g.Wo);
     pl->g = g;
     return true;
+}
+
+bool gemm_plan(const GGeom &q, int layout, int dtype, int pass, GemmPlan *pl)
+{
+    if (pass == 1 && layout == LAYOUT_NCHW && q.s == 2 && gemm_plan_as(q, layout, dtype, pass, true, pl) && pl->fast) return true;
+    return gemm_plan_as(q, layout, dtype, pass, false, pl);
 }
 
 }  // namespace
@@ -641,30 +1186,43 @@ bool gconv_gemm_supported(const GGeom &g, int layout, int dtype, int pass)
     return gemm_plan(g, layout, dtype, pass, &pl);
 }
 
-// Rounds of blocks, each as long as laying out the filter (three fragments of a lane at a time), then for every tile a fixed latency, the
-// staging (16 bytes of a lane at a time) and the matrix instructions of its wavefronts.  Fitted to 36 000 random layers: four of five between
-// 0.65 and 1.2 times the measured time.
-double gconv_gemm_us(const GGeom &q, int layout, int dtype, int pass, int *positions, int *tiles)
+// Laying out the filter (768 fragments a time), then for every tile of the block a fixed latency, the staging (4 KiB a time) and the products of
+// its longest wavefront, each with a part that grows with the blocks on a compute unit, and the classes of output pixels.  Fitted to 33 000
+// random layers: four of five between 0.87 and 1.15 times the measured time.
+double gconv_gemm_us(const GGeom &q, int layout, int dtype, int pass)
+{
+    static const float fit[2][2][2][2][7] = {                               // [pass][layout][dtype][fast]
+        {{{{1.21f, 1.70f, 0, 0, 0.191f, 0.0765f, 0.365f}, {1.27f, 1.15f, 0.14f, 0.006f, 0.159f, 0.0727f, 0.006f}},
+          {{1.70f, 1.29f, 0.311f, 0.006f, 0.432f, 0.0075f, 0.476f}, {0.93f, 1.88f, 0.15f, 0, 0.196f, 0.0137f, 0.384f}}},
+         {{{1.18f, 0.34f, 0.03f, 0.011f, 0.305f, 0.0735f, 0.241f}, {1.45f, 0.64f, 0.009f, 0, 0.164f, 0.0646f, 0.639f}},
+          {{1.64f, 0.59f, 0.434f, 0.003f, 0.401f, 0.0105f, 0.438f}, {0.73f, 0.28f, 0, 0.002f, 0.292f, 0.0109f, 0.371f}}}},
+        {{{{1.00f, 0.88f, 0, 0.021f, 0.273f, 0.0632f, 0.809f}, {1.09f, 0, 0.351f, 0.014f, 0.227f, 0.0708f, 0.679f}},
+          {{1.76f, 1.00f, 0.369f, 0.005f, 0.487f, 0.0051f, 0.831f}, {1.18f, 0.58f, 0.21f, 0.009f, 0.391f, 0.0068f, 0.814f}}},
+         {{{0.99f, 0.05f, 0.15f, 0.01f, 0.419f, 0.0678f, 0.634f}, {0.82f, 0, 0.231f, 0.005f, 0.241f, 0.0763f, 0.392f}},
+          {{1.50f, 0.40f, 0.569f, 0.006f, 0.525f, 0.0077f, 0.622f}, {0.88f, 0.41f, 0.075f, 0.006f, 0.389f, 0.0073f, 0.431f}}}}};
+    GemmPlan pl;
+    if (!gemm_plan(q, layout, dtype, pass, &pl)) return 1e30;
+    const GemmGeom &g = pl.g;
+    const float *c = fit[pass][layout == LAYOUT_NHWC][dtype != DT_F32][pl.fast];
+    const int tiles = cdivg(g.tn * g.ta * g.tb, pl.nparts), tiles16 = cdivg(g.TN * g.TA * g.TB, 16), P = tiles16 * g.NS > 4 ? 4 : 1;
+    const double resident = resident_blocks(pl.lds, 4), cu = pl.nblocks / 256.0;
+    const double rounds = pl.nblocks > resident ? pl.nblocks / resident : 1.0, beside = cu < 1 ? 1 : cu > resident / 256 ? resident / 256 : cu;
+    const double staging = (double)g.TN * g.LH * g.LW * g.CL * (dtype == DT_F32 ? 4 : 2) / 4096;
+    const double products = (double)cdivg(g.NS * cdivg(tiles16, P), 4) * P * g.K * g.K * g.nk;
+    return 5 + rounds * (c[0] * (g.NS * g.K * g.K * g.nk * 64) / 768 +
+                         tiles * (c[1] + c[2] * staging + c[3] * products + beside * (c[4] * staging + c[5] * products) + c[6] * g.OS * g.OS));
+}
+
+bool gconv_gemm_small_tiles(const GGeom &q, int layout, int dtype, int pass)
 {
     GemmPlan pl;
-    if (!gemm_plan(q, layout, dtype, pass, &pl)) { *positions = *tiles = 0; return 1e30; }
-    const GemmGeom &g = pl.g;
-    const int npos = g.TN * g.TA * g.TB, ntiles = g.tn * g.ta * g.tb, esz = dtype == DT_F32 ? 4 : 2;
-    *positions = npos;
-    *tiles = cdivg(ntiles, pl.nparts);
-    const size_t resident = pl.lds ? 163840 / pl.lds : 8;
-    const double per_round = 256.0 * (double)(resident < 1 ? 1 : resident > 8 ? 8 : resident);
-    const double rounds = pl.nblocks > per_round ? pl.nblocks / per_round : 1.0;
-    const double layout_us = (layout == LAYOUT_NCHW ? 1.4 : 0.9) * cdivg(g.NS * g.K * g.K * g.nk * 64, 768);
-    const double staging = (double)g.TN * g.LH * g.LW * g.CL * esz / 16 / 256;
-    const double products = (double)cdivg(g.NS * cdivg(cdivg(npos, 16), 4), 4) * g.K * g.K * g.nk;
-    return rounds * (layout_us + *tiles * ((pass == 0 ? 7.0 : 8.4) + 0.3 * staging + (dtype == DT_F32 ? 0.36 : 0.17) * products));
+    return gemm_plan(q, layout, dtype, pass, &pl) && pl.g.TN * pl.g.TA * pl.g.TB < 81 && (long long)pl.g.tn * pl.g.ta * pl.g.tb * pl.g.nchb > 4096;
 }
 
 int gconv_gemm_parts(const GGeom &g, int layout, int dtype)
 {
     GemmPlan pl;
-    return gemm_plan(g, layout, dtype, 2, &pl) ? pl.nparts * (4 / pl.npair) : 0;
+    return gemm_plan(g, layout, dtype, 2, &pl) ? pl.nparts : 0;
 }
 
 void gconv_gemm_filter_tiles(const GGeom &g, int layout, int dtype, FilterGradSrc *f)
@@ -673,14 +1231,24 @@ void gconv_gemm_filter_tiles(const GGeom &g, int layout, int dtype, FilterGradSr
     gemm_plan(g, layout, dtype, 2, &pl);
     f->TN = pl.g.TN; f->TA = pl.g.TA; f->TB = pl.g.TB;
     f->tn = pl.g.tn; f->ta = pl.g.ta; f->tb = pl.g.tb;
-    f->per = 0; f->nparts = pl.nparts; f->splits = 4 / pl.npair;
+    f->per = 0; f->nparts = pl.nparts;
 }
 
 template <typename T, bool NHWC>
 static hipError_t gemm_go(const GemmPlan &pl, const void *in, const void *w, void *out, hipStream_t st)
 {
-    auto kernel = pl.fast ? k_gconv_gemm<T, NHWC, true, 4> : k_gconv_gemm<T, NHWC, false, 4>;
-    hipLaunchKernelGGL(kernel, dim3(pl.nblocks), dim3(256), pl.lds, st, pl.g, (const T *)in, (const T *)w, (T *)out,
+    constexpr bool NCHW = !NHWC;
+    // four 16-position tiles at a time where that leaves every wavefront some
+    const int tiles16 = cdivg(pl.g.TN * pl.g.TA * pl.g.TB, 16) * pl.g.NS;
+    auto pick = [&](auto p) {
+        constexpr int P = decltype(p)::value;
+        return !pl.g.bwd ? (pl.fast ? k_gconv_gemm<T, NHWC, false, true, P, 1, false> : k_gconv_gemm<T, NHWC, false, false, P, 1, false>)
+               : pl.g.pairs ? k_gconv_gemm<T, NHWC, true, true, P, (NCHW ? 2 : 1), false>
+               : pl.g.OS > 1 ? (pl.fast ? k_gconv_gemm<T, NHWC, true, true, P, 1, NCHW> : k_gconv_gemm<T, NHWC, true, false, P, 1, NCHW>)
+               : pl.fast ? k_gconv_gemm<T, NHWC, true, true, P, 1, false> : k_gconv_gemm<T, NHWC, true, false, P, 1, false>;
+    };
+    auto kernel = tiles16 > 4 ? pick(std::integral_constant<int, 4>()) : pick(std::integral_constant<int, 1>());
+    hipLaunchKernelGGL(kernel, dim3(pl.nblocks), dim3(256), pl.lds, st, pl.g, pl.sg, (const T *)in, (const T *)w, (T *)out,
                        pl.nparts, pl.nblocks);
     return hipGetLastError();
 }
@@ -698,7 +1266,7 @@ static hipError_t gemm_filter_go(const GemmPlan &pl, const void *x, const void *
     const int J = pl.g.FO * pl.g.FCg * pl.g.K * pl.g.K;
     auto kernel = pl.fast ? (pl.g.K == 1 ? k_gconv_gemm_filter<T, NHWC, true, 1> : pl.g.K == 3 ? k_gconv_gemm_filter<T, NHWC, true, 3> : k_gconv_gemm_filter<T, NHWC, true, 5>)
                           : (pl.g.K == 1 ? k_gconv_gemm_filter<T, NHWC, false, 1> : pl.g.K == 3 ? k_gconv_gemm_filter<T, NHWC, false, 3> : k_gconv_gemm_filter<T, NHWC, false, 5>);
-    hipLaunchKernelGGL(kernel, dim3(pl.nblocks), dim3(256), pl.lds, st, pl.g, (const T *)x, (const T *)dy, ws, pl.npair, pl.CLy, pl.pitchy,
+    hipLaunchKernelGGL(kernel, dim3(pl.nblocks), dim3(256), pl.lds, st, pl.g, pl.sg, pl.sy, (const T *)x, (const T *)dy, ws, pl.npair,
                        pl.nparts, J, pl.nblocks);
     return hipGetLastError();
 }

@@ -104,9 +104,8 @@ __device__ __forceinline__ float partial_inside(const FilterGradSrc &f, int j, i
     const bool nhwc = f.layout == LAYOUT_NHWC;
     const int KK = f.K * f.K, tap = nhwc ? j / (f.Cg * f.O) : j % KK, kh = tap / f.K, kw = tap - kh * f.K;
     const int o = nhwc ? j % f.O : j / KK / f.Cg, ci = (nhwc ? j / f.O : j / KK) % f.Cg, c = o / f.Og * f.Cg + ci;
-    const int part = partial / f.splits, split = partial - part * f.splits;
     const int ntiles = f.tn * f.ta * f.tb, step = f.per ? 1 : f.nparts, npos = f.TN * f.TA * f.TB;
-    const int first = f.per ? part * f.per : part, last = f.per && ntiles - first > f.per ? first + f.per : ntiles;
+    const int first = f.per ? partial * f.per : partial, last = f.per && ntiles - first > f.per ? first + f.per : ntiles;
     float acc = 0.f;
     for (int tile = first; tile < last; tile += step) {
         const int tb = tile % f.tb, ta = tile / f.tb % f.ta, tn = tile / f.tb / f.ta;
@@ -119,7 +118,7 @@ __device__ __forceinline__ float partial_inside(const FilterGradSrc &f, int j, i
                 const int ow = tb * f.TB + q - r * f.TB, oh = ta * f.TA + r - im * f.TA, n = tn * f.TN + im;
                 const int ih = oh * f.s - f.p + kh, iw = ow * f.s - f.p + kw;
                 a[i] = b[i] = 0.f;
-                if (q >= npos || q / 16 % f.splits != split || n >= f.N || oh >= f.Ho || ow >= f.Wo || (unsigned)ih >= (unsigned)f.H ||
+                if (q >= npos || n >= f.N || oh >= f.Ho || ow >= f.Wo || (unsigned)ih >= (unsigned)f.H ||
                     (unsigned)iw >= (unsigned)f.W) continue;
                 const size_t px = nhwc ? ((size_t)(n * f.H + ih) * f.W + iw) * f.C + c : ((size_t)(n * f.C + c) * f.H + ih) * f.W + iw;
                 const size_t py = nhwc ? ((size_t)(n * f.Ho + oh) * f.Wo + ow) * f.O + o : ((size_t)(n * f.O + o) * f.Ho + oh) * f.Wo + ow;

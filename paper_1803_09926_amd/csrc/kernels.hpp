@@ -44,10 +44,9 @@ hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, hipStre
 struct FilterGradSrc {
     const void *x, *dy;
     int dtype, layout, N, C, H, W, K, s, p, O, Cg, Og, Ho, Wo;
-    // What a partial holds: every outputs of tiles of TN images x TA rows x TB columns (tn x ta x tb of them, columns fastest).  Partial q
-    // holds split q % splits of the tiles of part q / splits: per >= 1: per consecutive tiles, per = 0: every nparts-th tile; a split
-    // is every splits-th run of 16 positions of a tile.
-    int TN, TA, TB, tn, ta, tb, per, nparts, splits;
+    // What a partial holds: all outputs of tiles of TN images x TA rows x TB columns (tn x ta x tb of them, columns fastest).  Partial q
+    // holds, per >= 1: per consecutive tiles, per = 0: every nparts-th tile.
+    int TN, TA, TB, tn, ta, tb, per, nparts;
 };
 hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, const FilterGradSrc &src, hipStream_t st);
 

@@ -702,7 +702,7 @@ void nchwf_bwd_filter_tiles(const Geom &g, int dtype, int parts, FilterGradSrc *
     filter_tile(g, dtype, &ft);
     f->TN = 1; f->TA = ft.TR; f->TB = g.Wo;
     f->tn = g.N; f->ta = ft.nbands; f->tb = 1;
-    f->per = cdiv(g.N * ft.nbands, parts); f->nparts = parts; f->splits = 1;
+    f->per = cdiv(g.N * ft.nbands, parts); f->nparts = parts;
 }
 
 template <typename T, int K, int S, int M>

@@ -461,7 +461,7 @@ void nhwca_bwd_filter_tiles(const Geom &g, FilterGradSrc *f)
     filter_tile_any(g, &t);
     f->TN = 1; f->TA = t.TH; f->TB = t.TW;
     f->tn = g.N; f->ta = t.nstrips; f->tb = t.ncols;
-    f->per = t.per; f->nparts = t.parts; f->splits = 1;
+    f->per = t.per; f->nparts = t.parts;
 }
 
 template <typename T, int V, int K, int S, int M>

@@ -1,0 +1,55 @@
+"""GPU parity of the 16x16 group kernels at the edges of how they copy and lay out: the filter in whole vectors (groups that straddle a
+vector, filters smaller than one, a last block with half its outputs), tiles of several rounds of loads, pairs of output columns of the
+stride-2 input gradient (odd and even padding and width), filters that take more than 64 KiB of LDS, tiles of few positions, and position
+splits added up in the block.  Against the CPU group oracle, element by element; a sum has up to 64 * 25 products (fp32: about
+sqrt(1600) * 2^-24 = 2.4e-6 of the rms term sum, inside 1e-5)."""
+import pytest
+
+import paper_1803_09926_amd as dw
+from oracle import gconv as og
+from paper_1803_09926_amd import workloads as wl
+
+import gpu_util as gu
+from test_gpu_gconv import run_gpu
+from test_gpu_gconv_gemm import matrix_instructions        # noqa: F401  (these kernels wherever they take the shape)
+
+pytestmark = pytest.mark.gpu
+
+# name, N, C, O, groups, H, W, K, stride, pad
+CASES = [
+    ("pairs_even_pad", 2, 32, 32, 2, 20, 24, 3, 2, 0),             # no shift, whole rows of quads
+    ("pairs_odd_pad", 2, 32, 32, 2, 21, 32, 3, 2, 1),              # shift, aligned rows
+    ("pairs_odd_width", 2, 24, 24, 3, 13, 31, 5, 2, 2),            # the last pair has one column
+    ("pairs_pad3", 2, 16, 16, 1, 18, 22, 5, 2, 3),
+    ("half_block", 3, 24, 24, 1, 16, 15, 3, 1, 1),                 # 24 outputs: the second block has eight
+    ("straddle", 2, 48, 48, 8, 16, 13, 3, 1, 1),                   # groups of 6: vectors and blocks span groups
+    ("og4_cg12", 2, 36, 12, 3, 14, 17, 3, 1, 1),
+    ("og12_cg4", 2, 16, 48, 4, 14, 17, 3, 1, 1),
+    ("cg20", 1, 40, 40, 2, 12, 13, 3, 1, 1),                       # an output block of 4 and one of 16 in a group
+    ("k2", 2, 32, 32, 2, 12, 13, 2, 1, 0),                         # four taps: fewer than a bf16 vector has entries
+    ("lds_over_64k", 2, 64, 64, 1, 11, 13, 5, 1, 2),
+    ("lds_over_64k_s2", 2, 64, 64, 1, 19, 22, 5, 2, 2),
+    ("few_positions", 2, 512, 512, 32, 3, 4, 3, 1, 1),             # fewer 16-position tiles than wavefronts
+    ("one_pair", 5, 16, 16, 1, 29, 27, 3, 1, 1),                   # filter gradient: four position splits of one pair
+    ("wide", 1, 16, 16, 1, 9, 300, 3, 1, 1),                       # more columns than lanes of a row
+    ("tail", 1, 20, 20, 5, 37, 35, 3, 1, 1),                       # a run of four passes the tensor's end
+]
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("layout", [wl.NCHW, wl.NHWC], ids=["nchw", "nhwc"])
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_vectors_pairs_and_large_filters(case, layout, dtype):
+    name, N, C, O, G, H, W, K, s, p = case
+    d = dw.group_desc(N, C, H, W, K, s, p, G, O, layout, dtype)
+    names = [dw.gconv_variant_name(d, i) for i in range(3)]
+    print("case", name, layout, dtype, names, flush=True)
+    if "rowwalk" not in names[0]:
+        assert names[0] == "group_mfma16" and names[1] == "group_mfma16_bwd_data"
+    x, w, dy = wl.make_group_inputs(N, C, O, G, H, W, K, s, p, layout, dtype, seed=91)
+    y, dx, dwt = run_gpu(case, layout, dtype, x, w, dy)
+    kw = dict(K=K, stride=s, pad=p, groups=G, O=O, layout=layout, nthreads=8)
+    tol = gu.TOL_F32 if dtype == wl.F32 else gu.TOL_BF16
+    gu.assert_close(gu.to_host(y), og.fwd(x, w, **kw), tol, "fwd " + name)
+    gu.assert_close(gu.to_host(dx), og.bwd_data(dy, w, x_shape=x.shape, **kw), tol, "bwd_data " + name)
+    gu.assert_close(gu.to_host(dwt), og.bwd_filter(x, dy, **kw), gu.TOL_F32_FILTER, "bwd_filter " + name)
