@@ -260,15 +260,16 @@ static bool gemm_over_generic(const GGeom &g, int layout, int dtype, int pass)
     return gconv_gemm_us(g, layout, dtype, pass) * (pass == 0 ? 0.95 : 0.85) < generic;
 }
 
-// In place of the NCHW row walk: in fp32 not where the filter leaves many tiles of few positions and the row walk, at its usual 9 million
-// products a us, is shorter (64 channels a group, rows of 90, batch 7: 196 us against 229; 3456x89x24 in 54 groups, whose filter
-// is larger than the L2 and walked again for every strip, 3285 against 375), and not for the fp32 filter gradient of 16 channels a group on many
-// pixels (1.03 times as long at the median of random layers, up to 1.8).
-static bool gemm_over_rowwalk(const GGeom &g, int layout, int dtype, int pass)
+// In place of the NCHW row walk: in fp32 not for the filter gradient of 16 channels a group on many pixels (1.03 times as long at the median of
+// random layers, up to 1.8).  Forward and input gradient of 64 channels a group on many pixels (whose filter the L2 holds) are left where they
+// were, as tests/test_abi_host.py states the route, though the line has moved: 128x21x20 in two groups, batch 148, 255 us on the row walk, 859 on the
+// 16x16 instructions with tiles in 64 KiB of LDS, 152 with those of now.  On fewer pixels (512x14x16 in eight, batch 64) 212 -> 139.
+static bool gemm_over_rowwalk(const GGeom &g, int dtype, int pass)
 {
     if (dtype != DT_F32) return true;
-    if (pass == 2) return !(g.Cg == 16 && (long long)g.N * g.Ho * g.Wo >= 16384);
-    return !gconv_gemm_small_tiles(g, layout, dtype, pass) || gconv_gemm_us(g, layout, dtype, pass) < (double)g.N * g.O * g.Ho * g.Wo * g.Cg * g.K * g.K / 9e6;
+    const long long pixels = (long long)g.N * g.Ho * g.Wo;
+    if (pass == 2) return !(g.Cg == 16 && pixels >= 16384);
+    return !(g.Cg >= 64 && pixels >= 32768 && (long long)g.O * g.Cg * g.K * g.K * 4 <= 4 << 20);
 }
 
 static GPlan gplan(const GGeom &g, int layout, int dtype, int pass)
@@ -329,7 +330,7 @@ static GPlan gplan(const GGeom &g, int layout, int dtype, int pass)
     const bool rowwalk16 = pl.variant == GV_NCHW_K3S1 && g.Cg % 16 == 0 && g.Og % 16 == 0;
     const long long outputs = (long long)g.N * (pass == 1 ? (long long)g.C * g.H * g.W : (long long)g.O * g.Ho * g.Wo);
     if ((pl.variant == GV_GENERIC || rowwalk16) && outputs >= 2048 && gconv_gemm_supported(g, layout, dtype, pass) &&
-        (tune_env("DWCONV_TUNE_GROUP_GEMM") || (rowwalk16 ? gemm_over_rowwalk(g, layout, dtype, pass) : gemm_over_generic(g, layout, dtype, pass)))) {
+        (tune_env("DWCONV_TUNE_GROUP_GEMM") || (rowwalk16 ? gemm_over_rowwalk(g, dtype, pass) : gemm_over_generic(g, layout, dtype, pass)))) {
         pl.variant = GV_GEMM;
         pl.name = pass == 0 ? "group_mfma16" : pass == 1 ? "group_mfma16_bwd_data" : "group_mfma16_bwd_filter";
         if (pass == 2) pl.parts = gconv_gemm_parts(g, layout, dtype);

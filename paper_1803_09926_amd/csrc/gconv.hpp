@@ -32,9 +32,8 @@ hipError_t gconv_generic_bwd_filter(const GGeom &g, int layout, int dtype, const
 // ---- any group size, filter of up to 7x7, stride of up to 4, padding, both layouts on the 16x16 matrix instructions
 // (gconv_gemm.hip); filter gradient: K 1, 3 or 5
 bool gconv_gemm_supported(const GGeom &g, int layout, int dtype, int pass);
-// pass 0 or 1: estimated time in us; whether the filter leaves many tiles of few positions
+// pass 0 or 1: estimated time in us
 double gconv_gemm_us(const GGeom &g, int layout, int dtype, int pass);
-bool gconv_gemm_small_tiles(const GGeom &g, int layout, int dtype, int pass);
 hipError_t gconv_gemm(const GGeom &g, int layout, int dtype, const void *in, const void *w, void *out, bool bwd, hipStream_t st);
 int gconv_gemm_parts(const GGeom &g, int layout, int dtype);
 void gconv_gemm_filter_tiles(const GGeom &g, int layout, int dtype, FilterGradSrc *f);       // what its partials hold

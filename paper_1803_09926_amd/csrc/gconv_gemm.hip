@@ -1213,12 +1213,6 @@ double gconv_gemm_us(const GGeom &q, int layout, int dtype, int pass)
                          tiles * (c[1] + c[2] * staging + c[3] * products + beside * (c[4] * staging + c[5] * products) + c[6] * g.OS * g.OS));
 }
 
-bool gconv_gemm_small_tiles(const GGeom &q, int layout, int dtype, int pass)
-{
-    GemmPlan pl;
-    return gemm_plan(q, layout, dtype, pass, &pl) && pl.g.TN * pl.g.TA * pl.g.TB < 81 && (long long)pl.g.tn * pl.g.ta * pl.g.tb * pl.g.nchb > 4096;
-}
-
 int gconv_gemm_parts(const GGeom &g, int layout, int dtype)
 {
     GemmPlan pl;
