@@ -48,8 +48,10 @@ __device__ __forceinline__ Lane lane_of(unsigned nblocks, int ncols, int nstrips
 // item the entries run over (row, vector column) like the addresses do.  Two LDS buffers alternate,
 // so one barrier per RS rows is enough.  Every lane of the block must take part (no early exit), the
 // rows per strip must be a multiple of RS, and all lanes must produce rows in lockstep.
+// M = 2: an item has two consecutive output planes, and the two LDS buffers hold a row group of each
+// (two barriers for both groups; buffers for two more would halve the blocks on a compute unit).
 // ---------------------------------------------------------------------------------------------
-template <typename T, int RS>
+template <typename T, int RS, int M = 1>
 struct LineWriter {
     int idx[RS], rows[RS];
     T *ptr[RS];
@@ -74,7 +76,7 @@ struct LineWriter {
             const int o0 = stl * TH, o1 = min(H, o0 + TH);
             idx[k] = srow * 256 + ll;
             rows[k] = pl < nplanes ? o1 - (o0 + srow) : 0;     // rows from this entry's first one to the strip's end
-            ptr[k] = out + ((size_t)min(pl, nplanes - 1) * H + (o0 + srow)) * W + c4l * VE;
+            ptr[k] = out + ((size_t)min(pl, nplanes - 1) * M * H + (o0 + srow)) * W + c4l * VE;
         }
         slot = 0; buf = 0; done = 0;
     }
@@ -92,6 +94,25 @@ struct LineWriter {
                     __builtin_nontemporal_store(v, reinterpret_cast<u4v_t *>(ptr[k] + (size_t)done * W));
                 }
             slot = 0; buf ^= 1; done += RS;
+        }
+    }
+    // the same for the next row of both planes, `plane` elements apart
+    __device__ __forceinline__ void put2(u4v_t (&stage)[2][RS * 256], const u4v_t &p0, const u4v_t &p1, int W, int plane)
+    {
+        stage[0][slot * 256 + threadIdx.x] = p0;
+        stage[1][slot * 256 + threadIdx.x] = p1;
+        if (++slot == RS) {
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int k = 0; k < RS; ++k)
+                    if (done < rows[k]) {
+                        const u4v_t v = stage[q][idx[k]];
+                        __builtin_nontemporal_store(v, reinterpret_cast<u4v_t *>(ptr[k] + (size_t)q * plane + (size_t)done * W));
+                    }
+            __syncthreads();
+            slot = 0; done += RS;
         }
     }
 };
@@ -121,7 +142,7 @@ __device__ __forceinline__ u4v_t pack16(const float (&r)[16 / sizeof(T)])
 // RS > 0: whole-line write-out of RS-row groups (needs 16-byte vectors, TH % RS == 0, H % RS == 0);
 // RS == 0: each lane stores its vector directly (streamed if nt).
 // ---------------------------------------------------------------------------------------------
-template <typename T, int V, int K, int PF, bool FLIP, int RS>
+template <typename T, int V, int K, int PF, bool FLIP, int RS, int M = 1>
 __global__ __launch_bounds__(256) void k_nchwd_s1(Geom g, const T *__restrict__ x, const T *__restrict__ w,
                                                   T *__restrict__ y, int TH, int nstrips, unsigned nblocks, int nt)
 {
@@ -131,7 +152,7 @@ __global__ __launch_bounds__(256) void k_nchwd_s1(Geom g, const T *__restrict__ 
     constexpr int R = PF + 1;
     __shared__ u4v_t stage[2][RS > 0 ? RS * 256 : 1];
     const int W4 = g.W / V;
-    const int nplanes = g.N * g.O;
+    const int nch = M == 2 ? g.C : g.O, nplanes = g.N * nch;
     const unsigned lb = xcd_remap(blockIdx.x, nblocks);
     const unsigned f = lb * 256u + threadIdx.x;
     const unsigned ps = f / (unsigned)W4;
@@ -140,21 +161,23 @@ __global__ __launch_bounds__(256) void k_nchwd_s1(Geom g, const T *__restrict__ 
     const int strip = ps - plane * nstrips;
     const bool valid = plane < nplanes;
     if (!valid) plane = nplanes - 1;      // lanes past the end compute on the last plane; nothing of theirs is stored
-    const int n = plane / g.O, o = plane - n * g.O;
-    const int plane_in = n * g.C + o / g.m;
+    const int n = plane / nch, o = (plane - n * nch) * M;
+    const int plane_in = M == 2 ? plane : n * g.C + o / g.m;
 
-    float wr[K][K];
+    float wr[M][K][K];
 #pragma unroll
-    for (int kh = 0; kh < K; ++kh)
+    for (int q = 0; q < M; ++q)
 #pragma unroll
-        for (int kw = 0; kw < K; ++kw) wr[kh][kw] = ldf(w + (o * K + (FLIP ? K - 1 - kh : kh)) * K + (FLIP ? K - 1 - kw : kw));
+        for (int kh = 0; kh < K; ++kh)
+#pragma unroll
+            for (int kw = 0; kw < K; ++kw) wr[q][kh][kw] = ldf(w + ((o + q) * K + (FLIP ? K - 1 - kh : kh)) * K + (FLIP ? K - 1 - kw : kw));
 
     const bool has_left = c4 > 0, has_right = c4 < W4 - 1;
     const T *xin = x + (size_t)plane_in * g.H * g.W + c4 * V;
-    T *yout = y + (size_t)plane * g.H * g.W + c4 * V;
+    T *yout = y + (size_t)plane * M * g.H * g.W + c4 * V;
     const int oh0 = strip * TH, oh1 = min(g.H, oh0 + TH);
 
-    LineWriter<T, (RS > 0 ? RS : 1)> lw;
+    LineWriter<T, (RS > 0 ? RS : 1), M> lw;
     if constexpr (RS > 0) lw.init(lb, W4, V, nstrips, nplanes, TH, g.H, g.W, y);
 
     int loff[P > 0 ? P : 1], roff[P > 0 ? P : 1];
@@ -172,11 +195,13 @@ __global__ __launch_bounds__(256) void k_nchwd_s1(Geom g, const T *__restrict__ 
         for (int v = 0; v < V; ++v) dst[P + v] = mid[v];
     };
 
-    float acc[K - 1 > 0 ? K - 1 : 1][V];
+    float acc[M][K - 1 > 0 ? K - 1 : 1][V];
 #pragma unroll
-    for (int j = 0; j < K - 1; ++j)
+    for (int q = 0; q < M; ++q)
 #pragma unroll
-        for (int v = 0; v < V; ++v) acc[j][v] = 0.f;
+        for (int j = 0; j < K - 1; ++j)
+#pragma unroll
+            for (int v = 0; v < V; ++v) acc[q][j][v] = 0.f;
 
     auto consume = [&](int idx, int r, const float (&raw)[NW]) {
         const bool rowok = r >= 0 && r < g.H;
@@ -186,26 +211,33 @@ __global__ __launch_bounds__(256) void k_nchwd_s1(Geom g, const T *__restrict__ 
             const bool ok = rowok && (i < P ? has_left : (i >= P + V ? has_right : true));
             cur[i] = ok ? raw[i] : 0.f;
         }
-        float out[V];
+        float out[M][V];
 #pragma unroll
-        for (int v = 0; v < V; ++v) {
-            float s = (K > 1) ? acc[0][v] : 0.f;
-#pragma unroll
-            for (int kw = 0; kw < K; ++kw) s = fmaf(wr[K - 1][kw], cur[v + kw], s);
-            out[v] = s;
-        }
-#pragma unroll
-        for (int jj = 0; jj < K - 1; ++jj)
+        for (int q = 0; q < M; ++q) {
 #pragma unroll
             for (int v = 0; v < V; ++v) {
-                float s = (jj + 1 < K - 1) ? acc[jj + 1][v] : 0.f;
+                float s = (K > 1) ? acc[q][0][v] : 0.f;
 #pragma unroll
-                for (int kw = 0; kw < K; ++kw) s = fmaf(wr[K - 2 - jj][kw], cur[v + kw], s);
-                acc[jj][v] = s;
+                for (int kw = 0; kw < K; ++kw) s = fmaf(wr[q][K - 1][kw], cur[v + kw], s);
+                out[q][v] = s;
             }
+#pragma unroll
+            for (int jj = 0; jj < K - 1; ++jj)
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    float s = (jj + 1 < K - 1) ? acc[q][jj + 1][v] : 0.f;
+#pragma unroll
+                    for (int kw = 0; kw < K; ++kw) s = fmaf(wr[q][K - 2 - jj][kw], cur[v + kw], s);
+                    acc[q][jj][v] = s;
+                }
+        }
         if (idx >= 2 * P) {        // the row just finished is output row oh0 + idx - 2P
-            if constexpr (RS > 0) lw.put(stage, pack16<T>(out), g.W);
-            else if (valid && r - P < oh1) store_vec<T, V>(yout + (size_t)(r - P) * g.W, out, nt != 0);
+            if constexpr (RS > 0 && M == 2) lw.put2(stage, pack16<T>(out[0]), pack16<T>(out[M - 1]), g.W, g.H * g.W);
+            else if constexpr (RS > 0) lw.put(stage, pack16<T>(out[0]), g.W);
+            else if (valid && r - P < oh1) {
+#pragma unroll
+                for (int q = 0; q < M; ++q) store_vec<T, V>(yout + (size_t)q * g.H * g.W + (size_t)(r - P) * g.W, out[q], nt != 0);
+            }
         }
     };
 
@@ -237,7 +269,7 @@ __global__ __launch_bounds__(256) void k_nchwd_s1(Geom g, const T *__restrict__ 
 // Accumulation is fp32 as in the other kernels; products of bf16 values are exact in fp32.
 // RS > 0: whole-line write-out of RS-row groups (LineWriter); RS == 0: direct 16-byte stores.
 // ---------------------------------------------------------------------------------------------
-template <int V, int K, int PF, bool FLIP, int RS>
+template <int V, int K, int PF, bool FLIP, int RS, int M = 1>
 __global__ __launch_bounds__(256) void k_nchwd_s1_bf16x8(Geom g, const bf16_t *__restrict__ x, const bf16_t *__restrict__ w,
                                                          bf16_t *__restrict__ y, int TH, int nstrips, unsigned nblocks)
 {
@@ -248,7 +280,7 @@ __global__ __launch_bounds__(256) void k_nchwd_s1_bf16x8(Geom g, const bf16_t *_
     static_assert(K == 3 || K == 5, "left and right neighbours must fit one word each");
     __shared__ u4v_t stage[2][(RS > 0 ? RS : 1) * 256];
     const int W4 = g.W / V;
-    const int nplanes = g.N * g.O;
+    const int nch = M == 2 ? g.C : g.O, nplanes = g.N * nch;
     const unsigned lb = xcd_remap(blockIdx.x, nblocks);
     const unsigned f = lb * 256u + threadIdx.x;
     const unsigned ps = f / (unsigned)W4;
@@ -257,16 +289,17 @@ __global__ __launch_bounds__(256) void k_nchwd_s1_bf16x8(Geom g, const bf16_t *_
     const int strip = ps - plane * nstrips;
     const bool valid = plane < nplanes;
     if (!valid) plane = nplanes - 1;      // lanes past the end compute on the last plane; nothing of theirs is stored
-    const int n = plane / g.O, o = plane - n * g.O;
-    const int plane_in = n * g.C + o / g.m;
+    const int n = plane / nch, o = (plane - n * nch) * M;
+    const int plane_in = M == 2 ? plane : n * g.C + o / g.m;
 
     // filter rows packed for both starting halves: wp[kh][q][t], q = (j + P) & 1
-    uint32_t wp[K][2][NT];
+    uint32_t wp[M][K][2][NT];
 #pragma unroll
-    for (int kh = 0; kh < K; ++kh) {
+    for (int mkh = 0; mkh < M * K; ++mkh) {
+        const int m = mkh / K, kh = mkh % K;
         uint32_t wv[K];
 #pragma unroll
-        for (int kw = 0; kw < K; ++kw) wv[kw] = w[(o * K + (FLIP ? K - 1 - kh : kh)) * K + (FLIP ? K - 1 - kw : kw)];
+        for (int kw = 0; kw < K; ++kw) wv[kw] = w[((o + m) * K + (FLIP ? K - 1 - kh : kh)) * K + (FLIP ? K - 1 - kw : kw)];
 #pragma unroll
         for (int q = 0; q < 2; ++q)
 #pragma unroll
@@ -274,17 +307,17 @@ __global__ __launch_bounds__(256) void k_nchwd_s1_bf16x8(Geom g, const bf16_t *_
                 const int k0 = 2 * t - q, k1 = 2 * t + 1 - q;       // taps in the low and the high half
                 const uint32_t lo = (k0 >= 0 && k0 < K) ? wv[k0 < 0 ? 0 : (k0 < K ? k0 : 0)] : 0u;
                 const uint32_t hi = (k1 >= 0 && k1 < K) ? wv[k1 < 0 ? 0 : (k1 < K ? k1 : 0)] : 0u;
-                wp[kh][q][t] = lo | (hi << 16);
+                wp[m][kh][q][t] = lo | (hi << 16);
             }
     }
 
     const bool has_left = c4 > 0, has_right = c4 < W4 - 1;
     const bf16_t *xin = x + (size_t)plane_in * g.H * g.W + c4 * V;
-    bf16_t *yout = y + (size_t)plane * g.H * g.W + c4 * V;
+    bf16_t *yout = y + (size_t)plane * M * g.H * g.W + c4 * V;
     const int oh0 = strip * TH, oh1 = min(g.H, oh0 + TH);
     const int loff = has_left ? -2 : 0, roff = has_right ? V : V - 2;     // clamped into the lane's own words
 
-    LineWriter<bf16_t, (RS > 0 ? RS : 1)> lw;
+    LineWriter<bf16_t, (RS > 0 ? RS : 1), M> lw;
     if constexpr (RS > 0) lw.init(lb, W4, V, nstrips, nplanes, TH, g.H, g.W, y);
 
     uint32_t ring[R][NP];
@@ -301,20 +334,22 @@ __global__ __launch_bounds__(256) void k_nchwd_s1_bf16x8(Geom g, const bf16_t *_
         dst[NP - 1] = *reinterpret_cast<const uint32_t *>(rp + roff);
     };
 
-    float acc[K - 1][V];
+    float acc[M][K - 1][V];
 #pragma unroll
-    for (int j = 0; j < K - 1; ++j)
+    for (int m = 0; m < M; ++m)
 #pragma unroll
-        for (int v = 0; v < V; ++v) acc[j][v] = 0.f;
+        for (int j = 0; j < K - 1; ++j)
+#pragma unroll
+            for (int v = 0; v < V; ++v) acc[m][j][v] = 0.f;
 
     // contribution of input row `cur` through filter row kh to the lane's 8 outputs, added to `s`
-    auto tap_row = [&](int kh, const uint32_t (&cur)[NP], float (&s)[V]) {
+    auto tap_row = [&](int m, int kh, const uint32_t (&cur)[NP], float (&s)[V]) {
 #pragma unroll
         for (int j = 0; j < V; ++j) {
             const int q = (j + P) & 1, i0 = (j - P + 2) >> 1;
 #pragma unroll
             for (int t = 0; t < NT; ++t)
-                if (2 * t - q < K && 2 * t + 1 - q >= 0) s[j] = dot2_bf16(cur[i0 + t], wp[kh][q][t], s[j]);
+                if (2 * t - q < K && 2 * t + 1 - q >= 0) s[j] = dot2_bf16(cur[i0 + t], wp[m][kh][q][t], s[j]);
         }
     };
 
@@ -326,24 +361,31 @@ __global__ __launch_bounds__(256) void k_nchwd_s1_bf16x8(Geom g, const bf16_t *_
             const bool ok = rowok && (i == 0 ? has_left : (i == NP - 1 ? has_right : true));
             cur[i] = ok ? raw[i] : 0u;
         }
-        float out[V];
+        float out[M][V];
 #pragma unroll
-        for (int v = 0; v < V; ++v) out[v] = acc[0][v];
-        tap_row(K - 1, cur, out);
+        for (int m = 0; m < M; ++m) {
 #pragma unroll
-        for (int jj = 0; jj < K - 1; ++jj) {
-            float s[V];
+            for (int v = 0; v < V; ++v) out[m][v] = acc[m][0][v];
+            tap_row(m, K - 1, cur, out[m]);
 #pragma unroll
-            for (int v = 0; v < V; ++v) s[v] = (jj + 1 < K - 1) ? acc[jj + 1][v] : 0.f;
-            tap_row(K - 2 - jj, cur, s);
+            for (int jj = 0; jj < K - 1; ++jj) {
+                float s[V];
 #pragma unroll
-            for (int v = 0; v < V; ++v) acc[jj][v] = s[v];
+                for (int v = 0; v < V; ++v) s[v] = (jj + 1 < K - 1) ? acc[m][jj + 1][v] : 0.f;
+                tap_row(m, K - 2 - jj, cur, s);
+#pragma unroll
+                for (int v = 0; v < V; ++v) acc[m][jj][v] = s[v];
+            }
         }
         if (idx >= 2 * P) {        // the row just finished is output row oh0 + idx - 2P
-            if constexpr (RS > 0 && V == 8) lw.put(stage, pack16<bf16_t>(out), g.W);
+            if constexpr (RS > 0 && V == 8 && M == 2) lw.put2(stage, pack16<bf16_t>(out[0]), pack16<bf16_t>(out[M - 1]), g.W, g.H * g.W);
+            else if constexpr (RS > 0 && V == 8) lw.put(stage, pack16<bf16_t>(out[0]), g.W);
             else {
                 const int oh = r - P;
-                if (valid && oh < oh1) Vec<bf16_t, V>::store(yout + (size_t)oh * g.W, out);
+                if (valid && oh < oh1) {
+#pragma unroll
+                    for (int m = 0; m < M; ++m) Vec<bf16_t, V>::store(yout + (size_t)m * g.H * g.W + (size_t)oh * g.W, out[m]);
+                }
             }
         }
     };
@@ -559,15 +601,16 @@ __global__ __launch_bounds__(256) void k_nchwd_bwd_data_k3s2(Geom g, const T *__
 // end all 256 lanes hold sums for the same channel: wavefront butterfly, LDS across the four
 // wavefronts, one partial per block at ws[part][o][kh][kw].  Fixed order throughout.
 // ---------------------------------------------------------------------------------------------
-template <typename T, int V, int S>
+template <typename T, int V, int S, int M = 1>
 __global__ __launch_bounds__(256) void k_nchwd_bwd_filter_k3(Geom g, const T *__restrict__ x, const T *__restrict__ dy,
                                                              float *__restrict__ ws, int TH, int nstrips, int nsg,
                                                              int rounds)
 {
-    __shared__ float red[4][9];
+    static_assert(M == 1 || S == 1, "both outputs of a channel: stride 1 only");
+    __shared__ float red[4][M * 9];
     constexpr int NW = (S == 1) ? V + 2 : 2 * V;       // x columns per lane and row; stride 2: the 2V columns under the lane's dy columns
     constexpr int ND = (S == 1) ? V : V + 1;            // dy columns per lane and row; stride 2: and the one to their right
-    const int o = blockIdx.y, part = blockIdx.x;
+    const int o = blockIdx.y * M, part = blockIdx.x;
     const int ncols = g.Wo / V;                         // vectors per dy row
     // lanes are laid flat over (item, vector column): nsg = 256 / ncols items per round, no padding
     const int sg = threadIdx.x / ncols, c4 = threadIdx.x - sg * ncols;
@@ -575,11 +618,13 @@ __global__ __launch_bounds__(256) void k_nchwd_bwd_filter_k3(Geom g, const T *__
     const int c_in = o / g.m;
     const bool has_left = c4 > 0, has_right = c4 < ncols - 1;
 
-    float acc[3][3];
+    float acc[M][3][3];
 #pragma unroll
-    for (int kh = 0; kh < 3; ++kh)
+    for (int q = 0; q < M; ++q)
 #pragma unroll
-        for (int kw = 0; kw < 3; ++kw) acc[kh][kw] = 0.f;
+        for (int kh = 0; kh < 3; ++kh)
+#pragma unroll
+            for (int kw = 0; kw < 3; ++kw) acc[q][kh][kw] = 0.f;
 
     if (sg < nsg) {
         for (int rd = 0; rd < rounds; ++rd) {
@@ -618,16 +663,19 @@ __global__ __launch_bounds__(256) void k_nchwd_bwd_filter_k3(Geom g, const T *__
                     row[i] = ok ? row[i] : 0.f;
                 }
             };
-            auto load_dy = [&](int oh, float (&dst)[ND]) {
-                const T *rp = dyin + (size_t)min(oh, g.Ho - 1) * g.Wo;
-                float m[V];
-                Vec<T, V>::load(rp, m);
+            auto load_dy = [&](int oh, float (&dst)[M][ND]) {
 #pragma unroll
-                for (int v = 0; v < V; ++v) dst[v] = m[v];
-                if constexpr (S == 2) dst[V] = ldf(rp + roff);
+                for (int q = 0; q < M; ++q) {
+                    const T *rp = dyin + (size_t)q * g.Ho * g.Wo + (size_t)min(oh, g.Ho - 1) * g.Wo;
+                    float m[V];
+                    Vec<T, V>::load(rp, m);
+#pragma unroll
+                    for (int v = 0; v < V; ++v) dst[q][v] = m[v];
+                    if constexpr (S == 2) dst[q][V] = ldf(rp + roff);
+                }
             };
             // x rows oh*S-1, oh*S, oh*S+1 meet dy row oh at tap rows 0, 1, 2.
-            float xa[NW], xb[NW], xc[3][NW], d[3][ND], xs[2][NW];
+            float xa[NW], xb[NW], xc[3][NW], d[3][M][ND], xs[2][NW];
             load_x(oh0 * S - 1, xa);
             mask_x(oh0 * S - 1, xa);
             if constexpr (S == 1) {
@@ -640,15 +688,17 @@ __global__ __launch_bounds__(256) void k_nchwd_bwd_filter_k3(Geom g, const T *__
                     mask_x(oh + 1, xc[j]);
                     const bool dok = oh < oh1;
 #pragma unroll
-                    for (int v = 0; v < V; ++v) {
-                        const float dv = dok ? d[j][v] : 0.f;
+                    for (int q = 0; q < M; ++q)
 #pragma unroll
-                        for (int kw = 0; kw < 3; ++kw) {
-                            acc[0][kw] = fmaf(dv, xa[v + kw], acc[0][kw]);
-                            acc[1][kw] = fmaf(dv, xb[v + kw], acc[1][kw]);
-                            acc[2][kw] = fmaf(dv, xc[j][v + kw], acc[2][kw]);
+                        for (int v = 0; v < V; ++v) {
+                            const float dv = dok ? d[j][q][v] : 0.f;
+#pragma unroll
+                            for (int kw = 0; kw < 3; ++kw) {
+                                acc[q][0][kw] = fmaf(dv, xa[v + kw], acc[q][0][kw]);
+                                acc[q][1][kw] = fmaf(dv, xb[v + kw], acc[q][1][kw]);
+                                acc[q][2][kw] = fmaf(dv, xc[j][v + kw], acc[q][2][kw]);
+                            }
                         }
-                    }
 #pragma unroll
                     for (int i = 0; i < NW; ++i) { xa[i] = xb[i]; xb[i] = xc[j][i]; }
                 };
@@ -674,19 +724,19 @@ __global__ __launch_bounds__(256) void k_nchwd_bwd_filter_k3(Geom g, const T *__
                     const bool dok = oh < oh1;
                     float D[V + 1];
 #pragma unroll
-                    for (int v = 0; v < V; ++v) D[v] = dok ? d[j][v] : 0.f;
-                    D[V] = (dok && has_right) ? d[j][V] : 0.f;
+                    for (int v = 0; v < V; ++v) D[v] = dok ? d[j][0][v] : 0.f;
+                    D[V] = (dok && has_right) ? d[j][0][V] : 0.f;
 #pragma unroll
                     for (int v = 0; v < V; ++v) {
-                        acc[0][1] = fmaf(D[v], xa[2 * v], acc[0][1]);
-                        acc[1][1] = fmaf(D[v], xs[j][2 * v], acc[1][1]);
-                        acc[2][1] = fmaf(D[v], xc[j][2 * v], acc[2][1]);
-                        acc[0][2] = fmaf(D[v], xa[2 * v + 1], acc[0][2]);
-                        acc[1][2] = fmaf(D[v], xs[j][2 * v + 1], acc[1][2]);
-                        acc[2][2] = fmaf(D[v], xc[j][2 * v + 1], acc[2][2]);
-                        acc[0][0] = fmaf(D[v + 1], xa[2 * v + 1], acc[0][0]);
-                        acc[1][0] = fmaf(D[v + 1], xs[j][2 * v + 1], acc[1][0]);
-                        acc[2][0] = fmaf(D[v + 1], xc[j][2 * v + 1], acc[2][0]);
+                        acc[0][0][1] = fmaf(D[v], xa[2 * v], acc[0][0][1]);
+                        acc[0][1][1] = fmaf(D[v], xs[j][2 * v], acc[0][1][1]);
+                        acc[0][2][1] = fmaf(D[v], xc[j][2 * v], acc[0][2][1]);
+                        acc[0][0][2] = fmaf(D[v], xa[2 * v + 1], acc[0][0][2]);
+                        acc[0][1][2] = fmaf(D[v], xs[j][2 * v + 1], acc[0][1][2]);
+                        acc[0][2][2] = fmaf(D[v], xc[j][2 * v + 1], acc[0][2][2]);
+                        acc[0][0][0] = fmaf(D[v + 1], xa[2 * v + 1], acc[0][0][0]);
+                        acc[0][1][0] = fmaf(D[v + 1], xs[j][2 * v + 1], acc[0][1][0]);
+                        acc[0][2][0] = fmaf(D[v + 1], xc[j][2 * v + 1], acc[0][2][0]);
                     }
 #pragma unroll
                     for (int i = 0; i < NW; ++i) xa[i] = xc[j][i];
@@ -706,14 +756,16 @@ __global__ __launch_bounds__(256) void k_nchwd_bwd_filter_k3(Geom g, const T *__
 
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-    for (int kh = 0; kh < 3; ++kh)
+    for (int q = 0; q < M; ++q)
 #pragma unroll
-        for (int kw = 0; kw < 3; ++kw) {
-            const float s = wave_sum(acc[kh][kw]);
-            if (lane == 0) red[wv][kh * 3 + kw] = s;
-        }
+        for (int kh = 0; kh < 3; ++kh)
+#pragma unroll
+            for (int kw = 0; kw < 3; ++kw) {
+                const float s = wave_sum(acc[q][kh][kw]);
+                if (lane == 0) red[wv][(q * 3 + kh) * 3 + kw] = s;
+            }
     __syncthreads();
-    if (threadIdx.x < 9) {
+    if (threadIdx.x < M * 9) {
         const int t = threadIdx.x;
         ws[((size_t)part * g.O + o) * 9 + t] = (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
     }
@@ -1310,50 +1362,67 @@ int nchwd_vec(const Geom &g, int dtype, int pass)
     return wv % 8 == 0 ? 8 : (wv % 4 == 0 ? 4 : 0);
 }
 
+// Multiplier 2, 3x3: one lane walks a plane of x once for both of its outputs, where that leaves 1024 wavefronts.
+// (Outputs the same, fewer loads of x: 56x56x256 fp32 batch 32 forward 55 -> 47 us, filter gradient, from 1024 blocks on, 81 -> 71; 36x36x128 batch 64
+// 26.4 -> 23.9, 28x28x128 batch 32 11.3 -> 9.7; bf16 56x56x256 32.8 -> 30.5; 112x112x64 batch 16 ties.)
+static bool both_outputs(const Geom &g, int V, int TH)
+{
+    return g.m == 2 && (long long)g.N * g.C * ceil_div_h(g.H, TH) * (g.W / V) >= 65536;
+}
+
 template <typename T, int V, int K>
 static hipError_t go_s1(const Geom &g, const void *x, const void *w, void *y, bool flip, int TH, hipStream_t st)
 {
     const long long out_bytes = (long long)g.N * g.O * g.H * g.W * sizeof(T);
+    constexpr int BOTH = K == 3 ? 2 : 1;
+    const bool both = K == 3 && !flip && both_outputs(g, V, TH);
+    const int nch = both ? g.C : g.O;
     if constexpr (sizeof(T) * V == 16) {
         // whole-line write-out, streamed: rows grouped so that a group is a whole number of lines
         const int rs = row_group(g.W, (int)sizeof(T));
         if (rs >= 2 && g.H % rs == 0 && stream_stores(flip ? "NCHW_S1_BWD" : "NCHW_S1_FWD", out_bytes, 0)) {
             TH = (TH + rs - 1) / rs * rs;
             const int nstrips = ceil_div_h(g.H, TH);
-            const long long lanes = (long long)g.N * g.O * nstrips * (g.W / V);
+            const long long lanes = (long long)g.N * nch * nstrips * (g.W / V);
             const unsigned nblocks = (unsigned)((lanes + 255) / 256);
-#define GOL(FL, RSV) hipLaunchKernelGGL((k_nchwd_s1<T, V, K, 2, FL, RSV>), dim3(nblocks), dim3(256), 0, st, g, \
+#define GOL(FL, RSV, MV) hipLaunchKernelGGL((k_nchwd_s1<T, V, K, 2, FL, RSV, MV>), dim3(nblocks), dim3(256), 0, st, g, \
                                         (const T *)x, (const T *)w, (T *)y, TH, nstrips, nblocks, 1)
-#define GOB(FL, RSV) hipLaunchKernelGGL((k_nchwd_s1_bf16x8<V, K, 2, FL, RSV>), dim3(nblocks), dim3(256), 0, st, g, \
+#define GOB(FL, RSV, MV) hipLaunchKernelGGL((k_nchwd_s1_bf16x8<V, K, 2, FL, RSV, MV>), dim3(nblocks), dim3(256), 0, st, g, \
                                         (const bf16_t *)x, (const bf16_t *)w, (bf16_t *)y, TH, nstrips, nblocks)
             if constexpr (sizeof(T) == 2 && V == 8) {      // bf16: packed-pair arithmetic
                 if (!tune_env("DWCONV_TUNE_NODOT")) {
-                    if (rs == 2) { if (flip) GOB(true, 2); else GOB(false, 2); }
-                    else { if (flip) GOB(true, 4); else GOB(false, 4); }
+                    if (both) { if (rs == 2) GOB(false, 2, BOTH); else GOB(false, 4, BOTH); }
+                    else if (rs == 2) { if (flip) GOB(true, 2, 1); else GOB(false, 2, 1); }
+                    else { if (flip) GOB(true, 4, 1); else GOB(false, 4, 1); }
                     return hipGetLastError();
                 }
             }
-            if (rs == 2) { if (flip) GOL(true, 2); else GOL(false, 2); }
-            else { if (flip) GOL(true, 4); else GOL(false, 4); }
+            if (both) { if (rs == 2) GOL(false, 2, BOTH); else GOL(false, 4, BOTH); }
+            else if (rs == 2) { if (flip) GOL(true, 2, 1); else GOL(false, 2, 1); }
+            else { if (flip) GOL(true, 4, 1); else GOL(false, 4, 1); }
 #undef GOL
             return hipGetLastError();
         }
     }
     const int nstrips = ceil_div_h(g.H, TH);
-    const long long lanes = (long long)g.N * g.O * nstrips * (g.W / V);
+    const long long lanes = (long long)g.N * nch * nstrips * (g.W / V);
     const unsigned nblocks = (unsigned)((lanes + 255) / 256);
     // rows that are whole lines by themselves can be streamed as they are; otherwise a wave's store
     // covers pieces of several rows (partial lines) and stays cached
     if constexpr (sizeof(T) == 2) {
         if (!tune_env("DWCONV_TUNE_NODOT")) {
-            if (flip) GOB(true, 0); else GOB(false, 0);
+            if (both) GOB(false, 0, BOTH);
+            else if (flip) GOB(true, 0, 1); else GOB(false, 0, 1);
             return hipGetLastError();
         }
     }
 #undef GOB
     const int whole = (g.W * (int)sizeof(T)) % 128 == 0;
     const int nt = whole ? stream_stores(flip ? "NCHW_S1_BWD" : "NCHW_S1_FWD", out_bytes, 0) : 0;
-    if (flip)
+    if (both)
+        hipLaunchKernelGGL((k_nchwd_s1<T, V, K, 2, false, 0, BOTH>), dim3(nblocks), dim3(256), 0, st, g, (const T *)x, (const T *)w,
+                           (T *)y, TH, nstrips, nblocks, nt);
+    else if (flip)
         hipLaunchKernelGGL((k_nchwd_s1<T, V, K, 2, true, 0>), dim3(nblocks), dim3(256), 0, st, g, (const T *)x, (const T *)w,
                            (T *)y, TH, nstrips, nblocks, nt);
     else
@@ -1474,7 +1543,10 @@ hipError_t nchwd_bwd_filter(const Geom &g, int dtype, int V, const void *x, cons
         else return hipErrorInvalidValue;
 #undef GO5
     } else if (g.s == 1) {
-        if (dtype == DT_F32 && V == 4) GO(float, 4, 1);
+        if (dtype == DT_F32 && V == 4 && g.m == 2 && (long long)parts * g.C >= 1024)      // both outputs of a channel: x is read once
+            hipLaunchKernelGGL((k_nchwd_bwd_filter_k3<float, 4, 1, 2>), dim3(parts, g.C), dim3(256), 0, st, g, (const float *)x, (const float *)dy,
+                               ws, TH, nstrips, lg, rounds);
+        else if (dtype == DT_F32 && V == 4) GO(float, 4, 1);
         else if (dtype == DT_BF16 && V == 8) GO(bf16_t, 8, 1);
         else if (dtype == DT_BF16 && V == 4) GO(bf16_t, 4, 1);
         else return hipErrorInvalidValue;

@@ -1,0 +1,29 @@
+"""GPU parity of the NCHW row walk that takes both outputs of a channel (multiplier 2, 3x3, launches of 65536 lanes and more; filter
+gradient: 1024 blocks) against the CPU oracle, element by element: row groups of two and four for the whole-line write-out, rows
+that are whole lines, rows of 8-byte vectors, heights that leave a short last strip."""
+import pytest
+
+import paper_1803_09926_amd as dw
+from paper_1803_09926_amd import workloads as wl
+from paper_1803_09926_amd.workloads import Layer
+
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+# batch, layer
+CASES = [
+    (16, Layer("rows56", 96, 56, 56, 3, 1, 1, 2)),                 # groups of four rows
+    (9, Layer("rows112", 48, 112, 112, 3, 1, 1, 2)),               # groups of two; lanes past the last plane
+    (24, Layer("whole_lines", 128, 37, 32, 3, 1, 1, 2)),           # stored as they are
+    (20, Layer("short_vectors", 96, 45, 44, 3, 1, 1, 2)),          # bf16: four columns a lane
+]
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("case", CASES, ids=[c[1].name for c in CASES])
+def test_both_outputs_of_a_channel(case, dtype):
+    N, layer = case
+    d = gu.desc_for(layer, N, wl.NCHW, dtype)
+    print("case", layer.name, dtype, [dw.variant_name(d, i) for i in range(3)], flush=True)
+    gu.check_layer_full(layer, N, wl.NCHW, dtype, seed=51)
