@@ -147,7 +147,7 @@ int dwconv_bwd(const dwconv_desc *desc, const void *x, const void *dy, const voi
     if (misaligned(workspace)) return DWCONV_ERR_ALIGN;
     hipError_t e = launch_bwd_fused(pl, g, desc->layout, desc->dtype, x, dy, w, dx, (float *)workspace, (hipStream_t)stream);
     if (e != hipSuccess) return DWCONV_ERR_LAUNCH;
-    e = reduce_partials((const float *)workspace, pl.parts, g.O * g.K * g.K, (float *)dw, (hipStream_t)stream);
+    e = launch_reduce(pl, g, desc->layout, desc->dtype, x, dy, (const float *)workspace, (float *)dw, (hipStream_t)stream);
     return e == hipSuccess ? DWCONV_OK : DWCONV_ERR_LAUNCH;
 }
 

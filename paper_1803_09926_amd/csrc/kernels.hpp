@@ -95,6 +95,10 @@ hipError_t nchwf_bwd_data(const Geom &g, int dtype, const void *dy, const void *
 int nchwf_bwd_filter_parts(const Geom &g, int dtype);       // 0 = unsupported
 void nchwf_bwd_filter_tiles(const Geom &g, int dtype, int parts, FilterGradSrc *f);      // what its partials hold
 hipError_t nchwf_bwd_filter(const Geom &g, int dtype, const void *x, const void *dy, float *ws, int parts, hipStream_t st);
+// fused backward (input gradient + stage 1 of the filter gradient), 3x3 "same" stride 1, multiplier 1
+int nchwf_bwd_fused_parts(const Geom &g, int dtype);        // 0 = unsupported
+void nchwf_bwd_fused_tiles(const Geom &g, int dtype, int parts, FilterGradSrc *f);
+hipError_t nchwf_bwd_fused(const Geom &g, int dtype, const void *x, const void *dy, const void *w, void *dx, float *ws, int parts, hipStream_t st);
 
 // ---- NCHW row-walk kernels for rows that are whole 16-byte vectors (nchw_direct.hip) -----------
 // pass: 0 fwd, 1 bwd_data, 2 bwd_filter.  Returns the columns per lane, 0 if not applicable.

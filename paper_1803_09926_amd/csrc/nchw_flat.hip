@@ -342,6 +342,47 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_data_s2(const T *__restrict__
     }
 }
 
+// The sums of a block's lanes, channel by channel (`np` of them from o0 on, `ncol` lanes each), to its partial.
+template <int K, int SETS>
+__device__ __forceinline__ void add_columns(const float (&acc)[SETS][K][K], float *red, float *__restrict__ dst, int np, int ncol, int o0)
+{
+    // CH sums at a time (all of them up to 5x5): [CH][threads] in LDS, then Q lanes per (channel, tap) add every Q-th column
+    const int Q = ncol < 16 ? 1 : ncol < 64 ? 4 : 8;
+    constexpr int CH = K * K <= 25 ? K * K : 25;
+    const int nt = blockDim.x;
+#pragma unroll
+    for (int e0 = 0; e0 < K * K; e0 += CH) {
+        const int ne = K * K - e0 < CH ? K * K - e0 : CH;
+#pragma unroll
+        for (int e = 0; e < CH; ++e)
+            if (e0 + e < K * K) {
+                const float s = acc[0][(e0 + e) / K][(e0 + e) % K];
+                red[e * nt + threadIdx.x] = SETS == 2 ? s + acc[SETS - 1][(e0 + e) / K][(e0 + e) % K] : s;
+            }
+        __syncthreads();
+        const int jobs = np * ne;
+        for (int f0 = 0; f0 < jobs * Q; f0 += nt) {        // uniform trip count
+            const int f = f0 + (int)threadIdx.x, job = f / Q, q = f & (Q - 1);
+            const int uj = job / ne, e = job - uj * ne;
+            float s = 0.f;
+            if (job < jobs) {                              // four sums side by side: a chain of n adds 2^-24 * sqrt(n / 6) to the error
+                const float *col = red + e * nt + uj * ncol;
+                float p[4] = {0.f, 0.f, 0.f, 0.f};
+                int i = q;
+                for (; i + 3 * Q < ncol; i += 4 * Q) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) p[k] += col[i + k * Q];
+                }
+                for (; i < ncol; i += Q) p[0] += col[i];
+                s = (p[0] + p[1]) + (p[2] + p[3]);
+            }
+            for (int h = Q >> 1; h >= 1; h >>= 1) s += __shfl_xor(s, h, 64);
+            if (job < jobs && q == 0) dst[(o0 + uj) * K * K + e0 + e] = s;
+        }
+        __syncthreads();
+    }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Filter gradient, stage 1.  A block owns U output channels and walks (image, band) items: x bands staged as above, dy read by the
 // lanes that own its columns a few rows ahead (or from LDS, see DY_LDS); a lane keeps the K*K sums of its column over all of
@@ -478,42 +519,115 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__res
         __syncthreads();
     }
 
-    // CH sums at a time (all of them up to 5x5): [CH][threads] in LDS, then Q lanes per (channel, tap) add every Q-th column
-    const int Q = ncol < 16 ? 1 : ncol < 64 ? 4 : 8;
-    constexpr int CH = K * K <= 25 ? K * K : 25;
-    float *red = reinterpret_cast<float *>(smem);
-    const int J = g.O * K * K, nt = blockDim.x;
+    add_columns<K, SETS>(acc, reinterpret_cast<float *>(smem), ws + (size_t)part * g.O * K * K, np, ncol, o0);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Whole backward pass, 3x3 "same" stride 1, multiplier 1: the input gradient and stage 1 of the filter gradient from one walk over x and
+// dy.  Blocks and items of the filter gradient; the dy bands with their halo rows go to LDS, a lane reads x only in its own column, a few
+// rows ahead.  The 3x3 window of dy around (row t, column c) gives dx[t][c] and, its middle row against x rows t - 1, t and t + 1 of
+// column c, the filter gradient summed per x column: 18 multiply-adds for three LDS reads, one load and one store.
+// The two passes and this one, stage 2 in both, us on one MI355X: 19x19x728 batch 32 fp32 33.5 -> 25.3, bf16 28.3 -> 21.4; 74x74x256 batch 32 162 -> 129 and
+// 96 -> 83; 147x147x96 batch 16 134 -> 104; 10x10x240 batch 128 22.2 -> 16.8; 21x21x32 batch 8 11.3 -> 8.4; no size measured was longer.
+// ---------------------------------------------------------------------------------------------
+template <typename T>
+__global__ __launch_bounds__(512) void k_nchwf_bwd_fused(Geom g, const T *__restrict__ x, const T *__restrict__ dy, const T *__restrict__ w,
+                                                         T *__restrict__ dx, float *__restrict__ ws, int parts, int per_part, FlatTile ft,
+                                                         unsigned nblocks)
+{
+    extern __shared__ uint4 smem[];
+    constexpr int PD = 6;                                  // x rows on their way; a multiple of the window, so that it returns to its registers
+    const unsigned lb = xcd_remap(blockIdx.x, nblocks);
+    const int part = (int)(lb % (unsigned)parts), o0 = (int)(lb / (unsigned)parts) * ft.U;
+    const int np = min(ft.U, g.O - o0), W = g.W, HW = g.H * g.W;
+    const int u = (int)threadIdx.x / W, c = (int)threadIdx.x - u * W;
+    const bool active = u < np;
+    const int uu = active ? u : 0;
+    const uint32_t okl = c > 0 ? ~0u : 0u, okr = c < W - 1 ? ~0u : 0u;
+    T *ld = reinterpret_cast<T *>(smem) + GUARD;
+    const uint32_t off = active ? (uint32_t)(u * HW + c) * (uint32_t)sizeof(T) : BufView::OUTSIDE;      // a column that is none reads zero and is not stored
+    float wr[3][3];
+    NonFinite bad;
 #pragma unroll
-    for (int e0 = 0; e0 < K * K; e0 += CH) {
-        const int ne = K * K - e0 < CH ? K * K - e0 : CH;
+    for (int e = 0; e < 9; ++e) { wr[e / 3][e % 3] = ldf(w + (o0 + uu) * 9 + e); bad.add(wr[e / 3][e % 3]); }
+    const bool redo = bad.any() && active;
+    float acc[2][3][3];
 #pragma unroll
-        for (int e = 0; e < CH; ++e)
-            if (e0 + e < K * K) {
-                const float s = acc[0][(e0 + e) / K][(e0 + e) % K];
-                red[e * nt + threadIdx.x] = SETS == 2 ? s + acc[SETS - 1][(e0 + e) / K][(e0 + e) % K] : s;
-            }
+    for (int e = 0; e < 18; ++e) acc[e / 9][e / 3 % 3][e % 3] = 0.f;
+
+    const int items = g.N * ft.nbands, it1 = part_end(items, per_part, part);
+    for (int it = part * per_part; it < it1; ++it) {
+        __builtin_amdgcn_s_waitcnt(0xf70);                  // vmcnt(0): the last prefetches (see the filter gradient)
+        const int n = it / ft.nbands, band = it - n * ft.nbands;
+        const int oh0 = band * ft.TR, oh1 = min(g.H, oh0 + ft.TR), rows = oh1 - oh0;
+        const int r0 = max(oh0 - 1, 0), r1 = min(oh1 + 1, g.H);
+        const size_t image = (size_t)(n * g.O + o0) * HW;
+        const uint32_t bytes = (uint32_t)(np * HW) * (uint32_t)sizeof(T);
+        const BufView vx(x + image, bytes), vout(dx + image, bytes);
+        const Bands b = {n * g.O + o0, np, HW, W, r0, r1, ft.pin};
+        dma_bands<T>(dy, g.N * g.O * HW, b, ld);
+        T xq[PD];
+        auto fetch = [&](int t) { return load_one<T>(vx, off, (uint32_t)(min(max(oh0 + t, 0), g.H - 1) * W) * (uint32_t)sizeof(T)); };
+        const T xa = fetch(-1), xb = fetch(0);
+#pragma unroll
+        for (int i = 0; i < PD; ++i) xq[i] = fetch(min(i + 1, rows));
+        dma_wait();
         __syncthreads();
-        const int jobs = np * ne;
-        for (int f0 = 0; f0 < jobs * Q; f0 += nt) {        // uniform trip count
-            const int f = f0 + (int)threadIdx.x, job = f / Q, q = f & (Q - 1);
-            const int uj = job / ne, e = job - uj * ne;
-            float s = 0.f;
-            if (job < jobs) {                              // four sums side by side: a chain of n adds 2^-24 * sqrt(n / 6) to the error
-                const float *col = red + e * nt + uj * ncol;
-                float p[4] = {0.f, 0.f, 0.f, 0.f};
-                int i = q;
-                for (; i + 3 * Q < ncol; i += 4 * Q) {
+        const T *p = ld + b.at<T>(uu) + c - 1 - r0 * W;      // row r of the image at p + r * W
+        auto read = [&](int r, float (&v)[3]) {
+            const T *q = p + r * W;
+            v[0] = masked(ldf(q), okl); v[1] = ldf(q + 1); v[2] = masked(ldf(q + 2), okr);
+        };
+        float d[3][3], xw[3];
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) p[k] += col[i + k * Q];
-                }
-                for (; i < ncol; i += Q) p[0] += col[i];
-                s = (p[0] + p[1]) + (p[2] + p[3]);
+        for (int i = 0; i < 3; ++i) d[0][i] = 0.f;
+        if (oh0 > 0) read(oh0 - 1, d[0]);
+        read(oh0, d[1]);
+        xw[0] = oh0 > 0 ? ldf(&xa) : 0.f; xw[1] = ldf(&xb);
+        // step t: row oh0 + t of dx and of dy; the rows below it are read here
+        auto step = [&](int t, auto last, int set) {
+            constexpr bool LAST = decltype(last)::value;     // the plane's last row
+            if constexpr (LAST) {
+#pragma unroll
+                for (int i = 0; i < 3; ++i) d[2][i] = 0.f;
+                xw[2] = 0.f;
+            } else {
+                read(oh0 + t + 1, d[2]);
+                xw[2] = ldf(&xq[0]);
             }
-            for (int h = Q >> 1; h >= 1; h >>= 1) s += __shfl_xor(s, h, 64);
-            if (job < jobs && q == 0) ws[(size_t)part * J + (o0 + uj) * K * K + e0 + e] = s;
+#pragma unroll
+            for (int i = 0; i + 1 < PD; ++i) xq[i] = xq[i + 1];
+            if constexpr (!LAST) xq[PD - 1] = fetch(min(t + 1 + PD, rows));
+            float s = 0.f;
+#pragma unroll
+            for (int kh = 0; kh < 3; ++kh)
+#pragma unroll
+                for (int kw = 0; kw < 3; ++kw) {
+                    s = fmaf(wr[kh][kw], d[2 - kh][2 - kw], s);
+                    acc[set][kh][kw] = fmaf(d[1][2 - kw], xw[kh], acc[set][kh][kw]);
+                }
+            store_one<T>(vout, s, off, (uint32_t)((oh0 + t) * W) * (uint32_t)sizeof(T));
+#pragma unroll
+            for (int i = 0; i < 3; ++i) { d[0][i] = d[1][i]; d[1][i] = d[2][i]; }
+            xw[0] = xw[1]; xw[1] = xw[2];
+        };
+        const int tb = oh1 < g.H ? rows : rows - 1;
+        int t = 0;
+#pragma unroll 1
+        for (; t + PD <= tb; t += PD) {
+#pragma unroll
+            for (int i = 0; i < PD; ++i) step(t + i, std::false_type(), i % 2);
+        }
+#pragma unroll 1
+        for (; t < tb; ++t) step(t, std::false_type(), 0);
+        if (t < rows) step(t, std::true_type(), 0);
+        if (__builtin_expect(redo, 0)) {          // the lane's column again, without the padding
+#pragma unroll 1
+            for (int h = oh0; h < oh1; ++h) stf(dx + image + (size_t)u * HW + h * W + c, point_bwd_data<T, LAYOUT_NCHW>(g, dy, w, n, o0 + u, h, c));
         }
         __syncthreads();
     }
+    add_columns<3, 2>(acc, reinterpret_cast<float *>(smem), ws + (size_t)part * g.O * 9, np, W, o0);
 }
 
 // ---- host side --------------------------------------------------------------------------------
@@ -665,6 +779,27 @@ bool filter_tile(const Geom &g, int dtype, FlatTile *ft)
     return (lds && pick(true) && ft->nbands > 1) || pick(false);
 }
 
+bool fused_tile(const Geom &g, int dtype, FlatTile *ft)
+{
+    auto in_rows = [&](int t) { return t + 2; };
+    return pick_tile(dtype == DT_F32 ? 4 : 2, g.W, g.H, g.O, most_planes((long long)g.N * g.O, g.H, g.W), g.H, g.W, g.H, g.W, in_rows, 1, 1, lds_target(3), ft,
+                     g.N, LEAST_FILTER_BAND);
+}
+// Parts of the filter gradient: about eight blocks per compute unit in the launch, two items per block and more where the launch has more
+// than four blocks per compute unit that way, and at most 8 MiB of partials.
+int filter_parts(const Geom &g, const FlatTile &ft)
+{
+    const long long groups = (g.O + ft.U - 1) / ft.U, items = (long long)g.N * ft.nbands;
+    long long parts = (2048 + groups - 1) / groups;
+    if (groups * items > 1024 && parts > (items + 1) / 2) parts = (items + 1) / 2;
+    if (parts > items) parts = items;
+    const long long J = (long long)g.O * g.K * g.K;
+    if (parts * J * 4 > (8 << 20)) parts = (8 << 20) / (J * 4);
+    if (parts < 1) parts = 1;
+    const long long per = (items + parts - 1) / parts;
+    return (int)((items + per - 1) / per);
+}
+
 }  // namespace
 
 bool nchwf_fwd_supported(const Geom &g, int dtype)
@@ -683,17 +818,22 @@ int nchwf_bwd_filter_parts(const Geom &g, int dtype)
 {
     FlatTile ft;
     if (!flat_k(g) || !filter_tile(g, dtype, &ft)) return 0;
-    // about eight blocks per compute unit in the launch, two items per block and more where the launch has more than four
-    // blocks per compute unit that way, and at most 8 MiB of partials
-    const long long groups = (g.O + ft.U - 1) / ft.U, items = (long long)g.N * ft.nbands;
-    long long parts = (2048 + groups - 1) / groups;
-    if (groups * items > 1024 && parts > (items + 1) / 2) parts = (items + 1) / 2;
-    if (parts > items) parts = items;
-    const long long J = (long long)g.O * g.K * g.K;
-    if (parts * J * 4 > (8 << 20)) parts = (8 << 20) / (J * 4);
-    if (parts < 1) parts = 1;
-    const long long per = (items + parts - 1) / parts;
-    return (int)((items + per - 1) / per);
+    return filter_parts(g, ft);
+}
+
+int nchwf_bwd_fused_parts(const Geom &g, int dtype)
+{
+    FlatTile ft;
+    if (!(g.K == 3 && g.s == 1 && g.p == 1 && g.m == 1) || !fused_tile(g, dtype, &ft)) return 0;
+    return filter_parts(g, ft);
+}
+void nchwf_bwd_fused_tiles(const Geom &g, int dtype, int parts, FilterGradSrc *f)
+{
+    FlatTile ft;
+    fused_tile(g, dtype, &ft);
+    f->TN = 1; f->TA = ft.TR; f->TB = g.Wo;
+    f->tn = g.N; f->ta = ft.nbands; f->tb = 1;
+    f->per = cdiv(g.N * ft.nbands, parts); f->nparts = parts;
 }
 
 void nchwf_bwd_filter_tiles(const Geom &g, int dtype, int parts, FilterGradSrc *f)
@@ -754,6 +894,25 @@ static hipError_t filter_go(const Geom &g, int dtype, const void *x, const void 
     hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(ft.threads), lds, st, g, (const T *)x, (const T *)dy, ws, parts,
                        per, ft, nblocks);
     return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t fused_go(const Geom &g, int dtype, const void *x, const void *dy, const void *w, void *dx, float *ws, int parts, hipStream_t st)
+{
+    FlatTile ft;
+    if (!fused_tile(g, dtype, &ft)) return hipErrorInvalidValue;
+    const int items = g.N * ft.nbands, per = cdiv(items, parts);
+    const unsigned nblocks = (unsigned)cdiv(g.O, ft.U) * parts;
+    size_t lds = tile_lds(ft, sizeof(T));
+    const size_t red = (size_t)9 * ft.threads * 4;
+    if (red > lds) lds = red;
+    hipLaunchKernelGGL(k_nchwf_bwd_fused<T>, dim3(nblocks), dim3(ft.threads), lds, st, g, (const T *)x, (const T *)dy, (const T *)w, (T *)dx, ws, parts,
+                       per, ft, nblocks);
+    return hipGetLastError();
+}
+hipError_t nchwf_bwd_fused(const Geom &g, int dtype, const void *x, const void *dy, const void *w, void *dx, float *ws, int parts, hipStream_t st)
+{
+    return dtype == DT_F32 ? fused_go<float>(g, dtype, x, dy, w, dx, ws, parts, st) : fused_go<bf16_t>(g, dtype, x, dy, w, dx, ws, parts, st);
 }
 
 #define BY_K(F, ...) (g.K == 3 ? F<T, 3, __VA_ARGS__> : g.K == 5 ? F<T, 5, __VA_ARGS__> : F<T, 7, __VA_ARGS__>)

@@ -407,8 +407,14 @@ Plan plan_bwd(const Geom &g, int layout, int dtype)
                     pl = pf;
                     pl.variant = V_NCHWD_BWD_FUSED; pl.b = TH; pl.parts = parts;
                     pl.name = "nchw_bwd_fused_k3s1";
+                    return pl;
                 }
             }
+        }
+        // where both passes would run on the any-width kernels
+        if (g.s == 1 && g.K == 3 && plan_bwd_data(g, layout, dtype).variant == V_NCHWF_BWD_DATA && plan_bwd_filter(g, layout, dtype).variant == V_NCHWF_BWD_FILTER) {
+            const int parts = nchwf_bwd_fused_parts(g, dtype);
+            if (parts > 0) { pl = {V_NCHWF_BWD_FUSED, parts, 0, 0, 0, "nchw_flat_bwd_fused_k3s1"}; }
         }
     }
     return pl;
@@ -462,9 +468,10 @@ hipError_t launch_reduce(const Plan &pl, const Geom &g, int layout, int dtype, c
                          hipStream_t st)
 {
     const int J = g.O * g.K * g.K;
-    if (pl.variant != V_NCHWF_BWD_FILTER && pl.variant != V_NHWCA_BWD_FILTER) return reduce_partials(ws, pl.parts, J, dw, st);
+    if (pl.variant != V_NCHWF_BWD_FILTER && pl.variant != V_NHWCA_BWD_FILTER && pl.variant != V_NCHWF_BWD_FUSED) return reduce_partials(ws, pl.parts, J, dw, st);
     FilterGradSrc src = {x, dy, dtype, layout, g.N, g.C, g.H, g.W, g.K, g.s, g.p, g.O, 1, g.m, g.Ho, g.Wo};
     if (pl.variant == V_NCHWF_BWD_FILTER) nchwf_bwd_filter_tiles(g, dtype, pl.parts, &src);
+    else if (pl.variant == V_NCHWF_BWD_FUSED) nchwf_bwd_fused_tiles(g, dtype, pl.parts, &src);
     else nhwca_bwd_filter_tiles(g, &src);
     return reduce_partials(ws, pl.parts, J, dw, src, st);
 }
@@ -475,6 +482,7 @@ hipError_t launch_bwd_fused(const Plan &pl, const Geom &g, int layout, int dtype
     (void)layout;
     if (pl.variant == V_NCHWD_BWD_FUSED) return nchwd_bwd_fused(g, dtype, pl.a, x, dy, w, dx, ws, pl.b, st);
     if (pl.variant == V_NCHWS_BWD_FUSED) return nchws_bwd_fused(g, dtype, x, dy, w, dx, ws, pl.a, pl.c, st);
+    if (pl.variant == V_NCHWF_BWD_FUSED) return nchwf_bwd_fused(g, dtype, x, dy, w, dx, ws, pl.parts, st);
     if (pl.variant != V_NHWC_BWD_FUSED) return hipErrorInvalidValue;
     return nhwc_bwd_fused(g, dtype, pl.a, x, dy, w, dx, ws, pl.b, pl.c, st);
 }
