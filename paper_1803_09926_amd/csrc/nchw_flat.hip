@@ -226,6 +226,95 @@ __global__ __launch_bounds__(512) void k_nchwf_conv(const T *__restrict__ in, co
 }
 
 // ---------------------------------------------------------------------------------------------
+// The same for 3x3 "same" stride 1 in bf16 on rows of an even width: a lane owns two adjacent columns, which are one aligned word in LDS as in
+// the output, and reads the words beside it, half of each masked away.  A row of three taps is two packed dot products an output, nothing is
+// widened: 12 dot products, two masks and three LDS reads for two columns of three rows, against 18 multiply-adds, ten other
+// instructions and six reads.
+// us, one column a lane -> this, batch 32 74x74x256 47.0 -> 43.4, batch 16 146x146x96 32.3 -> 26.1 and 35.0 -> 28.0 (input gradient), batch 16
+// 50x50x300 14.8 -> 13.4, batch 64 13x90x64 8.7 -> 7.7.
+// ---------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(512) void k_nchwf_conv_pairs(const bf16_t *__restrict__ in, const bf16_t *__restrict__ w, bf16_t *__restrict__ out,
+                                                          int nplanes, int OC, int H, int W, int mdiv, int total_in, int flip, FlatTile ft,
+                                                          unsigned nblocks, Geom g)
+{
+    extern __shared__ uint4 smem[];
+    const unsigned lb = xcd_remap(blockIdx.x, nblocks);
+    const int band = (int)(lb % (unsigned)ft.nbands), p0 = (int)(lb / (unsigned)ft.nbands) * ft.U;
+    const int np = min(ft.U, nplanes - p0);
+    const int oh0 = band * ft.TR, oh1 = min(H, oh0 + ft.TR);
+    const int ip0 = p0 / mdiv, ip1 = (p0 + np - 1) / mdiv + 1;
+    const int r0 = max(oh0 - 1, 0), r1 = min(oh1 + 1, H);
+    const Bands bi = {ip0, ip1 - ip0, H * W, W, r0, r1, ft.pin};
+    bf16_t *lin = reinterpret_cast<bf16_t *>(smem) + GUARD;
+    dma_bands<bf16_t>(in, total_in, bi, lin);
+
+    const int ncol = W / 2, u = (int)threadIdx.x / ncol, ow = ((int)threadIdx.x - u * ncol) * 2;
+    const bool active = u < np;
+    const int pl = p0 + (active ? u : 0), oc = pl % OC;
+    // of the word to the left the right half, of the one to the right the left half
+    const uint32_t okl = ow > 0 ? 0xffff0000u : 0u, okr = ow + 2 < W ? 0x0000ffffu : 0u;
+    uint32_t wl[3], w12[3], w01[3], wrt[3];                 // filter rows against the three words: (0, w0), (w1, w2) and (w0, w1), (w2, 0)
+    NonFinite bad;
+#pragma unroll
+    for (int kh = 0; kh < 3; ++kh) {
+        uint32_t e[3];
+#pragma unroll
+        for (int kw = 0; kw < 3; ++kw) {
+            const int tap = kh * 3 + kw;
+            e[kw] = w[oc * 9 + (flip ? 8 - tap : tap)];
+            bad.add(bf16_to_f32((bf16_t)e[kw]));
+        }
+        wl[kh] = e[0] << 16; w12[kh] = e[1] | e[2] << 16;
+        w01[kh] = e[0] | e[1] << 16; wrt[kh] = e[2];
+    }
+    const bool redo = bad.any() && active;
+    // (rows of an even width start at even elements: the words are aligned)
+    const bf16_t *p = lin + bi.at<bf16_t>(pl / mdiv - ip0) + ow - r0 * W;
+    const BufView vout(out + (size_t)p0 * H * W, (uint32_t)(np * H * W) * 2u);
+    const uint32_t voff = active ? (uint32_t)((u * H + oh0) * W + ow) * 2u : BufView::OUTSIDE;
+    float acc[3][2];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) acc[i / 2][i % 2] = 0.f;
+    dma_wait();
+    __syncthreads();
+
+    // step t reads image row oh0 - 1 + t, which meets the outputs of rows oh0 + t - i; the one with i = 2 is complete
+    const int rows = oh1 - oh0;
+    auto step = [&](int t, auto checked) {
+        constexpr bool CK = decltype(checked)::value;
+        const int row = oh0 - 1 + t;                       // everything about the row is uniform
+        if (!CK || (unsigned)row < (unsigned)H) {
+            const uint32_t *q = reinterpret_cast<const uint32_t *>(p + row * W);
+            const uint32_t l = q[-1] & okl, m = q[0], r = q[1] & okr;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                acc[i][0] = dot2_bf16(m, w12[i], dot2_bf16(l, wl[i], acc[i][0]));
+                acc[i][1] = dot2_bf16(r, wrt[i], dot2_bf16(m, w01[i], acc[i][1]));
+            }
+        }
+        if (!CK || t >= 2) store_two<bf16_t>(vout, acc[2][0], acc[2][1], voff, (uint32_t)((t - 2) * W) * 2u);
+#pragma unroll
+        for (int i = 2; i > 0; --i) { acc[i][0] = acc[i - 1][0]; acc[i][1] = acc[i - 1][1]; }
+        acc[0][0] = acc[0][1] = 0.f;
+    };
+    const int steps = rows + 2, tb = min(steps, H + 1 - oh0);      // steps [2, tb) have their row inside the image
+    int t = 0;
+    for (; t < 2; ++t) step(t, std::true_type());
+#pragma unroll 3
+    for (; t < tb; ++t) step(t, std::false_type());
+    for (; t < steps; ++t) step(t, std::true_type());
+    if (__builtin_expect(redo, 0)) {          // the lane's columns again, without the padding
+        const int n = pl / OC;
+#pragma unroll 1
+        for (int i = 0; i < 2 * rows; ++i) {
+            const int row = oh0 + i / 2, cw = ow + i % 2;
+            stf(out + ((size_t)pl * H + row) * W + cw,
+                flip ? point_bwd_data<bf16_t, LAYOUT_NCHW>(g, in, w, n, oc, row, cw) : point_fwd<bf16_t, LAYOUT_NCHW>(g, in, w, n, oc, row, cw));
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
 // Input gradient of a stride-2 layer.  With h + p = 2a + f and c + p = 2b + e the taps that reach dx[h][c] are kh = 2k + f,
 // kw = 2l + e against dy[a - k][b - l]: a lane owns two neighbouring dx columns, walks down the dy rows with the K/2 row
 // pairs a row reaches in rotating accumulators, and a dy row costs (K+1)/2 reads and K*K multiply-adds for four outputs.
@@ -738,9 +827,18 @@ bool flat_k(const Geom &g) { return (g.K == 3 || g.K == 5 || g.K == 7) && (g.s =
 // (40 -> 52 us), and so they do for 3x3 in bf16 (74x74x256 forward 45 -> 58 us, filter gradient 56 -> 67).
 int flat_cols(const Geom &g, int dtype) { return g.K > 3 && dtype == DT_BF16 ? 2 : 1; }
 
+// Whether k_nchwf_conv_pairs takes the pass: rows of 36 and more in launches of some size.  Half the lanes mean bands of half the height where
+// the launch is short, and narrow rows gain nothing (us, one column a lane -> pairs: 150x150x32 batch 4 7.6 -> 8.6, 18x18x728 batch 2 5.0 -> 5.5, 30x30x128
+// batch 32 8.3 -> 8.6, 20x20x512 batch 256 62.0 -> 61.2; 36x36x256 batch 64 18.9 -> 18.6, 42x42x240 batch 8 8.2 -> 7.4).
+bool conv_pairs(const Geom &g, int dtype, bool bwd)
+{
+    return dtype == DT_BF16 && g.K == 3 && g.s == 1 && g.p == 1 && g.W % 2 == 0 && !(bwd && g.m > 1) && g.W >= 36 &&
+           (long long)g.N * g.O * (g.W / 2) >= 32768;
+}
+
 bool conv_tile(const Geom &g, int dtype, bool bwd, FlatTile *ft)
 {
-    const int esz = dtype == DT_F32 ? 4 : 2, nc = flat_cols(g, dtype), cols = ((bwd ? g.W : g.Wo) + nc - 1) / nc;
+    const int esz = dtype == DT_F32 ? 4 : 2, nc = conv_pairs(g, dtype, bwd) ? 2 : flat_cols(g, dtype), cols = ((bwd ? g.W : g.Wo) + nc - 1) / nc;
     auto in_rows = [&](int t) { return (t - 1) * g.s + g.K; };
     if (!bwd)
         return pick_tile(esz, cols, g.Ho, g.N * g.O, most_planes((long long)g.N * g.O, g.Ho, cols), g.H, g.W, g.Ho, g.Wo, in_rows, 1, g.m, lds_target(g.K), ft, 1, LEAST_BAND);
@@ -854,6 +952,13 @@ static hipError_t conv_go(const Geom &g, int dtype, const void *in, const void *
     const int OC = bwd ? g.C : g.O, nplanes = g.N * OC;
     const unsigned nblocks = (unsigned)cdiv(nplanes, ft.U) * ft.nbands;
     const int total_in = g.N * (bwd ? g.O : g.C) * Hi * Wi;
+    if constexpr (sizeof(T) == 2 && K == 3 && S == 1 && M == 1) {
+        if (conv_pairs(g, dtype, bwd)) {
+            hipLaunchKernelGGL(k_nchwf_conv_pairs, dim3(nblocks), dim3(ft.threads), tile_lds(ft, sizeof(T)), st, (const T *)in, (const T *)w, (T *)out, nplanes,
+                               OC, g.H, g.W, bwd ? 1 : g.m, total_in, bwd ? 1 : 0, ft, nblocks, g);
+            return hipGetLastError();
+        }
+    }
     const bool same = (bwd ? K - 1 - g.p : g.p) == K / 2;
     constexpr int NC = K > 3 && sizeof(T) == 2 ? 2 : 1;
     auto kernel = same ? k_nchwf_conv<T, K, S, M, true, NC> : k_nchwf_conv<T, K, S, M, false, NC>;
