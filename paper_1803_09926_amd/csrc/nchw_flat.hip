@@ -612,6 +612,96 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_filter(Geom g, const T *__res
 }
 
 // ---------------------------------------------------------------------------------------------
+// The same on column pairs (see k_nchwf_conv_pairs): the two products of a tap and a pair are one packed dot product, of the dy word with the
+// x word of the same columns or with one put together from two of them.
+// us with stage 2, one column a lane -> this: 74x74x256 batch 32 54.7 -> 52.5, 146x146x96 batch 16 44.4 -> 35.4, 13x90x64 batch 64 12.8 -> 11.1.
+// ---------------------------------------------------------------------------------------------
+template <bool DYLDS>
+__global__ __launch_bounds__(512) void k_nchwf_bwd_filter_pairs(Geom g, const bf16_t *__restrict__ x, const bf16_t *__restrict__ dy, float *__restrict__ ws,
+                                                                int parts, int per_part, FlatTile ft, unsigned nblocks)
+{
+    extern __shared__ uint4 smem[];
+    constexpr int PD = 6;
+    const unsigned lb = xcd_remap(blockIdx.x, nblocks);
+    const int part = (int)(lb % (unsigned)parts), o0 = (int)(lb / (unsigned)parts) * ft.U;
+    const int np = min(ft.U, g.O - o0), W = g.W, HW = g.H * g.W;
+    const int c0 = o0 / g.m, c1 = (o0 + np - 1) / g.m + 1;
+    const int ncol = W / 2, u = (int)threadIdx.x / ncol, ow = ((int)threadIdx.x - u * ncol) * 2;
+    const bool active = u < np;
+    const int uu = active ? u : 0, ju = (o0 + uu) / g.m - c0;
+    const uint32_t okl = ow > 0 ? ~0u : 0u, okr = ow + 2 < W ? ~0u : 0u, here = active ? ~0u : 0u;
+    bf16_t *lx = reinterpret_cast<bf16_t *>(smem) + GUARD;
+    const uint32_t offd = active ? (uint32_t)(u * HW + ow) * 2u : BufView::OUTSIDE;
+    float acc[2][3][3];
+#pragma unroll
+    for (int e = 0; e < 18; ++e) acc[e / 9][e / 3 % 3][e % 3] = 0.f;
+
+    const int items = g.N * ft.nbands, it1 = part_end(items, per_part, part);
+    for (int it = part * per_part; it < it1; ++it) {
+        __builtin_amdgcn_s_waitcnt(0xf70);                  // vmcnt(0): the last prefetches (see above)
+        const int n = it / ft.nbands, band = it - n * ft.nbands;
+        const int oh0 = band * ft.TR, oh1 = min(g.H, oh0 + ft.TR), rows = oh1 - oh0;
+        const int r0 = max(oh0 - 1, 0), r1 = min(oh1 + 1, g.H);
+        const Bands bx = {n * g.C + c0, c1 - c0, HW, W, r0, r1, ft.pin};
+        const BufView vd(dy + (size_t)(n * g.O + o0) * HW, (uint32_t)(np * HW) * 2u);
+        dma_bands<bf16_t>(x, g.N * g.C * HW, bx, lx);
+        const bf16_t *px = lx + bx.at<bf16_t>(ju) + ow - r0 * W;           // row r of the image at px + r * W
+        const bf16_t *pd = lx;
+        if constexpr (DYLDS) {
+            const Bands by = {n * g.O + o0, np, HW, W, oh0, oh1, ft.pout};
+            bf16_t *ldy = lx + ft.nin + GUARD;
+            dma_bands<bf16_t>(dy, g.N * g.O * HW, by, ldy);
+            pd = ldy + by.at<bf16_t>(uu) + ow;
+        }
+        uint32_t dq[PD];
+        auto fetch = [&](int t) { return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(vd.rsrc, (int)offd, (int)((uint32_t)((oh0 + min(t, rows - 1)) * W) * 2u), 0); };
+        if constexpr (!DYLDS) {
+#pragma unroll
+            for (int i = 0; i < PD; ++i) dq[i] = fetch(i);
+        }
+        dma_wait();
+        __syncthreads();
+        // x row oh0 - 1 + t meets dy rows oh0 + t - kh, tap row kh; d[kh]: that dy row, zero where the band has none
+        uint32_t d[3] = {0u, 0u, 0u};
+        auto step = [&](int t, auto checked, int set) {
+            constexpr bool CK = decltype(checked)::value;
+            if constexpr (DYLDS) d[0] = !CK || t < rows ? *reinterpret_cast<const uint32_t *>(pd + t * W) & here : 0u;
+            else {
+                d[0] = !CK || t < rows ? dq[0] : 0u;
+#pragma unroll
+                for (int i = 0; i + 1 < PD; ++i) dq[i] = dq[i + 1];
+                dq[PD - 1] = fetch(t + PD);
+            }
+            const int row = oh0 - 1 + t;
+            if (!CK || (unsigned)row < (unsigned)g.H) {
+                const uint32_t *q = reinterpret_cast<const uint32_t *>(px + row * W);
+                const uint32_t m = q[0];
+                // columns (c - 1, c), (c, c + 1), (c + 1, c + 2)
+                const uint32_t e[3] = {__builtin_amdgcn_perm(m, q[-1] & okl, 0x05040302u), m, __builtin_amdgcn_perm(q[1] & okr, m, 0x05040302u)};
+#pragma unroll
+                for (int kh = 0; kh < 3; ++kh)
+#pragma unroll
+                    for (int kw = 0; kw < 3; ++kw) acc[set][kh][kw] = dot2_bf16(d[kh], e[kw], acc[set][kh][kw]);
+            }
+            d[2] = d[1]; d[1] = d[0];
+        };
+        const int steps = rows + 2, tb = min(rows, g.H + 1 - oh0);         // steps [1, tb) have both their rows
+        int t = 0;
+        step(t++, std::true_type(), 0);
+#pragma unroll 1
+        for (; t + PD <= tb; t += PD) {
+#pragma unroll
+            for (int i = 0; i < PD; ++i) step(t + i, std::false_type(), i % 2);
+        }
+#pragma unroll 1
+        for (; t < tb; ++t) step(t, std::false_type(), 0);
+        for (; t < steps; ++t) step(t, std::true_type(), 0);
+        __syncthreads();
+    }
+    add_columns<3, 2>(acc, reinterpret_cast<float *>(smem), ws + (size_t)part * g.O * 9, np, ncol, o0);
+}
+
+// ---------------------------------------------------------------------------------------------
 // Whole backward pass, 3x3 "same" stride 1, multiplier 1: the input gradient and stage 1 of the filter gradient from one walk over x and
 // dy.  Blocks and items of the filter gradient; the dy bands with their halo rows go to LDS, a lane reads x only in its own column, a few
 // rows ahead.  The 3x3 window of dy around (row t, column c) gives dx[t][c] and, its middle row against x rows t - 1, t and t + 1 of
@@ -836,6 +926,10 @@ bool conv_pairs(const Geom &g, int dtype, bool bwd)
            (long long)g.N * g.O * (g.W / 2) >= 32768;
 }
 
+// Whether k_nchwf_bwd_filter_pairs does: wider rows, whose planes are bands with dy in LDS beside them or few rows (38x38x256 batch 64, whole planes
+// and dy read by the lanes: 27.5 -> 32.6; 50x50x300 batch 16 20.6 -> 20.7).
+bool filter_pairs(const Geom &g, int dtype) { return conv_pairs(g, dtype, false) && g.W >= 64; }
+
 bool conv_tile(const Geom &g, int dtype, bool bwd, FlatTile *ft)
 {
     const int esz = dtype == DT_F32 ? 4 : 2, nc = conv_pairs(g, dtype, bwd) ? 2 : flat_cols(g, dtype), cols = ((bwd ? g.W : g.Wo) + nc - 1) / nc;
@@ -868,7 +962,7 @@ constexpr int filter_sets(int K, bool dylds) { return K == 3 || (K == 5 && dylds
 template <typename T, int K, int S> constexpr bool DY_LDS = K == 3 ? sizeof(T) == 2 || S == 2 : K == 5 && S == 1 && sizeof(T) == 4;
 bool filter_tile(const Geom &g, int dtype, FlatTile *ft)
 {
-    const int esz = dtype == DT_F32 ? 4 : 2, nc = flat_cols(g, dtype), cols = (g.Wo + nc - 1) / nc;
+    const int esz = dtype == DT_F32 ? 4 : 2, nc = filter_pairs(g, dtype) ? 2 : flat_cols(g, dtype), cols = (g.Wo + nc - 1) / nc;
     auto in_rows = [&](int t) { return (t - 1) * g.s + g.K; };
     auto pick = [&](bool second) {
         return pick_tile(esz, cols, g.Ho, g.O, most_planes((long long)g.N * g.O, g.Ho, cols), g.H, g.W, g.Ho, g.Wo, in_rows, 1, g.m, lds_target(g.K), ft, g.N, LEAST_FILTER_BAND, second);
@@ -990,6 +1084,13 @@ static hipError_t filter_go(const Geom &g, int dtype, const void *x, const void 
     size_t lds = tile_lds(ft, sizeof(T)) + (ft.pout ? (size_t)second_area(ft) * sizeof(T) : 0);
     const size_t red = (size_t)(K * K <= 25 ? K * K : 25) * ft.threads * 4;
     if (red > lds) lds = red;
+    if constexpr (sizeof(T) == 2 && K == 3 && S == 1) {
+        if (filter_pairs(g, dtype)) {
+            auto pairs = ft.pout ? k_nchwf_bwd_filter_pairs<true> : k_nchwf_bwd_filter_pairs<false>;
+            hipLaunchKernelGGL(pairs, dim3(nblocks), dim3(ft.threads), lds, st, g, (const T *)x, (const T *)dy, ws, parts, per, ft, nblocks);
+            return hipGetLastError();
+        }
+    }
     constexpr int NC = K > 3 && sizeof(T) == 2 ? 2 : 1;
     constexpr int SETS = filter_sets(K, false), SETS_LDS = filter_sets(K, true);
     auto kernel = g.p == K / 2 ? k_nchwf_bwd_filter<T, K, S, true, NC, false, SETS> : k_nchwf_bwd_filter<T, K, S, false, NC, false, SETS>;
