@@ -782,7 +782,7 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_fused(Geom g, const T *__rest
             for (int kh = 0; kh < 3; ++kh)
 #pragma unroll
                 for (int kw = 0; kw < 3; ++kw) {
-                    s = fmaf(wr[kh][kw], d[2 - kh][2 - kw], s);
+                    s = fmaf(wr[2 - kh][2 - kw], d[kh][kw], s);       // in the order of the separate pass
                     acc[set][kh][kw] = fmaf(d[1][2 - kw], xw[kh], acc[set][kh][kw]);
                 }
             store_one<T>(vout, s, off, (uint32_t)((oh0 + t) * W) * (uint32_t)sizeof(T));
