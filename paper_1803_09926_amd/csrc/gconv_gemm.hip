@@ -399,11 +399,12 @@ template <typename T, bool NHWC, bool BWD> struct FilterLoader {
     float rnvr, rX;
     unsigned first;          // element that the first vector starts at
 
-    // NHWC backward needs quads inside a group, NCHW at least a vector's entries for a pair of channels and a whole last vector.
+    // NHWC backward needs quads inside a group, NCHW at least a vector's entries for a pair of channels and a whole last vector: of the
+    // filter forward, of every group backward (whose first vector starts where the group does).
     static __device__ __forceinline__ bool takes(const GemmGeom &g)
     {
         const int KK = g.K * g.K;
-        return NHWC ? !BWD || g.Cgi % 4 == 0 : KK >= VE && (unsigned)(g.FO * g.FCg * KK) % VE == 0;
+        return NHWC ? !BWD || g.Cgi % 4 == 0 : KK >= VE && (unsigned)((BWD ? g.Cgi : g.FO) * g.FCg * KK) % VE == 0;
     }
 
     const int *slots;        // where a tap's entries go (null: in order)
@@ -1045,7 +1046,7 @@ StageGeom stage_geom(int layout, int VE, int TN, int LH, int LW, int CL, int pit
     const int most = 256 / s.nv > 0 ? 256 / s.nv : 1, passes = cdivg(width, most);
     s.cols = cdivg(width, passes);
     s.per = s.cols * s.nv;
-    s.RPI = 256 / s.per;
+    s.RPI = s.per <= 256 ? 256 / s.per : 1;                                 // (more items a pixel than lanes: not FAST)
     s.nrit = cdivg(s.rows, s.RPI);
     s.iters = s.nrit * passes;
     s.rper = 1.0f / (float)s.per; s.rnv = 1.0f / (float)s.nv; s.rLH = 1.0f / (float)LH; s.rimrows = 1.0f / (float)s.imrows;
@@ -1167,6 +1168,9 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
                inpix * g.CI * esz < 1ll << 31 && outpix * g.CO * esz < 1ll << 31 && (long long)g.tn * g.ta * g.tb < 1 << 21;
     pl->sg = stage_geom(layout, VE, g.TN, g.LH, g.LW, g.CL, g.pitch, g.Wi);
     if (pass == 2) pl->sy = stage_geom(layout, VE, g.TN, g.TA, g.TB, pl->CLy, pl->pitchy, g.Wo);
+    // as many lanes as a pixel has vectors; four elements for the unaligned loads of the NCHW staging
+    pl->fast = pl->fast && pl->sg.per <= 256 && (pass < 2 || pl->sy.per <= 256) && (long long)g.N * g.CI * g.Hi * g.Wi >= 4 &&
+               (long long)g.N * g.CO * g.Ho * g.Wo >= 4;
     pl->g = g;
     return true;
 }

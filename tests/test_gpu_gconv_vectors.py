@@ -32,6 +32,9 @@ CASES = [
     ("few_positions", 2, 512, 512, 32, 3, 4, 3, 1, 1),             # fewer 16-position tiles than wavefronts
     ("one_pair", 5, 16, 16, 1, 29, 27, 3, 1, 1),                   # filter gradient: four position splits of one pair
     ("wide", 1, 16, 16, 1, 9, 300, 3, 1, 1),                       # more columns than lanes of a row
+    ("lds_over_140k", 1, 32, 32, 1, 28, 28, 7, 1, 3),              # fp32: one block on a compute unit
+    ("one_input", 1, 2, 2, 1, 1, 1, 3, 1, 20),                     # two input elements: no four to load at once
+    ("odd_groups", 2, 24, 40, 8, 13, 15, 3, 1, 1),                 # a group's filter is no whole number of vectors
     ("tail", 1, 20, 20, 5, 37, 35, 3, 1, 1),                       # a run of four passes the tensor's end
 ]
 
@@ -45,7 +48,7 @@ def test_vectors_pairs_and_large_filters(case, layout, dtype):
     names = [dw.gconv_variant_name(d, i) for i in range(3)]
     print("case", name, layout, dtype, names, flush=True)
     if "rowwalk" not in names[0]:
-        assert names[0] == "group_mfma16" and names[1] == "group_mfma16_bwd_data"
+        assert names[0] == "group_mfma16" and (names[1] == "group_mfma16_bwd_data" or N * C * H * W < 2048)      # (few outputs: one per thread)
     x, w, dy = wl.make_group_inputs(N, C, O, G, H, W, K, s, p, layout, dtype, seed=91)
     y, dx, dwt = run_gpu(case, layout, dtype, x, w, dy)
     kw = dict(K=K, stride=s, pad=p, groups=G, O=O, layout=layout, nthreads=8)
