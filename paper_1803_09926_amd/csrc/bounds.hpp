@@ -6,6 +6,11 @@ namespace dwc {
 // Whether the ve elements from a on lie inside a tensor of `total` elements; a + ve may be 2^31 and more.
 constexpr bool vector_inside(int a, int ve, int total) { return a <= total - ve; }
 
+// Four elements from p on are read from run_start(p, total) on, so that the read stays inside a tensor of total >= 4 elements wherever p lies in
+// it; they are then the ones from element p - run_start of the read on.  runs_past: whether that is not 0 for some p before `end`.
+constexpr unsigned run_start(unsigned p, unsigned total) { return p < total - 4 ? p : total - 4; }
+constexpr bool runs_past(unsigned end, unsigned total) { return end > total - 3; }
+
 // ceil(a / b) for a >= 1, b >= 1 (a + b - 1 may be 2^31 and more)
 constexpr int cdiv(int a, int b) { return (a - 1) / b + 1; }
 

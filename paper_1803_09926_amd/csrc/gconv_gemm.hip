@@ -21,6 +21,7 @@
 // 24.9 / 31.5 / 21.8 -> 16.4 / 22.8 / 18.6; 57x57x128, 4 channels a group, fp32 NCHW batch 64 151 / 144 / 151 -> 116 / 134 / 116 (there 3 of 4
 // products are zeros: 49 us of matrix instructions a pass).  A tile may take more than 64 KiB of LDS where the filter does: 28x28x512, 32
 // channels a group at stride 2, fp32 NCHW batch 16, forward 83 -> 33.
+#include "bounds.hpp"
 #include "gconv.hpp"
 #include <type_traits>
 
@@ -269,12 +270,12 @@ template <typename T, int BT> struct Stager<T, false, BT> {
         r = it * sg.RPI + rsub;
         return rsub < sg.RPI && r < sg.rows && run * 4 < W;
     }
-    // `in` at image 0 of nimg, `end` elements of the tensor from there
-    __device__ __forceinline__ void load(const StageGeom &sg, const T *__restrict__ in, unsigned end, int nimg, int C, int H, int W, int h0, int ca,
-                                         int it0)
+    // nimg images from element `first` of `in` on, a tensor of `total` elements (four and more, below 2^31)
+    __device__ __forceinline__ void load(const StageGeom &sg, const T *__restrict__ in, unsigned first, unsigned total, int nimg, int C, int H, int W,
+                                         int h0, int ca, int it0)
     {
         const unsigned plane = (unsigned)(H * W);
-        const bool last = W % 4 && end <= (unsigned)(nimg * C) * plane;        // a run may pass the tensor's end
+        const bool past = W % 4 && runs_past(first + (unsigned)(nimg * C) * plane, total);        // of this tile or, up to two elements, the ones behind
 #pragma unroll
         for (int b = 0; b < BT; ++b) {
             if (it0 + b >= sg.iters) break;
@@ -285,7 +286,7 @@ template <typename T, int BT> struct Stager<T, false, BT> {
             h += h0;
             const int c = ca + qd * 4;
             ok = ok && im < nimg && (unsigned)h < (unsigned)H && c < C;
-            unsigned p0 = (unsigned)(im * C + c) * plane + (unsigned)(h * W + run * 4);
+            unsigned p0 = first + (unsigned)(im * C + c) * plane + (unsigned)(h * W + run * 4);
 #pragma unroll
             for (int k = 0; k < 4; ++k)
 #pragma unroll
@@ -295,9 +296,9 @@ template <typename T, int BT> struct Stager<T, false, BT> {
 #pragma unroll
                 for (int k = 0; k < 4; ++k, p0 += c + k < C ? plane : 0u) {
                     // any alignment; a run that passes the row's end reads the elements behind it, at the tensor's end those before it
-                    const unsigned at = min(p0, end - 4);
+                    const unsigned at = run_start(p0, total);
                     __builtin_memcpy(&e[b][k], in + at, 4 * sizeof(T));
-                    if (last) e[b][k] = later(e[b][k], (int)(p0 - at));
+                    if (past) e[b][k] = later(e[b][k], (int)(p0 - at));
                 }
             }
         }
@@ -557,9 +558,8 @@ __global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg,
             int n0, a0, b0;
             tile_at(tile, n0, a0, b0);
             const int nimg = min(g.TN, g.N - n0), h0 = IS * a0 - g.ip + g.lo, w0 = IS * b0 - g.ip + g.lo;
-            const T *p = in + (size_t)n0 * imin;
-            if constexpr (NHWC) stager.load(sg, BufView(p, (uint32_t)nimg * imin * (uint32_t)sizeof(T)), nimg, g.CI, g.Hi, g.Wi, h0, w0, ca, it0);
-            else stager.load(sg, p, (unsigned)(g.N - n0) * imin, nimg, g.CI, g.Hi, g.Wi, h0, ca, it0);
+            if constexpr (NHWC) stager.load(sg, BufView(in + (size_t)n0 * imin, (uint32_t)nimg * imin * (uint32_t)sizeof(T)), nimg, g.CI, g.Hi, g.Wi, h0, w0, ca, it0);
+            else stager.load(sg, in, (unsigned)n0 * imin, (unsigned)g.N * imin, nimg, g.CI, g.Hi, g.Wi, h0, ca, it0);
         }
     };
 
@@ -830,15 +830,13 @@ __global__ __launch_bounds__(256, K > 3 ? 2 : sizeof(T) == 4 ? 3 : 4) void k_gco
     [[maybe_unused]] Stager<T, NHWC, BT> stx(sx), sty(sy);
     auto load_x = [&](int n0, int a0, int b0, int it0) {
         const int nimg = min(g.TN, g.N - n0), h0 = g.IS * a0 - g.ip, w0 = g.IS * b0 - g.ip;
-        const T *p = x + (size_t)n0 * imx;
-        if constexpr (NHWC) stx.load(sx, BufView(p, (uint32_t)nimg * imx * (uint32_t)sizeof(T)), nimg, g.CI, g.Hi, g.Wi, h0, w0, cxa, it0);
-        else stx.load(sx, p, (unsigned)(g.N - n0) * imx, nimg, g.CI, g.Hi, g.Wi, h0, cxa, it0);
+        if constexpr (NHWC) stx.load(sx, BufView(x + (size_t)n0 * imx, (uint32_t)nimg * imx * (uint32_t)sizeof(T)), nimg, g.CI, g.Hi, g.Wi, h0, w0, cxa, it0);
+        else stx.load(sx, x, (unsigned)n0 * imx, (unsigned)g.N * imx, nimg, g.CI, g.Hi, g.Wi, h0, cxa, it0);
     };
     auto load_y = [&](int n0, int a0, int b0, int it0) {
         const int nimg = min(g.TN, g.N - n0);
-        const T *p = dy + (size_t)n0 * imy;
-        if constexpr (NHWC) sty.load(sy, BufView(p, (uint32_t)nimg * imy * (uint32_t)sizeof(T)), nimg, g.CO, g.Ho, g.Wo, a0, b0, cya, it0);
-        else sty.load(sy, p, (unsigned)(g.N - n0) * imy, nimg, g.CO, g.Ho, g.Wo, a0, cya, it0);
+        if constexpr (NHWC) sty.load(sy, BufView(dy + (size_t)n0 * imy, (uint32_t)nimg * imy * (uint32_t)sizeof(T)), nimg, g.CO, g.Ho, g.Wo, a0, b0, cya, it0);
+        else sty.load(sy, dy, (unsigned)n0 * imy, (unsigned)g.N * imy, nimg, g.CO, g.Ho, g.Wo, a0, cya, it0);
     };
     if constexpr (FAST) {
         int n0, a0, b0;

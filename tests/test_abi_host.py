@@ -261,6 +261,50 @@ int main()
     assert subprocess.call([str(exe)]) == 0
 
 
+def test_runs_of_four_at_the_end_of_a_tensor(tmp_path):
+    """The NCHW staging of the 16x16 group kernels reads runs of four elements of a row, tile of images by tile of images: run for run over
+    small tensors, images of one to a few elements among them, every read stays inside the tensor and every element of a row arrives, also in a
+    tile that others of fewer than three elements follow."""
+    src = tmp_path / "runs.cpp"
+    src.write_text(r"""
+#include "bounds.hpp"
+#include <vector>
+using namespace dwc;
+int main()
+{
+    for (int N = 1; N <= 9; ++N)
+        for (int C = 1; C <= 5; ++C)
+            for (int H = 1; H <= 3; ++H)
+                for (int W = 1; W <= 9; ++W)
+                    for (int TN = 1; TN <= N; ++TN) {
+                        const unsigned total = N * C * H * W, plane = H * W;
+                        if (total < 4) continue;
+                        std::vector<int> t(total);
+                        for (unsigned i = 0; i < total; ++i) t[i] = (int)i + 1;
+                        for (int n0 = 0; n0 < N; n0 += TN) {
+                            const int nimg = TN < N - n0 ? TN : N - n0;
+                            const unsigned first = n0 * C * plane;
+                            const bool past = W % 4 && runs_past(first + nimg * C * plane, total);
+                            for (unsigned row = 0; row < (unsigned)(nimg * C * H); ++row)
+                                for (int run = 0; run * 4 < W; ++run) {
+                                    const unsigned p = first + row * W + run * 4, at = run_start(p, total);
+                                    if (at > total - 4) return 1;
+                                    for (unsigned j = 0; j < 4 && run * 4 + (int)j < W; ++j) {
+                                        const unsigned k = past ? j + (p - at) : j;
+                                        if (k > 3 || t[at + k] != (int)(p + j) + 1) return 2;
+                                    }
+                                }
+                        }
+                    }
+    const unsigned most = (1u << 31) - 1;
+    return run_start(most - 1, most) == most - 4 && !runs_past(most - 3, most) && runs_past(most, most) ? 0 : 3;
+}
+""")
+    exe = tmp_path / "runs"
+    subprocess.check_call(["g++", "-std=c++17", "-I", os.path.join(os.path.dirname(dw.__file__), "csrc"), str(src), "-o", str(exe)])
+    assert subprocess.call([str(exe)]) == 0
+
+
 def test_launches_of_2_32_lanes_stay_with_the_generic_kernels():
     """Many tiny images: the walks start whole wavefronts for each image, and the runtime refuses a launch of 2^32 lanes.  The generic kernels
     start one lane per output, so these shapes still run."""

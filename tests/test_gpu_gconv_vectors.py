@@ -34,6 +34,8 @@ CASES = [
     ("wide", 1, 16, 16, 1, 9, 300, 3, 1, 1),                       # more columns than lanes of a row
     ("lds_over_140k", 1, 32, 32, 1, 28, 28, 7, 1, 3),              # fp32: one block on a compute unit
     ("one_input", 1, 2, 2, 1, 1, 1, 3, 1, 20),                     # two input elements: no four to load at once
+    ("one_input_301", 301, 2, 1024, 1, 1, 1, 5, 1, 4),             # images of two elements: a tile of one image behind the others
+    ("one_pixel", 65537, 2, 64, 1, 1, 1, 1, 1, 0),                 # the same with many images a tile, all passes
     ("odd_groups", 2, 24, 40, 8, 13, 15, 3, 1, 1),                 # a group's filter is no whole number of vectors
     ("tail", 1, 20, 20, 5, 37, 35, 3, 1, 1),                       # a run of four passes the tensor's end
 ]
@@ -56,3 +58,25 @@ def test_vectors_pairs_and_large_filters(case, layout, dtype):
     gu.assert_close(gu.to_host(y), og.fwd(x, w, **kw), tol, "fwd " + name)
     gu.assert_close(gu.to_host(dx), og.bwd_data(dy, w, x_shape=x.shape, **kw), tol, "bwd_data " + name)
     gu.assert_close(gu.to_host(dwt), og.bwd_filter(x, dy, **kw), gu.TOL_F32_FILTER, "bwd_filter " + name)
+
+
+# the input gradient alone: images of two and three elements of dy, odd batches; x must come to 2048 elements, y need not
+DY_CASES = [
+    ("dy_of_two", 7, 64, 2, 1, 7, 7, 7, 1, 0),                     # input gradient: two elements of dy an image, an odd batch
+    ("dy_of_two_padded", 9, 64, 2, 1, 5, 5, 7, 1, 1),
+    ("dy_of_three", 9, 64, 3, 1, 7, 7, 7, 1, 0),
+]
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("layout", [wl.NCHW, wl.NHWC], ids=["nchw", "nhwc"])
+@pytest.mark.parametrize("case", DY_CASES, ids=[c[0] for c in DY_CASES])
+def test_input_gradient_of_images_of_few_elements(case, layout, dtype):
+    name, N, C, O, G, H, W, K, s, p = case
+    d = dw.group_desc(N, C, H, W, K, s, p, G, O, layout, dtype)
+    print("case", name, layout, dtype, dw.gconv_variant_name(d, 1), flush=True)
+    assert dw.gconv_variant_name(d, 1) == "group_mfma16_bwd_data"
+    x, w, dy = wl.make_group_inputs(N, C, O, G, H, W, K, s, p, layout, dtype, seed=93)
+    _, dx, _ = run_gpu(case, layout, dtype, x, w, dy)
+    ref = og.bwd_data(dy, w, x_shape=x.shape, K=K, stride=s, pad=p, groups=G, O=O, layout=layout, nthreads=8)
+    gu.assert_close(gu.to_host(dx), ref, gu.TOL_F32 if dtype == wl.F32 else gu.TOL_BF16, "bwd_data " + name)
