@@ -400,6 +400,11 @@ template <typename T, bool NHWC, bool BWD> struct FilterLoader {
     float rnvr, rX;
     unsigned first;          // element that the first vector starts at
 
+    // Of the shapes that takes() admits, a block takes vectors where they are no more than its fragments.  Backward a block whose outputs lie in two
+    // groups, or (NCHW) whose outputs of a group are no whole vectors, reads the groups' whole filter, which has no bound (12001 channels
+    // against 256: 27 million entries, beyond what fdiv divides) and keeps the launch waiting: us, such blocks by vectors too -> not, fp32
+    // NCHW 68x266x5x5 to 66 channels, stride 2, 92 -> 33, bf16 NHWC 4x560x5x5 in two groups, 1x1, 36 -> 17; 0.92 to 0.95 of the time at the mean over
+    // random layers of 17 to 300 channels a group.  At half the fragments NCHW is another half per cent shorter and NHWC 1 to 3 longer.
     // NHWC backward needs quads inside a group, NCHW at least a vector's entries for a pair of channels and a whole last vector: of the
     // filter forward, of every group backward (whose first vector starts where the group does).
     static __device__ __forceinline__ bool takes(const GemmGeom &g)
@@ -566,7 +571,8 @@ __global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg,
     load_tile(part, 0);
     // zeros: entries that pair different groups, inputs beside the group, outputs beside the tensor; pixels beside the rows
     Finite<T> wseen;
-    const bool vectors = FAST && FilterLoader<T, NHWC, BWD>::takes(g);
+    const FilterLoader<T, NHWC, BWD> fl(g, ob, slots);
+    const bool vectors = FAST && FilterLoader<T, NHWC, BWD>::takes(g) && fl.nvec <= nfrag;       // (see there)
     if (vectors && g.packed)
         for (int i = threadIdx.x; i < nfrag * 4 / VE; i += 256) reinterpret_cast<u4v_t *>(lw)[i] = u4v_t{0u, 0u, 0u, 0u};
     if (!NHWC && FAST)
@@ -579,7 +585,6 @@ __global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg,
     }
     if (!NHWC || g.packed || OS > 1) __syncthreads();
     if (vectors) {
-        const FilterLoader<T, NHWC, BWD> fl(g, ob, slots);
 #pragma unroll 1
         for (int i0 = threadIdx.x; i0 - (int)threadIdx.x < fl.nvec; i0 += 512) {
             const u4raw_t q0 = fl.load(w, i0), q1 = fl.load(w, i0 + 256);

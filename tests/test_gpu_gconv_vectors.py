@@ -60,18 +60,23 @@ def test_vectors_pairs_and_large_filters(case, layout, dtype):
     gu.assert_close(gu.to_host(dwt), og.bwd_filter(x, dy, **kw), gu.TOL_F32_FILTER, "bwd_filter " + name)
 
 
-# the input gradient alone: images of two and three elements of dy, odd batches; x must come to 2048 elements, y need not
+# the input gradient alone: images of two and three elements of dy, odd batches; x must come to 2048 elements, y need not.  Then blocks whose
+# outputs lie in two groups or are no whole vectors, which lay out the filter entry by entry beside others that take vectors.
 DY_CASES = [
     ("dy_of_two", 7, 64, 2, 1, 7, 7, 7, 1, 0),                     # input gradient: two elements of dy an image, an odd batch
     ("dy_of_two_padded", 9, 64, 2, 1, 5, 5, 7, 1, 1),
     ("dy_of_three", 9, 64, 3, 1, 7, 7, 7, 1, 0),
+    ("cg100", 3, 200, 200, 2, 9, 11, 3, 1, 1),
+    ("cg100_s2", 2, 200, 96, 2, 14, 13, 3, 2, 1),
+    ("cg131", 2, 131, 24, 1, 9, 8, 5, 1, 2),                       # NCHW: the last block has three outputs
+    ("cg36", 2, 144, 144, 4, 8, 9, 3, 1, 1),
 ]
 
 
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("layout", [wl.NCHW, wl.NHWC], ids=["nchw", "nhwc"])
 @pytest.mark.parametrize("case", DY_CASES, ids=[c[0] for c in DY_CASES])
-def test_input_gradient_of_images_of_few_elements(case, layout, dtype):
+def test_input_gradient_alone(case, layout, dtype):
     name, N, C, O, G, H, W, K, s, p = case
     d = dw.group_desc(N, C, H, W, K, s, p, G, O, layout, dtype)
     print("case", name, layout, dtype, dw.gconv_variant_name(d, 1), flush=True)
@@ -80,3 +85,16 @@ def test_input_gradient_of_images_of_few_elements(case, layout, dtype):
     _, dx, _ = run_gpu(case, layout, dtype, x, w, dy)
     ref = og.bwd_data(dy, w, x_shape=x.shape, K=K, stride=s, pad=p, groups=G, O=O, layout=layout, nthreads=8)
     gu.assert_close(gu.to_host(dx), ref, gu.TOL_F32 if dtype == wl.F32 else gu.TOL_BF16, "bwd_data " + name)
+
+
+def test_input_gradient_whose_filter_has_27_million_entries():
+    """12001 channels are 750 blocks of 16 outputs and one of one output, whose 256 x 9 entries are no run of the filter."""
+    N, C, O, H = 2, 12001, 256, 7
+    case = ("large_filter", N, C, O, 1, H, H, 3, 1, 1)
+    d = dw.group_desc(N, C, H, H, 3, 1, 1, 1, O, wl.NCHW, wl.BF16)
+    print("case large_filter", dw.gconv_variant_name(d, 1), flush=True)
+    assert dw.gconv_variant_name(d, 1) == "group_mfma16_bwd_data"
+    x, w, dy = wl.make_group_inputs(N, C, O, 1, H, H, 3, 1, 1, wl.NCHW, wl.BF16, seed=94)
+    _, dx, _ = run_gpu(case, wl.NCHW, wl.BF16, x, w, dy)
+    ref = og.bwd_data(dy, w, x_shape=x.shape, K=3, stride=1, pad=1, groups=1, O=O, layout=wl.NCHW, nthreads=8)
+    gu.assert_close(gu.to_host(dx), ref, gu.TOL_BF16, "bwd_data")
