@@ -1365,9 +1365,11 @@ int nchwd_vec(const Geom &g, int dtype, int pass)
 // Multiplier 2, 3x3: one lane walks a plane of x once for both of its outputs, where that leaves 1024 wavefronts.
 // (Outputs the same, fewer loads of x: 56x56x256 fp32 batch 32 forward 55 -> 47 us, filter gradient, from 1024 blocks on, 81 -> 71; 36x36x128 batch 64
 // 26.4 -> 23.9, 28x28x128 batch 32 11.3 -> 9.7; bf16 56x56x256 32.8 -> 30.5; 112x112x64 batch 16 ties.)
-static bool both_outputs(const Geom &g, int V, int TH)
+// Not for fp32 rows of one vector that every lane stores by itself (not `lines`): neighbouring lanes are two planes apart there, and a store
+// leaves more lines half written (19x4x438 batch 97 18 -> 31 us, 90x4x474 batch 46 39 -> 63; with heights of whole row groups 0.8 of the time).
+static bool both_outputs(const Geom &g, int esz, int V, int TH, bool lines)
 {
-    return g.m == 2 && (long long)g.N * g.C * ceil_div_h(g.H, TH) * (g.W / V) >= 65536;
+    return g.m == 2 && (lines || esz == 2 || g.W > V) && (long long)g.N * g.C * ceil_div_h(g.H, TH) * (g.W / V) >= 65536;
 }
 
 template <typename T, int V, int K>
@@ -1375,12 +1377,13 @@ static hipError_t go_s1(const Geom &g, const void *x, const void *w, void *y, bo
 {
     const long long out_bytes = (long long)g.N * g.O * g.H * g.W * sizeof(T);
     constexpr int BOTH = K == 3 ? 2 : 1;
-    const bool both = K == 3 && !flip && both_outputs(g, V, TH);
+    // whole-line write-out, streamed: rows grouped so that a group is a whole number of lines
+    const int rs = row_group(g.W, (int)sizeof(T));
+    const bool lines = sizeof(T) * V == 16 && rs >= 2 && g.H % rs == 0 && stream_stores(flip ? "NCHW_S1_BWD" : "NCHW_S1_FWD", out_bytes, 0);
+    const bool both = K == 3 && !flip && both_outputs(g, (int)sizeof(T), V, TH, lines);
     const int nch = both ? g.C : g.O;
     if constexpr (sizeof(T) * V == 16) {
-        // whole-line write-out, streamed: rows grouped so that a group is a whole number of lines
-        const int rs = row_group(g.W, (int)sizeof(T));
-        if (rs >= 2 && g.H % rs == 0 && stream_stores(flip ? "NCHW_S1_BWD" : "NCHW_S1_FWD", out_bytes, 0)) {
+        if (lines) {
             TH = (TH + rs - 1) / rs * rs;
             const int nstrips = ceil_div_h(g.H, TH);
             const long long lanes = (long long)g.N * nch * nstrips * (g.W / V);
