@@ -1014,6 +1014,22 @@ template <typename F> bool widest_tile(F tile, int from, int to, int most, size_
     return false;
 }
 
+// 16-position tiles that a wavefront computes at a time (P of k_gconv_gemm), of a tile of npos positions and NS output blocks.  Four share a read of the
+// filter, but only from 256 positions and output blocks on is there work for all four wavefronts of a block that way: at 128 half of them are idle.
+// So, the shortest longest wavefront: cycles of its matrix instructions, of the LDS reads of all four, and of the loop.  (us, four at a time from 80
+// on -> this: 30x492x19x19 in 41 groups, 7x7, fp32 NCHW input gradient 221 -> 138; 26x832x14x14 in 13 groups, fp32 NCHW forward 137 -> 87; random
+// layers 0.94 of the time at the mean in fp32, 0.98 in bf16.  One or four at a time, without two, 0.96 and 1.02.)
+int tiles_at_once(int NS, int npos, int dtype)
+{
+    const int tiles16 = cdivg(npos, 16), mfma = dtype == DT_F32 ? 128 : 16, read = dtype == DT_F32 ? 32 : 16, loop = 40;
+    int best = 1, least = 1 << 30;
+    for (int P = 1; P <= 4; P *= 2) {
+        const int cycles = cdivg(NS * cdivg(tiles16, P), 4) * (P * mfma + (1 + P) * read + loop);
+        if (cycles < least) { least = cycles; best = P; }
+    }
+    return best;
+}
+
 // positions of a tile: whole rows where they fit, several images of a small map; a row of a multiple of `quad` positions, so that
 // four of them have consecutive outputs
 void pick_positions(GemmGeom &g, int want, int maxb, int quad = 1)
@@ -1211,7 +1227,7 @@ double gconv_gemm_us(const GGeom &q, int layout, int dtype, int pass)
     if (!gemm_plan(q, layout, dtype, pass, &pl)) return 1e30;
     const GemmGeom &g = pl.g;
     const float *c = fit[pass][layout == LAYOUT_NHWC][dtype != DT_F32][pl.fast];
-    const int tiles = cdivg(g.tn * g.ta * g.tb, pl.nparts), tiles16 = cdivg(g.TN * g.TA * g.TB, 16), P = tiles16 * g.NS > 4 ? 4 : 1;
+    const int tiles = cdivg(g.tn * g.ta * g.tb, pl.nparts), tiles16 = cdivg(g.TN * g.TA * g.TB, 16), P = tiles_at_once(g.NS, g.TN * g.TA * g.TB, dtype);
     const double resident = resident_blocks(pl.lds, 4), cu = pl.nblocks / 256.0;
     const double rounds = pl.nblocks > resident ? pl.nblocks / resident : 1.0, beside = cu < 1 ? 1 : cu > resident / 256 ? resident / 256 : cu;
     const double staging = (double)g.TN * g.LH * g.LW * g.CL * (dtype == DT_F32 ? 4 : 2) / 4096;
@@ -1239,8 +1255,6 @@ template <typename T, bool NHWC>
 static hipError_t gemm_go(const GemmPlan &pl, const void *in, const void *w, void *out, hipStream_t st)
 {
     constexpr bool NCHW = !NHWC;
-    // four 16-position tiles at a time where that leaves every wavefront some
-    const int tiles16 = cdivg(pl.g.TN * pl.g.TA * pl.g.TB, 16) * pl.g.NS;
     auto pick = [&](auto p) {
         constexpr int P = decltype(p)::value;
         return !pl.g.bwd ? (pl.fast ? k_gconv_gemm<T, NHWC, false, true, P, 1, false> : k_gconv_gemm<T, NHWC, false, false, P, 1, false>)
@@ -1248,7 +1262,8 @@ static hipError_t gemm_go(const GemmPlan &pl, const void *in, const void *w, voi
                : pl.g.OS > 1 ? (pl.fast ? k_gconv_gemm<T, NHWC, true, true, P, 1, NCHW> : k_gconv_gemm<T, NHWC, true, false, P, 1, NCHW>)
                : pl.fast ? k_gconv_gemm<T, NHWC, true, true, P, 1, false> : k_gconv_gemm<T, NHWC, true, false, P, 1, false>;
     };
-    auto kernel = tiles16 > 4 ? pick(std::integral_constant<int, 4>()) : pick(std::integral_constant<int, 1>());
+    const int P = tiles_at_once(pl.g.NS, pl.g.TN * pl.g.TA * pl.g.TB, sizeof(T) == 4 ? DT_F32 : DT_BF16);
+    auto kernel = P == 4 ? pick(std::integral_constant<int, 4>()) : P == 2 ? pick(std::integral_constant<int, 2>()) : pick(std::integral_constant<int, 1>());
     hipLaunchKernelGGL(kernel, dim3(pl.nblocks), dim3(256), pl.lds, st, pl.g, pl.sg, (const T *)in, (const T *)w, (T *)out,
                        pl.nparts, pl.nblocks);
     return hipGetLastError();

@@ -98,3 +98,21 @@ def test_input_gradient_whose_filter_has_27_million_entries():
     _, dx, _ = run_gpu(case, wl.NCHW, wl.BF16, x, w, dy)
     ref = og.bwd_data(dy, w, x_shape=x.shape, K=3, stride=1, pad=1, groups=1, O=O, layout=wl.NCHW, nthreads=8)
     gu.assert_close(gu.to_host(dx), ref, gu.TOL_BF16, "bwd_data")
+
+
+# launches of about 200 blocks and more whose tiles have 65 to 128 positions and output blocks: a wavefront takes two 16-position tiles at a time
+TWO_AT_ONCE = [
+    ("g12_16x23", 12, 96, 96, 12, 16, 23, 3, 1, 1),
+    ("g12_13x5", 12, 384, 384, 12, 13, 5, 3, 1, 1),                # two output blocks
+    ("g8_10x13", 8, 256, 256, 8, 10, 13, 3, 1, 1),
+    ("g11_23x11", 12, 88, 88, 11, 23, 11, 3, 1, 1),                # 16 outputs span groups of 8
+    ("g6_s2", 11, 192, 192, 6, 20, 21, 3, 2, 1),
+    ("g5_s2", 12, 160, 160, 5, 23, 22, 3, 2, 1),
+]
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("layout", [wl.NCHW, wl.NHWC], ids=["nchw", "nhwc"])
+@pytest.mark.parametrize("case", TWO_AT_ONCE, ids=[c[0] for c in TWO_AT_ONCE])
+def test_two_tiles_at_once(case, layout, dtype):
+    test_vectors_pairs_and_large_filters(case, layout, dtype)
