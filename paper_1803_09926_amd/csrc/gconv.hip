@@ -250,14 +250,14 @@ static double generic_us(const GGeom &g, int layout, int pass)
 
 // Laying out the filter and staging a tile are a fixed 6 to 15 us, and a filter that takes the LDS leaves small tiles: few products per output
 // and few outputs, or few channels a group with a large filter, are shorter one output per thread.  Of random layers that came here by the
-// estimates from the generic kernels, 2.8 % of the forward passes and 1.2 % of the input gradients are slower by more than 8 % (at the mean
-// 0.47 and 0.28 of the time); the input gradient's generic estimate is the lower of the two by 0.85 at the median.  The filter gradient, whose
+// estimates from the generic kernels, 2.5 % of the forward passes and 1.8 % of the input gradients are slower by more than 8 % (at the mean
+// 0.39 and 0.26 of the time; without a factor 1.5 and 0.8 %, but 3 and 8 % would stay generic that are shorter here by as much).  The filter gradient, whose
 // time here hardly depends on the layer as long as it is short: 1 % either way.
 static bool gemm_over_generic(const GGeom &g, int layout, int dtype, int pass)
 {
     const double generic = generic_us(g, layout, pass);
     if (pass == 2) return generic > (g.K == 1 ? 10.5 : g.K == 3 ? 12.5 : 16.0);
-    return gconv_gemm_us(g, layout, dtype, pass) * (pass == 0 ? 0.95 : 0.85) < generic;
+    return gconv_gemm_us(g, layout, dtype, pass) * (pass == 0 ? 0.95 : 0.9) < generic;
 }
 
 // In place of the NCHW row walk: in fp32 not for the filter gradient of 16 channels a group on many pixels (1.03 times as long at the median of

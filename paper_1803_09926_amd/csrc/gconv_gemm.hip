@@ -998,20 +998,21 @@ int resident_blocks(size_t lds, int most)
 }
 
 // The widest tile (of positions from `from` down to `to`) that fits, as tile(positions) sets it up; half of it where that lets `most`
-// blocks onto a compute unit and it does not.  (14x14 16 channels a group 10.1 us with 256 positions, 13.0 with 128; 28x28 32 channels a
-// group, bf16 NHWC batch 64: 55 us with 256 positions and three blocks, 47 with 128 and four.)
-template <typename F> bool widest_tile(F tile, int from, int to, int most, size_t limit, const size_t *lds)
+// blocks onto a compute unit and it does not.  Returns the positions, 0 if nothing fits.  (14x14 16 channels a group 10.1 us with 256 positions,
+// 13.0 with 128; 28x28 32 channels a group, bf16 NHWC batch 64: 55 us with 256 positions and three blocks, 47 with 128 and four.)
+template <typename F> int widest_tile(F tile, int from, int to, int most, size_t limit, const size_t *lds)
 {
     for (int want = from; want >= to; want /= 2) {
         tile(want);
         if (*lds > limit) continue;
         if (want / 2 >= 64 && resident_blocks(*lds, most) < 256 * most) {
             tile(want / 2);
-            if (resident_blocks(*lds, most) < 256 * most) tile(want);
+            if (resident_blocks(*lds, most) == 256 * most) return want / 2;
+            tile(want);
         }
-        return true;
+        return want;
     }
-    return false;
+    return 0;
 }
 
 // 16-position tiles that a wavefront computes at a time (P of k_gconv_gemm), of a tile of npos positions and NS output blocks.  Four share a read of the
@@ -1091,6 +1092,11 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
     const int reach = pass == 1 ? 1 - g.lo : q.K;                           // input rows of one position
     const int blocks16 = cdivg(g.CO, 16);
     if (pass < 2) {
+        // A launch of few blocks is one short round of them beside idle compute units, each as long as its tile: smaller tiles, down to a
+        // 16-position tile for each wavefront, then one output block a block.  (us: 4x64x9x9 in 2 groups, stride 2, fp32 NCHW input gradient 30 -> 13,
+        // 8x480x21x11 in 15, stride 3, 37 -> 14.6; random layers 0.94 of the time at the mean forward, 0.86 (fp32) and 0.89 (bf16) in the input
+        // gradient, 0.3 % longer by more than 8 %.  Below 128 or 256 blocks 0.5 % longer.)
+        constexpr int FEW = 192;
         // output blocks of 16 per block: two where they read the same input channels (7x7 32 channels a group, batch 64, 1024
         // channels: bf16 NHWC 24 -> 21 us, fp32 NCHW 71 -> 54), otherwise one (14x14 16 channels a group, bf16 NHWC batch 32 15.6 us
         // with two, 14.4 with one; 56x56 24 channels a group 77 against 49)
@@ -1109,9 +1115,13 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
                 pl->lds = (size_t)ns * q.K * q.K * g.nk * 64 * 4 * esz + (size_t)cdivg(g.TN * g.TA * g.TB, 64) * 64 * (g.OS > 1 ? 16 : 8) + (g.OS > 1 ? 256 : 0) + 16 +
                           ((size_t)g.TN * g.LH * g.LW * g.pitch * esz + 15) / 16 * 16;
             };
-            if (widest_tile(tile, 256, 16, 4, LDS_OF_TWO, &pl->lds)) break;
-            if (ns == 1 && widest_tile(tile, 256, 16, 4, LDS_OF_ONE, &pl->lds)) break;
-            if (ns == 1) return false;
+            int want = widest_tile(tile, 256, 16, 4, LDS_OF_TWO, &pl->lds);
+            if (!want && ns == 1) want = widest_tile(tile, 256, 16, 4, LDS_OF_ONE, &pl->lds);
+            if (!want && ns == 1) return false;
+            if (!want) continue;
+            auto few = [&]() { return (long long)g.tn * g.ta * g.tb * cdivg(blocks16, ns) < FEW; };
+            for (; want > 64 && few(); tile(want)) want /= 2;
+            if (ns == 1 || !few()) break;
         }
         g.nchb = cdivg(blocks16, g.NS);
         const long long tiles = (long long)g.tn * g.ta * g.tb;
@@ -1163,7 +1173,7 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
                 const size_t sums = npair < 4 ? (size_t)npair * q.K * q.K * 1024 : 0;
                 if (pl->lds < sums) pl->lds = sums;
             };
-            fits = widest_tile(tile, 256, npair > 1 ? 64 : 16, blocks, LDS_OF_TWO, &pl->lds);
+            fits = widest_tile(tile, 256, npair > 1 ? 64 : 16, blocks, LDS_OF_TWO, &pl->lds) > 0;
             if (fits) break;
         }
         if (!fits) return false;
