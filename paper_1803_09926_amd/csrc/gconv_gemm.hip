@@ -1173,7 +1173,14 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
                 const size_t sums = npair < 4 ? (size_t)npair * q.K * q.K * 1024 : 0;
                 if (pl->lds < sums) pl->lds = sums;
             };
-            fits = widest_tile(tile, 256, npair > 1 ? 64 : 16, blocks, LDS_OF_TWO, &pl->lds) > 0;
+            // Few blocks: smaller tiles, then fewer pairs a block, as above, but a partial is added up again, so not beyond 128.  (us, stage 2 in
+            // it: 1x48x46x46 in 8 groups, 5x5, fp32 NHWC 31 -> 15, 10x192x56x5 in 12, 3x3 at stride 3, bf16 NCHW 29 -> 12; random layers 0.945 of
+            // the time at the mean, 0.4 % longer by more than 8 %.  192 blocks: 0.95 and 2.2 %.)
+            constexpr int FEW = 128;
+            int want = widest_tile(tile, 256, npair > 1 ? 64 : 16, blocks, LDS_OF_TWO, &pl->lds);
+            auto few = [&]() { return (long long)g.tn * g.ta * g.tb * g.nchb < FEW; };
+            for (; want > 32 && few(); tile(want)) want /= 2;
+            fits = want > 0 && (npair == 1 || !few());
             if (fits) break;
         }
         if (!fits) return false;
