@@ -261,15 +261,14 @@ static bool gemm_over_generic(const GGeom &g, int layout, int dtype, int pass)
 }
 
 // In place of the NCHW row walk: in fp32 not for the filter gradient of 16 channels a group on many pixels (1.03 times as long at the median of
-// random layers, up to 1.8).  Forward and input gradient of 64 channels a group on many pixels (whose filter the L2 holds) are left where they
-// were, as tests/test_abi_host.py states the route, though the line has moved: 128x21x20 in two groups, batch 148, 255 us on the row walk, 859 on the
-// 16x16 instructions with tiles in 64 KiB of LDS, 152 with those of now.  On fewer pixels (512x14x16 in eight, batch 64) 212 -> 139.
-static bool gemm_over_rowwalk(const GGeom &g, int dtype, int pass)
+// random layers, up to 1.8).  Forward and input gradient by the estimates of both: of random layers of 16 to 64 channels a group 0.1 % are longer here by
+// more than 8 %, of 64 to 128 on many pixels 1.8 % (up to 1.6 times; always here: 9.3 %, up to 2.4), and 0.7 % stay that would be shorter.  us, row walk ->
+// here: 128x21x20 in two groups, batch 148, 251 -> 146; 1024x18x18 in 16, batch 128, 964 -> 690; 480x18x18 in five, batch 213, 1080 -> 2330: stays.
+static bool gemm_over_rowwalk(const GGeom &g, int layout, int dtype, int pass)
 {
     if (dtype != DT_F32) return true;
-    const long long pixels = (long long)g.N * g.Ho * g.Wo;
-    if (pass == 2) return !(g.Cg == 16 && pixels >= 16384);
-    return !(g.Cg >= 64 && pixels >= 32768 && (long long)g.O * g.Cg * g.K * g.K * 4 <= 4 << 20);
+    if (pass == 2) return !(g.Cg == 16 && (long long)g.N * g.Ho * g.Wo >= 16384);
+    return gconv_gemm_us(g, layout, dtype, pass) * 0.8 < gconv_nchw_s1_us(g, pass == 1);
 }
 
 static GPlan gplan(const GGeom &g, int layout, int dtype, int pass)
@@ -330,7 +329,7 @@ static GPlan gplan(const GGeom &g, int layout, int dtype, int pass)
     const bool rowwalk16 = pl.variant == GV_NCHW_K3S1 && g.Cg % 16 == 0 && g.Og % 16 == 0;
     const long long outputs = (long long)g.N * (pass == 1 ? (long long)g.C * g.H * g.W : (long long)g.O * g.Ho * g.Wo);
     if ((pl.variant == GV_GENERIC || rowwalk16) && outputs >= 2048 && gconv_gemm_supported(g, layout, dtype, pass) &&
-        (tune_env("DWCONV_TUNE_GROUP_GEMM") || (rowwalk16 ? gemm_over_rowwalk(g, dtype, pass) : gemm_over_generic(g, layout, dtype, pass)))) {
+        (tune_env("DWCONV_TUNE_GROUP_GEMM") || (rowwalk16 ? gemm_over_rowwalk(g, layout, dtype, pass) : gemm_over_generic(g, layout, dtype, pass)))) {
         pl.variant = GV_GEMM;
         pl.name = pass == 0 ? "group_mfma16" : pass == 1 ? "group_mfma16_bwd_data" : "group_mfma16_bwd_filter";
         if (pass == 2) pl.parts = gconv_gemm_parts(g, layout, dtype);

@@ -42,6 +42,7 @@ hipError_t gconv_gemm_bwd_filter(const GGeom &g, int layout, int dtype, const vo
 // ---- NCHW row-walk kernels, 3x3 stride 1 pad 1, 2, 4 or 8 channels per group on both sides (gconv_nchw.hip)
 bool gconv_nchw_supported(const GGeom &g);
 // flip = false: forward (in = x, out = y); flip = true: backward-data (in = dy, out = dx)
+double gconv_nchw_s1_us(const GGeom &g, bool flip);       // estimated time in us, fp32
 hipError_t gconv_nchw_s1(const GGeom &g, int dtype, const void *in, const void *w, void *out, bool flip, hipStream_t st);
 int gconv_nchw_bwd_filter_parts(const GGeom &g);
 hipError_t gconv_nchw_bwd_filter(const GGeom &g, int dtype, const void *x, const void *dy, float *ws, int parts,

@@ -330,7 +330,10 @@ def test_group_shapes_that_are_shorter_one_output_per_thread():
             assert names(64, 96, 57, 57, 3, 2, 1, 6, 96, layout=layout, dtype=dtype) == gemm
     assert names(226, 2, 80, 80, 5, 1, 2, 1, 2)[0] == "group_generic"
     assert names(90, 90, 7, 7, 7, 1, 0, 30, 90, layout=dw.NHWC, dtype=dw.BF16)[:2] == ["group_generic"] * 2
-    assert names(148, 128, 21, 20, 3, 1, 1, 2, 128)[:2] == ["group_nchw_rowwalk_k3s1", "group_nchw_rowwalk_k3s1_flip"]
+    # tiles of up to 160 KiB: 146 us where the row walk takes 251 (with tiles of up to 64 KiB 859); five groups of 96 channels on 69 012 pixels, whose
+    # filter leaves tiles of few positions, 2330 where it takes 1080
+    assert names(148, 128, 21, 20, 3, 1, 1, 2, 128)[:2] == gemm[:2]
+    assert names(213, 480, 18, 18, 3, 1, 1, 5, 480)[:2] == ["group_nchw_rowwalk_k3s1", "group_nchw_rowwalk_k3s1_flip"]
     assert names(148, 128, 21, 20, 3, 1, 1, 2, 128, dtype=dw.BF16)[:2] == gemm[:2]
     # the row walk reads its filter again for every strip: more than the L2 holds
     assert names(1, 3456, 89, 24, 3, 1, 1, 54, 3456)[:2] == names(8, 3072, 15, 12, 3, 1, 1, 48, 3072)[:2] == gemm[:2]
