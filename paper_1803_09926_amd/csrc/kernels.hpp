@@ -96,7 +96,7 @@ int nchwf_bwd_filter_parts(const Geom &g, int dtype);       // 0 = unsupported
 void nchwf_bwd_filter_tiles(const Geom &g, int dtype, int parts, FilterGradSrc *f);      // what its partials hold
 hipError_t nchwf_bwd_filter(const Geom &g, int dtype, const void *x, const void *dy, float *ws, int parts, hipStream_t st);
 // fused backward (input gradient + stage 1 of the filter gradient), 3x3 "same" stride 1, multiplier 1
-int nchwf_bwd_fused_parts(const Geom &g, int dtype);        // 0 = unsupported
+int nchwf_bwd_fused_parts(const Geom &g, int dtype);        // 0 = unsupported, or the two passes are shorter
 void nchwf_bwd_fused_tiles(const Geom &g, int dtype, int parts, FilterGradSrc *f);
 hipError_t nchwf_bwd_fused(const Geom &g, int dtype, const void *x, const void *dy, const void *w, void *dx, float *ws, int parts, hipStream_t st);
 

@@ -707,7 +707,9 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_filter_pairs(Geom g, const bf
 // rows ahead.  The 3x3 window of dy around (row t, column c) gives dx[t][c] and, its middle row against x rows t - 1, t and t + 1 of
 // column c, the filter gradient summed per x column: 18 multiply-adds for three LDS reads, one load and one store.
 // The two passes and this one, stage 2 in both, us on one MI355X: 19x19x728 batch 32 fp32 33.5 -> 25.3, bf16 28.3 -> 21.4; 74x74x256 batch 32 162 -> 129 and
-// 96 -> 83; 147x147x96 batch 16 134 -> 104; 10x10x240 batch 128 22.2 -> 16.8; 21x21x32 batch 8 11.3 -> 8.4; no size measured was longer.
+// 96 -> 83 (one column a lane in both; on pairs 89); 147x147x96 batch 16 134 -> 104; 10x10x240 batch 128 22.2 -> 16.8; 21x21x32 batch 8 11.3 -> 8.4.  On
+// rows that neither pass takes in pairs it is 0.76 of the two at the mean of 40 000 random layers, and none was longer by 8 % and a microsecond;
+// for the others see two_passes_shorter.
 // ---------------------------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(512) void k_nchwf_bwd_fused(Geom g, const T *__restrict__ x, const T *__restrict__ dy, const T *__restrict__ w,
@@ -782,7 +784,7 @@ __global__ __launch_bounds__(512) void k_nchwf_bwd_fused(Geom g, const T *__rest
             for (int kh = 0; kh < 3; ++kh)
 #pragma unroll
                 for (int kw = 0; kw < 3; ++kw) {
-                    s = fmaf(wr[2 - kh][2 - kw], d[kh][kw], s);       // in the order of the separate pass
+                    s = fmaf(wr[2 - kh][2 - kw], d[kh][kw], s);       // in the order of the separate pass (one column a lane)
                     acc[set][kh][kw] = fmaf(d[1][2 - kw], xw[kh], acc[set][kh][kw]);
                 }
             store_one<T>(vout, s, off, (uint32_t)((oh0 + t) * W) * (uint32_t)sizeof(T));
@@ -1013,10 +1015,23 @@ int nchwf_bwd_filter_parts(const Geom &g, int dtype)
     return filter_parts(g, ft);
 }
 
+// Where both passes run on column pairs (bf16, an even width from 64 on) and the fused walk, which widens every value, is the longer way: large layers of
+// few rows, whose halo rows it reads twice, unless a row about fills its block of 256 lanes (193 to 256); and rows of just under half a
+// block, whose tall planes leave room for few of those blocks.  Fused / two passes, buffers in turn, 59 000 random layers: 4 million outputs and more, rows
+// of 128 to 192: 1.05 to 1.26 at 4 to 8 rows, 0.88 to 1.17 at 8 to 24, 0.83 to 1.02 beyond; of 258 to 512: 1.06 to 1.33, 0.97 to 1.32, 0.77 to
+// 1.04; of 193 to 256: 0.77 to 1.01; of 64 to 94: 0.79 to 1.07; of 98 to 126: 0.85 to 1.09, from 110 rows on 0.95 to 1.44.  Fewer outputs: 0.70 to
+// 1.0.  By this rule 4.7 % of the layers on pairs stay fused and are longer by more than a twentieth (always fused 15.7 %, up to 1.7 times), 2.0 % run in two
+// passes and are.
+static bool two_passes_shorter(const Geom &g, int dtype)
+{
+    if (!filter_pairs(g, dtype) || !conv_pairs(g, dtype, true) || (long long)g.N * g.O * g.H * g.W < 1 << 22) return false;
+    return (g.H < 24 && g.W >= 128 && (g.W <= 192 || g.W > 256)) || (g.H >= 110 && g.W > 96 && g.W < 128);
+}
+
 int nchwf_bwd_fused_parts(const Geom &g, int dtype)
 {
     FlatTile ft;
-    if (!(g.K == 3 && g.s == 1 && g.p == 1 && g.m == 1) || !fused_tile(g, dtype, &ft)) return 0;
+    if (!(g.K == 3 && g.s == 1 && g.p == 1 && g.m == 1) || two_passes_shorter(g, dtype) || !fused_tile(g, dtype, &ft)) return 0;
     return filter_parts(g, ft);
 }
 void nchwf_bwd_fused_tiles(const Geom &g, int dtype, int parts, FilterGradSrc *f)

@@ -218,6 +218,22 @@ def test_whole_backward_variant_names():
     assert dw.variant_name(dw.desc(256, 128, 56, 56, 5, 1, 2, 1, dw.NHWC, dw.BF16), 3) == "separate"
 
 
+def test_whole_backward_on_column_pairs_keeps_two_passes_where_they_are_shorter():
+    """bf16 rows of an even width from 64 on, which both passes take in pairs: few rows in large layers, and tall planes of rows of just under
+    half a block.  Everything else of any width is fused."""
+    def name(N, C, H, W, dtype=dw.BF16):
+        return dw.variant_name(dw.desc(N, C, H, W, 3, 1, 1, 1, dw.NCHW, dtype), 3)
+    fused = "nchw_flat_bwd_fused_k3s1"
+    assert name(64, 128, 14, 130) == name(64, 64, 14, 300) == name(64, 64, 14, 510) == "separate"
+    assert name(64, 128, 14, 126) == name(64, 64, 14, 194) == name(64, 64, 14, 254) == fused
+    assert name(64, 128, 24, 130) == name(4, 128, 14, 130) == name(64, 128, 14, 131) == name(64, 128, 14, 131, dw.F32) == fused
+    assert name(16, 64, 110, 98) == name(16, 64, 150, 126) == "separate"
+    assert name(16, 64, 109, 98) == name(32, 256, 74, 74) == name(16, 64, 150, 94) == name(16, 64, 150, 130) == fused
+    # the workspace is that of the passes that run
+    d = dw.desc(64, 128, 14, 130, 3, 1, 1, 1, dw.NCHW, dw.BF16)
+    assert dw.bwd_workspace_bytes(d) == dw.bwd_filter_workspace_bytes(d)
+
+
 def test_buffer_view_kernels_stay_within_two_gib_images():
     # the bf16 5x5 NHWC kernels address an image through a 32-bit buffer view: an image above 2 GiB goes to the
     # generic kernels, an image of exactly 2 GiB and every 3x3 shape keep the row walk
