@@ -131,7 +131,7 @@ struct GemmGeom {
     int nchb;              // channel blocks
     int packed;            // output blocks span groups
     int FO, FCg;           // filter dims: output channels, input channels per group (of the forward layer)
-    float rCgi, rCgo, rKK, rnk, rFCg, rTA, rTB, rta, rtb;   // reciprocals for fdiv
+    float rCgi, rCgo, rKK, rnk, rTA, rTB, rta, rtb;         // reciprocals for fdiv
 };
 
 // n / d for 0 <= n < 2^21 and d with reciprocal r = 1.0f / d: the half keeps the product away from the integers by more than
@@ -1196,7 +1196,7 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
         pl->nblocks = (unsigned)(parts * g.nchb);
     }
     g.rCgi = 1.0f / (float)g.Cgi; g.rCgo = 1.0f / (float)g.Cgo; g.rKK = 1.0f / (float)(q.K * q.K); g.rnk = 1.0f / (float)g.nk;
-    g.rFCg = 1.0f / (float)g.FCg; g.rTA = 1.0f / (float)g.TA; g.rTB = 1.0f / (float)g.TB;
+    g.rTA = 1.0f / (float)g.TA; g.rTB = 1.0f / (float)g.TB;
     g.rta = 1.0f / (float)g.ta; g.rtb = 1.0f / (float)g.tb;
     // whole vectors of channels, or whole rows; the images of a tile below 2 GiB and 2^24 pixels, for the staging's offsets and products
     const long long inpix = (long long)g.TN * g.Hi * g.Wi, outpix = (long long)g.TN * g.Ho * g.Wo;
