@@ -130,8 +130,8 @@ int dwconv_bwd_filter_noalloc(const dwconv_desc *desc, const void *x, const void
 /* Whole backward pass of the layer in one call: dx as dwconv_bwd_data, dw as dwconv_bwd_filter
  * (Section III-A, backward propagation: both gradients come from the same dy; the paper's
  * Table III reports them as one "Backward" time).  Where a fused kernel exists (3x3, pad 1,
- * multiplier 1, and multiplier 2 in NHWC at stride 1.  Stride 1: NHWC; NCHW with rows of whole
- * 16-byte vectors; NCHW planes with rows of 4, 7, 8, 14 or 28.  Stride 2: NHWC on even maps;
+ * multiplier 1, and multiplier 2 in NHWC at stride 1.  Stride 1: NHWC; NCHW with rows of up to 512
+ * or of whole 16-byte vectors, except some large bf16 layers whose two passes are shorter.  Stride 2: NHWC on even maps;
  * NCHW on even maps with rows of 56 and more in fp32, 112 and more in bf16; NCHW planes with
  * rows of 8, 14 or 28 and an even height) dy and x are read once and the pass moves
  * 2|x| + |y| elements instead of

@@ -1097,9 +1097,10 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
         // 8x480x21x11 in 15, stride 3, 37 -> 14.6; random layers 0.94 of the time at the mean forward, 0.86 (fp32) and 0.89 (bf16) in the input
         // gradient, 0.3 % longer by more than 8 %.  Below 128 or 256 blocks 0.5 % longer.)
         constexpr int FEW = 192;
-        // output blocks of 16 per block: two where they read the same input channels (7x7 32 channels a group, batch 64, 1024
-        // channels: bf16 NHWC 24 -> 21 us, fp32 NCHW 71 -> 54), otherwise one (14x14 16 channels a group, bf16 NHWC batch 32 15.6 us
-        // with two, 14.4 with one; 56x56 24 channels a group 77 against 49)
+        // output blocks of 16 per block: two where they read the same input channels (us, one -> two: 7x7 32 channels a group, batch 64, 1024
+        // channels, bf16 NHWC 16.1 -> 14.1, fp32 NCHW 39.3 -> 38.7; 28x28x512 batch 64 bf16 NHWC 55.5 -> 45.3), otherwise one (two against one: 14x14x512
+        // 16 channels a group, batch 32, bf16 NHWC 10.6 and 10.2, fp32 NCHW 26.0 and 22.9; 56x56x240 24 channels a group, bf16 NHWC batch 64 187 and
+        // 174; 57x57x128 4 channels a group, fp32 NCHW batch 64 124 and 109)
         int ns = g.Cgo % 32 == 0 ? 2 : 1;
         if (ns > blocks16) ns = blocks16;
         for (;; ns = (ns + 1) / 2) {
