@@ -20,7 +20,7 @@
 // a group, bf16 NHWC batch 32 15.0 / 19.7 / 17.0 -> 9.9 / 14.5 / 10.6; 56x56x256 stride 2, 8 channels a group, bf16 NCHW batch 16
 // 24.9 / 31.5 / 21.8 -> 16.4 / 22.8 / 18.6; 57x57x128, 4 channels a group, fp32 NCHW batch 64 151 / 144 / 151 -> 116 / 134 / 116 (there 3 of 4
 // products are zeros: 49 us of matrix instructions a pass).  A tile may take more than 64 KiB of LDS where the filter does: 28x28x512, 32
-// channels a group at stride 2, fp32 NCHW batch 16, forward 83 -> 33.
+// channels a group at stride 2, fp32 NCHW batch 16, forward 81 -> 27.
 #include "bounds.hpp"
 #include "gconv.hpp"
 #include <type_traits>
