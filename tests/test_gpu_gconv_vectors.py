@@ -116,3 +116,20 @@ TWO_AT_ONCE = [
 @pytest.mark.parametrize("case", TWO_AT_ONCE, ids=[c[0] for c in TWO_AT_ONCE])
 def test_two_tiles_at_once(case, layout, dtype):
     test_vectors_pairs_and_large_filters(case, layout, dtype)
+
+
+# the same with tiles of about 200 positions and output blocks and more: four at a time, in all passes' full tiles
+FOUR_AT_ONCE = [
+    ("g3_25x23", 22, 36, 36, 3, 25, 23, 3, 1, 1),                  # 16 outputs span groups of 12, the last block has four outputs
+    ("g7_10x29", 14, 112, 112, 7, 10, 29, 3, 1, 1),
+    ("g4_26x11", 23, 80, 80, 4, 26, 11, 3, 1, 1),                  # groups of 20
+    ("g7_s2", 15, 224, 224, 7, 25, 26, 3, 2, 1),                   # two output blocks; pairs of columns of the input gradient
+    ("g11_s2", 10, 352, 352, 11, 24, 27, 3, 2, 1),
+]
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("layout", [wl.NCHW, wl.NHWC], ids=["nchw", "nhwc"])
+@pytest.mark.parametrize("case", FOUR_AT_ONCE, ids=[c[0] for c in FOUR_AT_ONCE])
+def test_four_tiles_at_once(case, layout, dtype):
+    test_vectors_pairs_and_large_filters(case, layout, dtype)
