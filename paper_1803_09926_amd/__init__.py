@@ -134,8 +134,28 @@ def bwd_workspace_bytes(d: Desc) -> int:
 
 
 # ---- what a call checks and passes on --------------------------------------------------------------------
-# A small layer's kernels take 3 to 5 us, so the calls below avoid what costs a microsecond each: a stream object, wrapped
-# pointers (ctypes takes plain integers for void*), a second entry into the library for the output size.
+# A small layer's kernels take 2 to 5 us, as long as a few lookups of Python attributes.  So the calls below first go to native code
+# (csrc/binding.cpp), which checks plain device tensors and calls the library, and answers None to anything else; that is
+# then checked here, argument by argument.
+
+_native = None
+
+
+def _bind_native():
+    """The native call path, bound to the loaded library."""
+    global _native
+    lib = load()
+    import torch
+    try:
+        from . import _binding as native
+    except ImportError as e:
+        raise RuntimeError("the binding's native part is not built: run `python -m paper_1803_09926_amd.build` (or "
+                           "__graft_entry__.build()) first") from e
+    native.bind(lambda symbol: ctypes.cast(getattr(lib, symbol), ctypes.c_void_p).value, Desc, GroupDesc, torch.Tensor,
+                torch.nn.Parameter)
+    _native = native
+    return native
+
 
 _torch = _raw_stream = _device = None
 
@@ -198,9 +218,11 @@ def _sizes(d: Desc):
 
 def fwd(d: Desc, x, w, y, stream=None):
     """Enqueue y = depthwise cross-correlation of x with w on `stream` (default: torch's current)."""
-    nx, ny, nw = _sizes(d)
-    _check_tensor(x, "x", d, nx); _check_tensor(w, "w", d, nw); _check_tensor(y, "y", d, ny)
-    rc = load().dwconv_fwd(d, x.data_ptr(), w.data_ptr(), y.data_ptr(), _stream(stream))
+    rc = (_native or _bind_native()).fwd(d, x, w, y, stream)
+    if rc is None:
+        nx, ny, nw = _sizes(d)
+        _check_tensor(x, "x", d, nx); _check_tensor(w, "w", d, nw); _check_tensor(y, "y", d, ny)
+        rc = load().dwconv_fwd(d, x.data_ptr(), w.data_ptr(), y.data_ptr(), _stream(stream))
     if rc != 0:
         raise DwconvError(rc, "dwconv_fwd")
     return y
@@ -208,9 +230,11 @@ def fwd(d: Desc, x, w, y, stream=None):
 
 def bwd_data(d: Desc, dy, w, dx, stream=None):
     """Enqueue dx = input gradient."""
-    nx, ny, nw = _sizes(d)
-    _check_tensor(dy, "dy", d, ny); _check_tensor(w, "w", d, nw); _check_tensor(dx, "dx", d, nx)
-    rc = load().dwconv_bwd_data(d, dy.data_ptr(), w.data_ptr(), dx.data_ptr(), _stream(stream))
+    rc = (_native or _bind_native()).bwd_data(d, dy, w, dx, stream)
+    if rc is None:
+        nx, ny, nw = _sizes(d)
+        _check_tensor(dy, "dy", d, ny); _check_tensor(w, "w", d, nw); _check_tensor(dx, "dx", d, nx)
+        rc = load().dwconv_bwd_data(d, dy.data_ptr(), w.data_ptr(), dx.data_ptr(), _stream(stream))
     if rc != 0:
         raise DwconvError(rc, "dwconv_bwd_data")
     return dx
@@ -219,11 +243,13 @@ def bwd_data(d: Desc, dy, w, dx, stream=None):
 def bwd_filter(d: Desc, x, dy, dw, workspace, stream=None):
     """Enqueue dw = filter gradient (fp32).  `workspace` is a uint8 device tensor of at least
     bwd_filter_workspace_bytes(d) bytes."""
-    nx, ny, nw = _sizes(d)
-    _check_tensor(x, "x", d, nx); _check_tensor(dy, "dy", d, ny); _check_tensor(dw, "dw", d, nw, fp32_always=True)
-    ws, nbytes = _workspace(workspace)
-    rc = load().dwconv_bwd_filter(d, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), ws,
-                                  nbytes, _stream(stream))
+    rc = (_native or _bind_native()).bwd_filter(d, x, dy, dw, workspace, stream)
+    if rc is None:
+        nx, ny, nw = _sizes(d)
+        _check_tensor(x, "x", d, nx); _check_tensor(dy, "dy", d, ny); _check_tensor(dw, "dw", d, nw, fp32_always=True)
+        ws, nbytes = _workspace(workspace)
+        rc = load().dwconv_bwd_filter(d, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), ws,
+                                      nbytes, _stream(stream))
     if rc != 0:
         raise DwconvError(rc, "dwconv_bwd_filter")
     return dw
@@ -232,9 +258,11 @@ def bwd_filter(d: Desc, x, dy, dw, workspace, stream=None):
 def bwd_filter_noalloc(d: Desc, x, dy, dw, stream=None):
     """Enqueue dw = filter gradient (fp32) through the entry point that allocates nothing and takes no workspace
     (the partial sums go to a fixed array inside the library; shapes that need more raise DWCONV_ERR_SCRATCH)."""
-    nx, ny, nw = _sizes(d)
-    _check_tensor(x, "x", d, nx); _check_tensor(dy, "dy", d, ny); _check_tensor(dw, "dw", d, nw, fp32_always=True)
-    rc = load().dwconv_bwd_filter_noalloc(d, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), _stream(stream))
+    rc = (_native or _bind_native()).bwd_filter_noalloc(d, x, dy, dw, stream)
+    if rc is None:
+        nx, ny, nw = _sizes(d)
+        _check_tensor(x, "x", d, nx); _check_tensor(dy, "dy", d, ny); _check_tensor(dw, "dw", d, nw, fp32_always=True)
+        rc = load().dwconv_bwd_filter_noalloc(d, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), _stream(stream))
     if rc != 0:
         raise DwconvError(rc, "dwconv_bwd_filter_noalloc")
     return dw
@@ -243,12 +271,14 @@ def bwd_filter_noalloc(d: Desc, x, dy, dw, stream=None):
 def bwd(d: Desc, x, dy, w, dx, dw, workspace, stream=None):
     """Enqueue the whole backward pass: dx = input gradient, dw = filter gradient (fp32).  `workspace` is a
     uint8 device tensor of at least bwd_workspace_bytes(d) bytes."""
-    nx, ny, nw = _sizes(d)
-    _check_tensor(x, "x", d, nx); _check_tensor(dy, "dy", d, ny); _check_tensor(w, "w", d, nw)
-    _check_tensor(dx, "dx", d, nx); _check_tensor(dw, "dw", d, nw, fp32_always=True)
-    ws, nbytes = _workspace(workspace)
-    rc = load().dwconv_bwd(d, x.data_ptr(), dy.data_ptr(), w.data_ptr(), dx.data_ptr(), dw.data_ptr(), ws,
-                           nbytes, _stream(stream))
+    rc = (_native or _bind_native()).bwd(d, x, dy, w, dx, dw, workspace, stream)
+    if rc is None:
+        nx, ny, nw = _sizes(d)
+        _check_tensor(x, "x", d, nx); _check_tensor(dy, "dy", d, ny); _check_tensor(w, "w", d, nw)
+        _check_tensor(dx, "dx", d, nx); _check_tensor(dw, "dw", d, nw, fp32_always=True)
+        ws, nbytes = _workspace(workspace)
+        rc = load().dwconv_bwd(d, x.data_ptr(), dy.data_ptr(), w.data_ptr(), dx.data_ptr(), dw.data_ptr(), ws,
+                               nbytes, _stream(stream))
     if rc != 0:
         raise DwconvError(rc, "dwconv_bwd")
     return dx, dw
@@ -288,9 +318,11 @@ def _gsizes(d: GroupDesc):
 
 def gconv_fwd(d: GroupDesc, x, w, y, stream=None):
     """Enqueue y = group cross-correlation of x with w (w [O,Cg,K,K] for NCHW, [K,K,Cg,O] for NHWC)."""
-    nx, ny, nw = _gsizes(d)
-    _check_tensor(x, "x", d, nx); _check_tensor(w, "w", d, nw); _check_tensor(y, "y", d, ny)
-    rc = load().gconv_fwd(d, x.data_ptr(), w.data_ptr(), y.data_ptr(), _stream(stream))
+    rc = (_native or _bind_native()).gconv_fwd(d, x, w, y, stream)
+    if rc is None:
+        nx, ny, nw = _gsizes(d)
+        _check_tensor(x, "x", d, nx); _check_tensor(w, "w", d, nw); _check_tensor(y, "y", d, ny)
+        rc = load().gconv_fwd(d, x.data_ptr(), w.data_ptr(), y.data_ptr(), _stream(stream))
     if rc != 0:
         raise DwconvError(rc, "gconv_fwd")
     return y
@@ -298,9 +330,11 @@ def gconv_fwd(d: GroupDesc, x, w, y, stream=None):
 
 def gconv_bwd_data(d: GroupDesc, dy, w, dx, stream=None):
     """Enqueue dx = input gradient of the group convolution."""
-    nx, ny, nw = _gsizes(d)
-    _check_tensor(dy, "dy", d, ny); _check_tensor(w, "w", d, nw); _check_tensor(dx, "dx", d, nx)
-    rc = load().gconv_bwd_data(d, dy.data_ptr(), w.data_ptr(), dx.data_ptr(), _stream(stream))
+    rc = (_native or _bind_native()).gconv_bwd_data(d, dy, w, dx, stream)
+    if rc is None:
+        nx, ny, nw = _gsizes(d)
+        _check_tensor(dy, "dy", d, ny); _check_tensor(w, "w", d, nw); _check_tensor(dx, "dx", d, nx)
+        rc = load().gconv_bwd_data(d, dy.data_ptr(), w.data_ptr(), dx.data_ptr(), _stream(stream))
     if rc != 0:
         raise DwconvError(rc, "gconv_bwd_data")
     return dx
@@ -309,11 +343,13 @@ def gconv_bwd_data(d: GroupDesc, dy, w, dx, stream=None):
 def gconv_bwd_filter(d: GroupDesc, x, dy, dw, workspace, stream=None):
     """Enqueue dw = filter gradient (fp32) of the group convolution.  `workspace` is a uint8 device tensor of
     at least gconv_bwd_filter_workspace_bytes(d) bytes."""
-    nx, ny, nw = _gsizes(d)
-    _check_tensor(x, "x", d, nx); _check_tensor(dy, "dy", d, ny); _check_tensor(dw, "dw", d, nw, fp32_always=True)
-    ws, nbytes = _workspace(workspace)
-    rc = load().gconv_bwd_filter(d, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), ws,
-                                 nbytes, _stream(stream))
+    rc = (_native or _bind_native()).gconv_bwd_filter(d, x, dy, dw, workspace, stream)
+    if rc is None:
+        nx, ny, nw = _gsizes(d)
+        _check_tensor(x, "x", d, nx); _check_tensor(dy, "dy", d, ny); _check_tensor(dw, "dw", d, nw, fp32_always=True)
+        ws, nbytes = _workspace(workspace)
+        rc = load().gconv_bwd_filter(d, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), ws,
+                                     nbytes, _stream(stream))
     if rc != 0:
         raise DwconvError(rc, "gconv_bwd_filter")
     return dw

@@ -7,10 +7,12 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdwconv.so")
+BINDING = os.path.join(HERE, "_binding.so")
 OBJDIR = os.path.join(HERE, "_build")
 
 HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
@@ -31,12 +33,30 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _binding() -> None:
+    """The Python binding's call path, a CPython extension against torch's own headers and libraries (host code only)."""
+    import torch
+    from torch.utils import cpp_extension
+    inc = cpp_extension.include_paths() + [sysconfig.get_paths()["include"], os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(HIPCC))), "include")]
+    tmp = BINDING + ".tmp.%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI] + ["-isystem" + i for i in inc]
+    cmd += [os.path.join(CSRC, "binding.cpp"), "-o", tmp, "-L" + os.path.join(os.path.dirname(torch.__file__), "lib"),
+            "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for binding.cpp:\n%s" % r.stderr)
+    os.replace(tmp, BINDING)
+
+
 def build(verbose: bool = True) -> str:
-    """Compile every .hip file (always, even if a library is already there) and link."""
+    """Compile every .hip file and the binding (always, even if built ones are already there) and link."""
     os.makedirs(OBJDIR, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
-    with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
+    with concurrent.futures.ThreadPoolExecutor(max_workers=8) as ex:
+        native = ex.submit(_binding)
         objs = list(ex.map(_compile, srcs))
+        native.result()
     tmp = LIB + ".tmp.%d" % os.getpid()
     subprocess.check_call([HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp] + objs)
     os.replace(tmp, LIB)
