@@ -21,6 +21,11 @@
 // 24.9 / 31.5 / 21.8 -> 16.4 / 22.8 / 18.6; 57x57x128, 4 channels a group, fp32 NCHW batch 64 151 / 144 / 151 -> 116 / 134 / 116 (there 3 of 4
 // products are zeros: 49 us of matrix instructions a pass).  A tile may take more than 64 KiB of LDS where the filter does: 28x28x512, 32
 // channels a group at stride 2, fp32 NCHW batch 16, forward 81 -> 27.
+// Any channel count and row width comes in vectors (16 bytes of channels at any alignment in NHWC; in NCHW tiles narrower than the rows, runs of
+// four columns from the multiple of four before a tile), the NCHW filter by an entry's taps, so that a vector's place is found once, and two pairs of taps
+// are read at a time: random layers 0.85 (bf16) and 0.875 (fp32) of the time in NCHW forward, 0.88 and 0.92 in the input gradient, NHWC 0.94 and 0.96,
+// 0.93 and 0.98; 9x9x320 in ten groups, 5x5, bf16 NCHW batch 7, forward 15.3 -> 10.5;
+// 16x16x160 in five, 5x5, fp32 NCHW batch 4, 17.6 -> 12.6.
 #include "bounds.hpp"
 #include "gconv.hpp"
 #include <type_traits>
@@ -75,6 +80,10 @@ template <typename T> struct Finite;
 template <> struct Finite<float> {
     float m = 0.f;
     __device__ __forceinline__ void add(uint32_t q) { m = fmaf(__uint_as_float(q), 0.f, m); }
+    __device__ __forceinline__ void add(const Frag<float> &f)
+    {
+        m = fmaf(f.v.x, 0.f, m); m = fmaf(f.v.y, 0.f, m); m = fmaf(f.v.z, 0.f, m); m = fmaf(f.v.w, 0.f, m);
+    }
     __device__ __forceinline__ bool bad() const { return m != m; }
 };
 template <> struct Finite<bf16_t> {
@@ -83,6 +92,7 @@ template <> struct Finite<bf16_t> {
     {
         m = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, m), __builtin_bit_cast(u16x2, q & 0x7fff7fffu)));
     }
+    __device__ __forceinline__ void add(const Frag<bf16_t> &f) { add(f.v.x); add(f.v.y); }
     __device__ __forceinline__ bool bad() const { return (m & 0xffffu) >= 0x7f80u || m >> 16 >= 0x7f80u; }
 };
 
@@ -109,6 +119,7 @@ template <typename T, int V, typename A> __device__ __forceinline__ void store_r
 struct StageGeom {
     int LH, LW, pitch;               // the tile: rows of an image, columns, elements between pixels
     int imrows, rows, cols, per, nv; // imrows: rows of all images; nv: items of a pixel (NHWC)
+    int width;                       // items of a row
     int RPI, nrit, iters;
     float rper, rnv, rLH, rimrows;
 };
@@ -197,9 +208,33 @@ __device__ __forceinline__ bool stage_pixels(const T *__restrict__ in, T *lx, in
 
 // The same where FAST holds, in two steps: load() sends out the loads of BT items of a lane, commit() writes them to LDS, so that the
 // next tile is on its way while this one is computed.
-template <typename T, bool NHWC, int BT> struct Stager;
+// FAST: 1, channels of whole vectors (NHWC), tiles of whole rows (NCHW); 2, ragged channels, or tiles narrower than the rows.
+template <typename T, bool NHWC, int FAST, int BT> struct Stager;
 
-template <typename T, int BT> struct Stager<T, true, BT> {
+// The elements of 16 (or eight) bytes from element n on.
+template <int VE, typename Q> __device__ __forceinline__ Q later(Q q, int n)
+{
+    constexpr int WORDS = (int)sizeof(Q) / 4;
+    if constexpr (VE == 4 && WORDS == 2) return __builtin_bit_cast(Q, __builtin_bit_cast(uint64_t, q) >> 16 * n);
+    if constexpr (VE == WORDS) {
+        if (n & 1) {
+#pragma unroll
+            for (int i = 0; i + 1 < WORDS; ++i) q[i] = q[i + 1];
+        }
+    } else if (n & 1) {
+#pragma unroll
+        for (int i = 0; i < WORDS; ++i) q[i] = q[i] >> 16 | (i + 1 < WORDS ? q[i + 1] << 16 : 0u);
+    }
+#pragma unroll
+    for (int step = VE == WORDS ? 2 : 1; step < WORDS; step *= 2)          // words
+        if (n & step * (VE / WORDS)) {
+#pragma unroll
+            for (int i = 0; i + step < WORDS; ++i) q[i] = q[i + step];
+        }
+    return q;
+}
+
+template <typename T, int FAST, int BT> struct Stager<T, true, FAST, BT> {
     static constexpr int VE = 16 / (int)sizeof(T);
     u4raw_t q[BT];
     int rsub, csub, v;
@@ -218,9 +253,14 @@ template <typename T, int BT> struct Stager<T, true, BT> {
         r = it * sg.RPI + rsub;
         return rsub < sg.RPI && r < sg.rows && col < sg.LW;
     }
-    // from image 0 of the view, nimg images: rows from h0, columns from w0, channels from ca
-    __device__ __forceinline__ void load(const StageGeom &sg, const BufView &view, int nimg, int C, int H, int W, int h0, int w0, int ca, int it0)
+    // nimg images from element `first` of `in` on, a tensor of `total` elements (VE and more, below 2^31): rows from h0, columns from w0, channels from ca.
+    // Channels that are no whole number of vectors: unaligned loads, whose last elements are the next pixel's first (they meet zeros of
+    // the filter), at the tensor's end those before it.
+    __device__ __forceinline__ void load(const StageGeom &sg, const T *__restrict__ in, unsigned first, unsigned total, int nimg, int C, int H, int W,
+                                         int h0, int w0, int ca, int it0)
     {
+        const BufView view(in + first, (uint32_t)(nimg * C) * (uint32_t)(H * W) * (uint32_t)sizeof(T));
+        [[maybe_unused]] const bool past = first + (unsigned)(nimg * C) * (unsigned)(H * W) + VE > total;
 #pragma unroll
         for (int b = 0; b < BT; ++b) {
             if (it0 + b >= sg.iters) break;
@@ -230,8 +270,16 @@ template <typename T, int BT> struct Stager<T, true, BT> {
             h += h0; w += w0;
             ok = ok && im < nimg && (unsigned)h < (unsigned)H && (unsigned)w < (unsigned)W && ca + v < C;
             // (in range every factor is below 2^24)
-            const uint32_t at = (__umul24(__umul24(__umul24(im, H) + h, W) + w, C) + ca + v) * (uint32_t)sizeof(T);
-            q[b] = view.b128(ok ? at : BufView::OUTSIDE, 0);
+            const uint32_t e = __umul24(__umul24(__umul24(im, H) + h, W) + w, C) + ca + v;
+            if constexpr (FAST == 1) q[b] = view.b128(ok ? e * (uint32_t)sizeof(T) : BufView::OUTSIDE, 0);
+            else {
+                q[b] = u4raw_t{0u, 0u, 0u, 0u};
+                if (ok) {
+                    const unsigned p = first + e, at = min(p, total - VE);
+                    __builtin_memcpy(&q[b], in + at, 16);
+                    if (past) q[b] = later<VE>(q[b], (int)(p - at));
+                }
+            }
         }
     }
     __device__ __forceinline__ void commit(const StageGeom &sg, T *lx, int, int, int it0, bool check, Finite<T> &seen) const
@@ -250,9 +298,9 @@ template <typename T, int BT> struct Stager<T, true, BT> {
     }
 };
 
-// Four channels of four consecutive columns of a row, transposed in registers; the columns beside the row are zero from the start and
-// stay so.
-template <typename T, int BT> struct Stager<T, false, BT> {
+// Four channels of four consecutive columns of a row, transposed in registers.  Where a tile holds whole rows, the columns beside the row are
+// zero from the start and stay so; where it is narrower, its runs of four start at the multiple of four before it and bring their own zeros.
+template <typename T, int FAST, int BT> struct Stager<T, false, FAST, BT> {
     static constexpr int NW = (int)sizeof(T);      // 32-bit words of four columns
     typedef uint32_t word_t __attribute__((ext_vector_type(NW)));
     word_t e[BT][4];
@@ -262,31 +310,32 @@ template <typename T, int BT> struct Stager<T, false, BT> {
         rsub = fdiv(threadIdx.x, sg.rper);
         csub = threadIdx.x - rsub * sg.per;
     }
-    // row of all channel quads and run of four columns
-    __device__ __forceinline__ bool locate(const StageGeom &sg, int it, int W, int &r, int &run) const
+    // row of all channel quads and first column of the run of four; w0: the tile's first column
+    __device__ __forceinline__ bool locate(const StageGeom &sg, int it, int W, int w0, int &r, int &col) const
     {
-        run = csub;
+        int run = csub;
         while (it >= sg.nrit) { it -= sg.nrit; run += sg.cols; }
         r = it * sg.RPI + rsub;
-        return rsub < sg.RPI && r < sg.rows && run * 4 < W;
+        col = (FAST == 2 ? w0 & ~3 : 0) + run * 4;
+        return rsub < sg.RPI && r < sg.rows && (FAST == 2 ? run < sg.width : col < W);
     }
     // nimg images from element `first` of `in` on, a tensor of `total` elements (four and more, below 2^31)
     __device__ __forceinline__ void load(const StageGeom &sg, const T *__restrict__ in, unsigned first, unsigned total, int nimg, int C, int H, int W,
-                                         int h0, int ca, int it0)
+                                         int h0, int w0, int ca, int it0)
     {
         const unsigned plane = (unsigned)(H * W);
         const bool past = W % 4 && runs_past(first + (unsigned)(nimg * C) * plane, total);        // of this tile or, up to two elements, the ones behind
 #pragma unroll
         for (int b = 0; b < BT; ++b) {
             if (it0 + b >= sg.iters) break;
-            int h, run, im = 0, qd = 0;
-            bool ok = locate(sg, it0 + b, W, h, run);
+            int h, col, im = 0, qd = 0;
+            bool ok = locate(sg, it0 + b, W, w0, h, col);
             if (sg.rows != sg.imrows) { qd = fdiv(h, sg.rimrows); h -= qd * sg.imrows; }
             if (sg.imrows != sg.LH) { im = fdiv(h, sg.rLH); h -= im * sg.LH; }
             h += h0;
             const int c = ca + qd * 4;
-            ok = ok && im < nimg && (unsigned)h < (unsigned)H && c < C;
-            unsigned p0 = first + (unsigned)(im * C + c) * plane + (unsigned)(h * W + run * 4);
+            ok = ok && im < nimg && (unsigned)h < (unsigned)H && (FAST == 1 || (unsigned)col < (unsigned)W) && c < C;
+            unsigned p0 = first + (unsigned)(im * C + c) * plane + (unsigned)(h * W + col);
 #pragma unroll
             for (int k = 0; k < 4; ++k)
 #pragma unroll
@@ -298,34 +347,23 @@ template <typename T, int BT> struct Stager<T, false, BT> {
                     // any alignment; a run that passes the row's end reads the elements behind it, at the tensor's end those before it
                     const unsigned at = run_start(p0, total);
                     __builtin_memcpy(&e[b][k], in + at, 4 * sizeof(T));
-                    if (past) e[b][k] = later(e[b][k], (int)(p0 - at));
+                    if (past) e[b][k] = later<4>(e[b][k], (int)(p0 - at));
                 }
             }
-        }
-    }
-    // the four elements from element n on
-    static __device__ __forceinline__ word_t later(word_t q, int n)
-    {
-        if constexpr (sizeof(T) == 2) {
-            const uint64_t v = __builtin_bit_cast(uint64_t, q) >> 16 * n;
-            return __builtin_bit_cast(word_t, v);
-        } else {
-            if (n & 1) q = word_t{q[1], q[2], q[3], q[3]};
-            if (n & 2) q = word_t{q[2], q[3], q[3], q[3]};
-            return q;
         }
     }
     // w0: the tile's first column
     __device__ __forceinline__ void commit(const StageGeom &sg, T *lx, int W, int w0, int it0, bool check, Finite<T> &seen) const
     {
-        const bool whole = W % 4 == 0 && w0 <= 0 && W - w0 <= sg.LW;                // every column of a run is one of the tile
+        const bool whole = FAST == 1 && W % 4 == 0 && w0 <= 0 && W - w0 <= sg.LW;                // every column of a run is one of the tile
 #pragma unroll
         for (int b = 0; b < BT; ++b) {
             if (it0 + b >= sg.iters) break;
-            int r, run, qd = 0;
-            const bool ok = locate(sg, it0 + b, W, r, run);
+            int r, col, qd = 0;
+            const bool ok = locate(sg, it0 + b, W, w0, r, col);
             if (sg.rows != sg.imrows) { qd = fdiv(r, sg.rimrows); r -= qd * sg.imrows; }
-            const int col = run * 4 - w0, n = ok ? W - run * 4 : 0;
+            const int n = ok ? W - col : 0;                        // columns of the run inside the row
+            col -= w0;
             T *at = lx + ((int)__umul24(r, sg.LW) + col) * sg.pitch + qd * 4;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -336,12 +374,10 @@ template <typename T, int BT> struct Stager<T, false, BT> {
                     const uint32_t sel = j & 1 ? 0x07060302u : 0x05040100u;
                     f.v = make_uint2(__builtin_amdgcn_perm(e[b][1][j / 2], e[b][0][j / 2], sel), __builtin_amdgcn_perm(e[b][3][j / 2], e[b][2][j / 2], sel));
                 }
-                if (whole ? n > 0 : j < n && (unsigned)(col + j) < (unsigned)sg.LW) {
+                if (FAST == 2 && j >= n) f.v = decltype(f.v){};
+                if (whole ? n > 0 : (FAST == 2 ? ok : j < n) && (unsigned)(col + j) < (unsigned)sg.LW) {
                     if (check) {
-                        if constexpr (sizeof(T) == 4) {
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) seen.add(e[b][k][j]);
-                        } else { seen.add(f.v.x); seen.add(f.v.y); }
+                        seen.add(f);
                     }
                     *reinterpret_cast<Frag<T> *>(at + j * sg.pitch) = f;
                 }
@@ -350,12 +386,18 @@ template <typename T, int BT> struct Stager<T, false, BT> {
     }
 };
 
+// Fragments between quads of input channels.  NCHW: one more than there are, so that the entries that the lanes of a wavefront lay out (taps and
+// channels of a few outputs) lie in different banks: bf16 0.955 of the time forward and 0.977 backward, fp32 0.987 and 1.003 (mean over random
+// layers).  NHWC, where lanes write consecutive outputs: 1.00 in bf16, and 1.016 in fp32, whose tiles get smaller.
+template <bool NHWC> constexpr int quad_of() { return NHWC ? 16 : 17; }
+
 // A tile that holds an infinity or NaN where 16 outputs span several groups, or whose filter does: one output per lane, its own
 // group's channels and the taps inside the image only.
 template <typename T, bool NHWC>
 __device__ __forceinline__ void own_group_only(const GemmGeom &g, const Frag<T> *lw, const int *slots, const T *lx, T *__restrict__ out, int n0, int a0,
                                                          int b0, int ob, int ca)
 {
+    constexpr int QUAD = quad_of<NHWC>();
     const int npos = g.TN * g.TA * g.TB, nch = g.NS * 16, KK = g.K * g.K;
 #pragma unroll 1
     for (int i = threadIdx.x; i < g.OS * g.OS * npos * nch; i += 256) {
@@ -377,7 +419,7 @@ __device__ __forceinline__ void own_group_only(const GemmGeom &g, const Frag<T> 
 #pragma unroll 1
                 for (int c = c0; c < c0 + g.Cgi; ++c) {
                     const int j = c - cs;
-                    const T *pw = reinterpret_cast<const T *>(&lw[((s * KK + (slots ? slots[kh * g.K + kw] : kh * g.K + kw)) * g.nk + j / 16) * 64 + j % 16 / 4 * 16 + oc % 16]);
+                    const T *pw = reinterpret_cast<const T *>(&lw[((s * KK + (slots ? slots[kh * g.K + kw] : kh * g.K + kw)) * g.nk + j / 16) * (4 * QUAD) + j % 16 / 4 * QUAD + oc % 16]);
                     acc = fmaf(ldf(pw + j % 4), ldf(px + c - ca), acc);
                 }
             }
@@ -390,27 +432,25 @@ __device__ __forceinline__ void own_group_only(const GemmGeom &g, const Frag<T> 
 // chunk*16 + lane/16*4 .. +3 from cin_first of the block on.  FAST: 16 bytes of the filter a lane and load, each entry then written where it
 // belongs (one entry a load, gathered in operand order, cost a 14x14 layer of 16 channels a group 2 us forward and 4 us backward of its 13).
 // ---------------------------------------------------------------------------------------------
-template <typename T, bool NHWC, bool BWD> struct FilterLoader {
-    static constexpr int VE = 16 / (int)sizeof(T);
+template <typename T, bool NHWC, bool BWD, int FAST> struct FilterLoader {
+    static constexpr int VE = 16 / (int)sizeof(T), QUAD = quad_of<NHWC>();
     const GemmGeom &g;
     int ob, KK;
     int g0, g1;              // groups of the block's outputs
     int fc0, X;              // the places in a group that are read (forward: all input channels, backward: those of the block's outputs)
-    int nvr, nvec, run;      // vectors of a row, of all rows; NCHW: elements of a row (0: all rows are one run)
+    int nvr, nvec;           // vectors of a row (NCHW: of an entry's taps), of all rows
     float rnvr, rX;
-    unsigned first;          // element that the first vector starts at
+    unsigned first, total;   // element that the first vector starts at; of the filter
 
-    // Of the shapes that takes() admits, a block takes vectors where they are no more than its fragments.  Backward a block whose outputs lie in two
-    // groups, or (NCHW) whose outputs of a group are no whole vectors, reads the groups' whole filter, which has no bound (12001 channels
-    // against 256: 27 million entries, beyond what fdiv divides) and keeps the launch waiting: us, such blocks by vectors too -> not, fp32
-    // NCHW 68x266x5x5 to 66 channels, stride 2, 92 -> 33, bf16 NHWC 4x560x5x5 in two groups, 1x1, 36 -> 17; 0.92 to 0.95 of the time at the mean over
-    // random layers of 17 to 300 channels a group.  At half the fragments NCHW is another half per cent shorter and NHWC 1 to 3 longer.
-    // NHWC backward needs quads inside a group, NCHW at least a vector's entries for a pair of channels and a whole last vector: of the
-    // filter forward, of every group backward (whose first vector starts where the group does).
+    // Of the shapes that takes() admits, a block takes vectors where they are no more than its fragments (NCHW, where nine taps are three vectors in
+    // fp32: half as many again).  Backward a block whose outputs lie in two
+    // groups reads the groups' whole filter, which has no bound (12001 channels against 256: 27 million entries, beyond what fdiv divides) and
+    // keeps the launch waiting: us, such blocks by vectors too -> not, bf16 NHWC 4x560x5x5 in two groups, 1x1, 36 -> 17.
+    // NCHW needs at least a vector's taps, the filter a vector's entries.
     static __device__ __forceinline__ bool takes(const GemmGeom &g)
     {
-        const int KK = g.K * g.K;
-        return NHWC ? !BWD || g.Cgi % 4 == 0 : KK >= VE && (unsigned)((BWD ? g.Cgi : g.FO) * g.FCg * KK) % VE == 0;
+        if (!NHWC) return g.K * g.K >= VE;
+        return FAST != 2 || (unsigned)(g.FO * g.FCg * g.K * g.K) >= VE;
     }
 
     const int *slots;        // where a tap's entries go (null: in order)
@@ -419,11 +459,8 @@ template <typename T, bool NHWC, bool BWD> struct FilterLoader {
     {
         const int olast = min(ob + g.NS * 16, g.CO) - 1;
         g0 = fdiv(ob, g.rCgo); g1 = fdiv(olast, g.rCgo);
-        fc0 = 0; X = g.FCg; run = 0;
-        if (BWD && g0 == g1) {
-            const int n = olast + 1 - ob;
-            if (NHWC || n * KK % VE == 0) { fc0 = ob - g0 * g.Cgo; X = n; }
-        }
+        fc0 = 0; X = g.FCg;
+        if (BWD && g0 == g1) { fc0 = ob - g0 * g.Cgo; X = olast + 1 - ob; }
         int rows;
         if (NHWC) {
             // rows of (tap, place in the group): forward the block's outputs, backward the groups' input channels
@@ -431,12 +468,12 @@ template <typename T, bool NHWC, bool BWD> struct FilterLoader {
             nvr = BWD ? (int)((g1 + 1) * g.Cgi - first + VE - 1) / VE : g.NS * 16 / VE;
             rows = KK * X;
         } else {
-            first = BWD ? (unsigned)(g0 * g.Cgi * g.FCg + fc0) * KK : (unsigned)(ob * g.FCg) * KK;
-            rows = BWD ? (g1 - g0 + 1) * g.Cgi : olast + 1 - ob;
-            if (BWD && X < g.FCg) run = X * KK;
-            nvr = run ? run / VE : (rows * g.FCg * KK + VE - 1) / VE;
-            if (!run) rows = 1;
+            // rows of (output or, backward, input channel; place in the group): its taps, the last vector ending with the last one
+            first = (unsigned)((BWD ? g0 * g.Cgi : ob) * g.FCg + fc0) * KK;
+            nvr = (KK + VE - 1) / VE;
+            rows = (BWD ? (g1 - g0 + 1) * g.Cgi : olast + 1 - ob) * X;
         }
+        total = (unsigned)(g.FO * g.FCg * KK);
         nvec = rows * nvr;
         rnvr = __builtin_amdgcn_rcpf((float)nvr); rX = __builtin_amdgcn_rcpf((float)X);
     }
@@ -448,10 +485,19 @@ template <typename T, bool NHWC, bool BWD> struct FilterLoader {
         if constexpr (NHWC) {
             unsigned at = (unsigned)row;
             if (BWD) { const int tap = fdiv(row, rX); at = (unsigned)(tap * g.FCg + fc0 + row - tap * X); }
-            // (FO is a whole number of vectors, so is every row)
-            if ((int)first + v < g.FO) q = *reinterpret_cast<const u4raw_t *>(w + at * (unsigned)g.FO + first + v);
+            // (a vector beyond a row's end holds the next row's first entries, which put() leaves out)
+            if ((int)first + v < g.FO) {
+                const unsigned p = at * (unsigned)g.FO + first + v;
+                if constexpr (FAST == 1) q = *reinterpret_cast<const u4raw_t *>(w + p);
+                else {
+                    const unsigned from = min(p, total - VE);
+                    __builtin_memcpy(&q, w + from, 16);
+                    if (from != p) q = later<VE>(q, (int)(p - from));
+                }
+            }
         } else {
-            __builtin_memcpy(&q, w + first + (unsigned)(row * g.FCg * KK) + v, 16);               // any alignment
+            const int r = fdiv(row, rX);
+            __builtin_memcpy(&q, w + first + (unsigned)((r * g.FCg + row - r * X) * KK) + min(v, KK - VE), 16);               // any alignment
         }
         return q;
     }
@@ -465,12 +511,12 @@ template <typename T, bool NHWC, bool BWD> struct FilterLoader {
     {
         const int oi = o - ob, s = oi >> 4, rel = c - cin_first(ob + (s << 4), g);
         if ((unsigned)oi >= (unsigned)(g.NS * 16) || o >= g.CO) return -1;
-        return (((s * KK) * g.nk + (rel >> 4)) * 64 + (rel >> 2 & 3) * 16 + (oi & 15)) * 4 + (rel & 3);
+        return (((s * KK) * g.nk + (rel >> 4)) * (4 * QUAD) + (rel >> 2 & 3) * QUAD + (oi & 15)) * 4 + (rel & 3);
     }
     __device__ __forceinline__ void put(T *lw, int i, const u4raw_t &q, Finite<T> &seen) const
     {
         if (i >= nvec) return;
-        const int tstep = g.nk * 256;
+        const int tstep = g.nk * (4 * QUAD) * 4;
         const int row = fdiv(i, rnvr), v = (i - row * nvr) * VE;
 #pragma unroll
         for (int k = 0; k < 4; ++k) seen.add(q[k]);
@@ -482,40 +528,41 @@ template <typename T, bool NHWC, bool BWD> struct FilterLoader {
                 for (int j = 0; j < VE; ++j) at[4 * j] = entry(q, j);
             } else {
                 const int oi = o - ob, s = oi >> 4, c0 = cin_first(ob + (s << 4), g);
-                T *at = lw + (((s * KK + tap) * g.nk) * 64 + (oi & 15)) * 4;
+                T *at = lw + (((s * KK + tap) * g.nk) * (4 * QUAD) + (oi & 15)) * 4;
 #pragma unroll
                 for (int j = 0; j < VE; ++j) {
                     const int rel = fdiv(o + j, g.rCgo) * g.Cgi + x - c0;
-                    if (o + j < g.CO) at[(rel >> 4) * 256 + (rel >> 2 & 3) * 64 + 4 * j + (rel & 3)] = entry(q, j);
+                    if (o + j < g.CO) at[(rel >> 4) * (16 * QUAD) + (rel >> 2 & 3) * (QUAD * 4) + 4 * j + (rel & 3)] = entry(q, j);
                 }
             }
         } else if constexpr (NHWC) {
             const int tap = fdiv(row, rX), x = row - tap * X, c = (int)first + v;
+            T *to = lw + (slots ? slots[tap] : tap) * tstep;
+            if (g.Cgi % 4 == 0) {
 #pragma unroll
-            for (int u = 0; u < VE; u += 4) {
-                const int grp = fdiv(c + u, g.rCgi), at = place(grp * g.Cgo + fc0 + x, c + u);
-                if (at < 0 || grp < g0 || grp > g1) continue;
-                Frag<T> f;
-                if constexpr (sizeof(T) == 4) f.v = make_float4(entry(q, 0), entry(q, 1), entry(q, 2), entry(q, 3));
-                else f.v = make_uint2(q[u / 2], q[u / 2 + 1]);
-                *reinterpret_cast<Frag<T> *>(lw + at + (slots ? slots[tap] : tap) * tstep) = f;
+                for (int u = 0; u < VE; u += 4) {
+                    const int grp = fdiv(c + u, g.rCgi), at = place(grp * g.Cgo + fc0 + x, c + u);
+                    if (at < 0 || grp < g0 || grp > g1) continue;
+                    Frag<T> f;
+                    if constexpr (sizeof(T) == 4) f.v = make_float4(entry(q, 0), entry(q, 1), entry(q, 2), entry(q, 3));
+                    else f.v = make_uint2(q[u / 2], q[u / 2 + 1]);
+                    *reinterpret_cast<Frag<T> *>(to + at) = f;
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < VE; ++j) {
+                    const int grp = fdiv(c + j, g.rCgi), at = place(grp * g.Cgo + fc0 + x, c + j);
+                    if (at >= 0 && grp >= g0 && grp <= g1) to[at] = entry(q, j);
+                }
             }
         } else {
-            // entries of (row, place in the group, tap) one after the other; a vector touches two places at most
-            const int e = run ? row * run + v : v, t = fdiv(e, g.rKK), tap = e - t * KK;
-            auto at_place = [&](int t) {
-                const int r = fdiv(t, rX), x = t - r * X;
-                if (!BWD) return r + ob < g.CO ? place(ob + r, fdiv(ob + r, g.rCgo) * g.Cgi + x) : -1;
-                const int gr = g0 + fdiv(r, g.rCgi);
-                return gr <= g1 ? place(gr * g.Cgo + fc0 + x, g0 * g.Cgi + r) : -1;
-            };
-            const int at0 = at_place(t), at1 = at_place(t + 1);
+            const int r = fdiv(row, rX), x = row - r * X, tap = min(v, KK - VE);
+            int at;
+            if (!BWD) at = place(ob + r, fdiv(ob + r, g.rCgo) * g.Cgi + x);
+            else at = place((g0 + fdiv(r, g.rCgi)) * g.Cgo + fc0 + x, g0 * g.Cgi + r);
+            if (at < 0) return;
 #pragma unroll
-            for (int j = 0; j < VE; ++j) {
-                const bool next = tap + j >= KK;
-                const int at = next ? at1 : at0, tp = next ? tap + j - KK : tap + j;
-                if (at >= 0) lw[at + (BWD && slots ? slots[tp] : tp) * tstep] = entry(q, j);
-            }
+            for (int j = 0; j < VE; ++j) lw[at + (BWD && slots ? slots[tap + j] : tap + j) * tstep] = entry(q, j);
         }
     }
 };
@@ -525,7 +572,7 @@ template <typename T, bool NHWC, bool BWD> struct FilterLoader {
 // input gradient at stride 2 in NCHW, both columns of a pair of output classes at a time, so that a lane's four positions are eight
 // consecutive outputs (aligned for rows of whole vectors: with an odd padding the pair is class 1 of a position and class 0 of the next).
 // ---------------------------------------------------------------------------------------------
-template <typename T, bool NHWC, bool BWD, bool FAST, int P, int E, bool SCATTER>
+template <typename T, bool NHWC, bool BWD, int FAST, int P, int E, bool SCATTER>
 __global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg, const T *__restrict__ in, const T *__restrict__ w, T *__restrict__ out,
                                                     int nparts, unsigned nblocks)
 {
@@ -537,13 +584,13 @@ __global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg,
     constexpr bool OUTER = NHWC || SCATTER;                                // a lane has four outputs of one position, otherwise one output of four
     const int OS = BWD ? g.OS : 1, IS = BWD ? 1 : g.IS;
     const int K = g.K, KK = K * K, ob = chb * g.NS * 16;
-    constexpr int VE = 16 / (int)sizeof(T);
+    constexpr int VE = 16 / (int)sizeof(T), QUAD = quad_of<NHWC>(), CHUNK = 4 * QUAD;
     const int ca = cin_first(ob, g) & ~(VE - 1);
     Frag<T> *lw = reinterpret_cast<Frag<T> *>(smem);                       // [sub-block][tap][chunk][lane]
     const int npos = g.TN * g.TA * g.TB, ngrp = (npos + 16 * P - 1) / (16 * P), nent = ngrp * 16 * P;
     // of every position: element of its first input pixel in LDS, element of its output (-1: none; the image's first for OS > 1), and
     // for OS > 1 row and column of that
-    int *tabx = reinterpret_cast<int *>(lw + (size_t)g.NS * KK * g.nk * 64), *tabo = tabx + nent, *tabr = tabo + nent;
+    int *tabx = reinterpret_cast<int *>(lw + (size_t)g.NS * KK * g.nk * (4 * QUAD)), *tabo = tabx + nent, *tabr = tabo + nent;
     int *slots = OS > 1 ? tabr + 2 * nent : nullptr;       // taps in the order of their classes
     int *flag = OS > 1 ? slots + 64 : tabr;                // an infinity or NaN in the filter or the tile (two, in turn)
     T *lx = reinterpret_cast<T *>(flag + 4);
@@ -557,25 +604,24 @@ __global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg,
         n0 = tn * g.TN; a0 = g.a0 + (row - tn * g.ta) * g.TA; b0 = g.b0 + (tile - row * g.tb) * g.TB;
     };
     constexpr int BT = NHWC || sizeof(T) == 2 ? 4 : 2;       // items of a lane in flight
-    [[maybe_unused]] Stager<T, NHWC, BT> stager(sg);
+    [[maybe_unused]] Stager<T, NHWC, FAST, BT> stager(sg);
     auto load_tile = [&](int tile, int it0) {
         if constexpr (FAST) {
             int n0, a0, b0;
             tile_at(tile, n0, a0, b0);
             const int nimg = min(g.TN, g.N - n0), h0 = IS * a0 - g.ip + g.lo, w0 = IS * b0 - g.ip + g.lo;
-            if constexpr (NHWC) stager.load(sg, BufView(in + (size_t)n0 * imin, (uint32_t)nimg * imin * (uint32_t)sizeof(T)), nimg, g.CI, g.Hi, g.Wi, h0, w0, ca, it0);
-            else stager.load(sg, in, (unsigned)n0 * imin, (unsigned)g.N * imin, nimg, g.CI, g.Hi, g.Wi, h0, ca, it0);
+            stager.load(sg, in, (unsigned)n0 * imin, (unsigned)g.N * imin, nimg, g.CI, g.Hi, g.Wi, h0, w0, ca, it0);
         }
     };
 
     load_tile(part, 0);
     // zeros: entries that pair different groups, inputs beside the group, outputs beside the tensor; pixels beside the rows
     Finite<T> wseen;
-    const FilterLoader<T, NHWC, BWD> fl(g, ob, slots);
-    const bool vectors = FAST && FilterLoader<T, NHWC, BWD>::takes(g) && fl.nvec <= nfrag;       // (see there)
+    const FilterLoader<T, NHWC, BWD, FAST> fl(g, ob, slots);
+    const bool vectors = FAST && FilterLoader<T, NHWC, BWD, FAST>::takes(g) && fl.nvec <= (NHWC ? nfrag : nfrag * 3 / 2);       // (see there)
     if (vectors && g.packed)
-        for (int i = threadIdx.x; i < nfrag * 4 / VE; i += 256) reinterpret_cast<u4v_t *>(lw)[i] = u4v_t{0u, 0u, 0u, 0u};
-    if (!NHWC && FAST)
+        for (int i = threadIdx.x; i < g.NS * KK * g.nk * (4 * QUAD) * 4 / VE; i += 256) reinterpret_cast<u4v_t *>(lw)[i] = u4v_t{0u, 0u, 0u, 0u};
+    if (!NHWC && FAST == 1)
         for (int i = threadIdx.x; i < (g.TN * g.LH * g.LW * g.pitch + VE - 1) / VE; i += 256) reinterpret_cast<u4v_t *>(lx)[i] = u4v_t{0u, 0u, 0u, 0u};
     if (OS > 1 && (int)threadIdx.x < KK) {
         const int kh = (int)threadIdx.x / K, kw = (int)threadIdx.x - kh * K, f = kh % OS, e = kw % OS;
@@ -585,11 +631,14 @@ __global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg,
     }
     if (!NHWC || g.packed || OS > 1) __syncthreads();
     if (vectors) {
+        constexpr int FB = 2;                                              // vectors of a lane in flight (four: the same)
 #pragma unroll 1
-        for (int i0 = threadIdx.x; i0 - (int)threadIdx.x < fl.nvec; i0 += 512) {
-            const u4raw_t q0 = fl.load(w, i0), q1 = fl.load(w, i0 + 256);
-            fl.put(reinterpret_cast<T *>(lw), i0, q0, wseen);
-            fl.put(reinterpret_cast<T *>(lw), i0 + 256, q1, wseen);
+        for (int i0 = threadIdx.x; i0 - (int)threadIdx.x < fl.nvec; i0 += FB * 256) {
+            u4raw_t q[FB];
+#pragma unroll
+            for (int b = 0; b < FB; ++b) q[b] = fl.load(w, i0 + b * 256);
+#pragma unroll
+            for (int b = 0; b < FB; ++b) fl.put(reinterpret_cast<T *>(lw), i0 + b * 256, q[b], wseen);
         }
     } else {
         // four entries of a fragment at a time, in operand order
@@ -616,7 +665,7 @@ __global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg,
                 q.v = make_uint2((uint32_t)e[0] | (uint32_t)e[1] << 16, (uint32_t)e[2] | (uint32_t)e[3] << 16);
                 wseen.add(q.v.x); wseen.add(q.v.y);
             }
-            lw[slots ? ((s * KK + slots[tap]) * g.nk + kc) * 64 + ln : i] = q;
+            lw[((s * KK + (slots ? slots[tap] : tap)) * g.nk + kc) * (4 * QUAD) + (ln >> 4) * QUAD + (ln & 15)] = q;
         }
     }
     const bool wbad = wseen.bad();
@@ -681,7 +730,7 @@ __global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg,
                     if (OS > 1) { row0[p] = tabr[t]; col0[p] = tabr[nent + t]; }
                 }
             }
-            const Frag<T> *pw = lw + s * KK * g.nk * 64 + lane;
+            const Frag<T> *pw = lw + s * KK * g.nk * (4 * QUAD) + lk * QUAD + li;
             for (int f = 0; f < OS; ++f)
                 for (int e0 = 0; e0 < OS; e0 += E) {
                     v4f acc[E][P];
@@ -700,19 +749,34 @@ __global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg,
                             if (++kc == g.nk) { kc = 0; x += xs; if (++l == nl) { l = 0; x += rs; } }
                             return at;
                         };
-#pragma unroll 1
-                        for (; i + 1 < n; i += 2, pw += 128) {
-                            const Frag<T> a0 = pw[0], a1 = pw[64];
-                            const int x0 = next(), x1 = next();
-                            Frag<T> b0[P], b1[P];
+                        // (U pairs at a time: their reads are under way together)
+                        constexpr int U = E * P * (int)sizeof(T) <= 8 ? 2 : 1;
+                        auto pairs_of = [&](auto count) {
+                            constexpr int U = decltype(count)::value;
+                            Frag<T> a0[U], a1[U], b0[U][P], b1[U][P];
 #pragma unroll
-                            for (int p = 0; p < P; ++p) {
-                                b0[p] = *reinterpret_cast<const Frag<T> *>(lx + base[p] + x0);
-                                b1[p] = *reinterpret_cast<const Frag<T> *>(lx + base[p] + x1);
+                            for (int u = 0; u < U; ++u) {
+                                a0[u] = pw[u * 2 * (4 * QUAD)]; a1[u] = pw[(u * 2 + 1) * (4 * QUAD)];
+                                const int x0 = next(), x1 = next();
+#pragma unroll
+                                for (int p = 0; p < P; ++p) {
+                                    b0[u][p] = *reinterpret_cast<const Frag<T> *>(lx + base[p] + x0);
+                                    b1[u][p] = *reinterpret_cast<const Frag<T> *>(lx + base[p] + x1);
+                                }
                             }
 #pragma unroll
-                            for (int p = 0; p < P; ++p) acc[e][p] = OUTER ? mma32(a0, a1, b0[p], b1[p], acc[e][p]) : mma32(b0[p], b1[p], a0, a1, acc[e][p]);
+                            for (int u = 0; u < U; ++u)
+#pragma unroll
+                                for (int p = 0; p < P; ++p)
+                                    acc[e][p] = OUTER ? mma32(a0[u], a1[u], b0[u][p], b1[u][p], acc[e][p]) : mma32(b0[u][p], b1[u][p], a0[u], a1[u], acc[e][p]);
+                            i += 2 * U; pw += 2 * (4 * QUAD) * U;
+                        };
+                        if constexpr (U > 1) {
+#pragma unroll 1
+                            while (i + 2 * U <= n) pairs_of(std::integral_constant<int, U>());
                         }
+#pragma unroll 1
+                        while (i + 1 < n) pairs_of(std::integral_constant<int, 1>());
                         if (i < n) {
                             const Frag<T> a0 = *pw;
                             Frag<T> b0[P];
@@ -720,7 +784,7 @@ __global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg,
                             for (int p = 0; p < P; ++p) b0[p] = *reinterpret_cast<const Frag<T> *>(lx + base[p] + x + kc * 16);
 #pragma unroll
                             for (int p = 0; p < P; ++p) acc[e][p] = OUTER ? mma16(a0, b0[p], acc[e][p]) : mma16(b0[p], a0, acc[e][p]);
-                            pw += 64;
+                            pw += CHUNK;
                         }
                     }
                     // the outputs at a position's column and (E = 2) the next one
@@ -746,7 +810,8 @@ __global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg,
                             }
                             T *po = on + (unsigned)(at + o);
                             const float r[4] = {acc[0][p][0], acc[0][p][1], acc[0][p][2], acc[0][p][3]};
-                            if (FAST || g.CO % 4 == 0) Vec<T, 4>::store(po, r);
+                            if (FAST == 1 || g.CO % 4 == 0) Vec<T, 4>::store(po, r);
+                            else if (o + 3 < g.CO) store_run<T, 4>(po, acc[0][p]);
                             else {
 #pragma unroll
                                 for (int k = 0; k < 4; ++k) if (o + k < g.CO) stf(po + k, r[k]);
@@ -804,7 +869,7 @@ __device__ __forceinline__ v4s read_transposed(const bf16_t *p)
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s *)p);
 }
 
-template <typename T, bool NHWC, bool FAST, int K>
+template <typename T, bool NHWC, int FAST, int K>
 __global__ __launch_bounds__(256, K > 3 ? 2 : sizeof(T) == 4 ? 3 : 4) void k_gconv_gemm_filter(GemmGeom g, StageGeom sx, StageGeom sy, const T *__restrict__ x,
                                                                             const T *__restrict__ dy, float *__restrict__ ws, int npair, int nparts,
                                                                             int J, unsigned nblocks)
@@ -832,16 +897,14 @@ __global__ __launch_bounds__(256, K > 3 ? 2 : sizeof(T) == 4 ? 3 : 4) void k_gco
         n0 = tn * g.TN; a0 = (row - tn * g.ta) * g.TA; b0 = (tile - row * g.tb) * g.TB;
     };
     constexpr int BT = NHWC ? 4 : sizeof(T) == 2 && K <= 3 ? 2 : 1;        // items of a lane in flight
-    [[maybe_unused]] Stager<T, NHWC, BT> stx(sx), sty(sy);
+    [[maybe_unused]] Stager<T, NHWC, FAST, BT> stx(sx), sty(sy);
     auto load_x = [&](int n0, int a0, int b0, int it0) {
         const int nimg = min(g.TN, g.N - n0), h0 = g.IS * a0 - g.ip, w0 = g.IS * b0 - g.ip;
-        if constexpr (NHWC) stx.load(sx, BufView(x + (size_t)n0 * imx, (uint32_t)nimg * imx * (uint32_t)sizeof(T)), nimg, g.CI, g.Hi, g.Wi, h0, w0, cxa, it0);
-        else stx.load(sx, x, (unsigned)n0 * imx, (unsigned)g.N * imx, nimg, g.CI, g.Hi, g.Wi, h0, cxa, it0);
+        stx.load(sx, x, (unsigned)n0 * imx, (unsigned)g.N * imx, nimg, g.CI, g.Hi, g.Wi, h0, w0, cxa, it0);
     };
     auto load_y = [&](int n0, int a0, int b0, int it0) {
         const int nimg = min(g.TN, g.N - n0);
-        if constexpr (NHWC) sty.load(sy, BufView(dy + (size_t)n0 * imy, (uint32_t)nimg * imy * (uint32_t)sizeof(T)), nimg, g.CO, g.Ho, g.Wo, a0, b0, cya, it0);
-        else sty.load(sy, dy, (unsigned)n0 * imy, (unsigned)g.N * imy, nimg, g.CO, g.Ho, g.Wo, a0, cya, it0);
+        sty.load(sy, dy, (unsigned)n0 * imy, (unsigned)g.N * imy, nimg, g.CO, g.Ho, g.Wo, a0, b0, cya, it0);
     };
     if constexpr (FAST) {
         int n0, a0, b0;
@@ -854,7 +917,7 @@ __global__ __launch_bounds__(256, K > 3 ? 2 : sizeof(T) == 4 ? 3 : 4) void k_gco
         tab[p] = ((im * g.LH + g.IS * da) * g.LW + g.IS * db) * g.pitch;
     }
     // beside the rows of x (NCHW) and behind the positions of dy: zeros
-    if (!NHWC && FAST)
+    if (!NHWC && FAST == 1)
         for (int i = threadIdx.x; i < g.TN * g.LH * g.LW * g.pitch / 4; i += 256) reinterpret_cast<Frag<T> *>(lx)[i].v = decltype(Frag<T>::v){};
     for (int i = threadIdx.x; i < (steps * STEP - npos) * pitchy; i += 256) ly[npos * pitchy + i] = T(0);
     // fp32: the 16 positions of a step are added up on their own before they join a sum.  A chain of n matrix instructions has a relative error of
@@ -1051,10 +1114,10 @@ void pick_positions(GemmGeom &g, int want, int maxb, int quad = 1)
     g.tn = cdivg(g.N, g.TN); g.ta = cdivg(g.na, g.TA); g.tb = cdivg(g.nb, g.TB);
 }
 
-struct GemmPlan { GemmGeom g; StageGeom sg, sy; size_t lds; int nparts; unsigned nblocks; int npair, CLy, pitchy; bool fast; };
+struct GemmPlan { GemmGeom g; StageGeom sg, sy; size_t lds; int nparts; unsigned nblocks; int npair, CLy, pitchy, fast; };
 
 // copying a tile of TN images of LH x LW pixels and CL channels (NCHW: rows of W columns) with 256 lanes
-StageGeom stage_geom(int layout, int VE, int TN, int LH, int LW, int CL, int pitch, int W)
+StageGeom stage_geom(int layout, int VE, int TN, int LH, int LW, int CL, int pitch, int W, bool split)
 {
     StageGeom s = {};
     const bool nhwc = layout == LAYOUT_NHWC;
@@ -1062,7 +1125,8 @@ StageGeom stage_geom(int layout, int VE, int TN, int LH, int LW, int CL, int pit
     s.imrows = TN * LH;
     s.rows = nhwc ? s.imrows : s.imrows * (CL / 4);
     s.nv = nhwc ? CL / VE : 1;
-    const int width = nhwc ? LW : cdivg(W, 4);                              // columns, or runs of four
+    const int width = nhwc ? LW : cdivg(split ? LW + 3 : W, 4);             // columns, or runs of four
+    s.width = width;
     const int most = 256 / s.nv > 0 ? 256 / s.nv : 1, passes = cdivg(width, most);
     s.cols = cdivg(width, passes);
     s.per = s.cols * s.nv;
@@ -1113,7 +1177,7 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
                 pick_positions(g, want, layout == LAYOUT_NHWC ? 32 : 64, pairs ? 4 : 1);
                 g.LH = g.IS * (g.TA - 1) + reach; g.LW = g.IS * (g.TB - 1) + reach + g.shift;
                 // (positions in the tables up to a multiple of 64)
-                pl->lds = (size_t)ns * q.K * q.K * g.nk * 64 * 4 * esz + (size_t)cdivg(g.TN * g.TA * g.TB, 64) * 64 * (g.OS > 1 ? 16 : 8) + (g.OS > 1 ? 256 : 0) + 16 +
+                pl->lds = (size_t)ns * q.K * q.K * g.nk * 16 * (layout == LAYOUT_NHWC ? quad_of<true>() : quad_of<false>()) * esz + (size_t)cdivg(g.TN * g.TA * g.TB, 64) * 64 * (g.OS > 1 ? 16 : 8) + (g.OS > 1 ? 256 : 0) + 16 +
                           ((size_t)g.TN * g.LH * g.LW * g.pitch * esz + 15) / 16 * 16;
             };
             int want = widest_tile(tile, 256, 16, 4, LDS_OF_TWO, &pl->lds);
@@ -1199,15 +1263,20 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
     g.rCgi = 1.0f / (float)g.Cgi; g.rCgo = 1.0f / (float)g.Cgo; g.rKK = 1.0f / (float)(q.K * q.K); g.rnk = 1.0f / (float)g.nk;
     g.rTA = 1.0f / (float)g.TA; g.rTB = 1.0f / (float)g.TB;
     g.rta = 1.0f / (float)g.ta; g.rtb = 1.0f / (float)g.tb;
-    // whole vectors of channels, or whole rows; the images of a tile below 2 GiB and 2^24 pixels, for the staging's offsets and products
+    // whole vectors of channels, or whole rows, or neither; the images of a tile below 2 GiB and 2^24 pixels, for the staging's offsets and products
     const long long inpix = (long long)g.TN * g.Hi * g.Wi, outpix = (long long)g.TN * g.Ho * g.Wo;
-    pl->fast = (layout == LAYOUT_NHWC ? q.C % VE == 0 && q.O % VE == 0 : g.tb == 1) && inpix < 1 << 24 && outpix < 1 << 24 &&
+    pl->fast = (layout == LAYOUT_NHWC ? q.C % VE == 0 && q.O % VE == 0 : g.tb == 1) ? 1 : 2;
+    const bool small = inpix < 1 << 24 && outpix < 1 << 24 &&
                inpix * g.CI * esz < 1ll << 31 && outpix * g.CO * esz < 1ll << 31 && (long long)g.tn * g.ta * g.tb < 1 << 21;
-    pl->sg = stage_geom(layout, VE, g.TN, g.LH, g.LW, g.CL, g.pitch, g.Wi);
-    if (pass == 2) pl->sy = stage_geom(layout, VE, g.TN, g.TA, g.TB, pl->CLy, pl->pitchy, g.Wo);
-    // as many lanes as a pixel has vectors; four elements for the unaligned loads of the NCHW staging
-    pl->fast = pl->fast && pl->sg.per <= 256 && (pass < 2 || pl->sy.per <= 256) && (long long)g.N * g.CI * g.Hi * g.Wi >= 4 &&
-               (long long)g.N * g.CO * g.Ho * g.Wo >= 4;
+    pl->sg = stage_geom(layout, VE, g.TN, g.LH, g.LW, g.CL, g.pitch, g.Wi, g.tb > 1);
+    if (pass == 2) pl->sy = stage_geom(layout, VE, g.TN, g.TA, g.TB, pl->CLy, pl->pitchy, g.Wo, g.tb > 1);
+    // as many lanes as a pixel has vectors; a vector's elements for the unaligned loads
+    const bool stageable = small && pl->sg.per <= 256 && (pass < 2 || pl->sy.per <= 256) && (long long)g.N * g.CI * g.Hi * g.Wi >= 8 &&
+                           (long long)g.N * g.CO * g.Ho * g.Wo >= 8;
+    if (!stageable) pl->fast = 0;
+    // (tiles narrower than the rows, filter gradient in fp32: four loads of a lane, each of 64 lanes in a row, are the shorter way; us, 376x127x127 in 188
+    // groups 40 against 46)
+    if (pass == 2 && layout == LAYOUT_NCHW && dtype == DT_F32 && pl->fast == 2) pl->fast = 0;
     pl->g = g;
     return true;
 }
@@ -1244,7 +1313,7 @@ double gconv_gemm_us(const GGeom &q, int layout, int dtype, int pass)
     GemmPlan pl;
     if (!gemm_plan(q, layout, dtype, pass, &pl)) return 1e30;
     const GemmGeom &g = pl.g;
-    const float *c = fit[pass][layout == LAYOUT_NHWC][dtype != DT_F32][pl.fast];
+    const float *c = fit[pass][layout == LAYOUT_NHWC][dtype != DT_F32][pl.fast != 0];
     const int tiles = cdivg(g.tn * g.ta * g.tb, pl.nparts), tiles16 = cdivg(g.TN * g.TA * g.TB, 16), P = tiles_at_once(g.NS, g.TN * g.TA * g.TB, dtype);
     const double resident = resident_blocks(pl.lds, 4), cu = pl.nblocks / 256.0;
     const double rounds = pl.nblocks > resident ? pl.nblocks / resident : 1.0, beside = cu < 1 ? 1 : cu > resident / 256 ? resident / 256 : cu;
@@ -1273,15 +1342,17 @@ template <typename T, bool NHWC>
 static hipError_t gemm_go(const GemmPlan &pl, const void *in, const void *w, void *out, hipStream_t st)
 {
     constexpr bool NCHW = !NHWC;
-    auto pick = [&](auto p) {
-        constexpr int P = decltype(p)::value;
-        return !pl.g.bwd ? (pl.fast ? k_gconv_gemm<T, NHWC, false, true, P, 1, false> : k_gconv_gemm<T, NHWC, false, false, P, 1, false>)
-               : pl.g.pairs ? k_gconv_gemm<T, NHWC, true, true, P, (NCHW ? 2 : 1), false>
-               : pl.g.OS > 1 ? (pl.fast ? k_gconv_gemm<T, NHWC, true, true, P, 1, NCHW> : k_gconv_gemm<T, NHWC, true, false, P, 1, NCHW>)
-               : pl.fast ? k_gconv_gemm<T, NHWC, true, true, P, 1, false> : k_gconv_gemm<T, NHWC, true, false, P, 1, false>;
+    auto pick = [&](auto p, auto fast) {
+        constexpr int P = decltype(p)::value, FAST = decltype(fast)::value;
+        return !pl.g.bwd ? k_gconv_gemm<T, NHWC, false, FAST, P, 1, false>
+               : pl.g.pairs ? k_gconv_gemm<T, NHWC, true, FAST, P, (NCHW && FAST ? 2 : 1), false>
+               : pl.g.OS > 1 ? k_gconv_gemm<T, NHWC, true, FAST, P, 1, NCHW> : k_gconv_gemm<T, NHWC, true, FAST, P, 1, false>;
     };
     const int P = tiles_at_once(pl.g.NS, pl.g.TN * pl.g.TA * pl.g.TB, sizeof(T) == 4 ? DT_F32 : DT_BF16);
-    auto kernel = P == 4 ? pick(std::integral_constant<int, 4>()) : P == 2 ? pick(std::integral_constant<int, 2>()) : pick(std::integral_constant<int, 1>());
+    auto of = [&](auto fast) {
+        return P == 4 ? pick(std::integral_constant<int, 4>(), fast) : P == 2 ? pick(std::integral_constant<int, 2>(), fast) : pick(std::integral_constant<int, 1>(), fast);
+    };
+    auto kernel = pl.fast == 1 ? of(std::integral_constant<int, 1>()) : pl.fast ? of(std::integral_constant<int, 2>()) : of(std::integral_constant<int, 0>());
     hipLaunchKernelGGL(kernel, dim3(pl.nblocks), dim3(256), pl.lds, st, pl.g, pl.sg, (const T *)in, (const T *)w, (T *)out,
                        pl.nparts, pl.nblocks);
     return hipGetLastError();
@@ -1298,8 +1369,11 @@ template <typename T, bool NHWC>
 static hipError_t gemm_filter_go(const GemmPlan &pl, const void *x, const void *dy, float *ws, hipStream_t st)
 {
     const int J = pl.g.FO * pl.g.FCg * pl.g.K * pl.g.K;
-    auto kernel = pl.fast ? (pl.g.K == 1 ? k_gconv_gemm_filter<T, NHWC, true, 1> : pl.g.K == 3 ? k_gconv_gemm_filter<T, NHWC, true, 3> : k_gconv_gemm_filter<T, NHWC, true, 5>)
-                          : (pl.g.K == 1 ? k_gconv_gemm_filter<T, NHWC, false, 1> : pl.g.K == 3 ? k_gconv_gemm_filter<T, NHWC, false, 3> : k_gconv_gemm_filter<T, NHWC, false, 5>);
+    auto of = [&](auto fast) {
+        constexpr int FAST = decltype(fast)::value;
+        return pl.g.K == 1 ? k_gconv_gemm_filter<T, NHWC, FAST, 1> : pl.g.K == 3 ? k_gconv_gemm_filter<T, NHWC, FAST, 3> : k_gconv_gemm_filter<T, NHWC, FAST, 5>;
+    };
+    auto kernel = pl.fast == 1 ? of(std::integral_constant<int, 1>()) : pl.fast ? of(std::integral_constant<int, 2>()) : of(std::integral_constant<int, 0>());
     hipLaunchKernelGGL(kernel, dim3(pl.nblocks), dim3(256), pl.lds, st, pl.g, pl.sg, pl.sy, (const T *)x, (const T *)dy, ws, pl.npair,
                        pl.nparts, J, pl.nblocks);
     return hipGetLastError();
