@@ -268,7 +268,31 @@ static bool gemm_over_rowwalk(const GGeom &g, int layout, int dtype, int pass)
 {
     if (dtype != DT_F32) return true;
     if (pass == 2) return !(g.Cg == 16 && (long long)g.N * g.Ho * g.Wo >= 16384);
-    return gconv_gemm_us(g, layout, dtype, pass) * 0.8 < gconv_nchw_s1_us(g, pass == 1);
+    // (above 64 channels one block fits a compute unit, and the estimate is nearer)
+    return gconv_gemm_us(g, layout, dtype, pass) * (g.Cg > 64 ? 0.95 : 0.8) < gconv_nchw_s1_us(g, pass == 1);
+}
+
+// In place of the other row walks, whose lanes are few in short launches (a lane walks 7 to 28 rows of all its group's input channels) and, NHWC with eight channels
+// a group, many registers; in bf16 they widen every value.  Measured over 1500 random layers of 2 to 64 channels a group, up to 16 M outputs, walk
+// against these: NCHW forward and input gradient, bf16 0.27 and 0.31 of the time, 2 % longer (two channels a group, 12.7 M outputs 27.5 -> 30.8 us), fp32 0.45 up
+// to 2.5 M outputs, none longer, from 3.4 M on 1.4 to 2.5 times as long; filter gradient, bf16 0.67, of odd groups, whose walk takes one output channel at
+// a time, 1.1 to 1.3 times as long, fp32 with four output channels at a time 0.7 below 1 M and up to 1.6 from 3.4 M on.  NHWC forward and input gradient with
+// eight channels 0.4 to 0.9 in bf16, 0.6 to 0.9 in fp32 (up to 2.7 M); with two and four 0.8 to 1.8 and 1.0 to 2.5: they stay.  NHWC filter gradient in
+// bf16 0.28 to 0.96; fp32 with eight channels 0.38 to 0.97 below 1 M, 1.1 to 1.3 above.
+static bool gemm_over_walk(const GGeom &g, int dtype, int pass, int variant, long long outputs)
+{
+    const bool f32 = dtype == DT_F32;
+    if (tune_active()) return false;                             // forced tilings are those of the walks
+    if (variant == GV_NCHW_K3S1) {
+        if (pass < 2) return f32 ? outputs < 2000000 : !(g.Cg == 2 && outputs > 8000000);
+        return g.Og % 4 == 0 || (!f32 && g.Og % 2 == 0 && g.Cg >= 6) ? !f32 || outputs < 1000000 : false;
+    }
+    if (variant == GV_NHWC_K3S1) {
+        if (pass < 2) return g.Cg == 8 && g.Og == 8 && !gconv_nhwc_mfma_supported(g, dtype) && (!f32 || outputs < 2700000);
+        return f32 ? g.Cg == 8 && outputs < 1000000 : g.Cg > 2 || outputs < 1300000;
+    }
+    if (variant == GV_NHWC_BWD_FILTER_S2) return !f32 && outputs >= 8192 && (g.Cg == 8 || outputs < 1000000);
+    return false;
 }
 
 static GPlan gplan(const GGeom &g, int layout, int dtype, int pass)
@@ -328,8 +352,11 @@ static GPlan gplan(const GGeom &g, int layout, int dtype, int pass)
     // group, 512 channels, fp32 batch 64: 62 -> 45 us; 32 channels at batch 4: 53 -> 15): the 16x16 matrix instructions
     const bool rowwalk16 = pl.variant == GV_NCHW_K3S1 && g.Cg % 16 == 0 && g.Og % 16 == 0;
     const long long outputs = (long long)g.N * (pass == 1 ? (long long)g.C * g.H * g.W : (long long)g.O * g.Ho * g.Wo);
-    if ((pl.variant == GV_GENERIC || rowwalk16) && outputs >= 2048 && gconv_gemm_supported(g, layout, dtype, pass) &&
-        (tune_env("DWCONV_TUNE_GROUP_GEMM") || (rowwalk16 ? gemm_over_rowwalk(g, layout, dtype, pass) : gemm_over_generic(g, layout, dtype, pass)))) {
+    const bool walk = !rowwalk16 && gemm_over_walk(g, dtype, pass, pl.variant, outputs);
+    // (fewer outputs: only of many products, which a lane of the generic kernels adds up one after the other: 4x4x96 in three groups, 5x5, 99 us)
+    const bool enough = outputs >= 2048 || (pl.variant == GV_GENERIC && (pass == 1 ? g.Og : g.Cg) * g.K * g.K >= 256);
+    if ((pl.variant == GV_GENERIC || rowwalk16 || walk) && enough && gconv_gemm_supported(g, layout, dtype, pass) &&
+        (walk || tune_env("DWCONV_TUNE_GROUP_GEMM") || (rowwalk16 ? gemm_over_rowwalk(g, layout, dtype, pass) : gemm_over_generic(g, layout, dtype, pass)))) {
         pl.variant = GV_GEMM;
         pl.name = pass == 0 ? "group_mfma16" : pass == 1 ? "group_mfma16_bwd_data" : "group_mfma16_bwd_filter";
         if (pass == 2) pl.parts = gconv_gemm_parts(g, layout, dtype);

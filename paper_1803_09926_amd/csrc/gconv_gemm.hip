@@ -1298,7 +1298,7 @@ bool gconv_gemm_supported(const GGeom &g, int layout, int dtype, int pass)
 
 // Laying out the filter (768 fragments a time), then for every tile of the block a fixed latency, the staging (4 KiB a time) and the products of
 // its longest wavefront, each with a part that grows with the blocks on a compute unit, and the classes of output pixels.  Fitted to 33 000
-// random layers: four of five between 0.87 and 1.15 times the measured time.
+// random layers before filters and ragged tiles came in vectors: four of five between 0.87 and 1.15 times the time of then, which is up to a third longer.
 double gconv_gemm_us(const GGeom &q, int layout, int dtype, int pass)
 {
     static const float fit[2][2][2][2][7] = {                               // [pass][layout][dtype][fast]
@@ -1313,7 +1313,7 @@ double gconv_gemm_us(const GGeom &q, int layout, int dtype, int pass)
     GemmPlan pl;
     if (!gemm_plan(q, layout, dtype, pass, &pl)) return 1e30;
     const GemmGeom &g = pl.g;
-    const float *c = fit[pass][layout == LAYOUT_NHWC][dtype != DT_F32][pl.fast != 0];
+    const float *c = fit[pass][layout == LAYOUT_NHWC][dtype != DT_F32][pl.fast == 1];
     const int tiles = cdivg(g.tn * g.ta * g.tb, pl.nparts), tiles16 = cdivg(g.TN * g.TA * g.TB, 16), P = tiles_at_once(g.NS, g.TN * g.TA * g.TB, dtype);
     const double resident = resident_blocks(pl.lds, 4), cu = pl.nblocks / 256.0;
     const double rounds = pl.nblocks > resident ? pl.nblocks / resident : 1.0, beside = cu < 1 ? 1 : cu > resident / 256 ? resident / 256 : cu;
