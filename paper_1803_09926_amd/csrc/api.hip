@@ -94,8 +94,9 @@ int dwconv_bwd_filter(const dwconv_desc *desc, const void *x, const void *dy, vo
     const size_t need = (size_t)pl.parts * (size_t)g.O * g.K * g.K * sizeof(float);
     if (!workspace || workspace_bytes < need) return DWCONV_ERR_WORKSPACE;
     if (misaligned(workspace)) return DWCONV_ERR_ALIGN;
-    hipError_t e = launch_bwd_filter(pl, g, desc->layout, desc->dtype, x, dy, (float *)workspace, (hipStream_t)stream);
-    if (e != hipSuccess) return DWCONV_ERR_LAUNCH;
+    const bool final = sums_are_final(pl);
+    hipError_t e = launch_bwd_filter(pl, g, desc->layout, desc->dtype, x, dy, (float *)(final ? dw : workspace), (hipStream_t)stream);
+    if (final || e != hipSuccess) return e == hipSuccess ? DWCONV_OK : DWCONV_ERR_LAUNCH;
     e = launch_reduce(pl, g, desc->layout, desc->dtype, x, dy, (const float *)workspace, (float *)dw, (hipStream_t)stream);
     return e == hipSuccess ? DWCONV_OK : DWCONV_ERR_LAUNCH;
 }
@@ -145,8 +146,9 @@ int dwconv_bwd(const dwconv_desc *desc, const void *x, const void *dy, const voi
     const size_t need = (size_t)pl.parts * (size_t)g.O * g.K * g.K * sizeof(float);
     if (!workspace || workspace_bytes < need) return DWCONV_ERR_WORKSPACE;
     if (misaligned(workspace)) return DWCONV_ERR_ALIGN;
-    hipError_t e = launch_bwd_fused(pl, g, desc->layout, desc->dtype, x, dy, w, dx, (float *)workspace, (hipStream_t)stream);
-    if (e != hipSuccess) return DWCONV_ERR_LAUNCH;
+    const bool final = sums_are_final(pl);
+    hipError_t e = launch_bwd_fused(pl, g, desc->layout, desc->dtype, x, dy, w, dx, (float *)(final ? dw : workspace), (hipStream_t)stream);
+    if (final || e != hipSuccess) return e == hipSuccess ? DWCONV_OK : DWCONV_ERR_LAUNCH;
     e = launch_reduce(pl, g, desc->layout, desc->dtype, x, dy, (const float *)workspace, (float *)dw, (hipStream_t)stream);
     return e == hipSuccess ? DWCONV_OK : DWCONV_ERR_LAUNCH;
 }

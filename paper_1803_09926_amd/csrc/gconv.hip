@@ -4,6 +4,7 @@
 // are the depthwise layer and run on its kernels.
 #include "../../include/dwconv.h"
 #include "gconv.hpp"
+#include "short_filter.hpp"
 #include <math.h>
 
 namespace dwc {
@@ -361,6 +362,9 @@ static GPlan gplan(const GGeom &g, int layout, int dtype, int pass)
         pl.name = pass == 0 ? "group_mfma16" : pass == 1 ? "group_mfma16_bwd_data" : "group_mfma16_bwd_filter";
         if (pass == 2) pl.parts = gconv_gemm_parts(g, layout, dtype);
     }
+    // (under the name of the family that takes the shape in longer launches)
+    const FilterWay way = pl.variant == GV_GEMM ? FILTER_MATRIX : pl.variant == GV_GENERIC && pl.parts == 1 ? FILTER_GENERIC_ONE : FILTER_TWO;
+    if (pass == 2 && pl.variant != GV_NCHWS_MFMA_BWD_FILTER && short_bwd_filter_shorter(g, layout, way)) { pl.variant = GV_SHORT_BWD_FILTER; pl.parts = 1; }
     // a tuned filter gradient whose partial sums would not fit in 64 MiB (very wide rows): the generic kernels
     if (pass == 2 && pl.variant != GV_GENERIC && (long long)pl.parts * g.O * g.Cg * g.K * g.K * 4 > (64ll << 20)) {
         const GPlan gen = {GV_GENERIC, gconv_generic_bwd_filter_parts(g), 0, 0, 0, "group_generic"};
@@ -498,7 +502,10 @@ int gconv_bwd_filter(const dwconv_group_desc *desc, const void *x, const void *d
     if (!workspace || workspace_bytes < need) return DWCONV_ERR_WORKSPACE;
     if (gmisaligned(workspace)) return DWCONV_ERR_ALIGN;
     hipError_t e;
-    if (pl.variant == GV_NCHWS_K3S1) e = nchws_group_bwd_filter(as_geom(g), g.Cg, desc->dtype, x, dy, (float *)workspace, pl.a, pl.c, (hipStream_t)stream);
+    const bool final = pl.parts == 1 && pl.variant != GV_GEMM;             // a kernel without products of padding: its sums are the gradient
+    if (final) workspace = dw;
+    if (pl.variant == GV_SHORT_BWD_FILTER) e = short_bwd_filter(g, desc->layout, desc->dtype, x, dy, (float *)workspace, (hipStream_t)stream);
+    else if (pl.variant == GV_NCHWS_K3S1) e = nchws_group_bwd_filter(as_geom(g), g.Cg, desc->dtype, x, dy, (float *)workspace, pl.a, pl.c, (hipStream_t)stream);
     else if (pl.variant == GV_NCHWS_MFMA_BWD_FILTER) e = gconv_nchws_mfma_bwd_filter(g, desc->dtype, false, x, dy, (float *)workspace, pl.parts, (hipStream_t)stream);
     else if (pl.variant == GV_NHWC_TR_BWD_FILTER) e = gconv_nhwc_tr_bwd_filter(g, desc->dtype, x, dy, (float *)workspace, pl.parts, (hipStream_t)stream);
     else if (pl.variant == GV_NHWC_LDS_MFMA_BWD_FILTER) e = gconv_nchws_mfma_bwd_filter(g, desc->dtype, true, x, dy, (float *)workspace, pl.parts, (hipStream_t)stream);
@@ -507,7 +514,7 @@ int gconv_bwd_filter(const dwconv_group_desc *desc, const void *x, const void *d
     else if (pl.variant == GV_NHWC_K3S1) e = gconv_nhwc_bwd_filter(g, desc->dtype, x, dy, (float *)workspace, pl.parts, (hipStream_t)stream);
     else if (pl.variant == GV_GEMM) e = gconv_gemm_bwd_filter(g, desc->layout, desc->dtype, x, dy, (float *)workspace, (hipStream_t)stream);
     else e = gconv_generic_bwd_filter(g, desc->layout, desc->dtype, x, dy, (float *)workspace, pl.parts, (hipStream_t)stream);
-    if (e != hipSuccess) return DWCONV_ERR_LAUNCH;
+    if (final || e != hipSuccess) return e == hipSuccess ? DWCONV_OK : DWCONV_ERR_LAUNCH;
     if (pl.variant == GV_GEMM) {
         FilterGradSrc src = {x, dy, desc->dtype, desc->layout, g.N, g.C, g.H, g.W, g.K, g.s, g.p, g.O, g.Cg, g.Og, g.Ho, g.Wo};
         gconv_gemm_filter_tiles(g, desc->layout, desc->dtype, &src);

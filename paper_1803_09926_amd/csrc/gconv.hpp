@@ -12,7 +12,7 @@ struct GGeom {
     int Ho, Wo;
 };
 
-enum GVariant { GV_GENERIC = 0, GV_NCHW_K3S1, GV_NHWC_K3S1, GV_NCHWS_K3S1, GV_NHWC_MFMA_S2, GV_NHWC_BWD_FILTER_S2, GV_NCHWS_MFMA_BWD_FILTER, GV_NCHWS_MFMA_FWD, GV_NHWC_LDS_MFMA_BWD_FILTER, GV_NHWC_TR_BWD_FILTER, GV_GEMM };
+enum GVariant { GV_GENERIC = 0, GV_NCHW_K3S1, GV_NHWC_K3S1, GV_NCHWS_K3S1, GV_NHWC_MFMA_S2, GV_NHWC_BWD_FILTER_S2, GV_NCHWS_MFMA_BWD_FILTER, GV_NCHWS_MFMA_FWD, GV_NHWC_LDS_MFMA_BWD_FILTER, GV_NHWC_TR_BWD_FILTER, GV_GEMM, GV_SHORT_BWD_FILTER };
 
 struct GPlan {
     int variant;

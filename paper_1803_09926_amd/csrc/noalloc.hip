@@ -43,6 +43,8 @@ extern "C" int dwconv_bwd_filter_noalloc(const dwconv_desc *desc, const void *x,
     const Plan pl = plan_bwd_filter(g, desc->layout, desc->dtype);
     const size_t need = (size_t)pl.parts * (size_t)g.O * g.K * g.K * sizeof(float);
     if (need > (size_t)DWCONV_NOALLOC_SCRATCH_BYTES) return DWCONV_ERR_SCRATCH;
+    if (sums_are_final(pl))
+        return launch_bwd_filter(pl, g, desc->layout, desc->dtype, x, dy, (float *)dw, (hipStream_t)stream) == hipSuccess ? DWCONV_OK : DWCONV_ERR_LAUNCH;
     float *ws = nullptr;
     const int ra = scratch_address(&ws);
     if (ra != DWCONV_OK) return ra;

@@ -1,5 +1,6 @@
 // Variant selection and launch dispatch.
 #include "plan.hpp"
+#include "short_filter.hpp"
 #include <stdlib.h>
 
 namespace dwc {
@@ -291,6 +292,14 @@ static bool plan_bwd_filter_nchwd(const Geom &g, int dtype, Plan &pl)
     return true;
 }
 
+// the depthwise layer as a group convolution of one channel a group
+static GGeom as_group(const Geom &g)
+{
+    GGeom q;
+    q.N = g.N; q.C = g.C; q.H = g.H; q.W = g.W; q.K = g.K; q.s = g.s; q.p = g.p; q.G = g.C; q.O = g.O; q.Cg = 1; q.Og = g.m; q.Ho = g.Ho; q.Wo = g.Wo;
+    return q;
+}
+
 // force_v > 0: channels per lane of the NHWC kernel (the fused backward kernel has four in either type)
 static Plan plan_bwd_filter_v(const Geom &g, int layout, int dtype, int force_v)
 {
@@ -344,7 +353,12 @@ static Plan plan_bwd_filter_v(const Geom &g, int layout, int dtype, int force_v)
     return pl;
 }
 
-Plan plan_bwd_filter(const Geom &g, int layout, int dtype) { return plan_bwd_filter_v(g, layout, dtype, 0); }
+Plan plan_bwd_filter(const Geom &g, int layout, int dtype)
+{
+    Plan pl = plan_bwd_filter_v(g, layout, dtype, 0);
+    if (short_bwd_filter_shorter(as_group(g), layout, pl.variant == V_GENERIC && pl.parts == 1 ? FILTER_GENERIC_ONE : FILTER_TWO)) { pl.variant = V_SHORT_BWD_FILTER; pl.parts = 1; }
+    return pl;
+}
 
 Plan plan_bwd(const Geom &g, int layout, int dtype)
 {
@@ -412,7 +426,7 @@ Plan plan_bwd(const Geom &g, int layout, int dtype)
             }
         }
         // where both passes would run on the any-width kernels
-        if (g.s == 1 && g.K == 3 && plan_bwd_data(g, layout, dtype).variant == V_NCHWF_BWD_DATA && plan_bwd_filter(g, layout, dtype).variant == V_NCHWF_BWD_FILTER) {
+        if (g.s == 1 && g.K == 3 && plan_bwd_data(g, layout, dtype).variant == V_NCHWF_BWD_DATA && plan_bwd_filter_v(g, layout, dtype, 0).variant == V_NCHWF_BWD_FILTER) {
             const int parts = nchwf_bwd_fused_parts(g, dtype);
             if (parts > 0) { pl = {V_NCHWF_BWD_FUSED, parts, 0, 0, 0, "nchw_flat_bwd_fused_k3s1"}; }
         }
@@ -460,8 +474,14 @@ hipError_t launch_bwd_filter(const Plan &pl, const Geom &g, int layout, int dtyp
     case V_NCHWF_BWD_FILTER: return nchwf_bwd_filter(g, dtype, x, dy, ws, pl.parts, st);
     case V_NCHWD_BWD_FILTER: return nchwd_bwd_filter(g, dtype, pl.a, x, dy, ws, pl.b, st);
     case V_NCHWS_BWD_FILTER: return nchws_bwd_filter(g, dtype, x, dy, ws, pl.a, pl.c, st);
+    case V_SHORT_BWD_FILTER: return short_bwd_filter(as_group(g), layout, dtype, x, dy, ws, st);
     default: return generic_bwd_filter(g, layout, dtype, x, dy, ws, pl.parts, st);
     }
+}
+
+bool sums_are_final(const Plan &pl)
+{
+    return pl.parts == 1 && pl.variant != V_NCHWF_BWD_FILTER && pl.variant != V_NHWCA_BWD_FILTER && pl.variant != V_NCHWF_BWD_FUSED;
 }
 
 hipError_t launch_reduce(const Plan &pl, const Geom &g, int layout, int dtype, const void *x, const void *dy, const float *ws, float *dw,

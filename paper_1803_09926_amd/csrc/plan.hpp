@@ -27,6 +27,7 @@ enum Variant {
     V_NCHWD_BWD_FUSED,  // a = V, b = TH
     V_NCHWS_BWD_FUSED,  // a = U, c = NI
     V_NCHWF_BWD_FUSED,
+    V_SHORT_BWD_FILTER, // one launch, no partials, on the way of a family that takes the shape in longer launches (and gives it its name)
 };
 
 struct Plan {
@@ -54,6 +55,9 @@ hipError_t launch_bwd_filter(const Plan &pl, const Geom &g, int layout, int dtyp
 // second stage of the filter gradient for what launch_bwd_filter has left in ws
 hipError_t launch_reduce(const Plan &pl, const Geom &g, int layout, int dtype, const void *x, const void *dy, const float *ws, float *dw,
                          hipStream_t st);
+// Whether a single partial is the gradient itself, so that the kernel can write it where the caller wants it: a kernel without products
+// of padding, whose sums the second stage only copies.
+bool sums_are_final(const Plan &pl);
 hipError_t launch_bwd_fused(const Plan &pl, const Geom &g, int layout, int dtype, const void *x, const void *dy,
                             const void *w, void *dx, float *ws, hipStream_t st);
 
