@@ -275,7 +275,7 @@ static bool gemm_over_rowwalk(const GGeom &g, int layout, int dtype, int pass)
 
 // In place of the other row walks, whose lanes are few in short launches (a lane walks 7 to 28 rows of all its group's input channels) and, NHWC with eight channels
 // a group, many registers; in bf16 they widen every value.  Measured over 1500 random layers of 2 to 64 channels a group, up to 16 M outputs, walk
-// against these: NCHW forward and input gradient, bf16 0.27 and 0.31 of the time, 2 % longer (two channels a group, 12.7 M outputs 27.5 -> 30.8 us), fp32 0.45 up
+// against these: NCHW forward and input gradient, bf16 0.27 and 0.31 of the time, 2 % longer (all of two channels a group: 1.8 M outputs 10.8 -> 9.1 us, 5.4 M 13.9 -> 19.0), fp32 0.45 up
 // to 2.5 M outputs, none longer, from 3.4 M on 1.4 to 2.5 times as long; filter gradient, bf16 0.67, of odd groups, whose walk takes one output channel at
 // a time, 1.1 to 1.3 times as long, fp32 with four output channels at a time 0.7 below 1 M and up to 1.6 from 3.4 M on.  NHWC forward and input gradient with
 // eight channels 0.4 to 0.9 in bf16, 0.6 to 0.9 in fp32 (up to 2.7 M); with two and four 0.8 to 1.8 and 1.0 to 2.5: they stay.  NHWC filter gradient in
@@ -285,7 +285,7 @@ static bool gemm_over_walk(const GGeom &g, int dtype, int pass, int variant, lon
     const bool f32 = dtype == DT_F32;
     if (tune_active()) return false;                             // forced tilings are those of the walks
     if (variant == GV_NCHW_K3S1) {
-        if (pass < 2) return f32 ? outputs < 2000000 : !(g.Cg == 2 && outputs > 8000000);
+        if (pass < 2) return f32 ? outputs < 2000000 : !(g.Cg == 2 && outputs > 3000000);
         return g.Og % 4 == 0 || (!f32 && g.Og % 2 == 0 && g.Cg >= 6) ? !f32 || outputs < 1000000 : false;
     }
     if (variant == GV_NHWC_K3S1) {
