@@ -278,21 +278,24 @@ static bool gemm_over_rowwalk(const GGeom &g, int layout, int dtype, int pass)
 // against these: NCHW forward and input gradient, bf16 0.27 and 0.31 of the time, 2 % longer (all of two channels a group: 1.8 M outputs 10.8 -> 9.1 us, 5.4 M 13.9 -> 19.0), fp32 0.45 up
 // to 2.5 M outputs, none longer, from 3.4 M on 1.4 to 2.5 times as long; filter gradient, bf16 0.67, of odd groups, whose walk takes one output channel at
 // a time, 1.1 to 1.3 times as long, fp32 with four output channels at a time 0.7 below 1 M and up to 1.6 from 3.4 M on.  NHWC forward and input gradient with
-// eight channels 0.4 to 0.9 in bf16, 0.6 to 0.9 in fp32 (up to 2.7 M); with two and four 0.8 to 1.8 and 1.0 to 2.5: they stay.  NHWC filter gradient in
-// bf16 0.28 to 0.96; fp32 with eight channels 0.38 to 0.97 below 1 M, 1.1 to 1.3 above.
+// eight channels 0.4 to 0.9 in bf16, 0.6 to 0.9 in fp32 from 0.3 to 2.7 M (11x11x48, batch 35, 5.9 -> 7.0 us); with two and four 0.8 to 1.8 and 1.0 to 2.5:
+// they stay.  NHWC filter gradient in bf16 0.28 to 0.96, of two channels a group (at stride 2: four) only where the walk's lanes are few (8 channels in
+// all 0.5, 182 1.1 to 1.2); fp32 with eight channels 0.38 to 0.97 below 1 M, 1.1 to 1.3 above.
 static bool gemm_over_walk(const GGeom &g, int dtype, int pass, int variant, long long outputs)
 {
     const bool f32 = dtype == DT_F32;
     if (tune_active()) return false;                             // forced tilings are those of the walks
     if (variant == GV_NCHW_K3S1) {
-        if (pass < 2) return f32 ? outputs < 2000000 : !(g.Cg == 2 && outputs > 3000000);
+        // (16 output channels at a time, whether there are or not: 48x46x64 of four channels in two groups, fp32 10.5 on the walk, 15.9 here)
+        const long long padded = outputs / (pass == 1 ? g.C : g.O) * (((pass == 1 ? g.C : g.O) + 15) / 16 * 16);
+        if (pass < 2) return f32 ? padded < (g.Cg == 2 ? 500000 : 2000000) : !(g.Cg == 2 && outputs > 3000000);
         return g.Og % 4 == 0 || (!f32 && g.Og % 2 == 0 && g.Cg >= 6) ? !f32 || outputs < 1000000 : false;
     }
     if (variant == GV_NHWC_K3S1) {
-        if (pass < 2) return g.Cg == 8 && g.Og == 8 && !gconv_nhwc_mfma_supported(g, dtype) && (!f32 || outputs < 2700000);
-        return f32 ? g.Cg == 8 && outputs < 1000000 : g.Cg > 2 || outputs < 1300000;
+        if (pass < 2) return g.Cg == 8 && g.Og == 8 && !gconv_nhwc_mfma_supported(g, dtype) && (!f32 || (outputs >= 300000 && outputs < 2700000));
+        return f32 ? g.Cg == 8 && outputs < 1000000 : g.Cg > 2 || g.C <= 32;
     }
-    if (variant == GV_NHWC_BWD_FILTER_S2) return !f32 && outputs >= 8192 && (g.Cg == 8 || outputs < 1000000);
+    if (variant == GV_NHWC_BWD_FILTER_S2) return !f32 && outputs >= 8192 && (g.Cg == 8 || (g.C <= 64 && outputs < 1000000));
     return false;
 }
 

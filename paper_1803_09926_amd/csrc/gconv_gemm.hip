@@ -1060,17 +1060,21 @@ int resident_blocks(size_t lds, int most)
     return 256 * (int)(n < 1 ? 1 : n > (size_t)most ? most : n);
 }
 
-// The widest tile (of positions from `from` down to `to`) that fits, as tile(positions) sets it up; half of it where that lets `most`
+// The widest tile (of positions from `from` down to `to`) that fits, as tile(positions) sets it up; up to half of it less where that lets `most`
 // blocks onto a compute unit and it does not.  Returns the positions, 0 if nothing fits.  (14x14 16 channels a group 10.1 us with 256 positions,
 // 13.0 with 128; 28x28 32 channels a group, bf16 NHWC batch 64: 55 us with 256 positions and three blocks, 47 with 128 and four.)
-template <typename F> int widest_tile(F tile, int from, int to, int most, size_t limit, const size_t *lds)
+// In launches that fill the chip (`launched` blocks) that is as wide as it can be: 51x34x106 in 53 groups, fp32 NCHW batch 45, 49 us with 102 positions, 40
+// with 204; 6x6x224 in 14 groups, batch 93, 200 blocks, keeps 128 positions (8.3 us, 10.8 with 224, which leave wavefronts idle).
+template <typename F, typename B> int widest_tile(F tile, B launched, int from, int to, int most, size_t limit, const size_t *lds)
 {
     for (int want = from; want >= to; want /= 2) {
         tile(want);
         if (*lds > limit) continue;
         if (want / 2 >= 64 && resident_blocks(*lds, most) < 256 * most) {
-            tile(want / 2);
-            if (resident_blocks(*lds, most) == 256 * most) return want / 2;
+            for (int less = want - want / 8; less >= want / 2; less -= want / 8) {
+                tile(less);
+                if (resident_blocks(*lds, most) == 256 * most && (less == want / 2 || launched() >= 1024)) return less;
+            }
             tile(want);
         }
         return want;
@@ -1180,11 +1184,12 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
                 pl->lds = (size_t)ns * q.K * q.K * g.nk * 16 * (layout == LAYOUT_NHWC ? quad_of<true>() : quad_of<false>()) * esz + (size_t)cdivg(g.TN * g.TA * g.TB, 64) * 64 * (g.OS > 1 ? 16 : 8) + (g.OS > 1 ? 256 : 0) + 16 +
                           ((size_t)g.TN * g.LH * g.LW * g.pitch * esz + 15) / 16 * 16;
             };
-            int want = widest_tile(tile, 256, 16, 4, LDS_OF_TWO, &pl->lds);
-            if (!want && ns == 1) want = widest_tile(tile, 256, 16, 4, LDS_OF_ONE, &pl->lds);
+            auto blocks = [&]() { return (long long)g.tn * g.ta * g.tb * cdivg(blocks16, ns); };
+            int want = widest_tile(tile, blocks, 256, 16, 4, LDS_OF_TWO, &pl->lds);
+            if (!want && ns == 1) want = widest_tile(tile, blocks, 256, 16, 4, LDS_OF_ONE, &pl->lds);
             if (!want && ns == 1) return false;
             if (!want) continue;
-            auto few = [&]() { return (long long)g.tn * g.ta * g.tb * cdivg(blocks16, ns) < FEW; };
+            auto few = [&]() { return blocks() < FEW; };
             for (; want > 64 && few(); tile(want)) want /= 2;
             if (ns == 1 || !few()) break;
         }
@@ -1242,8 +1247,9 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
             // it: 1x48x46x46 in 8 groups, 5x5, fp32 NHWC 31 -> 15, 10x192x56x5 in 12, 3x3 at stride 3, bf16 NCHW 29 -> 12; random layers 0.945 of
             // the time at the mean, 0.4 % longer by more than 8 %.  192 blocks: 0.95 and 2.2 %.)
             constexpr int FEW = 128;
-            int want = widest_tile(tile, 256, npair > 1 ? 64 : 16, blocks, LDS_OF_TWO, &pl->lds);
-            auto few = [&]() { return (long long)g.tn * g.ta * g.tb * g.nchb < FEW; };
+            auto launched = [&]() { return (long long)g.tn * g.ta * g.tb * g.nchb; };
+            int want = widest_tile(tile, launched, 256, npair > 1 ? 64 : 16, blocks, LDS_OF_TWO, &pl->lds);
+            auto few = [&]() { return launched() < FEW; };
             for (; want > 32 && few(); tile(want)) want /= 2;
             fits = want > 0 && (npair == 1 || !few());
             if (fits) break;
@@ -1274,9 +1280,9 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
     const bool stageable = small && pl->sg.per <= 256 && (pass < 2 || pl->sy.per <= 256) && (long long)g.N * g.CI * g.Hi * g.Wi >= 8 &&
                            (long long)g.N * g.CO * g.Ho * g.Wo >= 8;
     if (!stageable) pl->fast = 0;
-    // (tiles narrower than the rows, filter gradient in fp32: four loads of a lane, each of 64 lanes in a row, are the shorter way; us, 376x127x127 in 188
-    // groups 40 against 46)
-    if (pass == 2 && layout == LAYOUT_NCHW && dtype == DT_F32 && pl->fast == 2) pl->fast = 0;
+    // (filter gradient in fp32: four loads of a lane, each of 64 lanes in a row, are the shorter way; us, 376x127x127 in 188 groups, NCHW, 40 against 46,
+    // 94x87x6 in three groups, 5x5, NHWC batch 7, 20 against 24)
+    if (pass == 2 && dtype == DT_F32 && pl->fast == 2) pl->fast = 0;
     pl->g = g;
     return true;
 }
