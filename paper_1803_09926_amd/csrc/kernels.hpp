@@ -78,12 +78,12 @@ hipError_t nhwc_bwd_filter_dot2(const Geom &g, int V, const void *x, const void 
 
 // ---- NHWC row walks for any channel count and padding, K 3, 5 or 7, stride 1 or 2 (nhwc_any.hip) ------------------
 // Any multiplier; the input gradient 1 or 2.
-bool nhwca_supported(const Geom &g, int pass);
+bool nhwca_supported(const Geom &g, int dtype, int pass);
 hipError_t nhwca_fwd(const Geom &g, int dtype, const void *x, const void *w, void *y, hipStream_t st);
 hipError_t nhwca_bwd_data(const Geom &g, int dtype, const void *dy, const void *w, void *dx, hipStream_t st);
-int nhwca_row_lanes(const Geom &g);                                          // lanes of the forward walk across a row
-int nhwca_bwd_filter_parts(const Geom &g);
-void nhwca_bwd_filter_tiles(const Geom &g, FilterGradSrc *f);               // what its partials hold
+int nhwca_row_lanes(const Geom &g, int dtype);                               // lanes of the forward walk across a row
+int nhwca_bwd_filter_parts(const Geom &g, int dtype);
+void nhwca_bwd_filter_tiles(const Geom &g, int dtype, FilterGradSrc *f);    // what its partials hold
 hipError_t nhwca_bwd_filter(const Geom &g, int dtype, const void *x, const void *dy, float *ws, hipStream_t st);
 
 // ---- NCHW kernels for rows of any width (nchw_flat.hip): K 3, 5 or 7, stride 1 or 2, any padding -----

@@ -5,7 +5,7 @@
 // flat over the channels x columns of a row.  Every row of the input is read once per strip and tap column through a buffer view
 // of the image (a column outside reads as the zero of the padding; the row offset is scalar), one step ahead of its use, and
 // meets ceil(K/S) rotating accumulators; what depends on the row is uniform.  V = 2 for 5x5 and 7x7: K*K*V filter registers (or
-// sums) are what limits the wavefronts in flight; V = 4 for 3x3; 1 where the channel count is odd or the multiplier is not 1.
+// sums) are what limits the wavefronts in flight; V = 4 for 3x3; 1 where the channel count is odd, the multiplier is not 1 or the lanes are few.
 //
 // One output per thread -> these kernels, us on one MI355X at batch 64, forward / input gradient / filter gradient: 56x56x128 5x5
 // stride 2 fp32 142 / 347 / 900 -> 36 / 37 / 41 (bound by its K vector loads per row and column, 8 bytes a lane); 28x28x256 7x7 fp32
@@ -351,18 +351,24 @@ bool any_k(const Geom &g)
            (long long)g.Ho * g.Wo * g.O * 4 <= (1LL << 31);
 }
 
-// channels per lane
-int any_vec(const Geom &g)
+// Channels per lane.  5x5 and 7x7 in launches of few lanes take one channel: the walk is then as long as its loads take, and twice the wavefronts with half the
+// registers hide more of them (random layers, share of the time with two: fp32 below 1.6 M outputs 5x5 0.72 to 1 (119x119x84 at stride 2, 1.5 M, filter gradient 1.7), 7x7 0.66 to 1 in every pass, from
+// 2 M on up to 1.1; bf16, whose lanes then read two bytes, filter gradient below 0.4 M 0.68 to 0.92, the other passes below 0.16 M 0.89 to 0.98, above up to 1.25).
+int any_vec(const Geom &g, int dtype, int pass)
 {
     if (g.m != 1) return 1;
     if (g.C % 4 == 0 && g.K == 3) return 4;
-    return g.C % 2 == 0 ? 2 : 1;
+    if (g.C % 2) return 1;
+    const long long outputs = (long long)g.N * g.O * g.Ho * g.Wo;
+    return g.K > 3 && outputs < (dtype == DT_F32 ? (pass == 2 && g.K == 5 ? 1200000 : 1600000) : pass == 2 ? 400000 : 160000) ? 1 : 2;
 }
 
-// balanced strips of about `target` rows, shorter while the launch has fewer than 1024 wavefronts
+// balanced strips of about `target` rows, shorter while the launch has fewer than 1024 wavefronts, down to four rows; to two below 256 (0.87 to 0.9 of
+// the time; above, the rows that strips share make it longer: 5x5 of 0.2 M outputs 1.2 to 1.4)
 int any_strips(int rows, int target, long long lanes)
 {
     while (target > 4 && lanes * cdiva(rows, target) < 65536) target = (target + 1) / 2;
+    while (target > 2 && lanes * cdiva(rows, target) < 16384) target = (target + 1) / 2;
     const int n = cdiva(rows, target);
     return cdiva(rows, n);
 }
@@ -392,18 +398,18 @@ WalkTile walk_tile(int N, int rows, long long lanes, int target)
     t.blocks = (long long)N * t.nstrips * t.nchunks;
     return t;
 }
-WalkTile walk_tile(const Geom &g, int pass)
+WalkTile walk_tile(const Geom &g, int dtype, int pass)
 {
-    const int V = any_vec(g), target = g.K == 3 ? 14 : 28;
+    const int V = any_vec(g, dtype, pass), target = g.K == 3 ? 14 : 28;
     if (pass == 0) return walk_tile(g.N, g.Ho, (long long)g.Wo * (g.O / V), target);
     if (g.s == 1) return walk_tile(g.N, g.H, (long long)g.W * (g.C / V), target);
     return walk_tile(g.N, s2a_pairs(g), (long long)s2a_cols(g) * (g.C / V), 14);
 }
 
 struct FilterTile { int V, CT, nct, TH, nstrips, TW, ncols, parts, per; };
-bool filter_tile_any(const Geom &g, FilterTile *f)
+bool filter_tile_any(const Geom &g, int dtype, FilterTile *f)
 {
-    f->V = any_vec(g);
+    f->V = any_vec(g, dtype, 2);
     const int Q = g.O / f->V;
     // channel vectors across a block: the widest power of two that leaves few lanes idle, across the channels and across the columns that
     // the other lanes take (181x3x3x572 7x7 fp32: two across, as the channels alone would have it, 265 us with 3 of 128 columns there)
@@ -439,26 +445,26 @@ bool filter_tile_any(const Geom &g, FilterTile *f)
 
 }  // namespace
 
-bool nhwca_supported(const Geom &g, int pass)
+bool nhwca_supported(const Geom &g, int dtype, int pass)
 {
     if (!any_k(g)) return false;
     if (pass == 2) return true;
-    const WalkTile t = walk_tile(g, pass);
+    const WalkTile t = walk_tile(g, dtype, pass);
     return launchable(t.blocks, t.bs) && (pass != 1 || g.m <= 2);
 }
 
-int nhwca_row_lanes(const Geom &g) { return g.Wo * (g.O / any_vec(g)); }
+int nhwca_row_lanes(const Geom &g, int dtype) { return g.Wo * (g.O / any_vec(g, dtype, 0)); }
 
-int nhwca_bwd_filter_parts(const Geom &g)
+int nhwca_bwd_filter_parts(const Geom &g, int dtype)
 {
     FilterTile f;
-    return any_k(g) && filter_tile_any(g, &f) ? f.parts : 0;
+    return any_k(g) && filter_tile_any(g, dtype, &f) ? f.parts : 0;
 }
 
-void nhwca_bwd_filter_tiles(const Geom &g, FilterGradSrc *f)
+void nhwca_bwd_filter_tiles(const Geom &g, int dtype, FilterGradSrc *f)
 {
     FilterTile t;
-    filter_tile_any(g, &t);
+    filter_tile_any(g, dtype, &t);
     f->TN = 1; f->TA = t.TH; f->TB = t.TW;
     f->tn = g.N; f->ta = t.nstrips; f->tb = t.ncols;
     f->per = t.per; f->nparts = t.parts;
@@ -469,7 +475,7 @@ static hipError_t conv_any(const Geom &q, const void *in, const void *w, void *o
 {
     AnyGeom g = bwd ? AnyGeom{q.N, q.O, q.C, q.Ho, q.Wo, q.H, q.W, K - 1 - q.p, 1, 0, 0, 0, 0, 0}
                     : AnyGeom{q.N, q.C, q.O, q.H, q.W, q.Ho, q.Wo, q.p, q.m, 0, 0, 0, 0, 0};
-    const WalkTile t = walk_tile(q, bwd ? 1 : 0);
+    const WalkTile t = walk_tile(q, sizeof(T) == 4 ? DT_F32 : DT_BF16, bwd ? 1 : 0);
     g.TH = t.TH; g.nstrips = t.nstrips; g.nchunks = t.nchunks;
     const unsigned nblocks = (unsigned)t.blocks;
     hipLaunchKernelGGL((k_nhwca_conv<T, V, K, S, M>), dim3(nblocks), dim3(t.bs), 0, st, g, (const T *)in, (const T *)w, (T *)out, q.O, bwd ? 1 : 0,
@@ -480,7 +486,7 @@ template <typename T, int V, int K, int M>
 static hipError_t s2_any(const Geom &q, const void *dy, const void *w, void *dx, hipStream_t st)
 {
     AnyGeom g = {q.N, q.O, q.C, q.Ho, q.Wo, q.H, q.W, q.p, 1, 0, 0, 0, 0, 0};
-    const WalkTile t = walk_tile(q, 1);
+    const WalkTile t = walk_tile(q, sizeof(T) == 4 ? DT_F32 : DT_BF16, 1);
     g.TH = t.TH; g.nstrips = t.nstrips; g.nchunks = t.nchunks;
     const unsigned nblocks = (unsigned)t.blocks;
     hipLaunchKernelGGL((k_nhwca_bwd_data_s2<T, V, K, M>), dim3(nblocks), dim3(t.bs), 0, st, g, (const T *)dy, (const T *)w, (T *)dx, s2a_cols(q), nblocks,
@@ -491,7 +497,7 @@ template <typename T, int V, int K, int S>
 static hipError_t filter_any(const Geom &q, const void *x, const void *dy, float *ws, hipStream_t st)
 {
     FilterTile f;
-    filter_tile_any(q, &f);
+    filter_tile_any(q, sizeof(T) == 4 ? DT_F32 : DT_BF16, &f);
     const AnyGeom g = {q.N, q.C, q.O, q.H, q.W, q.Ho, q.Wo, q.p, q.m, f.TH, f.nstrips, 0, f.TW, f.ncols};
     const unsigned nblocks = (unsigned)f.parts * f.nct;
     hipLaunchKernelGGL((k_nhwca_bwd_filter<T, V, K, S>), dim3(nblocks), dim3(256), 0, st, g, (const T *)x, (const T *)dy, ws, f.CT, f.parts, f.per,
@@ -506,7 +512,7 @@ static hipError_t filter_any(const Geom &q, const void *x, const void *dy, float
 template <typename T>
 static hipError_t fwd_any(const Geom &g, const void *x, const void *w, void *y, hipStream_t st)
 {
-    const int V = any_vec(g);
+    const int V = any_vec(g, sizeof(T) == 4 ? DT_F32 : DT_BF16, 0);
     if (V == 4) return (g.s == 1 ? conv_any<T, 4, 3, 1, 1> : conv_any<T, 4, 3, 2, 1>)(g, x, w, y, false, st);
     if (V == 2) return BY_KS(conv_any, 2, COMMA_ONE)(g, x, w, y, false, st);
     return BY_KS(conv_any, 1, COMMA_ONE)(g, x, w, y, false, st);
@@ -516,7 +522,7 @@ static hipError_t fwd_any(const Geom &g, const void *x, const void *w, void *y, 
 template <typename T>
 static hipError_t bwd_data_any(const Geom &g, const void *dy, const void *w, void *dx, hipStream_t st)
 {
-    const int V = any_vec(g);
+    const int V = any_vec(g, sizeof(T) == 4 ? DT_F32 : DT_BF16, 1);
     if (g.s == 2) {
         if (g.m == 2) return BY_K(s2_any, 1, 2)(g, dy, w, dx, st);
         if (V == 4) return s2_any<T, 4, 3, 1>(g, dy, w, dx, st);
@@ -531,7 +537,7 @@ static hipError_t bwd_data_any(const Geom &g, const void *dy, const void *w, voi
 template <typename T>
 static hipError_t bwd_filter_any(const Geom &g, const void *x, const void *dy, float *ws, hipStream_t st)
 {
-    const int V = any_vec(g);
+    const int V = any_vec(g, sizeof(T) == 4 ? DT_F32 : DT_BF16, 2);
     if (V == 4) return (g.s == 1 ? filter_any<T, 4, 3, 1> : filter_any<T, 4, 3, 2>)(g, x, dy, ws, st);
     if (V == 2) return BY_KS(filter_any, 2, )(g, x, dy, ws, st);
     return BY_KS(filter_any, 1, )(g, x, dy, ws, st);

@@ -168,7 +168,7 @@ static bool plan_flat(const Geom &g, int dtype, int pass, Plan &pl)
 }
 
 // The NHWC walks of nhwc_any.hip for what nhwc.hip does not take.
-static bool plan_any(const Geom &g, int pass, Plan &pl)
+static bool plan_any(const Geom &g, int dtype, int pass, Plan &pl)
 {
     static const char *const names[3][3][2] = {
         {{"nhwc_any_k3s1", "nhwc_any_k3s2"}, {"nhwc_any_k5s1", "nhwc_any_k5s2"}, {"nhwc_any_k7s1", "nhwc_any_k7s2"}},
@@ -176,18 +176,18 @@ static bool plan_any(const Geom &g, int pass, Plan &pl)
          {"nhwc_any_k7s1_flip", "nhwc_any_bwd_data_k7s2"}},
         {{"nhwc_any_bwd_filter_k3s1", "nhwc_any_bwd_filter_k3s2"}, {"nhwc_any_bwd_filter_k5s1", "nhwc_any_bwd_filter_k5s2"},
          {"nhwc_any_bwd_filter_k7s1", "nhwc_any_bwd_filter_k7s2"}}};
-    if (!nhwca_supported(g, pass)) return false;
+    if (!nhwca_supported(g, dtype, pass)) return false;
     const long long pixels = (long long)g.N * g.Ho * g.Wo;
     if (pass == 0) {
         // a forward pass of a few thousand outputs is as fast one output per thread (2x9x9x6 3.0 us against 2.5), and so is one whose rows
         // have so few lanes that most of a wavefront is idle (422x101x4x1 pad 0, multiplier 2 4.7 against 7.7, 506x90x3x2 5x5 stride 2 5.3 against 20)
         if (pixels * g.O < 2048) return false;
-        if (nhwca_row_lanes(g) <= 4 && (long long)g.N * g.Ho >= 4096) return false;
+        if (nhwca_row_lanes(g, dtype) <= 4 && (long long)g.N * g.Ho >= 4096) return false;
     }
     // The filter gradient of a few pixels: the reduction over the block is longer than the sums (us, generic against this kernel, 3x3 up to
     // 16 pixels 5.7 / 6.3, 32 6.7 / 6.2; 5x5 16 5.6 / 7.6, 64 8.8 / 7.5; 7x7 16 5.7 / 10.5, 64 8.4 / 10.9, 128 15.2 / 11.1).
     if (pass == 2 && pixels < 2 * g.K * g.K) return false;
-    if (pass == 2) pl.parts = nhwca_bwd_filter_parts(g);
+    if (pass == 2) pl.parts = nhwca_bwd_filter_parts(g, dtype);
     pl.variant = pass == 0 ? V_NHWCA_FWD : pass == 1 ? V_NHWCA_BWD_DATA : V_NHWCA_BWD_FILTER;
     pl.name = names[pass][(g.K - 3) / 2][g.s - 1];
     return true;
@@ -216,7 +216,7 @@ Plan plan_fwd(const Geom &g, int layout, int dtype)
         } else if (V && k3s2p1(g)) {
             pl.variant = V_NHWC_K3S2; pl.a = V; pl.b = pick_th(g.Ho, nhwc_lanes(g.N, g.Wo * (g.O / V)), 2);
             pl.name = "nhwc_rowwalk_fwd_k3s2";
-        } else plan_any(g, 0, pl);
+        } else plan_any(g, dtype, 0, pl);
     }
     return pl;
 }
@@ -248,7 +248,7 @@ Plan plan_bwd_data(const Geom &g, int layout, int dtype)
         } else if (V && k3s2p1(g)) {
             pl.variant = V_NHWC_K3S2; pl.a = V; pl.b = pick_th(g.Ho, nhwc_lanes(g.N, g.Wo * (g.O / V)), 2, 14, 4);
             pl.name = "nhwc_rowwalk_bwd_data_k3s2";
-        } else plan_any(g, 1, pl);
+        } else plan_any(g, dtype, 1, pl);
     }
     return pl;
 }
@@ -343,12 +343,12 @@ static Plan plan_bwd_filter_v(const Geom &g, int layout, int dtype, int force_v)
                 if (NI < g.N) NI = NI * 2 < g.N ? NI * 2 : g.N; else TH = TH * 2 < g.Ho ? TH * 2 : g.Ho;
                 nhwc_bwd_filter_tiling(g, V, TH, NI, &CT, &nct, &nowt, &nst, &ngr);
             }
-            if ((long long)nowt * nst * ngr * g.O * g.K * g.K * 4 > (64ll << 20)) { plan_any(g, 2, pl); return pl; }
+            if ((long long)nowt * nst * ngr * g.O * g.K * g.K * 4 > (64ll << 20)) { plan_any(g, dtype, 2, pl); return pl; }
             pl.variant = V_NHWC_BWD_FILTER; pl.a = V; pl.b = TH; pl.c = NI;
             pl.parts = nowt * nst * ngr;
             pl.name = g.m == 2 ? "nhwc_bwd_filter_k3s1_m2"
                                : (g.s == 2 ? "nhwc_bwd_filter_k3s2" : (g.K == 3 ? "nhwc_bwd_filter_k3s1" : "nhwc_bwd_filter_k5s1"));
-        } else plan_any(g, 2, pl);
+        } else plan_any(g, dtype, 2, pl);
     }
     return pl;
 }
@@ -492,7 +492,7 @@ hipError_t launch_reduce(const Plan &pl, const Geom &g, int layout, int dtype, c
     FilterGradSrc src = {x, dy, dtype, layout, g.N, g.C, g.H, g.W, g.K, g.s, g.p, g.O, 1, g.m, g.Ho, g.Wo};
     if (pl.variant == V_NCHWF_BWD_FILTER) nchwf_bwd_filter_tiles(g, dtype, pl.parts, &src);
     else if (pl.variant == V_NCHWF_BWD_FUSED) nchwf_bwd_fused_tiles(g, dtype, pl.parts, &src);
-    else nhwca_bwd_filter_tiles(g, &src);
+    else nhwca_bwd_filter_tiles(g, dtype, &src);
     return reduce_partials(ws, pl.parts, J, dw, src, st);
 }
 
