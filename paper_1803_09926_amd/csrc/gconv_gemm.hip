@@ -1063,19 +1063,23 @@ int resident_blocks(size_t lds, int most)
 // The widest tile (of positions from `from` down to `to`) that fits, as tile(positions) sets it up; up to half of it less where that lets `most`
 // blocks onto a compute unit and it does not.  Returns the positions, 0 if nothing fits.  (14x14 16 channels a group 10.1 us with 256 positions,
 // 13.0 with 128; 28x28 32 channels a group, bf16 NHWC batch 64: 55 us with 256 positions and three blocks, 47 with 128 and four.)
-// In launches that fill the chip (`launched` blocks) that is as wide as it can be: 51x34x106 in 53 groups, fp32 NCHW batch 45, 49 us with 102 positions, 40
-// with 204; 6x6x224 in 14 groups, batch 93, 200 blocks, keeps 128 positions (8.3 us, 10.8 with 224, which leave wavefronts idle).
-template <typename F, typename B> int widest_tile(F tile, B launched, int from, int to, int most, size_t limit, const size_t *lds)
+// Of such tiles the one whose `launched` blocks go through the chip in the shortest rounds, each its positions and 32 of fixed work: 51x34x106 in 53 groups,
+// fp32 NCHW batch 45, 204 positions (40 us, 49 with 102), 61x59x84 in 42, batch 27, 122 (44 us, 56 with 183).
+template <typename F, typename B> int widest_tile(const GemmGeom &g, F tile, B launched, int from, int to, int most, size_t limit, const size_t *lds)
 {
     for (int want = from; want >= to; want /= 2) {
         tile(want);
         if (*lds > limit) continue;
         if (want / 2 >= 64 && resident_blocks(*lds, most) < 256 * most) {
+            int best = 0;
+            long long least = 0;
             for (int less = want - want / 8; less >= want / 2; less -= want / 8) {
                 tile(less);
-                if (resident_blocks(*lds, most) == 256 * most && (less == want / 2 || launched() >= 1024)) return less;
+                const long long time = (launched() + 256 * most - 1) / (256 * most) * (g.TN * g.TA * g.TB + 32);
+                if (resident_blocks(*lds, most) == 256 * most && (!best || time <= least)) { best = less; least = time; }
             }
-            tile(want);
+            tile(best ? best : want);
+            if (best) return best;
         }
         return want;
     }
@@ -1185,8 +1189,8 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
                           ((size_t)g.TN * g.LH * g.LW * g.pitch * esz + 15) / 16 * 16;
             };
             auto blocks = [&]() { return (long long)g.tn * g.ta * g.tb * cdivg(blocks16, ns); };
-            int want = widest_tile(tile, blocks, 256, 16, 4, LDS_OF_TWO, &pl->lds);
-            if (!want && ns == 1) want = widest_tile(tile, blocks, 256, 16, 4, LDS_OF_ONE, &pl->lds);
+            int want = widest_tile(g, tile, blocks, 256, 16, 4, LDS_OF_TWO, &pl->lds);
+            if (!want && ns == 1) want = widest_tile(g, tile, blocks, 256, 16, 4, LDS_OF_ONE, &pl->lds);
             if (!want && ns == 1) return false;
             if (!want) continue;
             auto few = [&]() { return blocks() < FEW; };
@@ -1248,7 +1252,7 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
             // the time at the mean, 0.4 % longer by more than 8 %.  192 blocks: 0.95 and 2.2 %.)
             constexpr int FEW = 128;
             auto launched = [&]() { return (long long)g.tn * g.ta * g.tb * g.nchb; };
-            int want = widest_tile(tile, launched, 256, npair > 1 ? 64 : 16, blocks, LDS_OF_TWO, &pl->lds);
+            int want = widest_tile(g, tile, launched, 256, npair > 1 ? 64 : 16, blocks, LDS_OF_TWO, &pl->lds);
             auto few = [&]() { return launched() < FEW; };
             for (; want > 32 && few(); tile(want)) want /= 2;
             fits = want > 0 && (npair == 1 || !few());
