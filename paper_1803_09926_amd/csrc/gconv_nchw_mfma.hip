@@ -49,13 +49,20 @@ __global__ __launch_bounds__(256) void k_gconv_nchws_mfma_bwd_filter(GGeom g, co
     constexpr int DROW = WIDE ? W : L::WP, PPD = WIDE ? L::RS * W : L::PPD, AREA_D = 8 * PPD;
     constexpr int LEAD = 16 / (int)sizeof(T);       // zeros before the first plane: the pixel left of its first one
     // fills ahead in registers; fp32 strips and wide rows: one (two would leave registers for one wavefront per SIMD only)
-    constexpr int DEPTH = ((L::STRIP && (sizeof(T) == 4 || WIDE)) || (L::MOSAIC && sizeof(T) == 4)) ? 1 : 2;
     constexpr bool F32 = sizeof(T) == 4;
+    constexpr int DEPTH = ((L::STRIP && (F32 || WIDE)) || (L::MOSAIC && F32)) ? 1 : 2;
     constexpr int CPV = F32 ? 1 : 2;                // four-pixel vectors of a 16-byte chunk
     constexpr int HPP = F32 ? 2 : 1;                // NHWC: 16-byte chunks of a pixel's eight channels
     constexpr int EPC = 4 * CPV;                    // elements of a chunk
     constexpr int XCH = 8 * L::XROWS * L::VPR / CPV, DCH = 8 * L::RS * L::VPR / CPV;     // chunks of a fill
-    constexpr int XPASS = (XCH + 255) / 256, DPASS = (DCH + 255) / 256;
+    // NCHW strips in bf16: a pass takes whole planes (one or two), so that a lane's place is found once, a chunk is one LDS write and the
+    // addresses are scalar: 128x128x56x56 in groups of 4 42.9 -> 39.8 us, of 8 48.6 -> 45.5, 64x112x112 in groups of 2, batch 256, 143.6 -> 141.0,
+    // batch 32 28.6 -> 27.5.  It leaves 32 to 60 lanes of a pass idle, and fp32, whose large launches wait for memory, is up to 3 % longer
+    // (128x128x56x56 in groups of 8 112 -> 116).
+    constexpr bool PLANES = L::STRIP && !NHWC && !F32;
+    constexpr int XLP = XCH / 8, DLP = DCH / 8, XPP = 256 / XLP, DPP = 256 / DLP;        // chunks of a plane, planes of a pass
+    static_assert(!PLANES || (8 % XPP == 0 && 8 % DPP == 0 && L::VPR % CPV == 0), "whole planes, whole chunks of a row");
+    constexpr int XPASS = PLANES ? 8 / XPP : (XCH + 255) / 256, DPASS = PLANES ? 8 / DPP : (DCH + 255) / 256;
     __shared__ __align__(16) T lds_all[LEAD + L::AREA_X + AREA_D];    // x planes, then dy planes
     T *lds = lds_all + LEAD;
 
@@ -75,6 +82,10 @@ __global__ __launch_bounds__(256) void k_gconv_nchws_mfma_bwd_filter(GGeom g, co
     // nearest row inside and is zeroed on its way to LDS): the number of loads in flight is then the same on every
     // path, and the wait before a fill's LDS writes covers that fill's loads only.
     struct Stage { u4raw_t x[XPASS], d[DPASS]; uint32_t xok; };      // xok: per pass, the x chunk is inside the plane (mosaic: the dy chunk's image exists)
+    // PLANES: the lane's plane of a pass, row and chunk of the row
+    constexpr int CPR = L::VPR / CPV;
+    const int xl = min(tid, XPP * XLP - 1), xlp = xl / XLP, xlr = xl % XLP / CPR, xlc = xl % CPR * EPC;
+    const int dl = min(tid, DPP * DLP - 1), dlp = dl / DLP, dlr = dl % DLP / CPR, dlc = dl % CPR * EPC;
     auto gload = [&](Stage &s, int f) {
         const int ff = f < nfills ? f : part;
         const int n = ff / L::NSTRIP, r0 = (ff % L::NSTRIP) * L::RS;
@@ -110,6 +121,16 @@ __global__ __launch_bounds__(256) void k_gconv_nchws_mfma_bwd_filter(GGeom g, co
                 const int q = min(p * 256 + tid, DCH - 1), pq = q / HPP, hs = q % HPP;
                 s.d[p] = *reinterpret_cast<const u4raw_t *>(dy + (((size_t)n * H + r0 + pq / W) * W + pq % W) * g.O + cb * 8 + hs * 4);
             }
+            return;
+        }
+        if constexpr (PLANES) {
+            const int rg = r0 - 1 + xlr;
+            if (rg < 0 || rg >= H) s.xok = 0u;
+            const uint32_t xo = (uint32_t)(xlp * (H * W) + min(max(rg, 0), H - 1) * W + xlc), dd = (uint32_t)(dlp * (H * W) + (r0 + dlr) * W + dlc);
+#pragma unroll
+            for (int p = 0; p < XPASS; ++p) s.x[p] = *reinterpret_cast<const u4raw_t *>(xs + p * XPP * (H * W) + xo);
+#pragma unroll
+            for (int p = 0; p < DPASS; ++p) s.d[p] = *reinterpret_cast<const u4raw_t *>(ds + p * DPP * (H * W) + dd);
             return;
         }
 #pragma unroll
@@ -198,6 +219,22 @@ __global__ __launch_bounds__(256) void k_gconv_nchws_mfma_bwd_filter(GGeom g, co
             for (int p = 0; p < DPASS; ++p) {
                 const int q = p * 256 + tid;
                 if ((p + 1) * 256 <= DCH || q < DCH) scatter(lds + L::AREA_X, PPD, DROW, 0, q, s.d[p]);
+            }
+            return;
+        }
+        if constexpr (PLANES) {
+            T *xa = lds + xlp * L::PPX + xlr * L::WP + xlc, *da = lds + L::AREA_X + dlp * PPD + dlr * DROW + dlc;
+            if (tid < XPP * XLP) {
+#pragma unroll
+                for (int p = 0; p < XPASS; ++p) {
+                    const bool ok = s.xok != 0u;
+                    const u4raw_t v = s.x[p];
+                    *reinterpret_cast<u4raw_t *>(xa + p * XPP * L::PPX) = u4raw_t{ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u};
+                }
+            }
+            if (tid < DPP * DLP) {
+#pragma unroll
+                for (int p = 0; p < DPASS; ++p) *reinterpret_cast<u4raw_t *>(da + p * DPP * PPD) = s.d[p];
             }
             return;
         }

@@ -34,7 +34,13 @@ __global__ __launch_bounds__(256) void k_gconv_nchws_mfma_fwd(GGeom g, const T *
     constexpr bool F32 = sizeof(T) == 4;
     constexpr int CPV = F32 ? 1 : 2;                // four-pixel vectors of a 16-byte chunk
     constexpr int XCH = 8 * L::XROWS * L::VPR / CPV, YCH = 8 * L::RS * L::VPR / CPV;     // chunks of a fill
-    constexpr int XPASS = (XCH + 255) / 256, YPASS = (YCH + 255) / 256;
+    // strips in bf16, and in groups of 8: a pass takes whole planes, as in the filter gradient (bf16 128x128x56x56 in groups of 4 44.1 -> 42.7 us, of 8 57.7 ->
+    // 56.9, batch 16 of 64 channels 7.5 -> 7.0, 64x112x112 in groups of 2, batch 32, 24.6 -> 23.2; fp32 in groups of 8 126.4 -> 125.4, batch 16 of 256 channels 36.6 -> 35.3,
+    // of 4, which wait for memory, 86.4 -> 88)
+    constexpr bool PLANES = L::STRIP && (!F32 || CG == 8);
+    constexpr int XLP = XCH / 8, YLP = YCH / 8, XPP = 256 / XLP, YPL = 256 / YLP;        // chunks of a plane, planes of a pass
+    static_assert(!PLANES || (8 % XPP == 0 && 8 % YPL == 0 && L::VPR % CPV == 0), "whole planes, whole chunks of a row");
+    constexpr int XPASS = PLANES ? 8 / XPP : (XCH + 255) / 256, YPASS = PLANES ? 8 / YPL : (YCH + 255) / 256;
     constexpr int AREA_Y = L::MOSAIC ? 4 * 8 * H * W : 8 * L::RS * W;       // output planes of the fill, rows packed (mosaic: image after image)
     constexpr int EPC = 4 * CPV, CPI = XCH / 4;    // elements of a chunk; mosaic: chunks of one image's eight planes
     constexpr int LEAD = 16 / (int)sizeof(T);       // zeros before the first plane: the pixel left of its first one
@@ -54,12 +60,24 @@ __global__ __launch_bounds__(256) void k_gconv_nchws_mfma_fwd(GGeom g, const T *
     auto where = [](int v, int rows) { Where q; q.plane = v / (rows * L::VPR); const int rem = v % (rows * L::VPR); q.row = rem / L::VPR; q.cv = rem % L::VPR; return q; };
 
     // DEPTH fills ahead in registers; every load is issued unconditionally (see the filter gradient)
-    struct Stage { u4raw_t x[XPASS]; uint32_t xok; };
+    struct Stage { u4raw_t x[XPASS]; uint32_t xok; };              // xok: per pass, the chunk is inside the plane
+    // PLANES: the lane's plane of a pass, row and first element of its chunk of the row
+    constexpr int CPR = L::VPR / CPV;
+    const int xl = min(tid, XPP * XLP - 1), xlp = xl / XLP, xlr = xl % XLP / CPR, xlc = xl % CPR * EPC;
+    const int yl = min(tid, YPL * YLP - 1), ylp = yl / YLP, ylr = yl % YLP / CPR, ylc = yl % CPR * EPC;
     auto gload = [&](Stage &s, int f) {
         const int ff = f < nfills ? f : part;
         const int n = ff / L::NSTRIP, r0 = (ff % L::NSTRIP) * L::RS;
         const T *xs = in + ((size_t)n * g.C + (size_t)cb * 8) * (H * W);
         s.xok = 0xffffffffu;
+        if constexpr (PLANES) {
+            const int rg = r0 - 1 + xlr;
+            if (rg < 0 || rg >= H) s.xok = 0u;
+            const uint32_t at = (uint32_t)(xlp * (H * W) + min(max(rg, 0), H - 1) * W + xlc);
+#pragma unroll
+            for (int p = 0; p < XPASS; ++p) s.x[p] = *reinterpret_cast<const u4raw_t *>(xs + p * XPP * (H * W) + at);
+            return;
+        }
 #pragma unroll
         for (int p = 0; p < XPASS; ++p) {
             const int q = min(p * 256 + tid, XCH - 1);
@@ -79,6 +97,18 @@ __global__ __launch_bounds__(256) void k_gconv_nchws_mfma_fwd(GGeom g, const T *
         }
     };
     auto lstore = [&](const Stage &s) {
+        if constexpr (PLANES) {
+            T *xa = lds + xlp * L::PPX + xlr * L::WP + xlc;
+            if (tid < XPP * XLP) {
+#pragma unroll
+                for (int p = 0; p < XPASS; ++p) {
+                    const bool ok = s.xok != 0u;
+                    const u4raw_t v = s.x[p];
+                    *reinterpret_cast<u4raw_t *>(xa + p * XPP * L::PPX) = u4raw_t{ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u};
+                }
+            }
+            return;
+        }
 #pragma unroll
         for (int p = 0; p < XPASS; ++p) {
             const int q = p * 256 + tid;
@@ -113,6 +143,15 @@ __global__ __launch_bounds__(256) void k_gconv_nchws_mfma_fwd(GGeom g, const T *
     auto ystore = [&](int f) {
         const int n = f / L::NSTRIP, r0 = (f % L::NSTRIP) * L::RS;
         T *ys = out + ((size_t)n * g.C + (size_t)cb * 8) * (H * W);
+        if constexpr (PLANES) {
+            const uint32_t at = (uint32_t)(ylp * (H * W) + (r0 + ylr) * W + ylc);
+            if (tid < YPL * YLP) {
+#pragma unroll
+                for (int p = 0; p < YPASS; ++p)
+                    *reinterpret_cast<u4raw_t *>(ys + p * YPL * (H * W) + at) = *reinterpret_cast<const u4raw_t *>(ylds + p * YPL * YLP * EPC + tid * EPC);
+            }
+            return;
+        }
 #pragma unroll
         for (int p = 0; p < YPASS; ++p) {
             const int q = p * 256 + tid;
