@@ -6,7 +6,8 @@
 // three passes of a layer of 11 thousand outputs 19.3 -> 17.1.
 //
 // Every function returns the library's status, or None where an argument is anything but what it takes for granted (a descriptor of the
-// package's types, tensors and parameters in device memory of the expected type, size and contiguity, no function mode active): the
+// package's types, tensors and parameters in device memory of the expected type, size and contiguity, a stream whose handle is a
+// number, no function mode active): the
 // caller then checks argument by argument, raises, or takes the general way.  The library is not linked: bind() hands over its entry points.
 #include <Python.h>
 #include <ATen/ATen.h>
@@ -113,9 +114,11 @@ PyObject *call(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     else {
         PyObject *handle = PyObject_GetAttrString(given, "cuda_stream");
         if (!handle) return nullptr;
-        stream = PyLong_AsVoidPtr(handle);
+        bool taken = PyLong_Check(handle);   // (the foreign call also takes None, a c_void_p and what else stands for a pointer)
+        stream = taken ? PyLong_AsVoidPtr(handle) : nullptr;
         Py_DECREF(handle);
-        if (PyErr_Occurred()) return nullptr;
+        if (PyErr_Occurred()) { PyErr_Clear(); taken = false; }
+        if (!taken) Py_RETURN_NONE;
     }
     int rc;
     void *const fn = entry_points[E];

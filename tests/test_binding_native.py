@@ -1,4 +1,7 @@
 """The native call path of the binding: it takes plain device tensors and leaves everything else to the checks in Python."""
+import ctypes
+import types
+
 import pytest
 import torch
 
@@ -66,6 +69,29 @@ def test_every_call_by_both_ways(gpu_lib, name):
     if "s" in CALLS[name]:
         with pytest.raises(dw.DwconvError):
             getattr(dw, name)(d, *t[:-1], t[-1][:4])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", CALLS)
+def test_stream_handles_of_every_form_that_a_pointer_takes(gpu_lib, name):
+    """A handle that is no number is left to the foreign call, which takes None (the null stream) and c_void_p as well."""
+    d, t = _operands(name, "cuda")
+    native, side = dw._native or dw._bind_native(), torch.cuda.Stream()
+    getattr(dw, name)(d, *t)
+    torch.cuda.synchronize()
+    for handle, plain in ((side.cuda_stream, True), (ctypes.c_void_p(side.cuda_stream), False), (0, True), (None, False), (ctypes.c_void_p(None), False)):
+        stream = types.SimpleNamespace(cuda_stream=handle)
+        _, got = _operands(name, "cuda")
+        torch.cuda.synchronize()
+        assert (getattr(native, name)(d, *got, stream) is None) != plain
+        getattr(dw, name)(d, *got, stream=stream)
+        torch.cuda.synchronize()
+        for k, a, b in zip(CALLS[name], got, t):
+            assert k == "s" or torch.equal(a, b)
+    with pytest.raises(ctypes.ArgumentError):
+        getattr(dw, name)(d, *t, stream=types.SimpleNamespace(cuda_stream=1.5))
+    with pytest.raises(AttributeError):
+        getattr(dw, name)(d, *t, stream=object())
 
 
 @pytest.mark.gpu
