@@ -167,12 +167,12 @@ __device__ float entry_inside(const FilterGradSrc &f, int j, const float *ws, in
 }
 
 // total[e]: the block's entries j0 + e < J, in LDS
-template <int JT, bool CHECK>
-__device__ __forceinline__ void store_entries(const FilterGradSrc &src, const float *total, int j0, const float *ws, int parts, int J, float *dw)
+template <int JT, bool CHECK, typename S>
+__device__ __forceinline__ void store_entries(const FilterGradSrc &src, const S *total, int j0, const float *ws, int parts, int J, float *dw)
 {
     const int t = threadIdx.x;
     const bool mine = t < JT && j0 + t < J;
-    const float v = t < JT ? total[t] : 0.f;
+    const float v = t < JT ? (float)total[t] : 0.f;
     const bool bad = CHECK && mine && !(__builtin_fabsf(v) < __builtin_inff());
     if (mine && !bad) dw[j0 + t] = v;
     if constexpr (CHECK) {
@@ -181,7 +181,7 @@ __device__ __forceinline__ void store_entries(const FilterGradSrc &src, const fl
         __shared__ unsigned long long flags[4];
 #pragma unroll 1
         for (int e = 0; e < JT && j0 + e < J; ++e) {
-            if (__builtin_fabsf(total[e]) < __builtin_inff()) continue;
+            if (__builtin_fabsf((float)total[e]) < __builtin_inff()) continue;
             const float s = entry_inside(src, j0 + e, ws, parts, J, red, flags);
             if (t == 0) dw[j0 + e] = s;
         }
@@ -192,16 +192,17 @@ __device__ __forceinline__ void store_entries(const FilterGradSrc &src, const fl
 // take the partials p = r, r+PT, r+2PT, ... eight at a time.  All eight loads of a batch are issued
 // before the first is used, also in the last, partly filled batch (clamped index, value dropped):
 // the kernel is a few microseconds of pure load latency, so one latency per batch is what counts.
-// The batch is added in a fixed tree, then the PT sub-sums in a fixed tree through LDS.
-template <int JT, bool CHECK>
+// The batch is added in a fixed tree, then the PT sub-sums in a fixed tree through LDS, in S: 64 bits (wide) in place of
+// 32 are 0.6 to 0.9 of the error of a whole gradient, and no longer: what a batch loads is still on its way.
+template <int JT, bool CHECK, typename S>
 __global__ __launch_bounds__(256) void k_reduce_partials(const float *__restrict__ ws, int parts, int J,
                                                          float *__restrict__ dw, FilterGradSrc src)
 {
     constexpr int PT = 256 / JT;
-    __shared__ float red[PT][JT + 1];
+    __shared__ S red[PT][JT + 1];
     const int jj = threadIdx.x % JT, r = threadIdx.x / JT;
     const int j = blockIdx.x * JT + jj;
-    float acc = 0.f;
+    S acc = 0;
     if (j < J) {
         const float *p0 = ws + j;
         for (int p = r; p < parts; p += 8 * PT) {
@@ -227,16 +228,17 @@ __global__ __launch_bounds__(256) void k_reduce_partials(const float *__restrict
 
 // The same for J a multiple of 4: a lane takes four consecutive j, so that a wavefront reads 256 to 1024 consecutive bytes of a
 // partial row instead of 32 to 256; JT / 4 lanes across j, the others across the partials.
-template <int JT, bool CHECK>
+template <typename S> struct Sum4 { S x, y, z, w; };
+template <int JT, bool CHECK, typename S>
 __global__ __launch_bounds__(256) void k_reduce_partials4(const float *__restrict__ ws, int parts, int J, float *__restrict__ dw,
                                                           FilterGradSrc src)
 {
     constexpr int JL = JT / 4, PT = 256 / JL;
-    __shared__ float4 red[PT][JL];
+    __shared__ Sum4<S> red[PT][JL];
     const int jj = threadIdx.x % JL, r = threadIdx.x / JL;
     const int j = blockIdx.x * JT + jj * 4;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    auto add = [](float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); };
+    Sum4<S> acc = {0, 0, 0, 0};
+    auto add = [](auto a, auto b) { a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w; return a; };
     if (j < J) {
         const float *p0 = ws + j;
         for (int p = r; p < parts; p += 8 * PT) {
@@ -257,7 +259,7 @@ __global__ __launch_bounds__(256) void k_reduce_partials4(const float *__restric
         __syncthreads();
     }
     if constexpr (CHECK) store_entries<JT, true>(src, &red[0][0].x, blockIdx.x * JT, ws, parts, J, dw);
-    else if (r == 0 && j < J) *reinterpret_cast<float4 *>(dw + j) = red[0][jj];
+    else if (r == 0 && j < J) *reinterpret_cast<float4 *>(dw + j) = make_float4(red[0][jj].x, red[0][jj].y, red[0][jj].z, red[0][jj].w);
 }
 
 // ---- host side --------------------------------------------------------------------------------
@@ -317,7 +319,7 @@ hipError_t generic_bwd_filter(const Geom &g, int layout, int dtype, const void *
     return hipGetLastError();
 }
 
-template <bool CHECK>
+template <bool CHECK, typename S>
 static hipError_t reduce_go(const float *ws, int parts, int J, float *dw, const FilterGradSrc &src, hipStream_t st)
 {
     // threads per output chosen so that one batch of eight loads per thread covers the partials
@@ -327,7 +329,7 @@ static hipError_t reduce_go(const float *ws, int parts, int J, float *dw, const 
     if (J % 4 == 0 && J >= 2048) {
         int jt = 16;
         while (jt < 64 && (256 / (jt / 4)) * 8 > parts && (J + 2 * jt - 1) / (2 * jt) >= 128) jt *= 2;
-#define GO(JT) hipLaunchKernelGGL((k_reduce_partials4<JT, CHECK>), dim3((J + JT - 1) / JT), dim3(256), 0, st, ws, parts, J, dw, src)
+#define GO(JT) hipLaunchKernelGGL((k_reduce_partials4<JT, CHECK, S>), dim3((J + JT - 1) / JT), dim3(256), 0, st, ws, parts, J, dw, src)
         if (jt == 16) GO(16);
         else if (jt == 32) GO(32);
         else GO(64);
@@ -336,7 +338,7 @@ static hipError_t reduce_go(const float *ws, int parts, int J, float *dw, const 
     }
     int jt = 4;
     while (jt < 64 && (256 / jt) * 8 > parts && (J + 2 * jt - 1) / (2 * jt) >= 8) jt *= 2;
-#define GO(JT) hipLaunchKernelGGL((k_reduce_partials<JT, CHECK>), dim3((J + JT - 1) / JT), dim3(256), 0, st, ws, parts, J, dw, src)
+#define GO(JT) hipLaunchKernelGGL((k_reduce_partials<JT, CHECK, S>), dim3((J + JT - 1) / JT), dim3(256), 0, st, ws, parts, J, dw, src)
     switch (jt) {
     case 4: GO(4); break;
     case 8: GO(8); break;
@@ -350,11 +352,11 @@ static hipError_t reduce_go(const float *ws, int parts, int J, float *dw, const 
 
 hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, hipStream_t st)
 {
-    return reduce_go<false>(ws, parts, J, dw, FilterGradSrc{}, st);
+    return reduce_go<false, float>(ws, parts, J, dw, FilterGradSrc{}, st);
 }
-hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, const FilterGradSrc &src, hipStream_t st)
+hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, const FilterGradSrc &src, bool wide, hipStream_t st)
 {
-    return reduce_go<true>(ws, parts, J, dw, src, st);
+    return (wide ? reduce_go<true, double> : reduce_go<true, float>)(ws, parts, J, dw, src, st);
 }
 
 }  // namespace dwc

@@ -48,7 +48,8 @@ struct FilterGradSrc {
     // holds, per >= 1: per consecutive tiles, per = 0: every nparts-th tile.
     int TN, TA, TB, tn, ta, tb, per, nparts;
 };
-hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, const FilterGradSrc &src, hipStream_t st);
+// wide: the partials' sums of eight are added up in 64 bits.
+hipError_t reduce_partials(const float *ws, int parts, int J, float *dw, const FilterGradSrc &src, bool wide, hipStream_t st);
 
 // ---- NHWC row-walk kernels, multiplier 1 (nhwc.hip) ------------------------------------------
 // V = channels per lane (4 for fp32; 8 or 4 for bf16), TH = rows per strip.

@@ -493,7 +493,9 @@ hipError_t launch_reduce(const Plan &pl, const Geom &g, int layout, int dtype, c
     if (pl.variant == V_NCHWF_BWD_FILTER) nchwf_bwd_filter_tiles(g, dtype, pl.parts, &src);
     else if (pl.variant == V_NCHWF_BWD_FUSED) nchwf_bwd_fused_tiles(g, dtype, pl.parts, &src);
     else nhwca_bwd_filter_tiles(g, dtype, &src);
-    return reduce_partials(ws, pl.parts, J, dw, src, st);
+    // (the any-channel walks: one channel a lane leaves fewer lanes across the columns, each with more of them, in fp32 1.014 to 1.018 times the
+    // error against 64 bits of two channels a lane; with the partials in 64 bits 0.86 to 0.89, bf16 0.73 to 0.74, in the same time)
+    return reduce_partials(ws, pl.parts, J, dw, src, pl.variant == V_NHWCA_BWD_FILTER, st);
 }
 
 hipError_t launch_bwd_fused(const Plan &pl, const Geom &g, int layout, int dtype, const void *x, const void *dy,
