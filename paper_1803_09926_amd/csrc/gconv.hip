@@ -274,13 +274,16 @@ static bool gemm_over_rowwalk(const GGeom &g, int layout, int dtype, int pass)
 }
 
 // In place of the other row walks, whose lanes are few in short launches (a lane walks 7 to 28 rows of all its group's input channels) and, NHWC with eight channels
-// a group, many registers; in bf16 they widen every value.  Measured over 1500 random layers of 2 to 64 channels a group, up to 16 M outputs, walk
-// against these: NCHW forward and input gradient, bf16 0.27 and 0.31 of the time, 2 % longer (all of two channels a group: 1.8 M outputs 10.8 -> 9.1 us, 5.4 M 13.9 -> 19.0), fp32 0.45 up
-// to 2.5 M outputs, none longer, from 3.4 M on 1.4 to 2.5 times as long; filter gradient, bf16 0.67, of odd groups, whose walk takes one output channel at
-// a time, 1.1 to 1.3 times as long, fp32 with four output channels at a time 0.7 below 1 M and up to 1.6 from 3.4 M on.  NHWC forward and input gradient with
-// eight channels 0.4 to 0.9 in bf16, 0.6 to 0.9 in fp32 from 0.3 to 2.7 M (11x11x48, batch 35, 5.9 -> 7.0 us); with two and four 0.8 to 1.8 and 1.0 to 2.5:
-// they stay.  NHWC filter gradient in bf16 0.28 to 0.96, of two channels a group (at stride 2: four) only where the walk's lanes are few (8 channels in
-// all 0.5, 182 1.1 to 1.2); fp32 with eight channels 0.38 to 0.97 below 1 M, 1.1 to 1.3 above.
+// a group, many registers; in bf16 they widen every value.  Measured over 13 000 random layers of 2 to 64 channels a group, up to 120 M outputs in bf16, walk
+// against these, the share in brackets longer by more than 8 %.  NCHW forward and input gradient: bf16 of eight channels 0.2 up to 0.7 at 120 M [0.3 %], of
+// 3 to 5 0.45 up to 0.8 at 8 M [1 %], from 16 M on 0.98 to 1.15 [40 to 50 %, up to 2.3 times: 0.8 in rows of 16, 1.2 in rows of 60 and more], of two 0.6 to 0.9 up to
+// 2 M, 1.0 at 3 M [20 %]; fp32 0.2 to 0.7 up to 2 M, of two channels up to 0.5 M, of others that the walk takes one output at a time (3, 5, 6, 10) up to 1 M, above those
+// 0.9 to 2.  Filter gradient: bf16 0.57 to 0.8, of fewer than six channels from 16 M on 0.93 to 1.2 [22 to 72 %], of odd groups, whose walk takes one output channel at
+// a time, 1.0 to 1.2 throughout, fp32 with four output channels at a time 0.63 to 0.87 up to 0.7 M [1 %], 0.92 at 1 M [8 %], then 1.06 to 1.25.  NHWC forward and input gradient with
+// eight channels 0.4 to 0.87 in bf16, 0.7 to 0.83 in fp32 from 0.3 to 2.7 M; with two and four 0.8 to 1.8 and 1.0 to 2.5: they stay.  NHWC filter gradient in bf16 of
+// four and eight 0.4 to 0.75 throughout, of two channels a group only where the walk's lanes are few: up to 32 channels in all and 3 M outputs 0.65 to 0.82 [1 %], 0.98 at 8 M
+// [11 %], 1.1 to 1.35 above [50 %]; at stride 2 of eight 0.65 to 0.8, of four 0.72 to 0.85 from 0.1 to 1 M [5 %], 0.9 below [32 %]; fp32 with eight channels 0.8 to 0.86 up to 0.7 M
+// [2 %], 0.93 at 0.9 M [10 %], 1.06 to 1.12 above.
 static bool gemm_over_walk(const GGeom &g, int dtype, int pass, int variant, long long outputs)
 {
     const bool f32 = dtype == DT_F32;
@@ -288,14 +291,16 @@ static bool gemm_over_walk(const GGeom &g, int dtype, int pass, int variant, lon
     if (variant == GV_NCHW_K3S1) {
         // (16 output channels at a time, whether there are or not: 48x46x64 of four channels in two groups, fp32 10.5 on the walk, 15.9 here)
         const long long padded = outputs / (pass == 1 ? g.C : g.O) * (((pass == 1 ? g.C : g.O) + 15) / 16 * 16);
-        if (pass < 2) return f32 ? padded < (g.Cg == 2 ? 500000 : 2000000) : !(g.Cg == 2 && outputs > 3000000);
-        return g.Og % 4 == 0 || (!f32 && g.Og % 2 == 0 && g.Cg >= 6) ? !f32 || outputs < 1000000 : false;
+        const int few = g.Cg < g.Og ? g.Cg : g.Og;
+        const bool whole = g.Cg % 4 == 0 && g.Og % 4 == 0;       // the walk takes four output channels at a time
+        if (pass < 2) return f32 ? padded < (few == 2 ? 500000 : whole ? 2000000 : 1000000) : outputs < (few == 2 ? 2000000 : few < 6 ? 8000000 : 1ll << 31);
+        return g.Og % 4 == 0 || (!f32 && g.Og % 2 == 0 && g.Cg >= 6) ? outputs < (f32 ? 700000 : few < 6 ? 8000000 : 1ll << 31) : false;
     }
     if (variant == GV_NHWC_K3S1) {
         if (pass < 2) return g.Cg == 8 && g.Og == 8 && !gconv_nhwc_mfma_supported(g, dtype) && (!f32 || (outputs >= 300000 && outputs < 2700000));
-        return f32 ? g.Cg == 8 && outputs < 1000000 : g.Cg > 2 || g.C <= 32;
+        return f32 ? g.Cg == 8 && outputs < 700000 : g.Cg > 2 || (g.C <= 32 && outputs < 3000000);
     }
-    if (variant == GV_NHWC_BWD_FILTER_S2) return !f32 && outputs >= 8192 && (g.Cg == 8 || (g.C <= 64 && outputs < 1000000));
+    if (variant == GV_NHWC_BWD_FILTER_S2) return !f32 && (g.Cg == 8 ? outputs >= 8192 : g.C <= 64 && outputs >= 100000 && outputs < 1000000);
     return false;
 }
 

@@ -333,6 +333,31 @@ def test_launches_of_2_32_lanes_stay_with_the_generic_kernels():
 
 # ---- group convolution entry points --------------------------------------------------------------------
 
+def test_group_walks_keep_what_the_matrix_instructions_lengthen():
+    """Both sides of every line between the row walks and the 16x16 matrix instructions: 30 x 30 maps, by images."""
+    def name(which, N, C, cg, layout, dtype, og=None, stride=1):
+        return dw.gconv_variant_name(dw.group_desc(N, C, 30, 30, 3, stride, 1, C // cg, C // cg * (og or cg), layout, dtype), which)
+    lines = [
+        # pass, images on the matrix instructions, images on the walk, channels, channels a group
+        (0, 16, 80, 128, 4, dw.NCHW, dw.BF16), (1, 16, 80, 128, 4, dw.NCHW, dw.BF16), (2, 16, 80, 128, 4, dw.NCHW, dw.BF16),
+        (0, 16, 32, 128, 2, dw.NCHW, dw.BF16), (1, 16, 32, 128, 2, dw.NCHW, dw.BF16), (0, 16, 80, 126, 3, dw.NCHW, dw.BF16),
+        (0, 16, 32, 128, 4, dw.NCHW, dw.F32), (1, 16, 32, 128, 8, dw.NCHW, dw.F32), (2, 5, 8, 128, 4, dw.NCHW, dw.F32),
+        (0, 2, 8, 128, 2, dw.NCHW, dw.F32), (1, 8, 16, 126, 3, dw.NCHW, dw.F32), (0, 8, 16, 120, 10, dw.NCHW, dw.F32),
+        (2, 5, 8, 128, 8, dw.NHWC, dw.F32), (0, 16, 32, 120, 8, dw.NHWC, dw.F32), (2, 64, 128, 32, 2, dw.NHWC, dw.BF16),
+    ]
+    for which, short, long_, C, cg, layout, dtype in lines:
+        case = (which, C, cg, layout, dtype)
+        assert name(which, short, C, cg, layout, dtype).startswith("group_mfma16"), case
+        assert not name(which, long_, C, cg, layout, dtype).startswith(("group_mfma16", "group_generic")), case
+    for which in range(3):                                       # no end in bf16 from six channels a group on
+        for layout in (dw.NCHW, dw.NHWC):
+            assert name(which, 1000, 72, 8, layout, dw.BF16).startswith("group_mfma16")
+    # the smaller side of a group counts, and at stride 2 the shortest launches stay
+    assert not name(1, 60, 120, 12, dw.NCHW, dw.BF16, og=2).startswith("group_mfma16")
+    assert [name(2, N, 64, 4, dw.NHWC, dw.BF16, stride=2) for N in (6, 16, 80)] == ["group_nhwc_bwd_filter_k3s2", "group_mfma16_bwd_filter",
+                                                                                "group_nhwc_bwd_filter_k3s2"]
+
+
 def test_group_shapes_that_are_shorter_one_output_per_thread():
     """The 16x16 matrix instructions lay out a filter and stage a tile first: few products per output in few outputs, and tiles that a
     large filter leaves small, stay with the generic kernels; the row walk keeps what such tiles would lengthen."""
