@@ -386,18 +386,18 @@ template <typename T, int FAST, int BT> struct Stager<T, false, FAST, BT> {
     }
 };
 
-// Fragments between quads of input channels.  NCHW: one more than there are, so that the entries that the lanes of a wavefront lay out (taps and
-// channels of a few outputs) lie in different banks: bf16 0.955 of the time forward and 0.977 backward, fp32 0.987 and 1.003 (mean over random
-// layers).  NHWC, where lanes write consecutive outputs: 1.00 in bf16, and 1.016 in fp32, whose tiles get smaller.
-template <bool NHWC> constexpr int quad_of() { return NHWC ? 16 : 17; }
+// QUAD: fragments between quads of input channels.  NCHW: 17, one more than there are, where that costs no block on a compute unit, so that the entries that
+// the lanes of a wavefront lay out (taps and channels of a few outputs) lie in different banks: bf16 0.955 of the time forward and 0.977 backward, fp32 0.987 and
+// 1.003 (mean over random layers); always 17, a large filter left smaller tiles or fewer blocks (fp32 160x19x19 in one group, batch 30, 144 us with 16, 284
+// with 17; 80 and more channels a group 25 % longer by more than 8 %, 7x7 9 %).  NHWC: 16, lanes write consecutive outputs (17: 1.00 in bf16, and 1.016 in fp32,
+// whose tiles get smaller).
 
 // A tile that holds an infinity or NaN where 16 outputs span several groups, or whose filter does: one output per lane, its own
 // group's channels and the taps inside the image only.
-template <typename T, bool NHWC>
+template <typename T, bool NHWC, int QUAD>
 __device__ __forceinline__ void own_group_only(const GemmGeom &g, const Frag<T> *lw, const int *slots, const T *lx, T *__restrict__ out, int n0, int a0,
                                                          int b0, int ob, int ca)
 {
-    constexpr int QUAD = quad_of<NHWC>();
     const int npos = g.TN * g.TA * g.TB, nch = g.NS * 16, KK = g.K * g.K;
 #pragma unroll 1
     for (int i = threadIdx.x; i < g.OS * g.OS * npos * nch; i += 256) {
@@ -432,8 +432,8 @@ __device__ __forceinline__ void own_group_only(const GemmGeom &g, const Frag<T> 
 // chunk*16 + lane/16*4 .. +3 from cin_first of the block on.  FAST: 16 bytes of the filter a lane and load, each entry then written where it
 // belongs (one entry a load, gathered in operand order, cost a 14x14 layer of 16 channels a group 2 us forward and 4 us backward of its 13).
 // ---------------------------------------------------------------------------------------------
-template <typename T, bool NHWC, bool BWD, int FAST> struct FilterLoader {
-    static constexpr int VE = 16 / (int)sizeof(T), QUAD = quad_of<NHWC>();
+template <typename T, bool NHWC, bool BWD, int FAST, int QUAD> struct FilterLoader {
+    static constexpr int VE = 16 / (int)sizeof(T);
     const GemmGeom &g;
     int ob, KK;
     int g0, g1;              // groups of the block's outputs
@@ -572,7 +572,7 @@ template <typename T, bool NHWC, bool BWD, int FAST> struct FilterLoader {
 // input gradient at stride 2 in NCHW, both columns of a pair of output classes at a time, so that a lane's four positions are eight
 // consecutive outputs (aligned for rows of whole vectors: with an odd padding the pair is class 1 of a position and class 0 of the next).
 // ---------------------------------------------------------------------------------------------
-template <typename T, bool NHWC, bool BWD, int FAST, int P, int E, bool SCATTER>
+template <typename T, bool NHWC, bool BWD, int FAST, int P, int E, bool SCATTER, int QUAD>
 __global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg, const T *__restrict__ in, const T *__restrict__ w, T *__restrict__ out,
                                                     int nparts, unsigned nblocks)
 {
@@ -584,7 +584,7 @@ __global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg,
     constexpr bool OUTER = NHWC || SCATTER;                                // a lane has four outputs of one position, otherwise one output of four
     const int OS = BWD ? g.OS : 1, IS = BWD ? 1 : g.IS;
     const int K = g.K, KK = K * K, ob = chb * g.NS * 16;
-    constexpr int VE = 16 / (int)sizeof(T), QUAD = quad_of<NHWC>(), CHUNK = 4 * QUAD;
+    constexpr int VE = 16 / (int)sizeof(T), CHUNK = 4 * QUAD;
     const int ca = cin_first(ob, g) & ~(VE - 1);
     Frag<T> *lw = reinterpret_cast<Frag<T> *>(smem);                       // [sub-block][tap][chunk][lane]
     const int npos = g.TN * g.TA * g.TB, ngrp = (npos + 16 * P - 1) / (16 * P), nent = ngrp * 16 * P;
@@ -617,8 +617,8 @@ __global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg,
     load_tile(part, 0);
     // zeros: entries that pair different groups, inputs beside the group, outputs beside the tensor; pixels beside the rows
     Finite<T> wseen;
-    const FilterLoader<T, NHWC, BWD, FAST> fl(g, ob, slots);
-    const bool vectors = FAST && FilterLoader<T, NHWC, BWD, FAST>::takes(g) && fl.nvec <= (NHWC ? nfrag : nfrag * 3 / 2);       // (see there)
+    const FilterLoader<T, NHWC, BWD, FAST, QUAD> fl(g, ob, slots);
+    const bool vectors = FAST && FilterLoader<T, NHWC, BWD, FAST, QUAD>::takes(g) && fl.nvec <= (NHWC ? nfrag : nfrag * 3 / 2);       // (see there)
     if (vectors && g.packed)
         for (int i = threadIdx.x; i < g.NS * KK * g.nk * (4 * QUAD) * 4 / VE; i += 256) reinterpret_cast<u4v_t *>(lw)[i] = u4v_t{0u, 0u, 0u, 0u};
     if (!NHWC && FAST == 1)
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg,
         if (threadIdx.x == 0) flag[turn] = 0;                // read by all before the last barrier, set again behind the next one
         if (FAST && tile + nparts < ntiles) load_tile(tile + nparts, 0);       // on its way while this one is computed
         if (__builtin_expect(alone, 0)) {
-            own_group_only<T, NHWC>(g, lw, slots, lx, out, n0, a0, b0, ob, ca);
+            own_group_only<T, NHWC, QUAD>(g, lw, slots, lx, out, n0, a0, b0, ob, ca);
             continue;
         }
 
@@ -1122,7 +1122,7 @@ void pick_positions(GemmGeom &g, int want, int maxb, int quad = 1)
     g.tn = cdivg(g.N, g.TN); g.ta = cdivg(g.na, g.TA); g.tb = cdivg(g.nb, g.TB);
 }
 
-struct GemmPlan { GemmGeom g; StageGeom sg, sy; size_t lds; int nparts; unsigned nblocks; int npair, CLy, pitchy, fast; };
+struct GemmPlan { GemmGeom g; StageGeom sg, sy; size_t lds; int nparts; unsigned nblocks; int npair, CLy, pitchy, fast, quad; };
 
 // copying a tile of TN images of LH x LW pixels and CL channels (NCHW: rows of W columns) with 256 lanes
 StageGeom stage_geom(int layout, int VE, int TN, int LH, int LW, int CL, int pitch, int W, bool split)
@@ -1185,7 +1185,7 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
                 pick_positions(g, want, layout == LAYOUT_NHWC ? 32 : 64, pairs ? 4 : 1);
                 g.LH = g.IS * (g.TA - 1) + reach; g.LW = g.IS * (g.TB - 1) + reach + g.shift;
                 // (positions in the tables up to a multiple of 64)
-                pl->lds = (size_t)ns * q.K * q.K * g.nk * 16 * (layout == LAYOUT_NHWC ? quad_of<true>() : quad_of<false>()) * esz + (size_t)cdivg(g.TN * g.TA * g.TB, 64) * 64 * (g.OS > 1 ? 16 : 8) + (g.OS > 1 ? 256 : 0) + 16 +
+                pl->lds = (size_t)ns * q.K * q.K * g.nk * 256 * esz + (size_t)cdivg(g.TN * g.TA * g.TB, 64) * 64 * (g.OS > 1 ? 16 : 8) + (g.OS > 1 ? 256 : 0) + 16 +
                           ((size_t)g.TN * g.LH * g.LW * g.pitch * esz + 15) / 16 * 16;
             };
             auto blocks = [&]() { return (long long)g.tn * g.ta * g.tb * cdivg(blocks16, ns); };
@@ -1287,6 +1287,11 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
     // (filter gradient in fp32: four loads of a lane, each of 64 lanes in a row, are the shorter way; us, 376x127x127 in 188 groups, NCHW, 40 against 46,
     // 94x87x6 in three groups, 5x5, NHWC batch 7, 20 against 24)
     if (pass == 2 && dtype == DT_F32 && pl->fast == 2) pl->fast = 0;
+    pl->quad = 16;
+    if (pass < 2 && layout == LAYOUT_NCHW && pl->fast) {
+        const size_t padded = pl->lds + (size_t)g.NS * q.K * q.K * g.nk * 16 * esz;
+        if (padded <= LDS_OF_ONE && resident_blocks(padded, 4) == resident_blocks(pl->lds, 4)) { pl->quad = 17; pl->lds = padded; }
+    }
     pl->g = g;
     return true;
 }
@@ -1352,17 +1357,25 @@ template <typename T, bool NHWC>
 static hipError_t gemm_go(const GemmPlan &pl, const void *in, const void *w, void *out, hipStream_t st)
 {
     constexpr bool NCHW = !NHWC;
-    auto pick = [&](auto p, auto fast) {
-        constexpr int P = decltype(p)::value, FAST = decltype(fast)::value;
-        return !pl.g.bwd ? k_gconv_gemm<T, NHWC, false, FAST, P, 1, false>
-               : pl.g.pairs ? k_gconv_gemm<T, NHWC, true, FAST, P, (NCHW && FAST ? 2 : 1), false>
-               : pl.g.OS > 1 ? k_gconv_gemm<T, NHWC, true, FAST, P, 1, NCHW> : k_gconv_gemm<T, NHWC, true, FAST, P, 1, false>;
+    auto pick = [&](auto p, auto fast, auto quad) {
+        constexpr int P = decltype(p)::value, FAST = decltype(fast)::value, QUAD = decltype(quad)::value;
+        return !pl.g.bwd ? k_gconv_gemm<T, NHWC, false, FAST, P, 1, false, QUAD>
+               : pl.g.pairs ? k_gconv_gemm<T, NHWC, true, FAST, P, (NCHW && FAST ? 2 : 1), false, QUAD>
+               : pl.g.OS > 1 ? k_gconv_gemm<T, NHWC, true, FAST, P, 1, NCHW, QUAD> : k_gconv_gemm<T, NHWC, true, FAST, P, 1, false, QUAD>;
     };
     const int P = tiles_at_once(pl.g.NS, pl.g.TN * pl.g.TA * pl.g.TB, sizeof(T) == 4 ? DT_F32 : DT_BF16);
-    auto of = [&](auto fast) {
-        return P == 4 ? pick(std::integral_constant<int, 4>(), fast) : P == 2 ? pick(std::integral_constant<int, 2>(), fast) : pick(std::integral_constant<int, 1>(), fast);
+    auto of = [&](auto fast, auto quad) {
+        return P == 4 ? pick(std::integral_constant<int, 4>(), fast, quad)
+               : P == 2 ? pick(std::integral_constant<int, 2>(), fast, quad) : pick(std::integral_constant<int, 1>(), fast, quad);
     };
-    auto kernel = pl.fast == 1 ? of(std::integral_constant<int, 1>()) : pl.fast ? of(std::integral_constant<int, 2>()) : of(std::integral_constant<int, 0>());
+    auto padded = [&](auto fast) {
+        if constexpr (NCHW) {
+            if (pl.quad == 17) return of(fast, std::integral_constant<int, 17>());
+        }
+        return of(fast, std::integral_constant<int, 16>());
+    };
+    auto kernel = pl.fast == 1 ? padded(std::integral_constant<int, 1>()) : pl.fast ? padded(std::integral_constant<int, 2>())
+                  : of(std::integral_constant<int, 0>(), std::integral_constant<int, 16>());
     hipLaunchKernelGGL(kernel, dim3(pl.nblocks), dim3(256), pl.lds, st, pl.g, pl.sg, (const T *)in, (const T *)w, (T *)out,
                        pl.nparts, pl.nblocks);
     return hipGetLastError();

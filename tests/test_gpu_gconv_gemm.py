@@ -63,6 +63,22 @@ def test_mfma16_group_conv_matches_oracle(case, layout, dtype):
     gu.assert_close(gu.to_host(dwt), og.bwd_filter(x, dy, **kw), gu.TOL_F32_FILTER, "bwd_filter " + name)
 
 
+# NCHW layers whose filter has no room for a padding of its own: a block less would fit a compute unit, or none at all
+TIGHT = [
+    ("tight_cg160", 1, 160, 160, 1, 19, 19, 3, 1, 1),
+    ("tight_k5", 1, 16, 16, 1, 12, 20, 5, 1, 2),
+    ("tight_k5_bf16", 3, 32, 32, 1, 7, 33, 5, 1, 2),
+    ("tight_pairs", 1, 96, 96, 2, 7, 12, 3, 2, 1),                 # input gradient, two classes at a time
+    ("tight_s3", 1, 10, 41, 1, 7, 6, 5, 3, 0),
+]
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("case", TIGHT, ids=[c[0] for c in TIGHT])
+def test_filters_without_padding_match_oracle(case, dtype):
+    test_mfma16_group_conv_matches_oracle(case, wl.NCHW, dtype)
+
+
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("layout", [wl.NCHW, wl.NHWC], ids=["nchw", "nhwc"])
 def test_infinity_stays_inside_its_group(layout, dtype):
