@@ -356,7 +356,8 @@ static Plan plan_bwd_filter_v(const Geom &g, int layout, int dtype, int force_v)
 Plan plan_bwd_filter(const Geom &g, int layout, int dtype)
 {
     Plan pl = plan_bwd_filter_v(g, layout, dtype, 0);
-    if (short_bwd_filter_shorter(as_group(g), layout, pl.variant == V_GENERIC && pl.parts == 1 ? FILTER_GENERIC_ONE : FILTER_TWO)) { pl.variant = V_SHORT_BWD_FILTER; pl.parts = 1; }
+    const FilterWay way = pl.variant == V_GENERIC && pl.parts == 1 ? FILTER_GENERIC_ONE : pl.variant == V_NCHWS_BWD_FILTER ? FILTER_SMALL_PLANES : FILTER_TWO;
+    if (short_bwd_filter_shorter(as_group(g), layout, dtype, way)) { pl.variant = V_SHORT_BWD_FILTER; pl.parts = 1; }
     return pl;
 }
 

@@ -113,16 +113,23 @@ hipError_t short_go(const ShortGeom &g, int K, const void *x, const void *dy, fl
 
 }  // namespace
 
-// Estimated time in us: the launch with the sums of a block, the rounds of a lane's loads, all loads of a compute unit, and its blocks.  Fitted to
-// 7000 random layers of up to 40 000 positions: four of five between 0.85 and 1.12 times the measured time.
-static double short_us(const ShortGeom &g, int K, int layout)
+// Estimated time in us: the launch with the sums of a block, the rounds of a lane's loads, all loads of a compute unit, its blocks, and what the loads touch: NCHW
+// the lines of a wavefront's positions in x (those of small or strided planes lie far apart), NHWC all of x, of which a block takes a part of every
+// line.  Fitted to 110 000 random layers of up to 13 us: nine of ten between 0.9 and 1.1 times the measured time, one in a hundred
+// longer by 1.25 (without the lines 1.3 to 1.5, and 2.2 in planes of 2 x 2 outputs).
+static double short_us(const ShortGeom &g, int K, int layout, int dtype, double xelems)
 {
-    static const float fit[2][3][4] = {{{2.82f, 1.2f, 0.65f, 1.75f}, {4.17f, 0.59f, 0.52f, 4.7f}, {5.8f, 1.07f, 0.44f, 8.5f}},
-                                       {{2.63f, 1.21f, 0.8f, 0.66f}, {3.4f, 0.65f, 0.58f, 2.1f}, {4.63f, 2.07f, 0.7f, 1.6f}}};
+    static const float fit[2][3][5] = {{{2.87f, 1.12f, 0.375f, 1.59f, 0.0168f}, {4.02f, 0.54f, 0.417f, 4.38f, 0.0457f}, {4.59f, 1.18f, 0.161f, 11.95f, 0.0802f}},
+                                       {{2.92f, 1.14f, 0.669f, 0.45f, 0.68f}, {3.54f, 0.666f, 0.559f, 1.65f, 0.68f}, {5.25f, 1.92f, 0.f, 6.9f, 0.81f}}};
     const float *c = fit[layout == LAYOUT_NHWC][K / 2 - 1];
-    const int U = K == 3 ? 2 : 1, step = (64 >> g.lcw) * g.ws * U, per = g.cw * (4 / g.ws);
+    const int U = K == 3 ? 2 : 1, step = (64 >> g.lcw) * g.ws * U, per = g.cw * (4 / g.ws), esz = dtype == DT_F32 ? 4 : 2;
     const double rounds = (g.npix + step - 1) / step, blocks = (g.npairs + per - 1) / per;
-    return c[0] + c[1] * rounds + c[2] * blocks * rounds * U * K * K / (256 * 64) + c[3] * blocks / 1024;
+    double touched = xelems * esz * 1e-6;
+    if (layout == LAYOUT_NCHW) {
+        const double planes = 64.0 / ((double)g.Ho * g.Wo), lines = planes * g.H * g.W * esz / 128 + (planes > 1 ? planes : 1);
+        touched = (blocks > 256 ? blocks / 256 : 1) * rounds * U * lines;
+    }
+    return c[0] + c[1] * rounds + c[2] * blocks * rounds * U * K * K / (256 * 64) + c[3] * blocks / 1024 + c[4] * touched;
 }
 
 // One launch of the generic kernels (a single partial, written where the gradient goes), fitted to 30 000 random layers: 0.9 to 1.3 of the time.
@@ -136,11 +143,12 @@ static double generic_one_us(const ShortGeom &g, int K, int layout)
     return 2.2 + 0.3 * steps + 0.53 * blocks * steps;
 }
 
-// Instead of two launches up to the estimates below: on 1493 random layers below 7 us in NCHW 3x3 0.69 of the time, 3 % longer by more than 8 %, 5x5 0.68 and 3 %,
-// 7x7 0.8 and 4 %; NHWC 0.70 and 3 %, 5x5 0.79 and 4 %, 7x7 is no shorter; instead of the matrix instructions 0.70 and 3 % (NHWC 0.74 and 6 %), 5x5
-// 0.69 and 1 % (0.67 and 5 %).  That is the GPU's time; the host saves 2.9 us of the second launch beside it.  Instead of one launch of the generic
+// Instead of two launches up to the estimates below, over 66 000 random layers in a loop of calls, in brackets the share longer by more than 8 %: 3x3 0.63 to
+// 0.67 of the time [0.04 %], instead of the small-plane kernels, whose two launches take 5.6 us, 0.65 [0.1 %]; 5x5 NCHW 0.63 [0.2 %], small planes 0.72 [0 %], NHWC
+// 0.56 and 0.70 [0.05 and 0.3 %]; 7x7 NCHW 0.75 [0.8 %], NHWC no shorter; instead of the matrix instructions 3x3 0.67 [0.1 %] and 0.61 [0.8 %], 5x5
+// 0.67 [0.3 %] and 0.59 [0.8 %].  An estimate of half a us more is where 3 to 10 % are longer.  Instead of one launch of the generic
 // kernels where its own estimate is that much below theirs: 0.40 to 0.73 of the time, 1 % longer.
-bool short_bwd_filter_shorter(const GGeom &q, int layout, FilterWay way)
+bool short_bwd_filter_shorter(const GGeom &q, int layout, int dtype, FilterWay way)
 {
     ShortGeom g;
     if (!short_geom(q, layout, &g)) return false;
@@ -149,11 +157,12 @@ bool short_bwd_filter_shorter(const GGeom &q, int layout, FilterWay way)
         return e && atoi(e) != 0;
     }
     const bool nhwc = layout == LAYOUT_NHWC;
-    const double us = short_us(g, q.K, layout);
+    const double us = short_us(g, q.K, layout, dtype, (double)q.N * q.C * q.H * q.W);
     switch (way) {
     case FILTER_GENERIC_ONE: return us < 0.85 * generic_one_us(g, q.K, layout);
-    case FILTER_MATRIX: return us < (q.K == 3 ? (nhwc ? 9.0 : 10.0) : (nhwc ? 10.0 : 12.0));
-    default: return us < (q.K == 3 ? 7.0 : q.K == 5 ? (nhwc ? 8.0 : 9.0) : (nhwc ? 0.0 : 11.5));
+    case FILTER_MATRIX: return us < (q.K == 3 ? (nhwc ? 8.0 : 10.0) : (nhwc ? 9.0 : 12.0));
+    case FILTER_SMALL_PLANES: return us < (q.K == 3 ? 6.0 : 6.5);
+    default: return us < (q.K == 3 ? 7.25 : q.K == 5 ? (nhwc ? 8.0 : 9.0) : (nhwc ? 0.0 : 11.0));
     }
 }
 

@@ -331,6 +331,27 @@ def test_launches_of_2_32_lanes_stay_with_the_generic_kernels():
     assert [dw.variant_name(ok, i) for i in range(3)] == ["nhwc_any_k3s1", "nhwc_any_k3s1_flip", "nhwc_any_bwd_filter_k3s1"]
 
 
+def test_short_filter_gradients_where_one_launch_is_no_shorter():
+    """Layers on which the one-launch filter gradient measured 1.2 to 2.2 times the two launches: few blocks beside the small-plane kernels, planes whose positions
+    lie far apart; and neighbours on which it is 0.5 to 0.8 of them (one partial)."""
+    def partials(*a, groups=0, **kw):
+        if groups:
+            d = dw.group_desc(*a, groups=groups, **kw)
+            return dw.gconv_bwd_filter_workspace_bytes(d) // (4 * d.O * d.C // groups * d.K ** 2)
+        d = dw.desc(*a, **kw)
+        return dw.bwd_filter_workspace_bytes(d) // (4 * d.C * d.mult * d.K ** 2)
+    for dtype in (dw.F32, dw.BF16):
+        for a in ((51, 8, 5, 7, 5, 1, 2), (39, 8, 7, 7, 5, 1, 2), (224, 8, 5, 6, 5, 2, 2), (23, 24, 8, 8, 3, 1, 1)):
+            assert partials(*a, dtype=dtype) > 1, a
+        for a, groups in (((55, 336, 4, 4, 3, 2, 1), 21), ((244, 72, 4, 4, 5, 2, 2), 9), ((120, 104, 4, 4, 5, 2, 2), 13)):
+            assert partials(*a, groups=groups, dtype=dtype) > 1, a
+        for layout in (dw.NCHW, dw.NHWC):
+            for a in ((8, 8, 5, 7, 5, 1, 2), (8, 10, 9, 9, 5, 2, 2), (3, 24, 8, 8, 3, 1, 1), (1, 300, 14, 14, 3, 1, 1)):
+                assert partials(*a, layout=layout, dtype=dtype) == 1, a
+            for a, groups in (((4, 336, 8, 8, 3, 2, 1), 21), ((2, 72, 9, 9, 5, 1, 2), 9)):
+                assert partials(*a, groups=groups, layout=layout, dtype=dtype) == 1, a
+
+
 # ---- group convolution entry points --------------------------------------------------------------------
 
 def test_group_walks_keep_what_the_matrix_instructions_lengthen():
