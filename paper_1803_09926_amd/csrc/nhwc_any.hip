@@ -352,15 +352,19 @@ bool any_k(const Geom &g)
 }
 
 // Channels per lane.  5x5 and 7x7 in launches of few lanes take one channel: the walk is then as long as its loads take, and twice the wavefronts with half the
-// registers hide more of them (random layers, share of the time with two: fp32 below 1.6 M outputs 5x5 0.72 to 1 (119x119x84 at stride 2, 1.5 M, filter gradient 1.7), 7x7 0.66 to 1 in every pass, from
-// 2 M on up to 1.1; bf16, whose lanes then read two bytes, filter gradient below 0.4 M 0.68 to 0.92, the other passes below 0.16 M 0.89 to 0.98, above up to 1.25).
+// registers hide more of them (50 000 random layers, share of the time with two: fp32 5x5 0.80 to 0.97, filter gradient 0.80 to 0.90 below 1.2 M outputs and up to 1.7 above
+// (119x119x84 at stride 2, 1.5 M), 7x7 0.75 to 0.92 up to 1.4 M, from there on 0.92 with one in seven longer by more than 8 %, but for the filter gradient, 0.83 up to
+// 1.6 M; bf16, whose lanes then read two bytes, filter gradient below 0.4 M 0.75 to 0.93, the other passes below 0.16 M 0.84 to 0.98, above up to 1.25).
 int any_vec(const Geom &g, int dtype, int pass)
 {
     if (g.m != 1) return 1;
     if (g.C % 4 == 0 && g.K == 3) return 4;
     if (g.C % 2) return 1;
+    if (g.K == 3) return 2;
+    if (const char *e = tune_env("DWCONV_TUNE_ANY_V")) return atoi(e) == 1 ? 1 : 2;
     const long long outputs = (long long)g.N * g.O * g.Ho * g.Wo;
-    return g.K > 3 && outputs < (dtype == DT_F32 ? (pass == 2 && g.K == 5 ? 1200000 : 1600000) : pass == 2 ? 400000 : 160000) ? 1 : 2;
+    const long long few = dtype == DT_F32 ? (pass < 2 ? 1400000 : g.K == 5 ? 1200000 : 1600000) : pass == 2 ? 400000 : 160000;
+    return outputs < few ? 1 : 2;
 }
 
 // balanced strips of about `target` rows, shorter while the launch has fewer than 1024 wavefronts, down to four rows; to two below 256 (0.87 to 0.9 of

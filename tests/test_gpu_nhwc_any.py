@@ -45,3 +45,30 @@ def test_any_channel_walks_match_oracle(gpu_lib, N, layer, dtype):
     print("case", layer, N, dtype, [dw.variant_name(d, i) for i in range(3)], flush=True)
     assert dw.variant_name(d, 0).startswith("nhwc_any") and dw.variant_name(d, 2).startswith("nhwc_any")
     gu.check_layer_full(layer, N, wl.NHWC, dtype, seed=8200 + layer.C + dtype)
+
+
+# 5x5 and 7x7 with two channels a lane: beyond the sizes below which a lane takes one, and forced in small layers at the edges of the tiling
+LARGE = [
+    (11, Layer("k7_above", 226, 28, 28, 7, 1, 3)),
+    (10, Layer("k5_s2_above", 230, 57, 56, 5, 2, 2)),
+]
+TWO = [c for c in CASES if c[1].K > 3 and c[1].mult == 1 and c[1].C % 2 == 0]
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("N,layer", LARGE, ids=[l.name for _, l in LARGE])
+def test_launches_of_many_lanes_match_oracle(gpu_lib, N, layer, dtype):
+    d = gu.desc_for(layer, N, wl.NHWC, dtype)
+    print("case", layer, N, dtype, [dw.variant_name(d, i) for i in range(3)], flush=True)
+    need = dw.bwd_filter_workspace_bytes(d)
+    for channels, same in ((1, False), (2, True)):                    # the partials tell which of the two is planned
+        with dw.tuning_overrides({"DWCONV_TUNE_ANY_V": channels}):
+            assert (dw.bwd_filter_workspace_bytes(d) == need) == same
+    gu.check_layer_full(layer, N, wl.NHWC, dtype, seed=8250 + dtype)
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("N,layer", TWO, ids=[l.name for _, l in TWO])
+def test_two_channels_a_lane_match_oracle(gpu_lib, N, layer, dtype):
+    with dw.tuning_overrides({"DWCONV_TUNE_ANY_V": 2, "DWCONV_TUNE_SHORT": 0}):
+        test_any_channel_walks_match_oracle(gpu_lib, N, layer, dtype)
