@@ -76,6 +76,17 @@ def test_padding_is_no_product(gpu_lib, layout, N, layer, dtype):
 
 
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("layout,N,layer", LAYERS, ids=[c[2].name for c in LAYERS])
+def test_padding_is_no_product_in_the_kernels_of_longer_launches(gpu_lib, layout, N, layer, dtype):
+    """The same layers without the one-launch filter gradient and with two channels a lane in the any-channel walks: kernels that do multiply with
+    the padding, and a second stage that adds entries up again."""
+    with dw.tuning_overrides({"DWCONV_TUNE_SHORT": 0, "DWCONV_TUNE_ANY_V": 2}):
+        d = gu.desc_for(layer, N, layout, dtype)
+        assert dw.bwd_filter_workspace_bytes(d) > layer.O * layer.K ** 2 * 4               # several partials
+        test_padding_is_no_product(gpu_lib, layout, N, layer, dtype)
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("layout", [wl.NCHW, wl.NHWC], ids=["nchw", "nhwc"])
 @pytest.mark.parametrize("case", GROUPS, ids=[c[0] for c in GROUPS])
 def test_padding_is_no_product_in_a_group(gpu_lib, case, layout, dtype):

@@ -47,6 +47,24 @@ def test_noalloc_filter_gradient_matches_the_workspace_entry_point(name, layout,
         gu.assert_close(gu.to_host(got), ref, gu.TOL_F32_FILTER, "noalloc bwd_filter %s call %d" % (name, step))
 
 
+# the same where both calls leave several partials in the array (a single one goes where the gradient goes, past the array)
+SEVERAL = [
+    ("nchw_f32", wl.NCHW, wl.F32, [(wl.Layer("big", 48, 28, 28), 12), (wl.Layer("small", 40, 14, 14), 7)]),
+    ("nchw_bf16_s2", wl.NCHW, wl.BF16, [(wl.Layer("big", 32, 64, 64, 3, 2, 1), 40), (wl.Layer("small", 8, 56, 56, 3, 2, 1), 24)]),
+    ("nhwc_bf16_k5", wl.NHWC, wl.BF16, [(wl.Layer("big", 32, 28, 28, 5, 1, 2), 8), (wl.Layer("small", 24, 17, 19, 5, 1, 2), 5)]),
+    ("nchw_flat_k5", wl.NCHW, wl.F32, [(wl.Layer("big", 24, 75, 75, 5, 1, 2), 8), (wl.Layer("small", 11, 41, 43, 5, 1, 2), 4)]),
+    ("generic", wl.NCHW, wl.F32, [(wl.Layer("big", 10, 119, 123, 4, 3, 2), 25), (wl.Layer("small", 6, 90, 85, 4, 1, 0), 4)]),
+]
+
+
+@pytest.mark.parametrize("name,layout,dtype,seq", SEVERAL, ids=[s[0] for s in SEVERAL])
+def test_noalloc_filter_gradient_of_several_partials(name, layout, dtype, seq):
+    for layer, N in seq:
+        d = gu.desc_for(layer, N, layout, dtype)
+        assert dw.bwd_filter_workspace_bytes(d) > layer.O * layer.K ** 2 * 4
+    test_noalloc_filter_gradient_matches_the_workspace_entry_point(name, layout, dtype, seq)
+
+
 def test_noalloc_rejects_shapes_beyond_its_scratch_and_bad_arguments():
     lib = dw.load()
     # very many channels: 18 MiB of partial sums, beyond the 16 MiB array (nothing is launched for it)
