@@ -109,7 +109,9 @@ int dwconv_bwd_data(const dwconv_desc *desc, const void *dy, const void *w, void
  * 16-byte aligned; contents on entry are ignored and on exit unspecified.
  * The reduction uses no atomics: per-thread fp32 partial sums, a fixed-order reduction inside
  * each workgroup, one partial per workgroup in the workspace, and a second kernel that adds the
- * partials in a fixed order.  The result is bit-identical from run to run. */
+ * partials in a fixed order.  Short launches run one kernel whose workgroups own their filter entries,
+ * and a single partial is written to dw at once; the workspace is asked for all the same.
+ * The result is bit-identical from run to run. */
 int dwconv_bwd_filter(const dwconv_desc *desc, const void *x, const void *dy, void *dw,
                       void *workspace, size_t workspace_bytes, void *stream);
 
@@ -205,7 +207,7 @@ int gconv_fwd(const dwconv_group_desc *desc, const void *x, const void *w, void 
 /* dy, w: device, read.  dx: device, every element written. */
 int gconv_bwd_data(const dwconv_group_desc *desc, const void *dy, const void *w, void *dx, void *stream);
 /* x, dy: device, read.  dw: device, fp32, written in full.  workspace as for dwconv_bwd_filter;
- * two-stage reduction without atomics, bit-identical from run to run. */
+ * one or two kernels as there, without atomics, bit-identical from run to run. */
 int gconv_bwd_filter(const dwconv_group_desc *desc, const void *x, const void *dy, void *dw,
                      void *workspace, size_t workspace_bytes, void *stream);
 /* Name of the kernel variant for `pass` (0 fwd, 1 bwd_data, 2 bwd_filter); "invalid" for a bad desc. */

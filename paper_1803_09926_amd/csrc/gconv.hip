@@ -370,10 +370,12 @@ static GPlan gplan(const GGeom &g, int layout, int dtype, int pass)
         pl.name = pass == 0 ? "group_mfma16" : pass == 1 ? "group_mfma16_bwd_data" : "group_mfma16_bwd_filter";
         if (pass == 2) pl.parts = gconv_gemm_parts(g, layout, dtype);
     }
-    // (under the name of the family that takes the shape in longer launches)
     const FilterWay way = pl.variant == GV_GEMM ? FILTER_MATRIX : pl.variant == GV_GENERIC && pl.parts == 1 ? FILTER_GENERIC_ONE
                           : pl.variant == GV_NCHWS_K3S1 ? FILTER_SMALL_PLANES : FILTER_TWO;
-    if (pass == 2 && pl.variant != GV_NCHWS_MFMA_BWD_FILTER && short_bwd_filter_shorter(g, layout, dtype, way)) { pl.variant = GV_SHORT_BWD_FILTER; pl.parts = 1; }
+    if (pass == 2 && pl.variant != GV_NCHWS_MFMA_BWD_FILTER && short_bwd_filter_shorter(g, layout, dtype, way)) {
+        pl.variant = GV_SHORT_BWD_FILTER; pl.parts = 1;
+        pl.name = layout == LAYOUT_NCHW ? "group_nchw_short_bwd_filter" : "group_nhwc_short_bwd_filter";
+    }
     // a tuned filter gradient whose partial sums would not fit in 64 MiB (very wide rows): the generic kernels
     if (pass == 2 && pl.variant != GV_GENERIC && (long long)pl.parts * g.O * g.Cg * g.K * g.K * 4 > (64ll << 20)) {
         const GPlan gen = {GV_GENERIC, gconv_generic_bwd_filter_parts(g), 0, 0, 0, "group_generic"};

@@ -357,7 +357,10 @@ Plan plan_bwd_filter(const Geom &g, int layout, int dtype)
 {
     Plan pl = plan_bwd_filter_v(g, layout, dtype, 0);
     const FilterWay way = pl.variant == V_GENERIC && pl.parts == 1 ? FILTER_GENERIC_ONE : pl.variant == V_NCHWS_BWD_FILTER ? FILTER_SMALL_PLANES : FILTER_TWO;
-    if (short_bwd_filter_shorter(as_group(g), layout, dtype, way)) { pl.variant = V_SHORT_BWD_FILTER; pl.parts = 1; }
+    if (short_bwd_filter_shorter(as_group(g), layout, dtype, way)) {
+        pl.variant = V_SHORT_BWD_FILTER; pl.parts = 1;
+        pl.name = layout == LAYOUT_NCHW ? "nchw_short_bwd_filter" : "nhwc_short_bwd_filter";
+    }
     return pl;
 }
 

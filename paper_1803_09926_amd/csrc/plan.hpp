@@ -27,7 +27,7 @@ enum Variant {
     V_NCHWD_BWD_FUSED,  // a = V, b = TH
     V_NCHWS_BWD_FUSED,  // a = U, c = NI
     V_NCHWF_BWD_FUSED,
-    V_SHORT_BWD_FILTER, // one launch, no partials, on the way of a family that takes the shape in longer launches (and gives it its name)
+    V_SHORT_BWD_FILTER, // one launch, no partials
 };
 
 struct Plan {

@@ -83,6 +83,11 @@ VARIANT_KERNELS = {
     # k_gconv_nhwc_mfma<T, CG, FLIP, PF>
     "fwd:group_nhwc_mfma_k3s1": [r"k_gconv_nhwc_mfma<[\w ]+, \d+, false, \d+>"],
     "bwd_data:group_nhwc_mfma_k3s1_flip": [r"k_gconv_nhwc_mfma<[\w ]+, \d+, true, \d+>"],
+    # k_short_bwd_filter<T, LAYOUT, K>: the whole filter gradient in one launch (group layers have the same kernel)
+    "bwd_filter:nchw_short_bwd_filter": [r"k_short_bwd_filter<[\w ]+, 0, \d+>"],
+    "bwd_filter:nhwc_short_bwd_filter": [r"k_short_bwd_filter<[\w ]+, 1, \d+>"],
+    "bwd_filter:group_nchw_short_bwd_filter": [r"k_short_bwd_filter<[\w ]+, 0, \d+>"],
+    "bwd_filter:group_nhwc_short_bwd_filter": [r"k_short_bwd_filter<[\w ]+, 1, \d+>"],
     "bwd_filter:group_nhwc_bwd_filter_k3s1": [r"k_gconv_nhwc_bwd_filter<", r"k_gconv_nhwc_bwd_filter_dot2<", r"k_gconv_nhwc_xchg_bwd_filter<"],
 }
 
@@ -165,7 +170,8 @@ def stats(d, config=None, fused=False):
     steps = sorted(per_key[k][0] / launches[k] for k in known)[len(known) // 2]
     red = [r for r in rows if "k_reduce_partials" in r["Name"]]
     red_us = sum(int(r["TotalDurationNs"]) for r in red) / 1e3
-    nfilter = sum(v for k, v in launches.items() if k.startswith("bwd_filter:") or k.startswith("bwd:"))
+    two_stage = lambda k: k.startswith(("bwd_filter:", "bwd:")) and "short_bwd_filter" not in k
+    nfilter = sum(v for k, v in launches.items() if two_stage(k))
     print("# workload %s: %.0f steps in the trace; per layout and pass, per step: kernel time, algorithmic bytes, rate" % (cfg["name"], steps))
     print("# (bwd_filter, and bwd = the whole backward pass in one call: stage 1 + its share of the stage-2 launches k_reduce_partials, split by launch count)")
     print("%-6s %-11s %10s %12s %9s %7s" % ("layout", "pass", "us/step", "MB/step", "GB/s", "%peak"))
@@ -177,7 +183,7 @@ def stats(d, config=None, fused=False):
                 continue
             us = sum(per_key[k][1] for k in ks) / steps
             if pname in ("bwd_filter", "bwd") and nfilter:
-                us += red_us / steps * sum(launches[k] for k in ks) / nfilter
+                us += red_us / steps * sum(launches[k] for k in ks if two_stage(k)) / nfilter
             b = sum(nbytes[k] for k in ks)
             grand_us += us; grand_b += b
             print("pass %-6s %-11s %10.1f %12.1f %9.1f %7.2f" % (lay, pname, us, b / 1e6, b / us / 1e3, b / us / 1e3 / 80.0))

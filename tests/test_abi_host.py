@@ -1,6 +1,7 @@
 """Host-side checks of the C ABI: the library loads, exports every symbol the header declares,
 and every validation error is reported before any HIP call (so this runs with no GPU)."""
 import ctypes
+import itertools
 import os
 import re
 import subprocess
@@ -163,7 +164,9 @@ def test_shapes_too_small_for_the_nhwc_walks_stay_generic():
     for K, pixels in ((3, 18), (5, 50), (7, 98)):
         for n in (pixels - 1, pixels):
             d = dw.desc(n, 7, 1, 1, K, 2, K // 2, 1, dw.NHWC)          # n images of one output pixel
-            assert dw.variant_name(d, 2) == ("generic" if n < pixels else "nhwc_any_bwd_filter_k%ds2" % K), (K, n)
+            with dw.tuning_overrides({"DWCONV_TUNE_SHORT": 0}):        # (the one-launch kernel takes some of them before either)
+                name = dw.variant_name(d, 2)
+            assert name == ("generic" if n < pixels else "nhwc_any_bwd_filter_k%ds2" % K), (K, n)
     assert dw.variant_name(dw.desc(64, 1, 101, 4, 3, 1, 1, 1, dw.NHWC), 0) == "generic"      # 4 lanes a row, 6464 rows
     assert dw.variant_name(dw.desc(64, 1, 101, 5, 3, 1, 1, 1, dw.NHWC), 0) == "nhwc_any_k3s1"
     assert dw.variant_name(dw.desc(16, 1, 101, 8, 3, 2, 1, 1, dw.NHWC), 0) == "nhwc_any_k3s2"         # 4 lanes, 816 rows
@@ -340,6 +343,13 @@ def test_short_filter_gradients_where_one_launch_is_no_shorter():
             return dw.gconv_bwd_filter_workspace_bytes(d) // (4 * d.O * d.C // groups * d.K ** 2)
         d = dw.desc(*a, **kw)
         return dw.bwd_filter_workspace_bytes(d) // (4 * d.C * d.mult * d.K ** 2)
+    for group, layout in itertools.product((False, True), (dw.NCHW, dw.NHWC)):     # reported under its own name
+        name = "%s%s_short_bwd_filter" % ("group_" if group else "", "nchw" if layout == dw.NCHW else "nhwc")
+        long_, short = [(dw.group_desc(n, 32, 12, 12, groups=8, layout=layout) if group else dw.desc(n, 32, 12, 12, layout=layout)) for n in (64, 1)]
+        of = dw.gconv_variant_name if group else dw.variant_name
+        assert of(short, 2) == name and "short" not in of(long_, 2)
+        with dw.tuning_overrides({"DWCONV_TUNE_SHORT": 0}):
+            assert "short" not in of(short, 2)
     for dtype in (dw.F32, dw.BF16):
         for a in ((51, 8, 5, 7, 5, 1, 2), (39, 8, 7, 7, 5, 1, 2), (224, 8, 5, 6, 5, 2, 2), (23, 24, 8, 8, 3, 1, 1)):
             assert partials(*a, dtype=dtype) > 1, a

@@ -43,7 +43,8 @@ CASES = [
 def test_any_channel_walks_match_oracle(gpu_lib, N, layer, dtype):
     d = gu.desc_for(layer, N, wl.NHWC, dtype)
     print("case", layer, N, dtype, [dw.variant_name(d, i) for i in range(3)], flush=True)
-    assert dw.variant_name(d, 0).startswith("nhwc_any") and dw.variant_name(d, 2).startswith("nhwc_any")
+    # (short filter gradients run one launch of another kernel; here again with that switched off: test_gpu_short_filter)
+    assert dw.variant_name(d, 0).startswith("nhwc_any") and dw.variant_name(d, 2).startswith(("nhwc_any", "nhwc_short"))
     gu.check_layer_full(layer, N, wl.NHWC, dtype, seed=8200 + layer.C + dtype)
 
 
