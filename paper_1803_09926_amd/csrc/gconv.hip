@@ -249,28 +249,27 @@ static double generic_us(const GGeom &g, int layout, int pass)
     return sqrt(latency * latency + all * all);
 }
 
-// Laying out the filter and staging a tile are a fixed 6 to 15 us, and a filter that takes the LDS leaves small tiles: few products per output
-// and few outputs, or few channels a group with a large filter, are shorter one output per thread.  Of random layers that came here by the
-// estimates from the generic kernels, 2.5 % of the forward passes and 1.8 % of the input gradients are slower by more than 8 % (at the mean
-// 0.39 and 0.26 of the time; without a factor 1.5 and 0.8 %, but 3 and 8 % would stay generic that are shorter here by as much).  The filter gradient, whose
+// Laying out the filter and staging a tile are a fixed 5 to 12 us, and a filter that takes the LDS leaves small tiles: few products per output
+// and few outputs, or few channels a group with a large filter, are shorter one output per thread.  Of 17 000 random layers, 0.04 % of the forward passes and
+// 0.1 % of the input gradients that the estimates send here are longer by more than 8 % than one output per thread, and 13 and 22 % of the 1050 and 540 that they leave
+// there would be shorter here by as much (0.9 of the estimate, without the us by which the shortest generic ones are below theirs: 1.1 and 0.1 %).  The filter gradient, whose
 // time here hardly depends on the layer as long as it is short: 1 % either way.
 static bool gemm_over_generic(const GGeom &g, int layout, int dtype, int pass)
 {
     const double generic = generic_us(g, layout, pass);
     if (pass == 2) return generic > (g.K == 1 ? 10.5 : g.K == 3 ? 12.5 : 16.0);
-    return gconv_gemm_us(g, layout, dtype, pass) * (pass == 0 ? 0.95 : 0.9) < generic;
+    return gconv_gemm_us(g, layout, dtype, pass) < 0.95 * generic - (pass == 0 ? 1.0 : 0.7);
 }
 
 // In place of the NCHW row walk: in fp32 not for the filter gradient of 16 channels a group on many pixels (1.03 times as long at the median of
-// random layers, up to 1.8).  Forward and input gradient by the estimates of both: of random layers of 16 to 64 channels a group 0.1 % are longer here by
-// more than 8 %, of 64 to 128 on many pixels 1.8 % (up to 1.6 times; always here: 9.3 %, up to 2.4), and 0.7 % stay that would be shorter.  us, row walk ->
+// random layers, up to 1.8).  Forward and input gradient by the estimates of both: of 440 random layers of 16 to 64 channels a group none is longer here by
+// more than 8 %, of 350 of 80 to 160 on many pixels 0.6 to 1.7 % (always here: 5 to 10 %, up to 2.4 times), and none stays that would be shorter.  us, row walk ->
 // here: 128x21x20 in two groups, batch 148, 251 -> 146; 1024x18x18 in 16, batch 128, 964 -> 690; 480x18x18 in five, batch 213, 1080 -> 2330: stays.
 static bool gemm_over_rowwalk(const GGeom &g, int layout, int dtype, int pass)
 {
     if (dtype != DT_F32) return true;
     if (pass == 2) return !(g.Cg == 16 && (long long)g.N * g.Ho * g.Wo >= 16384);
-    // (above 64 channels one block fits a compute unit, and the estimate is nearer)
-    return gconv_gemm_us(g, layout, dtype, pass) * (g.Cg > 64 ? 0.95 : 0.8) < gconv_nchw_s1_us(g, pass == 1);
+    return gconv_gemm_us(g, layout, dtype, pass) * (g.Cg > 64 ? 0.85 : 0.7) < gconv_nchw_s1_us(g, pass == 1);
 }
 
 // In place of the other row walks, whose lanes are few in short launches (a lane walks 7 to 28 rows of all its group's input channels) and, NHWC with eight channels

@@ -1311,31 +1311,31 @@ bool gconv_gemm_supported(const GGeom &g, int layout, int dtype, int pass)
     return gemm_plan(g, layout, dtype, pass, &pl);
 }
 
-// Laying out the filter (768 fragments a time), then for every tile of the block a fixed latency, the staging (4 KiB a time) and the products of
-// its longest wavefront, each with a part that grows with the blocks on a compute unit, and the classes of output pixels.  Fitted to 33 000
-// random layers before filters and ragged tiles came in vectors: four of five between 0.87 and 1.15 times the time of then, which is up to a third longer.
+// The launch, laying out the filter (768 fragments a time), then for every tile of the block a fixed latency, the staging (4 KiB a time) and the products of
+// its longest wavefront, each with a part that grows with the blocks on a compute unit, and the classes of output pixels.  Fitted to 64 000
+// random layers: four of five between 0.85 and 1.12 (NCHW input gradient 0.81 and 1.15) times the measured time.
 double gconv_gemm_us(const GGeom &q, int layout, int dtype, int pass)
 {
-    static const float fit[2][2][2][2][7] = {                               // [pass][layout][dtype][fast]
-        {{{{1.21f, 1.70f, 0, 0, 0.191f, 0.0765f, 0.365f}, {1.27f, 1.15f, 0.14f, 0.006f, 0.159f, 0.0727f, 0.006f}},
-          {{1.70f, 1.29f, 0.311f, 0.006f, 0.432f, 0.0075f, 0.476f}, {0.93f, 1.88f, 0.15f, 0, 0.196f, 0.0137f, 0.384f}}},
-         {{{1.18f, 0.34f, 0.03f, 0.011f, 0.305f, 0.0735f, 0.241f}, {1.45f, 0.64f, 0.009f, 0, 0.164f, 0.0646f, 0.639f}},
-          {{1.64f, 0.59f, 0.434f, 0.003f, 0.401f, 0.0105f, 0.438f}, {0.73f, 0.28f, 0, 0.002f, 0.292f, 0.0109f, 0.371f}}}},
-        {{{{1.00f, 0.88f, 0, 0.021f, 0.273f, 0.0632f, 0.809f}, {1.09f, 0, 0.351f, 0.014f, 0.227f, 0.0708f, 0.679f}},
-          {{1.76f, 1.00f, 0.369f, 0.005f, 0.487f, 0.0051f, 0.831f}, {1.18f, 0.58f, 0.21f, 0.009f, 0.391f, 0.0068f, 0.814f}}},
-         {{{0.99f, 0.05f, 0.15f, 0.01f, 0.419f, 0.0678f, 0.634f}, {0.82f, 0, 0.231f, 0.005f, 0.241f, 0.0763f, 0.392f}},
-          {{1.50f, 0.40f, 0.569f, 0.006f, 0.525f, 0.0077f, 0.622f}, {0.88f, 0.41f, 0.075f, 0.006f, 0.389f, 0.0073f, 0.431f}}}}};
+    static const float fit[2][2][2][2][8] = {                               // [pass][layout][dtype][ragged channels or tiles]
+        {{{{4.57f, 0.474f, 0, 0.142f, 0.0103f, 0.169f, 0.0784f, 0}, {5.31f, 0.383f, 0, 0.172f, 0.00555f, 0.151f, 0.0768f, 0}},
+          {{2.62f, 0.518f, 2.18f, 0.193f, 0.0101f, 0.23f, 0.00959f, 0}, {2.34f, 0.38f, 3.27f, 0.0859f, 0.0117f, 0.253f, 0.0058f, 0}}},
+         {{{3.73f, 0.558f, 0, 0.0646f, 0.0402f, 0.232f, 0.0602f, 0}, {3.88f, 0.297f, 0, 0.264f, 0.0102f, 0.167f, 0.0801f, 0}},
+          {{3.14f, 0.65f, 0.848f, 0.0247f, 0.0132f, 0.268f, 0.00746f, 0}, {2.72f, 0.454f, 1.44f, 0.217f, 0.016f, 0.234f, 0.00353f, 0}}}},
+        {{{{4.58f, 0.777f, 0, 0.0718f, 0.021f, 0.269f, 0.07f, 0.398f}, {4.82f, 0.857f, 0, 0.0165f, 0.0263f, 0.305f, 0.0505f, 0.914f}},
+          {{3.72f, 0.817f, 0.955f, 0.0757f, 0.018f, 0.434f, 0.00379f, 0.437f}, {3.31f, 0.46f, 1.73f, 0.109f, 0.0141f, 0.379f, 0.00206f, 0.896f}}},
+         {{{3.86f, 0.703f, 0, 0, 0.0416f, 0.349f, 0.0573f, 0.284f}, {4.72f, 0.0744f, 0, 0, 0.0645f, 0.484f, 0.0413f, 0.368f}},
+          {{4.01f, 0.823f, 0.132f, 0, 0.0101f, 0.393f, 0.00718f, 0.285f}, {4.16f, 0.417f, 0.9f, 0.21f, 0.0213f, 0.354f, 0, 0.352f}}}}};
     GemmPlan pl;
     if (!gemm_plan(q, layout, dtype, pass, &pl)) return 1e30;
     const GemmGeom &g = pl.g;
-    const float *c = fit[pass][layout == LAYOUT_NHWC][dtype != DT_F32][pl.fast == 1];
+    const float *c = fit[pass][layout == LAYOUT_NHWC][dtype != DT_F32][pl.fast != 1];
     const int tiles = cdivg(g.tn * g.ta * g.tb, pl.nparts), tiles16 = cdivg(g.TN * g.TA * g.TB, 16), P = tiles_at_once(g.NS, g.TN * g.TA * g.TB, dtype);
     const double resident = resident_blocks(pl.lds, 4), cu = pl.nblocks / 256.0;
     const double rounds = pl.nblocks > resident ? pl.nblocks / resident : 1.0, beside = cu < 1 ? 1 : cu > resident / 256 ? resident / 256 : cu;
     const double staging = (double)g.TN * g.LH * g.LW * g.CL * (dtype == DT_F32 ? 4 : 2) / 4096;
     const double products = (double)cdivg(g.NS * cdivg(tiles16, P), 4) * P * g.K * g.K * g.nk;
-    return 5 + rounds * (c[0] * (g.NS * g.K * g.K * g.nk * 64) / 768 +
-                         tiles * (c[1] + c[2] * staging + c[3] * products + beside * (c[4] * staging + c[5] * products) + c[6] * g.OS * g.OS));
+    return c[0] + rounds * (c[1] * (g.NS * g.K * g.K * g.nk * 64) / 768 +
+                            tiles * (c[2] + c[3] * staging + c[4] * products + beside * (c[5] * staging + c[6] * products) + c[7] * g.OS * g.OS));
 }
 
 int gconv_gemm_parts(const GGeom &g, int layout, int dtype)
