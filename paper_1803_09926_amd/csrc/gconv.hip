@@ -254,22 +254,22 @@ static double generic_us(const GGeom &g, int layout, int pass)
 // 0.1 % of the input gradients that the estimates send here are longer by more than 8 % than one output per thread, and 13 and 22 % of the 1050 and 540 that they leave
 // there would be shorter here by as much (0.9 of the estimate, without the us by which the shortest generic ones are below theirs: 1.1 and 0.1 %).  The filter gradient, whose
 // time here hardly depends on the layer as long as it is short: 1 % either way.
-static bool gemm_over_generic(const GGeom &g, int layout, int dtype, int pass)
+static bool gemm_over_generic(const GGeom &g, int layout, int dtype, int pass, GemmPlan *pl)
 {
     const double generic = generic_us(g, layout, pass);
-    if (pass == 2) return generic > (g.K == 1 ? 10.5 : g.K == 3 ? 12.5 : 16.0);
-    return gconv_gemm_us(g, layout, dtype, pass) < 0.95 * generic - (pass == 0 ? 1.0 : 0.7);
+    if (pass == 2) return generic > (g.K == 1 ? 10.5 : g.K == 3 ? 12.5 : 16.0) && gconv_gemm_plan(g, layout, dtype, pass, pl);
+    return gconv_gemm_plan(g, layout, dtype, pass, pl) && gconv_gemm_us(*pl, layout, dtype) < 0.95 * generic - (pass == 0 ? 1.0 : 0.7);
 }
 
 // In place of the NCHW row walk: in fp32 not for the filter gradient of 16 channels a group on many pixels (1.03 times as long at the median of
 // random layers, up to 1.8).  Forward and input gradient by the estimates of both: of 440 random layers of 16 to 64 channels a group none is longer here by
 // more than 8 %, of 350 of 80 to 160 on many pixels 0.6 to 1.7 % (always here: 5 to 10 %, up to 2.4 times), and none stays that would be shorter.  us, row walk ->
 // here: 128x21x20 in two groups, batch 148, 251 -> 146; 1024x18x18 in 16, batch 128, 964 -> 690; 480x18x18 in five, batch 213, 1080 -> 2330: stays.
-static bool gemm_over_rowwalk(const GGeom &g, int layout, int dtype, int pass)
+static bool gemm_over_rowwalk(const GGeom &g, int layout, int dtype, int pass, GemmPlan *pl)
 {
-    if (dtype != DT_F32) return true;
-    if (pass == 2) return !(g.Cg == 16 && (long long)g.N * g.Ho * g.Wo >= 16384);
-    return gconv_gemm_us(g, layout, dtype, pass) * (g.Cg > 64 ? 0.85 : 0.7) < gconv_nchw_s1_us(g, pass == 1);
+    if (dtype == DT_F32 && pass == 2 && g.Cg == 16 && (long long)g.N * g.Ho * g.Wo >= 16384) return false;
+    if (!gconv_gemm_plan(g, layout, dtype, pass, pl)) return false;
+    return dtype != DT_F32 || pass == 2 || gconv_gemm_us(*pl, layout, dtype) * (g.Cg > 64 ? 0.85 : 0.7) < gconv_nchw_s1_us(g, pass == 1);
 }
 
 // In place of the other row walks, whose lanes are few in short launches (a lane walks 7 to 28 rows of all its group's input channels) and, NHWC with eight channels
@@ -305,7 +305,7 @@ static bool gemm_over_walk(const GGeom &g, int dtype, int pass, int variant, lon
 
 static GPlan gplan(const GGeom &g, int layout, int dtype, int pass)
 {
-    GPlan pl = {GV_GENERIC, pass == 2 ? gconv_generic_bwd_filter_parts(g) : 0, 0, 0, 0, "group_generic"};
+    GPlan pl = {GV_GENERIC, pass == 2 ? gconv_generic_bwd_filter_parts(g) : 0, 0, 0, 0, "group_generic", {}};
     if (tune_env("DWCONV_TUNE_GROUP_GENERIC")) return pl;
     // The filter gradient takes the small-plane form for groups of up to 4 on rows of up to 14, and on 28-wide rows in
     // bf16 (fp32 batch 128: 14x14 groups of 4 37 against 55 us, 28x28 groups of 4 83 against 85, groups of 8 122 against
@@ -356,28 +356,36 @@ static GPlan gplan(const GGeom &g, int layout, int dtype, int pass)
                 : pass == 1 ? (mm ? "group_nhwc_mfma_k3s1_flip" : "group_nhwc_rowwalk_k3s1_flip") : "group_nhwc_bwd_filter_k3s1";
         if (pass == 2) pl.parts = gconv_nhwc_bwd_filter_parts(g, dtype);
     }
+    // the one-launch filter gradient in place of two; a walk's line is below that of the kernels that may take its place, so it is asked first
+    auto short_one = [&](FilterWay way) {
+        if (pass != 2 || pl.variant == GV_NCHWS_MFMA_BWD_FILTER || !short_bwd_filter_shorter(g, layout, dtype, way)) return false;
+        pl.variant = GV_SHORT_BWD_FILTER; pl.parts = 1;
+        pl.name = layout == LAYOUT_NCHW ? "group_nchw_short_bwd_filter" : "group_nhwc_short_bwd_filter";
+        return true;
+    };
+    const bool shorter = pl.variant != GV_GENERIC && short_one(pl.variant == GV_NCHWS_K3S1 ? FILTER_SMALL_PLANES : FILTER_TWO);
     // What no kernel above takes, and NCHW groups of a multiple of 16 channels in place of the row walk (14x14, 16 channels a
     // group, 512 channels, fp32 batch 64: 62 -> 45 us; 32 channels at batch 4: 53 -> 15): the 16x16 matrix instructions
     const bool rowwalk16 = pl.variant == GV_NCHW_K3S1 && g.Cg % 16 == 0 && g.Og % 16 == 0;
     const long long outputs = (long long)g.N * (pass == 1 ? (long long)g.C * g.H * g.W : (long long)g.O * g.Ho * g.Wo);
-    const bool walk = !rowwalk16 && gemm_over_walk(g, dtype, pass, pl.variant, outputs);
     // (fewer outputs: only of many products, which a lane of the generic kernels adds up one after the other: 4x4x96 in three groups, 5x5, 99 us)
     const bool enough = outputs >= 2048 || (pl.variant == GV_GENERIC && (pass == 1 ? g.Og : g.Cg) * g.K * g.K >= 256);
-    if ((pl.variant == GV_GENERIC || rowwalk16 || walk) && enough && gconv_gemm_supported(g, layout, dtype, pass) &&
-        (walk || tune_env("DWCONV_TUNE_GROUP_GEMM") || (rowwalk16 ? gemm_over_rowwalk(g, layout, dtype, pass) : gemm_over_generic(g, layout, dtype, pass)))) {
+    auto gemm = [&]() {
+        if (shorter || !enough) return false;
+        if ((pl.variant == GV_GENERIC || rowwalk16) && tune_env("DWCONV_TUNE_GROUP_GEMM")) return gconv_gemm_plan(g, layout, dtype, pass, &pl.gemm);
+        if (pl.variant == GV_GENERIC) return gemm_over_generic(g, layout, dtype, pass, &pl.gemm);
+        if (rowwalk16) return gemm_over_rowwalk(g, layout, dtype, pass, &pl.gemm);
+        return gemm_over_walk(g, dtype, pass, pl.variant, outputs) && gconv_gemm_plan(g, layout, dtype, pass, &pl.gemm);
+    };
+    if (gemm()) {
         pl.variant = GV_GEMM;
         pl.name = pass == 0 ? "group_mfma16" : pass == 1 ? "group_mfma16_bwd_data" : "group_mfma16_bwd_filter";
-        if (pass == 2) pl.parts = gconv_gemm_parts(g, layout, dtype);
-    }
-    const FilterWay way = pl.variant == GV_GEMM ? FILTER_MATRIX : pl.variant == GV_GENERIC && pl.parts == 1 ? FILTER_GENERIC_ONE
-                          : pl.variant == GV_NCHWS_K3S1 ? FILTER_SMALL_PLANES : FILTER_TWO;
-    if (pass == 2 && pl.variant != GV_NCHWS_MFMA_BWD_FILTER && short_bwd_filter_shorter(g, layout, dtype, way)) {
-        pl.variant = GV_SHORT_BWD_FILTER; pl.parts = 1;
-        pl.name = layout == LAYOUT_NCHW ? "group_nchw_short_bwd_filter" : "group_nhwc_short_bwd_filter";
-    }
+        if (pass == 2) pl.parts = pl.gemm.nparts;
+        short_one(FILTER_MATRIX);
+    } else if (pl.variant == GV_GENERIC) short_one(pl.parts == 1 ? FILTER_GENERIC_ONE : FILTER_TWO);
     // a tuned filter gradient whose partial sums would not fit in 64 MiB (very wide rows): the generic kernels
     if (pass == 2 && pl.variant != GV_GENERIC && (long long)pl.parts * g.O * g.Cg * g.K * g.K * 4 > (64ll << 20)) {
-        const GPlan gen = {GV_GENERIC, gconv_generic_bwd_filter_parts(g), 0, 0, 0, "group_generic"};
+        const GPlan gen = {GV_GENERIC, gconv_generic_bwd_filter_parts(g), 0, 0, 0, "group_generic", {}};
         return gen;
     }
     return pl;
@@ -465,7 +473,7 @@ int gconv_fwd(const dwconv_group_desc *desc, const void *x, const void *w, void 
     else if (pl.variant == GV_NCHW_K3S1) e = gconv_nchw_s1(g, desc->dtype, x, w, y, false, (hipStream_t)stream);
     else if (pl.variant == GV_NHWC_K3S1) e = gconv_nhwc_s1(g, desc->dtype, x, w, y, false, (hipStream_t)stream);
     else if (pl.variant == GV_NHWC_MFMA_S2) e = gconv_nhwc_mfma_s2(g, desc->dtype, x, w, y, false, (hipStream_t)stream);
-    else if (pl.variant == GV_GEMM) e = gconv_gemm(g, desc->layout, desc->dtype, x, w, y, false, (hipStream_t)stream);
+    else if (pl.variant == GV_GEMM) e = gconv_gemm(pl.gemm, desc->layout, desc->dtype, x, w, y, (hipStream_t)stream);
     else e = gconv_generic_fwd(g, desc->layout, desc->dtype, x, w, y, (hipStream_t)stream);
     return e == hipSuccess ? DWCONV_OK : DWCONV_ERR_LAUNCH;
 }
@@ -489,7 +497,7 @@ int gconv_bwd_data(const dwconv_group_desc *desc, const void *dy, const void *w,
     else if (pl.variant == GV_NCHW_K3S1) e = gconv_nchw_s1(g, desc->dtype, dy, w, dx, true, (hipStream_t)stream);
     else if (pl.variant == GV_NHWC_K3S1) e = gconv_nhwc_s1(g, desc->dtype, dy, w, dx, true, (hipStream_t)stream);
     else if (pl.variant == GV_NHWC_MFMA_S2) e = gconv_nhwc_mfma_s2(g, desc->dtype, dy, w, dx, true, (hipStream_t)stream);
-    else if (pl.variant == GV_GEMM) e = gconv_gemm(g, desc->layout, desc->dtype, dy, w, dx, true, (hipStream_t)stream);
+    else if (pl.variant == GV_GEMM) e = gconv_gemm(pl.gemm, desc->layout, desc->dtype, dy, w, dx, (hipStream_t)stream);
     else e = gconv_generic_bwd_data(g, desc->layout, desc->dtype, dy, w, dx, (hipStream_t)stream);
     return e == hipSuccess ? DWCONV_OK : DWCONV_ERR_LAUNCH;
 }
@@ -522,12 +530,12 @@ int gconv_bwd_filter(const dwconv_group_desc *desc, const void *x, const void *d
     else if (pl.variant == GV_NHWC_BWD_FILTER_S2) e = gconv_nhwc_bwd_filter_s2(g, desc->dtype, x, dy, (float *)workspace, pl.parts, (hipStream_t)stream);
     else if (pl.variant == GV_NCHW_K3S1) e = gconv_nchw_bwd_filter(g, desc->dtype, x, dy, (float *)workspace, pl.parts, (hipStream_t)stream);
     else if (pl.variant == GV_NHWC_K3S1) e = gconv_nhwc_bwd_filter(g, desc->dtype, x, dy, (float *)workspace, pl.parts, (hipStream_t)stream);
-    else if (pl.variant == GV_GEMM) e = gconv_gemm_bwd_filter(g, desc->layout, desc->dtype, x, dy, (float *)workspace, (hipStream_t)stream);
+    else if (pl.variant == GV_GEMM) e = gconv_gemm_bwd_filter(pl.gemm, desc->layout, desc->dtype, x, dy, (float *)workspace, (hipStream_t)stream);
     else e = gconv_generic_bwd_filter(g, desc->layout, desc->dtype, x, dy, (float *)workspace, pl.parts, (hipStream_t)stream);
     if (final || e != hipSuccess) return e == hipSuccess ? DWCONV_OK : DWCONV_ERR_LAUNCH;
     if (pl.variant == GV_GEMM) {
         FilterGradSrc src = {x, dy, desc->dtype, desc->layout, g.N, g.C, g.H, g.W, g.K, g.s, g.p, g.O, g.Cg, g.Og, g.Ho, g.Wo};
-        gconv_gemm_filter_tiles(g, desc->layout, desc->dtype, &src);
+        gconv_gemm_filter_tiles(pl.gemm, &src);
         // (a partial is a longer chain of sums than the walks', which short launches took before: 1.01 to 1.03 times their error against 64 bits in
         // bf16, 1.09 in fp32 NHWC; with the partials in 64 bits 0.69 to 0.82 and 0.84 to 0.93, in the same time)
         e = reduce_partials((const float *)workspace, pl.parts, J, (float *)dw, src, true, (hipStream_t)stream);

@@ -1,5 +1,6 @@
 // Group convolution (more than one channel per group): geometry and host-side launch entry points.
 #pragma once
+#include "gconv_gemm.hpp"
 #include "kernels.hpp"
 
 namespace dwc {
@@ -19,6 +20,7 @@ struct GPlan {
     int parts;          // bwd_filter: partial sums per weight entry
     int a, b, c;        // variant-specific tiling
     const char *name;
+    GemmPlan gemm;      // GV_GEMM
 };
 
 // ---- generic kernels: any K, stride, pad, group size, both layouts (gconv.hip) ---------------------
@@ -31,13 +33,12 @@ hipError_t gconv_generic_bwd_filter(const GGeom &g, int layout, int dtype, const
 
 // ---- any group size, filter of up to 7x7, stride of up to 4, padding, both layouts on the 16x16 matrix instructions
 // (gconv_gemm.hip); filter gradient: K 1, 3 or 5
-bool gconv_gemm_supported(const GGeom &g, int layout, int dtype, int pass);
-// pass 0 or 1: estimated time in us
-double gconv_gemm_us(const GGeom &g, int layout, int dtype, int pass);
-hipError_t gconv_gemm(const GGeom &g, int layout, int dtype, const void *in, const void *w, void *out, bool bwd, hipStream_t st);
-int gconv_gemm_parts(const GGeom &g, int layout, int dtype);
-void gconv_gemm_filter_tiles(const GGeom &g, int layout, int dtype, FilterGradSrc *f);       // what its partials hold
-hipError_t gconv_gemm_bwd_filter(const GGeom &g, int layout, int dtype, const void *x, const void *dy, float *ws, hipStream_t st);
+// The launch of a pass (0 forward, 1 input gradient, 2 filter gradient); false where these kernels do not take the shape.
+bool gconv_gemm_plan(const GGeom &g, int layout, int dtype, int pass, GemmPlan *pl);
+double gconv_gemm_us(const GemmPlan &pl, int layout, int dtype);             // pass 0 or 1: estimated time in us
+hipError_t gconv_gemm(const GemmPlan &pl, int layout, int dtype, const void *in, const void *w, void *out, hipStream_t st);
+void gconv_gemm_filter_tiles(const GemmPlan &pl, FilterGradSrc *f);         // what its partials hold
+hipError_t gconv_gemm_bwd_filter(const GemmPlan &pl, int layout, int dtype, const void *x, const void *dy, float *ws, hipStream_t st);
 
 // ---- NCHW row-walk kernels, 3x3 stride 1 pad 1, 2, 4 or 8 channels per group on both sides (gconv_nchw.hip)
 bool gconv_nchw_supported(const GGeom &g);

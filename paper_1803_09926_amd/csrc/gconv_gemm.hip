@@ -112,39 +112,6 @@ template <typename T, int V, typename A> __device__ __forceinline__ void store_r
     }
 }
 
-// How the 256 lanes of a block copy a tile into LDS where FAST holds: lane t takes item t % per of row t / per, so that the divisions
-// are done once and an item costs a few additions; `rows` rows in nrit steps of RPI, for every `cols` columns of a wider tile again.
-// NHWC: an item is 16 bytes of channels of a pixel, a row one of the tile (all images); NCHW: four channels of four columns, a row one
-// of a channel quad.
-struct StageGeom {
-    int LH, LW, pitch;               // the tile: rows of an image, columns, elements between pixels
-    int imrows, rows, cols, per, nv; // imrows: rows of all images; nv: items of a pixel (NHWC)
-    int width;                       // items of a row
-    int RPI, nrit, iters;
-    float rper, rnv, rLH, rimrows;
-};
-
-// One launch: the convolution from `in` (CI channels, Hi x Wi) to `out` (CO channels, Ho x Wo).  Position (a, b) of a tile
-// reads input row IS*a - ip + roff and writes output row OS*a + f - op; roff = kh forward, -k for tap kh = f + OS*k backward.
-struct GemmGeom {
-    int N, CI, CO, Hi, Wi, Ho, Wo;
-    int Cgi, Cgo;          // channels per group, input and output side
-    int K, IS, OS, ip, op;
-    int a0, na, b0, nb;    // positions of the whole image
-    int bwd;
-    int pairs, shift;      // E = 2: a position's outputs are columns 2b - 2*(op/2) and the next one; shift: odd op, the second one is class 0 of position b + 1
-    // tile
-    int TN, TA, TB;        // images, rows and columns of positions
-    int tn, ta, tb;        // tiles in each direction
-    int LH, LW;            // input pixels of a tile, per image
-    int lo;                // lowest roff (backward: -(taps per class - 1))
-    int NS, nk, CL, pitch; // 16-channel output blocks, 16-channel input chunks of each, channels in LDS, elements between pixels
-    int nchb;              // channel blocks
-    int packed;            // output blocks span groups
-    int FO, FCg;           // filter dims: output channels, input channels per group (of the forward layer)
-    float rCgi, rCgo, rKK, rnk, rTA, rTB, rta, rtb;         // reciprocals for fdiv
-};
-
 // n / d for 0 <= n < 2^21 and d with reciprocal r = 1.0f / d: the half keeps the product away from the integers by more than
 // its rounding error (0.5 / d against n / d * 2^-22), four instructions instead of the twenty of an integer division.
 __device__ __forceinline__ int fdiv(int n, float r) { return (int)(((float)n + 0.5f) * r); }
@@ -1032,18 +999,27 @@ __global__ __launch_bounds__(256, K > 3 ? 2 : sizeof(T) == 4 ? 3 : 4) void k_gco
 
 int cdivg(int a, int b) { return (a + b - 1) / b; }
 
+// Output channels after which the blocks of 16 lie in their groups, and the inputs of those in the 16-byte vectors, as at the first one (a layer of 1024 channels in
+// groups of 8 is planned in 0.3 us, by all its blocks in 1.5).
+int span_period(const GemmGeom &g)
+{
+    int p = 16;
+    while (p < g.CO && (p % g.Cgo || p / g.Cgo * g.Cgi % 8)) p += 16;
+    return p;
+}
+
 // channel chunks of 16 that the inputs of any 16 consecutive outputs span, and the channels in LDS of `ns` such blocks
-void channel_span(GemmGeom &g, int ns, int VE, int *CL)
+void channel_span(GemmGeom &g, int ns, int VE, int period, int *CL)
 {
     int nk = 1;
     auto first = [&](int o) { return o / g.Cgo * g.Cgi & ~3; };
-    for (int o = 0; o < g.CO; o += 16) {
+    for (int o = 0; o < g.CO && o < period; o += 16) {
         const int end = ((o + 15 < g.CO ? o + 15 : g.CO - 1) / g.Cgo + 1) * g.Cgi;
         if (cdivg(end - first(o), 16) > nk) nk = cdivg(end - first(o), 16);
     }
     g.nk = nk;
     int cl = 0;
-    for (int o = 0; o < g.CO; o += 16 * ns) {
+    for (int o = 0; o < g.CO && o < ns * period; o += 16 * ns) {
         const int ca = first(o) & ~(VE - 1);
         for (int s = 0; s < ns && o + s * 16 < g.CO; ++s)
             if (first(o + s * 16) + nk * 16 - ca > cl) cl = first(o + s * 16) + nk * 16 - ca;
@@ -1122,8 +1098,6 @@ void pick_positions(GemmGeom &g, int want, int maxb, int quad = 1)
     g.tn = cdivg(g.N, g.TN); g.ta = cdivg(g.na, g.TA); g.tb = cdivg(g.nb, g.TB);
 }
 
-struct GemmPlan { GemmGeom g; StageGeom sg, sy; size_t lds; int nparts; unsigned nblocks; int npair, CLy, pitchy, fast, quad; };
-
 // copying a tile of TN images of LH x LW pixels and CL channels (NCHW: rows of W columns) with 256 lanes
 StageGeom stage_geom(int layout, int VE, int TN, int LH, int LW, int CL, int pitch, int W, bool split)
 {
@@ -1162,7 +1136,7 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
         if (pairs) { g.pairs = 1; g.shift = q.p & 1; g.nb = (q.W + 1) / 2; }
     }
     const int reach = pass == 1 ? 1 - g.lo : q.K;                           // input rows of one position
-    const int blocks16 = cdivg(g.CO, 16);
+    const int blocks16 = cdivg(g.CO, 16), period = span_period(g);
     if (pass < 2) {
         // A launch of few blocks is one short round of them beside idle compute units, each as long as its tile: smaller tiles, down to a
         // 16-position tile for each wavefront, then one output block a block.  (us: 4x64x9x9 in 2 groups, stride 2, fp32 NCHW input gradient 30 -> 13,
@@ -1177,7 +1151,7 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
         if (ns > blocks16) ns = blocks16;
         for (;; ns = (ns + 1) / 2) {
             g.NS = ns;
-            channel_span(g, ns, VE, &g.CL);
+            channel_span(g, ns, VE, period, &g.CL);
             g.packed = !(g.Cgo % 16 == 0 && g.Cgi % 16 == 0);
             // (16-byte or, in NCHW, four-channel LDS stores)
             g.pitch = g.CL + (layout == LAYOUT_NHWC ? VE : 4);
@@ -1210,7 +1184,7 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
     } else {
         if (q.K > 5) return false;
         int dummy;
-        channel_span(g, 1, VE, &dummy);
+        channel_span(g, 1, VE, period, &dummy);
         const int pairs = blocks16 * g.nk;
         // NHWC: two pairs a block read whole 64-byte runs of channels (14x14 16 channels a group, bf16 batch 32: 14.5 us, with one 15.5); NCHW
         // gains nothing by it and a pair alone leaves smaller tiles (56x56 8 channels a group at stride 2, bf16 batch 16: 23.6 against 28)
@@ -1224,7 +1198,8 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
             // channels in LDS of any block: its pairs run over (output block, chunk)
             int clx = 0, cly = 0;
             auto first = [&](int o) { return o / g.Cgo * g.Cgi & ~3; };
-            for (int b = 0; b < g.nchb; ++b) {
+            const long long pairs_of_period = (long long)(period / 16) * g.nk;
+            for (int b = 0; b < g.nchb && (b == 0 || (long long)b * npair % pairs_of_period != 0); ++b) {
                 const int s0 = b * npair / g.nk, cxa = (first(s0 * 16) + (b * npair - s0 * g.nk) * 16) & ~(VE - 1);
                 for (int j = 0; j < npair && b * npair + j < pairs; ++j) {
                     const int s = (b * npair + j) / g.nk, kc = b * npair + j - s * g.nk;
@@ -1296,25 +1271,19 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
     return true;
 }
 
-bool gemm_plan(const GGeom &q, int layout, int dtype, int pass, GemmPlan *pl)
-{
-    if (pass == 1 && layout == LAYOUT_NCHW && q.s == 2 && gemm_plan_as(q, layout, dtype, pass, true, pl) && pl->fast) return true;
-    return gemm_plan_as(q, layout, dtype, pass, false, pl);
-}
-
 }  // namespace
 
-bool gconv_gemm_supported(const GGeom &g, int layout, int dtype, int pass)
+bool gconv_gemm_plan(const GGeom &q, int layout, int dtype, int pass, GemmPlan *pl)
 {
-    GemmPlan pl;
-    if (pass == 2 && g.K != 1 && g.K != 3 && g.K != 5) return false;
-    return gemm_plan(g, layout, dtype, pass, &pl);
+    if (pass == 2 && q.K != 1 && q.K != 3 && q.K != 5) return false;
+    if (pass == 1 && layout == LAYOUT_NCHW && q.s == 2 && gemm_plan_as(q, layout, dtype, pass, true, pl) && pl->fast) return true;
+    return gemm_plan_as(q, layout, dtype, pass, false, pl);
 }
 
 // The launch, laying out the filter (768 fragments a time), then for every tile of the block a fixed latency, the staging (4 KiB a time) and the products of
 // its longest wavefront, each with a part that grows with the blocks on a compute unit, and the classes of output pixels.  Fitted to 64 000
 // random layers: four of five between 0.85 and 1.12 (NCHW input gradient 0.81 and 1.15) times the measured time.
-double gconv_gemm_us(const GGeom &q, int layout, int dtype, int pass)
+double gconv_gemm_us(const GemmPlan &pl, int layout, int dtype)
 {
     static const float fit[2][2][2][2][8] = {                               // [pass][layout][dtype][ragged channels or tiles]
         {{{{4.57f, 0.474f, 0, 0.142f, 0.0103f, 0.169f, 0.0784f, 0}, {5.31f, 0.383f, 0, 0.172f, 0.00555f, 0.151f, 0.0768f, 0}},
@@ -1325,10 +1294,8 @@ double gconv_gemm_us(const GGeom &q, int layout, int dtype, int pass)
           {{3.72f, 0.817f, 0.955f, 0.0757f, 0.018f, 0.434f, 0.00379f, 0.437f}, {3.31f, 0.46f, 1.73f, 0.109f, 0.0141f, 0.379f, 0.00206f, 0.896f}}},
          {{{3.86f, 0.703f, 0, 0, 0.0416f, 0.349f, 0.0573f, 0.284f}, {4.72f, 0.0744f, 0, 0, 0.0645f, 0.484f, 0.0413f, 0.368f}},
           {{4.01f, 0.823f, 0.132f, 0, 0.0101f, 0.393f, 0.00718f, 0.285f}, {4.16f, 0.417f, 0.9f, 0.21f, 0.0213f, 0.354f, 0, 0.352f}}}}};
-    GemmPlan pl;
-    if (!gemm_plan(q, layout, dtype, pass, &pl)) return 1e30;
     const GemmGeom &g = pl.g;
-    const float *c = fit[pass][layout == LAYOUT_NHWC][dtype != DT_F32][pl.fast != 1];
+    const float *c = fit[g.bwd][layout == LAYOUT_NHWC][dtype != DT_F32][pl.fast != 1];
     const int tiles = cdivg(g.tn * g.ta * g.tb, pl.nparts), tiles16 = cdivg(g.TN * g.TA * g.TB, 16), P = tiles_at_once(g.NS, g.TN * g.TA * g.TB, dtype);
     const double resident = resident_blocks(pl.lds, 4), cu = pl.nblocks / 256.0;
     const double rounds = pl.nblocks > resident ? pl.nblocks / resident : 1.0, beside = cu < 1 ? 1 : cu > resident / 256 ? resident / 256 : cu;
@@ -1338,16 +1305,8 @@ double gconv_gemm_us(const GGeom &q, int layout, int dtype, int pass)
                             tiles * (c[2] + c[3] * staging + c[4] * products + beside * (c[5] * staging + c[6] * products) + c[7] * g.OS * g.OS));
 }
 
-int gconv_gemm_parts(const GGeom &g, int layout, int dtype)
+void gconv_gemm_filter_tiles(const GemmPlan &pl, FilterGradSrc *f)
 {
-    GemmPlan pl;
-    return gemm_plan(g, layout, dtype, 2, &pl) ? pl.nparts : 0;
-}
-
-void gconv_gemm_filter_tiles(const GGeom &g, int layout, int dtype, FilterGradSrc *f)
-{
-    GemmPlan pl;
-    gemm_plan(g, layout, dtype, 2, &pl);
     f->TN = pl.g.TN; f->TA = pl.g.TA; f->TB = pl.g.TB;
     f->tn = pl.g.tn; f->ta = pl.g.ta; f->tb = pl.g.tb;
     f->per = 0; f->nparts = pl.nparts;
@@ -1380,10 +1339,8 @@ static hipError_t gemm_go(const GemmPlan &pl, const void *in, const void *w, voi
                        pl.nparts, pl.nblocks);
     return hipGetLastError();
 }
-hipError_t gconv_gemm(const GGeom &q, int layout, int dtype, const void *in, const void *w, void *out, bool bwd, hipStream_t st)
+hipError_t gconv_gemm(const GemmPlan &pl, int layout, int dtype, const void *in, const void *w, void *out, hipStream_t st)
 {
-    GemmPlan pl;
-    if (!gemm_plan(q, layout, dtype, bwd ? 1 : 0, &pl)) return hipErrorInvalidValue;
     if (dtype == DT_F32) return layout == LAYOUT_NHWC ? gemm_go<float, true>(pl, in, w, out, st) : gemm_go<float, false>(pl, in, w, out, st);
     return layout == LAYOUT_NHWC ? gemm_go<bf16_t, true>(pl, in, w, out, st) : gemm_go<bf16_t, false>(pl, in, w, out, st);
 }
@@ -1401,10 +1358,8 @@ static hipError_t gemm_filter_go(const GemmPlan &pl, const void *x, const void *
                        pl.nparts, J, pl.nblocks);
     return hipGetLastError();
 }
-hipError_t gconv_gemm_bwd_filter(const GGeom &q, int layout, int dtype, const void *x, const void *dy, float *ws, hipStream_t st)
+hipError_t gconv_gemm_bwd_filter(const GemmPlan &pl, int layout, int dtype, const void *x, const void *dy, float *ws, hipStream_t st)
 {
-    GemmPlan pl;
-    if (!gemm_plan(q, layout, dtype, 2, &pl)) return hipErrorInvalidValue;
     if (dtype == DT_F32) return layout == LAYOUT_NHWC ? gemm_filter_go<float, true>(pl, x, dy, ws, st) : gemm_filter_go<float, false>(pl, x, dy, ws, st);
     return layout == LAYOUT_NHWC ? gemm_filter_go<bf16_t, true>(pl, x, dy, ws, st) : gemm_filter_go<bf16_t, false>(pl, x, dy, ws, st);
 }
