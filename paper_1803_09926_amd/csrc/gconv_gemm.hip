@@ -1353,7 +1353,10 @@ static hipError_t gemm_filter_go(const GemmPlan &pl, const void *x, const void *
         constexpr int FAST = decltype(fast)::value;
         return pl.g.K == 1 ? k_gconv_gemm_filter<T, NHWC, FAST, 1> : pl.g.K == 3 ? k_gconv_gemm_filter<T, NHWC, FAST, 3> : k_gconv_gemm_filter<T, NHWC, FAST, 5>;
     };
-    auto kernel = pl.fast == 1 ? of(std::integral_constant<int, 1>()) : pl.fast ? of(std::integral_constant<int, 2>()) : of(std::integral_constant<int, 0>());
+    auto kernel = pl.fast == 1 ? of(std::integral_constant<int, 1>()) : of(std::integral_constant<int, 0>());
+    if constexpr (sizeof(T) == 2) {                                        // (fp32: not planned, see there)
+        if (pl.fast == 2) kernel = of(std::integral_constant<int, 2>());
+    }
     hipLaunchKernelGGL(kernel, dim3(pl.nblocks), dim3(256), pl.lds, st, pl.g, pl.sg, pl.sy, (const T *)x, (const T *)dy, ws, pl.npair,
                        pl.nparts, J, pl.nblocks);
     return hipGetLastError();
