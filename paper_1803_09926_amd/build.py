@@ -39,7 +39,7 @@ def _binding() -> None:
     from torch.utils import cpp_extension
     inc = cpp_extension.include_paths() + [sysconfig.get_paths()["include"], os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(HIPCC))), "include")]
     tmp = BINDING + ".tmp.%d" % os.getpid()
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI] + ["-isystem" + i for i in inc]
     cmd += [os.path.join(CSRC, "binding.cpp"), "-o", tmp, "-L" + os.path.join(os.path.dirname(torch.__file__), "lib"),
             "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
