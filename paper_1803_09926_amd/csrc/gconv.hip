@@ -370,17 +370,19 @@ static GPlan gplan(const GGeom &g, int layout, int dtype, int pass)
     const long long outputs = (long long)g.N * (pass == 1 ? (long long)g.C * g.H * g.W : (long long)g.O * g.Ho * g.Wo);
     // (fewer outputs: only of many products, which a lane of the generic kernels adds up one after the other: 4x4x96 in three groups, 5x5, 99 us)
     const bool enough = outputs >= 2048 || (pl.variant == GV_GENERIC && (pass == 1 ? g.Og : g.Cg) * g.K * g.K >= 256);
+    bool walk = false;
     auto gemm = [&]() {
         if (shorter || !enough) return false;
         if ((pl.variant == GV_GENERIC || rowwalk16) && tune_env("DWCONV_TUNE_GROUP_GEMM")) return gconv_gemm_plan(g, layout, dtype, pass, &pl.gemm);
         if (pl.variant == GV_GENERIC) return gemm_over_generic(g, layout, dtype, pass, &pl.gemm);
         if (rowwalk16) return gemm_over_rowwalk(g, layout, dtype, pass, &pl.gemm);
-        return gemm_over_walk(g, dtype, pass, pl.variant, outputs) && gconv_gemm_plan(g, layout, dtype, pass, &pl.gemm);
+        walk = gemm_over_walk(g, dtype, pass, pl.variant, outputs);
+        return walk && gconv_gemm_plan(g, layout, dtype, pass, &pl.gemm);
     };
     if (gemm()) {
         pl.variant = GV_GEMM;
         pl.name = pass == 0 ? "group_mfma16" : pass == 1 ? "group_mfma16_bwd_data" : "group_mfma16_bwd_filter";
-        if (pass == 2) pl.parts = pl.gemm.nparts;
+        if (pass == 2) { pl.parts = pl.gemm.nparts; pl.a = walk; }
         short_one(FILTER_MATRIX);
     } else if (pl.variant == GV_GENERIC) short_one(pl.parts == 1 ? FILTER_GENERIC_ONE : FILTER_TWO);
     // a tuned filter gradient whose partial sums would not fit in 64 MiB (very wide rows): the generic kernels
@@ -536,9 +538,10 @@ int gconv_bwd_filter(const dwconv_group_desc *desc, const void *x, const void *d
     if (pl.variant == GV_GEMM) {
         FilterGradSrc src = {x, dy, desc->dtype, desc->layout, g.N, g.C, g.H, g.W, g.K, g.s, g.p, g.O, g.Cg, g.Og, g.Ho, g.Wo};
         gconv_gemm_filter_tiles(pl.gemm, &src);
-        // (a partial is a longer chain of sums than the walks', which short launches took before: 1.01 to 1.03 times their error against 64 bits in
-        // bf16, 1.09 in fp32 NHWC; with the partials in 64 bits 0.69 to 0.82 and 0.84 to 0.93, in the same time)
-        e = reduce_partials((const float *)workspace, pl.parts, J, (float *)dw, src, true, (hipStream_t)stream);
+        // (in place of a walk a partial is a longer chain of sums than the walks', 1.01 to 1.03 times their error against 64 bits in bf16, 1.09 in
+        // fp32 NHWC; with the partials in 64 bits 0.69 to 0.82 and 0.84 to 0.93, in the same time.  Up to 16 384 entries that is as short as 32 bits or shorter, from there on
+        // 0.2 us a launch longer (74 000 entries 4.2 -> 4.4), which the others need not pay.)
+        e = reduce_partials((const float *)workspace, pl.parts, J, (float *)dw, src, pl.a != 0 || J < 16384, (hipStream_t)stream);
     } else e = reduce_partials((const float *)workspace, pl.parts, J, (float *)dw, (hipStream_t)stream);
     return e == hipSuccess ? DWCONV_OK : DWCONV_ERR_LAUNCH;
 }

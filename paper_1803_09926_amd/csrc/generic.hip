@@ -192,8 +192,8 @@ __device__ __forceinline__ void store_entries(const FilterGradSrc &src, const S 
 // take the partials p = r, r+PT, r+2PT, ... eight at a time.  All eight loads of a batch are issued
 // before the first is used, also in the last, partly filled batch (clamped index, value dropped):
 // the kernel is a few microseconds of pure load latency, so one latency per batch is what counts.
-// The batch is added in a fixed tree, then the PT sub-sums in a fixed tree through LDS, in S: 64 bits (wide) in place of
-// 32 are 0.6 to 0.9 of the error of a whole gradient, and no longer: what a batch loads is still on its way.
+// The batch is added in a fixed tree, then the PT sub-sums in a fixed tree, in S: 32 bits through LDS; 64 bits (wide: 0.6 to 0.9 of the
+// error of a whole gradient) over the wavefront first, which is a barrier instead of two to six (as short as 32 bits through LDS up to 16 000 entries, 0.97 to 0.99 of a gradient below 9 us).
 template <int JT, bool CHECK, typename S>
 __global__ __launch_bounds__(256) void k_reduce_partials(const float *__restrict__ ws, int parts, int J,
                                                          float *__restrict__ dw, FilterGradSrc src)
@@ -216,12 +216,21 @@ __global__ __launch_bounds__(256) void k_reduce_partials(const float *__restrict
             acc += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
         }
     }
-    red[r][jj] = acc;
-    __syncthreads();
-    // tree over the PT sub-sums: thread (r, jj) adds red[r + half]
-    for (int half = PT / 2; half >= 1; half >>= 1) {
-        if (r < half) red[r][jj] += red[r + half][jj];
+    if constexpr (sizeof(S) == 8) {
+#pragma unroll
+        for (int off = 32; off >= JT; off >>= 1) acc += __shfl_xor(acc, off, 64);
+        if ((threadIdx.x & 63) < JT) red[threadIdx.x >> 6][jj] = acc;
         __syncthreads();
+        if (r == 0) red[0][jj] = (red[0][jj] + red[1][jj]) + (red[2][jj] + red[3][jj]);
+        __syncthreads();
+    } else {
+        red[r][jj] = acc;
+        __syncthreads();
+        // tree over the PT sub-sums: thread (r, jj) adds red[r + half]
+        for (int half = PT / 2; half >= 1; half >>= 1) {
+            if (r < half) red[r][jj] += red[r + half][jj];
+            __syncthreads();
+        }
     }
     store_entries<JT, CHECK>(src, red[0], blockIdx.x * JT, ws, parts, J, dw);
 }
@@ -252,11 +261,21 @@ __global__ __launch_bounds__(256) void k_reduce_partials4(const float *__restric
             acc = add(acc, add(add(add(v[0], v[1]), add(v[2], v[3])), add(add(v[4], v[5]), add(v[6], v[7]))));
         }
     }
-    red[r][jj] = acc;
-    __syncthreads();
-    for (int half = PT / 2; half >= 1; half >>= 1) {
-        if (r < half) red[r][jj] = add(red[r][jj], red[r + half][jj]);
+    if constexpr (sizeof(S) == 8) {
+#pragma unroll
+        for (int off = 32; off >= JL; off >>= 1)
+            acc = add(acc, Sum4<S>{__shfl_xor(acc.x, off, 64), __shfl_xor(acc.y, off, 64), __shfl_xor(acc.z, off, 64), __shfl_xor(acc.w, off, 64)});
+        if ((threadIdx.x & 63) < JL) red[threadIdx.x >> 6][jj] = acc;
         __syncthreads();
+        if (r == 0) red[0][jj] = add(add(red[0][jj], red[1][jj]), add(red[2][jj], red[3][jj]));
+        __syncthreads();
+    } else {
+        red[r][jj] = acc;
+        __syncthreads();
+        for (int half = PT / 2; half >= 1; half >>= 1) {
+            if (r < half) red[r][jj] = add(red[r][jj], red[r + half][jj]);
+            __syncthreads();
+        }
     }
     if constexpr (CHECK) store_entries<JT, true>(src, &red[0][0].x, blockIdx.x * JT, ws, parts, J, dw);
     else if (r == 0 && j < J) *reinterpret_cast<float4 *>(dw + j) = make_float4(red[0][jj].x, red[0][jj].y, red[0][jj].z, red[0][jj].w);
