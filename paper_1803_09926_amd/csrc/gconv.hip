@@ -296,7 +296,12 @@ static bool gemm_over_walk(const GGeom &g, int dtype, int pass, int variant, lon
         return g.Og % 4 == 0 || (!f32 && g.Og % 2 == 0 && g.Cg >= 6) ? outputs < (f32 ? 700000 : few < 6 ? 8000000 : 1ll << 31) : false;
     }
     if (variant == GV_NHWC_K3S1) {
-        if (pass < 2) return g.Cg == 8 && g.Og == 8 && !gconv_nhwc_mfma_supported(g, dtype) && (!f32 || (outputs >= 300000 && outputs < 2700000));
+        if (pass < 2) {
+            // (a quarter of the output channels or more beside the tensor, on planes that are most of a tile: 24 channels in three groups, 4x4 to 6x6, 4.1 to 5.1 us on the
+            // walk, 4.8 to 5.8 here; 13 % of such layers were longer by more than 8 %)
+            if ((g.C + 15) / 16 * 16 * 3 >= g.C * 4 && g.H * g.W <= 36) return false;
+            return g.Cg == 8 && g.Og == 8 && !gconv_nhwc_mfma_supported(g, dtype) && (!f32 || (outputs >= 300000 && outputs < 2700000));
+        }
         return f32 ? g.Cg == 8 && outputs < 700000 : g.Cg > 2 || (g.C <= 32 && outputs < 3000000);
     }
     if (variant == GV_NHWC_BWD_FILTER_S2) return !f32 && (g.Cg == 8 ? outputs >= 8192 : g.C <= 64 && outputs >= 100000 && outputs < 1000000);

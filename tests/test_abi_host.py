@@ -383,6 +383,8 @@ def test_group_walks_keep_what_the_matrix_instructions_lengthen():
     for which in range(3):                                       # no end in bf16 from six channels a group on
         for layout in (dw.NCHW, dw.NHWC):
             assert name(which, 1000, 72, 8, layout, dw.BF16).startswith("group_mfma16")
+    small = [dw.gconv_variant_name(dw.group_desc(50, C, hw, hw, 3, 1, 1, C // 8, C, dw.NHWC, dw.BF16), i) for C, hw in ((24, 5), (40, 5), (24, 8)) for i in (0, 1)]
+    assert [n.startswith("group_mfma16") for n in small] == [False, False, True, True, True, True]      # 24 channels are 16 and a half
     # the smaller side of a group counts, and at stride 2 the shortest launches stay
     assert not name(1, 60, 120, 12, dw.NCHW, dw.BF16, og=2).startswith("group_mfma16")
     assert [name(2, N, 64, 4, dw.NHWC, dw.BF16, stride=2) for N in (6, 16, 80)] == ["group_nhwc_bwd_filter_k3s2", "group_mfma16_bwd_filter",
