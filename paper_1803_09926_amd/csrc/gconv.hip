@@ -250,15 +250,16 @@ static double generic_us(const GGeom &g, int layout, int pass)
 }
 
 // Laying out the filter and staging a tile are a fixed 5 to 12 us, and a filter that takes the LDS leaves small tiles: few products per output
-// and few outputs, or few channels a group with a large filter, are shorter one output per thread.  Of 17 000 random layers, 0.04 % of the forward passes and
-// 0.1 % of the input gradients that the estimates send here are longer by more than 8 % than one output per thread, and 13 and 22 % of the 1050 and 540 that they leave
-// there would be shorter here by as much (0.9 of the estimate, without the us by which the shortest generic ones are below theirs: 1.1 and 0.1 %).  The filter gradient, whose
+// and few outputs, or few channels a group with a large filter, are shorter one output per thread.  Their estimate is a fifth above the measured time below 10 us
+// and a tenth to a third below it from 40 us on, hence the line: over 24 000 random layers 0.2 % of those that go here are longer by more than 8 % than one output per thread, 6 % (forward pass) and
+// 17 % (input gradient) of the 900 and 450 that stay would be shorter here by as much, and the time is 1.002 of the shorter of the two throughout (0.95 of the estimate less 1 us:
+// 0.06, 13 and 28 % and 1.004, up to 1.67 times as long at two channels a group).  The filter gradient, whose
 // time here hardly depends on the layer as long as it is short: 1 % either way.
 static bool gemm_over_generic(const GGeom &g, int layout, int dtype, int pass, GemmPlan *pl)
 {
     const double generic = generic_us(g, layout, pass);
     if (pass == 2) return generic > (g.K == 1 ? 10.5 : g.K == 3 ? 12.5 : 16.0) && gconv_gemm_plan(g, layout, dtype, pass, pl);
-    return gconv_gemm_plan(g, layout, dtype, pass, pl) && gconv_gemm_us(*pl, layout, dtype) < 0.95 * generic - (pass == 0 ? 1.0 : 0.7);
+    return gconv_gemm_plan(g, layout, dtype, pass, pl) && gconv_gemm_us(*pl, layout, dtype) < 1.3 * generic - 3.2;
 }
 
 // In place of the NCHW row walk: in fp32 not for the filter gradient of 16 channels a group on many pixels (1.03 times as long at the median of

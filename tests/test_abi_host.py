@@ -405,9 +405,12 @@ def test_group_shapes_that_are_shorter_one_output_per_thread():
     assert names(226, 2, 80, 80, 5, 1, 2, 1, 2)[0] == "group_generic"
     # (forward, whose 147 products are most of the work, 26.7 us one output per thread and 14.2 with the filter in vectors; input gradient 15.4 and 23.7)
     assert names(90, 90, 7, 7, 7, 1, 0, 30, 90, layout=dw.NHWC, dtype=dw.BF16)[:2] == [gemm[0], "group_generic"]
-    # both sides of the line by the estimates, measured: us here / one output per thread 15.9 / 33.3, 18.3 / 33.8; 5.4 / 4.8, 6.7 / 5.9
+    # both sides of the line by the estimates, measured: us here / one output per thread 15.9 / 33.3, 18.3 / 33.8; 5.4 / 4.8, 5.3 / 4.7
     assert names(5, 126, 59, 72, 5, 2, 2, 63, 126)[0] == names(14, 14, 102, 141, 5, 2, 2, 7, 14)[0] == gemm[0]
-    assert names(45, 4, 13, 13, 3, 1, 1, 2, 4, dtype=dw.BF16)[0] == names(2, 204, 6, 5, 3, 2, 1, 68, 204, dtype=dw.BF16)[0] == "group_generic"
+    # (57 / 95, 53 / 87, input gradient 12 / 20, 14 / 23)
+    assert names(149, 18, 35, 32, 5, 1, 1, 9, 18, layout=dw.NHWC)[0] == names(19, 8, 139, 139, 5, 1, 1, 4, 8, layout=dw.NHWC)[0] == gemm[0]
+    assert names(100, 4, 26, 26, 5, 2, 1, 2, 4, layout=dw.NHWC)[1] == names(22, 4, 115, 115, 3, 2, 1, 2, 4, layout=dw.NHWC)[1] == gemm[1]
+    assert names(45, 4, 13, 13, 3, 1, 1, 2, 4, dtype=dw.BF16)[0] == names(1, 178, 9, 9, 3, 2, 0, 89, 178, dtype=dw.BF16)[0] == "group_generic"
     # tiles of up to 160 KiB: 146 us where the row walk takes 251 (with tiles of up to 64 KiB 859); five groups of 96 channels on 69 012 pixels, whose
     # filter leaves tiles of few positions, 2330 where it takes 1080
     assert names(148, 128, 21, 20, 3, 1, 1, 2, 128)[:2] == gemm[:2]
