@@ -250,10 +250,11 @@ static double generic_us(const GGeom &g, int layout, int pass)
 }
 
 // Laying out the filter and staging a tile are a fixed 5 to 12 us, and a filter that takes the LDS leaves small tiles: few products per output
-// and few outputs, or few channels a group with a large filter, are shorter one output per thread.  Their estimate is a fifth above the measured time below 10 us
-// and a tenth to a third below it from 40 us on, hence the line: over 24 000 random layers 0.2 % of those that go here are longer by more than 8 % than one output per thread, 6 % (forward pass) and
-// 17 % (input gradient) of the 900 and 450 that stay would be shorter here by as much, and the time is 1.002 of the shorter of the two throughout (0.95 of the estimate less 1 us:
-// 0.06, 13 and 28 % and 1.004, up to 1.67 times as long at two channels a group).  The filter gradient, whose
+// and few outputs, or few channels a group with a large filter, are shorter one output per thread.  Where the two are close, the estimate of the latter is a fifth above
+// the measured time below 10 us and a sixth to a quarter below it from 20 us on (medians), hence the line.  Over 24 000 random layers 0.25 % of the forward passes and 0.16 % of the
+// input gradients that go here are longer by more than 8 % than one output per thread, 6 and 17 % of the 900 and 450 that stay would be shorter here by as much, and
+// the time is 1.002 of the shorter of the two throughout.  (0.95 of the estimate less 1 and 0.7 us: 0.05 and 0.08, 13 and 22 %, 1.003, and
+// 149x18x35x32 in nine groups, 5x5, fp32 NHWC, 95 us in place of 57.)  The filter gradient, whose
 // time here hardly depends on the layer as long as it is short: 1 % either way.
 static bool gemm_over_generic(const GGeom &g, int layout, int dtype, int pass, GemmPlan *pl)
 {
