@@ -290,11 +290,14 @@ static bool gemm_over_walk(const GGeom &g, int dtype, int pass, int variant, lon
     const bool f32 = dtype == DT_F32;
     if (tune_active()) return false;                             // forced tilings are those of the walks
     if (variant == GV_NCHW_K3S1) {
-        // (16 output channels at a time, whether there are or not: 48x46x64 of four channels in two groups, fp32 10.5 on the walk, 15.9 here)
+        // (16 output channels at a time, whether there are or not: 48x46x64 of four channels in two groups, fp32 10.5 on the walk, 15.9 here; 48x48x4 of two,
+        // bf16 batch 202, input gradient 10.9 and 16.5.  In bf16, of 30 000 layers below the lines on outputs: two channels a group with 3.5 M padded outputs and more
+        // 1.2 and 1.3 times as long here, forward and input gradient; three from 6 M on 0.96 and 1.0, up to 2.5 and 2.7; four from 8 M on 1.01 and 1.07)
         const long long padded = outputs / (pass == 1 ? g.C : g.O) * (((pass == 1 ? g.C : g.O) + 15) / 16 * 16);
         const int few = g.Cg < g.Og ? g.Cg : g.Og;
         const bool whole = g.Cg % 4 == 0 && g.Og % 4 == 0;       // the walk takes four output channels at a time
-        if (pass < 2) return f32 ? padded < (few == 2 ? 500000 : whole ? 2000000 : 1000000) : outputs < (few == 2 ? 2000000 : few < 6 ? 8000000 : 1ll << 31);
+        if (pass < 2 && f32) return padded < (few == 2 ? 500000 : whole ? 2000000 : 1000000);
+        if (pass < 2) return few == 2 ? outputs < 2000000 && padded < 3500000 : few < 6 ? padded < (few == 3 ? 6000000 : 8000000) : outputs < 1ll << 31;
         return g.Og % 4 == 0 || (!f32 && g.Og % 2 == 0 && g.Cg >= 6) ? outputs < (f32 ? 700000 : few < 6 ? 8000000 : 1ll << 31) : false;
     }
     if (variant == GV_NHWC_K3S1) {

@@ -385,6 +385,9 @@ def test_group_walks_keep_what_the_matrix_instructions_lengthen():
             assert name(which, 1000, 72, 8, layout, dw.BF16).startswith("group_mfma16")
     small = [dw.gconv_variant_name(dw.group_desc(50, C, hw, hw, 3, 1, 1, C // 8, C, dw.NHWC, dw.BF16), i) for C, hw in ((24, 5), (40, 5), (24, 8)) for i in (0, 1)]
     assert [n.startswith("group_mfma16") for n in small] == [False, False, True, True, True, True]      # 24 channels are 16 and a half
+    # 16 output channels at a time whether there are or not: the lines count those
+    few = [dw.group_desc(202, 4, 48, 48, 3, 1, 1, 2, 4, dw.NCHW, dt) for dt in (dw.BF16, dw.F32)] + [dw.group_desc(35, 21, 84, 84, 3, 1, 1, 7, 21, dw.NCHW, dw.BF16)]
+    assert [dw.gconv_variant_name(d, i) for d in few for i in (0, 1)] == ["group_nchw_rowwalk_k3s1", "group_nchw_rowwalk_k3s1_flip"] * 3
     # the smaller side of a group counts, and at stride 2 the shortest launches stay
     assert not name(1, 60, 120, 12, dw.NCHW, dw.BF16, og=2).startswith("group_mfma16")
     assert [name(2, N, 64, 4, dw.NHWC, dw.BF16, stride=2) for N in (6, 16, 80)] == ["group_nhwc_bwd_filter_k3s2", "group_mfma16_bwd_filter",
