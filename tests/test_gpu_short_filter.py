@@ -13,6 +13,7 @@ from paper_1803_09926_amd.workloads import Layer
 
 import gpu_util as gu
 import test_gpu_flat
+import test_gpu_flat_pairs
 import test_gpu_gconv
 import test_gpu_nhwc_any
 import test_gpu_parity
@@ -120,6 +121,13 @@ def test_chosen_for_short_launches_alone(gpu_lib):
 @pytest.mark.parametrize("N,layer", test_gpu_flat.CASES, ids=[l.name for _, l in test_gpu_flat.CASES])
 def test_any_width_kernels(gpu_lib, no_short, N, layer, dtype):
     test_gpu_flat.test_any_width_kernels_match_oracle(gpu_lib, N, layer, dtype)
+
+
+@pytest.mark.parametrize("case", test_gpu_flat_pairs.CASES, ids=[c[1].name for c in test_gpu_flat_pairs.CASES])
+def test_column_pairs(gpu_lib, no_short, case):
+    N, layer = case
+    assert dw.variant_name(gu.desc_for(layer, N, wl.NCHW, wl.BF16), 2).startswith("nchw_flat_bwd_filter")
+    test_gpu_flat_pairs.test_column_pairs(case)
 
 
 @DTYPE
