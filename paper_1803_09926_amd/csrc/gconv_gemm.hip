@@ -176,7 +176,8 @@ __device__ __forceinline__ bool stage_pixels(const T *__restrict__ in, T *lx, in
 // The same where FAST holds, in two steps: load() sends out the loads of BT items of a lane, commit() writes them to LDS, so that the
 // next tile is on its way while this one is computed.
 // FAST: 1, channels of whole vectors (NHWC), tiles of whole rows (NCHW); 2, ragged channels, or tiles narrower than the rows.
-template <typename T, bool NHWC, int FAST, int BT> struct Stager;
+// LATE: what the loads at a tensor's end need is done in commit() (not in the filter gradient: its registers are at the limit, 125 -> 131 in fp32 NCHW).
+template <typename T, bool NHWC, int FAST, int BT, bool LATE> struct Stager;
 
 // The elements of 16 (or eight) bytes from element n on.
 template <int VE, typename Q> __device__ __forceinline__ Q later(Q q, int n)
@@ -201,9 +202,10 @@ template <int VE, typename Q> __device__ __forceinline__ Q later(Q q, int n)
     return q;
 }
 
-template <typename T, int FAST, int BT> struct Stager<T, true, FAST, BT> {
+template <typename T, int FAST, int BT, bool LATE> struct Stager<T, true, FAST, BT, LATE> {
     static constexpr int VE = 16 / (int)sizeof(T);
     u4raw_t q[BT];
+    uint32_t late;           // per item, how far behind the start of its load it begins: seen to in commit(), where the load has been waited for
     int rsub, csub, v;
     __device__ __forceinline__ Stager(const StageGeom &sg)
     {
@@ -222,12 +224,15 @@ template <typename T, int FAST, int BT> struct Stager<T, true, FAST, BT> {
     }
     // nimg images from element `first` of `in` on, a tensor of `total` elements (VE and more, below 2^31): rows from h0, columns from w0, channels from ca.
     // Channels that are no whole number of vectors: unaligned loads, whose last elements are the next pixel's first (they meet zeros of
-    // the filter), at the tensor's end those before it.
+    // the filter), at the tensor's end those before it (`late`; shifted here, every load of a launch's last images, in a batch of one every load, was
+    // waited for before the next was sent out: 926x102x27 in two groups to 5556 channels, fp32, input gradient 145 -> 116 us, NCHW 864x35x107 in nine
+    // forward 192 -> 143, random layers of one image 0.98 at the mean, the shortest 0.72, the longest 1.05).
     __device__ __forceinline__ void load(const StageGeom &sg, const T *__restrict__ in, unsigned first, unsigned total, int nimg, int C, int H, int W,
                                          int h0, int w0, int ca, int it0)
     {
         const BufView view(in + first, (uint32_t)(nimg * C) * (uint32_t)(H * W) * (uint32_t)sizeof(T));
         [[maybe_unused]] const bool past = first + (unsigned)(nimg * C) * (unsigned)(H * W) + VE > total;
+        late = 0u;
 #pragma unroll
         for (int b = 0; b < BT; ++b) {
             if (it0 + b >= sg.iters) break;
@@ -244,13 +249,20 @@ template <typename T, int FAST, int BT> struct Stager<T, true, FAST, BT> {
                 if (ok) {
                     const unsigned p = first + e, at = min(p, total - VE);
                     __builtin_memcpy(&q[b], in + at, 16);
-                    if (past) q[b] = later<VE>(q[b], (int)(p - at));
+                    if (past) {
+                        if constexpr (LATE) late |= (p - at) << 3 * b;
+                        else q[b] = later<VE>(q[b], (int)(p - at));
+                    }
                 }
             }
         }
     }
-    __device__ __forceinline__ void commit(const StageGeom &sg, T *lx, int, int, int it0, bool check, Finite<T> &seen) const
+    __device__ __forceinline__ void commit(const StageGeom &sg, T *lx, int, int, int it0, bool check, Finite<T> &seen)
     {
+        if (FAST == 2 && LATE && late != 0u) {
+#pragma unroll
+            for (int b = 0; b < BT; ++b) q[b] = later<VE>(q[b], (int)(late >> 3 * b & 7u));
+        }
 #pragma unroll
         for (int b = 0; b < BT; ++b) {
             if (it0 + b >= sg.iters) break;
@@ -267,10 +279,11 @@ template <typename T, int FAST, int BT> struct Stager<T, true, FAST, BT> {
 
 // Four channels of four consecutive columns of a row, transposed in registers.  Where a tile holds whole rows, the columns beside the row are
 // zero from the start and stay so; where it is narrower, its runs of four start at the multiple of four before it and bring their own zeros.
-template <typename T, int FAST, int BT> struct Stager<T, false, FAST, BT> {
+template <typename T, int FAST, int BT, bool LATE> struct Stager<T, false, FAST, BT, LATE> {
     static constexpr int NW = (int)sizeof(T);      // 32-bit words of four columns
     typedef uint32_t word_t __attribute__((ext_vector_type(NW)));
     word_t e[BT][4];
+    uint32_t late;           // per item and channel, as above
     int rsub, csub;
     __device__ __forceinline__ Stager(const StageGeom &sg)
     {
@@ -292,6 +305,7 @@ template <typename T, int FAST, int BT> struct Stager<T, false, FAST, BT> {
     {
         const unsigned plane = (unsigned)(H * W);
         const bool past = W % 4 && runs_past(first + (unsigned)(nimg * C) * plane, total);        // of this tile or, up to two elements, the ones behind
+        late = 0u;
 #pragma unroll
         for (int b = 0; b < BT; ++b) {
             if (it0 + b >= sg.iters) break;
@@ -314,14 +328,23 @@ template <typename T, int FAST, int BT> struct Stager<T, false, FAST, BT> {
                     // any alignment; a run that passes the row's end reads the elements behind it, at the tensor's end those before it
                     const unsigned at = run_start(p0, total);
                     __builtin_memcpy(&e[b][k], in + at, 4 * sizeof(T));
-                    if (past) e[b][k] = later<4>(e[b][k], (int)(p0 - at));
+                    if (past) {
+                        if constexpr (LATE) late |= (p0 - at) << (b * 4 + k) * 2;
+                        else e[b][k] = later<4>(e[b][k], (int)(p0 - at));
+                    }
                 }
             }
         }
     }
     // w0: the tile's first column
-    __device__ __forceinline__ void commit(const StageGeom &sg, T *lx, int W, int w0, int it0, bool check, Finite<T> &seen) const
+    __device__ __forceinline__ void commit(const StageGeom &sg, T *lx, int W, int w0, int it0, bool check, Finite<T> &seen)
     {
+        if (LATE && late != 0u) {
+#pragma unroll
+            for (int b = 0; b < BT; ++b)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) e[b][k] = later<4>(e[b][k], (int)(late >> (b * 4 + k) * 2 & 3u));
+        }
         const bool whole = FAST == 1 && W % 4 == 0 && w0 <= 0 && W - w0 <= sg.LW;                // every column of a run is one of the tile
 #pragma unroll
         for (int b = 0; b < BT; ++b) {
@@ -571,7 +594,7 @@ __global__ __launch_bounds__(256, 4) void k_gconv_gemm(GemmGeom g, StageGeom sg,
         n0 = tn * g.TN; a0 = g.a0 + (row - tn * g.ta) * g.TA; b0 = g.b0 + (tile - row * g.tb) * g.TB;
     };
     constexpr int BT = NHWC || sizeof(T) == 2 ? 4 : 2;       // items of a lane in flight
-    [[maybe_unused]] Stager<T, NHWC, FAST, BT> stager(sg);
+    [[maybe_unused]] Stager<T, NHWC, FAST, BT, true> stager(sg);
     auto load_tile = [&](int tile, int it0) {
         if constexpr (FAST) {
             int n0, a0, b0;
@@ -864,7 +887,7 @@ __global__ __launch_bounds__(256, K > 3 ? 2 : sizeof(T) == 4 ? 3 : 4) void k_gco
         n0 = tn * g.TN; a0 = (row - tn * g.ta) * g.TA; b0 = (tile - row * g.tb) * g.TB;
     };
     constexpr int BT = NHWC ? 4 : sizeof(T) == 2 && K <= 3 ? 2 : 1;        // items of a lane in flight
-    [[maybe_unused]] Stager<T, NHWC, FAST, BT> stx(sx), sty(sy);
+    [[maybe_unused]] Stager<T, NHWC, FAST, BT, false> stx(sx), sty(sy);
     auto load_x = [&](int n0, int a0, int b0, int it0) {
         const int nimg = min(g.TN, g.N - n0), h0 = g.IS * a0 - g.ip, w0 = g.IS * b0 - g.ip;
         stx.load(sx, x, (unsigned)n0 * imx, (unsigned)g.N * imx, nimg, g.CI, g.Hi, g.Wi, h0, w0, cxa, it0);

@@ -20,6 +20,7 @@ RAGGED = [
     ("c15_o20", 3, 15, 20, 5, 18, 16, 3, 1, 1),                    # odd channels: loads at odd elements
     ("c9_o33", 2, 9, 33, 1, 15, 19, 5, 2, 2),                      # outputs end inside a quad
     ("c34_o6", 3, 34, 6, 2, 14, 18, 3, 1, 1),                      # more input channels than a chunk
+    ("one_image", 1, 11, 15, 1, 15, 17, 3, 1, 1),
     ("k1", 3, 18, 26, 2, 21, 17, 1, 1, 0),
     ("pixels_of_two", 2500, 2, 2, 1, 1, 1, 5, 1, 2),               # a vector spans pixels and images
 ]
