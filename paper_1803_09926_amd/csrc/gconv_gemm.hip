@@ -1059,12 +1059,30 @@ int resident_blocks(size_t lds, int most)
     return 256 * (int)(n < 1 ? 1 : n > (size_t)most ? most : n);
 }
 
+// 16-position tiles that a wavefront computes at a time (P of k_gconv_gemm), of a tile of npos positions and NS output blocks.  Four share a read of the
+// filter, but only from 256 positions and output blocks on is there work for all four wavefronts of a block that way: at 128 half of them are idle.
+// So, the shortest longest wavefront: cycles of its matrix instructions, of the LDS reads of all four, and of the loop.  (us, four at a time from 80
+// on -> this: 30x492x19x19 in 41 groups, 7x7, fp32 NCHW input gradient 221 -> 138; 26x832x14x14 in 13 groups, fp32 NCHW forward 137 -> 87; random
+// layers 0.94 of the time at the mean in fp32, 0.98 in bf16.  One or four at a time, without two, 0.96 and 1.02.)
+int tiles_at_once(int NS, int npos, int dtype, int *longest = nullptr)
+{
+    const int tiles16 = cdivg(npos, 16), mfma = dtype == DT_F32 ? 128 : 16, read = dtype == DT_F32 ? 32 : 16, loop = 40;
+    int best = 1, least = 1 << 30;
+    for (int P = 1; P <= 4; P *= 2) {
+        const int cycles = cdivg(NS * cdivg(tiles16, P), 4) * (P * mfma + (1 + P) * read + loop);
+        if (cycles < least) { least = cycles; best = P; }
+    }
+    if (longest) *longest = least;
+    return best;
+}
+
 // The widest tile (of positions from `from` down to `to`) that fits, as tile(positions) sets it up; up to half of it less where that lets `most`
 // blocks onto a compute unit and it does not.  Returns the positions, 0 if nothing fits.  (14x14 16 channels a group 10.1 us with 256 positions,
 // 13.0 with 128; 28x28 32 channels a group, bf16 NHWC batch 64: 55 us with 256 positions and three blocks, 47 with 128 and four.)
 // Of such tiles the one whose `launched` blocks go through the chip in the shortest rounds, each its positions and 32 of fixed work: 51x34x106 in 53 groups,
-// fp32 NCHW batch 45, 204 positions (40 us, 49 with 102), 61x59x84 in 42, batch 27, 122 (44 us, 56 with 183).
-template <typename F, typename B> int widest_tile(const GemmGeom &g, F tile, B launched, int from, int to, int most, size_t limit, const size_t *lds)
+// fp32 NCHW batch 45, 204 positions (40 us, 49 with 102), 61x59x84 in 42, batch 27, 122 (44 us, 56 with 183).  `positions`: the tile's, or what its time is that of.
+template <typename F, typename B, typename P>
+int widest_tile(const GemmGeom &g, F tile, B launched, P positions, int from, int to, int most, size_t limit, const size_t *lds)
 {
     for (int want = from; want >= to; want /= 2) {
         tile(want);
@@ -1074,7 +1092,7 @@ template <typename F, typename B> int widest_tile(const GemmGeom &g, F tile, B l
             long long least = 0;
             for (int less = want - want / 8; less >= want / 2; less -= want / 8) {
                 tile(less);
-                const long long time = (launched() + 256 * most - 1) / (256 * most) * (g.TN * g.TA * g.TB + 32);
+                const long long time = (launched() + 256 * most - 1) / (256 * most) * (positions() + 32);
                 if (resident_blocks(*lds, most) == 256 * most && (!best || time <= least)) { best = less; least = time; }
             }
             tile(best ? best : want);
@@ -1083,22 +1101,6 @@ template <typename F, typename B> int widest_tile(const GemmGeom &g, F tile, B l
         return want;
     }
     return 0;
-}
-
-// 16-position tiles that a wavefront computes at a time (P of k_gconv_gemm), of a tile of npos positions and NS output blocks.  Four share a read of the
-// filter, but only from 256 positions and output blocks on is there work for all four wavefronts of a block that way: at 128 half of them are idle.
-// So, the shortest longest wavefront: cycles of its matrix instructions, of the LDS reads of all four, and of the loop.  (us, four at a time from 80
-// on -> this: 30x492x19x19 in 41 groups, 7x7, fp32 NCHW input gradient 221 -> 138; 26x832x14x14 in 13 groups, fp32 NCHW forward 137 -> 87; random
-// layers 0.94 of the time at the mean in fp32, 0.98 in bf16.  One or four at a time, without two, 0.96 and 1.02.)
-int tiles_at_once(int NS, int npos, int dtype)
-{
-    const int tiles16 = cdivg(npos, 16), mfma = dtype == DT_F32 ? 128 : 16, read = dtype == DT_F32 ? 32 : 16, loop = 40;
-    int best = 1, least = 1 << 30;
-    for (int P = 1; P <= 4; P *= 2) {
-        const int cycles = cdivg(NS * cdivg(tiles16, P), 4) * (P * mfma + (1 + P) * read + loop);
-        if (cycles < least) { least = cycles; best = P; }
-    }
-    return best;
 }
 
 // positions of a tile: whole rows where they fit, several images of a small map; a row of a multiple of `quad` positions, so that
@@ -1186,8 +1188,17 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
                           ((size_t)g.TN * g.LH * g.LW * g.pitch * esz + 15) / 16 * 16;
             };
             auto blocks = [&]() { return (long long)g.tn * g.ta * g.tb * cdivg(blocks16, ns); };
-            int want = widest_tile(g, tile, blocks, 256, 16, 4, LDS_OF_TWO, &pl->lds);
-            if (!want && ns == 1) want = widest_tile(g, tile, blocks, 256, 16, 4, LDS_OF_ONE, &pl->lds);
+            // (two output blocks: a wavefront's work comes in steps, and 144 to 224 positions take as long as 256.  By the positions alone 28x28x512 in 16
+            // groups, bf16 NHWC batch 64, had 196 and took 51 us, with 112 41.5; 44x44x32 in one, batch 356, 50 -> 42, input gradient 58 -> 47)
+            auto positions = [&]() {
+                const int npos = g.TN * g.TA * g.TB;
+                int steps, full;
+                if (ns == 1) return npos;
+                tiles_at_once(ns, npos, dtype, &steps); tiles_at_once(ns, 256, dtype, &full);
+                return 256 * steps / full;
+            };
+            int want = widest_tile(g, tile, blocks, positions, 256, 16, 4, LDS_OF_TWO, &pl->lds);
+            if (!want && ns == 1) want = widest_tile(g, tile, blocks, positions, 256, 16, 4, LDS_OF_ONE, &pl->lds);
             if (!want && ns == 1) return false;
             if (!want) continue;
             auto few = [&]() { return blocks() < FEW; };
@@ -1250,7 +1261,8 @@ bool gemm_plan_as(const GGeom &q, int layout, int dtype, int pass, bool pairs, G
             // the time at the mean, 0.4 % longer by more than 8 %.  192 blocks: 0.95 and 2.2 %.)
             constexpr int FEW = 128;
             auto launched = [&]() { return (long long)g.tn * g.ta * g.tb * g.nchb; };
-            int want = widest_tile(g, tile, launched, 256, npair > 1 ? 64 : 16, blocks, LDS_OF_TWO, &pl->lds);
+            auto positions = [&]() { return g.TN * g.TA * g.TB; };
+            int want = widest_tile(g, tile, launched, positions, 256, npair > 1 ? 64 : 16, blocks, LDS_OF_TWO, &pl->lds);
             auto few = [&]() { return launched() < FEW; };
             for (; want > 32 && few(); tile(want)) want /= 2;
             fits = want > 0 && (npair == 1 || !few());
