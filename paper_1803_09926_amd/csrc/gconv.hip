@@ -254,13 +254,16 @@ static double generic_us(const GGeom &g, int layout, int pass)
 // the measured time below 10 us and a sixth to a quarter below it from 20 us on (medians), hence the line.  Over 24 000 random layers 0.25 % of the forward passes and 0.16 % of the
 // input gradients that go here are longer by more than 8 % than one output per thread, 6 and 17 % of the 900 and 450 that stay would be shorter here by as much, and
 // the time is 1.002 of the shorter of the two throughout.  (0.95 of the estimate less 1 and 0.7 us: 0.05 and 0.08, 13 and 22 %, 1.003, and
-// 149x18x35x32 in nine groups, 5x5, fp32 NHWC, 95 us in place of 57.)  The filter gradient, whose
+// 149x18x35x32 in nine groups, 5x5, fp32 NHWC, 95 us in place of 57.)  Two kinds have a line of their own, over layers between it and the common one: NCHW input gradients of 2x2 filters and larger, of 4000
+// layers 608 + 88 (fp32, bf16) longer here by more than 8 % with 1.3, 7 + 0 with 1.25, and 61 that stay would be shorter here by as much; NCHW 7x7 forward in fp32, of 1600 570
+// with 1.3, 98 with 1.1, and 153 (48x103x103 in 16 groups, 30 us generic, 42 here).  The filter gradient, whose
 // time here hardly depends on the layer as long as it is short: 1 % either way.
 static bool gemm_over_generic(const GGeom &g, int layout, int dtype, int pass, GemmPlan *pl)
 {
     const double generic = generic_us(g, layout, pass);
     if (pass == 2) return generic > (g.K == 1 ? 10.5 : g.K == 3 ? 12.5 : 16.0) && gconv_gemm_plan(g, layout, dtype, pass, pl);
-    return gconv_gemm_plan(g, layout, dtype, pass, pl) && gconv_gemm_us(*pl, layout, dtype) < 1.3 * generic - 3.2;
+    const double line = layout == LAYOUT_NHWC ? 1.3 : pass == 1 && g.K > 1 ? 1.25 : g.K == 7 && pass == 0 && dtype == DT_F32 ? 1.1 : 1.3;
+    return gconv_gemm_plan(g, layout, dtype, pass, pl) && gconv_gemm_us(*pl, layout, dtype) < line * generic - 3.2;
 }
 
 // In place of the NCHW row walk: in fp32 not for the filter gradient of 16 channels a group on many pixels (1.03 times as long at the median of

@@ -414,6 +414,10 @@ def test_group_shapes_that_are_shorter_one_output_per_thread():
     assert names(149, 18, 35, 32, 5, 1, 1, 9, 18, layout=dw.NHWC)[0] == names(19, 8, 139, 139, 5, 1, 1, 4, 8, layout=dw.NHWC)[0] == gemm[0]
     assert names(100, 4, 26, 26, 5, 2, 1, 2, 4, layout=dw.NHWC)[1] == names(22, 4, 115, 115, 3, 2, 1, 2, 4, layout=dw.NHWC)[1] == gemm[1]
     assert names(45, 4, 13, 13, 3, 1, 1, 2, 4, dtype=dw.BF16)[0] == names(1, 178, 9, 9, 3, 2, 0, 89, 178, dtype=dw.BF16)[0] == "group_generic"
+    # the lines of NCHW 7x7 forward in fp32 and of NCHW input gradients (41.9 / 30.0, 43.4 / 32.5; 7.4 / 6.1, 7.9 / 6.8)
+    assert names(1, 48, 103, 103, 7, 1, 0, 16, 48)[0] == names(1, 171, 54, 54, 7, 1, 3, 57, 171)[0] == "group_generic"
+    assert names(1, 502, 7, 7, 3, 2, 1, 251, 502)[1] == names(1, 132, 31, 31, 3, 2, 1, 66, 132)[1] == "group_generic"
+    assert names(8, 48, 103, 103, 7, 1, 0, 8, 48)[0] == gemm[0] and names(20, 132, 31, 31, 3, 2, 1, 66, 132)[1] == gemm[1]
     # tiles of up to 160 KiB: 146 us where the row walk takes 251 (with tiles of up to 64 KiB 859); five groups of 96 channels on 69 012 pixels, whose
     # filter leaves tiles of few positions, 2330 where it takes 1080
     assert names(148, 128, 21, 20, 3, 1, 1, 2, 128)[:2] == gemm[:2]
