@@ -57,7 +57,8 @@ __global__ __launch_bounds__(256) void k_gconv_nchws_mfma_bwd_filter(GGeom g, co
     constexpr int XCH = 8 * L::XROWS * L::VPR / CPV, DCH = 8 * L::RS * L::VPR / CPV;     // chunks of a fill
     // NCHW strips in bf16: a pass takes whole planes (one or two), so that a lane's place is found once, a chunk is one LDS write and the
     // addresses are scalar: 128x128x56x56 in groups of 4 42.9 -> 39.8 us, of 8 48.6 -> 45.5, 64x112x112 in groups of 2, batch 256, 143.6 -> 141.0,
-    // batch 32 28.6 -> 27.5.  It leaves 32 to 60 lanes of a pass idle, and fp32, whose large launches wait for memory, is up to 3 % longer
+    // batch 32 28.6 -> 27.5, each launched alone again and again; behind a forward pass, whose outputs are still being written back, the large ones wait for
+    // memory: 108.8 -> 108.2 and 182.4 -> 184.9.  It leaves 32 to 60 lanes of a pass idle, and fp32, whose large launches wait for memory, is up to 3 % longer
     // (128x128x56x56 in groups of 8 112 -> 116).
     constexpr bool PLANES = L::STRIP && !NHWC && !F32;
     constexpr int XLP = XCH / 8, DLP = DCH / 8, XPP = 256 / XLP, DPP = 256 / DLP;        // chunks of a plane, planes of a pass
